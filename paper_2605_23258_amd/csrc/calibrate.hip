@@ -2,17 +2,13 @@
 // from m calibration tokens per KV head, through the normal equations
 //   (K^T K) W = K^T V.
 //
-//   gram_kernel  : grid (token chunks, kv heads).  The two d x d products contract over
-//                  tokens, so the operands are columns of the [token][dim] tiles: a workgroup
-//                  stages 32-token tiles of K and V in LDS with coalesced 16-byte loads and
-//                  its waves read them back down the columns (eight 2-byte reads per MFMA
-//                  operand register set).  Wave w owns the 32-row block w of both products
-//                  (d = 128; for d = 64 two waves take K^T K and two K^T V).  fp32 MFMA
-//                  accumulation inside a chunk; one fp32 partial pair per chunk.
-//   gram_valu_kernel : the same partials for fp32 inputs with plain FMAs (small problems).
-//   solve_kernel : one workgroup per head.  Sums the chunk partials in fp64, factors
-//                  K^T K = L L^T in LDS (fp64 Cholesky), and solves the d right-hand sides,
-//                  one thread per column of W.
+//   gram_kernel / gram_f32_kernel : grid (token chunks, kv heads).  The two d x d products on the matrix
+//                  cores, fp32 accumulation inside a chunk; one fp32 partial pair per chunk.
+//   gram_reduce_kernel : the chunks' partials summed in fp64, in chunk order.
+//   solve_kernel : grid (d / 16 column blocks, heads).  Blocked fp64 Cholesky of K^T K with the column
+//                  block of K^T V riding along, then the backward substitution; all on fp64 matrix
+//                  instructions out of LDS.
+// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 64 + 12 + 51 us (products, sums, solve).
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -21,8 +17,9 @@ namespace vec {
 namespace {
 
 constexpr int kCalThreads = 256;
-constexpr int kCalTile = 32;                 // tokens per staged tile
+constexpr int kCalTile = 128;                // chunks are multiples of the longest tile
 constexpr int kCalMaxChunks = 64;
+constexpr int kCalMinTokens = 256;
 
 struct CalParams {
   const void* k; const void* v;
@@ -30,37 +27,54 @@ struct CalParams {
   int m;                                    // calibration tokens per head
   int tokens_per_chunk, n_chunks;
   float* part;                              // [Hkv, n_chunks, 2, d, d] fp32: K^T K, then K^T V
-  double* c64;                              // [Hkv, d, d] fp64 scratch: the Cholesky factor during the solves
+  double* sums;                             // [Hkv, tiles, 16, 16] fp64: what solve_kernel loads, in its tile order
   void* W;                                  // [Hkv, d, d] out
-  int* status;                              // [Hkv]: 0 ok, 1 not positive definite
 };
 
-typedef __attribute__((ext_vector_type(8))) unsigned short cal_u16x8;
+// ---------------------------------------------------------------------------
+// bf16 inputs.  Both products contract over tokens, so an MFMA operand is a run of eight tokens of
+// one dim: the tiles are turned round on their way into LDS.  A thread takes an 8 x 8 block (eight
+// 16-byte loads, one per token), swaps it with one v_perm per output word and stores eight 16-byte
+// runs; every operand is then one 16-byte LDS read (reading a [token][dim] tile down its columns took
+// eight 2-byte reads per operand, and those reads bound the launch).  A row of LDS holds one dim's tokens
+// of the tile; the 16-byte slots of a row are permuted by the dim so that neither the stores (dims
+// eight apart) nor the operand reads (dims next to each other) meet in a bank.
+// Bound: HBM, every key and value once: 64 us (4.2 TB/s; 5.1 is a plain copy) at 65536 tokens x 8 heads, 74 us
+// with column reads of plain tiles.  Wave w owns the 32-row block w of both products
+// (d = 128; for d = 64 two waves take K^T K and two K^T V).
+// ---------------------------------------------------------------------------
+template <int D> struct GramTile {
+  static constexpr int kTokens = 64 * 128 / D;                    // one 8 x 8 block per thread and tile
+  static constexpr int kOctets = kTokens / 8;
+  static constexpr int kRowBytes = kTokens * 2;
+  static constexpr int kBytes = (D + (D == 128 ? 1 : 0)) * kRowBytes;
+  static __device__ __forceinline__ int at(int dim, int octet) {
+    return (dim + (D == 128 ? dim >> 6 : 0)) * kRowBytes + ((octet ^ (((dim >> 3) ^ dim) & 7)) * 16);
+  }
+};
 
 template <int D>
-__global__ __launch_bounds__(kCalThreads) void gram_kernel(CalParams p) {
+__global__ __launch_bounds__(kCalThreads, 2) void gram_kernel(CalParams p) {
   using T = bf16_t;
-  constexpr int kRowBytes = D * 2;
-  constexpr int kStride = kRowBytes + 16;
-  constexpr int kPieces = kRowBytes / 16;
-  constexpr int kLoads = kCalTile * kPieces / kCalThreads;       // 16-byte pieces per thread, tile and tensor
-  static_assert(kCalTile * kPieces % kCalThreads == 0 && kLoads >= 1, "tile shape");
+  using TL = GramTile<D>;
   constexpr int JB = D / 32;
-  constexpr int kTileBytes = kCalTile * kStride;
-  // wave -> (row block, which products): d = 128: row block = wave, both products;
-  // d = 64: waves 0,1 take K^T K, waves 2,3 take K^T V
+  constexpr int kBlocks = kCalThreads / 2;                        // 8 x 8 blocks of K, and of V, per tile
+  static_assert((D / 8) * TL::kOctets == kBlocks, "one block per thread");
   constexpr bool kBoth = (JB == 4);
-  __shared__ __align__(16) unsigned char lds[2][2][kTileBytes];   // [buffer][K, V]
+  extern __shared__ __align__(16) unsigned char gram_lds[];       // [buffer][K, V][kBytes]
 
   const int h = blockIdx.y, chunk = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, half = lane >> 5;
   const int ib = kBoth ? wave : (wave % JB);
   const bool do_g = kBoth || wave < JB, do_c = kBoth || wave >= JB;
-  const T* k_head = reinterpret_cast<const T*>(p.k) + (int64_t)h * p.k_sh;
-  const T* v_head = reinterpret_cast<const T*>(p.v) + (int64_t)h * p.v_sh;
+  // this thread's block of a tile: K or V, eight dims, eight tokens
+  const bool is_v = (int)threadIdx.x >= kBlocks;
+  const int bi = (int)threadIdx.x % kBlocks, dims0 = (bi % (D / 8)) * 8, octet = bi / (D / 8);
+  const T* src = (is_v ? reinterpret_cast<const T*>(p.v) + (int64_t)h * p.v_sh : reinterpret_cast<const T*>(p.k) + (int64_t)h * p.k_sh) + dims0;
+  const int64_t st = is_v ? p.v_st : p.k_st;
   const int c_begin = chunk * p.tokens_per_chunk;
   const int c_end = min(p.m, c_begin + p.tokens_per_chunk);
-  const int n_tiles = (c_end - c_begin + kCalTile - 1) / kCalTile;
+  const int n_tiles = (c_end - c_begin + TL::kTokens - 1) / TL::kTokens;
 
   f32x16 accg[JB], accc[JB];
 #pragma unroll
@@ -68,55 +82,53 @@ __global__ __launch_bounds__(kCalThreads) void gram_kernel(CalParams p) {
 #pragma unroll
     for (int x = 0; x < 16; ++x) { accg[jb][x] = 0.f; accc[jb][x] = 0.f; }
 
-  // rows past the chunk are staged as zeros: they add nothing to either product
-  auto fetch = [&](uint4* kr, uint4* vr, int tile) {
+  uint4 raw[8];
+  auto fetch = [&](int tile) {
+    const int t0 = c_begin + tile * TL::kTokens + octet * 8;
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) {
-      const int i = threadIdx.x + u * kCalThreads;
-      const int t = c_begin + tile * kCalTile + i / kPieces;
-      kr[u] = make_uint4(0, 0, 0, 0);
-      vr[u] = make_uint4(0, 0, 0, 0);
-      if (t < c_end) {
-        kr[u] = load_chunk(reinterpret_cast<const unsigned char*>(k_head + (int64_t)t * p.k_st) + (i % kPieces) * 16);
-        vr[u] = load_chunk(reinterpret_cast<const unsigned char*>(v_head + (int64_t)t * p.v_st) + (i % kPieces) * 16);
-      }
-    }
+    for (int u = 0; u < 8; ++u) raw[u] = load_chunk(src + (int64_t)min(t0 + u, p.m - 1) * st);
   };
-  auto stash = [&](const uint4* kr, const uint4* vr, int buf) {
+  // rows past the chunk are staged as zeros: they add nothing to either product
+  auto stash = [&](int tile, int buf) {
+    const int t0 = c_begin + tile * TL::kTokens + octet * 8;
+    if (t0 + 8 > c_end) {
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) {
-      const int i = threadIdx.x + u * kCalThreads;
-      const int off = (i / kPieces) * kStride + (i % kPieces) * 16;
-      *reinterpret_cast<uint4*>(lds[buf][0] + off) = kr[u];
-      *reinterpret_cast<uint4*>(lds[buf][1] + off) = vr[u];
+      for (int u = 0; u < 8; ++u)
+        if (t0 + u >= c_end) raw[u] = make_uint4(0, 0, 0, 0);
+    }
+    unsigned char* to = gram_lds + (buf * 2 + (is_v ? 1 : 0)) * TL::kBytes;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;   // dim j of two tokens, the earlier one in the low half
+      auto word = [&](int i) {
+        const uint32_t a[4] = {raw[2 * i].x, raw[2 * i].y, raw[2 * i].z, raw[2 * i].w};
+        const uint32_t b[4] = {raw[2 * i + 1].x, raw[2 * i + 1].y, raw[2 * i + 1].z, raw[2 * i + 1].w};
+        return __builtin_amdgcn_perm(b[j >> 1], a[j >> 1], sel);
+      };
+      *reinterpret_cast<uint4*>(to + TL::at(dims0 + j, octet)) = make_uint4(word(0), word(1), word(2), word(3));
     }
   };
   // operand of one 16-token step: lane (dim 32*blk + l31, half) holds tokens 16*ks + 8*half + e
-  auto column = [&](const unsigned char* tile, int blk, int ks) {
-    cal_u16x8 a;
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      a[e] = *reinterpret_cast<const unsigned short*>(tile + (16 * ks + 8 * half + e) * kStride + (blk * 32 + l31) * 2);
-    return __builtin_bit_cast(bf16x8, a);
+  auto operand = [&](const unsigned char* tile, int blk, int ks) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const chunk_t*>(tile + TL::at(blk * 32 + l31, 2 * ks + half)));
   };
 
-  uint4 kr[kLoads], vr[kLoads];
-  if (n_tiles > 0) { fetch(kr, vr, 0); stash(kr, vr, 0); }
+  if (n_tiles > 0) { fetch(0); stash(0, 0); }
   for (int tile = 0; tile < n_tiles; ++tile) {
     __syncthreads();                         // tile is staged; the other buffer is free
-    if (tile + 1 < n_tiles) fetch(kr, vr, tile + 1);
-    const unsigned char* kt = lds[tile & 1][0];
-    const unsigned char* vt = lds[tile & 1][1];
-#pragma unroll
-    for (int ks = 0; ks < kCalTile / 16; ++ks) {
-      const bf16x8 a = column(kt, ib, ks);
+    if (tile + 1 < n_tiles) fetch(tile + 1);
+    const unsigned char* kt = gram_lds + (tile & 1) * 2 * TL::kBytes;
+    const unsigned char* vt = kt + TL::kBytes;
+#pragma unroll (D == 128 ? 4 : 2)
+    for (int ks = 0; ks < TL::kTokens / 16; ++ks) {
+      const bf16x8 a = operand(kt, ib, ks);
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb) {
-        if (do_g) accg[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, column(kt, jb, ks), accg[jb], 0, 0, 0);
-        if (do_c) accc[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, column(vt, jb, ks), accc[jb], 0, 0, 0);
+        if (do_g) accg[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, operand(kt, jb, ks), accg[jb], 0, 0, 0);
+        if (do_c) accc[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, operand(vt, jb, ks), accc[jb], 0, 0, 0);
       }
     }
-    if (tile + 1 < n_tiles) stash(kr, vr, (tile + 1) & 1);
+    if (tile + 1 < n_tiles) stash(tile + 1, (tile + 1) & 1);
   }
   // accumulator register x of block jb: row 32*ib + acc_row(x, half), column 32*jb + l31
   float* out = p.part + ((size_t)h * p.n_chunks + chunk) * 2 * D * D;
@@ -125,179 +137,269 @@ __global__ __launch_bounds__(kCalThreads) void gram_kernel(CalParams p) {
 #pragma unroll
     for (int x = 0; x < 16; ++x) {
       const size_t at = (size_t)(32 * ib + acc_row(x, half)) * D + 32 * jb + l31;
-      if (do_g) out[at] = accg[jb][x];
+      if (do_g && jb <= ib) out[at] = accg[jb][x];                // K^T K is symmetric: the blocks up to the diagonal
       if (do_c) out[(size_t)D * D + at] = accc[jb][x];
     }
 }
 
-// fp32 inputs: plain FMAs; a thread owns one column and every other row of both products
+// fp32 inputs: the same products on the fp32 matrix instructions, whose operands (one element per
+// lane: 32 dims of one token, two tokens side by side) come straight out of [token][dim] tiles
 template <int D>
-__global__ __launch_bounds__(kCalThreads) void gram_valu_kernel(CalParams p) {
-  constexpr int kStride = D + 1;
-  constexpr int kPer = D * D / kCalThreads;          // outputs per thread and product
-  __shared__ float kt[kCalTile][kStride], vt[kCalTile][kStride];
+__global__ __launch_bounds__(kCalThreads) void gram_f32_kernel(CalParams p) {
+  constexpr int kTok = 16;                           // tokens per tile
+  constexpr int kStride = D + 32;                    // the two tokens of an operand read lie 32 banks apart
+  constexpr int JB = D / 32;
+  constexpr bool kBoth = (JB == 4);
+  __shared__ __align__(16) float kt[kTok * kStride], vt[kTok * kStride];
   const int h = blockIdx.y, chunk = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, half = lane >> 5;
+  const int ib = kBoth ? wave : (wave % JB);
+  const bool do_g = kBoth || wave < JB, do_c = kBoth || wave >= JB;
   const float* k_head = reinterpret_cast<const float*>(p.k) + (int64_t)h * p.k_sh;
   const float* v_head = reinterpret_cast<const float*>(p.v) + (int64_t)h * p.v_sh;
   const int c_begin = chunk * p.tokens_per_chunk;
   const int c_end = min(p.m, c_begin + p.tokens_per_chunk);
-  // outputs o = tid + u * kCalThreads of either product: row o / D, column o % D
-  float ag[kPer], ac[kPer];
+  f32x16 accg[JB], accc[JB];
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) { ag[u] = 0.f; ac[u] = 0.f; }
-  for (int t0 = c_begin; t0 < c_end; t0 += kCalTile) {
+  for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+    for (int x = 0; x < 16; ++x) { accg[jb][x] = 0.f; accc[jb][x] = 0.f; }
+  constexpr int kPieces = kTok * D / 4 / kCalThreads;
+  uint4 kr[kPieces], vr[kPieces];
+  auto fetch = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+      const int i = threadIdx.x + u * kCalThreads, t = min(t0 + i / (D / 4), p.m - 1), c = (i % (D / 4)) * 4;
+      kr[u] = load_chunk(k_head + (int64_t)t * p.k_st + c);
+      vr[u] = load_chunk(v_head + (int64_t)t * p.v_st + c);
+    }
+  };
+  if (c_begin < c_end) fetch(c_begin);
+  for (int t0 = c_begin; t0 < c_end; t0 += kTok) {
     __syncthreads();
-    for (int i = threadIdx.x; i < kCalTile * D; i += kCalThreads) {
-      const int r = i / D, c = i % D, t = t0 + r;
-      kt[r][c] = (t < c_end) ? k_head[(int64_t)t * p.k_st + c] : 0.f;
-      vt[r][c] = (t < c_end) ? v_head[(int64_t)t * p.v_st + c] : 0.f;
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+      const int i = threadIdx.x + u * kCalThreads, r = i / (D / 4), c = (i % (D / 4)) * 4;
+      const bool live = t0 + r < c_end;
+      *reinterpret_cast<uint4*>(kt + r * kStride + c) = live ? kr[u] : make_uint4(0, 0, 0, 0);
+      *reinterpret_cast<uint4*>(vt + r * kStride + c) = live ? vr[u] : make_uint4(0, 0, 0, 0);
     }
     __syncthreads();
+    if (t0 + kTok < c_end) fetch(t0 + kTok);
 #pragma unroll 4
-    for (int r = 0; r < kCalTile; ++r) {
+    for (int ks = 0; ks < kTok / 2; ++ks) {
+      const float* kp = kt + (2 * ks + half) * kStride + l31;
+      const float* vp = vt + (2 * ks + half) * kStride + l31;
+      const float a = kp[ib * 32];
 #pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        const int o = threadIdx.x + u * kCalThreads, i = o / D, j = o % D;
-        ag[u] = fmaf(kt[r][i], kt[r][j], ag[u]);
-        ac[u] = fmaf(kt[r][i], vt[r][j], ac[u]);
+      for (int jb = 0; jb < JB; ++jb) {
+        if (do_g) accg[jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, kp[jb * 32], accg[jb], 0, 0, 0);
+        if (do_c) accc[jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, vp[jb * 32], accc[jb], 0, 0, 0);
       }
     }
   }
   float* out = p.part + ((size_t)h * p.n_chunks + chunk) * 2 * D * D;
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int o = threadIdx.x + u * kCalThreads;
-    out[o] = ag[u];
-    out[(size_t)D * D + o] = ac[u];
+  for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      const size_t at = (size_t)(32 * ib + acc_row(x, half)) * D + 32 * jb + l31;
+      if (do_g && jb <= ib) out[at] = accg[jb][x];
+      if (do_c) out[(size_t)D * D + at] = accc[jb][x];
+    }
+}
+
+// Chunk partials -> fp64 sums in 16 x 16 tiles, the order solve_kernel keeps them in LDS: tile (i, j),
+// j <= i, of K^T K, then tile (r, j) of (K^T V)^T.  Grid (tiles, heads), one element per thread; a wave
+// reads four 64-byte runs per partial.  (One workgroup per head summing all of it took most of the solve's
+// 0.9 ms at 65536 tokens.)
+template <int D>
+__global__ __launch_bounds__(256) void gram_reduce_kernel(CalParams p) {
+  constexpr int NB = D / 16, kTri = NB * (NB + 1) / 2;
+  const int h = blockIdx.y, tile = blockIdx.x;
+  const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+  const float* part = p.part + (size_t)h * p.n_chunks * 2 * D * D;
+  size_t at, to;
+  if (tile < kTri) {
+    int i = 0;
+    while ((i + 1) * (i + 2) / 2 <= tile) ++i;
+    const int j = tile - i * (i + 1) / 2;
+    at = (size_t)(16 * i + r) * D + 16 * j + c;
+    to = (size_t)tile * 256 + r * 16 + c;
+  } else {
+    const int t = tile - kTri, cb = t / NB, j = t % NB;           // rows 16 j .. of K^T V, columns 16 cb ..: stored transposed
+    at = (size_t)D * D + (size_t)(16 * j + r) * D + 16 * cb + c;
+    to = (size_t)(kTri + cb * NB + j) * 256 + c * 16 + r;
+  }
+  double s = 0.0;
+  constexpr int U = 16;
+  for (int c0 = 0; c0 < p.n_chunks; c0 += U) {
+    float x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = part[(size_t)min(c0 + u, p.n_chunks - 1) * 2 * D * D + at];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c0 + u < p.n_chunks) s += (double)x[u];
+  }
+  p.sums[(size_t)h * (kTri + NB * NB) * 256 + to] = s;
+}
+
+// Cholesky of a 16 x 16 diagonal tile and the inverse of its factor, by one wave: every lane group of
+// 16 holds a row of the tile and a row of the inverse in the making per lane, and the pivot row's
+// elements are broadcast by readlane.  The tile is replaced by the inverse (zeros above its diagonal).
+// A pivot that is not positive marks the head.
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+constexpr int kLdt = 18;                      // doubles between rows of a tile: operand reads of 16 rows hit distinct banks
+constexpr int kTileDoubles = 16 * kLdt;
+
+__device__ __forceinline__ double readlane_f64(double x, int lane) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
+  return __builtin_bit_cast(double, (unsigned long long)lo | ((unsigned long long)hi << 32));
+}
+
+__device__ __forceinline__ void factor_invert_tile(double* tile, int* bad) {
+  const int lane = threadIdx.x & 63, r = lane & 15;
+  double a[16], v[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    a[j] = tile[r * kLdt + j];
+    v[j] = (j == r) ? 1.0 : 0.0;
+  }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const double piv = readlane_f64(a[k], k);
+    if (!(piv > 0.0) && lane == 0) *bad = 1;
+    // 1 / sqrt(pivot): the hardware's estimate and two Newton steps
+    double y = __builtin_amdgcn_rsq(piv);
+    y = y * fma(-0.5 * piv * y, y, 1.5);
+    y = y * fma(-0.5 * piv * y, y, 1.5);
+    const double l = a[k] * y;                // column k of the factor; rows above k hold values nothing reads
+    const double f = r > k ? l : 0.0;
+#pragma unroll
+    for (int j = k + 1; j < 16; ++j) a[j] = fma(-f, readlane_f64(l, j), a[j]);
+#pragma unroll
+    for (int j = 0; j <= k; ++j) {
+      const double row = readlane_f64(v[j], k) * y;
+      v[j] = (r == k) ? row : fma(-f, row, v[j]);
+    }
+  }
+  if (lane < 16) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) tile[r * kLdt + j] = (j <= r) ? v[j] : 0.0;
   }
 }
 
+// (K^T K) W = K^T V for 16 columns of W.  Grid (d / 16, heads), eight waves; every workgroup factors
+// its head's matrix itself (the factorisation is a chain of d / 16 steps that another workgroup could not
+// shorten).  Everything lies in LDS as 16 x 16 fp64 tiles and every product is a v_mfma_f64_16x16x4:
+//   right-looking blocked Cholesky: the diagonal tile is factored and its factor inverted by one wave,
+//   the tiles below it are multiplied by that inverse, the tiles right of it lose their products.
+//   The wave that updates the next diagonal tile goes on to factor it while the others finish the step.
+//   The right-hand sides ride along as one more block row, (K^T V)^T: after step s its tile s holds the
+//   forward solution, and the backward substitution runs over the same tiles.
+// Bound: the chain of pivots (16 reciprocal square roots and broadcasts per step).  51 us for d = 128, eight
+// heads; one workgroup per head with a thread per row and plain loops took 934 us (the sums included).
 template <typename T, int D>
-__global__ __launch_bounds__(kCalThreads) void solve_kernel(CalParams p) {
-  extern __shared__ __align__(16) unsigned char cal_smem[];
-  constexpr int LD = D + 1;                                  // padded row: a column walk hits distinct banks
-  double* G = reinterpret_cast<double*>(cal_smem);           // [D][LD]: K^T K, then its Cholesky factor; later K^T V / W
+__global__ __launch_bounds__(512) void solve_kernel(CalParams p) {
+  constexpr int NB = D / 16, kTri = NB * (NB + 1) / 2, NW = 512 / kWave;
+  extern __shared__ __align__(16) double cal_tiles[];        // [kTri + NB][kTileDoubles]
   __shared__ int bad;
-  const int h = blockIdx.x;
-  const float* part = p.part + (size_t)h * p.n_chunks * 2 * D * D;
-  double* Lg = p.c64 + (size_t)h * D * D;                    // the factor, parked in global memory for the solves
+  const int h = blockIdx.y, cb = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, l4 = lane >> 4;
+  auto tile = [&](int i, int j) { return cal_tiles + (i * (i + 1) / 2 + j) * kTileDoubles; };   // row NB: the right-hand sides
   if (threadIdx.x == 0) bad = 0;
-  for (int o = threadIdx.x; o < D * D; o += kCalThreads) {
-    double g = 0.0;
-#pragma unroll 8
-    for (int ch = 0; ch < p.n_chunks; ++ch) g += (double)part[(size_t)ch * 2 * D * D + o];
-    G[(o / D) * LD + o % D] = g;
-  }
-  __syncthreads();
-  // left-looking Cholesky, one thread per row: column kk of the factor is
-  //   L[i][kk] = (G[i][kk] - sum_{q < kk} L[i][q] L[kk][q]) / L[kk][kk],   i >= kk
-  for (int kk = 0; kk < D; ++kk) {
-    const int i = threadIdx.x;
-    double v = 0.0;
-    if (i >= kk && i < D) {
-      // four running sums and an unrolled body: the loads of several steps are in flight together
-      double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-      int q = 0;
-#pragma unroll 2
-      for (; q + 4 <= kk; q += 4) {
-        a0 += G[i * LD + q] * G[kk * LD + q];
-        a1 += G[i * LD + q + 1] * G[kk * LD + q + 1];
-        a2 += G[i * LD + q + 2] * G[kk * LD + q + 2];
-        a3 += G[i * LD + q + 3] * G[kk * LD + q + 3];
-      }
-      for (; q < kk; ++q) a0 += G[i * LD + q] * G[kk * LD + q];
-      v = G[i * LD + kk] - ((a0 + a1) + (a2 + a3));
+  {
+    const double* src = p.sums + (size_t)h * (kTri + NB * NB) * 256;
+    constexpr int kPairs = (kTri + NB) * 128;                  // 16-byte pairs
+    for (int o = threadIdx.x; o < kPairs; o += 512) {
+      const int t = o >> 7, e = (o & 127) * 2;
+      const size_t from = (size_t)(t < kTri ? t : kTri + cb * NB + (t - kTri)) * 256 + e;
+      *reinterpret_cast<double2*>(cal_tiles + t * kTileDoubles + (e >> 4) * kLdt + (e & 15)) = *reinterpret_cast<const double2*>(src + from);
     }
-    if (i == kk && !(v > 0.0)) bad = 1;
-    __syncthreads();                            // every row has read what it needs of column kk's old values
-    if (bad) break;
-    if (i == kk) G[kk * LD + kk] = sqrt(v);
-    __syncthreads();
-    if (i > kk && i < D) G[i * LD + kk] = v / G[kk * LD + kk];
-    __syncthreads();
   }
-  T* Wh = reinterpret_cast<T*>(p.W) + (size_t)h * D * D;
-  if (bad) {                                    // not positive definite: say so, write NaN
-    if (threadIdx.x == 0) p.status[h] = 1;
-    for (int o = threadIdx.x; o < D * D; o += kCalThreads) store_elem(Wh + o, __builtin_nanf(""));
-    return;
-  }
-  if (threadIdx.x == 0) p.status[h] = 0;
-  // Solves out of LDS: the factor is repacked as its lower triangle (through global memory,
-  // which avoids an in-place shuffle), and the right-hand sides come in blocks of kCols columns.
-  for (int o = threadIdx.x; o < D * D; o += kCalThreads) Lg[o] = G[(o / D) * LD + o % D];
   __syncthreads();
-  double* Lp = G;                                             // packed: L[i][q] at i (i + 1) / 2 + q
-  for (int o = threadIdx.x; o < D * D; o += kCalThreads) {
-    const int i = o / D, q = o % D;
-    if (q <= i) Lp[i * (i + 1) / 2 + q] = Lg[o];
-  }
-  constexpr int kSplit = 4;                                   // adjacent lanes that share a column's inner sums
-  constexpr int kCols = kCalThreads / kSplit;                 // columns per block
-  static_assert(D % kCols == 0 || kCols % D == 0, "column blocks");
-  constexpr int kBlockCols = kCols < D ? kCols : D;
-  double* C = Lp + D * (D + 1) / 2;                           // [D][kBlockCols]
-  const int jl = threadIdx.x / kSplit, r = threadIdx.x % kSplit;
-  auto wave_sync = [&]() {                                    // the lanes of a column sit in one wave
+  // C + sign * A B, or with kTransB A B^T: operand A row l15, element 4 kk + l4; operand B element 4 kk + l4, column l15;
+  // accumulator register v: row 4 v + l4, column l15
+  auto product = [&](const double* A, const double* B, bool trans_b, f64x4 acc, double sign) {
+    double av[4], bv[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      av[kk] = sign * A[l15 * kLdt + 4 * kk + l4];
+      bv[kk] = trans_b ? B[l15 * kLdt + 4 * kk + l4] : B[(4 * kk + l4) * kLdt + l15];
+    }
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kk], bv[kk], acc, 0, 0, 0);
+    return acc;
+  };
+  auto load_acc = [&](const double* X) {
+    f64x4 acc;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = X[(4 * v + l4) * kLdt + l15];
+    return acc;
+  };
+  auto store_acc = [&](double* X, const f64x4& acc) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) X[(4 * v + l4) * kLdt + l15] = acc[v];
+  };
+  auto wave_fence = [&]() {                                    // a tile handed over inside one wave
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  for (int j0 = 0; j0 < D; j0 += kBlockCols) {
-    __syncthreads();                                          // packed factor in place / previous block done
-    for (int o = threadIdx.x; o < D * kBlockCols; o += kCalThreads) {
-      const int i = o / kBlockCols, jj = o % kBlockCols;
-      double c = 0.0;
-#pragma unroll 8
-      for (int ch = 0; ch < p.n_chunks; ++ch) c += (double)part[(size_t)ch * 2 * D * D + D * D + i * D + j0 + jj];
-      C[o] = c;
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+  if (wave == 0) factor_invert_tile(tile(0, 0), &bad);
+  __syncthreads();
+  for (int s = 0; s < NB; ++s) {
+    for (int i = s + 1 + wave; i <= NB; i += NW) {
+      const f64x4 x = product(tile(i, s), tile(s, s), true, zero, 1.0);
+      wave_fence();
+      store_acc(tile(i, s), x);
     }
     __syncthreads();
-    if (jl < kBlockCols) {
-      // L y = c_j
-      for (int i = 0; i < D; ++i) {
-        const double* Li = Lp + i * (i + 1) / 2;
-        double s = 0.0, s1 = 0.0;
-        int q = r;
-#pragma unroll 4
-        for (; q + kSplit < i; q += 2 * kSplit) {
-          s += Li[q] * C[q * kBlockCols + jl];
-          s1 += Li[q + kSplit] * C[(q + kSplit) * kBlockCols + jl];
-        }
-        if (q < i) s += Li[q] * C[q * kBlockCols + jl];
-        s += s1;
-#pragma unroll
-        for (int o = 1; o < kSplit; o <<= 1) s += __shfl_xor(s, o, kWave);
-        if (r == 0) C[i * kBlockCols + jl] = (C[i * kBlockCols + jl] - s) / Li[i];
-        wave_sync();
+    // tiles (i, j), s < j <= i: number 0 is the next diagonal tile
+    int t = 0;
+    for (int j = s + 1; j < NB; ++j)
+      for (int i = j; i <= NB; ++i, ++t) {
+        if ((t == 0 ? 0 : 1 + (t - 1) % (NW - 1)) != wave) continue;
+        store_acc(tile(i, j), product(tile(i, s), tile(j, s), true, load_acc(tile(i, j)), -1.0));
       }
-      // L^T x = y
-      for (int i = D - 1; i >= 0; --i) {
-        double s = 0.0, s1 = 0.0;
-        int q = i + 1 + r;
-#pragma unroll 4
-        for (; q + kSplit < D; q += 2 * kSplit) {
-          s += Lp[q * (q + 1) / 2 + i] * C[q * kBlockCols + jl];
-          s1 += Lp[(q + kSplit) * (q + kSplit + 1) / 2 + i] * C[(q + kSplit) * kBlockCols + jl];
-        }
-        if (q < D) s += Lp[q * (q + 1) / 2 + i] * C[q * kBlockCols + jl];
-        s += s1;
-#pragma unroll
-        for (int o = 1; o < kSplit; o <<= 1) s += __shfl_xor(s, o, kWave);
-        const double x = (C[i * kBlockCols + jl] - s) / Lp[i * (i + 1) / 2 + i];
-        wave_sync();
-        if (r == 0) {
-          C[i * kBlockCols + jl] = x;
-          store_elem(Wh + (size_t)i * D + j0 + jl, (float)x);
-        }
-        wave_sync();
-      }
+    if (wave == 0 && s + 1 < NB) {
+      wave_fence();
+      factor_invert_tile(tile(s + 1, s + 1), &bad);
     }
+    __syncthreads();
+  }
+  // L^T X = Y, on the transposed right-hand sides: X_s^T = Y_s^T L_ss^-1, then Y_j^T -= X_s^T L_sj for j < s
+  T* Wh = reinterpret_cast<T*>(p.W) + (size_t)h * D * D;
+  for (int s = NB - 1; s >= 0; --s) {
+    if (wave == 0) {
+      const f64x4 x = product(tile(NB, s), tile(s, s), false, zero, 1.0);
+      wave_fence();
+      store_acc(tile(NB, s), x);
+    }
+    __syncthreads();
+    for (int j = wave; j < s; j += NW)
+      store_acc(tile(NB, j), product(tile(NB, s), tile(s, j), false, load_acc(tile(NB, j)), -1.0));
+    __syncthreads();
+  }
+  // row i of W, 16 columns side by side
+  for (int o = threadIdx.x; o < D * 16; o += 512) {
+    const int i = o >> 4, c = o & 15;
+    const double x = tile(NB, i >> 4)[c * kLdt + (i & 15)];
+    store_elem(Wh + (size_t)i * D + cb * 16 + c, bad ? __builtin_nanf("") : (float)x);       // not positive definite: say so
   }
 }
 
-void calibrate_chunks(int m, int& tokens_per_chunk, int& n_chunks) {
-  n_chunks = (m + 1023) / 1024;
+// fp64 tiles a head's sums take: K^T K up to its diagonal, and (K^T V)^T
+constexpr int cal_tiles_per_head(int d) { return (d / 16) * (d / 16 + 1) / 2 + (d / 16) * (d / 16); }
+
+// 1024 tokens per chunk, shorter ones while that leaves CUs without a workgroup (a chunk's tiles are a
+// chain, and shorter chunks only tighten the fp32 sums), longer ones past 64 chunks
+void calibrate_chunks(int m, int n_kv_heads, int& tokens_per_chunk, int& n_chunks) {
+  int want = 1024;
+  while (want > kCalMinTokens && (int64_t)((m + want - 1) / want) * n_kv_heads < 256) want >>= 1;
+  n_chunks = (m + want - 1) / want;
   if (n_chunks > kCalMaxChunks) n_chunks = kCalMaxChunks;
   if (n_chunks < 1) n_chunks = 1;
   tokens_per_chunk = ((m + n_chunks - 1) / n_chunks + kCalTile - 1) / kCalTile * kCalTile;
@@ -308,14 +410,18 @@ void calibrate_chunks(int m, int& tokens_per_chunk, int& n_chunks) {
 template <typename T, int D>
 int run_calibrate(const vector_shape& s, CalParams& p, hipStream_t stream) {
   const dim3 grid(p.n_chunks, s.n_kv_heads);
-  if constexpr (Elem<T>::kDtype == VECTOR_BF16) hipLaunchKernelGGL(gram_kernel<D>, grid, dim3(kCalThreads), 0, stream, p);
-  else hipLaunchKernelGGL(gram_valu_kernel<D>, grid, dim3(kCalThreads), 0, stream, p);
-  // padded square for the factorisation; packed triangle plus a block of right-hand sides for the solves
-  constexpr int kBlockCols = (kCalThreads / 4) < D ? (kCalThreads / 4) : D;
-  constexpr size_t kFactor = (size_t)D * (D + 1), kSolve = (size_t)D * (D + 1) / 2 + (size_t)D * kBlockCols;
-  const size_t lds = (kFactor > kSolve ? kFactor : kSolve) * sizeof(double);
+  if constexpr (Elem<T>::kDtype == VECTOR_BF16) {
+    constexpr size_t lds = 4 * GramTile<D>::kBytes;
+    VEC_HIP(set_max_lds(reinterpret_cast<const void*>(gram_kernel<D>), lds));
+    hipLaunchKernelGGL(gram_kernel<D>, grid, dim3(kCalThreads), lds, stream, p);
+  } else {
+    hipLaunchKernelGGL(gram_f32_kernel<D>, grid, dim3(kCalThreads), 0, stream, p);
+  }
+  hipLaunchKernelGGL(gram_reduce_kernel<D>, dim3(cal_tiles_per_head(D), s.n_kv_heads), dim3(256), 0, stream, p);
+  constexpr int NB = D / 16;
+  constexpr size_t lds = (size_t)(NB * (NB + 1) / 2 + NB) * kTileDoubles * sizeof(double);
   VEC_HIP(set_max_lds(reinterpret_cast<const void*>(solve_kernel<T, D>), lds));
-  hipLaunchKernelGGL((solve_kernel<T, D>), dim3(s.n_kv_heads), dim3(kCalThreads), lds, stream, p);
+  hipLaunchKernelGGL((solve_kernel<T, D>), dim3(NB, s.n_kv_heads), dim3(512), lds, stream, p);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
@@ -324,10 +430,10 @@ int run_calibrate(const vector_shape& s, CalParams& p, hipStream_t stream) {
 
 size_t calibrate_workspace_bytes(const vector_shape& s) {
   int tpc, nc;
-  calibrate_chunks(s.seq_len, tpc, nc);
+  calibrate_chunks(s.seq_len, s.n_kv_heads, tpc, nc);
   const size_t dd = (size_t)s.head_dim * s.head_dim;
-  return align_up((size_t)s.n_kv_heads * nc * 2 * dd * sizeof(float), 256) + align_up((size_t)s.n_kv_heads * dd * sizeof(double), 256) +
-         align_up((size_t)s.n_kv_heads * sizeof(int), 256);
+  return align_up((size_t)s.n_kv_heads * nc * 2 * dd * sizeof(float), 256) +
+         align_up((size_t)s.n_kv_heads * cal_tiles_per_head(s.head_dim) * 256 * sizeof(double), 256);
 }
 
 int launch_calibrate(const vector_shape& s, const void* k, const void* v, void* W, void* ws, hipStream_t stream) {
@@ -338,14 +444,12 @@ int launch_calibrate(const vector_shape& s, const void* k, const void* v, void* 
   p.k_sh = s.k_stride_head ? s.k_stride_head : (int64_t)s.seq_len * p.k_st;
   p.v_st = s.v_stride_tok ? s.v_stride_tok : D;
   p.v_sh = s.v_stride_head ? s.v_stride_head : (int64_t)s.seq_len * p.v_st;
-  calibrate_chunks(s.seq_len, p.tokens_per_chunk, p.n_chunks);
+  calibrate_chunks(s.seq_len, s.n_kv_heads, p.tokens_per_chunk, p.n_chunks);
   const size_t dd = (size_t)D * D;
   unsigned char* w8 = reinterpret_cast<unsigned char*>(ws);
   p.part = reinterpret_cast<float*>(w8);
   w8 += align_up((size_t)s.n_kv_heads * p.n_chunks * 2 * dd * sizeof(float), 256);
-  p.c64 = reinterpret_cast<double*>(w8);
-  w8 += align_up((size_t)s.n_kv_heads * dd * sizeof(double), 256);
-  p.status = reinterpret_cast<int*>(w8);
+  p.sums = reinterpret_cast<double*>(w8);
   if (s.dtype == VECTOR_BF16) {
     if (D == 128) return run_calibrate<bf16_t, 128>(s, p, stream);
     if (D == 64) return run_calibrate<bf16_t, 64>(s, p, stream);

@@ -109,3 +109,23 @@ def test_r2_of_the_fitted_map(name):
     for i, f in enumerate(vb.R2_FIELDS):
         np.testing.assert_allclose(got[:, i], ref[f], rtol=2e-4, atol=1e-6, err_msg=f)
     assert (got[:, 0] > 0.5).all()                                         # the planted map explains most of the variance
+
+
+@pytest.mark.parametrize("dtype,d,hkv,n", [("bf16", 128, 1, 128), ("bf16", 128, 1, 129), ("bf16", 128, 2, 255), ("bf16", 128, 1, 1025),
+                                           ("bf16", 64, 1, 65), ("bf16", 64, 3, 127), ("bf16", 64, 1, 2049), ("bf16", 128, 1, 20000),
+                                           ("f32", 64, 1, 67), ("f32", 64, 2, 257), ("f32", 128, 1, 143), ("f32", 128, 3, 769)])
+def test_fit_at_the_edges_of_tiles_and_chunks(dtype, d, hkv, n):
+    """Residual orthogonality K^T (V - K W) = 0 in fp64 from the inputs: the normal equations themselves,
+    whatever their conditioning at few tokens, and the oracle's fit where they are well posed."""
+    cfg = dg.scaled(dg.CONFIGS["cfg2" if dtype == "bf16" else "cfg1"], head_dim=d, n_kv_heads=hkv, n_q_heads=hkv, seq_len=n)
+    li = wl.make_layer(cfg, n)
+    got = _fit_gpu(cfg, pl.to_device(li.k), pl.to_device(li.v))
+    k, v = dg.widen(li.k), dg.widen(li.v)
+    ref = vo.ols_fit(k, v)
+    kt = np.swapaxes(k, 1, 2)
+    gram, cross = np.matmul(kt, k), np.matmul(kt, v)
+    rel = 2.0 ** -8 if dtype == "bf16" else 1e-5
+    slack = rel * np.matmul(np.abs(gram), np.abs(got)) + 2e-6 * np.matmul(np.abs(kt), np.abs(v))
+    assert (np.abs(np.matmul(gram, got) - cross) <= slack).all()
+    if n >= 2 * d:
+        assert np.abs(got - ref).max() <= (2e-2 if dtype == "bf16" else 1e-3)
