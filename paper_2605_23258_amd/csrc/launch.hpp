@@ -55,7 +55,11 @@ struct QueryLse { const float* lse; int64_t stride_head; };
 
 int launch_score_residual(const vector_shape& s, const void* q, const void* k, const void* v, const void* W,
                           float* score, float* eps, void* ws, hipStream_t stream, const RopeParams* rope = nullptr,
-                          void* route_ws = nullptr, const SeqStack* stack = nullptr, const QueryLse* lse = nullptr);
+                          void* route_ws = nullptr, const SeqStack* stack = nullptr, const QueryLse* lse = nullptr,
+                          bool leave_mass = false);
+// where launch_score_residual leaves the un-pooled attention mass [Hkv, n] in its workspace (leave_mass: and
+// does not pool it)
+float* score_mass(const vector_shape& s, void* ws);
 
 // A batch of sequences of different lengths through one set of launches.  Every sequence is
 // the one-sequence problem it would be alone (its own shape with explicit strides, pointers to
@@ -78,14 +82,15 @@ struct RaggedSeq {
 };
 struct PoolSeq { const float* mass; float* score; int seq_len, n_prefix; void* route_ws; int n_range; };
 size_t ragged_table_bytes(int count);
+size_t score_ragged_table_bytes(int count);     // the scorer's part of it, at its start
 // whether the G * w query rows of a KV head go through the two passes at once (a ragged launch needs that)
 bool score_heads_in_one_group(const vector_shape& s);
 size_t route_ragged_table_bytes(int count);
 int launch_score_residual_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, const void* W, void* tables,
-                                 hipStream_t stream, const RopeParams* rope = nullptr);
+                                 hipStream_t stream, const RopeParams* rope = nullptr, bool leave_mass = false);
 int launch_pool_scores_ragged(const PoolSeq* seqs, int count, int n_kv_heads, int pool_kernel, int pool_mode, void* tables,
                               hipStream_t stream);
-// tables: the part of the table area after the scorer's (ragged_table_bytes - route_ragged_table_bytes from its start)
+// tables: the part of the table area after the scorer's
 int launch_route_compact_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, void* tables, hipStream_t stream);
 // host bytes -> device memory in stream order, as kernel arguments of small copy launches (no
 // host buffer has to outlive the call, and the copies can be captured into a graph)
@@ -126,6 +131,23 @@ int launch_route(int n_kv_heads, int seq_len, const float* score, const float* e
 int launch_compact(const vector_shape& s, const void* k, const void* v, const int32_t* idx_retain,
                    const int32_t* idx_approx, int n_retain, int n_approx, void* k_ret, void* v_ret, void* k_apx,
                    int cap_retain, hipStream_t stream, const SeqStack* stack = nullptr);
+
+// Routing and compaction of heads of up to 24576 tokens in one launch (route_head.hip).
+bool route_head_fits(int seq_len);
+bool route_head_pools(int pool_kernel);         // whether it can form the pooled score itself
+struct HeadPool { const float* mass; float* score; int n_prefix, kernel, mode; };
+struct PackedRows {
+  const vector_shape* shape;
+  const void *k, *v;
+  void *k_ret, *v_ret, *k_apx;
+  int cap_retain;
+  const SeqStack* stack;
+};
+// pool: null, or the mass to pool into pool->score first (score is not read then); rows: null, or the packed cache
+int launch_route_head(int n_kv_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx, uint8_t* tier,
+                      int32_t* idx_retain, int32_t* idx_approx, const HeadPool* pool, const PackedRows* rows, hipStream_t stream);
+size_t route_head_table_bytes(int count);
+int launch_route_head_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, void* tables, hipStream_t stream);
 
 size_t decode_workspace_bytes(int batch, int n_q_heads, int n_kv_heads, int head_dim, int cap_retain, int n_approx);
 int launch_decode_attn(const vector_cache& c, const void* q, float scale, void* out, int flags, void* ws,

@@ -1,0 +1,159 @@
+// What the routing kernels share: order-preserving keys, bucket maps, scans, the pooling of the attention
+// mass, and the description of the packed cache's row copies.
+#pragma once
+#include "common.hpp"
+#include "launch.hpp"
+
+namespace vec {
+
+namespace {
+
+// Order-preserving map float -> u32 (larger float, larger key); -0 and +0 share a key.
+__device__ __forceinline__ uint32_t float_key(float x) {
+  uint32_t b = __float_as_uint(x + 0.0f);
+  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+
+// Leading digit of a key: which of the 2048 buckets of the first radix level it falls in.  Plain:
+// the key's top 11 bits, a quarter of an octave of scores per bucket.  When the scorer has told
+// where the bulk of a head's scores lies, 2046 buckets of 2^shift keys each are laid over that
+// range instead, so that scores which agree in their leading bits (a flat attention row: every
+// score within a few per cent of 1/n) still spread over the buckets; bucket 0 takes every key below
+// the range and bucket 2047 every key above it (attention sinks, the +inf of the window columns).
+// Keys of one bucket between 1 and 2046 agree in all bits from `shift` up; the two end buckets
+// (and they alone) may hold keys that differ anywhere.  Wherever a score falls the select stays
+// exact: the range only decides how evenly the buckets fill.
+struct DigitMap {
+  uint32_t lowq;
+  int shift;
+  __device__ __forceinline__ bool plain() const { return shift == 21 && lowq == 0u; }
+  __device__ __forceinline__ uint32_t digit(uint32_t key) const {
+    // a saturating difference: written with max (a compare-and-select around `q - lowq` is folded away by
+    // this compiler at -O3, which then lets the difference wrap)
+    const uint32_t q = key >> shift;
+    return min(max(q, lowq) - lowq, 2047u);
+  }
+  __device__ __forceinline__ bool shares_high_bits(int d) const { return plain() || (d > 0 && d < 2047); }
+};
+// 2046 buckets of 2^shift keys each over [klo, khi], shift as small as that allows
+__device__ __forceinline__ DigitMap digit_map_for_keys(uint32_t klo, uint32_t khi) {
+  DigitMap plain = {0u, 21};
+  if (khi < klo) return plain;
+  // (khi >> s) - (klo >> s) <= ((khi - klo) >> s) + 1: start where the difference has 11 bits left
+  const uint32_t diff = khi - klo;
+  int s = diff ? max(0, 21 - (int)__clz(diff)) : 0;
+  if ((khi >> s) - (klo >> s) > 2045u) ++s;
+  if (s >= 21) return plain;
+  DigitMap m = {max(klo >> s, 1u) - 1u, s};
+  return m;
+}
+// cnt, sum_l, sum_ll: over the head's prefix columns of positive attention mass m, their number and
+// the sums of l = log2(m) - log_ref and of l * l.  The buckets cover the mean of log2(m) give or
+// take four standard deviations (and a 64th of an octave, so that equal masses still get a
+// range): at most a sixteenth of the columns lie outside, whatever their distribution, and a few
+// columns far from the rest (attention sinks, the zero-padded edges of the pooling) move the range
+// very little.
+__device__ __forceinline__ DigitMap digit_map_for_stats(float cnt, float sum_l, float sum_ll, float log_ref) {
+  DigitMap plain = {0u, 21};
+  if (!(cnt >= 1.f)) return plain;
+  // hardware reciprocal, square root and exponential: a rough range is all that is needed, and
+  // every wave of the head gets the same bits from the same inputs
+  const float inv = __builtin_amdgcn_rcpf(cnt);
+  const float mu = sum_l * inv;
+  const float sd = __builtin_amdgcn_sqrtf(fmaxf(sum_ll * inv - mu * mu, 0.f));
+  const float mid = log_ref + mu, half = 4.f * sd + 0.015625f;
+  if (!(mid - half > -120.f) || !(mid + half < 120.f)) return plain;        // also NaN
+  return digit_map_for_keys(float_key(__builtin_amdgcn_exp2f(mid - half)), float_key(__builtin_amdgcn_exp2f(mid + half)));
+}
+// The same from a sample of the keys themselves, for scores of any sign that arrive without
+// statistics (vector_route on its own): cnt keys k = key >> 12 with sum s1 and sum of squares s2.
+// For positive floats the key is linear in the score inside an octave and counts octaves across
+// them, so its mean and deviation bound the bulk the same way.
+__device__ __forceinline__ DigitMap digit_map_for_sample(unsigned long long cnt, unsigned long long s1, unsigned long long s2) {
+  DigitMap plain = {0u, 21};
+  if (cnt < 32) return plain;
+  const double inv = 1.0 / (double)cnt, mu = (double)s1 * inv;
+  const double var = (double)s2 * inv - mu * mu;
+  const double half = 4.0 * sqrt(var > 0.0 ? var : 0.0) + 32.0;             // 32 * 4096 keys: a 64th of an octave
+  const double lo = (mu - half) * 4096.0, hi = (mu + half) * 4096.0;
+  const uint32_t klo = lo > 0.0 ? (uint32_t)lo : 0u, khi = hi < 4294967295.0 ? (uint32_t)hi : 0xffffffffu;
+  return digit_map_for_keys(klo, khi);
+}
+
+// ---------------------------------------------------------------------------
+// prefix sums inside a wave on the DPP network
+// ---------------------------------------------------------------------------
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ int dpp_take(int v) {   // 0 where no lane feeds this one
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, false);
+}
+__device__ __forceinline__ int wave_incl_scan_dpp(int v) {
+  v += dpp_take<0x111, 0xf>(v);      // row_shr:1 .. 8: inclusive scan inside each row of 16 lanes
+  v += dpp_take<0x112, 0xf>(v);
+  v += dpp_take<0x114, 0xf>(v);
+  v += dpp_take<0x118, 0xf>(v);
+  v += dpp_take<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+  v += dpp_take<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
+  return v;
+}
+__device__ __forceinline__ int wave_total_of_scan(int incl) { return __builtin_amdgcn_readlane(incl, 63); }
+
+
+// RAGGED launches (several sequences of different lengths at once): launch head hv is head
+// hv % seq_hps of sequence hv / seq_hps, whose parameter block replaces the launch's own
+template <bool RAGGED, typename P>
+__device__ __forceinline__ void take_sequence(P& p, int& h) {
+  if constexpr (RAGGED) {
+    const int seq = h / p.seq_hps;
+    h -= seq * p.seq_hps;
+    p = p.seq_table[seq];
+  }
+}
+
+// Average pooling ends in sum / kernel: the quotient through the reciprocal and one correction, which is
+// the correctly rounded one (three instructions instead of the ten of a division).
+__device__ __forceinline__ float pool_mean(float sum, float kernel, float inv_kernel) {
+  const float q = sum * inv_kernel;
+  return fmaf(fmaf(-q, kernel, sum), inv_kernel, q);
+}
+
+struct GatherParams;
+struct GatherParams {
+  const unsigned char* k; const unsigned char* v;
+  int64_t k_sh, k_st, v_sh, v_st;          // byte strides
+  int hps;                                 // stacked sequences: KV heads per sequence (0: one sequence)
+  int64_t k_sb, v_sb;                      // byte strides between sequences
+  const int32_t* idx_retain; const int32_t* idx_approx;
+  int n_retain, n_approx, cap_retain, row_bytes, n;
+  unsigned char* k_ret; unsigned char* v_ret; unsigned char* k_apx;
+  const GatherParams* seq_table;               // RAGGED launches: the sequences' parameter blocks, seq_hps heads each
+  int seq_hps;
+};
+
+inline GatherParams gather_params(const vector_shape& s, const void* k, const void* v, const int32_t* idx_retain, const int32_t* idx_approx,
+                           int n_retain, int n_approx, void* k_ret, void* v_ret, void* k_apx, int cap_retain, const SeqStack* stack) {
+  const int esz = (s.dtype == VECTOR_BF16) ? 2 : 4;
+  GatherParams p;
+  p.k = reinterpret_cast<const unsigned char*>(k);
+  p.v = reinterpret_cast<const unsigned char*>(v);
+  const int64_t k_st = s.k_stride_tok ? s.k_stride_tok : s.head_dim;
+  const int64_t v_st = s.v_stride_tok ? s.v_stride_tok : s.head_dim;
+  p.k_st = k_st * esz;
+  p.v_st = v_st * esz;
+  p.k_sh = (s.k_stride_head ? s.k_stride_head : (int64_t)s.seq_len * k_st) * esz;
+  p.v_sh = (s.v_stride_head ? s.v_stride_head : (int64_t)s.seq_len * v_st) * esz;
+  p.hps = stack ? stack->heads_per_seq : 0;
+  p.k_sb = stack ? stack->k_stride_seq * esz : 0;
+  p.v_sb = stack ? stack->v_stride_seq * esz : 0;
+  p.idx_retain = idx_retain; p.idx_approx = idx_approx;
+  p.n_retain = n_retain; p.n_approx = n_approx; p.cap_retain = cap_retain;
+  p.row_bytes = s.head_dim * esz; p.n = s.seq_len;
+  p.k_ret = reinterpret_cast<unsigned char*>(k_ret);
+  p.v_ret = reinterpret_cast<unsigned char*>(v_ret);
+  p.k_apx = reinterpret_cast<unsigned char*>(k_apx);
+  p.seq_table = nullptr; p.seq_hps = 0;
+  return p;
+}
+
+}  // namespace
+
+}  // namespace vec

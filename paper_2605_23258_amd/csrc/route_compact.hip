@@ -31,6 +31,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "route_common.hpp"
 
 #ifdef VEC_ROUTE_TRACE      // tuning builds only: time stamps of workgroup (0, 0)
 __device__ long long g_route_trace[32];
@@ -60,78 +61,6 @@ constexpr int kCandCap = 12288;           // candidates (keys sharing the thresh
 constexpr int kWaveCand = kCandCap / SW;  // each wave keeps its own: no shared counter
 constexpr int kMinChunk = 2048;           // tokens per chunk: doubled until a head has at most kMaxChunks
 constexpr int kMaxChunks = 32;
-
-// Order-preserving map float -> u32 (larger float, larger key); -0 and +0 share a key.
-__device__ __forceinline__ uint32_t float_key(float x) {
-  uint32_t b = __float_as_uint(x + 0.0f);
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-
-// Leading digit of a key: which of the 2048 buckets of the first radix level it falls in.  Plain:
-// the key's top 11 bits, a quarter of an octave of scores per bucket.  When the scorer has told
-// where the bulk of a head's scores lies, 2046 buckets of 2^shift keys each are laid over that
-// range instead, so that scores which agree in their leading bits (a flat attention row: every
-// score within a few per cent of 1/n) still spread over the buckets; bucket 0 takes every key below
-// the range and bucket 2047 every key above it (attention sinks, the +inf of the window columns).
-// Keys of one bucket between 1 and 2046 agree in all bits from `shift` up; the two end buckets
-// (and they alone) may hold keys that differ anywhere.  Wherever a score falls the select stays
-// exact: the range only decides how evenly the buckets fill.
-struct DigitMap {
-  uint32_t lowq;
-  int shift;
-  __device__ __forceinline__ bool plain() const { return shift == 21 && lowq == 0u; }
-  __device__ __forceinline__ uint32_t digit(uint32_t key) const {
-    // a saturating difference: written with max (a compare-and-select around `q - lowq` is folded away by
-    // this compiler at -O3, which then lets the difference wrap)
-    const uint32_t q = key >> shift;
-    return min(max(q, lowq) - lowq, 2047u);
-  }
-  __device__ __forceinline__ bool shares_high_bits(int d) const { return plain() || (d > 0 && d < 2047); }
-};
-// 2046 buckets of 2^shift keys each over [klo, khi], shift as small as that allows
-__device__ __forceinline__ DigitMap digit_map_for_keys(uint32_t klo, uint32_t khi) {
-  DigitMap plain = {0u, 21};
-  if (khi < klo) return plain;
-  // (khi >> s) - (klo >> s) <= ((khi - klo) >> s) + 1: start where the difference has 11 bits left
-  const uint32_t diff = khi - klo;
-  int s = diff ? max(0, 21 - (int)__clz(diff)) : 0;
-  if ((khi >> s) - (klo >> s) > 2045u) ++s;
-  if (s >= 21) return plain;
-  DigitMap m = {max(klo >> s, 1u) - 1u, s};
-  return m;
-}
-// cnt, sum_l, sum_ll: over the head's prefix columns of positive attention mass m, their number and
-// the sums of l = log2(m) - log_ref and of l * l.  The buckets cover the mean of log2(m) give or
-// take four standard deviations (and a 64th of an octave, so that equal masses still get a
-// range): at most a sixteenth of the columns lie outside, whatever their distribution, and a few
-// columns far from the rest (attention sinks, the zero-padded edges of the pooling) move the range
-// very little.
-__device__ __forceinline__ DigitMap digit_map_for_stats(float cnt, float sum_l, float sum_ll, float log_ref) {
-  DigitMap plain = {0u, 21};
-  if (!(cnt >= 1.f)) return plain;
-  // hardware reciprocal, square root and exponential: a rough range is all that is needed, and
-  // every wave of the head gets the same bits from the same inputs
-  const float inv = __builtin_amdgcn_rcpf(cnt);
-  const float mu = sum_l * inv;
-  const float sd = __builtin_amdgcn_sqrtf(fmaxf(sum_ll * inv - mu * mu, 0.f));
-  const float mid = log_ref + mu, half = 4.f * sd + 0.015625f;
-  if (!(mid - half > -120.f) || !(mid + half < 120.f)) return plain;        // also NaN
-  return digit_map_for_keys(float_key(__builtin_amdgcn_exp2f(mid - half)), float_key(__builtin_amdgcn_exp2f(mid + half)));
-}
-// The same from a sample of the keys themselves, for scores of any sign that arrive without
-// statistics (vector_route on its own): cnt keys k = key >> 12 with sum s1 and sum of squares s2.
-// For positive floats the key is linear in the score inside an octave and counts octaves across
-// them, so its mean and deviation bound the bulk the same way.
-__device__ __forceinline__ DigitMap digit_map_for_sample(unsigned long long cnt, unsigned long long s1, unsigned long long s2) {
-  DigitMap plain = {0u, 21};
-  if (cnt < 32) return plain;
-  const double inv = 1.0 / (double)cnt, mu = (double)s1 * inv;
-  const double var = (double)s2 * inv - mu * mu;
-  const double half = 4.0 * sqrt(var > 0.0 ? var : 0.0) + 32.0;             // 32 * 4096 keys: a 64th of an octave
-  const double lo = (mu - half) * 4096.0, hi = (mu + half) * 4096.0;
-  const uint32_t klo = lo > 0.0 ? (uint32_t)lo : 0u, khi = hi < 4294967295.0 ? (uint32_t)hi : 0xffffffffu;
-  return digit_map_for_keys(klo, khi);
-}
 
 // hist[digit] += cnt (cnt in 0..7) for every lane.  Keys of neighbouring tokens often share their
 // leading bits, so a plain LDS atomic would serialise up to 64 lanes on one bin: lanes that agree
@@ -179,20 +108,6 @@ __device__ __forceinline__ void hist_add_thread_keys(int* hist, const uint32_t (
 // prefix sums: inside a wave on the DPP network, across the waves through one LDS row that
 // every thread reads whole (no chain of dependent LDS reads)
 // ---------------------------------------------------------------------------
-template <int CTRL, int ROW_MASK> __device__ __forceinline__ int dpp_take(int v) {   // 0 where no lane feeds this one
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, false);
-}
-__device__ __forceinline__ int wave_incl_scan_dpp(int v) {
-  v += dpp_take<0x111, 0xf>(v);      // row_shr:1 .. 8: inclusive scan inside each row of 16 lanes
-  v += dpp_take<0x112, 0xf>(v);
-  v += dpp_take<0x114, 0xf>(v);
-  v += dpp_take<0x118, 0xf>(v);
-  v += dpp_take<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
-  v += dpp_take<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
-  return v;
-}
-__device__ __forceinline__ int wave_total_of_scan(int incl) { return __builtin_amdgcn_readlane(incl, 63); }
-
 // NW per-wave values -> their sum over the waves before `wave`, and over all waves
 template <int NW> __device__ __forceinline__ void wave_row_sums(const int* row, int wave, int& before, int& total) {
   before = 0;
@@ -248,6 +163,7 @@ struct BucketParams {
   uint32_t* bkey;         // [H, n]: chunk c owns [c * chunk_tokens, ...), keys grouped by digit, highest first
   int32_t* bpos;          // [H, n]: the token each key belongs to
   int n, n_prefix, kernel, chunk_tokens, n_chunks;
+  float inv_kernel;       // POOL: 1 / kernel
   int take_max;           // POOL: the window's largest mass instead of its sum over the kernel size
   uint32_t* map;          // [H, 2] with the buckets: the digit map (lowq, shift) this launch chooses, for the selecting launch
   const float4* range;    // [H, n_range] (count, sum l, sum l * l) of the mass left by the scorer's workgroups, when n_range > 0
@@ -256,17 +172,6 @@ struct BucketParams {
   const BucketParams* seq_table;   // RAGGED launches: the sequences' parameter blocks, seq_hps heads each
   int seq_hps;
 };
-
-// RAGGED launches (several sequences of different lengths at once): launch head hv is head
-// hv % seq_hps of sequence hv / seq_hps, whose parameter block replaces the launch's own
-template <bool RAGGED, typename P>
-__device__ __forceinline__ void take_sequence(P& p, int& h) {
-  if constexpr (RAGGED) {
-    const int seq = h / p.seq_hps;
-    h -= seq * p.seq_hps;
-    p = p.seq_table[seq];
-  }
-}
 
 template <bool POOL, bool RAGGED = false>
 __global__ __launch_bounds__(BT) void route_bucket_kernel(BucketParams p) {
@@ -394,7 +299,7 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(BucketParams p) {
 #pragma unroll
           for (int d = -EPT; d <= EPT; ++d)
             if (d >= -half && d <= half && t + d < p.n_prefix) acc = p.take_max ? fmaxf(acc, m[EPT + j + d]) : acc + m[EPT + j + d];
-          s[j] = (ok[j] && t < p.n_prefix) ? (p.take_max ? acc : acc / (float)p.kernel) : INFINITY;
+          s[j] = (ok[j] && t < p.n_prefix) ? (p.take_max ? acc : pool_mean(acc, (float)p.kernel, p.inv_kernel)) : INFINITY;
         }
       } else {
 #pragma unroll
@@ -405,7 +310,7 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(BucketParams p) {
             const int lo = max(0, t - half), hi = min(p.n_prefix - 1, t + half);
             float acc = 0.f;
             for (int i = lo; i <= hi; ++i) acc = p.take_max ? fmaxf(acc, src[i]) : acc + src[i];
-            out = p.take_max ? acc : acc / (float)p.kernel;
+            out = p.take_max ? acc : pool_mean(acc, (float)p.kernel, p.inv_kernel);
           }
           s[j] = out;
         }
@@ -1083,19 +988,6 @@ __global__ __launch_bounds__(256) void route_evict_all_kernel(uint8_t* __restric
 // ---------------------------------------------------------------------------
 // compaction: one 16-byte piece per thread, P pieces per row
 // ---------------------------------------------------------------------------
-struct GatherParams;
-struct GatherParams {
-  const unsigned char* k; const unsigned char* v;
-  int64_t k_sh, k_st, v_sh, v_st;          // byte strides
-  int hps;                                 // stacked sequences: KV heads per sequence (0: one sequence)
-  int64_t k_sb, v_sb;                      // byte strides between sequences
-  const int32_t* idx_retain; const int32_t* idx_approx;
-  int n_retain, n_approx, cap_retain, row_bytes, n;
-  unsigned char* k_ret; unsigned char* v_ret; unsigned char* k_apx;
-  const GatherParams* seq_table;               // RAGGED launches: the sequences' parameter blocks, seq_hps heads each
-  int seq_hps;
-};
-
 template <bool RAGGED>
 __global__ __launch_bounds__(256) void gather_rows_kernel(GatherParams p) {
   int h = blockIdx.y;
@@ -1184,7 +1076,7 @@ BucketParams pool_bucket_params(const float* mass, float* score, int n_kv_heads,
                                 int pool_mode, void* route_ws, int n_range, RouteLayout& L) {
   L = route_layout(n_kv_heads, seq_len, 0);      // the bucket areas do not depend on the pool size
   BucketParams bp;
-  bp.src = mass; bp.score = score; bp.n = seq_len; bp.n_prefix = n_prefix; bp.kernel = pool_kernel; bp.take_max = pool_mode == VECTOR_POOL_MAX;
+  bp.src = mass; bp.score = score; bp.n = seq_len; bp.n_prefix = n_prefix; bp.kernel = pool_kernel; bp.inv_kernel = 1.0f / (float)pool_kernel; bp.take_max = pool_mode == VECTOR_POOL_MAX;
   fill_bucket_params(bp, L, route_ws);
   bp.n_range = route_ws ? n_range : 0;
   bp.log_ref = -log2f((float)(n_prefix > 0 ? n_prefix : 1));     // as in the scorer's second pass
@@ -1209,31 +1101,6 @@ RouteParams route_params(int n_kv_heads, int seq_len, const float* score, const 
   p.pool_idx = reinterpret_cast<int32_t*>(w8 + L.off_idx);
   p.pool_key = reinterpret_cast<uint32_t*>(w8 + L.off_key);
   p.tier = tier; p.idx_retain = idx_retain; p.idx_approx = idx_approx;
-  p.seq_table = nullptr; p.seq_hps = 0;
-  return p;
-}
-
-GatherParams gather_params(const vector_shape& s, const void* k, const void* v, const int32_t* idx_retain, const int32_t* idx_approx,
-                           int n_retain, int n_approx, void* k_ret, void* v_ret, void* k_apx, int cap_retain, const SeqStack* stack) {
-  const int esz = (s.dtype == VECTOR_BF16) ? 2 : 4;
-  GatherParams p;
-  p.k = reinterpret_cast<const unsigned char*>(k);
-  p.v = reinterpret_cast<const unsigned char*>(v);
-  const int64_t k_st = s.k_stride_tok ? s.k_stride_tok : s.head_dim;
-  const int64_t v_st = s.v_stride_tok ? s.v_stride_tok : s.head_dim;
-  p.k_st = k_st * esz;
-  p.v_st = v_st * esz;
-  p.k_sh = (s.k_stride_head ? s.k_stride_head : (int64_t)s.seq_len * k_st) * esz;
-  p.v_sh = (s.v_stride_head ? s.v_stride_head : (int64_t)s.seq_len * v_st) * esz;
-  p.hps = stack ? stack->heads_per_seq : 0;
-  p.k_sb = stack ? stack->k_stride_seq * esz : 0;
-  p.v_sb = stack ? stack->v_stride_seq * esz : 0;
-  p.idx_retain = idx_retain; p.idx_approx = idx_approx;
-  p.n_retain = n_retain; p.n_approx = n_approx; p.cap_retain = cap_retain;
-  p.row_bytes = s.head_dim * esz; p.n = s.seq_len;
-  p.k_ret = reinterpret_cast<unsigned char*>(k_ret);
-  p.v_ret = reinterpret_cast<unsigned char*>(v_ret);
-  p.k_apx = reinterpret_cast<unsigned char*>(k_apx);
   p.seq_table = nullptr; p.seq_hps = 0;
   return p;
 }
@@ -1264,6 +1131,8 @@ int launch_route(int n_kv_heads, int seq_len, const float* score, const float* e
     VEC_HIP(hipGetLastError());
     return VECTOR_OK;
   }
+  if (!have_buckets && route_head_fits(seq_len))
+    return launch_route_head(n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, nullptr, nullptr, stream);
   RouteLayout L;
   const RouteParams p = route_params(n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, ws, L);
   VEC_HIP(set_max_lds(reinterpret_cast<const void*>(route_pool_kernel<false>), kSelectLds));
@@ -1272,7 +1141,7 @@ int launch_route(int n_kv_heads, int seq_len, const float* score, const float* e
   if (t_) timing_begin(K_ROUTE, stream);             // the launches count as one routing step
   if (!have_buckets) {
     BucketParams bp;
-    bp.src = score; bp.score = nullptr; bp.n = seq_len; bp.n_prefix = seq_len; bp.kernel = 1; bp.take_max = 0;
+    bp.src = score; bp.score = nullptr; bp.n = seq_len; bp.n_prefix = seq_len; bp.kernel = 1; bp.inv_kernel = 1.f; bp.take_max = 0;
     fill_bucket_params(bp, L, ws);
     hipLaunchKernelGGL(route_bucket_kernel<false>, dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, bp);
   }

@@ -1,0 +1,595 @@
+// Routing of a whole head in one launch (Section 3.2, Steps 1 and 3, and the packed cache), for heads of
+// up to kHeadTokens tokens: pooling of the attention mass, both selections, tiers, index lists and
+// row copies.
+//
+// The chain of selections is latency: with the pieces of a head spread over workgroups, every exchange
+// between them is a kernel boundary, and the boundaries (bucket tables, pool list, split, gather: four
+// launches of 4-12 us whatever the size) cost more than the work.  So nothing is exchanged.  Every workgroup
+// of a head loads the head's scores and residuals whole into registers (24576 tokens: 48 + 48 per thread) and
+// finds both thresholds itself; then it emits and copies its own part of the tokens.  The redundant part
+// is about 50 vector instructions and two LDS atomics per token and workgroup: a workgroup lives 13 us at 8192 tokens,
+// 27 at 20000, 37 at 32768, against 34, 38 and 41 us for the four launches (8 heads).  There lies the line to
+// the launches of route_compact.hip.
+//
+// A selection finds the k-th largest of the keys in registers: one LDS histogram over buckets laid
+// where a sample says that the keys lie (DigitMap), then the keys of the bucket that holds it are ranked
+// against each other by (key, lower token first); a bucket of more keys than kRankCap is cut further by
+// histograms over its own range, and equal keys by histograms over their tokens.
+#include "common.hpp"
+#include "launch.hpp"
+#include "route_common.hpp"
+
+namespace vec {
+
+namespace {
+
+constexpr int HT = 512;                         // threads of a workgroup
+constexpr int kMaxBlocks = 12;                  // 24576 tokens
+constexpr int HW = HT / kWave;
+constexpr int kHeadBlock = HT * 4;              // tokens per block: four consecutive ones per thread
+constexpr int kHeadBins = 2048;
+constexpr int kRankCap = 256;                   // candidates ranked by comparison
+
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_u;   // 16-byte access at any element
+
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+struct HeadParams;
+struct HeadParams {
+  const float* src;       // POOL: attention mass [H, n]; otherwise the scores [H, n]
+  float* score;           // POOL: output [H, n]
+  const float* eps;       // [H, n]
+  int n, n_prefix, half, take_max;      // POOL: prefix columns, half the kernel (at most 4), maximum instead of mean
+  float kernel, inv_kernel;
+  int n_pool, n_approx;
+  int sub_parts;          // workgroups per block of kHeadBlock tokens (1 .. HW), or 1 and
+  int blocks_per_part;    // blocks per workgroup
+  uint8_t* tier; int32_t* idx_retain; int32_t* idx_approx;
+  GatherParams g;         // row copies (k null: none)
+  const HeadParams* seq_table;          // RAGGED launches: the sequences' parameter blocks, seq_hps heads each
+  int seq_hps;
+};
+
+struct HeadShared {
+  __align__(16) int hist[kHeadBins];
+  __align__(16) f32x4 first[kMaxBlocks * HW], last[kMaxBlocks * HW];     // POOL: the quads at the edges of every wave's run of a block
+  __align__(16) unsigned long long cand[kRankCap];     // (key, ~token)
+  __align__(16) int list[kHeadBlock];                  // tokens whose rows this workgroup copies: retained, then approximated
+  int wsum[3][HW];
+  float stat[3][HW];
+  uint32_t center[2];
+  int pick[3];            // bucket, #keys above it, keys in it
+  int n_cand;
+  uint32_t thr, thr_tok, next_key;
+};
+
+// Workgroup barrier for data in LDS alone: global loads in flight (the residuals, while the scores are worked
+// on) and stores (score, tiers, lists) are not waited for.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// packed pairs of counts: retained in the low half, approximated in the high one
+__device__ __forceinline__ int low16(int x) { return x & 0xffff; }
+__device__ __forceinline__ int high16(int x) { return (int)((uint32_t)x >> 16); }
+
+// the k-th largest (key, lower token first): keys above thr, and keys equal to thr up to token tok, are the k;
+// all_equal: every key equal to thr is among them
+struct Threshold { uint32_t thr, tok; bool all_equal; };
+
+// token of a thread's slot; base: first_token(), taken anew where slots are walked (its sums with the slots'
+// constants would otherwise be kept in registers for the whole kernel)
+__device__ __forceinline__ int first_token() {
+  int t = (int)threadIdx.x * 4;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+__device__ __forceinline__ int head_token(int base, int slot) { return (slot >> 2) * kHeadBlock + base + (slot & 3); }
+
+// sum of a float over the waves' entries, the same bits in every lane
+__device__ __forceinline__ float sum_of_waves(const float* row, int lane) {
+  static_assert(HW == 8, "eight waves");
+  float x = row[lane & 7];
+  x += dpp_take_f<0x111, 0xf>(0.f, x);
+  x += dpp_take_f<0x112, 0xf>(0.f, x);
+  x += dpp_take_f<0x114, 0xf>(0.f, x);
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 7));
+}
+
+// exclusive prefix over the workgroup's threads of a packed pair of counts, and the total; row: [HW]
+__device__ __forceinline__ void head_scan(int v, int* row, int& before, int& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int incl = wave_incl_scan_dpp(v);
+  if (lane == 63) row[wave] = incl;
+  lds_barrier();
+  int x = row[lane & 7];                         // every lane one wave's total
+  x += dpp_take<0x111, 0xf>(x);
+  x += dpp_take<0x112, 0xf>(x);
+  x += dpp_take<0x114, 0xf>(x);
+  const int upto = wave ? __builtin_amdgcn_readlane(x, wave - 1) : 0;
+  total = __builtin_amdgcn_readlane(x, 7);
+  before = upto + incl - v;
+}
+
+__device__ __forceinline__ void clear_hist(HeadShared& sh) {
+  static_assert(kHeadBins == 4 * HT, "four buckets per thread");
+  *reinterpret_cast<int4*>(sh.hist + 4 * threadIdx.x) = make_int4(0, 0, 0, 0);
+}
+
+// histogram counts -> the bucket with #(keys above it) < k <= #(keys in or above it)
+__device__ __forceinline__ void head_pick(HeadShared& sh, int k, int& d, int& above, int& count) {
+  const int lo = kHeadBins - 4 - 4 * (int)threadIdx.x;
+  const int4 c = *reinterpret_cast<const int4*>(sh.hist + lo);        // buckets lo .. lo + 3
+  int before, total;
+  head_scan(c.x + c.y + c.z + c.w, sh.wsum[0], before, total);
+  if (before < k && k <= before + c.x + c.y + c.z + c.w) {
+    int b = lo + 3, in = c.w;
+    if (k > before + in) { before += in; in = c.z; --b; }
+    if (b == lo + 2 && k > before + in) { before += in; in = c.y; --b; }
+    if (b == lo + 1 && k > before + in) { before += in; in = c.x; --b; }
+    sh.pick[0] = b; sh.pick[1] = before; sh.pick[2] = in;
+  }
+  lds_barrier();
+  d = sh.pick[0]; above = sh.pick[1]; count = sh.pick[2];
+}
+
+// Threshold of the k largest of the workgroup's keys (0: no key in that slot); 1 <= k <= number of keys.
+// center: a typical key.  Starts by clearing the histogram; the caller has passed a barrier since the
+// last use of sh.
+template <int NS>
+__device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int k, uint32_t center, HeadShared& sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  clear_hist(sh);
+  // mean and deviation of a sample (in units of 4096 keys, about the center): where to lay the buckets
+  float cnt = 0.f, s1 = 0.f, s2 = 0.f;
+  constexpr int kStep = NS / 4 > 8 ? 2 : 1;
+#pragma unroll
+  for (int j = 0; j < NS / 4; j += kStep) {
+    const uint32_t x = key[4 * j];
+    const bool ok = x > 0x007fffffu && x < 0xff800000u;                 // a finite number
+    const float dlt = ok ? (float)((int)(x >> 12) - (int)(center >> 12)) : 0.f;
+    cnt += ok ? 1.f : 0.f;
+    s1 += dlt;
+    s2 = fmaf(dlt, dlt, s2);
+  }
+  cnt = wave_sum_dpp(cnt); s1 = wave_sum_dpp(s1); s2 = wave_sum_dpp(s2);
+  if (lane == 0) { sh.stat[0][wave] = cnt; sh.stat[1][wave] = s1; sh.stat[2][wave] = s2; }
+  lds_barrier();
+  if (threadIdx.x == 0) { sh.n_cand = 0; sh.next_key = 0u; }
+  cnt = sum_of_waves(sh.stat[0], lane); s1 = sum_of_waves(sh.stat[1], lane); s2 = sum_of_waves(sh.stat[2], lane);
+  DigitMap map = {0u, 21};
+  if (cnt >= 32.f) {
+    const float inv = __builtin_amdgcn_rcpf(cnt), mu = s1 * inv;
+    const float half = 4.f * __builtin_amdgcn_sqrtf(fmaxf(s2 * inv - mu * mu, 0.f)) + 32.f;
+    const float mid = (float)(center >> 12) + mu;
+    map = digit_map_for_keys((uint32_t)fmaxf(mid - half, 0.f) << 12, (uint32_t)fminf(mid + half, 1048575.f) << 12);
+  }
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    if (key[i] != 0u) atomicAdd(&sh.hist[map.digit(key[i])], 1);
+    if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);                // four at a time: the digits of all would not fit the registers
+  }
+  lds_barrier();
+  int d, above, count;
+  head_pick(sh, k, d, above, count);
+  k -= above;
+  // the bucket's keys: [lo, lo + span]
+  uint32_t lo, span;
+  if (map.plain()) {
+    lo = (uint32_t)d << 21;
+    span = (1u << 21) - 1u;
+  } else {
+    lo = d == 0 ? 0u : (map.lowq + (uint32_t)d) << map.shift;
+    const uint32_t hi = d == 2047 ? 0xffffffffu : ((map.lowq + (uint32_t)d + 1u) << map.shift) - 1u;
+    span = hi - lo;
+  }
+  if (lo == 0u) { lo = 1u; span -= 1u; }                                // no key is 0
+  while (count > kRankCap && span != 0u) {                              // uniform
+    const int s = max(0, 21 - (int)__clz(span));                        // at most 2048 buckets over the range
+    clear_hist(sh);
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+      if (key[i] - lo <= span) atomicAdd(&sh.hist[(key[i] - lo) >> s], 1), __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    head_pick(sh, k, d, above, count);
+    k -= above;
+    lo += (uint32_t)d << s;
+    span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
+  }
+  Threshold out;
+  if (count > kRankCap) {
+    // one key, many tokens: cut the range of ~token the same way until one is left
+    const uint32_t thr = lo;
+    uint32_t tlo = 0u, tspan = 0xffffu;                                 // values 65535 - token
+    while (tspan != 0u) {
+      const int s = max(0, 21 - (int)__clz(tspan));
+      clear_hist(sh);
+      lds_barrier();
+      const int base = first_token();
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        const uint32_t v = 65535u - (uint32_t)head_token(base, i) - tlo;
+        if (key[i] == thr && v <= tspan) atomicAdd(&sh.hist[v >> s], 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      lds_barrier();
+      head_pick(sh, k, d, above, count);
+      k -= above;
+      tlo += (uint32_t)d << s;
+      tspan = min(tspan - ((uint32_t)d << s), (1u << s) - 1u);
+    }
+    out.thr = thr; out.tok = 65535u - tlo; out.all_equal = false;
+    lds_barrier();
+    return out;
+  }
+  const int base = first_token();
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    if (key[i] - lo <= span) {
+      const int at = atomicAdd(&sh.n_cand, 1);
+      if (at < kRankCap) sh.cand[at] = ((unsigned long long)key[i] << 32) | (uint32_t)~head_token(base, i);
+    }
+    if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+  lds_barrier();
+  if ((int)threadIdx.x < count) {
+    const unsigned long long mine = sh.cand[threadIdx.x];
+    int rank = 0;
+#pragma unroll 4
+    for (int j = 0; j < count; ++j) rank += sh.cand[j] > mine;
+    if (rank == k - 1) { sh.thr = (uint32_t)(mine >> 32); sh.thr_tok = ~(uint32_t)mine; }
+    if (rank == k) sh.next_key = (uint32_t)(mine >> 32);
+  }
+  lds_barrier();
+  out.thr = sh.thr; out.tok = sh.thr_tok; out.all_equal = sh.next_key != sh.thr;
+  return out;
+}
+
+// J: blocks of kHeadBlock tokens a head may have
+template <int J, bool POOL, bool RAGGED>
+__global__ __launch_bounds__(HT) void route_head_kernel(HeadParams p) {
+  int part, h;
+  if (RAGGED) { part = blockIdx.x; h = blockIdx.y; }
+  else xcd_chunk_head(part, h);
+  take_sequence<RAGGED>(p, h);
+  const int n = p.n;
+  const int n_blocks = (n + kHeadBlock - 1) / kHeadBlock;
+  const int block0 = part / p.sub_parts * p.blocks_per_part, sub = part % p.sub_parts;
+  if (block0 >= n_blocks) return;
+  const int block1 = min(n_blocks, block0 + p.blocks_per_part);
+  __shared__ HeadShared sh;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // the waves of a block whose tokens this workgroup emits
+  const int live = n < kHeadBlock ? (n + 4 * kWave - 1) / (4 * kWave) : HW;       // waves of a block that hold tokens
+  const int wave0 = sub * live / p.sub_parts, wave1 = (sub + 1) * live / p.sub_parts;
+  const bool my_wave = wave >= wave0 && wave < wave1;
+
+  const float* src = p.src + (size_t)h * n;
+  const float* eps = p.eps + (size_t)h * n;
+  auto load4 = [&](const float* a, int t0) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (t0 + 4 <= n) {
+      x = *reinterpret_cast<const f32x4_u*>(a + t0);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (t0 + e < n) x[e] = a[t0 + e];
+    }
+    return x;
+  };
+  f32x4 q[J], ev[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) q[j] = load4(src, j * kHeadBlock + (int)threadIdx.x * 4);
+#pragma unroll
+  for (int j = 0; j < J; ++j) ev[j] = load4(eps, j * kHeadBlock + (int)threadIdx.x * 4);
+
+  uint32_t key[J * 4];
+  // a typical token, for the samples: the middle of the first block (or of what there is of it)
+  const bool center_thread = (int)threadIdx.x == min(n, kHeadBlock) / 8;
+  if constexpr (POOL) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int t0 = j * kHeadBlock + (int)threadIdx.x * 4;
+      if (t0 - lane * 4 + 4 * kWave > p.n_prefix) {            // uniform per wave: window columns have no mass
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (t0 + e >= p.n_prefix) q[j][e] = 0.f;
+      }
+      if (lane == 0) sh.first[j * HW + wave] = q[j];
+      if (lane == 63) sh.last[j * HW + wave] = q[j];
+    }
+    lds_barrier();
+    float* dst = p.score + (size_t)h * n;
+    // one block after the other through `fold`, which makes the pooled value of token e out of the 12 masses around the quad
+    auto pool_blocks = [&](auto fold) {
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int t0 = j * kHeadBlock + (int)threadIdx.x * 4, slot = j * HW + wave;
+        f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
+        if (slot > 0) lo = sh.last[slot - 1];
+        if (slot + 1 < J * HW) hi = sh.first[slot + 1];
+        float m[12];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          m[e] = dpp_take_f<0x138, 0xf>(lo[e], q[j][e]);         // wave_shr:1, the quad before
+          m[4 + e] = q[j][e];
+          m[8 + e] = dpp_take_f<0x130, 0xf>(hi[e], q[j][e]);     // wave_shl:1, the quad after
+        }
+        f32x4 s;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = fold(m + 4 + e);
+        if (t0 - lane * 4 + 4 * kWave > p.n_prefix) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (t0 + e >= p.n_prefix) s[e] = INFINITY;
+        }
+        if (my_wave && j >= block0 && j < block1) {
+          if (t0 + 4 <= n) {
+            *reinterpret_cast<f32x4_u*>(dst + t0) = s;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (t0 + e < n) dst[t0 + e] = s[e];
+          }
+        }
+        q[j] = s;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // in ascending token order; mass is never negative, so the sums and maxima may start from zero
+    if (p.half == 3 && !p.take_max) {
+      pool_blocks([&](const float* m) {
+        float acc = m[-3];
+#pragma unroll
+        for (int dlt = -2; dlt <= 3; ++dlt) acc += m[dlt];
+        return pool_mean(acc, 7.f, p.inv_kernel);
+      });
+    } else {
+      pool_blocks([&](const float* m) {
+        float sum = 0.f, most = 0.f;
+#pragma unroll
+        for (int dlt = -4; dlt <= 4; ++dlt) {
+          const float x = (dlt >= -p.half && dlt <= p.half) ? m[dlt] : 0.f;
+          sum += x;
+          most = fmaxf(most, x);
+        }
+        return p.take_max ? most : pool_mean(sum, p.kernel, p.inv_kernel);
+      });
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) key[4 * j + e] = float_key(q[j][e]);
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int t0 = j * kHeadBlock + (int)threadIdx.x * 4;
+    if (t0 - lane * 4 + 4 * kWave > n) {                       // no key beyond the head's end
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (t0 + e >= n) key[4 * j + e] = 0u;
+    }
+  }
+  if (center_thread) { sh.center[0] = key[0]; sh.center[1] = ~float_key(ev[0][0]); }
+  lds_barrier();
+  const uint32_t center0 = sh.center[0], center1 = sh.center[1];
+
+  // Step 1: the pool.  Then key[] turns into the residual keys of its members (smaller residual, larger
+  // key), 0 elsewhere, and Step 3: the n_approx tokens of lowest residual in it lose their value.  One
+  // copy of the selection's code for both: the instruction cache is filled once.
+  uint64_t in_pool = 0, in_apx = 0;                            // bit i: slot i
+#pragma unroll 1
+  for (int step = 0; step < 2; ++step) {
+    const int k = step == 0 ? p.n_pool : p.n_approx;
+    if (k == 0) break;
+    const Threshold t = head_select(key, k, step == 0 ? center0 : center1, sh);
+    uint32_t bits[2] = {0u, 0u};
+    const int base = first_token();
+#pragma unroll
+    for (int i = 4 * J - 1; i >= 0; --i) {                     // shifting in from the last slot: compare and add-with-carry
+      const bool in = key[i] >= t.thr;
+      bits[i >> 5] = bits[i >> 5] + bits[i >> 5] + (in ? 1u : 0u);
+      if ((i & 3) == 0) __builtin_amdgcn_sched_barrier(0);
+    }
+    if (!t.all_equal) {                                        // uniform: some keys equal to the threshold stay out
+#pragma unroll
+      for (int i = 0; i < 4 * J; ++i)
+        if (key[i] == t.thr && (uint32_t)head_token(base, i) > t.tok) bits[i >> 5] &= ~(1u << (i & 31));
+    }
+    const uint64_t set = ((uint64_t)bits[1] << 32) | bits[0];
+    if (step == 1) { in_apx = set; break; }
+    in_pool = set;
+#pragma unroll
+    for (int i = 0; i < 4 * J; ++i) {
+      key[i] = (bits[i >> 5] >> (i & 31)) & 1u ? ~float_key(ev[i >> 2][i & 3]) : 0u;
+      if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  const uint64_t in_ret = in_pool & ~in_apx;
+  // ranks: members in earlier blocks, then the exclusive prefix inside the block
+  const uint64_t earlier_slots = ((uint64_t)1 << (4 * block0)) - 1u;
+  const int earlier = __popcll(in_ret & earlier_slots) + (__popcll(in_apx & earlier_slots) << 16);
+  int carry = 0;
+  if (block0 > 0) {                                            // uniform
+    int unused;
+    head_scan(earlier, sh.wsum[1], unused, carry);
+  }
+  const int n_retain = p.n_pool - p.n_approx;
+  uint8_t* tier = p.tier + (size_t)h * n;
+  int32_t* ir = p.idx_retain + (size_t)h * n_retain;
+  int32_t* ia = p.idx_approx + (size_t)h * p.n_approx;
+  const bool tier_words = ((reinterpret_cast<uintptr_t>(tier)) & 3u) == 0;
+  for (int b = block0; b < block1; ++b) {
+    const uint32_t ret4 = (uint32_t)(in_ret >> (4 * b)) & 15u, apx4 = (uint32_t)(in_apx >> (4 * b)) & 15u;
+    int before, total;
+    head_scan(__popc(ret4) + (__popc(apx4) << 16), sh.wsum[2], before, total);
+    // the part's own range of ranks, from the waves' totals
+    int first = 0, own = 0;
+    {
+      const int x = wave_incl_scan_dpp(lane < HW ? sh.wsum[2][lane] : 0);
+      first = wave0 ? __builtin_amdgcn_readlane(x, wave0 - 1) : 0;
+      own = __builtin_amdgcn_readlane(x, wave1 - 1) - first;
+    }
+    const int own_r = low16(own), own_a = high16(own);
+    const int base_r = low16(carry) + low16(first), base_a = high16(carry) + high16(first);
+    if (my_wave) {
+      const int t0 = b * kHeadBlock + (int)threadIdx.x * 4;
+      int at_r = low16(before) - low16(first), at_a = high16(before) - high16(first);
+      uint32_t word = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int t = t0 + e;
+        if ((ret4 >> e) & 1u) {
+          word |= (uint32_t)VECTOR_TIER_RETAIN << (8 * e);
+          sh.list[at_r] = t;
+          if (base_r + at_r < n_retain) ir[base_r + at_r] = t;
+          ++at_r;
+        } else if ((apx4 >> e) & 1u) {
+          word |= (uint32_t)VECTOR_TIER_APPROX << (8 * e);
+          sh.list[own_r + at_a] = t;
+          if (base_a + at_a < p.n_approx) ia[base_a + at_a] = t;
+          ++at_a;
+        }
+      }
+      if (tier_words && t0 + 4 <= n) {
+        *reinterpret_cast<uint32_t*>(tier + t0) = word;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (t0 + e < n) tier[t0 + e] = (uint8_t)(word >> (8 * e));
+      }
+    }
+    carry += total;
+    lds_barrier();                                           // the list is whole
+    if (p.g.k) {
+      // rows of the part: retained keys, retained values, approximated keys; each set goes to consecutive rows
+      const GatherParams& g = p.g;
+      const int pieces = g.row_bytes / 16, log_pieces = 31 - __clz(pieces);
+      const int64_t hs = g.hps ? h / g.hps : 0, hh = g.hps ? h % g.hps : h;
+      const unsigned char* k_head = g.k + hs * g.k_sb + hh * g.k_sh;
+      const unsigned char* v_head = g.v + hs * g.v_sb + hh * g.v_sh;
+      unsigned char* k_ret = g.k_ret + ((size_t)h * g.cap_retain + base_r) * g.row_bytes;
+      unsigned char* v_ret = g.v_ret + ((size_t)h * g.cap_retain + base_r) * g.row_bytes;
+      unsigned char* k_apx = g.k_apx + ((size_t)h * p.n_approx + base_a) * g.row_bytes;
+      const int items = (2 * own_r + own_a) << log_pieces;
+      constexpr int U = 4;
+      for (int i0 = threadIdx.x; i0 < items; i0 += HT * U) {
+        u32x4 x[U];
+        unsigned char* to[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = min(i0 + u * HT, items - 1);
+          const int row = i >> log_pieces, piece = i & (pieces - 1);
+          const bool is_v = row >= own_r && row < 2 * own_r, is_a = row >= 2 * own_r;
+          const int t = sh.list[is_v || is_a ? row - own_r : row];
+          const unsigned char* from = (is_v ? v_head + (int64_t)t * g.v_st : k_head + (int64_t)t * g.k_st) + piece * 16;
+          to[u] = (is_v ? v_ret + (size_t)(row - own_r) * g.row_bytes
+                        : (is_a ? k_apx + (size_t)(row - 2 * own_r) * g.row_bytes : k_ret + (size_t)row * g.row_bytes)) + piece * 16;
+          x[u] = *reinterpret_cast<const u32x4*>(from);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (i0 + u * HT < items) *reinterpret_cast<u32x4*>(to[u]) = x[u];
+      }
+    }
+    lds_barrier();                                           // the list may be written again
+  }
+}
+
+// Workgroups per head: as many as fill the chip once; blocks are cut into runs of waves, or grouped
+void head_parts(int seq_len, int n_heads, HeadParams& p, unsigned& parts) {
+  const int n_blocks = (seq_len + kHeadBlock - 1) / kHeadBlock;
+  const int want = n_heads >= 256 ? 1 : 256 / n_heads;
+  p.sub_parts = 1;
+  p.blocks_per_part = 1;
+  if (want >= n_blocks) {
+    p.sub_parts = want / n_blocks;
+    // a part of fewer than 256 tokens per wave has nothing to share out
+    const int tokens = seq_len < kHeadBlock ? seq_len : kHeadBlock, most = (tokens + 255) / 256;
+    if (p.sub_parts > most) p.sub_parts = most;
+  } else {
+    p.blocks_per_part = (n_blocks + want - 1) / want;
+  }
+  parts = (unsigned)((n_blocks + p.blocks_per_part - 1) / p.blocks_per_part * p.sub_parts);
+}
+
+template <bool POOL, bool RAGGED>
+void (*head_kernel(int n_blocks))(HeadParams) {
+  if (n_blocks <= 1) return route_head_kernel<1, POOL, RAGGED>;
+  if (n_blocks <= 2) return route_head_kernel<2, POOL, RAGGED>;
+  if (n_blocks <= 4) return route_head_kernel<4, POOL, RAGGED>;
+  if (n_blocks <= 8) return route_head_kernel<8, POOL, RAGGED>;
+  return route_head_kernel<12, POOL, RAGGED>;
+}
+
+HeadParams head_params(const float* mass, const float* score_in, float* score_out, const float* eps, int n, int n_prefix, int pool_kernel,
+                       int pool_mode, int n_pool, int n_approx, uint8_t* tier, int32_t* idx_retain, int32_t* idx_approx) {
+  HeadParams p;
+  p.src = mass ? mass : score_in; p.score = score_out; p.eps = eps;
+  p.n = n; p.n_prefix = n_prefix; p.half = pool_kernel / 2; p.take_max = pool_mode == VECTOR_POOL_MAX;
+  p.kernel = (float)pool_kernel; p.inv_kernel = 1.0f / (float)pool_kernel;
+  p.n_pool = n_pool; p.n_approx = n_approx;
+  p.tier = tier; p.idx_retain = idx_retain; p.idx_approx = idx_approx;
+  p.g = GatherParams{};
+  p.seq_table = nullptr; p.seq_hps = 0;
+  return p;
+}
+
+}  // namespace
+
+bool route_head_fits(int seq_len) { return seq_len <= kMaxBlocks * kHeadBlock; }
+bool route_head_pools(int pool_kernel) { return pool_kernel / 2 <= 4; }
+
+int launch_route_head(int n_kv_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx, uint8_t* tier,
+                      int32_t* idx_retain, int32_t* idx_approx, const HeadPool* pool, const PackedRows* rows, hipStream_t stream) {
+  if (n_pool < 1 || !route_head_fits(seq_len) || (pool && !route_head_pools(pool->kernel))) return VECTOR_ERR_ARG;
+  HeadParams p = head_params(pool ? pool->mass : nullptr, score, pool ? pool->score : nullptr, eps, seq_len, pool ? pool->n_prefix : seq_len,
+                             pool ? pool->kernel : 1, pool ? pool->mode : VECTOR_POOL_AVG, n_pool, n_approx, tier, idx_retain, idx_approx);
+  if (rows)
+    p.g = gather_params(*rows->shape, rows->k, rows->v, idx_retain, idx_approx, n_pool - n_approx, n_approx, rows->k_ret, rows->v_ret,
+                        rows->k_apx, rows->cap_retain, rows->stack);
+  unsigned parts;
+  head_parts(seq_len, n_kv_heads, p, parts);
+  const int n_blocks = (seq_len + kHeadBlock - 1) / kHeadBlock;
+  void (*k)(HeadParams) = pool ? head_kernel<true, false>(n_blocks) : head_kernel<false, false>(n_blocks);
+  VEC_LAUNCH(K_ROUTE, k, dim3(parts, n_kv_heads), dim3(HT), 0, stream, p);
+  VEC_HIP(hipGetLastError());
+  return VECTOR_OK;
+}
+
+size_t route_head_table_bytes(int count) { return align_up(sizeof(HeadParams) * count, 256); }
+
+int launch_route_head_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, void* tables, hipStream_t stream) {
+  if (count < 1 || count > kMaxRaggedSeqs || !route_head_pools(s.pool_kernel)) return VECTOR_ERR_ARG;
+  HeadParams host[kMaxRaggedSeqs];
+  unsigned most = 0;
+  int blocks = 1;
+  for (int b = 0; b < count; ++b) {
+    const RaggedSeq& q = seqs[b];
+    const int n = q.shape.seq_len;
+    if (q.n_pool < 1 || !route_head_fits(n)) return VECTOR_ERR_ARG;
+    host[b] = head_params(score_mass(q.shape, q.score_ws), nullptr, q.score, q.eps, n, n - q.shape.window, s.pool_kernel, s.pool_mode, q.n_pool,
+                          q.n_approx, q.tier, q.idx_retain, q.idx_approx);
+    host[b].g = gather_params(q.shape, q.k, q.v, q.idx_retain, q.idx_approx, q.n_pool - q.n_approx, q.n_approx, q.k_ret, q.v_ret, q.k_apx,
+                              q.cap_retain, nullptr);
+    unsigned parts;
+    head_parts(n, count * s.n_kv_heads, host[b], parts);
+    if (parts > most) most = parts;
+    const int nb = (n + kHeadBlock - 1) / kHeadBlock;
+    if (nb > blocks) blocks = nb;
+  }
+  const int rc = upload_table(host, sizeof(HeadParams) * count, tables, stream);
+  if (rc != VECTOR_OK) return rc;
+  HeadParams lp = host[0];
+  lp.seq_table = reinterpret_cast<const HeadParams*>(tables);
+  lp.seq_hps = s.n_kv_heads;
+  void (*k)(HeadParams) = head_kernel<true, true>(blocks);
+  VEC_LAUNCH(K_ROUTE, k, dim3(most, (unsigned)count * s.n_kv_heads), dim3(HT), 0, stream, lp);
+  VEC_HIP(hipGetLastError());
+  return VECTOR_OK;
+}
+
+}  // namespace vec

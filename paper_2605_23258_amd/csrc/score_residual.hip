@@ -26,6 +26,8 @@
 // pass 2 walks a chunk backwards, towards what pass 1 left in that XCD's L2.
 // Template flags of pass 2: PROBE (repeat a tile's arithmetic on resident operands, for
 // measuring the contraction alone), ROPE (keys are un-rotated by position for the residual).
+#include <algorithm>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -1213,6 +1215,12 @@ size_t score_workspace_bytes(const vector_shape& s) {
   return b;
 }
 
+float* score_mass(const vector_shape& s, void* ws) {
+  const int rows_pad = ((s.n_q_heads / s.n_kv_heads) * s.window + 31) / 32 * 32;
+  return reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ws) +
+                                  align_up((size_t)s.n_kv_heads * ((s.seq_len + 255) / 256) * rows_pad * sizeof(float2), 256));
+}
+
 // One pair of passes over the keys for the query rows [q_row0, q_row0 + rows of `g`) of every KV
 // head (g: the shape with the group's query-head count).  accumulate: the column mass is added to
 // what earlier groups left.  The residual rides along when eps is given.  prepare_passes fills in
@@ -1246,11 +1254,8 @@ static int prepare_passes(const SeqStack* stack, const vector_shape& s, const ve
     p.hps = stack->heads_per_seq; p.k_sb = stack->k_stride_seq; p.v_sb = stack->v_stride_seq;
   }
   // workspace: partials (sized for all rows of a head, so any group fits), then the mass
-  const int rows_all_pad = (rows_all + 31) / 32 * 32;
-  unsigned char* w8 = reinterpret_cast<unsigned char*>(ws);
-  p.part = reinterpret_cast<float2*>(w8);
-  w8 += align_up((size_t)s.n_kv_heads * ((s.seq_len + 255) / 256) * rows_all_pad * sizeof(float2), 256);
-  p.mass = reinterpret_cast<float*>(w8);
+  p.part = reinterpret_cast<float2*>(ws);
+  p.mass = score_mass(s, ws);
   L.rp = RopeParams{};
   L.use_rope = rope != nullptr && L.do_res;                // the scores use the keys as cached
   if (L.use_rope) L.rp = *rope;
@@ -1321,7 +1326,7 @@ static int heads_per_group(const vector_shape& s, bool do_res) {
 // score workspace: one pair of passes for all of them, then one pooling launch.
 template <typename T, int D>
 static int run_score_residual_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, const void* W, void* tables,
-                                     hipStream_t stream, const RopeParams* rope) {
+                                     hipStream_t stream, const RopeParams* rope, bool leave_mass) {
   if (count < 1 || count > kMaxRaggedSeqs) return VECTOR_ERR_ARG;
   PassParams host[kMaxRaggedSeqs];
   PassLaunch first;
@@ -1330,7 +1335,7 @@ static int run_score_residual_ragged(const vector_shape& s, const RaggedSeq* seq
     vector_shape t = seqs[b].shape;
     if (heads_per_group<T, D>(t, true) != t.n_q_heads / t.n_kv_heads) return VECTOR_ERR_SHAPE;
     PassLaunch L;
-    float4* range = reinterpret_cast<float4*>(route_mass_range(seqs[b].route_ws, t.n_kv_heads));
+    float4* range = leave_mass ? nullptr : reinterpret_cast<float4*>(route_mass_range(seqs[b].route_ws, t.n_kv_heads));
     const QueryLse ql = {seqs[b].lse, seqs[b].lse_stride_head};
     const int rc = prepare_passes<T, D>(nullptr, t, t, 0, false, seqs[b].q, seqs[b].k, seqs[b].v, W, true, seqs[b].eps, seqs[b].score_ws,
                                         rope, seqs[b].lse ? &ql : nullptr, range, L);
@@ -1349,6 +1354,7 @@ static int run_score_residual_ragged(const vector_shape& s, const RaggedSeq* seq
   lp.seq_hps = s.n_kv_heads;
   const unsigned heads = (unsigned)count * s.n_kv_heads;
   if ((rc = launch_passes<T, D, true>(lp, first, dim3(g1, heads), dim3(g2, heads), stream)) != VECTOR_OK) return rc;
+  if (leave_mass) return VECTOR_OK;
   // pooling + score-key buckets of every sequence
   PoolSeq pool[kMaxRaggedSeqs];
   for (int b = 0; b < count; ++b) {
@@ -1361,7 +1367,7 @@ static int run_score_residual_ragged(const vector_shape& s, const RaggedSeq* seq
 template <typename T, int D>
 static int run_score_residual(const SeqStack* stack, const vector_shape& s, const void* q, const void* k, const void* v, const void* W,
                               float* score, float* eps, void* ws, hipStream_t stream, const RopeParams* rope,
-                              void* route_ws, const QueryLse* lse) {
+                              void* route_ws, const QueryLse* lse, bool leave_mass) {
   const bool do_mass = score != nullptr;
   if (!do_mass) return run_passes<T, D>(stack, s, s, 0, false, q, k, v, W, false, eps, ws, stream, rope, nullptr, nullptr, nullptr, nullptr, nullptr);
   // The query heads of a KV head go through the two passes a group at a time; usually one group.
@@ -1380,6 +1386,7 @@ static int run_score_residual(const SeqStack* stack, const vector_shape& s, cons
                                     lse, range, &n_range, &mass, &n_prefix);
     if (rc != VECTOR_OK) return rc;
   }
+  if (leave_mass) return VECTOR_OK;
   return launch_pool_scores(mass, score, s.n_kv_heads, s.seq_len, n_prefix, s.pool_kernel, s.pool_mode, route_ws, n_range, stream);
 }
 
@@ -1409,13 +1416,13 @@ int launch_residual_probe(const vector_shape& s, const void* k, const void* v, c
 
 int launch_score_residual(const vector_shape& s, const void* q, const void* k, const void* v, const void* W,
                           float* score, float* eps, void* ws, hipStream_t stream, const RopeParams* rope,
-                          void* route_ws, const SeqStack* stack, const QueryLse* lse) {
+                          void* route_ws, const SeqStack* stack, const QueryLse* lse, bool leave_mass) {
   if (s.dtype == VECTOR_BF16) {
-    if (s.head_dim == 128) return run_score_residual<bf16_t, 128>(stack, s, q, k, v, W, score, eps, ws, stream, rope, route_ws, lse);
-    if (s.head_dim == 64) return run_score_residual<bf16_t, 64>(stack, s, q, k, v, W, score, eps, ws, stream, rope, route_ws, lse);
+    if (s.head_dim == 128) return run_score_residual<bf16_t, 128>(stack, s, q, k, v, W, score, eps, ws, stream, rope, route_ws, lse, leave_mass);
+    if (s.head_dim == 64) return run_score_residual<bf16_t, 64>(stack, s, q, k, v, W, score, eps, ws, stream, rope, route_ws, lse, leave_mass);
   } else if (s.dtype == VECTOR_F32) {
-    if (s.head_dim == 128) return run_score_residual<float, 128>(stack, s, q, k, v, W, score, eps, ws, stream, rope, route_ws, lse);
-    if (s.head_dim == 64) return run_score_residual<float, 64>(stack, s, q, k, v, W, score, eps, ws, stream, rope, route_ws, lse);
+    if (s.head_dim == 128) return run_score_residual<float, 128>(stack, s, q, k, v, W, score, eps, ws, stream, rope, route_ws, lse, leave_mass);
+    if (s.head_dim == 64) return run_score_residual<float, 64>(stack, s, q, k, v, W, score, eps, ws, stream, rope, route_ws, lse, leave_mass);
   } else {
     return VECTOR_ERR_DTYPE;
   }
@@ -1428,18 +1435,19 @@ bool score_heads_in_one_group(const vector_shape& s) {
   return s.head_dim == 128 ? heads_per_group<float, 128>(s, true) == G : heads_per_group<float, 64>(s, true) == G;
 }
 
+size_t score_ragged_table_bytes(int count) { return align_up(sizeof(PassParams) * count, 256); }
 size_t ragged_table_bytes(int count) {
-  return align_up(sizeof(PassParams) * count, 256) + route_ragged_table_bytes(count);
+  return score_ragged_table_bytes(count) + std::max(route_ragged_table_bytes(count), route_head_table_bytes(count));
 }
 
 int launch_score_residual_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, const void* W, void* tables,
-                                 hipStream_t stream, const RopeParams* rope) {
+                                 hipStream_t stream, const RopeParams* rope, bool leave_mass) {
   if (s.dtype == VECTOR_BF16) {
-    if (s.head_dim == 128) return run_score_residual_ragged<bf16_t, 128>(s, seqs, count, W, tables, stream, rope);
-    if (s.head_dim == 64) return run_score_residual_ragged<bf16_t, 64>(s, seqs, count, W, tables, stream, rope);
+    if (s.head_dim == 128) return run_score_residual_ragged<bf16_t, 128>(s, seqs, count, W, tables, stream, rope, leave_mass);
+    if (s.head_dim == 64) return run_score_residual_ragged<bf16_t, 64>(s, seqs, count, W, tables, stream, rope, leave_mass);
   } else if (s.dtype == VECTOR_F32) {
-    if (s.head_dim == 128) return run_score_residual_ragged<float, 128>(s, seqs, count, W, tables, stream, rope);
-    if (s.head_dim == 64) return run_score_residual_ragged<float, 64>(s, seqs, count, W, tables, stream, rope);
+    if (s.head_dim == 128) return run_score_residual_ragged<float, 128>(s, seqs, count, W, tables, stream, rope, leave_mass);
+    if (s.head_dim == 64) return run_score_residual_ragged<float, 64>(s, seqs, count, W, tables, stream, rope, leave_mass);
   } else {
     return VECTOR_ERR_DTYPE;
   }

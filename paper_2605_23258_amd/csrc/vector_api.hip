@@ -170,6 +170,14 @@ static int compress_impl(const vector_shape* s, const void* q_win, const void* k
   if ((rc = check_ws(ws, ws_bytes, vector_compress_workspace_bytes(s, n_pool, n_approx)))) return rc;
   hipStream_t st = (hipStream_t)stream;
   void* route_ws = reinterpret_cast<unsigned char*>(ws) + (score_ws + 255) / 256 * 256;
+  if (n_pool > 0 && vec::route_head_fits(s->seq_len)) {      // pooling, routing and compaction in one launch
+    const bool pools = vec::route_head_pools(s->pool_kernel);
+    if ((rc = vec::launch_score_residual(*s, q_win, k, v, W, score, eps, ws, st, rope, nullptr, stack, lse, pools))) return rc;
+    const vec::HeadPool pool = {vec::score_mass(*s, ws), score, s->seq_len - s->window, s->pool_kernel, s->pool_mode};
+    const vec::PackedRows rows = {s, k, v, k_ret, v_ret, k_apx, cap_retain, stack};
+    return vec::launch_route_head(s->n_kv_heads, s->seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx,
+                                  pools ? &pool : nullptr, &rows, st);
+  }
   // the scorer's pooling launch also builds the routing's buckets of score keys
   void* buckets = n_pool > 0 ? route_ws : nullptr;
   if ((rc = vec::launch_score_residual(*s, q_win, k, v, W, score, eps, ws, st, rope, buckets, stack, lse))) return rc;
@@ -364,10 +372,13 @@ static int compress_batch_impl(const vector_shape* s, const vector_batch* bt, co
         rp_part = *rope;
         if (rope->positions) rp_part.positions = rope->positions + seqs_tok0;
       }
-      if ((rc = vec::launch_score_residual_ragged(*s, seqs, part.count, W, tables, st, rope ? &rp_part : nullptr))) return rc;
-      unsigned char* route_tables = reinterpret_cast<unsigned char*>(tables) + vec::ragged_table_bytes(part.count) -
-                                    vec::route_ragged_table_bytes(part.count);
-      if ((rc = vec::launch_route_compact_ragged(*s, seqs, part.count, route_tables, st))) return rc;
+      bool one_launch = vec::route_head_pools(s->pool_kernel);
+      for (int i = 0; i < part.count; ++i) one_launch = one_launch && vec::route_head_fits(seqs[i].shape.seq_len);
+      if ((rc = vec::launch_score_residual_ragged(*s, seqs, part.count, W, tables, st, rope ? &rp_part : nullptr, one_launch))) return rc;
+      unsigned char* route_tables = reinterpret_cast<unsigned char*>(tables) + vec::score_ragged_table_bytes(part.count);
+      rc = one_launch ? vec::launch_route_head_ragged(*s, seqs, part.count, route_tables, st)
+                      : vec::launch_route_compact_ragged(*s, seqs, part.count, route_tables, st);
+      if (rc) return rc;
       b += part.count;
       continue;
     }
