@@ -1066,7 +1066,7 @@ void fill_bucket_params(BucketParams& bp, const RouteLayout& L, void* route_ws) 
 size_t route_workspace_bytes(int n_kv_heads, int seq_len, int n_pool) { return route_layout(n_kv_heads, seq_len, n_pool).total; }
 
 // the scorer's second pass runs at least 512 tokens per workgroup
-int route_mass_range_slots(int seq_len) { return (seq_len + 511) / 512; }
+int route_mass_range_slots(int seq_len) { return seq_len < 256 ? seq_len : 256; }     // the scorer's second pass has no more workgroups per head
 void* route_mass_range(void* route_ws, int n_kv_heads) {
   return reinterpret_cast<unsigned char*>(route_ws) + route_layout(n_kv_heads, 1, 0).off_range;
 }

@@ -1,0 +1,10 @@
+// The scoring and residual kernels for bf16 keys of 64 dims (a file of their own: they compile in parallel).
+#define VEC_DEFINE_PASSES
+#include "score_stream.hpp"
+
+namespace vec {
+
+template int launch_passes<bf16_t, 64>(const PassParams&, const PassLaunch&, bool, dim3, dim3, hipStream_t);
+template int launch_probe<bf16_t, 64>(const PassLaunch&, hipStream_t);
+
+}  // namespace vec

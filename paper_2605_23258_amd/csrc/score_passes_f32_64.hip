@@ -1,0 +1,9 @@
+// The scoring and residual kernels for fp32 keys of 64 dims (a file of their own: they compile in parallel).
+#define VEC_DEFINE_PASSES
+#include "score_stream.hpp"
+
+namespace vec {
+
+template int launch_passes<float, 64>(const PassParams&, const PassLaunch&, bool, dim3, dim3, hipStream_t);
+
+}  // namespace vec
