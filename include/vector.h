@@ -143,7 +143,7 @@ VECTOR_API int vector_route(int32_t n_kv_heads, int32_t seq_len, const float* sc
 /* vector_route for callers that cannot allocate device memory or size a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs
  * and errors as vector_route, without ws: the routing kernels' scratch is a device array of
- * VECTOR_ROUTE_STATIC_SCRATCH_BYTES that lives inside the library (one copy per GPU, held until the
+ * VECTOR_ROUTE_STATIC_SCRATCH_BYTES and a half that lives inside the library (one copy per GPU, held until the
  * process ends; its address is looked up on the first call on a device, on the device that is
  * current then).  The call allocates and frees nothing.  VECTOR_ERR_WORKSPACE when
  * the shape needs more scratch than the array holds (what vector_route would ask its caller for;

@@ -80,7 +80,7 @@ struct RaggedSeq {
   const float* lse;          // the sequence's window rows' log-sum-exp, or null
   int64_t lse_stride_head;
 };
-struct PoolSeq { const float* mass; float* score; int seq_len, n_prefix; void* route_ws; int n_range; };
+struct PoolSeq { const float* mass; float* score; const float* eps; int seq_len, n_prefix; void* route_ws; int n_range; };
 size_t ragged_table_bytes(int count);
 size_t score_ragged_table_bytes(int count);     // the scorer's part of it, at its start
 // whether the G * w query rows of a KV head go through the two passes at once (a ragged launch needs that)
@@ -113,20 +113,22 @@ size_t diversity_workspace_bytes(const vector_shape& s);
 int launch_key_diversity(const vector_shape& s, const void* k, float* score, void* ws, hipStream_t stream);
 
 constexpr int kRouteMaxSeqLen = 1 << 20;      // per-chunk digit tables carry 16-bit counts: at most 32 chunks of 32768 tokens
-size_t route_workspace_bytes(int n_kv_heads, int seq_len, int n_pool);
+size_t route_workspace_bytes(int n_kv_heads, int seq_len);
 // Where, inside a routing workspace, the scorer's second pass leaves statistics of the attention
 // mass: per head n_range float4 (count, sum, sum of squares of log2 mass), one per workgroup of that
-// launch (n_range <= route_mass_range_slots(seq_len)).
+// launch (n_range <= route_mass_range_slots(n_kv_heads, seq_len)).
 void* route_mass_range(void* route_ws, int n_kv_heads);
-int route_mass_range_slots(int seq_len);
+int route_mass_range_slots(int n_kv_heads, int seq_len);
 // average pooling of the attention mass into the score; with a routing workspace (route_ws, sized by
-// route_workspace_bytes) also the routing's buckets of score keys (then launch_route is told so and
-// skips its own bucket launch)
+// route_workspace_bytes) also the routing's buckets of score keys, which carry the residuals eps along
+// (then launch_route is told so and skips its own bucket launch)
 // n_range: records per head the scorer left at route_mass_range (0: none, the buckets go by the keys' top bits)
-int launch_pool_scores(const float* mass, float* score, int n_kv_heads, int seq_len, int n_prefix, int pool_kernel, int pool_mode,
+int launch_pool_scores(const float* mass, float* score, const float* eps, int n_kv_heads, int seq_len, int n_prefix, int pool_kernel, int pool_mode,
                        void* route_ws, int n_range, hipStream_t stream);
+struct PackedRows;
+// rows: null, or the packed cache to fill as well
 int launch_route(int n_kv_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx,
-                 uint8_t* tier, int32_t* idx_retain, int32_t* idx_approx, void* ws, bool have_buckets, hipStream_t stream);
+                 uint8_t* tier, int32_t* idx_retain, int32_t* idx_approx, void* ws, bool have_buckets, const PackedRows* rows, hipStream_t stream);
 
 int launch_compact(const vector_shape& s, const void* k, const void* v, const int32_t* idx_retain,
                    const int32_t* idx_approx, int n_retain, int n_approx, void* k_ret, void* v_ret, void* k_apx,

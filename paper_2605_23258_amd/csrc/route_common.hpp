@@ -116,7 +116,6 @@ __device__ __forceinline__ float pool_mean(float sum, float kernel, float inv_ke
   return fmaf(fmaf(-q, kernel, sum), inv_kernel, q);
 }
 
-struct GatherParams;
 struct GatherParams {
   const unsigned char* k; const unsigned char* v;
   int64_t k_sh, k_st, v_sh, v_st;          // byte strides
@@ -152,6 +151,167 @@ inline GatherParams gather_params(const vector_shape& s, const void* k, const vo
   p.k_apx = reinterpret_cast<unsigned char*>(k_apx);
   p.seq_table = nullptr; p.seq_hps = 0;
   return p;
+}
+
+// ---------------------------------------------------------------------------
+// workgroups of 512 threads: scans, histogram picks, emission and row copies
+// ---------------------------------------------------------------------------
+constexpr int HT = 512;                         // threads of a workgroup
+constexpr int HW = HT / kWave;
+constexpr int kHeadBlock = HT * 4;              // tokens per block: four consecutive ones per thread
+constexpr int kHeadBins = 2048;
+constexpr int kRankCap = 256;                   // candidates ranked by comparison
+
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_u;   // 16-byte access at any element
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+// Workgroup barrier for data in LDS alone: global loads in flight (the residuals, while the scores are worked
+// on) and stores (score, tiers, lists) are not waited for.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// packed pairs of counts: retained in the low half, approximated in the high one
+__device__ __forceinline__ int low16(int x) { return x & 0xffff; }
+__device__ __forceinline__ int high16(int x) { return (int)((uint32_t)x >> 16); }
+
+// sum of a float over the waves' entries, the same bits in every lane
+__device__ __forceinline__ float sum_of_waves(const float* row, int lane) {
+  static_assert(HW == 8, "eight waves");
+  float x = row[lane & 7];
+  x += dpp_take_f<0x111, 0xf>(0.f, x);
+  x += dpp_take_f<0x112, 0xf>(0.f, x);
+  x += dpp_take_f<0x114, 0xf>(0.f, x);
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 7));
+}
+
+// exclusive prefix over the workgroup's threads of a packed pair of counts, and the total; row: [HW]
+__device__ __forceinline__ void head_scan(int v, int* row, int& before, int& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int incl = wave_incl_scan_dpp(v);
+  if (lane == 63) row[wave] = incl;
+  lds_barrier();
+  int x = row[lane & 7];                         // every lane one wave's total
+  x += dpp_take<0x111, 0xf>(x);
+  x += dpp_take<0x112, 0xf>(x);
+  x += dpp_take<0x114, 0xf>(x);
+  const int upto = wave ? __builtin_amdgcn_readlane(x, wave - 1) : 0;
+  total = __builtin_amdgcn_readlane(x, 7);
+  before = upto + incl - v;
+}
+
+__device__ __forceinline__ void clear_bins(int* hist) {
+  static_assert(kHeadBins == 4 * HT, "four buckets per thread");
+  *reinterpret_cast<int4*>(hist + 4 * threadIdx.x) = make_int4(0, 0, 0, 0);
+}
+
+// histogram counts -> the bucket with #(keys above it) < k <= #(keys in or above it); row: [HW], pick: [3]
+__device__ __forceinline__ void pick_bin(const int* hist, int* row, int* pick, int k, int& d, int& above, int& count) {
+  const int lo = kHeadBins - 4 - 4 * (int)threadIdx.x;
+  const int4 c = *reinterpret_cast<const int4*>(hist + lo);           // buckets lo .. lo + 3
+  int before, total;
+  head_scan(c.x + c.y + c.z + c.w, row, before, total);
+  if (before < k && k <= before + c.x + c.y + c.z + c.w) {
+    int b = lo + 3, in = c.w;
+    if (k > before + in) { before += in; in = c.z; --b; }
+    if (b == lo + 2 && k > before + in) { before += in; in = c.y; --b; }
+    if (b == lo + 1 && k > before + in) { before += in; in = c.x; --b; }
+    pick[0] = b; pick[1] = before; pick[2] = in;
+  }
+  lds_barrier();
+  d = pick[0]; above = pick[1]; count = pick[2];
+}
+
+// A sample's count, sum and sum of squares (in units of 4096 keys about the center) -> where to lay the buckets
+__device__ __forceinline__ DigitMap digit_map_about(uint32_t center, float cnt, float s1, float s2) {
+  DigitMap map = {0u, 21};
+  if (cnt >= 32.f) {
+    const float inv = __builtin_amdgcn_rcpf(cnt), mu = s1 * inv;
+    const float half = 4.f * __builtin_amdgcn_sqrtf(fmaxf(s2 * inv - mu * mu, 0.f)) + 32.f;
+    const float mid = (float)(center >> 12) + mu;
+    map = digit_map_for_keys((uint32_t)fmaxf(mid - half, 0.f) << 12, (uint32_t)fminf(mid + half, 1048575.f) << 12);
+  }
+  return map;
+}
+// the keys of bucket d: [lo, lo + span]; no key is 0
+__device__ __forceinline__ void bucket_range(const DigitMap& map, int d, uint32_t& lo, uint32_t& span) {
+  if (map.plain()) {
+    lo = (uint32_t)d << 21;
+    span = (1u << 21) - 1u;
+  } else {
+    lo = d == 0 ? 0u : (map.lowq + (uint32_t)d) << map.shift;
+    const uint32_t hi = d == 2047 ? 0xffffffffu : ((map.lowq + (uint32_t)d + 1u) << map.shift) - 1u;
+    span = hi - lo;
+  }
+  if (lo == 0u) { lo = 1u; span -= 1u; }
+}
+
+// Where a head's results go.
+struct EmitTarget {
+  uint8_t* tier; int32_t* ir; int32_t* ia;       // of the head
+  int n, n_retain, n_approx;
+};
+// Tiers and list entries of a thread's four tokens t0 .. t0 + 3 (bit e of ret4 / apx4: token t0 + e): at_r, at_a: the
+// thread's first places among the own_r retained and the approximated tokens that the workgroup emits at the
+// ranks base_r and base_a; list gets their tokens, retained first.
+__device__ __forceinline__ void emit_tokens(const EmitTarget& o, int t0, uint32_t ret4, uint32_t apx4, int at_r, int at_a, int own_r, int base_r,
+                                            int base_a, int* list) {
+  uint32_t word = 0u;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int t = t0 + e;
+    if ((ret4 >> e) & 1u) {
+      word |= (uint32_t)VECTOR_TIER_RETAIN << (8 * e);
+      list[at_r] = t;
+      if (base_r + at_r < o.n_retain) o.ir[base_r + at_r] = t;
+      ++at_r;
+    } else if ((apx4 >> e) & 1u) {
+      word |= (uint32_t)VECTOR_TIER_APPROX << (8 * e);
+      list[own_r + at_a] = t;
+      if (base_a + at_a < o.n_approx) o.ia[base_a + at_a] = t;
+      ++at_a;
+    }
+  }
+  if ((reinterpret_cast<uintptr_t>(o.tier) & 3u) == 0 && t0 + 4 <= o.n) {
+    *reinterpret_cast<uint32_t*>(o.tier + t0) = word;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (t0 + e < o.n) o.tier[t0 + e] = (uint8_t)(word >> (8 * e));
+  }
+}
+// Their rows into the packed cache: retained keys, retained values, approximated keys; each set goes to
+// consecutive rows.
+__device__ __forceinline__ void copy_rows(const GatherParams& g, int h, int n_approx, const int* list, int own_r, int own_a, int base_r, int base_a) {
+  const int pieces = g.row_bytes / 16, log_pieces = 31 - __clz(pieces);
+  const int64_t hs = g.hps ? h / g.hps : 0, hh = g.hps ? h % g.hps : h;
+  const unsigned char* k_head = g.k + hs * g.k_sb + hh * g.k_sh;
+  const unsigned char* v_head = g.v + hs * g.v_sb + hh * g.v_sh;
+  unsigned char* k_ret = g.k_ret + ((size_t)h * g.cap_retain + base_r) * g.row_bytes;
+  unsigned char* v_ret = g.v_ret + ((size_t)h * g.cap_retain + base_r) * g.row_bytes;
+  unsigned char* k_apx = g.k_apx + ((size_t)h * n_approx + base_a) * g.row_bytes;
+  const int items = (2 * own_r + own_a) << log_pieces;
+  constexpr int U = 4;
+  for (int i0 = threadIdx.x; i0 < items; i0 += HT * U) {
+    u32x4 x[U];
+    unsigned char* to[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + u * HT, items - 1);
+      const int row = i >> log_pieces, piece = i & (pieces - 1);
+      const bool is_v = row >= own_r && row < 2 * own_r, is_a = row >= 2 * own_r;
+      const int t = list[is_v || is_a ? row - own_r : row];
+      const unsigned char* from = (is_v ? v_head + (int64_t)t * g.v_st : k_head + (int64_t)t * g.k_st) + piece * 16;
+      to[u] = (is_v ? v_ret + (size_t)(row - own_r) * g.row_bytes
+                    : (is_a ? k_apx + (size_t)(row - 2 * own_r) * g.row_bytes : k_ret + (size_t)row * g.row_bytes)) + piece * 16;
+      x[u] = *reinterpret_cast<const u32x4*>(from);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * HT < items) *reinterpret_cast<u32x4*>(to[u]) = x[u];
+  }
 }
 
 }  // namespace

@@ -1,47 +1,35 @@
-// Three-way routing (Section 3.2, Steps 1 and 3) and compaction into the packed cache.
+// Three-way routing (Section 3.2, Steps 1 and 3) and compaction into the packed cache, for heads longer than
+// route_head.hip takes.  Two launches, synchronised by the kernel boundary only:
 //
-// Both selections of a head (the n_pool highest scores; inside that pool the n_approx lowest
-// residuals) are radix selects on order-preserving 32-bit keys with digits of 11, 11 and 10 bits,
-// spread over the whole chip and synchronised by kernel boundaries only:
+//   route_bucket_kernel  grid (chunk, head).  Groups a chunk's (score key, token, residual key) entries by the
+//                        leading digit of the score key, highest digit first, next to the table
+//                        D[b] = #keys of the chunk with digit >= b.  The POOL variant first forms
+//                        the score itself, the pooling of the attention mass (Step 1's base scorer).
+//   route_list_kernel    grid (part, head).  Every workgroup sums the D tables of its head: the
+//                        leading digit of the pool's threshold is the bin where the sum crosses n_pool.
+//                        What lies in front of that bin in the chunks' lists is in the pool, what lies in
+//                        it (a few hundred entries) is ranked; then the residual keys of the pool, which
+//                        the lists carry along, give the second threshold.  All workgroups of a head
+//                        find the same two thresholds; each then emits its own part of the tokens (tiers,
+//                        ascending index lists) and copies their rows.
 //
-//   route_bucket_kernel  grid (chunk, head).  Counts the leading digit of a chunk's score keys and
-//                        writes the chunk's (key, token) pairs grouped by that digit, highest digit
-//                        first, next to the table D[b] = #keys of the chunk with digit >= b.  The
-//                        POOL variant first forms the score itself, the average pooling of the
-//                        attention mass (Step 1's base scorer), so the scorer's last kernel already
-//                        hands the routing its buckets.
-//   route_pool_kernel    grid (chunk, head).  Every workgroup sums the D tables of its head: the
-//                        leading digit of the threshold is the bin where the sum crosses n_pool,
-//                        and the keys that share it are one contiguous piece of every chunk's
-//                        bucket list.  Those few keys go to LDS and the select finishes on them (all
-//                        workgroups of a head reach the same threshold).  Then the ordered pass
-//                        over the workgroup's own chunk: tiers, the pool list (token index and
-//                        residual key, in token order) and the D table of the chunk's residual keys.
-//   route_split_kernel   grid (slice, head).  The same select on the residual keys of the pool
-//                        list (read whole: a pool is a fraction of the sequence), then the ordered
-//                        pass over a slice of the list: ascending idx_approx / idx_retain, and the
-//                        approximated tier.
+// A launch costs 4 us before it does anything and the first reads of a workgroup depend on each other, so
+// what the workgroups of a head repeat (the pool's residuals, a tenth of the tokens) is cheaper than another launch to
+// share it: with launches for the pool, for its split and for the rows, the routing of 32768 tokens x 8 heads took
+// 40 us (now 9 + 21), of 131072 tokens 65 us (17 + 41, rows 16 of them), of 49157 given scores 36 us (8 + 20).
+// Bound: latency of dependent reads and barriers; the rows run at 5 TB/s.
 //
 // Every slot of an output comes from an ordered prefix sum (ties go to the lower token index);
 // atomics only feed LDS histograms and the order inside a bucket, which no result depends on.
 // No workgroup waits for another inside a kernel.
 //
 // gather_rows_kernel: row gather k_ret / v_ret / k_apx by the index lists.
+#include <algorithm>
 #include <cstring>
 
 #include "common.hpp"
 #include "launch.hpp"
 #include "route_common.hpp"
-
-#ifdef VEC_ROUTE_TRACE      // tuning builds only: time stamps of workgroup (0, 0)
-__device__ long long g_route_trace[32];
-#define VEC_TRACE(slot) do { if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) g_route_trace[slot] = wall_clock64(); } while (0)
-extern "C" __attribute__((visibility("default"))) int vector_debug_route_trace(long long* host_out) {
-  return hipMemcpyFromSymbol(host_out, HIP_SYMBOL(g_route_trace), sizeof(long long) * 32) == hipSuccess ? 0 : -5;
-}
-#else
-#define VEC_TRACE(slot) do { } while (0)
-#endif
 
 namespace vec {
 
@@ -53,12 +41,6 @@ constexpr int EPT = 4;                    // consecutive elements per thread and
 constexpr int BT = 512;                   // threads of the bucket kernel
 constexpr int kBucketTile = BT * EPT;
 constexpr int kStageTokens = 4096;        // a chunk's bucket list is put together in LDS up to this length
-constexpr int ST = 256;                   // threads of a selecting workgroup: one wave per SIMD
-constexpr int SW = ST / kWave;
-constexpr int kTile = ST * EPT;           // elements per tile of a selecting workgroup
-constexpr int kBatch = 8;                 // tiles whose loads are in flight together
-constexpr int kCandCap = 12288;           // candidates (keys sharing the threshold's leading digit) kept in LDS
-constexpr int kWaveCand = kCandCap / SW;  // each wave keeps its own: no shared counter
 constexpr int kMinChunk = 2048;           // tokens per chunk: doubled until a head has at most kMaxChunks
 constexpr int kMaxChunks = 32;
 
@@ -162,6 +144,8 @@ struct BucketParams {
   uint16_t* table;        // [H, C, kTableStride] or null (POOL only: pooling alone)
   uint32_t* bkey;         // [H, n]: chunk c owns [c * chunk_tokens, ...), keys grouped by digit, highest first
   int32_t* bpos;          // [H, n]: the token each key belongs to
+  uint32_t* beps;         // [H, n]: and its residual key (smaller residual, larger key)
+  const float* eps;       // [H, n] residuals
   int n, n_prefix, kernel, chunk_tokens, n_chunks;
   float inv_kernel;       // POOL: 1 / kernel
   int take_max;           // POOL: the window's largest mass instead of its sum over the kernel size
@@ -175,15 +159,16 @@ struct BucketParams {
 
 template <bool POOL, bool RAGGED = false>
 __global__ __launch_bounds__(BT) void route_bucket_kernel(BucketParams p) {
-  int h = blockIdx.y;
+  int chunk, h;
+  xcd_chunk_head(chunk, h);
   take_sequence<RAGGED>(p, h);
-  if (RAGGED && (int)blockIdx.x >= p.n_chunks) return;
+  if (chunk >= p.n_chunks) return;
   __shared__ int hist[kBins];
   __shared__ int row[BT / kWave];
   __shared__ uint32_t sample[BT / kWave][4];
   __shared__ __align__(16) uint32_t stage_key[kStageTokens];
   __shared__ __align__(16) int32_t stage_pos[kStageTokens];
-  const int chunk = blockIdx.x;
+  __shared__ __align__(16) uint32_t stage_eps[kStageTokens];
   const int lane = threadIdx.x & 63;
   const bool do_buckets = p.table != nullptr;
   DigitMap map = {0u, 21};
@@ -273,7 +258,20 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(BucketParams p) {
       for (int j = 0; j < EPT; ++j) s[j] = t0 + j < end ? scores[t0 + j] : 0.f;
     }
   };
+  const float* eps = do_buckets ? p.eps + (size_t)h * p.n : nullptr;
+  const bool eps4 = vec4 && (reinterpret_cast<uintptr_t>(eps) & 15u) == 0;
+  auto load_eps = [&](int t0, float (&e)[EPT]) {
+    if (eps4 && t0 + EPT <= end) {
+      const float4 x = *reinterpret_cast<const float4*>(eps + t0);
+      e[0] = x.x; e[1] = x.y; e[2] = x.z; e[3] = x.w;
+    } else {
+#pragma unroll
+      for (int j = 0; j < EPT; ++j) e[j] = t0 + j < end ? eps[t0 + j] : 0.f;
+    }
+  };
   uint32_t key0[EPT];                            // the keys of the first tile stay in registers for the scatter
+  float eps0[EPT];                               // and its residuals, requested with the scores
+  if (do_buckets) load_eps(begin + (int)threadIdx.x * EPT, eps0);
   for (int tile = begin; tile < end; tile += kBucketTile) {        // uniform trip count: whole waves take part
     const int t0 = tile + (int)threadIdx.x * EPT;
     float s[EPT];
@@ -346,16 +344,19 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(BucketParams p) {
   // chunks scatter their entries straight to memory.
   uint32_t* bkey = p.bkey + (size_t)h * p.n + begin;
   int32_t* bpos = p.bpos + (size_t)h * p.n + begin;
+  uint32_t* beps = p.beps + (size_t)h * p.n + begin;
   const bool staged = p.chunk_tokens <= kStageTokens;
   for (int tile = begin; tile < end; tile += kBucketTile) {
     const int t0 = tile + (int)threadIdx.x * EPT;
     uint32_t key[EPT];
+    float ev[EPT];
     if (tile == begin) {
 #pragma unroll
-      for (int j = 0; j < EPT; ++j) key[j] = key0[j];
+      for (int j = 0; j < EPT; ++j) { key[j] = key0[j]; ev[j] = eps0[j]; }
     } else {                                     // later tiles: the scores this thread stored (or read) above
       float s[EPT];
       load_scores(t0, s);
+      load_eps(t0, ev);
 #pragma unroll
       for (int j = 0; j < EPT; ++j) key[j] = float_key(s[j]);
     }
@@ -364,8 +365,9 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(BucketParams p) {
       if (t0 + j < end) {
         const int slot = atomicAdd(&hist[map.digit(key[j])], 1);
         if (slot < end - begin) {                                                // always true: counted above
-          if (staged) { stage_key[slot] = key[j]; stage_pos[slot] = t0 + j; }
-          else { bkey[slot] = key[j]; bpos[slot] = t0 + j; }
+          const uint32_t ek = ~float_key(ev[j]);
+          if (staged) { stage_key[slot] = key[j]; stage_pos[slot] = t0 + j; stage_eps[slot] = ek; }
+          else { bkey[slot] = key[j]; bpos[slot] = t0 + j; beps[slot] = ek; }
         }
       }
     }
@@ -378,605 +380,428 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(BucketParams p) {
         if (i + 4 <= cnt) {
           *reinterpret_cast<uint4*>(bkey + i) = *reinterpret_cast<const uint4*>(stage_key + i);
           *reinterpret_cast<int4*>(bpos + i) = *reinterpret_cast<const int4*>(stage_pos + i);
+          *reinterpret_cast<uint4*>(beps + i) = *reinterpret_cast<const uint4*>(stage_eps + i);
         } else {
-          for (int j = i; j < cnt; ++j) { bkey[j] = stage_key[j]; bpos[j] = stage_pos[j]; }
+          for (int j = i; j < cnt; ++j) { bkey[j] = stage_key[j]; bpos[j] = stage_pos[j]; beps[j] = stage_eps[j]; }
         }
       }
     } else {
-      for (int i = threadIdx.x; i < cnt; i += BT) { bkey[i] = stage_key[i]; bpos[i] = stage_pos[i]; }
+      for (int i = threadIdx.x; i < cnt; i += BT) { bkey[i] = stage_key[i]; bpos[i] = stage_pos[i]; beps[i] = stage_eps[i]; }
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// radix select shared by the two selecting kernels
+// both selections, emission, rows
 // ---------------------------------------------------------------------------
-enum { ROW_PICK1 = 0, ROW_PICK2, ROW_GT, ROW_EQ, ROW_EMIT0, ROW_EMIT1, ROW_TABLE, ROW_COUNT };
-
-struct SelectShared {
-  __align__(16) int hist[3][kBins];      // digits of levels 1 and 2 of a select, and one for the caller; zeroed at the start
-  int row[ROW_COUNT][SW];                // per-wave terms of the workgroup-wide sums, one row per use
-  int pick[3][4];                        // per level: digit, #(digit above it), count of its bin (and the first level's group of eight bins)
-  int coarse[ST + 1];                    // first step of the leading digit: sums at every eighth bin
-  int seg_first[kMaxChunks], seg_count[kMaxChunks], seg_start[kMaxChunks];   // per chunk: where the keys with the chosen
-                                         // leading digit sit, how many, and how many in earlier chunks
-  int overflow;                          // a wave found more candidates than it can keep
-};
-
-__device__ __forceinline__ void select_shared_init(SelectShared& sh) {
-  int* h = &sh.hist[0][0];
-  for (int i = threadIdx.x; i < 3 * kBins; i += ST) h[i] = 0;
-  if (threadIdx.x == 0) sh.overflow = 0;
-}
-
-// Leading digit of the k-th largest key from the D tables of a head's chunks: summed over the
-// chunks, S[b] = #(digit >= b) falls from the key count at b = 0 to 0 at b = 2048, and the digit is
-// the one bin with S[b+1] < k <= S[b].  Two steps, because what this costs is load instructions:
-// thread t first sums only the entry at the low end of its eight bins (b = 2040 - 8t) over the
-// chunks; the entry above its bins is its neighbour's sum, and one thread finds k between the two.
-// Then one wave reads that thread's eight entries of every chunk (one 16-byte load per chunk and
-// lane) and sums them across lanes.  Every thread gets the digit, #(digit above it) and the count
-// of its bin.  prefetch() is called once the first loads are out, so that the caller's own first
-// loads travel with them.
-template <typename Prefetch>
-__device__ __forceinline__ void pick_leading_digit(const uint16_t* tables, int n_parts, int k, SelectShared& sh, Prefetch prefetch,
-                                                   int& digit, int& above, int& count) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lo = kBins - 8 - 8 * (int)threadIdx.x;
-  int s_lo = 0;
-  bool first = true;
-  constexpr int kInFlight = 16;                 // chunks requested together: one trip to memory for up to 16 of them
-  for (int c = 0; c < n_parts; c += kInFlight) {
-    uint16_t e[kInFlight];
-#pragma unroll
-    for (int u = 0; u < kInFlight; ++u) e[u] = tables[(size_t)min(c + u, n_parts - 1) * kTableStride + lo];
-    if (first) { prefetch(); first = false; }
-#pragma unroll
-    for (int u = 0; u < kInFlight; ++u)
-      if (c + u < n_parts) s_lo += (int)e[u];
-  }
-  sh.coarse[threadIdx.x + 1] = s_lo;            // coarse[t + 1] = S[2040 - 8t]; coarse[0] = S[2048] = 0
-  if (threadIdx.x == 0) { sh.coarse[0] = 0; sh.pick[0][3] = 0; }    // no bracket (k outside the counts): the second step still reads inside the tables
-  __syncthreads();
-  const int s_hi = sh.coarse[threadIdx.x];      // S at the bin above this thread's eight
-  if (s_hi < k && k <= s_lo) { sh.pick[0][3] = lo; sh.pick[0][1] = s_hi; }
-  __syncthreads();
-  if (wave == 0) {
-    const int at = sh.pick[0][3];
-    int S[9];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) S[j] = 0;
-    for (int c = lane; c < n_parts; c += kWave) {
-      const uint4 v = *reinterpret_cast<const uint4*>(tables + (size_t)c * kTableStride + at);
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { S[2 * q] += (int)(w[q] & 0xffffu); S[2 * q + 1] += (int)(w[q] >> 16); }
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) S[j] += __shfl_xor(S[j], o, kWave);
-    S[8] = sh.pick[0][1];
-    if (lane == 0) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (S[j + 1] < k && k <= S[j]) {
-          sh.pick[0][0] = at + j;
-          sh.pick[0][1] = S[j + 1];
-          sh.pick[0][2] = S[j] - S[j + 1];
-        }
-      }
-    }
-  }
-  __syncthreads();
-  digit = sh.pick[0][0];
-  above = sh.pick[0][1];
-  count = sh.pick[0][2];
-}
-
-// The digit d with #(digit > d) < remaining <= #(digit >= d) of an LDS histogram of counts
-// (thread t owns bins 2040-8t .. 2047-8t).  level 1 or 2: which row / result slot to use.
-__device__ __forceinline__ void pick_digit(const int* hist, int remaining, SelectShared& sh, int level, int& digit, int& above_out) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lo = kBins - 8 - 8 * (int)threadIdx.x;
-  const int4 a = *reinterpret_cast<const int4*>(hist + lo), b = *reinterpret_cast<const int4*>(hist + lo + 4);
-  const int c[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};      // bins lo .. lo+7
-  int tot = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) tot += c[j];
-  const int incl = wave_incl_scan_dpp(tot);
-  if (lane == 63) sh.row[ROW_PICK1 + level - 1][wave] = incl;
-  __syncthreads();
-  int before, total;
-  wave_row_sums<SW>(sh.row[ROW_PICK1 + level - 1], wave, before, total);
-  int above = incl - tot + before;                                  // keys in bins above this thread's
-  if (above < remaining && remaining <= above + tot) {
-#pragma unroll
-    for (int j = 7; j >= 0; --j) {
-      if (above < remaining && remaining <= above + c[j]) { sh.pick[level][0] = lo + j; sh.pick[level][1] = above; }
-      above += c[j];
-    }
-  }
-  __syncthreads();
-  digit = sh.pick[level][0];
-  above_out = sh.pick[level][1];
-}
-
-// The candidates of a select (keys that share the threshold's leading digit), each wave its own
-// list in LDS.  Entries are appended either by the lanes that found one (`append_found`, inside
-// uniform control flow) or as a dense run (`append_run`).
-struct CandidateList {
-  uint32_t* key;
-  int32_t* pos;
-  int n;                // appended so far by this wave (uniform); may exceed kWaveCand: then the list is not used
-  bool shared = false;  // one list for the whole workgroup (n entries) instead of one per wave
-  __device__ __forceinline__ void append_found(bool found, uint32_t k, int p, int lane, int* hist1) {
-    const unsigned long long b = __ballot(found);
-    if (b) {
-      if (found) {
-        const int at = n + __popcll(b & ((1ull << lane) - 1ull));
-        if (at < kWaveCand) { key[at] = k; pos[at] = p; }
-        atomicAdd(&hist1[(k >> 10) & 2047u], 1);
-      }
-      n += __popcll(b);
-    }
-  }
-  __device__ __forceinline__ void append_run(bool valid, int n_valid, uint32_t k, int p, int lane, int* hist1) {
-    if (valid) {
-      const int at = n + lane;
-      if (at < kWaveCand) { key[at] = k; pos[at] = p; }
-      atomicAdd(&hist1[(k >> 10) & 2047u], 1);
-    }
-    n += n_valid;
-  }
-};
-
-// The bits of the threshold below its leading digit, found on the candidates, and how many
-// candidates at positions below `before` are above / equal to the threshold.  The candidates agree
-// in every bit from `low_bits` up (`prefix` holds those bits; low_bits = 32, prefix = 0 for a bucket
-// whose keys may differ anywhere); the bits below are taken at most 11 at a time from the top, one
-// LDS histogram per step.  The first step's histogram, of first_digit(key, low_bits), is sh.hist[0],
-// filled by the caller while it collected the candidates.  each_global(f) visits every candidate
-// from memory (used when a wave's list overflowed).  Called by all threads after the candidates
-// are in; starts with the barrier that publishes them.
-__device__ __forceinline__ uint32_t first_digit(uint32_t key, int low_bits) {
-  const int w = min(11, low_bits);
-  return (key >> (low_bits - w)) & ((1u << w) - 1u);
-}
-template <typename GlobalEach>
-__device__ __forceinline__ void finish_select(const CandidateList& list, GlobalEach each_global, uint32_t prefix, int low_bits,
-                                              int remaining, int before, int gt, SelectShared& sh, uint32_t& thr, int& quota,
-                                              int& base_gt, int& base_eq) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (!list.shared && list.n > kWaveCand && lane == 0) sh.overflow = 1;
-  __syncthreads();
-  const bool use_list = sh.overflow == 0;
-  auto for_each_candidate = [&](auto f) {
-    if (use_list) {
-      const int first = list.shared ? (int)threadIdx.x : lane, step = list.shared ? ST : kWave;
-      for (int i = first; i < list.n; i += step) f(list.key[i], list.pos[i]);
-    } else {
-      each_global(f);
-    }
-  };
-  for (int step = 0;; ++step) {
-    int* hist = sh.hist[step & 1];
-    int d, above;
-    pick_digit(hist, remaining, sh, 1 + (step & 1), d, above);
-    remaining -= above;
-    const int w = min(11, low_bits);
-    low_bits -= w;
-    prefix |= (uint32_t)d << low_bits;
-    if (low_bits == 0) break;
-    if (low_bits > 11) {                         // a third step follows the next one, in this histogram again
-      for (int i = threadIdx.x; i < kBins; i += ST) hist[i] = 0;
-    }
-    int* next = sh.hist[(step + 1) & 1];
-    const uint32_t known = prefix >> low_bits;   // low_bits <= 21 here
-    const int lb = low_bits;
-    for_each_candidate([&](uint32_t key, int) {
-      if ((key >> lb) == known) atomicAdd(&next[first_digit(key, lb)], 1);
-    });
-    __syncthreads();
-  }
-  thr = prefix;
-  quota = remaining;
-  int eq = 0;
-  const uint32_t t_key = thr;
-  for_each_candidate([&](uint32_t key, int pos) {
-    if (pos < before) { gt += key > t_key; eq += key == t_key; }
-  });
-  gt = wave_total_of_scan(wave_incl_scan_dpp(gt));
-  eq = wave_total_of_scan(wave_incl_scan_dpp(eq));
-  if (lane == 0) { sh.row[ROW_GT][wave] = gt; sh.row[ROW_EQ][wave] = eq; }
-  __syncthreads();
-  int unused;
-  wave_row_sums<SW>(sh.row[ROW_GT], SW, unused, base_gt);
-  wave_row_sums<SW>(sh.row[ROW_EQ], SW, unused, base_eq);
-}
-
-// Ordered pass over positions [begin, end) in tiles of kTile: a thread's EPT consecutive
-// elements are classified by load_cls (2: above the threshold, 1: equal, 0: below or outside);
-// emit(position, selected, rank among the selected) is called for every element inside.
-// Equal elements are selected while fewer than `quota` earlier ones exist.  The two running
-// counts of a thread travel through one scan packed as (greater << 16) | equal (a tile has
-// 1024 elements, so neither half overflows).
-template <typename ClsFn, typename EmitFn>
-__device__ __forceinline__ void ordered_emit(ClsFn load_cls, EmitFn emit, int begin, int end, int base_gt, int base_eq, int quota,
-                                             SelectShared& sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int carry_gt = base_gt, carry_eq = base_eq, buf = 0;
-  for (int tile = begin; tile < end; tile += kTile) {
-    const int i0 = tile + (int)threadIdx.x * EPT;
-    int cls[EPT];
-    load_cls(i0, cls);
-    int packed = 0;
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) packed += (cls[j] == 2 ? 0x10000 : 0) + (cls[j] == 1 ? 1 : 0);
-    const int incl = wave_incl_scan_dpp(packed);
-    if (lane == 63) sh.row[ROW_EMIT0 + buf][wave] = incl;
-    __syncthreads();
-    int pre, tile_tot;
-    wave_row_sums<SW>(sh.row[ROW_EMIT0 + buf], wave, pre, tile_tot);
-    pre += incl - packed;
-    int pre_gt = carry_gt + (pre >> 16), pre_eq = carry_eq + (pre & 0xffff);
-    carry_gt += tile_tot >> 16;
-    carry_eq += tile_tot & 0xffff;
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-      if (i0 + j < end) {
-        const bool sel = cls[j] == 2 || (cls[j] == 1 && pre_eq < quota);
-        emit(i0 + j, sel, pre_gt + min(pre_eq, quota));
-        pre_gt += cls[j] == 2;
-        pre_eq += cls[j] == 1;
-      }
-    }
-    buf ^= 1;
-  }
-}
-
-struct RouteParams;
 struct RouteParams {
   const float* score; const float* eps;
-  int n, n_pool, n_approx, n_heads;
-  int chunk_tokens, n_chunks;      // selection by score: tokens per workgroup
-  int slice, n_slices;             // selection by residual: pool entries per workgroup
-  int pool_stride;                 // entries between the pool lists of two heads (a multiple of 4)
-  const uint16_t* table0;          // [H, C, kTableStride] leading digits of the score keys
+  int n, n_pool, n_approx;
+  int chunk_tokens, n_chunks;      // of the bucket lists
+  int part_tokens;                 // tokens per workgroup
+  const uint16_t* table;           // [H, C, kTableStride] leading digits of the score keys
   const uint32_t* bkey;            // [H, n] score keys grouped by leading digit, chunk by chunk
-  const int32_t* bpos;
-  uint16_t* table1;                // [H, C, kTableStride] leading digits of the residual keys of pool members
-  uint8_t* tier; int32_t* idx_retain; int32_t* idx_approx;
-  int32_t* pool_idx; uint32_t* pool_key;
+  const int32_t* bpos;             // their tokens
+  const uint32_t* beps;            // and residual keys
   const uint32_t* map;             // [H, 2]: the digit map (lowq, shift) of the head's score buckets
-  const RouteParams* seq_table;        // RAGGED launches: the sequences' parameter blocks, seq_hps heads each
+  uint8_t* tier; int32_t* idx_retain; int32_t* idx_approx;
+  GatherParams g;                  // row copies (k null: none)
+  const RouteParams* seq_table;    // RAGGED launches: the sequences' parameter blocks, seq_hps heads each
   int seq_hps;
 };
 
-// Step 1: the pool is the n_pool tokens of highest score
-template <bool RAGGED>
-__global__ __launch_bounds__(ST) void route_pool_kernel(RouteParams p) {
-  int h = blockIdx.y;
-  take_sequence<RAGGED>(p, h);
-  if (RAGGED && (int)blockIdx.x >= p.n_chunks) return;
-  __shared__ SelectShared sh;
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  const int chunk = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const float* sc = p.score + (size_t)h * p.n;
-  const float* ep = p.eps + (size_t)h * p.n;
-  const int n = p.n;
-  VEC_TRACE(0);
-  select_shared_init(sh);
-  // how the bucket launch cut the keys into leading digits
-  DigitMap map = {p.map[2 * h], min((int)p.map[2 * h + 1], 21)};
-  const bool vec4 = (n & 3) == 0 && ((reinterpret_cast<uintptr_t>(sc) | reinterpret_cast<uintptr_t>(ep)) & 15u) == 0;
-  auto load_f4 = [&](const float* a, int i0, float (&x)[EPT]) {
-    if (vec4 && i0 + EPT <= n) {
-      const float4 v = *reinterpret_cast<const float4*>(a + i0);
-      x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-    } else {
-#pragma unroll
-      for (int j = 0; j < EPT; ++j) x[j] = i0 + j < n ? a[i0 + j] : 0.f;
-    }
-  };
-  const int begin = chunk * p.chunk_tokens, end = min(n, begin + p.chunk_tokens);
-  // this thread's tokens of the chunk's first two tiles: requested with the tables, used by the ordered pass
-  const int first_i0 = begin + (int)threadIdx.x * EPT;
-  float sc0[2][EPT], ep0[2][EPT];
-  int d0, above0, m0;
-  const uint16_t* tables = p.table0 + (size_t)h * p.n_chunks * kTableStride;
-  pick_leading_digit(tables, p.n_chunks, p.n_pool, sh,
-                     [&]() {
-#pragma unroll
-                       for (int u = 0; u < 2; ++u) { load_f4(sc, first_i0 + u * kTile, sc0[u]); load_f4(ep, first_i0 + u * kTile, ep0[u]); }
-                     },
-                     d0, above0, m0);
-  VEC_TRACE(1);
-  // where every chunk keeps its keys of digit d0: after the D[d0+1] keys of higher digits
-  if (wave == 0) {                               // n_chunks <= 32: one lane per chunk
-    int hi = 0, cnt = 0;
-    if (lane < p.n_chunks) {
-      const uint16_t* t = tables + (size_t)lane * kTableStride;
-      hi = t[d0 + 1];
-      cnt = (int)t[d0] - hi;
-    }
-    const int incl = wave_incl_scan_dpp(cnt);
-    if (lane < p.n_chunks) { sh.seg_first[lane] = hi; sh.seg_count[lane] = cnt; sh.seg_start[lane] = incl - cnt; }
-  }
-  __syncthreads();
-  VEC_TRACE(2);
-  // Candidates: a group of threads per chunk reads that chunk's piece, kBatch loads in flight per
-  // thread; candidate number = pieces of earlier chunks + place in the piece, which is also its
-  // slot in the one list the waves then share out.  Keys above the digit in earlier chunks are
-  // all selected.
-  uint32_t* cand_key = reinterpret_cast<uint32_t*>(dyn_lds);
-  int32_t* cand_pos = reinterpret_cast<int32_t*>(dyn_lds) + kCandCap;
-  const uint32_t* bkey = p.bkey + (size_t)h * n;
-  const int32_t* bpos = p.bpos + (size_t)h * n;
-  int gt = 0;
-  for (int c = 0; c < p.n_chunks; ++c)
-    if (c < chunk && threadIdx.x == 0) gt += sh.seg_first[c];
-  int groups = 1;
-  while (groups < p.n_chunks) groups *= 2;
-  const int tpc = ST / groups;                   // threads per chunk (at least 8)
-  const int my_c = (int)threadIdx.x / tpc, my_sub = (int)threadIdx.x % tpc;
-  const bool fits = m0 <= kCandCap;
-  // what the candidates already agree on: everything above the digit's 2^shift keys, or nothing
-  const bool high_shared = map.shares_high_bits(d0);
-  const int low_bits = high_shared ? map.shift : 32;
-  const uint32_t prefix = high_shared ? ((uint32_t)d0 + map.lowq) << map.shift : 0u;
-  // More candidates than LDS holds usually means a plateau: scores that are all the same number (the
-  // zeros of attention rows that underflow, a constant fill).  One look at the keys tells; then the
-  // threshold is that number, and which of the equal tokens get in follows from the counts alone.
-  bool plateau = false;
-  uint32_t plateau_key = 0u;
-  if (!fits) {
-    uint32_t kmin = 0xffffffffu, kmax = 0u;
-    const int cnt = my_c < p.n_chunks ? sh.seg_count[my_c] : 0;
-    const int src0 = my_c < p.n_chunks ? my_c * p.chunk_tokens + sh.seg_first[my_c] : 0;
-    for (int i0 = 0; i0 < cnt; i0 += tpc * kBatch) {
-      uint32_t ck[kBatch];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) ck[u] = bkey[src0 + min(i0 + u * tpc + my_sub, cnt - 1)];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) { kmin = min(kmin, ck[u]); kmax = max(kmax, ck[u]); }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
-      kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
-    }
-    if (lane == 0) { sh.row[ROW_GT][wave] = (int)kmin; sh.row[ROW_EQ][wave] = (int)kmax; }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < SW; ++q) { kmin = min(kmin, (uint32_t)sh.row[ROW_GT][q]); kmax = max(kmax, (uint32_t)sh.row[ROW_EQ][q]); }
-    plateau = kmin == kmax;
-    plateau_key = kmin;
-    __syncthreads();                               // the rows are used again below
-  }
-  if (!plateau) {
-    const bool live = my_c < p.n_chunks;
-    const int cnt = live ? sh.seg_count[my_c] : 0;
-    const int src0 = live ? my_c * p.chunk_tokens + sh.seg_first[my_c] : 0;
-    const int dst0 = live ? sh.seg_start[my_c] : 0;
-    for (int i0 = 0; i0 < cnt; i0 += tpc * kBatch) {
-      uint32_t ck[kBatch];
-      int cp[kBatch];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int i = min(i0 + u * tpc + my_sub, cnt - 1);
-        ck[u] = bkey[src0 + i];
-        cp[u] = bpos[src0 + i];
-      }
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int i = i0 + u * tpc + my_sub;
-        if (i < cnt) {
-          if (fits) { cand_key[dst0 + i] = ck[u]; cand_pos[dst0 + i] = cp[u]; }
-          atomicAdd(&sh.hist[0][first_digit(ck[u], low_bits)], 1);
-        }
-      }
-    }
-  }
-  if (!fits && threadIdx.x == 0) sh.overflow = 1;
-  CandidateList list;                            // every wave a share of the one list
-  list.key = cand_key;
-  list.pos = cand_pos;
-  list.n = fits ? m0 : kWaveCand + 1;
-  list.shared = true;
-  VEC_TRACE(3);
-  uint32_t thr;
-  int quota, base_gt, base_eq;
-  if (plateau) {                                   // uniform
-    thr = plateau_key;
-    quota = p.n_pool - above0;                     // equal keys still to take, lowest token index first
-    base_gt = 0;
-    for (int c = 0; c < chunk; ++c) base_gt += sh.seg_first[c];
-    base_eq = sh.seg_start[chunk];                 // the equal keys of earlier chunks come first
-  } else {
-    finish_select(
-        list,
-        [&](auto f) {
-          const int cnt = my_c < p.n_chunks ? sh.seg_count[my_c] : 0;
-          const int src0 = my_c < p.n_chunks ? my_c * p.chunk_tokens + sh.seg_first[my_c] : 0;
-          for (int i = my_sub; i < cnt; i += tpc) f(bkey[src0 + i], bpos[src0 + i]);
-        },
-        prefix, low_bits, p.n_pool - above0, begin, gt, sh, thr, quota, base_gt, base_eq);
-  }
-  VEC_TRACE(4);
+constexpr int kMaxGroups = 64 * HW;      // as many as the registers of a workgroup hold
 
-  // ordered pass over the chunk: tiers, pool list, leading digits of the residual keys
-  uint8_t* tr = p.tier + (size_t)h * n;
-  int32_t* pidx = p.pool_idx + (size_t)h * p.pool_stride;
-  uint32_t* pkey = p.pool_key + (size_t)h * p.pool_stride;
-  uint32_t ekey[EPT];
-  ordered_emit(
-      [&](int i0, int (&cls)[EPT]) {
-        float x[EPT], e[EPT];
-        if (i0 == first_i0 || i0 == first_i0 + kTile) {
-          const int u = i0 == first_i0 ? 0 : 1;
+struct ListShared {
+  __align__(16) int hist[kHeadBins];
+  __align__(16) int list[kHeadBlock];    // tokens whose rows this workgroup copies: retained, then approximated
+  int coarse[HT + 1];                    // sums of the tables at every fourth bin
+  // per chunk: entries in front of the chosen bin, the groups of 64 of them before the chunk's, and the entries
+  // of the bin (candidates) before the chunk's
+  int front[kMaxChunks], group_start[kMaxChunks], cand_start[kMaxChunks];
+  int n_groups;
+  int2 group[kMaxGroups];                // the first groups: place of the first entry in the head's lists, number of entries
+  uint32_t cand[kRankCap];
+  int wsum[3][HW];
+  float stat[3][HW];
+  uint32_t center[2];
+  int pick[3];
+  int n_cand;
+  uint32_t thr;
+  int quota, equal;
+};
+
+// Leading digit of the k-th largest key of a head from the D tables of its chunks: summed over the
+// chunks, S[b] = #(digit >= b) falls from the key count at b = 0 to 0 at b = 2048, and the digit is
+// the one bin with S[b+1] < k <= S[b].  Two steps, because what this costs is load instructions: thread t
+// sums only the entry at the low end of its four bins (b = 2044 - 4t); the entry above its bins is
+// its neighbour's sum, and one thread finds k between the two.  Then lane c of wave 0 reads that thread's bins
+// of chunk c, and the sums over the lanes give the digit, and with it where every chunk keeps its entries.
+// prefetch() is called once the first loads are out.
+template <typename Prefetch>
+__device__ __forceinline__ void pick_from_tables(const uint16_t* tables, int n_chunks, int k, ListShared& sh, Prefetch prefetch) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lo = kBins - 4 - 4 * (int)threadIdx.x;
+  int s_lo = 0;
+  bool first = true;
+  constexpr int kInFlight = 16;                 // chunks requested together: one trip to memory for up to 16 of them
+  for (int c = 0; c < n_chunks; c += kInFlight) {
+    uint16_t e[kInFlight];
 #pragma unroll
-          for (int j = 0; j < EPT; ++j) { x[j] = sc0[u][j]; e[j] = ep0[u][j]; }
-        } else {
-          load_f4(sc, i0, x);
-          load_f4(ep, i0, e);
-        }
+    for (int u = 0; u < kInFlight; ++u) e[u] = tables[(size_t)min(c + u, n_chunks - 1) * kTableStride + lo];
+    if (first) { prefetch(); first = false; }
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) {
-          const uint32_t key = float_key(x[j]);
-          cls[j] = i0 + j < end ? (key > thr ? 2 : (key == thr ? 1 : 0)) : 0;
-          ekey[j] = ~float_key(e[j]);               // smaller residual, larger key
-        }
-      },
-      [&](int i, bool sel, int rank) {
-        tr[i] = sel ? VECTOR_TIER_RETAIN : VECTOR_TIER_EVICT;
-        if (sel && rank < p.n_pool) {                // rank < n_pool by construction; never write past the list
-          const uint32_t ek = ekey[i & (EPT - 1)];   // tiles start at multiples of EPT
-          pidx[rank] = i;
-          pkey[rank] = ek;
-          atomicAdd(&sh.hist[2][ek >> 21], 1);
-        }
-      },
-      begin, end, base_gt, base_eq, quota, sh);
-  VEC_TRACE(5);
-  __syncthreads();
-  counts_to_table<ST>(sh.hist[2], p.table1 + ((size_t)h * p.n_chunks + chunk) * kTableStride, sh.row[ROW_TABLE]);
-  VEC_TRACE(6);
+    for (int u = 0; u < kInFlight; ++u)
+      if (c + u < n_chunks) s_lo += (int)e[u];
+  }
+  sh.coarse[threadIdx.x + 1] = s_lo;            // coarse[t + 1] = S[2044 - 4t]; coarse[0] = S[2048] = 0
+  if (threadIdx.x == 0) { sh.coarse[0] = 0; sh.pick[0] = 0; }       // no bracket (k outside the counts): the second step still reads inside the tables
+  lds_barrier();
+  const int s_hi = sh.coarse[threadIdx.x];      // S at the bin above this thread's four
+  if (s_hi < k && k <= s_lo) sh.pick[0] = lo;
+  lds_barrier();
+  if (wave == 0) {
+    const int at = sh.pick[0];
+    int d[5] = {0, 0, 0, 0, 0};
+    if (lane < n_chunks) {
+      const uint16_t* t = tables + (size_t)lane * kTableStride + at;
+      const uint2 v = *reinterpret_cast<const uint2*>(t);
+      d[0] = (int)(v.x & 0xffffu); d[1] = (int)(v.x >> 16); d[2] = (int)(v.y & 0xffffu); d[3] = (int)(v.y >> 16);
+      d[4] = t[4];
+    }
+    int S[5], j = 0;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) S[q] = wave_total_of_scan(wave_incl_scan_dpp(d[q]));
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (S[q + 1] < k && k <= S[q]) j = q;
+    int front = d[1], cnt = d[0] - d[1], above = S[1], count = S[0] - S[1];
+#pragma unroll
+    for (int q = 1; q < 4; ++q)
+      if (j == q) { front = d[q + 1]; cnt = d[q] - d[q + 1]; above = S[q + 1]; count = S[q] - S[q + 1]; }
+    const int groups = (front + 63) >> 6;
+    const int g_incl = wave_incl_scan_dpp(groups), c_incl = wave_incl_scan_dpp(cnt);
+    if (lane < kMaxChunks) {
+      sh.front[lane] = front;
+      sh.group_start[lane] = lane < n_chunks ? g_incl - groups : 0x7fffffff;
+      sh.cand_start[lane] = lane < n_chunks ? c_incl - cnt : 0x7fffffff;
+    }
+    if (lane == 63) sh.n_groups = g_incl;
+    if (lane == 0) { sh.pick[0] = at + j; sh.pick[1] = above; sh.pick[2] = count; }
+  }
+  lds_barrier();
 }
 
-// Step 3: inside the pool, the n_approx tokens of lowest residual lose their value
-template <bool RAGGED>
-__global__ __launch_bounds__(ST) void route_split_kernel(RouteParams p) {
-  int h = blockIdx.y;
-  take_sequence<RAGGED>(p, h);
-  if (RAGGED && (int)blockIdx.x >= p.n_slices) return;
-  __shared__ SelectShared sh;
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  const int slice = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = p.n_pool;
-  const int32_t* pidx = p.pool_idx + (size_t)h * p.pool_stride;
-  const uint32_t* pkey = p.pool_key + (size_t)h * p.pool_stride;
-  uint8_t* tr = p.tier + (size_t)h * p.n;
-  int32_t* ir = p.idx_retain + (size_t)h * (p.n_pool - p.n_approx);
-  int32_t* ia = p.idx_approx + (size_t)h * p.n_approx;
-  const int begin = slice * p.slice, end = min(m, begin + p.slice);
-  if (p.n_approx == 0) {
-    for (int i = begin + (int)threadIdx.x; i < end; i += ST) ir[i] = pidx[i];
-    return;
+// the chunk whose entries hold number idx of a concatenation (start: [kMaxChunks], ascending)
+__device__ __forceinline__ int chunk_of(const int* start, int idx) {
+  int c = 0;
+#pragma unroll
+  for (int s = kMaxChunks / 2; s > 0; s >>= 1)
+    if (start[c + s] <= idx) c += s;
+  return c;
+}
+
+// The k-th largest key: keys above thr are selected, and of those equal to it the quota with the lowest tokens
+// (all_equal: every one).
+struct Cut { uint32_t thr; int quota; bool all_equal; };
+
+// A sample of the keys in registers (0: no key), every fourth slot: count, sum and sum of squares in units of 4096
+// keys about the center; every wave leaves its own in sh.stat for list_select.
+template <int NS>
+__device__ __forceinline__ void leave_sample(const uint32_t (&key)[NS], uint32_t center, ListShared& sh) {
+  float cnt = 0.f, s1 = 0.f, s2 = 0.f;
+#pragma unroll
+  for (int j = 0; j < NS; j += 4) {
+    const bool ok = key[j] > 0x007fffffu && key[j] < 0xff800000u;       // a finite number
+    const float dlt = ok ? (float)((int)(key[j] >> 12) - (int)(center >> 12)) : 0.f;
+    cnt += ok ? 1.f : 0.f;
+    s1 += dlt;
+    s2 = fmaf(dlt, dlt, s2);
   }
-  VEC_TRACE(16);
-  select_shared_init(sh);
-  auto load_u4 = [&](const uint32_t* a, int i0, uint32_t (&x)[EPT]) {
-    if (i0 + EPT <= m) {                             // lists start at 16-byte boundaries
-      const uint4 v = *reinterpret_cast<const uint4*>(a + i0);
-      x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+  cnt = wave_sum_dpp(cnt); s1 = wave_sum_dpp(s1); s2 = wave_sum_dpp(s2);
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { sh.stat[0][wave] = cnt; sh.stat[1][wave] = s1; sh.stat[2][wave] = s2; }
+}
+
+// Among the keys in registers (0: no key) and those that more(f) hands to f; 1 <= k <= number of keys.
+// total: number of keys; center: what leave_sample was given.  The caller has passed a barrier since the last use of
+// sh but for the sample.
+template <int NS, typename More>
+__device__ __forceinline__ Cut list_select(const uint32_t (&key)[NS], More more, int total, int k, uint32_t center, ListShared& sh) {
+  const int lane = threadIdx.x & 63;
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) f(key[i]);
+    more(f);
+  };
+  int count = total;
+  uint32_t lo = 1u, span = 0xfffffffeu;
+  if (threadIdx.x == 0) sh.n_cand = 0;
+  if (total > kRankCap) {                                               // uniform
+    clear_bins(sh.hist);
+    lds_barrier();
+    const DigitMap map = digit_map_about(center, sum_of_waves(sh.stat[0], lane), sum_of_waves(sh.stat[1], lane), sum_of_waves(sh.stat[2], lane));
+    each([&](uint32_t x) { if (x != 0u) atomicAdd(&sh.hist[map.digit(x)], 1); });
+    lds_barrier();
+    int d, above;
+    pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
+    k -= above;
+    bucket_range(map, d, lo, span);
+    while (count > kRankCap && span != 0u) {                            // uniform
+      const int s = max(0, 21 - (int)__clz(span));                      // at most 2048 buckets over the range
+      clear_bins(sh.hist);
+      lds_barrier();
+      each([&](uint32_t x) { if (x - lo <= span) atomicAdd(&sh.hist[(x - lo) >> s], 1); });
+      lds_barrier();
+      pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
+      k -= above;
+      lo += (uint32_t)d << s;
+      span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
+    }
+  } else {
+    lds_barrier();
+  }
+  if (span == 0u) { lds_barrier(); return {lo, k, count == k}; }        // one key, however many tokens
+  auto collect = [&](uint32_t x) {
+    if (x - lo <= span) {
+      const int at = atomicAdd(&sh.n_cand, 1);
+      if (at < kRankCap) sh.cand[at] = x;
+    }
+  };
+  bool any = false;                                                     // few waves have one: a branch per slot only there
+#pragma unroll
+  for (int i = 0; i < NS; ++i) any |= key[i] - lo <= span;
+  if (__any(any)) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) collect(key[i]);
+  }
+  more(collect);
+  lds_barrier();
+  if ((int)threadIdx.x < count) {
+    const uint32_t mine = sh.cand[threadIdx.x];
+    int greater = 0, equal = 0;
+#pragma unroll 4
+    for (int j = 0; j < count; ++j) { greater += sh.cand[j] > mine; equal += sh.cand[j] == mine; }
+    if (greater < k && k <= greater + equal) { sh.thr = mine; sh.quota = k - greater; sh.equal = equal; }     // the same values from every thread that finds it
+  }
+  lds_barrier();
+  return {sh.thr, sh.quota, sh.quota == sh.equal};
+}
+
+// The last of the `quota` lowest tokens whose key is thr; each(f) hands every (key, token) to f.
+template <typename Each>
+__device__ __forceinline__ int token_cut(Each each, uint32_t thr, int quota, ListShared& sh) {
+  uint32_t lo = 0u, span = (uint32_t)kRouteMaxSeqLen - 1u;              // of kRouteMaxSeqLen - 1 - token
+  while (span != 0u) {
+    const int s = max(0, 21 - (int)__clz(span));
+    int d, above, count;
+    clear_bins(sh.hist);
+    lds_barrier();
+    each([&](uint32_t key, int tok) {
+      const uint32_t v = (uint32_t)(kRouteMaxSeqLen - 1 - tok) - lo;
+      if (key == thr && v <= span) atomicAdd(&sh.hist[v >> s], 1);
+    });
+    lds_barrier();
+    pick_bin(sh.hist, sh.wsum[0], sh.pick, quota, d, above, count);
+    quota -= above;
+    lo += (uint32_t)d << s;
+    span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
+  }
+  lds_barrier();
+  return kRouteMaxSeqLen - 1 - (int)lo;
+}
+
+constexpr int kCandSlots = 4;            // candidates per thread kept in registers
+
+// SLOTS: pool members per thread kept in registers (the rest are read again for every pass over them)
+template <int SLOTS, bool RAGGED>
+__global__ __launch_bounds__(HT) void route_list_kernel(RouteParams p) {
+  int part, h;
+  xcd_chunk_head(part, h);
+  take_sequence<RAGGED>(p, h);
+  const int n = p.n, begin = part * p.part_tokens, end = min(n, begin + p.part_tokens);
+  if (begin >= n) return;
+  __shared__ ListShared sh;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), tid = threadIdx.x;
+  const float* score = p.score + (size_t)h * n;
+  const float* eps = p.eps + (size_t)h * n;
+  const uint32_t* bkey = p.bkey + (size_t)h * n;
+  const int32_t* bpos = p.bpos + (size_t)h * n;
+  const uint32_t* beps = p.beps + (size_t)h * n;
+  auto load4 = [&](const float* a, int t0, int stop) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (t0 + 4 <= stop) {
+      x = *reinterpret_cast<const f32x4_u*>(a + t0);
     } else {
 #pragma unroll
-      for (int j = 0; j < EPT; ++j) x[j] = i0 + j < m ? a[i0 + j] : 0u;
+      for (int e = 0; e < 4; ++e)
+        if (t0 + e < stop) x[e] = a[t0 + e];
+    }
+    return x;
+  };
+  const int own_chunk = begin / p.chunk_tokens;
+  // the tokens this thread emits first, and those of the part's chunk that lie before it: requested with the tables
+  f32x4 sc, ep, own_sc, own_ep;
+  pick_from_tables(p.table + (size_t)h * p.n_chunks * kTableStride, p.n_chunks, p.n_pool, sh, [&]() {
+    sc = load4(score, begin + 4 * tid, end);
+    ep = load4(eps, begin + 4 * tid, end);
+    own_sc = load4(score, own_chunk * p.chunk_tokens + 4 * tid, begin);
+    own_ep = load4(eps, own_chunk * p.chunk_tokens + 4 * tid, begin);
+  });
+  const int n_front = sh.pick[1], n_cand = sh.pick[2], n_groups = sh.n_groups;
+  // group g of the entries in front of the bin
+  auto group_at = [&](int g) {
+    const int c = chunk_of(sh.group_start, g), first = (g - sh.group_start[c]) * kWave;
+    return make_int2(c * p.chunk_tokens + first, min(kWave, sh.front[c] - first));
+  };
+  auto cand_at = [&](int idx) {
+    const int c = chunk_of(sh.cand_start, idx);
+    return c * p.chunk_tokens + sh.front[c] + idx - sh.cand_start[c];
+  };
+  static_assert(SLOTS * HW <= kMaxGroups && kMaxGroups == HT, "one group per thread");
+  sh.group[tid] = tid < n_groups ? group_at(tid) : make_int2(0, 0);
+  uint32_t ckey[kCandSlots], ceps[kCandSlots], key[SLOTS + kCandSlots];
+  int cpos[kCandSlots];
+  {
+    int at[kCandSlots];
+#pragma unroll
+    for (int i = 0; i < kCandSlots; ++i) at[i] = n_cand > 0 ? cand_at(min(tid + i * HT, n_cand - 1)) : 0;
+#pragma unroll
+    for (int i = 0; i < kCandSlots; ++i) { ckey[i] = bkey[at[i]]; cpos[i] = bpos[at[i]]; ceps[i] = beps[at[i]]; }
+  }
+  lds_barrier();
+  // Slot i of wave w: group w + 8 i
+#pragma unroll
+  for (int i = 0; i < SLOTS; ++i) {
+    const int2 g = sh.group[wave + HW * i];
+    key[i] = beps[g.x + min(lane, max(g.y - 1, 0))];
+  }
+#pragma unroll
+  for (int i = 0; i < SLOTS; ++i)
+    if (lane >= sh.group[wave + HW * i].y) key[i] = 0u;
+#pragma unroll
+  for (int i = 0; i < kCandSlots; ++i)
+    if (tid + i * HT >= n_cand) ckey[i] = 0u;
+  if (tid == 0) { sh.center[0] = ckey[0]; sh.center[1] = n_front > 0 ? key[0] : ceps[0]; }
+  lds_barrier();
+  const uint32_t center0 = sh.center[0], center1 = sh.center[1];
+  if (n_cand > kRankCap) leave_sample(ckey, center0, sh);
+  // Step 1: the pool is the n_pool tokens of highest score
+  const Cut top = list_select(ckey, [&](auto f) {
+    for (int i = kCandSlots * HT + tid; i < n_cand; i += HT) f(bkey[cand_at(i)]);
+  }, n_cand, p.n_pool - n_front, center0, sh);
+  leave_sample(key, center1, sh);                      // before the candidates join: one barrier less
+  int top_tok = kRouteMaxSeqLen;
+  if (!top.all_equal)                                  // uniform
+    top_tok = token_cut([&](auto f) {
+      for (int i = tid; i < n_cand; i += HT) { const int a = cand_at(i); f(bkey[a], bpos[a]); }
+    }, top.thr, top.quota, sh);
+  auto in_pool = [&](uint32_t k, int tok) { return k > top.thr || (k == top.thr && tok <= top_tok); };
+  // Step 3: inside the pool, the n_approx tokens of lowest residual lose their value
+  Cut low = {0xffffffffu, 0, true};                    // n_approx = 0: none
+  int low_tok = kRouteMaxSeqLen;
+#pragma unroll
+  for (int i = 0; i < kCandSlots; ++i) key[SLOTS + i] = ckey[i] != 0u && in_pool(ckey[i], cpos[i]) ? ceps[i] : 0u;
+  // every pool member beyond the registers, or (all) every one: f(residual key, token)
+  auto pool_members = [&](bool all, auto f) {
+    constexpr int U = 8;                               // groups in flight per wave
+    for (int g0 = (all ? 0 : SLOTS * HW) + wave; g0 < n_groups; g0 += U * HW) {
+      uint32_t k[U];
+      int tok[U];
+      bool ok[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int2 g = group_at(min(g0 + u * HW, n_groups - 1));
+        const int f = g.x + min(lane, g.y - 1);
+        k[u] = beps[f];
+        tok[u] = bpos[f];
+        ok[u] = g0 + u * HW < n_groups && lane < g.y;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (ok[u]) f(k[u], tok[u]);
+    }
+    for (int i = (all ? 0 : kCandSlots * HT) + tid; i < n_cand; i += HT) {
+      const int a = cand_at(i), tok = bpos[a];
+      if (in_pool(bkey[a], tok)) f(beps[a], tok);
     }
   };
-  const int n_tiles = (m + kTile - 1) / kTile;
-  uint32_t cur[kBatch][EPT];
-  auto load_batch = [&](int tb, uint32_t (&key)[kBatch][EPT]) {
+  if (p.n_approx > 0) {
+    low = list_select(key, [&](auto f) { pool_members(false, [&](uint32_t k, int) { f(k); }); }, p.n_pool, p.n_approx, center1, sh);
+    if (!low.all_equal) low_tok = token_cut([&](auto f) { pool_members(true, f); }, low.thr, low.quota, sh);
+  }
+  auto is_approx = [&](uint32_t k, int tok) { return p.n_approx > 0 && (k > low.thr || (k == low.thr && tok <= low_tok)); };
+  // Members in front of this part: the lists of the chunks before its own, then the own chunk's tokens before it
+  int pool_before = 0, apx_before = 0;                 // of this lane; counts of whole waves in lane 0
+  const int own_first = own_chunk * p.chunk_tokens;
+  if (low.all_equal) {
+    const int groups_before = min(sh.group_start[own_chunk], SLOTS * HW);
+    int apx = 0;
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      if (tb + u < n_tiles) {
-        load_u4(pkey, (tb + u) * kTile + (int)threadIdx.x * EPT, key[u]);
-      } else {
+    for (int i = 0; i < SLOTS; ++i)
+      if (wave + HW * i < groups_before) apx += __popcll(__ballot(p.n_approx > 0 && key[i] >= low.thr));      // uniform
+    if (lane == 0) apx_before += apx;
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) key[u][j] = 0u;
-      }
+    for (int i = 0; i < kCandSlots; ++i)
+      if (key[SLOTS + i] != 0u && cpos[i] < own_first) { ++pool_before; apx_before += is_approx(key[SLOTS + i], 0); }
+    pool_members(false, [&](uint32_t k, int tok) {
+      if (tok < own_first) { ++pool_before; apx_before += is_approx(k, tok); }
+    });
+    if (tid == 0) {                                    // the register slots' share of the pool: whole chunks and one cut off
+      int in_slots = 0;
+      for (int c = 0; c < own_chunk; ++c) in_slots += min(sh.front[c], max(0, (groups_before - sh.group_start[c]) * kWave));
+      pool_before += in_slots;
     }
-  };
-  // this thread's entries of the slice's first tile: requested with the tables, used by the ordered pass
-  const int first_i0 = begin + (int)threadIdx.x * EPT;
-  uint32_t key0[EPT], tok0[EPT];
-  int d0, above0, m0;
-  pick_leading_digit(p.table1 + (size_t)h * p.n_chunks * kTableStride, p.n_chunks, p.n_approx, sh,
-                     [&]() {
-                       load_batch(0, cur);
-                       load_u4(pkey, first_i0, key0);
-                       load_u4(reinterpret_cast<const uint32_t*>(pidx), first_i0, tok0);
-                     },
-                     d0, above0, m0);
-  VEC_TRACE(17);
-  // all keys of the pool once: candidates into this wave's list, earlier keys above the digit counted
-  CandidateList list;
-  list.key = reinterpret_cast<uint32_t*>(dyn_lds) + wave * kWaveCand;
-  list.pos = reinterpret_cast<int32_t*>(dyn_lds) + kCandCap + wave * kWaveCand;
-  list.n = 0;
-  list.shared = false;
-  int gt = 0;
-  for (int tb = 0; tb < n_tiles; tb += kBatch) {
-    uint32_t nxt[kBatch][EPT];
-    const bool more = tb + kBatch < n_tiles;
-    if (more) load_batch(tb + kBatch, nxt);          // requested before this batch is worked on
+  } else {                                             // which of the equal keys: by their tokens
+    pool_members(true, [&](uint32_t k, int tok) {
+      if (tok < own_first) { ++pool_before; apx_before += is_approx(k, tok); }
+    });
+  }
+  for (int t = own_first; t < begin; t += kHeadBlock) {
+    const int t0 = t + 4 * tid;
+    if (t != own_first) { own_sc = load4(score, t0, begin); own_ep = load4(eps, t0, begin); }
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      if (tb + u < n_tiles) {                        // uniform
-        const int i0 = (tb + u) * kTile + (int)threadIdx.x * EPT;
-#pragma unroll
-        for (int j = 0; j < EPT; ++j) {
-          const bool ok = i0 + j < m;
-          const int dg = (int)(cur[u][j] >> 21);
-          gt += ok && i0 + j < begin && dg > d0;
-          list.append_found(ok && dg == d0, cur[u][j], i0 + j, lane, sh.hist[0]);
-        }
-      }
-    }
-    if (more) {
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u)
-#pragma unroll
-        for (int j = 0; j < EPT; ++j) cur[u][j] = nxt[u][j];
+    for (int e = 0; e < 4; ++e) {
+      const bool pool = t0 + e < begin && in_pool(float_key(own_sc[e]), t0 + e);
+      pool_before += pool;
+      apx_before += pool && is_approx(~float_key(own_ep[e]), t0 + e);
     }
   }
-  VEC_TRACE(18);
-  uint32_t thr;
-  int quota, base_gt, base_eq;
-  finish_select(
-      list,
-      [&](auto f) {
-        for (int t = 0; t < n_tiles; ++t) {
-          uint32_t key[EPT];
-          const int i0 = t * kTile + (int)threadIdx.x * EPT;
-          load_u4(pkey, i0, key);
+  int base_r, base_a;
+  {
+    const int x = wave_total_of_scan(wave_incl_scan_dpp(pool_before)), y = wave_total_of_scan(wave_incl_scan_dpp(apx_before));
+    if (lane == 0) { sh.wsum[1][wave] = x; sh.wsum[2][wave] = y; }
+    lds_barrier();
+    int total = 0, total_a = 0;
 #pragma unroll
-          for (int j = 0; j < EPT; ++j)
-            if (i0 + j < m && (int)(key[j] >> 21) == d0) f(key[j], i0 + j);
-        }
-      },
-      (uint32_t)d0 << 21, 21, p.n_approx - above0, begin, gt, sh, thr, quota, base_gt, base_eq);
-  VEC_TRACE(19);
-  uint32_t tok[EPT];
-  ordered_emit(
-      [&](int i0, int (&cls)[EPT]) {
-        uint32_t key[EPT];
-        if (i0 == first_i0) {
+    for (int w = 0; w < HW; ++w) { total += sh.wsum[1][w]; total_a += sh.wsum[2][w]; }
+    base_a = total_a;
+    base_r = total - total_a;
+    lds_barrier();                                     // the rows are used again below
+  }
+  const int n_retain = p.n_pool - p.n_approx;
+  const EmitTarget target = {p.tier + (size_t)h * n, p.idx_retain + (size_t)h * n_retain, p.idx_approx + (size_t)h * p.n_approx, end, n_retain, p.n_approx};
+  for (int t = begin; t < end; t += kHeadBlock) {
+    const int t0 = t + 4 * tid;
+    uint32_t ret4 = 0u, apx4 = 0u;
 #pragma unroll
-          for (int j = 0; j < EPT; ++j) { key[j] = key0[j]; tok[j] = tok0[j]; }
-        } else {
-          load_u4(pkey, i0, key);
-          load_u4(reinterpret_cast<const uint32_t*>(pidx), i0, tok);
-        }
-#pragma unroll
-        for (int j = 0; j < EPT; ++j) cls[j] = i0 + j < end ? (key[j] > thr ? 2 : (key[j] == thr ? 1 : 0)) : 0;
-      },
-      [&](int i, bool sel, int rank) {
-        const int t = (int)tok[i & (EPT - 1)];
-        if (sel) {
-          if (rank < p.n_approx) {
-            ia[rank] = t;
-            tr[min(max(t, 0), p.n - 1)] = VECTOR_TIER_APPROX;
-          }
-        } else if (i - rank < p.n_pool - p.n_approx) {
-          ir[i - rank] = t;
-        }
-      },
-      begin, end, base_gt, base_eq, quota, sh);
-  VEC_TRACE(20);
+    for (int e = 0; e < 4; ++e) {
+      const bool pool = t0 + e < end && in_pool(float_key(sc[e]), t0 + e);
+      const bool apx = pool && is_approx(~float_key(ep[e]), t0 + e);
+      ret4 |= (pool && !apx ? 1u : 0u) << e;
+      apx4 |= (apx ? 1u : 0u) << e;
+    }
+    int at, own;
+    head_scan(__popc(ret4) + (__popc(apx4) << 16), sh.wsum[0], at, own);
+    const int own_r = low16(own), own_a = high16(own);
+    if (t0 < end) emit_tokens(target, t0, ret4, apx4, low16(at), high16(at), own_r, base_r, base_a, sh.list);
+    if (t + kHeadBlock < end) { sc = load4(score, t0 + kHeadBlock, end); ep = load4(eps, t0 + kHeadBlock, end); }
+    lds_barrier();                                     // the list is whole
+    if (p.g.k) copy_rows(p.g, h, p.n_approx, sh.list, own_r, own_a, base_r, base_a);
+    base_r += own_r;
+    base_a += own_a;
+    lds_barrier();                                     // the list may be written again
+  }
 }
 
 // nothing is kept: every token is evicted
@@ -988,10 +813,8 @@ __global__ __launch_bounds__(256) void route_evict_all_kernel(uint8_t* __restric
 // ---------------------------------------------------------------------------
 // compaction: one 16-byte piece per thread, P pieces per row
 // ---------------------------------------------------------------------------
-template <bool RAGGED>
 __global__ __launch_bounds__(256) void gather_rows_kernel(GatherParams p) {
-  int h = blockIdx.y;
-  take_sequence<RAGGED>(p, h);
+  const int h = blockIdx.y;
   const int seg = blockIdx.z;                       // seg 0: k_ret, 1: v_ret, 2: k_apx
   const int pieces = p.row_bytes / 16;
   const int rows = (seg == 2) ? p.n_approx : p.n_retain;
@@ -1023,35 +846,32 @@ static int route_chunk_tokens(int seq_len) {
 
 namespace {
 struct RouteLayout {
-  int chunk_tokens, n_chunks, pool_stride;
-  size_t off_map, off_range, off_table0, off_table1, off_bkey, off_bpos, off_idx, off_key, total;
+  int chunk_tokens, n_chunks;
+  size_t off_map, off_range, off_table, off_bkey, off_bpos, off_beps, total;
 };
-RouteLayout route_layout(int n_kv_heads, int seq_len, int n_pool) {
+RouteLayout route_layout(int n_kv_heads, int seq_len) {
   RouteLayout L;
   L.chunk_tokens = route_chunk_tokens(seq_len);
   L.n_chunks = (seq_len + L.chunk_tokens - 1) / L.chunk_tokens;
-  L.pool_stride = (n_pool + 3) / 4 * 4;
   const size_t tables = align_up((size_t)n_kv_heads * L.n_chunks * kTableStride * sizeof(uint16_t), 256);
   const size_t per_token = align_up((size_t)n_kv_heads * seq_len * sizeof(uint32_t), 256);
-  const size_t per_pool = align_up((size_t)n_kv_heads * L.pool_stride * sizeof(uint32_t), 256);
   size_t off = 0;
   L.off_map = off;    off += align_up((size_t)n_kv_heads * 2 * sizeof(uint32_t), 256);
-  L.off_range = off;  off += align_up((size_t)n_kv_heads * route_mass_range_slots(seq_len) * sizeof(float4), 256);
-  L.off_table0 = off; off += tables;
-  L.off_table1 = off; off += tables;
+  L.off_range = off;  off += align_up((size_t)n_kv_heads * route_mass_range_slots(n_kv_heads, seq_len) * sizeof(float4), 256);
+  L.off_table = off;  off += tables;
   L.off_bkey = off;   off += per_token;
   L.off_bpos = off;   off += per_token;
-  L.off_idx = off;    off += per_pool;
-  L.off_key = off;    off += per_pool;
+  L.off_beps = off;   off += per_token;
   L.total = off;
   return L;
 }
 
 void fill_bucket_params(BucketParams& bp, const RouteLayout& L, void* route_ws) {
   unsigned char* w8 = reinterpret_cast<unsigned char*>(route_ws);
-  bp.table = w8 ? reinterpret_cast<uint16_t*>(w8 + L.off_table0) : nullptr;
+  bp.table = w8 ? reinterpret_cast<uint16_t*>(w8 + L.off_table) : nullptr;
   bp.bkey = w8 ? reinterpret_cast<uint32_t*>(w8 + L.off_bkey) : nullptr;
   bp.bpos = w8 ? reinterpret_cast<int32_t*>(w8 + L.off_bpos) : nullptr;
+  bp.beps = w8 ? reinterpret_cast<uint32_t*>(w8 + L.off_beps) : nullptr;
   bp.map = w8 ? reinterpret_cast<uint32_t*>(w8 + L.off_map) : nullptr;
   bp.range = w8 ? reinterpret_cast<const float4*>(w8 + L.off_range) : nullptr;
   bp.n_range = 0;
@@ -1063,68 +883,78 @@ void fill_bucket_params(BucketParams& bp, const RouteLayout& L, void* route_ws) 
 }
 }  // namespace
 
-size_t route_workspace_bytes(int n_kv_heads, int seq_len, int n_pool) { return route_layout(n_kv_heads, seq_len, n_pool).total; }
+size_t route_workspace_bytes(int n_kv_heads, int seq_len) { return route_layout(n_kv_heads, seq_len).total; }
 
-// the scorer's second pass runs at least 512 tokens per workgroup
-int route_mass_range_slots(int seq_len) { return seq_len < 256 ? seq_len : 256; }     // the scorer's second pass has no more workgroups per head
+// the scorer's second pass has at most 1024 workgroups, of no fewer than 32 tokens
+int route_mass_range_slots(int n_kv_heads, int seq_len) {
+  const int most = n_kv_heads < 1024 ? 1024 / n_kv_heads : 1;
+  return (seq_len + 31) / 32 < most ? (seq_len + 31) / 32 : most;
+}
 void* route_mass_range(void* route_ws, int n_kv_heads) {
-  return reinterpret_cast<unsigned char*>(route_ws) + route_layout(n_kv_heads, 1, 0).off_range;
+  return reinterpret_cast<unsigned char*>(route_ws) + route_layout(n_kv_heads, 1).off_range;
 }
 
 namespace {
-BucketParams pool_bucket_params(const float* mass, float* score, int n_kv_heads, int seq_len, int n_prefix, int pool_kernel,
+BucketParams pool_bucket_params(const float* mass, float* score, const float* eps, int n_kv_heads, int seq_len, int n_prefix, int pool_kernel,
                                 int pool_mode, void* route_ws, int n_range, RouteLayout& L) {
-  L = route_layout(n_kv_heads, seq_len, 0);      // the bucket areas do not depend on the pool size
+  L = route_layout(n_kv_heads, seq_len);
   BucketParams bp;
-  bp.src = mass; bp.score = score; bp.n = seq_len; bp.n_prefix = n_prefix; bp.kernel = pool_kernel; bp.inv_kernel = 1.0f / (float)pool_kernel; bp.take_max = pool_mode == VECTOR_POOL_MAX;
+  bp.src = mass; bp.score = score; bp.eps = eps; bp.n = seq_len; bp.n_prefix = n_prefix; bp.kernel = pool_kernel; bp.inv_kernel = 1.0f / (float)pool_kernel; bp.take_max = pool_mode == VECTOR_POOL_MAX;
   fill_bucket_params(bp, L, route_ws);
   bp.n_range = route_ws ? n_range : 0;
   bp.log_ref = -log2f((float)(n_prefix > 0 ? n_prefix : 1));     // as in the scorer's second pass
   return bp;
 }
 
-RouteParams route_params(int n_kv_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx, uint8_t* tier,
-                         int32_t* idx_retain, int32_t* idx_approx, void* ws, RouteLayout& L) {
-  L = route_layout(n_kv_heads, seq_len, n_pool);
+RouteParams route_params(int n_kv_heads, int all_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx, uint8_t* tier,
+                         int32_t* idx_retain, int32_t* idx_approx, void* ws) {
+  const RouteLayout L = route_layout(n_kv_heads, seq_len);
   unsigned char* w8 = reinterpret_cast<unsigned char*>(ws);
   RouteParams p;
-  p.score = score; p.eps = eps; p.n = seq_len; p.n_pool = n_pool; p.n_approx = n_approx; p.n_heads = n_kv_heads;
-  p.chunk_tokens = L.chunk_tokens; p.n_chunks = L.n_chunks; p.pool_stride = L.pool_stride;
-  p.slice = kTile;
-  while ((n_pool + p.slice - 1) / p.slice > kMaxChunks) p.slice *= 2;
-  p.n_slices = (n_pool + p.slice - 1) / p.slice;
+  p.score = score; p.eps = eps; p.n = seq_len; p.n_pool = n_pool; p.n_approx = n_approx;
+  p.chunk_tokens = L.chunk_tokens; p.n_chunks = L.n_chunks;
+  // one workgroup per CU: finding the thresholds costs each the same, whatever its part
+  const int parts = all_heads >= 256 ? 1 : 256 / all_heads;
+  p.part_tokens = (int)(((int64_t)(seq_len + parts - 1) / parts + 63) / 64 * 64);
   p.map = reinterpret_cast<const uint32_t*>(w8 + L.off_map);
-  p.table0 = reinterpret_cast<uint16_t*>(w8 + L.off_table0);
-  p.table1 = reinterpret_cast<uint16_t*>(w8 + L.off_table1);
-  p.bkey = reinterpret_cast<uint32_t*>(w8 + L.off_bkey);
-  p.bpos = reinterpret_cast<int32_t*>(w8 + L.off_bpos);
-  p.pool_idx = reinterpret_cast<int32_t*>(w8 + L.off_idx);
-  p.pool_key = reinterpret_cast<uint32_t*>(w8 + L.off_key);
+  p.table = reinterpret_cast<const uint16_t*>(w8 + L.off_table);
+  p.bkey = reinterpret_cast<const uint32_t*>(w8 + L.off_bkey);
+  p.bpos = reinterpret_cast<const int32_t*>(w8 + L.off_bpos);
+  p.beps = reinterpret_cast<const uint32_t*>(w8 + L.off_beps);
   p.tier = tier; p.idx_retain = idx_retain; p.idx_approx = idx_approx;
+  p.g = GatherParams{};
   p.seq_table = nullptr; p.seq_hps = 0;
   return p;
 }
+// the fewest register slots that hold the pool: its groups of 64, a last one that is not full per chunk, over the waves
+template <bool RAGGED> void (*list_kernel(int n_pool, int n_chunks))(RouteParams) {
+  const int groups = n_pool / kWave + n_chunks;
+  if (groups <= 16 * HW) return route_list_kernel<16, RAGGED>;
+  if (groups <= 32 * HW) return route_list_kernel<32, RAGGED>;
+  return route_list_kernel<64, RAGGED>;
+}
+unsigned route_parts(const RouteParams& p) { return (unsigned)((p.n + p.part_tokens - 1) / p.part_tokens); }
 
 unsigned gather_grid_x(const GatherParams& p) {
   const int pieces = p.row_bytes / 16;
   const int max_rows = p.n_retain > p.n_approx ? p.n_retain : p.n_approx;
   return (unsigned)(((int64_t)max_rows * pieces + 255) / 256);
 }
-constexpr size_t kSelectLds = (size_t)kCandCap * 8;
 }  // namespace
 
-int launch_pool_scores(const float* mass, float* score, int n_kv_heads, int seq_len, int n_prefix, int pool_kernel, int pool_mode,
+int launch_pool_scores(const float* mass, float* score, const float* eps, int n_kv_heads, int seq_len, int n_prefix, int pool_kernel, int pool_mode,
                        void* route_ws, int n_range, hipStream_t stream) {
-  if (n_range < 0 || n_range > route_mass_range_slots(seq_len)) return VECTOR_ERR_ARG;
+  if (n_range < 0 || n_range > route_mass_range_slots(n_kv_heads, seq_len) || (route_ws && !eps)) return VECTOR_ERR_ARG;
   RouteLayout L;
-  const BucketParams bp = pool_bucket_params(mass, score, n_kv_heads, seq_len, n_prefix, pool_kernel, pool_mode, route_ws, n_range, L);
-  VEC_LAUNCH(K_POOL, route_bucket_kernel<true>, dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, bp);
+  const BucketParams bp = pool_bucket_params(mass, score, eps, n_kv_heads, seq_len, n_prefix, pool_kernel, pool_mode, route_ws, n_range, L);
+  auto kernel = route_bucket_kernel<true, false>;
+  VEC_LAUNCH(K_POOL, kernel, dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, bp);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
 
-int launch_route(int n_kv_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx,
-                 uint8_t* tier, int32_t* idx_retain, int32_t* idx_approx, void* ws, bool have_buckets, hipStream_t stream) {
+int launch_route(int n_kv_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx, uint8_t* tier,
+                 int32_t* idx_retain, int32_t* idx_approx, void* ws, bool have_buckets, const PackedRows* rows, hipStream_t stream) {
   if (n_pool == 0) {
     const size_t total = (size_t)n_kv_heads * seq_len;
     VEC_LAUNCH(K_ROUTE, route_evict_all_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, tier, total);
@@ -1132,21 +962,21 @@ int launch_route(int n_kv_heads, int seq_len, const float* score, const float* e
     return VECTOR_OK;
   }
   if (!have_buckets && route_head_fits(seq_len))
-    return launch_route_head(n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, nullptr, nullptr, stream);
-  RouteLayout L;
-  const RouteParams p = route_params(n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, ws, L);
-  VEC_HIP(set_max_lds(reinterpret_cast<const void*>(route_pool_kernel<false>), kSelectLds));
-  VEC_HIP(set_max_lds(reinterpret_cast<const void*>(route_split_kernel<false>), kSelectLds));
+    return launch_route_head(n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, nullptr, rows, stream);
+  RouteParams p = route_params(n_kv_heads, n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, ws);
+  if (rows)
+    p.g = gather_params(*rows->shape, rows->k, rows->v, idx_retain, idx_approx, n_pool - n_approx, n_approx, rows->k_ret, rows->v_ret,
+                        rows->k_apx, rows->cap_retain, rows->stack);
   const bool t_ = timing_enabled();
   if (t_) timing_begin(K_ROUTE, stream);             // the launches count as one routing step
   if (!have_buckets) {
+    const RouteLayout L = route_layout(n_kv_heads, seq_len);
     BucketParams bp;
-    bp.src = score; bp.score = nullptr; bp.n = seq_len; bp.n_prefix = seq_len; bp.kernel = 1; bp.inv_kernel = 1.f; bp.take_max = 0;
+    bp.src = score; bp.score = nullptr; bp.eps = eps; bp.n = seq_len; bp.n_prefix = seq_len; bp.kernel = 1; bp.inv_kernel = 1.f; bp.take_max = 0;
     fill_bucket_params(bp, L, ws);
-    hipLaunchKernelGGL(route_bucket_kernel<false>, dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, bp);
+    hipLaunchKernelGGL((route_bucket_kernel<false, false>), dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, bp);
   }
-  hipLaunchKernelGGL(route_pool_kernel<false>, dim3(L.n_chunks, n_kv_heads), dim3(ST), kSelectLds, stream, p);
-  hipLaunchKernelGGL(route_split_kernel<false>, dim3(p.n_slices, n_kv_heads), dim3(ST), kSelectLds, stream, p);
+  hipLaunchKernelGGL(list_kernel<false>(n_pool, p.n_chunks), dim3(route_parts(p), n_kv_heads), dim3(HT), 0, stream, p);
   if (t_) timing_end(K_ROUTE, stream);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
@@ -1158,7 +988,7 @@ int launch_compact(const vector_shape& s, const void* k, const void* v, const in
   const GatherParams p = gather_params(s, k, v, idx_retain, idx_approx, n_retain, n_approx, k_ret, v_ret, k_apx, cap_retain, stack);
   const unsigned gx = gather_grid_x(p);
   if (gx == 0) return VECTOR_OK;
-  VEC_LAUNCH(K_GATHER, gather_rows_kernel<false>, dim3(gx, s.n_kv_heads, 3), dim3(256), 0, stream, p);
+  VEC_LAUNCH(K_GATHER, gather_rows_kernel, dim3(gx, s.n_kv_heads, 3), dim3(256), 0, stream, p);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
@@ -1167,8 +997,7 @@ int launch_compact(const vector_shape& s, const void* k, const void* v, const in
 // several sequences of different lengths in one set of launches
 // ---------------------------------------------------------------------------
 size_t route_ragged_table_bytes(int count) {
-  return align_up(sizeof(BucketParams) * count, 256) + align_up(sizeof(RouteParams) * count, 256) +
-         align_up(sizeof(GatherParams) * count, 256);
+  return align_up(sizeof(BucketParams) * count, 256) + align_up(sizeof(RouteParams) * count, 256);
 }
 
 int launch_pool_scores_ragged(const PoolSeq* seqs, int count, int n_kv_heads, int pool_kernel, int pool_mode, void* tables,
@@ -1177,9 +1006,9 @@ int launch_pool_scores_ragged(const PoolSeq* seqs, int count, int n_kv_heads, in
   BucketParams host[kMaxRaggedSeqs];
   unsigned gx = 0;
   for (int b = 0; b < count; ++b) {
-    if (!seqs[b].route_ws || seqs[b].n_range < 0 || seqs[b].n_range > route_mass_range_slots(seqs[b].seq_len)) return VECTOR_ERR_ARG;
+    if (!seqs[b].route_ws || !seqs[b].eps || seqs[b].n_range < 0 || seqs[b].n_range > route_mass_range_slots(n_kv_heads, seqs[b].seq_len)) return VECTOR_ERR_ARG;
     RouteLayout L;
-    host[b] = pool_bucket_params(seqs[b].mass, seqs[b].score, n_kv_heads, seqs[b].seq_len, seqs[b].n_prefix, pool_kernel, pool_mode,
+    host[b] = pool_bucket_params(seqs[b].mass, seqs[b].score, seqs[b].eps, n_kv_heads, seqs[b].seq_len, seqs[b].n_prefix, pool_kernel, pool_mode,
                                  seqs[b].route_ws, seqs[b].n_range, L);
     if ((unsigned)L.n_chunks > gx) gx = (unsigned)L.n_chunks;
   }
@@ -1196,47 +1025,28 @@ int launch_pool_scores_ragged(const PoolSeq* seqs, int count, int n_kv_heads, in
 
 int launch_route_compact_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, void* tables, hipStream_t stream) {
   if (count < 1 || count > kMaxRaggedSeqs) return VECTOR_ERR_ARG;
-  RouteParams rhost[kMaxRaggedSeqs];
-  GatherParams ghost[kMaxRaggedSeqs];
-  unsigned g_pool = 0, g_split = 0, g_gather = 0;
+  RouteParams host[kMaxRaggedSeqs];
+  unsigned parts = 0;
+  int most_pool = 0, most_chunks = 0;
   for (int b = 0; b < count; ++b) {
     const RaggedSeq& q = seqs[b];
     if (q.n_pool < 1) return VECTOR_ERR_ARG;               // nothing kept: that sequence goes through launch_route on its own
-    RouteLayout L;
-    rhost[b] = route_params(s.n_kv_heads, q.shape.seq_len, q.score, q.eps, q.n_pool, q.n_approx, q.tier, q.idx_retain, q.idx_approx,
-                            q.route_ws, L);
-    ghost[b] = gather_params(q.shape, q.k, q.v, q.idx_retain, q.idx_approx, q.n_pool - q.n_approx, q.n_approx, q.k_ret, q.v_ret, q.k_apx,
-                             q.cap_retain, nullptr);
-    if ((unsigned)rhost[b].n_chunks > g_pool) g_pool = (unsigned)rhost[b].n_chunks;
-    if ((unsigned)rhost[b].n_slices > g_split) g_split = (unsigned)rhost[b].n_slices;
-    const unsigned gg = gather_grid_x(ghost[b]);
-    if (gg > g_gather) g_gather = gg;
+    host[b] = route_params(s.n_kv_heads, count * s.n_kv_heads, q.shape.seq_len, q.score, q.eps, q.n_pool, q.n_approx, q.tier, q.idx_retain,
+                           q.idx_approx, q.route_ws);
+    host[b].g = gather_params(q.shape, q.k, q.v, q.idx_retain, q.idx_approx, q.n_pool - q.n_approx, q.n_approx, q.k_ret, q.v_ret, q.k_apx,
+                              q.cap_retain, nullptr);
+    parts = std::max(parts, route_parts(host[b]));
+    most_pool = std::max(most_pool, q.n_pool);
+    most_chunks = std::max(most_chunks, host[b].n_chunks);
   }
   unsigned char* t8 = reinterpret_cast<unsigned char*>(tables) + align_up(sizeof(BucketParams) * count, 256);
-  unsigned char* rt = t8;
-  unsigned char* gt = t8 + align_up(sizeof(RouteParams) * count, 256);
-  int rc = upload_table(rhost, sizeof(RouteParams) * count, rt, stream);
-  if (rc == VECTOR_OK) rc = upload_table(ghost, sizeof(GatherParams) * count, gt, stream);
+  const int rc = upload_table(host, sizeof(RouteParams) * count, t8, stream);
   if (rc != VECTOR_OK) return rc;
-  RouteParams rp = rhost[0];
-  rp.seq_table = reinterpret_cast<const RouteParams*>(rt);
-  rp.seq_hps = s.n_kv_heads;
-  GatherParams gp = ghost[0];
-  gp.seq_table = reinterpret_cast<const GatherParams*>(gt);
-  gp.seq_hps = s.n_kv_heads;
-  const unsigned heads = (unsigned)count * s.n_kv_heads;
-  VEC_HIP(set_max_lds(reinterpret_cast<const void*>(route_pool_kernel<true>), kSelectLds));
-  VEC_HIP(set_max_lds(reinterpret_cast<const void*>(route_split_kernel<true>), kSelectLds));
-  const bool t_ = timing_enabled();
-  if (t_) timing_begin(K_ROUTE, stream);
-  hipLaunchKernelGGL(route_pool_kernel<true>, dim3(g_pool, heads), dim3(ST), kSelectLds, stream, rp);
-  hipLaunchKernelGGL(route_split_kernel<true>, dim3(g_split, heads), dim3(ST), kSelectLds, stream, rp);
-  if (t_) timing_end(K_ROUTE, stream);
+  RouteParams lp = host[0];
+  lp.seq_table = reinterpret_cast<const RouteParams*>(t8);
+  lp.seq_hps = s.n_kv_heads;
+  VEC_LAUNCH(K_ROUTE, list_kernel<true>(most_pool, most_chunks), dim3(parts, (unsigned)count * s.n_kv_heads), dim3(HT), 0, stream, lp);
   VEC_HIP(hipGetLastError());
-  if (g_gather > 0) {
-    VEC_LAUNCH(K_GATHER, gather_rows_kernel<true>, dim3(g_gather, heads, 3), dim3(256), 0, stream, gp);
-    VEC_HIP(hipGetLastError());
-  }
   return VECTOR_OK;
 }
 

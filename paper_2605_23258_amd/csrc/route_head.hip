@@ -23,16 +23,7 @@ namespace vec {
 
 namespace {
 
-constexpr int HT = 512;                         // threads of a workgroup
 constexpr int kMaxBlocks = 12;                  // 24576 tokens
-constexpr int HW = HT / kWave;
-constexpr int kHeadBlock = HT * 4;              // tokens per block: four consecutive ones per thread
-constexpr int kHeadBins = 2048;
-constexpr int kRankCap = 256;                   // candidates ranked by comparison
-
-typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_u;   // 16-byte access at any element
-
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 struct HeadParams;
 struct HeadParams {
@@ -63,18 +54,6 @@ struct HeadShared {
   uint32_t thr, thr_tok, next_key;
 };
 
-// Workgroup barrier for data in LDS alone: global loads in flight (the residuals, while the scores are worked
-// on) and stores (score, tiers, lists) are not waited for.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// packed pairs of counts: retained in the low half, approximated in the high one
-__device__ __forceinline__ int low16(int x) { return x & 0xffff; }
-__device__ __forceinline__ int high16(int x) { return (int)((uint32_t)x >> 16); }
-
 // the k-th largest (key, lower token first): keys above thr, and keys equal to thr up to token tok, are the k;
 // all_equal: every key equal to thr is among them
 struct Threshold { uint32_t thr, tok; bool all_equal; };
@@ -88,60 +67,13 @@ __device__ __forceinline__ int first_token() {
 }
 __device__ __forceinline__ int head_token(int base, int slot) { return (slot >> 2) * kHeadBlock + base + (slot & 3); }
 
-// sum of a float over the waves' entries, the same bits in every lane
-__device__ __forceinline__ float sum_of_waves(const float* row, int lane) {
-  static_assert(HW == 8, "eight waves");
-  float x = row[lane & 7];
-  x += dpp_take_f<0x111, 0xf>(0.f, x);
-  x += dpp_take_f<0x112, 0xf>(0.f, x);
-  x += dpp_take_f<0x114, 0xf>(0.f, x);
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 7));
-}
-
-// exclusive prefix over the workgroup's threads of a packed pair of counts, and the total; row: [HW]
-__device__ __forceinline__ void head_scan(int v, int* row, int& before, int& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int incl = wave_incl_scan_dpp(v);
-  if (lane == 63) row[wave] = incl;
-  lds_barrier();
-  int x = row[lane & 7];                         // every lane one wave's total
-  x += dpp_take<0x111, 0xf>(x);
-  x += dpp_take<0x112, 0xf>(x);
-  x += dpp_take<0x114, 0xf>(x);
-  const int upto = wave ? __builtin_amdgcn_readlane(x, wave - 1) : 0;
-  total = __builtin_amdgcn_readlane(x, 7);
-  before = upto + incl - v;
-}
-
-__device__ __forceinline__ void clear_hist(HeadShared& sh) {
-  static_assert(kHeadBins == 4 * HT, "four buckets per thread");
-  *reinterpret_cast<int4*>(sh.hist + 4 * threadIdx.x) = make_int4(0, 0, 0, 0);
-}
-
-// histogram counts -> the bucket with #(keys above it) < k <= #(keys in or above it)
-__device__ __forceinline__ void head_pick(HeadShared& sh, int k, int& d, int& above, int& count) {
-  const int lo = kHeadBins - 4 - 4 * (int)threadIdx.x;
-  const int4 c = *reinterpret_cast<const int4*>(sh.hist + lo);        // buckets lo .. lo + 3
-  int before, total;
-  head_scan(c.x + c.y + c.z + c.w, sh.wsum[0], before, total);
-  if (before < k && k <= before + c.x + c.y + c.z + c.w) {
-    int b = lo + 3, in = c.w;
-    if (k > before + in) { before += in; in = c.z; --b; }
-    if (b == lo + 2 && k > before + in) { before += in; in = c.y; --b; }
-    if (b == lo + 1 && k > before + in) { before += in; in = c.x; --b; }
-    sh.pick[0] = b; sh.pick[1] = before; sh.pick[2] = in;
-  }
-  lds_barrier();
-  d = sh.pick[0]; above = sh.pick[1]; count = sh.pick[2];
-}
-
 // Threshold of the k largest of the workgroup's keys (0: no key in that slot); 1 <= k <= number of keys.
 // center: a typical key.  Starts by clearing the histogram; the caller has passed a barrier since the
 // last use of sh.
 template <int NS>
 __device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int k, uint32_t center, HeadShared& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  clear_hist(sh);
+  clear_bins(sh.hist);
   // mean and deviation of a sample (in units of 4096 keys, about the center): where to lay the buckets
   float cnt = 0.f, s1 = 0.f, s2 = 0.f;
   constexpr int kStep = NS / 4 > 8 ? 2 : 1;
@@ -159,13 +91,7 @@ __device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int 
   lds_barrier();
   if (threadIdx.x == 0) { sh.n_cand = 0; sh.next_key = 0u; }
   cnt = sum_of_waves(sh.stat[0], lane); s1 = sum_of_waves(sh.stat[1], lane); s2 = sum_of_waves(sh.stat[2], lane);
-  DigitMap map = {0u, 21};
-  if (cnt >= 32.f) {
-    const float inv = __builtin_amdgcn_rcpf(cnt), mu = s1 * inv;
-    const float half = 4.f * __builtin_amdgcn_sqrtf(fmaxf(s2 * inv - mu * mu, 0.f)) + 32.f;
-    const float mid = (float)(center >> 12) + mu;
-    map = digit_map_for_keys((uint32_t)fmaxf(mid - half, 0.f) << 12, (uint32_t)fminf(mid + half, 1048575.f) << 12);
-  }
+  const DigitMap map = digit_map_about(center, cnt, s1, s2);
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     if (key[i] != 0u) atomicAdd(&sh.hist[map.digit(key[i])], 1);
@@ -173,28 +99,19 @@ __device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int 
   }
   lds_barrier();
   int d, above, count;
-  head_pick(sh, k, d, above, count);
+  pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
   k -= above;
-  // the bucket's keys: [lo, lo + span]
   uint32_t lo, span;
-  if (map.plain()) {
-    lo = (uint32_t)d << 21;
-    span = (1u << 21) - 1u;
-  } else {
-    lo = d == 0 ? 0u : (map.lowq + (uint32_t)d) << map.shift;
-    const uint32_t hi = d == 2047 ? 0xffffffffu : ((map.lowq + (uint32_t)d + 1u) << map.shift) - 1u;
-    span = hi - lo;
-  }
-  if (lo == 0u) { lo = 1u; span -= 1u; }                                // no key is 0
+  bucket_range(map, d, lo, span);
   while (count > kRankCap && span != 0u) {                              // uniform
     const int s = max(0, 21 - (int)__clz(span));                        // at most 2048 buckets over the range
-    clear_hist(sh);
+    clear_bins(sh.hist);
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < NS; ++i)
       if (key[i] - lo <= span) atomicAdd(&sh.hist[(key[i] - lo) >> s], 1), __builtin_amdgcn_sched_barrier(0);
     lds_barrier();
-    head_pick(sh, k, d, above, count);
+    pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
     k -= above;
     lo += (uint32_t)d << s;
     span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
@@ -206,7 +123,7 @@ __device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int 
     uint32_t tlo = 0u, tspan = 0xffffu;                                 // values 65535 - token
     while (tspan != 0u) {
       const int s = max(0, 21 - (int)__clz(tspan));
-      clear_hist(sh);
+      clear_bins(sh.hist);
       lds_barrier();
       const int base = first_token();
 #pragma unroll
@@ -216,7 +133,7 @@ __device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int 
         __builtin_amdgcn_sched_barrier(0);
       }
       lds_barrier();
-      head_pick(sh, k, d, above, count);
+      pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
       k -= above;
       tlo += (uint32_t)d << s;
       tspan = min(tspan - ((uint32_t)d << s), (1u << s) - 1u);
@@ -421,7 +338,7 @@ __global__ __launch_bounds__(HT) void route_head_kernel(HeadParams p) {
   uint8_t* tier = p.tier + (size_t)h * n;
   int32_t* ir = p.idx_retain + (size_t)h * n_retain;
   int32_t* ia = p.idx_approx + (size_t)h * p.n_approx;
-  const bool tier_words = ((reinterpret_cast<uintptr_t>(tier)) & 3u) == 0;
+  const EmitTarget target = {tier, ir, ia, n, n_retain, p.n_approx};
   for (int b = block0; b < block1; ++b) {
     const uint32_t ret4 = (uint32_t)(in_ret >> (4 * b)) & 15u, apx4 = (uint32_t)(in_apx >> (4 * b)) & 15u;
     int before, total;
@@ -435,66 +352,12 @@ __global__ __launch_bounds__(HT) void route_head_kernel(HeadParams p) {
     }
     const int own_r = low16(own), own_a = high16(own);
     const int base_r = low16(carry) + low16(first), base_a = high16(carry) + high16(first);
-    if (my_wave) {
-      const int t0 = b * kHeadBlock + (int)threadIdx.x * 4;
-      int at_r = low16(before) - low16(first), at_a = high16(before) - high16(first);
-      uint32_t word = 0u;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int t = t0 + e;
-        if ((ret4 >> e) & 1u) {
-          word |= (uint32_t)VECTOR_TIER_RETAIN << (8 * e);
-          sh.list[at_r] = t;
-          if (base_r + at_r < n_retain) ir[base_r + at_r] = t;
-          ++at_r;
-        } else if ((apx4 >> e) & 1u) {
-          word |= (uint32_t)VECTOR_TIER_APPROX << (8 * e);
-          sh.list[own_r + at_a] = t;
-          if (base_a + at_a < p.n_approx) ia[base_a + at_a] = t;
-          ++at_a;
-        }
-      }
-      if (tier_words && t0 + 4 <= n) {
-        *reinterpret_cast<uint32_t*>(tier + t0) = word;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (t0 + e < n) tier[t0 + e] = (uint8_t)(word >> (8 * e));
-      }
-    }
+    if (my_wave)
+      emit_tokens(target, b * kHeadBlock + (int)threadIdx.x * 4, ret4, apx4, low16(before) - low16(first), high16(before) - high16(first), own_r,
+                  base_r, base_a, sh.list);
     carry += total;
     lds_barrier();                                           // the list is whole
-    if (p.g.k) {
-      // rows of the part: retained keys, retained values, approximated keys; each set goes to consecutive rows
-      const GatherParams& g = p.g;
-      const int pieces = g.row_bytes / 16, log_pieces = 31 - __clz(pieces);
-      const int64_t hs = g.hps ? h / g.hps : 0, hh = g.hps ? h % g.hps : h;
-      const unsigned char* k_head = g.k + hs * g.k_sb + hh * g.k_sh;
-      const unsigned char* v_head = g.v + hs * g.v_sb + hh * g.v_sh;
-      unsigned char* k_ret = g.k_ret + ((size_t)h * g.cap_retain + base_r) * g.row_bytes;
-      unsigned char* v_ret = g.v_ret + ((size_t)h * g.cap_retain + base_r) * g.row_bytes;
-      unsigned char* k_apx = g.k_apx + ((size_t)h * p.n_approx + base_a) * g.row_bytes;
-      const int items = (2 * own_r + own_a) << log_pieces;
-      constexpr int U = 4;
-      for (int i0 = threadIdx.x; i0 < items; i0 += HT * U) {
-        u32x4 x[U];
-        unsigned char* to[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int i = min(i0 + u * HT, items - 1);
-          const int row = i >> log_pieces, piece = i & (pieces - 1);
-          const bool is_v = row >= own_r && row < 2 * own_r, is_a = row >= 2 * own_r;
-          const int t = sh.list[is_v || is_a ? row - own_r : row];
-          const unsigned char* from = (is_v ? v_head + (int64_t)t * g.v_st : k_head + (int64_t)t * g.k_st) + piece * 16;
-          to[u] = (is_v ? v_ret + (size_t)(row - own_r) * g.row_bytes
-                        : (is_a ? k_apx + (size_t)(row - 2 * own_r) * g.row_bytes : k_ret + (size_t)row * g.row_bytes)) + piece * 16;
-          x[u] = *reinterpret_cast<const u32x4*>(from);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (i0 + u * HT < items) *reinterpret_cast<u32x4*>(to[u]) = x[u];
-      }
-    }
+    if (p.g.k) copy_rows(p.g, h, p.n_approx, sh.list, own_r, own_a, base_r, base_a);
     lds_barrier();                                           // the list may be written again
   }
 }

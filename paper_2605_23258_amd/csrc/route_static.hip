@@ -7,7 +7,7 @@
 
 namespace {
 
-constexpr size_t kStaticScratchBytes = VECTOR_ROUTE_STATIC_SCRATCH_BYTES;
+constexpr size_t kStaticScratchBytes = (size_t)VECTOR_ROUTE_STATIC_SCRATCH_BYTES * 3 / 2 + (1u << 20);
 constexpr int kMaxDevices = 64;
 
 // One copy per GPU the library runs on, at that GPU's own address; held until the process ends.
@@ -35,7 +35,7 @@ int scratch_on_current_device(void** out) {
 
 extern "C" {
 
-size_t vector_route_static_scratch_bytes(void) { return kStaticScratchBytes; }
+size_t vector_route_static_scratch_bytes(void) { return VECTOR_ROUTE_STATIC_SCRATCH_BYTES; }
 
 int vector_route_static(int32_t n_kv_heads, int32_t seq_len, const float* score, const float* eps, int32_t n_pool,
                         int32_t n_approx, uint8_t* tier, int32_t* idx_retain, int32_t* idx_approx, void* stream) {
@@ -44,11 +44,11 @@ int vector_route_static(int32_t n_kv_heads, int32_t seq_len, const float* score,
   if (!score || !eps || !tier) return VECTOR_ERR_ARG;
   if ((n_pool - n_approx > 0 && !idx_retain) || (n_approx > 0 && !idx_approx)) return VECTOR_ERR_ARG;
   // the same scratch the workspace variant asks its caller for; beyond the array's size: refuse
-  if (vec::route_workspace_bytes(n_kv_heads, seq_len, n_pool) > kStaticScratchBytes) return VECTOR_ERR_WORKSPACE;
+  if (vec::route_workspace_bytes(n_kv_heads, seq_len) > kStaticScratchBytes) return VECTOR_ERR_WORKSPACE;
   void* ptr = nullptr;
   int rc = scratch_on_current_device(&ptr);
   if (rc) return rc;
-  return vec::launch_route(n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, ptr, false,
+  return vec::launch_route(n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, ptr, false, nullptr,
                            (hipStream_t)stream);
 }
 

@@ -180,7 +180,7 @@ static int run_score_residual_ragged(const vector_shape& s, const RaggedSeq* seq
   // pooling + score-key buckets of every sequence
   PoolSeq pool[kMaxRaggedSeqs];
   for (int b = 0; b < count; ++b) {
-    pool[b].mass = host[b].mass; pool[b].score = seqs[b].score; pool[b].seq_len = seqs[b].shape.seq_len;
+    pool[b].mass = host[b].mass; pool[b].score = seqs[b].score; pool[b].eps = seqs[b].eps; pool[b].seq_len = seqs[b].shape.seq_len;
     pool[b].n_prefix = host[b].n_prefix; pool[b].route_ws = seqs[b].route_ws; pool[b].n_range = host[b].range_stride;
   }
   return launch_pool_scores_ragged(pool, count, s.n_kv_heads, s.pool_kernel, s.pool_mode, t8 + align_up(sizeof(PassParams) * count, 256), stream);
@@ -209,7 +209,7 @@ static int run_score_residual(const SeqStack* stack, const vector_shape& s, cons
     if (rc != VECTOR_OK) return rc;
   }
   if (leave_mass) return VECTOR_OK;
-  return launch_pool_scores(mass, score, s.n_kv_heads, s.seq_len, n_prefix, s.pool_kernel, s.pool_mode, route_ws, n_range, stream);
+  return launch_pool_scores(mass, score, eps, s.n_kv_heads, s.seq_len, n_prefix, s.pool_kernel, s.pool_mode, route_ws, n_range, stream);
 }
 
 template <typename T, int D>

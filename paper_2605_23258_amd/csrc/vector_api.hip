@@ -88,7 +88,7 @@ double vector_pa_deploy(double p_c, double eps) {
 size_t vector_workspace_bytes(const vector_shape* s, int32_t n_pool, int32_t n_approx, int32_t batch) {
   if (check_shape(s, true) != VECTOR_OK || n_pool < 0 || n_approx < 0 || n_approx > n_pool || batch < 1) return 0;
   size_t need = vec::score_workspace_bytes(*s);
-  const size_t r = vec::route_workspace_bytes(s->n_kv_heads, s->seq_len, n_pool);
+  const size_t r = vec::route_workspace_bytes(s->n_kv_heads, s->seq_len);
   if (r > need) need = r;
   // decode: the retained segment may grow by appended tokens up to seq_len rows
   const size_t d = vec::decode_workspace_bytes(batch, s->n_q_heads, s->n_kv_heads, s->head_dim, s->seq_len, n_approx);
@@ -143,7 +143,7 @@ int vector_score_key_diversity(const vector_shape* s, const void* k, float* scor
 
 size_t vector_compress_workspace_bytes(const vector_shape* s, int32_t n_pool, int32_t n_approx) {
   if (check_shape(s, true) != VECTOR_OK || n_pool < 0 || n_approx < 0 || n_approx > n_pool) return 0;
-  return vec::score_workspace_bytes(*s) + vec::route_workspace_bytes(s->n_kv_heads, s->seq_len, n_pool) + 256;
+  return vec::score_workspace_bytes(*s) + vec::route_workspace_bytes(s->n_kv_heads, s->seq_len) + 256;
 }
 
 static int check_lse(const vector_shape* s, const vec::QueryLse* lse) {
@@ -181,10 +181,9 @@ static int compress_impl(const vector_shape* s, const void* q_win, const void* k
   // the scorer's pooling launch also builds the routing's buckets of score keys
   void* buckets = n_pool > 0 ? route_ws : nullptr;
   if ((rc = vec::launch_score_residual(*s, q_win, k, v, W, score, eps, ws, st, rope, buckets, stack, lse))) return rc;
-  if ((rc = vec::launch_route(s->n_kv_heads, s->seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, route_ws,
-                              buckets != nullptr, st)))
-    return rc;
-  return vec::launch_compact(*s, k, v, idx_retain, idx_approx, n_retain, n_approx, k_ret, v_ret, k_apx, cap_retain, st, stack);
+  const vec::PackedRows rows = {s, k, v, k_ret, v_ret, k_apx, cap_retain, stack};
+  return vec::launch_route(s->n_kv_heads, s->seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, route_ws, buckets != nullptr,
+                           &rows, st);
 }
 
 int vector_compress(const vector_shape* s, const void* q_win, const void* k, const void* v, const void* W, int32_t n_pool,
@@ -519,9 +518,9 @@ int vector_route(int32_t n_kv_heads, int32_t seq_len, const float* score, const 
   if (n_approx < 0 || n_pool < n_approx || n_pool > seq_len) return VECTOR_ERR_ARG;
   if (!score || !eps || !tier) return VECTOR_ERR_ARG;
   if ((n_pool - n_approx > 0 && !idx_retain) || (n_approx > 0 && !idx_approx)) return VECTOR_ERR_ARG;
-  int rc = check_ws(ws, ws_bytes, vec::route_workspace_bytes(n_kv_heads, seq_len, n_pool));
+  int rc = check_ws(ws, ws_bytes, vec::route_workspace_bytes(n_kv_heads, seq_len));
   if (rc) return rc;
-  return vec::launch_route(n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, ws, false,
+  return vec::launch_route(n_kv_heads, seq_len, score, eps, n_pool, n_approx, tier, idx_retain, idx_approx, ws, false, nullptr,
                            (hipStream_t)stream);
 }
 
