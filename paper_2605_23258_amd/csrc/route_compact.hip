@@ -421,7 +421,7 @@ struct ListShared {
   int front[kMaxChunks], group_start[kMaxChunks], cand_start[kMaxChunks];
   int n_groups;
   int2 group[kMaxGroups];                // the first groups: place of the first entry in the head's lists, number of entries
-  uint32_t cand[kRankCap];
+  __align__(16) uint32_t cand[kRankCap];
   int wsum[3][HW];
   float stat[3][HW];
   uint32_t center[2];
@@ -443,16 +443,21 @@ __device__ __forceinline__ void pick_from_tables(const uint16_t* tables, int n_c
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lo = kBins - 4 - 4 * (int)threadIdx.x;
   int s_lo = 0;
-  bool first = true;
-  constexpr int kInFlight = 16;                 // chunks requested together: one trip to memory for up to 16 of them
-  for (int c = 0; c < n_chunks; c += kInFlight) {
-    uint16_t e[kInFlight];
+  uint16_t e[2][kMaxChunks / 2];                // all chunks' entries requested together
 #pragma unroll
-    for (int u = 0; u < kInFlight; ++u) e[u] = tables[(size_t)min(c + u, n_chunks - 1) * kTableStride + lo];
-    if (first) { prefetch(); first = false; }
+  for (int u = 0; u < kMaxChunks / 2; ++u) e[0][u] = tables[(size_t)min(u, n_chunks - 1) * kTableStride + lo];
+  if (n_chunks > kMaxChunks / 2) {              // uniform
 #pragma unroll
-    for (int u = 0; u < kInFlight; ++u)
-      if (c + u < n_chunks) s_lo += (int)e[u];
+    for (int u = 0; u < kMaxChunks / 2; ++u) e[1][u] = tables[(size_t)min(kMaxChunks / 2 + u, n_chunks - 1) * kTableStride + lo];
+  }
+  prefetch();
+#pragma unroll
+  for (int u = 0; u < kMaxChunks / 2; ++u)
+    if (u < n_chunks) s_lo += (int)e[0][u];
+  if (n_chunks > kMaxChunks / 2) {
+#pragma unroll
+    for (int u = 0; u < kMaxChunks / 2; ++u)
+      if (kMaxChunks / 2 + u < n_chunks) s_lo += (int)e[1][u];
   }
   sh.coarse[threadIdx.x + 1] = s_lo;            // coarse[t + 1] = S[2044 - 4t]; coarse[0] = S[2048] = 0
   if (threadIdx.x == 0) { sh.coarse[0] = 0; sh.pick[0] = 0; }       // no bracket (k outside the counts): the second step still reads inside the tables
@@ -537,6 +542,7 @@ __device__ __forceinline__ Cut list_select(const uint32_t (&key)[NS], More more,
   int count = total;
   uint32_t lo = 1u, span = 0xfffffffeu;
   if (threadIdx.x == 0) sh.n_cand = 0;
+  if ((int)threadIdx.x < kRankCap) sh.cand[threadIdx.x] = 0u;
   if (total > kRankCap) {                                               // uniform
     clear_bins(sh.hist);
     lds_barrier();
@@ -580,8 +586,14 @@ __device__ __forceinline__ Cut list_select(const uint32_t (&key)[NS], More more,
   if ((int)threadIdx.x < count) {
     const uint32_t mine = sh.cand[threadIdx.x];
     int greater = 0, equal = 0;
-#pragma unroll 4
-    for (int j = 0; j < count; ++j) { greater += sh.cand[j] > mine; equal += sh.cand[j] == mine; }
+    for (int j = 0; j < count; j += 16) {                               // the rest of the list is 0: below every key
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint4 x = *reinterpret_cast<const uint4*>(sh.cand + j + 4 * q);
+        greater += (x.x > mine) + (x.y > mine) + (x.z > mine) + (x.w > mine);
+        equal += (x.x == mine) + (x.y == mine) + (x.z == mine) + (x.w == mine);
+      }
+    }
     if (greater < k && k <= greater + equal) { sh.thr = mine; sh.quota = k - greater; sh.equal = equal; }     // the same values from every thread that finds it
   }
   lds_barrier();
