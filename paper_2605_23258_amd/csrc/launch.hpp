@@ -134,7 +134,7 @@ int launch_compact(const vector_shape& s, const void* k, const void* v, const in
                    const int32_t* idx_approx, int n_retain, int n_approx, void* k_ret, void* v_ret, void* k_apx,
                    int cap_retain, hipStream_t stream, const SeqStack* stack = nullptr);
 
-// Routing and compaction of heads of up to 24576 tokens in one launch (route_head.hip).
+// Routing and compaction of heads of up to 16384 tokens in one launch (route_head.hip).
 bool route_head_fits(int seq_len);
 bool route_head_pools(int pool_kernel);         // whether it can form the pooled score itself
 struct HeadPool { const float* mass; float* score; int n_prefix, kernel, mode; };

@@ -5,11 +5,11 @@
 // The chain of selections is latency: with the pieces of a head spread over workgroups, every exchange
 // between them is a kernel boundary, and the boundaries (bucket tables, pool list, split, gather: four
 // launches of 4-12 us whatever the size) cost more than the work.  So nothing is exchanged.  Every workgroup
-// of a head loads the head's scores and residuals whole into registers (24576 tokens: 48 + 48 per thread) and
+// of a head loads the head's scores and residuals whole into registers (16384 tokens: 32 + 32 per thread) and
 // finds both thresholds itself; then it emits and copies its own part of the tokens.  The redundant part
-// is about 50 vector instructions and two LDS atomics per token and workgroup: a workgroup lives 13 us at 8192 tokens,
-// 27 at 20000, 37 at 32768, against 34, 38 and 41 us for the four launches (8 heads).  There lies the line to
-// the launches of route_compact.hip.
+// is about 50 vector instructions and two LDS atomics per token and workgroup: 16 us at 8192 tokens x 8 heads, 25
+// at 12289, 31 at 20011, against 29 and 28 us for the two launches of route_compact.hip at the last two.  There lies the line
+// between them.
 //
 // A selection finds the k-th largest of the keys in registers: one LDS histogram over buckets laid
 // where a sample says that the keys lie (DigitMap), then the keys of the bucket that holds it are ranked
@@ -23,7 +23,7 @@ namespace vec {
 
 namespace {
 
-constexpr int kMaxBlocks = 12;                  // 24576 tokens
+constexpr int kMaxBlocks = 8;                   // 16384 tokens
 
 struct HeadParams;
 struct HeadParams {
@@ -384,8 +384,7 @@ void (*head_kernel(int n_blocks))(HeadParams) {
   if (n_blocks <= 1) return route_head_kernel<1, POOL, RAGGED>;
   if (n_blocks <= 2) return route_head_kernel<2, POOL, RAGGED>;
   if (n_blocks <= 4) return route_head_kernel<4, POOL, RAGGED>;
-  if (n_blocks <= 8) return route_head_kernel<8, POOL, RAGGED>;
-  return route_head_kernel<12, POOL, RAGGED>;
+  return route_head_kernel<8, POOL, RAGGED>;
 }
 
 HeadParams head_params(const float* mass, const float* score_in, float* score_out, const float* eps, int n, int n_prefix, int pool_kernel,

@@ -21,7 +21,7 @@ KINDS = {
 
 
 @pytest.mark.parametrize("n,heads", [(1, 1), (2, 3), (5, 1), (255, 2), (256, 1), (257, 3), (2047, 2), (2048, 1), (2049, 2), (4100, 40),
-                                     (16385, 3), (24575, 1), (24576, 2), (24577, 1)])
+                                     (16384, 2), (16385, 3), (24575, 1), (24576, 2), (24577, 1)])
 @pytest.mark.parametrize("kind", list(KINDS))
 def test_route_at_block_edges(n, heads, kind):
     rng = np.random.default_rng(n * 31 + heads)
