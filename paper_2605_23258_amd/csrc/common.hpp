@@ -83,6 +83,21 @@ __device__ __forceinline__ void xcd_chunk_head(int& chunk, int& h) {
   }
 }
 
+// RAGGED launches (several sequences of different lengths at once): launch head hv is head hv % seq_hps of sequence
+// hv / seq_hps, whose parameter block replaces the launch's own.  It is read with scalar loads, from behind
+// the launch's own parameters (the first kernel argument) or from a table that an earlier launch wrote.
+template <bool RAGGED, typename P>
+__device__ __forceinline__ void take_sequence(P& p, int& h) {
+  if constexpr (RAGGED) {
+    typedef const __attribute__((address_space(4))) unsigned char* bytes;
+    const int seq = h / p.seq_hps;
+    h -= seq * p.seq_hps;
+    bytes table = p.seq_table ? (bytes)(const unsigned char*)p.seq_table
+                              : (bytes)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(P);
+    __builtin_memcpy(&p, (const unsigned char*)(table + (size_t)seq * sizeof(P)), sizeof(P));
+  }
+}
+
 __device__ __forceinline__ chunk_t load_chunk(const void* p) { return *reinterpret_cast<const chunk_t*>(p); }
 
 // acc += A(32 x chunk) * B(chunk x 32): a holds rows of the M side, b rows of the N side.

@@ -92,9 +92,32 @@ int launch_pool_scores_ragged(const PoolSeq* seqs, int count, int n_kv_heads, in
                               hipStream_t stream);
 // tables: the part of the table area after the scorer's
 int launch_route_compact_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, void* tables, hipStream_t stream);
+// The first argument of every kernel with a ragged variant: its own parameters, and in that variant the sequences'
+// parameter blocks behind them.  As arguments they are there when the launch starts; as a table in memory they took a
+// copy launch of 4.6 us each.  More sequences than fit go through a table (P::seq_table).
+template <typename P> constexpr int kInlineSeqs = (3400 - (int)sizeof(P)) / (int)sizeof(P);      // arguments stay under 4 KB
+template <typename P, bool RAGGED> struct KernelArgs { P p; };
+template <typename P> struct KernelArgs<P, true> { P p; P seq[kInlineSeqs<P>]; };
+
 // host bytes -> device memory in stream order, as kernel arguments of small copy launches (no
 // host buffer has to outlive the call, and the copies can be captured into a graph)
 int upload_table(const void* host, size_t bytes, void* dev, hipStream_t stream);
+
+// the arguments of a ragged launch for `count` blocks of `heads` heads each; table: where they go if they are too many
+template <typename P>
+int ragged_args(const P* host, int count, int heads, void* table, hipStream_t stream, KernelArgs<P, true>& a) {
+  a.p = host[0];
+  a.p.seq_hps = heads;
+  a.p.seq_table = nullptr;
+  if (count <= kInlineSeqs<P>) {
+    for (int i = 0; i < count; ++i) a.seq[i] = host[i];
+    for (int i = count; i < kInlineSeqs<P>; ++i) a.seq[i] = host[0];
+    return VECTOR_OK;
+  }
+  a.p.seq_table = reinterpret_cast<const P*>(table);
+  for (int i = 0; i < kInlineSeqs<P>; ++i) a.seq[i] = host[0];
+  return upload_table(host, sizeof(P) * count, table, stream);
+}
 
 int launch_residual_probe(const vector_shape& s, const void* k, const void* v, const void* W, float* eps, int repeat,
                           hipStream_t stream);

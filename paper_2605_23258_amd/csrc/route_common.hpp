@@ -98,17 +98,6 @@ __device__ __forceinline__ int wave_incl_scan_dpp(int v) {
 __device__ __forceinline__ int wave_total_of_scan(int incl) { return __builtin_amdgcn_readlane(incl, 63); }
 
 
-// RAGGED launches (several sequences of different lengths at once): launch head hv is head
-// hv % seq_hps of sequence hv / seq_hps, whose parameter block replaces the launch's own
-template <bool RAGGED, typename P>
-__device__ __forceinline__ void take_sequence(P& p, int& h) {
-  if constexpr (RAGGED) {
-    const int seq = h / p.seq_hps;
-    h -= seq * p.seq_hps;
-    p = p.seq_table[seq];
-  }
-}
-
 // Average pooling ends in sum / kernel: the quotient through the reciprocal and one correction, which is
 // the correctly rounded one (three instructions instead of the ten of a division).
 __device__ __forceinline__ float pool_mean(float sum, float kernel, float inv_kernel) {

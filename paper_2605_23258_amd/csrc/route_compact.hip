@@ -158,7 +158,8 @@ struct BucketParams {
 };
 
 template <bool POOL, bool RAGGED = false>
-__global__ __launch_bounds__(BT) void route_bucket_kernel(BucketParams p) {
+__global__ __launch_bounds__(BT) void route_bucket_kernel(KernelArgs<BucketParams, RAGGED> args) {
+  BucketParams p = args.p;
   int chunk, h;
   xcd_chunk_head(chunk, h);
   take_sequence<RAGGED>(p, h);
@@ -627,7 +628,8 @@ constexpr int kCandSlots = 4;            // candidates per thread kept in regist
 
 // SLOTS: pool members per thread kept in registers (the rest are read again for every pass over them)
 template <int SLOTS, bool RAGGED>
-__global__ __launch_bounds__(HT) void route_list_kernel(RouteParams p) {
+__global__ __launch_bounds__(HT) void route_list_kernel(KernelArgs<RouteParams, RAGGED> args) {
+  RouteParams p = args.p;
   int part, h;
   xcd_chunk_head(part, h);
   take_sequence<RAGGED>(p, h);
@@ -939,7 +941,7 @@ RouteParams route_params(int n_kv_heads, int all_heads, int seq_len, const float
   return p;
 }
 // the fewest register slots that hold the pool: its groups of 64, a last one that is not full per chunk, over the waves
-template <bool RAGGED> void (*list_kernel(int n_pool, int n_chunks))(RouteParams) {
+template <bool RAGGED> void (*list_kernel(int n_pool, int n_chunks))(KernelArgs<RouteParams, RAGGED>) {
   const int groups = n_pool / kWave + n_chunks;
   if (groups <= 16 * HW) return route_list_kernel<16, RAGGED>;
   if (groups <= 32 * HW) return route_list_kernel<32, RAGGED>;
@@ -960,7 +962,7 @@ int launch_pool_scores(const float* mass, float* score, const float* eps, int n_
   RouteLayout L;
   const BucketParams bp = pool_bucket_params(mass, score, eps, n_kv_heads, seq_len, n_prefix, pool_kernel, pool_mode, route_ws, n_range, L);
   auto kernel = route_bucket_kernel<true, false>;
-  VEC_LAUNCH(K_POOL, kernel, dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, bp);
+  VEC_LAUNCH(K_POOL, kernel, dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, KernelArgs<BucketParams, false>{bp});
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
@@ -986,9 +988,9 @@ int launch_route(int n_kv_heads, int seq_len, const float* score, const float* e
     BucketParams bp;
     bp.src = score; bp.score = nullptr; bp.eps = eps; bp.n = seq_len; bp.n_prefix = seq_len; bp.kernel = 1; bp.inv_kernel = 1.f; bp.take_max = 0;
     fill_bucket_params(bp, L, ws);
-    hipLaunchKernelGGL((route_bucket_kernel<false, false>), dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, bp);
+    hipLaunchKernelGGL((route_bucket_kernel<false, false>), dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, KernelArgs<BucketParams, false>{bp});
   }
-  hipLaunchKernelGGL(list_kernel<false>(n_pool, p.n_chunks), dim3(route_parts(p), n_kv_heads), dim3(HT), 0, stream, p);
+  hipLaunchKernelGGL(list_kernel<false>(n_pool, p.n_chunks), dim3(route_parts(p), n_kv_heads), dim3(HT), 0, stream, KernelArgs<RouteParams, false>{p});
   if (t_) timing_end(K_ROUTE, stream);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
@@ -1024,13 +1026,11 @@ int launch_pool_scores_ragged(const PoolSeq* seqs, int count, int n_kv_heads, in
                                  seqs[b].route_ws, seqs[b].n_range, L);
     if ((unsigned)L.n_chunks > gx) gx = (unsigned)L.n_chunks;
   }
-  const int rc = upload_table(host, sizeof(BucketParams) * count, tables, stream);
+  KernelArgs<BucketParams, true> args;
+  const int rc = ragged_args(host, count, n_kv_heads, tables, stream, args);
   if (rc != VECTOR_OK) return rc;
-  BucketParams lp = host[0];
-  lp.seq_table = reinterpret_cast<const BucketParams*>(tables);
-  lp.seq_hps = n_kv_heads;
   auto kernel = route_bucket_kernel<true, true>;
-  VEC_LAUNCH(K_POOL, kernel, dim3(gx, (unsigned)count * n_kv_heads), dim3(BT), 0, stream, lp);
+  VEC_LAUNCH(K_POOL, kernel, dim3(gx, (unsigned)count * n_kv_heads), dim3(BT), 0, stream, args);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
@@ -1052,12 +1052,10 @@ int launch_route_compact_ragged(const vector_shape& s, const RaggedSeq* seqs, in
     most_chunks = std::max(most_chunks, host[b].n_chunks);
   }
   unsigned char* t8 = reinterpret_cast<unsigned char*>(tables) + align_up(sizeof(BucketParams) * count, 256);
-  const int rc = upload_table(host, sizeof(RouteParams) * count, t8, stream);
+  KernelArgs<RouteParams, true> args;
+  const int rc = ragged_args(host, count, s.n_kv_heads, t8, stream, args);
   if (rc != VECTOR_OK) return rc;
-  RouteParams lp = host[0];
-  lp.seq_table = reinterpret_cast<const RouteParams*>(t8);
-  lp.seq_hps = s.n_kv_heads;
-  VEC_LAUNCH(K_ROUTE, list_kernel<true>(most_pool, most_chunks), dim3(parts, (unsigned)count * s.n_kv_heads), dim3(HT), 0, stream, lp);
+  VEC_LAUNCH(K_ROUTE, list_kernel<true>(most_pool, most_chunks), dim3(parts, (unsigned)count * s.n_kv_heads), dim3(HT), 0, stream, args);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }

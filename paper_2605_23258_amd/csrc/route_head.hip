@@ -167,7 +167,8 @@ __device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int 
 
 // J: blocks of kHeadBlock tokens a head may have
 template <int J, bool POOL, bool RAGGED>
-__global__ __launch_bounds__(HT) void route_head_kernel(HeadParams p) {
+__global__ __launch_bounds__(HT) void route_head_kernel(KernelArgs<HeadParams, RAGGED> args) {
+  HeadParams p = args.p;
   int part, h;
   if (RAGGED) { part = blockIdx.x; h = blockIdx.y; }
   else xcd_chunk_head(part, h);
@@ -380,7 +381,7 @@ void head_parts(int seq_len, int n_heads, HeadParams& p, unsigned& parts) {
 }
 
 template <bool POOL, bool RAGGED>
-void (*head_kernel(int n_blocks))(HeadParams) {
+void (*head_kernel(int n_blocks))(KernelArgs<HeadParams, RAGGED>) {
   if (n_blocks <= 1) return route_head_kernel<1, POOL, RAGGED>;
   if (n_blocks <= 2) return route_head_kernel<2, POOL, RAGGED>;
   if (n_blocks <= 4) return route_head_kernel<4, POOL, RAGGED>;
@@ -416,8 +417,9 @@ int launch_route_head(int n_kv_heads, int seq_len, const float* score, const flo
   unsigned parts;
   head_parts(seq_len, n_kv_heads, p, parts);
   const int n_blocks = (seq_len + kHeadBlock - 1) / kHeadBlock;
-  void (*k)(HeadParams) = pool ? head_kernel<true, false>(n_blocks) : head_kernel<false, false>(n_blocks);
-  VEC_LAUNCH(K_ROUTE, k, dim3(parts, n_kv_heads), dim3(HT), 0, stream, p);
+  auto k = pool ? head_kernel<true, false>(n_blocks) : head_kernel<false, false>(n_blocks);
+  const KernelArgs<HeadParams, false> args = {p};
+  VEC_LAUNCH(K_ROUTE, k, dim3(parts, n_kv_heads), dim3(HT), 0, stream, args);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
@@ -443,13 +445,11 @@ int launch_route_head_ragged(const vector_shape& s, const RaggedSeq* seqs, int c
     const int nb = (n + kHeadBlock - 1) / kHeadBlock;
     if (nb > blocks) blocks = nb;
   }
-  const int rc = upload_table(host, sizeof(HeadParams) * count, tables, stream);
+  KernelArgs<HeadParams, true> args;
+  const int rc = ragged_args(host, count, s.n_kv_heads, tables, stream, args);
   if (rc != VECTOR_OK) return rc;
-  HeadParams lp = host[0];
-  lp.seq_table = reinterpret_cast<const HeadParams*>(tables);
-  lp.seq_hps = s.n_kv_heads;
-  void (*k)(HeadParams) = head_kernel<true, true>(blocks);
-  VEC_LAUNCH(K_ROUTE, k, dim3(most, (unsigned)count * s.n_kv_heads), dim3(HT), 0, stream, lp);
+  auto k = head_kernel<true, true>(blocks);
+  VEC_LAUNCH(K_ROUTE, k, dim3(most, (unsigned)count * s.n_kv_heads), dim3(HT), 0, stream, args);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }

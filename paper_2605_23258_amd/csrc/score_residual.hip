@@ -129,7 +129,7 @@ static int run_passes(const SeqStack* stack, const vector_shape& s, const vector
   if (mass_out) *mass_out = L.pp.mass;
   if (n_prefix_out) *n_prefix_out = L.pp.n_prefix;
   if (n_range_out) *n_range_out = (int)L.grid2.x;
-  return launch_passes<T, D>(L.pp, L, false, L.grid1, L.grid2, stream);
+  return launch_passes<T, D, false>(KernelArgs<PassParams, false>{L.pp}, L, L.grid1, L.grid2, stream);
 }
 
 // Query heads per pair of passes: all G of a KV head when their G * w rows fit the kernels, else the largest
@@ -169,13 +169,11 @@ static int run_score_residual_ragged(const vector_shape& s, const RaggedSeq* seq
     if (L.grid2.x > g2) g2 = L.grid2.x;
   }
   unsigned char* t8 = reinterpret_cast<unsigned char*>(tables);
-  int rc = upload_table(host, sizeof(PassParams) * count, t8, stream);
+  KernelArgs<PassParams, true> args;
+  int rc = ragged_args(host, count, s.n_kv_heads, t8, stream, args);
   if (rc != VECTOR_OK) return rc;
-  PassParams lp = host[0];
-  lp.seq_table = reinterpret_cast<const PassParams*>(t8);
-  lp.seq_hps = s.n_kv_heads;
   const unsigned heads = (unsigned)count * s.n_kv_heads;
-  if ((rc = launch_passes<T, D>(lp, first, true, dim3(g1, heads), dim3(g2, heads), stream)) != VECTOR_OK) return rc;
+  if ((rc = launch_passes<T, D, true>(args, first, dim3(g1, heads), dim3(g2, heads), stream)) != VECTOR_OK) return rc;
   if (leave_mass) return VECTOR_OK;
   // pooling + score-key buckets of every sequence
   PoolSeq pool[kMaxRaggedSeqs];

@@ -66,16 +66,6 @@ struct PassParams {
   int repeat;           // probe kernels only: times each tile's arithmetic is run on the same operands
 };
 
-// RAGGED launches: swap in the parameters of the sequence this workgroup belongs to
-template <bool RAGGED>
-__device__ __forceinline__ void take_sequence(PassParams& p, int& h) {
-  if constexpr (RAGGED) {
-    const int seq = h / p.seq_hps;
-    h -= seq * p.seq_hps;
-    p = p.seq_table[seq];
-  }
-}
-
 // element offset of a launch head's keys (or values), and the KV head whose W it uses
 __device__ __forceinline__ int64_t head_offset(const PassParams& p, int h, int64_t seq_stride, int64_t head_stride) {
   return p.hps ? (int64_t)(h / p.hps) * seq_stride + (int64_t)(h % p.hps) * head_stride : (int64_t)h * head_stride;
@@ -240,7 +230,8 @@ template <typename T, int D> struct KeyOperands {
 constexpr int kStages1 = 4;
 
 template <typename T, int D, int NRB, bool RAGGED>
-__global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassParams p) {
+__global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<PassParams, RAGGED> args) {
+  PassParams p = args.p;
   int wg, h;
   xcd_chunk_head(wg, h);
   take_sequence<RAGGED>(p, h);
@@ -535,7 +526,8 @@ __device__ __forceinline__ float add_halves(float x) {
 // with memory out of the picture.  ROPE: the keys are cached after rotary position embedding; the
 // residual un-rotates them (the scores use them as cached).
 template <typename T, int D, int NRB, bool MASS, bool RES, bool ROPE, bool RAGGED, bool PROBE = false>
-__global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassParams p, RopeParams rp) {
+__global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArgs<PassParams, RAGGED> args, RopeParams rp) {
+  PassParams p = args.p;
   int wg, h;
   xcd_chunk_head(wg, h);
   take_sequence<RAGGED>(p, h);
@@ -1024,8 +1016,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassParam
 // ---------------------------------------------------------------------------
 // launching: the kernels for one element type and head size
 // ---------------------------------------------------------------------------
-// The parameters of one pair of passes; what decides the kernels is the same for every sequence of a ragged
-// launch (p then only carries seq_table / seq_hps).
+// The parameters of one pair of passes; what decides the kernels is the same for every sequence of a ragged launch.
 struct PassLaunch {
   PassParams pp;
   int units;                 // 32-row units of query rows the kernels are built for: 4, 8 or 16
@@ -1034,35 +1025,31 @@ struct PassLaunch {
   RopeParams rp;
 };
 
-template <typename T, int D, int NRB>
-int launch_passes_units(const PassParams& p, const PassLaunch& L, bool ragged, dim3 grid1, dim3 grid2, hipStream_t stream) {
+template <typename T, int D, int NRB, bool RAGGED>
+int launch_passes_units(const KernelArgs<PassParams, RAGGED>& a, const PassLaunch& L, dim3 grid1, dim3 grid2, hipStream_t stream) {
+  using Args = KernelArgs<PassParams, RAGGED>;
   if (L.do_mass && !L.pp.lse) {               // pass 1; not needed when the caller brings the rows' log-sum-exp
     constexpr size_t lds = kStages1 * Stream<T, D>::kTileBytes + kStreamWaves * 32 * sizeof(float2);
-    void (*k1)(PassParams) = ragged ? score_stats_kernel<T, D, NRB, true> : score_stats_kernel<T, D, NRB, false>;
+    auto k1 = score_stats_kernel<T, D, NRB, RAGGED>;
     VEC_HIP(set_max_lds(reinterpret_cast<const void*>(k1), lds));
-    VEC_LAUNCH(K_SCORE_STATS, k1, grid1, dim3(kStreamThreads), lds, stream, p);
+    VEC_LAUNCH(K_SCORE_STATS, k1, grid1, dim3(kStreamThreads), lds, stream, a);
   }
-  void (*k2)(PassParams, RopeParams);
+  void (*k2)(Args, RopeParams);
   size_t lds;
   if (L.do_mass && L.do_res) {
-    if (L.use_rope) {
-      k2 = ragged ? mass_residual_kernel<T, D, NRB, true, true, true, true> : mass_residual_kernel<T, D, NRB, true, true, true, false>;
-      lds = Pass2Lds<T, D, NRB, true, true, true>::kTotal;
-    } else {
-      k2 = ragged ? mass_residual_kernel<T, D, NRB, true, true, false, true> : mass_residual_kernel<T, D, NRB, true, true, false, false>;
-      lds = Pass2Lds<T, D, NRB, true, true, false>::kTotal;
-    }
+    k2 = L.use_rope ? mass_residual_kernel<T, D, NRB, true, true, true, RAGGED> : mass_residual_kernel<T, D, NRB, true, true, false, RAGGED>;
+    lds = L.use_rope ? Pass2Lds<T, D, NRB, true, true, true>::kTotal : Pass2Lds<T, D, NRB, true, true, false>::kTotal;
+  } else if constexpr (RAGGED) {
+    return VECTOR_ERR_ARG;
   } else if (L.do_mass) {
-    if (ragged) return VECTOR_ERR_ARG;
     k2 = mass_residual_kernel<T, D, NRB, true, false, false, false>;
     lds = Pass2Lds<T, D, NRB, true, false, false>::kTotal;
   } else {
-    if (ragged) return VECTOR_ERR_ARG;
     k2 = L.use_rope ? mass_residual_kernel<T, D, 4, false, true, true, false> : mass_residual_kernel<T, D, 4, false, true, false, false>;
     lds = L.use_rope ? Pass2Lds<T, D, 4, false, true, true>::kTotal : Pass2Lds<T, D, 4, false, true, false>::kTotal;
   }
   VEC_HIP(set_max_lds(reinterpret_cast<const void*>(k2), lds));
-  VEC_LAUNCH(K_MASS_RESIDUAL, k2, grid2, dim3(kStreamThreads), lds, stream, p, L.rp);
+  VEC_LAUNCH(K_MASS_RESIDUAL, k2, grid2, dim3(kStreamThreads), lds, stream, a, L.rp);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
@@ -1070,12 +1057,12 @@ int launch_passes_units(const PassParams& p, const PassLaunch& L, bool ragged, d
 // units of query rows that fit the registers of a workgroup (two per wave; fp32 operands of 128 dims: one)
 template <typename T, int D> constexpr int kMaxUnits = (sizeof(T) == 4 && D == 128) ? 8 : 16;
 
-template <typename T, int D>
-int launch_passes(const PassParams& p, const PassLaunch& L, bool ragged, dim3 grid1, dim3 grid2, hipStream_t stream) {
-  if (L.units == 4 || !L.do_mass) return launch_passes_units<T, D, 4>(p, L, ragged, grid1, grid2, stream);
-  if (L.units == 8) return launch_passes_units<T, D, 8>(p, L, ragged, grid1, grid2, stream);
+template <typename T, int D, bool RAGGED>
+int launch_passes(const KernelArgs<PassParams, RAGGED>& a, const PassLaunch& L, dim3 grid1, dim3 grid2, hipStream_t stream) {
+  if (L.units == 4 || !L.do_mass) return launch_passes_units<T, D, 4, RAGGED>(a, L, grid1, grid2, stream);
+  if (L.units == 8) return launch_passes_units<T, D, 8, RAGGED>(a, L, grid1, grid2, stream);
   if constexpr (kMaxUnits<T, D> == 16) {
-    if (L.units == 16) return launch_passes_units<T, D, 16>(p, L, ragged, grid1, grid2, stream);
+    if (L.units == 16) return launch_passes_units<T, D, 16, RAGGED>(a, L, grid1, grid2, stream);
   }
   return VECTOR_ERR_SHAPE;
 }
@@ -1085,16 +1072,20 @@ int launch_probe(const PassLaunch& L, hipStream_t stream) {
   auto k2 = mass_residual_kernel<T, D, 4, false, true, false, false, true>;
   constexpr size_t lds = Pass2Lds<T, D, 4, false, true, false>::kTotal;
   VEC_HIP(set_max_lds(reinterpret_cast<const void*>(k2), lds));
-  VEC_LAUNCH(K_MASS_RESIDUAL, k2, L.grid2, dim3(kStreamThreads), lds, stream, L.pp, L.rp);
+  VEC_LAUNCH(K_MASS_RESIDUAL, k2, L.grid2, dim3(kStreamThreads), lds, stream, KernelArgs<PassParams, false>{L.pp}, L.rp);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
 
 #ifndef VEC_DEFINE_PASSES
-extern template int launch_passes<bf16_t, 128>(const PassParams&, const PassLaunch&, bool, dim3, dim3, hipStream_t);
-extern template int launch_passes<bf16_t, 64>(const PassParams&, const PassLaunch&, bool, dim3, dim3, hipStream_t);
-extern template int launch_passes<float, 128>(const PassParams&, const PassLaunch&, bool, dim3, dim3, hipStream_t);
-extern template int launch_passes<float, 64>(const PassParams&, const PassLaunch&, bool, dim3, dim3, hipStream_t);
+extern template int launch_passes<bf16_t, 128, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
+extern template int launch_passes<bf16_t, 128, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
+extern template int launch_passes<bf16_t, 64, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
+extern template int launch_passes<bf16_t, 64, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
+extern template int launch_passes<float, 128, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
+extern template int launch_passes<float, 128, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
+extern template int launch_passes<float, 64, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
+extern template int launch_passes<float, 64, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
 extern template int launch_probe<bf16_t, 128>(const PassLaunch&, hipStream_t);
 extern template int launch_probe<bf16_t, 64>(const PassLaunch&, hipStream_t);
 #endif
