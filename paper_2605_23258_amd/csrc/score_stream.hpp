@@ -238,7 +238,7 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<
   using S = Stream<T, D>;
   using WW = WaveWork<T, D, NRB>;
   constexpr int NC = S::NC, U = WW::U, PH = WW::PH;
-  extern __shared__ __align__(16) unsigned char smem[];        // [kStages1][tile], then [8][32] float2
+  extern __shared__ __align__(16) unsigned char smem[];        // [kStages1][tile], then [2][4][32] float2
 
   int chunk = wg * p.chunks_per_wg;
   const int chunk_end = min(p.n_chunks, chunk + p.chunks_per_wg);
@@ -309,14 +309,30 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<
     m_ref[u] = m_new;
   };
 
+  auto fold_last = [&](const f32x16& x, int u) VEC_INLINE {
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      s0 += fast_exp2(fmaf(x[v], p.c2, -m_ref[u]));
+      s1 += fast_exp2(fmaf(x[v + 1], p.c2, -m_ref[u]));
+    }
+    s0 += s1;
+    if (__builtin_expect(__any(!(s0 < 1.0e18f)), 0)) refold(x, u);
+    else l_run[u] += s0;
+  };
+
   // rows = tokens, columns = query rows.  A phase runs the products of one subtile, one operand chunk at a
   // time, each followed by its share of the exponentials of the phase before: the matrix pipe works through
   // the new products while the vector ALU folds the finished ones.
   f32x16 acc[2][U];
   KeyOperands<T, D> keys_op(smem0, l31, half);
-  auto phase = [&](auto cur_tag, auto fold_tag, uint32_t this_at, uint32_t next_at) VEC_INLINE {
+  auto phase = [&](auto cur_tag, auto fold_tag, auto refold_tag, uint32_t this_at, uint32_t next_at) VEC_INLINE {
     constexpr int kCur = decltype(cur_tag)::value;
     constexpr bool kFold = decltype(fold_tag)::value;
+    if constexpr (decltype(refold_tag)::value) {     // a chunk's first products: there is no reference yet
+#pragma unroll
+      for (int u = 0; u < U; ++u) refold(acc[1 - kCur][u], u);
+    }
     float s0[U], s1[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) { s0[u] = 0.f; s1[u] = 0.f; }
@@ -371,15 +387,36 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<
   keys_op.load(sub_at(0));
   uint32_t slot = 0;
   int t0 = t_begin, left = n_steps;            // tiles from this one on
+  auto merge = [&](float& m, float& l, float m2, float l2) VEC_INLINE {
+    const float mn = fmaxf(m, m2);
+    const float ms = (mn == -INFINITY) ? 0.f : mn;
+    l = l * fast_exp2(m - ms) + l2 * fast_exp2(m2 - ms);
+    m = mn;
+  };
+  // four units: two waves saw a row's tokens; the first adds the other's share, left in LDS, a barrier later
+  constexpr bool kPaired = NRB == 4 && S::kSub > 1;
+  int finished = -1;                           // chunk whose shares are to be merged
+  float m_own = 0.f, l_own = 0.f;
+  auto finish_chunk = [&]() VEC_INLINE {
+    if (kPaired && finished >= 0) {
+      if (wave < 4) {
+        const float2 o = grp[((finished & 1) * 4 + wave) * 32 + l31];
+        merge(m_own, l_own, o.x, o.y);
+        if (half == 0) p.part[((size_t)h * p.n_chunks + finished) * p.R_pad + qrow[0]] = make_float2(m_own, l_own);
+      }
+      finished = -1;
+    }
+  };
   // One tile.  Its successor is waited for here as well, so that the last phase can already read the next
   // phase's operands; the products of the last phase of a tile are folded during the first of the next.
+  // first_tag: phases of this chunk already run (0, 1, or 2 for more).
   auto run_step = [&](auto par_tag, auto first_tag, int c_end) VEC_INLINE {
     constexpr int kPar = decltype(par_tag)::value;
-    constexpr bool kFirst = decltype(first_tag)::value;
     if (__builtin_expect(left > kStages1 - 2, 1)) wait_loads<(kStages1 - 3) * S::kLoads>();
     else wait_loads<0>();
     lds_barrier();                             // tile and successor are there for all, the stage before them is free
     if (to_fetch > 0) fetch();
+    finish_chunk();
     const uint32_t next_slot = slot + S::kTileBytes == kRing ? 0 : slot + S::kTileBytes;
     if (ww.has_rows) {
       const bool tail = t0 + S::kTokens > min(p.n_prefix + 1, c_end);
@@ -387,7 +424,8 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<
         constexpr int ph = decltype(ph_tag)::value;
         if constexpr (ph < PH) {
           constexpr int cur = (kPar + ph) & 1;
-          phase(std::integral_constant<int, cur>{}, std::integral_constant<bool, !(kFirst && ph == 0)>{},
+          constexpr int kNth = decltype(first_tag)::value + ph;          // phases of this chunk before this one (at most two counted)
+          phase(std::integral_constant<int, cur>{}, std::integral_constant<bool, (kNth > 1)>{}, std::integral_constant<bool, kNth == 1>{},
                 slot + sub_at(ph), ph + 1 < PH ? slot + sub_at(ph + 1) : next_slot + sub_at(0));
           if (__builtin_expect(tail, 0)) mask(acc[cur], t0 + 32 * ww.sub(ph), c_end);
         }
@@ -406,45 +444,43 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<
     const int steps = (c_end - chunk * p.tpc1 + S::kTokens - 1) / S::kTokens;
     restart();
     constexpr int kFlip = PH & 1;              // an odd number of phases per tile swaps the accumulators' roles
-    run_step(std::integral_constant<int, 0>{}, std::true_type{}, c_end);
-    if constexpr (kFlip) {
-      for (int i = 1; i < steps; i += 2) {
-        run_step(std::integral_constant<int, 1>{}, std::false_type{}, c_end);
-        if (i + 1 < steps) run_step(std::integral_constant<int, 0>{}, std::false_type{}, c_end);
+    using Zero = std::integral_constant<int, 0>;
+    using One = std::integral_constant<int, 1>;
+    using Many = std::integral_constant<int, 2>;
+    run_step(Zero{}, Zero{}, c_end);
+    if constexpr (kFlip) {                     // one phase per tile
+      if (steps > 1) run_step(One{}, One{}, c_end);
+      for (int i = 2; i < steps; i += 2) {
+        run_step(Zero{}, Many{}, c_end);
+        if (i + 1 < steps) run_step(One{}, Many{}, c_end);
       }
     } else {
-      for (int i = 1; i < steps; ++i) run_step(std::integral_constant<int, 0>{}, std::false_type{}, c_end);
+      for (int i = 1; i < steps; ++i) run_step(Zero{}, Many{}, c_end);
     }
     // the last phase's products; then one (reference, sum) per row and chunk
     if (ww.has_rows) {
       const bool odd = (PH * steps - 1) & 1;   // which accumulators hold them
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        if (odd) refold(acc[1][u], u);
-        else refold(acc[0][u], u);
+        if (odd) fold_last(acc[1][u], u);
+        else fold_last(acc[0][u], u);
       }
     }
-    auto merge = [&](float& m, float& l, float m2, float l2) VEC_INLINE {
-      const float mn = fmaxf(m, m2);
-      const float ms = (mn == -INFINITY) ? 0.f : mn;
-      l = l * fast_exp2(m - ms) + l2 * fast_exp2(m2 - ms);
-      m = mn;
-    };
     float2* out = p.part + ((size_t)h * p.n_chunks + chunk) * p.R_pad;     // [head][chunk][row]: rows of a chunk side by side
 #pragma unroll
     for (int u = 0; u < U; ++u) merge(m_ref[u], l_run[u], __shfl_xor(m_ref[u], 32, kWave), __shfl_xor(l_run[u], 32, kWave));
-    if (NRB == 4 && S::kSub > 1) {             // two waves saw the row's tokens
-      if (half == 0 && wave >= 4) grp[(wave - 4) * 32 + l31] = make_float2(m_ref[0], l_run[0]);
-      lds_barrier();
-      if (wave < 4) {
-        const float2 o = grp[wave * 32 + l31];
-        merge(m_ref[0], l_run[0], o.x, o.y);
-        if (half == 0) out[qrow[0]] = make_float2(m_ref[0], l_run[0]);
-      }
+    if (kPaired) {                             // the other wave's share is there after the next barrier
+      if (half == 0 && wave >= 4) grp[((chunk & 1) * 4 + wave - 4) * 32 + l31] = make_float2(m_ref[0], l_run[0]);
+      if (wave < 4) { m_own = m_ref[0]; l_own = l_run[0]; }
+      finished = chunk;
     } else if (ww.has_rows && half == 0) {
 #pragma unroll
       for (int u = 0; u < U; ++u) out[qrow[u]] = make_float2(m_ref[u], l_run[u]);
     }
+  }
+  if (kPaired) {
+    lds_barrier();
+    finish_chunk();
   }
 }
 
