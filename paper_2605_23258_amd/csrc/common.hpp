@@ -98,6 +98,31 @@ __device__ __forceinline__ void take_sequence(P& p, int& h) {
   }
 }
 
+// The parameters read anew, for what a kernel needs only at its end: held from the start they would fill the scalar
+// registers in between.  launch_head: the head as take_sequence was given it.  (Word by word through the constant
+// address space: that keeps the loads scalar behind the kernel's stores.)
+template <typename P> __device__ __forceinline__ P read_constant(uint64_t at) {
+  typedef const __attribute__((address_space(4))) uint32_t* words;
+  static_assert(sizeof(P) % 4 == 0, "whole words");
+  uint32_t w[sizeof(P) / 4];
+#pragma unroll
+  for (size_t i = 0; i < sizeof(P) / 4; ++i) w[i] = ((words)at)[i];
+  P p;
+  __builtin_memcpy(&p, w, sizeof(P));
+  return p;
+}
+template <bool RAGGED, typename P>
+__device__ __forceinline__ P params_again(int launch_head) {
+  uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(at));                   // not the value that the first reads came from
+  P p = read_constant<P>(at);
+  if constexpr (RAGGED) {
+    const int seq = launch_head / p.seq_hps;
+    p = read_constant<P>((p.seq_table ? (uint64_t)p.seq_table : at + sizeof(P)) + (size_t)seq * sizeof(P));
+  }
+  return p;
+}
+
 __device__ __forceinline__ chunk_t load_chunk(const void* p) { return *reinterpret_cast<const chunk_t*>(p); }
 
 // acc += A(32 x chunk) * B(chunk x 32): a holds rows of the M side, b rows of the N side.

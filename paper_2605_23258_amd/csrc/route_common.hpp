@@ -153,6 +153,7 @@ constexpr int kRankCap = 256;                   // candidates ranked by comparis
 
 typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_u;   // 16-byte access at any element
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(4), aligned(4))) uint32_t u32x4_u;
 
 // Workgroup barrier for data in LDS alone: global loads in flight (the residuals, while the scores are worked
 // on) and stores (score, tiers, lists) are not waited for.
@@ -210,7 +211,7 @@ __device__ __forceinline__ void pick_bin(const int* hist, int* row, int* pick, i
     pick[0] = b; pick[1] = before; pick[2] = in;
   }
   lds_barrier();
-  d = pick[0]; above = pick[1]; count = pick[2];
+  d = __builtin_amdgcn_readfirstlane(pick[0]); above = __builtin_amdgcn_readfirstlane(pick[1]); count = __builtin_amdgcn_readfirstlane(pick[2]);
 }
 
 // A sample's count, sum and sum of squares (in units of 4096 keys about the center) -> where to lay the buckets
@@ -235,6 +236,105 @@ __device__ __forceinline__ void bucket_range(const DigitMap& map, int d, uint32_
     span = hi - lo;
   }
   if (lo == 0u) { lo = 1u; span -= 1u; }
+}
+
+// ---------------------------------------------------------------------------
+// many keys in one bucket: scores that are equal or nearly so (attention rows that underflow to zero, scorers
+// with few values)
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xf, 0xf, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xf, 0xf, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xf, 0xf, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xf, 0xf, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xa, 0xf, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xc, 0xf, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// smallest and largest of the workgroup's keys in [lo, lo + span]; each(f) hands every key to f; row: [2][HW], free
+// until the barrier after this
+template <typename Each>
+__device__ __forceinline__ void key_range(Each each, uint32_t lo, uint32_t span, uint32_t (*row)[HW], uint32_t& least, uint32_t& most) {
+  uint32_t a = 0xffffffffu, b = 0u;
+  each([&](uint32_t x) {
+    const bool in = x - lo <= span;
+    a = min(a, in ? x : 0xffffffffu);
+    b = max(b, in ? x : 0u);
+  });
+  a = wave_min_u32(a);
+  b = ~wave_min_u32(~b);
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { row[0][wave] = a; row[1][wave] = b; }
+  lds_barrier();
+#pragma unroll
+  for (int w = 0; w < HW; ++w) { a = min(a, row[0][w]); b = max(b, row[1][w]); }
+  least = (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
+  most = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+}
+
+// Of the `count` keys in [lo, lo + span] the k-th largest is wanted: cuts the range until it holds at most kRankCap
+// keys, or one number (span 0).  Where the keys lie in it is looked up before they are counted: equal keys need
+// no count at all, and 64 lanes that add to the same word of a histogram take 64 turns (7 us for 16384 equal
+// keys, against 1 us for the look).  The buckets come in several copies, a lane's own by its number, for the same
+// reason.  tight: [lo, lo + span] starts and ends with a key already.
+template <typename Each>
+__device__ __forceinline__ void narrow(Each each, bool tight, uint32_t& lo, uint32_t& span, int& k, int& count, int* hist, int* row, int* pick,
+                                       uint32_t (*range)[HW]) {
+  const int lane = threadIdx.x & 63;
+  while (__builtin_expect(count > kRankCap && span != 0u, 0)) {         // uniform
+    if (!tight) {
+      uint32_t most;
+      key_range(each, lo, span, range, lo, most);
+      span = most - lo;
+      if (span == 0u) break;
+    }
+    tight = false;
+    const int s = max(0, 23 - (int)__clz(span));                        // at most 512 buckets over the range,
+    const uint32_t last = span >> s;
+    const int copies_log = min(6, (int)__clz(last) - 21);               // 4 to 64 copies of each
+    const int copy = lane & ((1 << copies_log) - 1);
+    clear_bins(hist);
+    lds_barrier();
+    each([&](uint32_t x) { if (x - lo <= span) atomicAdd(&hist[(int)(((x - lo) >> s) << copies_log) + copy], 1); });
+    lds_barrier();
+    int sum = 0;                                                        // a bucket's copies lie side by side
+    if ((int)threadIdx.x < (kHeadBins >> copies_log))
+      for (int j = 0; j < (1 << copies_log); ++j) sum += hist[((int)threadIdx.x << copies_log) + ((j + lane) & ((1 << copies_log) - 1))];
+    lds_barrier();
+    hist[threadIdx.x] = sum;
+#pragma unroll
+    for (int q = 1; q < kHeadBins / HT; ++q) hist[q * HT + threadIdx.x] = 0;
+    lds_barrier();
+    int d, above;
+    pick_bin(hist, row, pick, k, d, above, count);
+    k -= above;
+    lo += (uint32_t)d << s;
+    span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
+  }
+}
+
+// Whether the k-th largest key lies among those that agree with `center` but for their last 12 bits; then lo, span,
+// k and count describe these.  Worth a try where every key of a sample does (its sum of squares about the
+// center is 0): a histogram would put all of them into a few words.  row: [HW]
+template <typename Each>
+__device__ __forceinline__ bool around_center(Each each, uint32_t center, uint32_t& lo, uint32_t& span, int& k, int& count, int* row) {
+  const uint32_t first = center & ~0xfffu;
+  int in = 0, above = 0;
+  each([&](uint32_t x) {
+    in += x - first <= 0xfffu;
+    above += x > first + 0xfffu;
+  });
+  int unused, total_in, total_above;
+  head_scan(in, row, unused, total_in);
+  lds_barrier();                                                        // the row is used again
+  head_scan(above, row, unused, total_above);
+  if (k <= total_above || k > total_above + total_in) return false;    // uniform
+  lo = first;
+  span = 0xfffu;
+  k -= total_above;
+  count = total_in;
+  return true;
 }
 
 // Where a head's results go.

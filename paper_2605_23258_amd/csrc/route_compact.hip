@@ -413,24 +413,54 @@ struct RouteParams {
 
 constexpr int kMaxGroups = 64 * HW;      // as many as the registers of a workgroup hold
 
+// Per chunk a run of the head's lists: its first entry, its length, and the groups of kRunGroup entries before it
+struct Runs {
+  int at[kMaxChunks], count[kMaxChunks], group_start[kMaxChunks], n_groups;
+};
+constexpr int kRunGroup = 4 * kWave;     // entries that a wave takes at a time
+
 struct ListShared {
   __align__(16) int hist[kHeadBins];
   __align__(16) int list[kHeadBlock];    // tokens whose rows this workgroup copies: retained, then approximated
   int coarse[HT + 1];                    // sums of the tables at every fourth bin
-  // per chunk: entries in front of the chosen bin, the groups of 64 of them before the chunk's, and the entries
-  // of the bin (candidates) before the chunk's
-  int front[kMaxChunks], group_start[kMaxChunks], cand_start[kMaxChunks];
+  // per chunk: entries in front of the chosen bin, the groups of 64 of them before the chunk's, the entries
+  // of the bin (candidates) before the chunk's, and the chunk's own
+  int front[kMaxChunks], group_start[kMaxChunks], cand_start[kMaxChunks], cand_count[kMaxChunks];
   int n_groups;
+  // runs of entries that do not fit the registers: candidates; entries in front of the bin, [1] all or [0] the rest
+  Runs cand_runs, front_runs[2];
+  int2 run_group[HT];                    // for walk_runs
   int2 group[kMaxGroups];                // the first groups: place of the first entry in the head's lists, number of entries
   __align__(16) uint32_t cand[kRankCap];
   int wsum[3][HW];
   float stat[3][HW];
+  uint32_t range[2][HW];
   uint32_t center[2];
   int pick[3];
   int n_cand;
   uint32_t thr;
   int quota, equal;
 };
+
+// Lane c of one wave holds chunk c's numbers of entries in front of the bin and in it (0 beyond the chunks)
+__device__ __forceinline__ void leave_chunk_counts(int front, int cnt, int n_chunks, ListShared& sh) {
+  const int lane = threadIdx.x & 63, groups = (front + 63) >> 6;
+  const int g_incl = wave_incl_scan_dpp(groups), c_incl = wave_incl_scan_dpp(cnt);
+  if (lane < kMaxChunks) {
+    sh.front[lane] = front;
+    sh.group_start[lane] = lane < n_chunks ? g_incl - groups : 0x7fffffff;
+    sh.cand_start[lane] = lane < n_chunks ? c_incl - cnt : 0x7fffffff;
+    sh.cand_count[lane] = cnt;
+  }
+  if (lane == 63) sh.n_groups = g_incl;
+}
+// the same for a run of every chunk (count 0 beyond the chunks)
+__device__ __forceinline__ void leave_runs(int at, int count, int n_chunks, Runs& r) {
+  const int lane = threadIdx.x & 63, groups = (count + kRunGroup - 1) / kRunGroup;
+  const int incl = wave_incl_scan_dpp(groups);
+  if (lane < kMaxChunks) { r.at[lane] = at; r.count[lane] = count; r.group_start[lane] = lane < n_chunks ? incl - groups : 0x7fffffff; }
+  if (lane == 63) r.n_groups = incl;
+}
 
 // Leading digit of the k-th largest key of a head from the D tables of its chunks: summed over the
 // chunks, S[b] = #(digit >= b) falls from the key count at b = 0 to 0 at b = 2048, and the digit is
@@ -485,14 +515,7 @@ __device__ __forceinline__ void pick_from_tables(const uint16_t* tables, int n_c
 #pragma unroll
     for (int q = 1; q < 4; ++q)
       if (j == q) { front = d[q + 1]; cnt = d[q] - d[q + 1]; above = S[q + 1]; count = S[q] - S[q + 1]; }
-    const int groups = (front + 63) >> 6;
-    const int g_incl = wave_incl_scan_dpp(groups), c_incl = wave_incl_scan_dpp(cnt);
-    if (lane < kMaxChunks) {
-      sh.front[lane] = front;
-      sh.group_start[lane] = lane < n_chunks ? g_incl - groups : 0x7fffffff;
-      sh.cand_start[lane] = lane < n_chunks ? c_incl - cnt : 0x7fffffff;
-    }
-    if (lane == 63) sh.n_groups = g_incl;
+    leave_chunk_counts(front, cnt, n_chunks, sh);
     if (lane == 0) { sh.pick[0] = at + j; sh.pick[1] = above; sh.pick[2] = count; }
   }
   lds_barrier();
@@ -505,6 +528,48 @@ __device__ __forceinline__ int chunk_of(const int* start, int idx) {
   for (int s = kMaxChunks / 2; s > 0; s >>= 1)
     if (start[c + s] <= idx) c += s;
   return c;
+}
+
+// The runs of chunks [c0, c1): use(load(place in the head's lists), e) for e = 0 .. 3, the entries at that place and
+// behind it.  A wave takes kRunGroup entries of a run at a time, four neighbours per lane, and has U such groups on
+// their way; the groups' places are laid out by the threads, one each.  At a run's end the lanes read from four before
+// the end on and skip what another lane has, so a run of fewer than four reads up to three entries in front of it
+// (at the very first place: the end of the array before, see route_layout).  Whole workgroup.  An entry per lane
+// and a look-up of the chunk per group took three times as long (131072 tokens x 8 heads, 64 scores a few ulps
+// apart: 360 us for the routing, now 214).
+template <int U, typename Load, typename Use>
+__device__ __forceinline__ void walk_runs(const Runs& runs, int2* table, int n_chunks, int c0, int c1, Load load, Use use) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int g0 = __builtin_amdgcn_readfirstlane(runs.group_start[c0]);
+  const int g1 = __builtin_amdgcn_readfirstlane(c1 < n_chunks ? runs.group_start[c1] : runs.n_groups);
+  for (int r = g0; r < g1; r += HT) {
+    const int g = r + (int)threadIdx.x, count = min(HT, g1 - r);
+    lds_barrier();
+    if (g < g1) {
+      const int c = chunk_of(runs.group_start, g), first = (g - runs.group_start[c]) * kRunGroup;
+      table[threadIdx.x] = make_int2(runs.at[c] + first, min(kRunGroup, runs.count[c] - first));
+    }
+    lds_barrier();
+    for (int i = wave; i < count; i += U * HW) {
+      decltype(load(0)) x[U];
+      int skip[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int2 at = table[min(i + u * HW, count - 1)];
+        const int first = min(4 * lane, at.y - 4);
+        x[u] = load(at.x + first);
+        skip[u] = i + u * HW < count ? 4 * lane - first : 4;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e >= skip[u]) use(x[u], e);
+    }
+  }
+}
+__device__ __forceinline__ u32x4 load_entries(const void* list, int at) {
+  return *reinterpret_cast<const u32x4_u*>(reinterpret_cast<const uint32_t*>(list) + at);
 }
 
 // The k-th largest key: keys above thr are selected, and of those equal to it the quota with the lowest tokens
@@ -530,44 +595,43 @@ __device__ __forceinline__ void leave_sample(const uint32_t (&key)[NS], uint32_t
 }
 
 // Among the keys in registers (0: no key) and those that more(f) hands to f; 1 <= k <= number of keys.
-// total: number of keys; center: what leave_sample was given.  The caller has passed a barrier since the last use of
-// sh but for the sample.
-template <int NS, typename More>
-__device__ __forceinline__ Cut list_select(const uint32_t (&key)[NS], More more, int total, int k, uint32_t center, ListShared& sh) {
+// total: number of keys, all in [lo, lo + span]; center: what leave_sample was given, or tight: the range starts and
+// ends with a key (then no sample is needed).  MORE_IS_TIGHT: more() has none where the range is not tight.  The
+// caller has passed a barrier since the last use of sh but for the sample.
+template <bool MORE_IS_TIGHT, int NS, typename More>
+__device__ __forceinline__ Cut list_select(const uint32_t (&key)[NS], More more, int total, int k, uint32_t center, bool tight, uint32_t lo,
+                                           uint32_t span, ListShared& sh) {
   const int lane = threadIdx.x & 63;
   auto each = [&](auto f) {
 #pragma unroll
     for (int i = 0; i < NS; ++i) f(key[i]);
     more(f);
   };
+  auto each_first = [&](auto f) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) f(key[i]);
+    if (!MORE_IS_TIGHT) more(f);
+  };
   int count = total;
-  uint32_t lo = 1u, span = 0xfffffffeu;
   if (threadIdx.x == 0) sh.n_cand = 0;
   if ((int)threadIdx.x < kRankCap) sh.cand[threadIdx.x] = 0u;
-  if (total > kRankCap) {                                               // uniform
+  if (total > kRankCap && !tight) {                                     // uniform
     clear_bins(sh.hist);
     lds_barrier();
-    const DigitMap map = digit_map_about(center, sum_of_waves(sh.stat[0], lane), sum_of_waves(sh.stat[1], lane), sum_of_waves(sh.stat[2], lane));
-    each([&](uint32_t x) { if (x != 0u) atomicAdd(&sh.hist[map.digit(x)], 1); });
-    lds_barrier();
-    int d, above;
-    pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
-    k -= above;
-    bucket_range(map, d, lo, span);
-    while (count > kRankCap && span != 0u) {                            // uniform
-      const int s = max(0, 21 - (int)__clz(span));                      // at most 2048 buckets over the range
-      clear_bins(sh.hist);
+    const float cnt = sum_of_waves(sh.stat[0], lane), s1 = sum_of_waves(sh.stat[1], lane), s2 = sum_of_waves(sh.stat[2], lane);
+    if (!(cnt >= 32.f && s2 == 0.f && around_center(each_first, center, lo, span, k, count, sh.wsum[0]))) {
+      const DigitMap map = digit_map_about(center, cnt, s1, s2);
+      each_first([&](uint32_t x) { if (x != 0u) atomicAdd(&sh.hist[map.digit(x)], 1); });
       lds_barrier();
-      each([&](uint32_t x) { if (x - lo <= span) atomicAdd(&sh.hist[(x - lo) >> s], 1); });
-      lds_barrier();
+      int d, above;
       pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
       k -= above;
-      lo += (uint32_t)d << s;
-      span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
+      bucket_range(map, d, lo, span);
     }
   } else {
     lds_barrier();
   }
+  narrow(each, tight, lo, span, k, count, sh.hist, sh.wsum[0], sh.pick, sh.range);
   if (span == 0u) { lds_barrier(); return {lo, k, count == k}; }        // one key, however many tokens
   auto collect = [&](uint32_t x) {
     if (x - lo <= span) {
@@ -601,17 +665,18 @@ __device__ __forceinline__ Cut list_select(const uint32_t (&key)[NS], More more,
   return {sh.thr, sh.quota, sh.quota == sh.equal};
 }
 
-// The last of the `quota` lowest tokens whose key is thr; each(f) hands every (key, token) to f.
+// The last of the `quota` lowest tokens in [first, last] whose key is thr; each(a, b, f) hands every (key, token) with
+// a token in [a, b], and maybe others, to f.
 template <typename Each>
-__device__ __forceinline__ int token_cut(Each each, uint32_t thr, int quota, ListShared& sh) {
-  uint32_t lo = 0u, span = (uint32_t)kRouteMaxSeqLen - 1u;              // of kRouteMaxSeqLen - 1 - token
+__device__ __forceinline__ int token_cut(Each each, uint32_t thr, int quota, int first, int last, ListShared& sh) {
+  uint32_t lo = 0u, span = (uint32_t)(last - first);                    // of last - token
   while (span != 0u) {
     const int s = max(0, 21 - (int)__clz(span));
     int d, above, count;
     clear_bins(sh.hist);
     lds_barrier();
-    each([&](uint32_t key, int tok) {
-      const uint32_t v = (uint32_t)(kRouteMaxSeqLen - 1 - tok) - lo;
+    each(last - (int)(lo + span), last - (int)lo, [&](uint32_t key, int tok) {
+      const uint32_t v = (uint32_t)(last - tok) - lo;
       if (key == thr && v <= span) atomicAdd(&sh.hist[v >> s], 1);
     });
     lds_barrier();
@@ -621,48 +686,75 @@ __device__ __forceinline__ int token_cut(Each each, uint32_t thr, int quota, Lis
     span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
   }
   lds_barrier();
-  return kRouteMaxSeqLen - 1 - (int)lo;
+  return last - (int)lo;
 }
 
 constexpr int kCandSlots = 4;            // candidates per thread kept in registers
 
-// SLOTS: pool members per thread kept in registers (the rest are read again for every pass over them)
-template <int SLOTS, bool RAGGED>
-__global__ __launch_bounds__(HT) void route_list_kernel(KernelArgs<RouteParams, RAGGED> args) {
-  RouteParams p = args.p;
-  int part, h;
-  xcd_chunk_head(part, h);
-  take_sequence<RAGGED>(p, h);
-  const int n = p.n, begin = part * p.part_tokens, end = min(n, begin + p.part_tokens);
-  if (begin >= n) return;
-  __shared__ ListShared sh;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), tid = threadIdx.x;
-  const float* score = p.score + (size_t)h * n;
-  const float* eps = p.eps + (size_t)h * n;
+// Where a head's tokens are cut: in_pool() and, inside the pool, is_approx(), of order-preserving keys and tokens; and how
+// many of the pool, and of its approximated tokens, this thread found in the chunks before the workgroup's own
+// (counts of whole waves in lane 0).
+struct HeadCut {
+  uint32_t top_thr, low_thr;
+  int top_tok, low_tok;                  // the last token that an equal key is taken of
+  bool any_approx;
+  int pool_before, apx_before;
+  __device__ __forceinline__ bool in_pool(uint32_t key, int tok) const { return key > top_thr || (key == top_thr && tok <= top_tok); }
+  __device__ __forceinline__ bool is_approx(uint32_t key, int tok) const {
+    return any_approx && (key > low_thr || (key == low_thr && tok <= low_tok));
+  }
+};
+
+// Both selections of a head, by every workgroup of it.  SLOTS: pool members per thread kept in registers.  ALL: they and
+// the candidates all fit; otherwise the rest is read again for every pass over it.  The two are apart because the
+// passes over what does not fit would lie between the others in the instruction cache (one code for both: 0.3 to 3 us
+// more for heads that fit).
+template <int SLOTS, bool ALL>
+__device__ __forceinline__ HeadCut cut_head(const RouteParams& p, int h, int own_chunk, ListShared& sh) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), tid = threadIdx.x, n = p.n;
   const uint32_t* bkey = p.bkey + (size_t)h * n;
   const int32_t* bpos = p.bpos + (size_t)h * n;
   const uint32_t* beps = p.beps + (size_t)h * n;
-  auto load4 = [&](const float* a, int t0, int stop) {
-    f32x4 x = {0.f, 0.f, 0.f, 0.f};
-    if (t0 + 4 <= stop) {
-      x = *reinterpret_cast<const f32x4_u*>(a + t0);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (t0 + e < stop) x[e] = a[t0 + e];
+  auto keys_at = [&](int at) { return load_entries(bkey, at); };
+  struct Tokens { u32x4 key, tok; };
+  struct Entries { u32x4 key, tok, eps; };
+  int n_front = __builtin_amdgcn_readfirstlane(sh.pick[1]), n_cand = __builtin_amdgcn_readfirstlane(sh.pick[2]);
+  // More candidates than the registers hold: their range first.  If all are one number (a plateau of scores), those
+  // of the lowest tokens are in the pool: whole chunks, which join the entries in front of the bin, and a part of
+  // one chunk, whose candidates stay.
+  uint32_t least = 1u, most = 0xffffffffu;
+  bool plateau = false;
+  int cut_chunk = 0;
+  const bool all_candidates = p.n_pool - n_front == n_cand;            // are in the pool
+  if (!ALL && n_cand > kCandSlots * HT) {                              // uniform
+    int front = 0, cnt = 0;
+    if (lane < p.n_chunks) { front = sh.front[lane]; cnt = sh.cand_count[lane]; }
+    if (wave == 0) leave_runs(lane * p.chunk_tokens + front, cnt, p.n_chunks, sh.cand_runs);
+    lds_barrier();
+    key_range([&](auto f) { walk_runs<4>(sh.cand_runs, sh.run_group, p.n_chunks, 0, p.n_chunks, keys_at, [&](u32x4 x, int e) { f(x[e]); }); }, least,
+              most - least, sh.range, least, most);
+    plateau = least == most;
+    if (plateau) {
+      cut_chunk = __builtin_amdgcn_readfirstlane(chunk_of(sh.cand_start, p.n_pool - n_front - 1));
+      n_front += __builtin_amdgcn_readfirstlane(sh.cand_start[cut_chunk]);
+      n_cand = __builtin_amdgcn_readfirstlane(sh.cand_count[cut_chunk]);
+      lds_barrier();
+      if (wave == 0) {
+        if (lane < cut_chunk) front += cnt;
+        if (lane != cut_chunk) cnt = 0;
+        leave_chunk_counts(front, cnt, p.n_chunks, sh);
+        leave_runs(lane * p.chunk_tokens + front, cnt, p.n_chunks, sh.cand_runs);
+      }
+      lds_barrier();
     }
-    return x;
-  };
-  const int own_chunk = begin / p.chunk_tokens;
-  // the tokens this thread emits first, and those of the part's chunk that lie before it: requested with the tables
-  f32x4 sc, ep, own_sc, own_ep;
-  pick_from_tables(p.table + (size_t)h * p.n_chunks * kTableStride, p.n_chunks, p.n_pool, sh, [&]() {
-    sc = load4(score, begin + 4 * tid, end);
-    ep = load4(eps, begin + 4 * tid, end);
-    own_sc = load4(score, own_chunk * p.chunk_tokens + 4 * tid, begin);
-    own_ep = load4(eps, own_chunk * p.chunk_tokens + 4 * tid, begin);
-  });
-  const int n_front = sh.pick[1], n_cand = sh.pick[2], n_groups = sh.n_groups;
+  }
+  const bool dense = !ALL && n_cand > kCandSlots * HT;                 // uniform; then the registers hold no candidate
+  const int n_groups = __builtin_amdgcn_readfirstlane(sh.n_groups);
+  if (!ALL && wave == 0) {                                             // the entries of the groups beyond the registers
+    const int front = lane < p.n_chunks ? sh.front[lane] : 0;
+    const int here = lane < p.n_chunks ? min(front, max(0, SLOTS * HW - sh.group_start[lane]) * kWave) : 0;
+    leave_runs(lane * p.chunk_tokens + here, front - here, p.n_chunks, sh.front_runs[0]);
+  }
   // group g of the entries in front of the bin
   auto group_at = [&](int g) {
     const int c = chunk_of(sh.group_start, g), first = (g - sh.group_start[c]) * kWave;
@@ -695,58 +787,68 @@ __global__ __launch_bounds__(HT) void route_list_kernel(KernelArgs<RouteParams, 
     if (lane >= sh.group[wave + HW * i].y) key[i] = 0u;
 #pragma unroll
   for (int i = 0; i < kCandSlots; ++i)
-    if (tid + i * HT >= n_cand) ckey[i] = 0u;
+    if (dense || tid + i * HT >= n_cand) ckey[i] = 0u;
   if (tid == 0) { sh.center[0] = ckey[0]; sh.center[1] = n_front > 0 ? key[0] : ceps[0]; }
   lds_barrier();
   const uint32_t center0 = sh.center[0], center1 = sh.center[1];
-  if (n_cand > kRankCap) leave_sample(ckey, center0, sh);
   // Step 1: the pool is the n_pool tokens of highest score
-  const Cut top = list_select(ckey, [&](auto f) {
-    for (int i = kCandSlots * HT + tid; i < n_cand; i += HT) f(bkey[cand_at(i)]);
-  }, n_cand, p.n_pool - n_front, center0, sh);
-  leave_sample(key, center1, sh);                      // before the candidates join: one barrier less
-  int top_tok = kRouteMaxSeqLen;
-  if (!top.all_equal)                                  // uniform
-    top_tok = token_cut([&](auto f) {
-      for (int i = tid; i < n_cand; i += HT) { const int a = cand_at(i); f(bkey[a], bpos[a]); }
-    }, top.thr, top.quota, sh);
-  auto in_pool = [&](uint32_t k, int tok) { return k > top.thr || (k == top.thr && tok <= top_tok); };
-  // Step 3: inside the pool, the n_approx tokens of lowest residual lose their value
-  Cut low = {0xffffffffu, 0, true};                    // n_approx = 0: none
-  int low_tok = kRouteMaxSeqLen;
-#pragma unroll
-  for (int i = 0; i < kCandSlots; ++i) key[SLOTS + i] = ckey[i] != 0u && in_pool(ckey[i], cpos[i]) ? ceps[i] : 0u;
-  // every pool member beyond the registers, or (all) every one: f(residual key, token)
-  auto pool_members = [&](bool all, auto f) {
-    constexpr int U = 8;                               // groups in flight per wave
-    for (int g0 = (all ? 0 : SLOTS * HW) + wave; g0 < n_groups; g0 += U * HW) {
-      uint32_t k[U];
-      int tok[U];
-      bool ok[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int2 g = group_at(min(g0 + u * HW, n_groups - 1));
-        const int f = g.x + min(lane, g.y - 1);
-        k[u] = beps[f];
-        tok[u] = bpos[f];
-        ok[u] = g0 + u * HW < n_groups && lane < g.y;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (ok[u]) f(k[u], tok[u]);
-    }
-    for (int i = (all ? 0 : kCandSlots * HT) + tid; i < n_cand; i += HT) {
-      const int a = cand_at(i), tok = bpos[a];
-      if (in_pool(bkey[a], tok)) f(beps[a], tok);
-    }
-  };
-  if (p.n_approx > 0) {
-    low = list_select(key, [&](auto f) { pool_members(false, [&](uint32_t k, int) { f(k); }); }, p.n_pool, p.n_approx, center1, sh);
-    if (!low.all_equal) low_tok = token_cut([&](auto f) { pool_members(true, f); }, low.thr, low.quota, sh);
+  Cut top = {least, p.n_pool - n_front, all_candidates};
+  if (!plateau) {                                      // uniform
+    if (n_cand > kRankCap && !dense) leave_sample(ckey, center0, sh);
+    top = list_select<true>(ckey, [&](auto f) {
+      if (dense) walk_runs<4>(sh.cand_runs, sh.run_group, p.n_chunks, 0, p.n_chunks, keys_at, [&](u32x4 x, int e) { f(x[e]); });
+    }, n_cand, p.n_pool - n_front, center0, dense, least, most - least, sh);
   }
-  auto is_approx = [&](uint32_t k, int tok) { return p.n_approx > 0 && (k > low.thr || (k == low.thr && tok <= low_tok)); };
-  // Members in front of this part: the lists of the chunks before its own, then the own chunk's tokens before it
-  int pool_before = 0, apx_before = 0;                 // of this lane; counts of whole waves in lane 0
+  leave_sample(key, center1, sh);                      // before the candidates join: one barrier less
+  HeadCut cut;
+  cut.top_thr = top.thr;
+  cut.top_tok = kRouteMaxSeqLen;
+  if (!top.all_equal) {                                // uniform
+    const int first = plateau ? cut_chunk * p.chunk_tokens : 0;
+    cut.top_tok = token_cut([&](int a, int b, auto f) {
+#pragma unroll
+      for (int i = 0; i < kCandSlots; ++i) f(ckey[i], cpos[i]);        // no key is 0
+      if (dense)
+        walk_runs<2>(sh.cand_runs, sh.run_group, p.n_chunks, a / p.chunk_tokens, b / p.chunk_tokens + 1,
+                           [&](int at) { return Tokens{load_entries(bkey, at), load_entries(bpos, at)}; },
+                           [&](const Tokens& x, int e) { f(x.key[e], (int)x.tok[e]); });
+    }, top.thr, top.quota, first, plateau ? min(n, first + p.chunk_tokens) - 1 : n - 1, sh);
+  }
+  // Step 3: inside the pool, the n_approx tokens of lowest residual lose their value
+#pragma unroll
+  for (int i = 0; i < kCandSlots; ++i) key[SLOTS + i] = ckey[i] != 0u && cut.in_pool(ckey[i], cpos[i]) ? ceps[i] : 0u;
+  // every pool member of chunks [c0, c1) beyond the registers, or (every) all of them: f(residual key, token)
+  auto pool_members = [&](bool every, int c0, int c1, auto f) {
+    if (!ALL || every)
+      walk_runs<2>(sh.front_runs[every], sh.run_group, p.n_chunks, c0, c1,
+                   [&](int at) { return Tokens{load_entries(beps, at), load_entries(bpos, at)}; },
+                   [&](const Tokens& x, int e) { f(x.key[e], (int)x.tok[e]); });
+    if (every) {
+#pragma unroll
+      for (int i = 0; i < kCandSlots; ++i)
+        if (key[SLOTS + i] != 0u) f(key[SLOTS + i], cpos[i]);
+    }
+    if (dense)
+      walk_runs<2>(sh.cand_runs, sh.run_group, p.n_chunks, c0, c1,
+                         [&](int at) { return Entries{load_entries(bkey, at), load_entries(bpos, at), load_entries(beps, at)}; },
+                         [&](const Entries& x, int e) { if (cut.in_pool(x.key[e], (int)x.tok[e])) f(x.eps[e], (int)x.tok[e]); });
+  };
+  Cut low = {0xffffffffu, 0, true};                    // n_approx = 0: none
+  cut.low_tok = kRouteMaxSeqLen;
+  if (p.n_approx > 0) {
+    low = list_select<false>(key, [&](auto f) { if (!ALL) pool_members(false, 0, p.n_chunks, [&](uint32_t k, int) { f(k); }); }, p.n_pool,
+                             p.n_approx, center1, false, 1u, 0xfffffffeu, sh);
+    if (!low.all_equal) {
+      if (wave == 0) leave_runs(lane * p.chunk_tokens, lane < p.n_chunks ? sh.front[lane] : 0, p.n_chunks, sh.front_runs[1]);
+      lds_barrier();
+      cut.low_tok = token_cut([&](int a, int b, auto f) { pool_members(true, a / p.chunk_tokens, b / p.chunk_tokens + 1, f); }, low.thr, low.quota,
+                              0, n - 1, sh);
+    }
+  }
+  cut.low_thr = low.thr;
+  cut.any_approx = p.n_approx > 0;
+  // Those in registers by their residuals, or (which of the equal keys?) every one by its token
+  cut.pool_before = cut.apx_before = 0;
   const int own_first = own_chunk * p.chunk_tokens;
   if (low.all_equal) {
     const int groups_before = min(sh.group_start[own_chunk], SLOTS * HW);
@@ -754,31 +856,70 @@ __global__ __launch_bounds__(HT) void route_list_kernel(KernelArgs<RouteParams, 
 #pragma unroll
     for (int i = 0; i < SLOTS; ++i)
       if (wave + HW * i < groups_before) apx += __popcll(__ballot(p.n_approx > 0 && key[i] >= low.thr));      // uniform
-    if (lane == 0) apx_before += apx;
+    if (lane == 0) cut.apx_before += apx;
 #pragma unroll
     for (int i = 0; i < kCandSlots; ++i)
-      if (key[SLOTS + i] != 0u && cpos[i] < own_first) { ++pool_before; apx_before += is_approx(key[SLOTS + i], 0); }
-    pool_members(false, [&](uint32_t k, int tok) {
-      if (tok < own_first) { ++pool_before; apx_before += is_approx(k, tok); }
-    });
+      if (key[SLOTS + i] != 0u && cpos[i] < own_first) { ++cut.pool_before; cut.apx_before += cut.is_approx(key[SLOTS + i], 0); }
     if (tid == 0) {                                    // the register slots' share of the pool: whole chunks and one cut off
       int in_slots = 0;
       for (int c = 0; c < own_chunk; ++c) in_slots += min(sh.front[c], max(0, (groups_before - sh.group_start[c]) * kWave));
-      pool_before += in_slots;
+      cut.pool_before += in_slots;
     }
-  } else {                                             // which of the equal keys: by their tokens
-    pool_members(true, [&](uint32_t k, int tok) {
-      if (tok < own_first) { ++pool_before; apx_before += is_approx(k, tok); }
-    });
   }
+  if (own_chunk > 0 && (!ALL || !low.all_equal))       // uniform
+    pool_members(!low.all_equal, 0, own_chunk, [&](uint32_t k, int tok) {
+      if (tok < own_first) { ++cut.pool_before; cut.apx_before += cut.is_approx(k, tok); }
+    });
+  return cut;
+}
+
+template <int SLOTS, bool RAGGED>
+__global__ __launch_bounds__(HT) void route_list_kernel(KernelArgs<RouteParams, RAGGED> args) {
+  RouteParams p = args.p;
+  int part, h;
+  xcd_chunk_head(part, h);
+  const int launch_head = h;
+  take_sequence<RAGGED>(p, h);
+  const int n = p.n, begin = part * p.part_tokens, end = min(n, begin + p.part_tokens);
+  if (begin >= n) return;
+  __shared__ ListShared sh;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), tid = threadIdx.x;
+  const float* score = p.score + (size_t)h * n;
+  const float* eps = p.eps + (size_t)h * n;
+  auto load4 = [&](const float* a, int t0, int stop) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (t0 + 4 <= stop) {
+      x = *reinterpret_cast<const f32x4_u*>(a + t0);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (t0 + e < stop) x[e] = a[t0 + e];
+    }
+    return x;
+  };
+  const int own_chunk = begin / p.chunk_tokens, own_first = own_chunk * p.chunk_tokens;
+  // the tokens this thread emits first, and those of the part's chunk that lie before it: requested with the tables
+  f32x4 sc, ep, own_sc, own_ep;
+  pick_from_tables(p.table + (size_t)h * p.n_chunks * kTableStride, p.n_chunks, p.n_pool, sh, [&]() {
+    sc = load4(score, begin + 4 * tid, end);
+    ep = load4(eps, begin + 4 * tid, end);
+    own_sc = load4(score, own_first + 4 * tid, begin);
+    own_ep = load4(eps, own_first + 4 * tid, begin);
+  });
+  const bool fits = __builtin_amdgcn_readfirstlane(sh.pick[2]) <= kCandSlots * HT && __builtin_amdgcn_readfirstlane(sh.n_groups) <= SLOTS * HW;
+  HeadCut cut;
+  if (__builtin_expect(fits, 1)) cut = cut_head<SLOTS, true>(p, h, own_chunk, sh);      // uniform
+  else cut = cut_head<SLOTS, false>(p, h, own_chunk, sh);
+  // Members in front of this part: the chunks before its own, then the own chunk's tokens before it
+  int pool_before = cut.pool_before, apx_before = cut.apx_before;
   for (int t = own_first; t < begin; t += kHeadBlock) {
     const int t0 = t + 4 * tid;
     if (t != own_first) { own_sc = load4(score, t0, begin); own_ep = load4(eps, t0, begin); }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const bool pool = t0 + e < begin && in_pool(float_key(own_sc[e]), t0 + e);
+      const bool pool = t0 + e < begin && cut.in_pool(float_key(own_sc[e]), t0 + e);
       pool_before += pool;
-      apx_before += pool && is_approx(~float_key(own_ep[e]), t0 + e);
+      apx_before += pool && cut.is_approx(~float_key(own_ep[e]), t0 + e);
     }
   }
   int base_r, base_a;
@@ -793,6 +934,7 @@ __global__ __launch_bounds__(HT) void route_list_kernel(KernelArgs<RouteParams, 
     base_r = total - total_a;
     lds_barrier();                                     // the rows are used again below
   }
+  p = params_again<RAGGED, RouteParams>(launch_head);
   const int n_retain = p.n_pool - p.n_approx;
   const EmitTarget target = {p.tier + (size_t)h * n, p.idx_retain + (size_t)h * n_retain, p.idx_approx + (size_t)h * p.n_approx, end, n_retain, p.n_approx};
   for (int t = begin; t < end; t += kHeadBlock) {
@@ -800,8 +942,8 @@ __global__ __launch_bounds__(HT) void route_list_kernel(KernelArgs<RouteParams, 
     uint32_t ret4 = 0u, apx4 = 0u;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const bool pool = t0 + e < end && in_pool(float_key(sc[e]), t0 + e);
-      const bool apx = pool && is_approx(~float_key(ep[e]), t0 + e);
+      const bool pool = t0 + e < end && cut.in_pool(float_key(sc[e]), t0 + e);
+      const bool apx = pool && cut.is_approx(~float_key(ep[e]), t0 + e);
       ret4 |= (pool && !apx ? 1u : 0u) << e;
       apx4 |= (apx ? 1u : 0u) << e;
     }
@@ -873,7 +1015,7 @@ RouteLayout route_layout(int n_kv_heads, int seq_len) {
   L.off_map = off;    off += align_up((size_t)n_kv_heads * 2 * sizeof(uint32_t), 256);
   L.off_range = off;  off += align_up((size_t)n_kv_heads * route_mass_range_slots(n_kv_heads, seq_len) * sizeof(float4), 256);
   L.off_table = off;  off += tables;
-  L.off_bkey = off;   off += per_token;
+  L.off_bkey = off;   off += per_token;          // behind other arrays: walk_runs reads up to 12 bytes in front of a list
   L.off_bpos = off;   off += per_token;
   L.off_beps = off;   off += per_token;
   L.total = off;

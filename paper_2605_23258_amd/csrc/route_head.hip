@@ -48,6 +48,7 @@ struct HeadShared {
   __align__(16) int list[kHeadBlock];                  // tokens whose rows this workgroup copies: retained, then approximated
   int wsum[3][HW];
   float stat[3][HW];
+  uint32_t range[2][HW];
   uint32_t center[2];
   int pick[3];            // bucket, #keys above it, keys in it
   int n_cand;
@@ -91,36 +92,32 @@ __device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int 
   lds_barrier();
   if (threadIdx.x == 0) { sh.n_cand = 0; sh.next_key = 0u; }
   cnt = sum_of_waves(sh.stat[0], lane); s1 = sum_of_waves(sh.stat[1], lane); s2 = sum_of_waves(sh.stat[2], lane);
-  const DigitMap map = digit_map_about(center, cnt, s1, s2);
+  auto each = [&](auto f) {
 #pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    if (key[i] != 0u) atomicAdd(&sh.hist[map.digit(key[i])], 1);
-    if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);                // four at a time: the digits of all would not fit the registers
-  }
-  lds_barrier();
-  int d, above, count;
-  pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
-  k -= above;
+    for (int i = 0; i < NS; ++i) {
+      f(key[i]);
+      if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);              // four at a time: the digits of all would not fit the registers
+    }
+  };
   uint32_t lo, span;
-  bucket_range(map, d, lo, span);
-  while (count > kRankCap && span != 0u) {                              // uniform
-    const int s = max(0, 21 - (int)__clz(span));                        // at most 2048 buckets over the range
-    clear_bins(sh.hist);
+  int count;
+  if (!(cnt >= 32.f && s2 == 0.f && around_center(each, center, lo, span, k, count, sh.wsum[0]))) {      // uniform
+    const DigitMap map = digit_map_about(center, cnt, s1, s2);
+    each([&](uint32_t x) { if (x != 0u) atomicAdd(&sh.hist[map.digit(x)], 1); });
     lds_barrier();
-#pragma unroll
-    for (int i = 0; i < NS; ++i)
-      if (key[i] - lo <= span) atomicAdd(&sh.hist[(key[i] - lo) >> s], 1), __builtin_amdgcn_sched_barrier(0);
-    lds_barrier();
+    int d, above;
     pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
     k -= above;
-    lo += (uint32_t)d << s;
-    span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
+    bucket_range(map, d, lo, span);
   }
+  narrow(each, false, lo, span, k, count, sh.hist, sh.wsum[0], sh.pick, sh.range);
   Threshold out;
   if (count > kRankCap) {
-    // one key, many tokens: cut the range of ~token the same way until one is left
+    // one key, many tokens: cut the range of last - token the same way until one is left
     const uint32_t thr = lo;
-    uint32_t tlo = 0u, tspan = 0xffffu;                                 // values 65535 - token
+    constexpr uint32_t kLast = NS * HT - 1;
+    uint32_t tlo = 0u, tspan = k == count ? 0u : kLast;                 // uniform; all of them taken: no cut
+    out.all_equal = tspan == 0u;
     while (tspan != 0u) {
       const int s = max(0, 21 - (int)__clz(tspan));
       clear_bins(sh.hist);
@@ -128,17 +125,18 @@ __device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int 
       const int base = first_token();
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
-        const uint32_t v = 65535u - (uint32_t)head_token(base, i) - tlo;
+        const uint32_t v = kLast - (uint32_t)head_token(base, i) - tlo;
         if (key[i] == thr && v <= tspan) atomicAdd(&sh.hist[v >> s], 1);
         __builtin_amdgcn_sched_barrier(0);
       }
       lds_barrier();
+      int d, above;
       pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
       k -= above;
       tlo += (uint32_t)d << s;
       tspan = min(tspan - ((uint32_t)d << s), (1u << s) - 1u);
     }
-    out.thr = thr; out.tok = 65535u - tlo; out.all_equal = false;
+    out.thr = thr; out.tok = kLast - tlo;
     lds_barrier();
     return out;
   }
@@ -172,6 +170,7 @@ __global__ __launch_bounds__(HT) void route_head_kernel(KernelArgs<HeadParams, R
   int part, h;
   if (RAGGED) { part = blockIdx.x; h = blockIdx.y; }
   else xcd_chunk_head(part, h);
+  const int launch_head = h;
   take_sequence<RAGGED>(p, h);
   const int n = p.n;
   const int n_blocks = (n + kHeadBlock - 1) / kHeadBlock;
@@ -327,6 +326,8 @@ __global__ __launch_bounds__(HT) void route_head_kernel(KernelArgs<HeadParams, R
     }
   }
   const uint64_t in_ret = in_pool & ~in_apx;
+  // fewer tokens leave the registers for them (1024 tokens: the second read costs 0.4 us; 8192 and 12289 gain 0.6 and 1.4)
+  if constexpr (J >= 4) p = params_again<RAGGED, HeadParams>(launch_head);
   // ranks: members in earlier blocks, then the exclusive prefix inside the block
   const uint64_t earlier_slots = ((uint64_t)1 << (4 * block0)) - 1u;
   const int earlier = __popcll(in_ret & earlier_slots) + (__popcll(in_apx & earlier_slots) << 16);
