@@ -143,11 +143,12 @@ VECTOR_API int vector_route(int32_t n_kv_heads, int32_t seq_len, const float* sc
 /* vector_route for callers that cannot allocate device memory or size a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs
  * and errors as vector_route, without ws: the routing kernels' scratch is a device array of
- * VECTOR_ROUTE_STATIC_SCRATCH_BYTES and a half that lives inside the library (one copy per GPU, held until the
+ * VECTOR_ROUTE_STATIC_SCRATCH_BYTES that lives inside the library (one copy per GPU, held until the
  * process ends; its address is looked up on the first call on a device, on the device that is
- * current then).  The call allocates and frees nothing.  VECTOR_ERR_WORKSPACE when
- * the shape needs more scratch than the array holds (what vector_route would ask its caller for;
- * 8 heads of 131072 tokens fit).  Every call on a GPU uses that GPU's one array: calls on different
+ * current then).  The call allocates and frees nothing.  Where vector_route would ask its caller for
+ * more than the array holds (more than 9 heads of 131072 tokens), the heads are routed a group at a time;
+ * VECTOR_ERR_WORKSPACE when it would ask for more than one and a half times the array and 1 MiB (more
+ * than 15 such heads).  Every call on a GPU uses that GPU's one array: calls on different
  * streams of one GPU must not overlap; calls on one stream are ordered and safe.  Nothing in the
  * array has to be cleared between calls (every call rewrites what it reads). */
 #define VECTOR_ROUTE_STATIC_SCRATCH_BYTES (16u << 20)
