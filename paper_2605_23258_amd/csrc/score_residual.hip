@@ -48,12 +48,17 @@ constexpr int kMaxChunks = 256;                 // per head; reached by a single
 
 int units_of(int rows) { return rows <= 128 ? 4 : rows <= 256 ? 8 : 16; }
 
+int stream_tile_tokens(int dtype, int head_dim) { return kStreamTileBytes / (head_dim * (dtype == VECTOR_BF16 ? 2 : 4)); }
+
 }  // namespace
 
-// partials for the longest row block of any group, and the most chunks any plan gives a head
+// Partials for the longest row block of any group, and the most chunks that any plan gives a head: kMaxChunks, of a tile
+// of tokens at least.  A plan for several heads has fewer (256 over the number of heads), but s may be sequences
+// stacked, each with the chunks it would have alone, and how many heads those have the shape does not say.
 static size_t partial_bytes(const vector_shape& s) {
   const int64_t rows = (int64_t)(s.n_q_heads / s.n_kv_heads) * s.window;
-  const int64_t chunks = std::min<int64_t>((s.seq_len + 31) / 32, kMaxChunks);
+  const int64_t tile = stream_tile_tokens(s.dtype, s.head_dim);
+  const int64_t chunks = std::min<int64_t>((s.seq_len + tile - 1) / tile, kMaxChunks);
   return align_up((size_t)s.n_kv_heads * chunks * units_of((int)std::min<int64_t>(rows, 512)) * 32 * sizeof(float2), 256);
 }
 

@@ -25,6 +25,7 @@
 namespace vec {
 
 constexpr int kStreamThreads = 512, kStreamWaves = kStreamThreads / kWave;
+constexpr int kStreamTileBytes = 16384;
 
 struct PassParams {
   const void* q;        // [Hq, w, d]
@@ -79,7 +80,7 @@ __device__ __forceinline__ int w_head(const PassParams& p, int h) { return p.hps
 template <typename T, int D> struct Stream {
   static constexpr int E = Elem<T>::kPerChunk;
   static constexpr int kRowBytes = D * (int)sizeof(T);
-  static constexpr int kTileBytes = 16384;
+  static constexpr int kTileBytes = kStreamTileBytes;
   static constexpr int kTokens = kTileBytes / kRowBytes;     // tokens per tile: 64 (bf16 d = 128, fp32 d = 64), 128 or 32
   static constexpr int kSub = kTokens / 32;                  // 32-token subtiles
   static constexpr int kPieces = kRowBytes / 16;

@@ -97,6 +97,23 @@ def test_batch_workspace_follows_how_the_sequences_share_launches():
     assert batch_bytes([4096, 1000, 2500, 8192, 8192]) == max(ragged, one(8192, 2))
 
 
+@pytest.mark.parametrize("dtype,esz", [("bf16", 2), ("f32", 4)])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,n", [(8, 8192), (1, 600), (64, 4097), (8, 131072)])
+def test_scorer_workspace_holds_a_partial_per_row_and_tile_at_most(dtype, esz, d, heads, n):
+    """Softmax partials (8 bytes per padded query row and chunk; a chunk is one 16 KB tile of keys or more, and a head
+    has at most 256) and the attention mass."""
+    s = vb.Shape(n_q_heads=4 * heads, n_kv_heads=heads, head_dim=d, seq_len=n, window=32, pool_kernel=7,
+                 dtype=vb.VECTOR_BF16 if dtype == "bf16" else vb.VECTOR_F32)
+    route_only = vb.Shape(n_q_heads=heads, n_kv_heads=heads, head_dim=d, seq_len=n, window=1, pool_kernel=1, dtype=s.dtype)
+    tile = 16384 // (d * esz)
+    partials = heads * min(-(-n // tile), 256) * 128 * 8             # 4 x 32 query rows
+    more = vb.vector_compress_workspace_bytes(s, 100, 50) - vb.vector_compress_workspace_bytes(route_only, 100, 50)
+    assert more <= 1024                                              # one to 128 rows: one unit count, one block of partials
+    route = heads * (n * 12 + 33 * 2056 * 2 + 1024 * 16) + 2048      # lists, digit tables, range records
+    assert vb.vector_compress_workspace_bytes(s, 100, 50) <= partials + heads * n * 4 + route
+
+
 def test_batch_and_option_arguments_are_rejected_on_the_host():
     import ctypes as C
     L = vb.lib()
