@@ -98,8 +98,12 @@ __device__ __forceinline__ int wave_incl_scan_dpp(int v) {
 __device__ __forceinline__ int wave_total_of_scan(int incl) { return __builtin_amdgcn_readlane(incl, 63); }
 
 
-// Average pooling ends in sum / kernel: the quotient through the reciprocal and one correction, which is
-// the correctly rounded one (three instructions instead of the ten of a division).
+// Average pooling ends in sum / kernel, correctly rounded with three instructions instead of a division's ten: the
+// product with the rounded reciprocal, corrected once by the remainder (P. Markstein, IBM J. Res. Dev. 34 (1990),
+// 111-119).  Why that is enough here: kernel is an odd integer, below 2^21 say.  The remainder sum - q * kernel is then a
+// whole number, below 2^24, of q's last places, so the inner fma is exact, also for denormals.  And sum / kernel
+// lies at least 1 / (4 kernel) of a last place away from the middle between two floats, further than the
+// reciprocal's error in the correction (2^-23 of a last place) can move it.
 __device__ __forceinline__ float pool_mean(float sum, float kernel, float inv_kernel) {
   const float q = sum * inv_kernel;
   return fmaf(fmaf(-q, kernel, sum), inv_kernel, q);
