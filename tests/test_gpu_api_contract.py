@@ -185,8 +185,8 @@ def test_one_call_pass_equals_the_three_calls(base, over):
 
 
 def test_query_row_limit():
-    """The query rows of a KV head are staged in LDS.  288 rows go in one group; 320 rows go as
-    groups of query heads; a single head's window that does not fit is refused."""
+    """288 and 320 query rows per KV head (nine and ten 32-row units, padded to sixteen); a single head's window beyond
+    the limit of the interface is refused."""
     def run(cfg):
         li = wl.make_layer(cfg, 0)
         shape = pl.shape_of(cfg)

@@ -58,8 +58,8 @@ CASES = {
     # maximum pooling: the vector path (kernel <= 9), the general loop (kernel 13), an unaligned length
     "bf16_maxpool7": ("cfg2", dict(seq_len=2048, n_kv_heads=2, n_q_heads=8, pool_mode="max")),
     "bf16_maxpool5_ragged": ("cfg2", dict(seq_len=1777, n_kv_heads=2, n_q_heads=8, window=24, pool_kernel=5, pool_mode="max")),
-    # more query rows per KV head than the kernels hold at once: the query heads go in groups
-    # (two groups of 4 heads; 4 + 2 heads; 3 + 1 heads of fp32 rows; 6 + 1 heads at d = 64)
+    # 512, 384, 192 (fp32) and 420 query rows per KV head: two 32-row units per wave, some of them padding; one
+    # group of query heads each (more than one: test_gpu_query_groups.py)
     "bf16_G8_w64_groups": ("cfg3", dict(seq_len=1536, n_kv_heads=2, n_q_heads=16, layers=1)),
     "bf16_G6_w64_groups": ("cfg3", dict(seq_len=1300, n_kv_heads=1, n_q_heads=6, layers=1)),
     "f32_d128_G4_w48_groups": ("cfg1", dict(seq_len=700, head_dim=128, n_kv_heads=1, n_q_heads=4, window=48, pool_kernel=3)),
@@ -139,7 +139,7 @@ def _assert_route_equal(score, eps, n_pool, n_approx):
 @pytest.mark.parametrize("n,n_pool,n_approx", [
     (1, 1, 1), (1, 0, 0), (5, 5, 0), (64, 10, 10), (1000, 300, 150), (4096, 1228, 614), (4097, 4097, 2000),
     (5000, 0, 0), (12345, 2469, 1234), (40000, 8000, 4000),
-    # beyond 32768 tokens per head the selection by score runs chip-wide in chunks of 8192
+    # beyond 16384 tokens per head: two launches, chunks of 2048 tokens (4096 beyond 65536)
     (32769, 100, 50), (65536, 65536, 30000), (70000, 40000, 20000), (100000, 1, 1), (49152, 0, 0), (90001, 9000, 0)])
 def test_route_bit_exact_random(n, n_pool, n_approx):
     rng = np.random.default_rng(n * 7 + n_pool)
@@ -163,7 +163,7 @@ def test_route_bit_exact_heavy_ties_and_signed_zero():
 
 
 def test_route_long_sequence_with_heavy_ties():
-    """Ties across chunk boundaries of the chip-wide path: the lowest token indices win."""
+    """Ties across the chunks of the two launches: the lowest token indices win."""
     rng = np.random.default_rng(9)
     n = 50000
     score = rng.integers(0, 4, size=(3, n)).astype(np.float32) * 0.5
@@ -175,9 +175,9 @@ def test_route_long_sequence_with_heavy_ties():
 
 
 def test_route_many_candidates_one_ulp_apart():
-    """More keys share the threshold's bucket than the kernel keeps in LDS, and they are not all
-    equal (two neighbouring floats, for the scores and for the residuals): the select has to go
-    back to memory for every level.  With one value only, the plateau shortcut takes over."""
+    """More keys share the threshold's bucket than the kernel keeps in registers, and they are not all
+    equal (two neighbouring floats, for the scores and for the residuals): every pass over them reads
+    them again.  With one value only they join the pool by whole chunks."""
     rng = np.random.default_rng(21)
     n = 60000
     one, nxt = np.float32(1.0), np.nextafter(np.float32(1.0), np.float32(2.0))

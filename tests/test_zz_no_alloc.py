@@ -47,7 +47,7 @@ def _route_both(H, n, n_pool, n_approx, seed):
 def test_static_scratch_matches_workspace_variant_twice():
     _route_both(8, 32768, 6552, 3276, seed=1)       # a benchmark-sized layer first
     _route_both(3, 5001, 1234, 600, seed=2)         # then a smaller, ragged one on the same scratch
-    _route_both(2, 70000, 9000, 0, seed=3)          # nothing approximated: the split step only copies
+    _route_both(2, 70000, 9000, 0, seed=3)          # nothing approximated: no second selection
 
 
 def test_static_scratch_rejects_what_does_not_fit():
