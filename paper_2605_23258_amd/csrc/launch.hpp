@@ -63,9 +63,10 @@ float* score_mass(const vector_shape& s, void* ws);
 
 // A batch of sequences of different lengths through one set of launches.  Every sequence is
 // the one-sequence problem it would be alone (its own shape with explicit strides, pointers to
-// its own blocks, its own workspace), and gets exactly the parameters that call would compute;
-// the parameter blocks go to `tables` (device, ragged_table_bytes(count) bytes) and every
-// workgroup picks its sequence's block (launch head hv: sequence hv / Hkv, head hv % Hkv).
+// its own blocks, its own workspace), and gets exactly the parameters that call would compute.
+// The parameter blocks are kernel arguments (KernelArgs), or go to `tables` (device,
+// ragged_table_bytes(count) bytes) where they are too many, and every workgroup picks its
+// sequence's block (launch head hv: sequence hv / Hkv, head hv % Hkv).
 constexpr int kMaxRaggedSeqs = 64;
 struct RaggedSeq {
   vector_shape shape;

@@ -33,7 +33,6 @@ struct DigitMap {
     const uint32_t q = key >> shift;
     return min(max(q, lowq) - lowq, 2047u);
   }
-  __device__ __forceinline__ bool shares_high_bits(int d) const { return plain() || (d > 0 && d < 2047); }
 };
 // 2046 buckets of 2^shift keys each over [klo, khi], shift as small as that allows
 __device__ __forceinline__ DigitMap digit_map_for_keys(uint32_t klo, uint32_t khi) {
@@ -117,8 +116,6 @@ struct GatherParams {
   const int32_t* idx_retain; const int32_t* idx_approx;
   int n_retain, n_approx, cap_retain, row_bytes, n;
   unsigned char* k_ret; unsigned char* v_ret; unsigned char* k_apx;
-  const GatherParams* seq_table;               // RAGGED launches: the sequences' parameter blocks, seq_hps heads each
-  int seq_hps;
 };
 
 inline GatherParams gather_params(const vector_shape& s, const void* k, const void* v, const int32_t* idx_retain, const int32_t* idx_approx,
@@ -142,7 +139,6 @@ inline GatherParams gather_params(const vector_shape& s, const void* k, const vo
   p.k_ret = reinterpret_cast<unsigned char*>(k_ret);
   p.v_ret = reinterpret_cast<unsigned char*>(v_ret);
   p.k_apx = reinterpret_cast<unsigned char*>(k_apx);
-  p.seq_table = nullptr; p.seq_hps = 0;
   return p;
 }
 

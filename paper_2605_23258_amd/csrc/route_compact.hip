@@ -137,7 +137,6 @@ __device__ __forceinline__ void counts_to_table(int* hist, uint16_t* table, int*
 // ---------------------------------------------------------------------------
 // buckets of the score keys by leading digit (and, POOL, the pooled score itself)
 // ---------------------------------------------------------------------------
-struct BucketParams;
 struct BucketParams {
   const float* src;       // POOL: attention mass [H, n]; otherwise the scores [H, n]
   float* score;           // POOL: output [H, n]
@@ -149,7 +148,6 @@ struct BucketParams {
   int n, n_prefix, kernel, chunk_tokens, n_chunks;
   float inv_kernel;       // POOL: 1 / kernel
   int take_max;           // POOL: the window's largest mass instead of its sum over the kernel size
-  uint32_t* map;          // [H, 2] with the buckets: the digit map (lowq, shift) this launch chooses, for the selecting launch
   const float4* range;    // [H, n_range] (count, sum l, sum l * l) of the mass left by the scorer's workgroups, when n_range > 0
   int n_range;
   float log_ref;          // what the scorer subtracted from log2(mass)
@@ -246,7 +244,6 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(KernelArgs<BucketParam
       }
       map = digit_map_for_sample(tc, t1, t2);
     }
-    if (chunk == 0 && threadIdx.x == 0) { p.map[2 * h] = map.lowq; p.map[2 * h + 1] = (uint32_t)map.shift; }
     __syncthreads();
   }
   const bool vec4 = (p.n & 3) == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(scores)) & 15u) == 0;
@@ -404,7 +401,6 @@ struct RouteParams {
   const uint32_t* bkey;            // [H, n] score keys grouped by leading digit, chunk by chunk
   const int32_t* bpos;             // their tokens
   const uint32_t* beps;            // and residual keys
-  const uint32_t* map;             // [H, 2]: the digit map (lowq, shift) of the head's score buckets
   uint8_t* tier; int32_t* idx_retain; int32_t* idx_approx;
   GatherParams g;                  // row copies (k null: none)
   const RouteParams* seq_table;    // RAGGED launches: the sequences' parameter blocks, seq_hps heads each
@@ -1003,7 +999,7 @@ static int route_chunk_tokens(int seq_len) {
 namespace {
 struct RouteLayout {
   int chunk_tokens, n_chunks;
-  size_t off_map, off_range, off_table, off_bkey, off_bpos, off_beps, total;
+  size_t off_range, off_table, off_bkey, off_bpos, off_beps, total;
 };
 RouteLayout route_layout(int n_kv_heads, int seq_len) {
   RouteLayout L;
@@ -1012,7 +1008,6 @@ RouteLayout route_layout(int n_kv_heads, int seq_len) {
   const size_t tables = align_up((size_t)n_kv_heads * L.n_chunks * kTableStride * sizeof(uint16_t), 256);
   const size_t per_token = align_up((size_t)n_kv_heads * seq_len * sizeof(uint32_t), 256);
   size_t off = 0;
-  L.off_map = off;    off += align_up((size_t)n_kv_heads * 2 * sizeof(uint32_t), 256);
   L.off_range = off;  off += align_up((size_t)n_kv_heads * route_mass_range_slots(n_kv_heads, seq_len) * sizeof(float4), 256);
   L.off_table = off;  off += tables;
   L.off_bkey = off;   off += per_token;          // behind other arrays: walk_runs reads up to 12 bytes in front of a list
@@ -1028,7 +1023,6 @@ void fill_bucket_params(BucketParams& bp, const RouteLayout& L, void* route_ws) 
   bp.bkey = w8 ? reinterpret_cast<uint32_t*>(w8 + L.off_bkey) : nullptr;
   bp.bpos = w8 ? reinterpret_cast<int32_t*>(w8 + L.off_bpos) : nullptr;
   bp.beps = w8 ? reinterpret_cast<uint32_t*>(w8 + L.off_beps) : nullptr;
-  bp.map = w8 ? reinterpret_cast<uint32_t*>(w8 + L.off_map) : nullptr;
   bp.range = w8 ? reinterpret_cast<const float4*>(w8 + L.off_range) : nullptr;
   bp.n_range = 0;
   bp.log_ref = 0.f;
@@ -1072,7 +1066,6 @@ RouteParams route_params(int n_kv_heads, int all_heads, int seq_len, const float
   // one workgroup per CU: finding the thresholds costs each the same, whatever its part
   const int parts = all_heads >= 256 ? 1 : 256 / all_heads;
   p.part_tokens = (int)(((int64_t)(seq_len + parts - 1) / parts + 63) / 64 * 64);
-  p.map = reinterpret_cast<const uint32_t*>(w8 + L.off_map);
   p.table = reinterpret_cast<const uint16_t*>(w8 + L.off_table);
   p.bkey = reinterpret_cast<const uint32_t*>(w8 + L.off_bkey);
   p.bpos = reinterpret_cast<const int32_t*>(w8 + L.off_bpos);

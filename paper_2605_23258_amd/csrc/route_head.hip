@@ -25,7 +25,6 @@ namespace {
 
 constexpr int kMaxBlocks = 8;                   // 16384 tokens
 
-struct HeadParams;
 struct HeadParams {
   const float* src;       // POOL: attention mass [H, n]; otherwise the scores [H, n]
   float* score;           // POOL: output [H, n]

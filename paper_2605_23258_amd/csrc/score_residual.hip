@@ -138,7 +138,8 @@ static int run_passes(const SeqStack* stack, const vector_shape& s, const vector
 }
 
 // Query heads per pair of passes: all G of a KV head when their G * w rows fit the kernels, else the largest
-// count that does (0: one head's window is longer than the interface allows).
+// count that does (0: one head's window is longer than the interface allows: the lengths that vector_score states.  The
+// kernels would take any of kMaxUnits * 32 rows; fp32 at d = 128 has no more than its 256.)
 template <typename T, int D>
 static int heads_per_group(const vector_shape& s) {
   constexpr int kMaxWindow = sizeof(T) == 4 ? (D == 128 ? 256 : 288) : (D == 128 ? 288 : 384);

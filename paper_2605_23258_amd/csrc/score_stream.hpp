@@ -7,9 +7,9 @@
 // from memory straight into a ring of LDS stages (global_load_lds, 16 bytes a lane), three tiles ahead of
 // their use, with one barrier per tile.  The loads need no registers and no wave waits on its own trip to
 // memory, so the copies run on while the matrix cores and the exponentials work.
-// The kernel before this one kept keys in registers and query rows in LDS: a wave's next keys could only be
-// asked for after the last product of the tile, and its staging (query rows, W^T two bytes at a time)
-// took 5 us per workgroup.
+// With keys in registers and query rows in LDS instead, a wave's next keys can only be asked for after the last product
+// of the tile, and the staging (query rows, W^T two bytes at a time) takes 5 us per workgroup: the times in brackets
+// below.
 // Bounds: 32768 tokens x 8 heads, 256 query rows: 25 us (pass 1; 28 before) and 38 us (pass 2; 39), instruction
 // issue; 131072 tokens, 128 rows: 59 us (63) and 98 us (107), HBM at 4.6 and 5.5 TB/s; 8192 tokens: 9 us (9) and
 // 13 us (19), latency.
@@ -53,13 +53,12 @@ struct PassParams {
                         // l = log2(m) - log_ref; the routing's bucket launch turns them into the head's
                         // typical score range
   int range_stride;     // entries of `range` per head (the second pass's workgroups per head)
-  // Several sequences of different lengths in one launch (template flag RAGGED): the launch's
-  // own parameters only say where the sequences' parameter blocks lie; launch head hv belongs
-  // to sequence hv / seq_hps and is its head hv % seq_hps, and a workgroup whose chunk
-  // index lies beyond its sequence's chunks leaves at once.
   int64_t pos_base;     // post-RoPE keys with a position array: token t of this head is at positions[pos_base + t]
                         // (+ the sequence's share when sequences are stacked)
-  const PassParams* seq_table;
+  // Several sequences of different lengths in one launch (template flag RAGGED, see KernelArgs): launch head hv
+  // belongs to sequence hv / seq_hps and is its head hv % seq_hps, and a workgroup whose chunk index lies beyond
+  // its sequence's chunks leaves at once.
+  const PassParams* seq_table;     // the sequences' parameter blocks, where they are too many for kernel arguments
   int seq_hps;
   const float* lse;     // null, or the log-sum-exp (natural log, logits scaled by 1/sqrt(d)) of every query row,
   int64_t lse_sh;       // row r of query head hq at lse[hq * lse_sh + r]: then pass 2 needs no pass 1
@@ -111,7 +110,7 @@ template <int PER> __device__ __forceinline__ void wait_tiles(int tiles) {
   else wait_loads<0>();
 }
 // own LDS accesses done, then everyone's; no fence of vector memory (the tiles in flight stay in flight)
-__device__ __forceinline__ void lds_barrier() {
+__device__ __forceinline__ void tile_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -384,7 +383,7 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<
   // byte offset of phase ph's subtile in its tile
   auto sub_at = [&](int ph) VEC_INLINE { return (uint32_t)(ww.sub(ph) * 32 * S::kRowBytes); };
   wait_tiles<S::kLoads>(min(kStages1 - 2, n_steps - 1));
-  lds_barrier();
+  tile_barrier();
   keys_op.load(sub_at(0));
   uint32_t slot = 0;
   int t0 = t_begin, left = n_steps;            // tiles from this one on
@@ -415,7 +414,7 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<
     constexpr int kPar = decltype(par_tag)::value;
     if (__builtin_expect(left > kStages1 - 2, 1)) wait_loads<(kStages1 - 3) * S::kLoads>();
     else wait_loads<0>();
-    lds_barrier();                             // tile and successor are there for all, the stage before them is free
+    tile_barrier();                             // tile and successor are there for all, the stage before them is free
     if (to_fetch > 0) fetch();
     finish_chunk();
     const uint32_t next_slot = slot + S::kTileBytes == kRing ? 0 : slot + S::kTileBytes;
@@ -480,7 +479,7 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<
     }
   }
   if (kPaired) {
-    lds_barrier();
+    tile_barrier();
     finish_chunk();
   }
 }
@@ -488,19 +487,6 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<
 // ---------------------------------------------------------------------------
 // pass 2: column mass of the normalised probabilities, and/or the residual
 // ---------------------------------------------------------------------------
-template <typename T> struct Unpack;
-template <> struct Unpack<bf16_t> {   // 16 bytes -> 8 floats
-  static __device__ __forceinline__ void run(const uint4& r, float* f) {
-    f[0] = bf16_lo(r.x); f[1] = bf16_hi(r.x); f[2] = bf16_lo(r.y); f[3] = bf16_hi(r.y);
-    f[4] = bf16_lo(r.z); f[5] = bf16_hi(r.z); f[6] = bf16_lo(r.w); f[7] = bf16_hi(r.w);
-  }
-};
-template <> struct Unpack<float> {    // 16 bytes -> 4 floats
-  static __device__ __forceinline__ void run(const uint4& r, float* f) {
-    f[0] = __uint_as_float(r.x); f[1] = __uint_as_float(r.y); f[2] = __uint_as_float(r.z); f[3] = __uint_as_float(r.w);
-  }
-};
-
 // 16 bytes of un-rotated key elements back into operand form.  bf16 operands cannot hold
 // the turned-back values exactly, so they go to the matrix core twice: the rounded value and
 // the remainder of that rounding (about 2^-17 relative together).
@@ -686,7 +672,11 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArg
       if (half == 0 && ww.has_rows) bias_lds[(ww.unit + 8 * u) * 32 + l31] = qrow[u] < p.R ? bias : INFINITY;
     }
   }
-  // all of it has arrived from here on: nothing below waits on vector memory but wait_tiles
+  // All of it has arrived from here on: what is waited for below are tiles.  The waits count the tiles' loads back from the
+  // last one issued; the counter falls in order of issue, so whatever else lies between (the stores of finish(),
+  // registers spilled to scratch and read back) can make a wait longer than need be, never shorter.  Spilled
+  // registers per lane: bf16 at d = 128 6 to 9 on rotated keys (51 with 16 units; unequal batches 46 to 81), 11 with 16
+  // units (40); fp32 at d = 128 99 to 191, at d = 64 up to 44 (91); elsewhere none.
   if (MASS) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -719,7 +709,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArg
         *reinterpret_cast<uint4*>(w_lds + w_slot(wb_j0 + j, wb_d0 / 8)) = make_uint4(word(0), word(1), word(2), word(3));
       }
     }
-    lds_barrier();
+    tile_barrier();
 #pragma unroll
     for (int c = 0; c < NC; ++c) wf[c] = *reinterpret_cast<const chunk_t*>(w_lds + w_slot(my_dim, 2 * c + half));
   }
@@ -806,7 +796,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArg
 #pragma unroll
         for (int v = lo; v < hi; ++v) {
           float f[E];
-          Unpack<T>::run(vf[v / E], f);
+          Unpack16<T>::run(vf[v / E], f);
           const float df = f[v % E] - res_acc[kOld][v];
           if (v & 1) e1 = fmaf(df, df, e1); else e0 = fmaf(df, df, e0);
         }
@@ -885,8 +875,8 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArg
     const int at_pos = reinterpret_cast<const int*>(smem + tile + 2 * S::kTileBytes)[(tok >> 6) * 64 + (tok & 63)];
     const float pos = (float)((positions ? at_pos : t) + rp.pos_offset);
     float a[E], b[E];
-    Unpack<T>::run(ra, a);
-    Unpack<T>::run(rb, b);
+    Unpack16<T>::run(ra, a);
+    Unpack16<T>::run(rb, b);
     if (!rp.interleaved) {
 #pragma unroll
       for (int e = 0; e < E; ++e) {
@@ -922,7 +912,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArg
   const bool has_mass = MASS && ww.has_rows, has_res = RES && ww.has_res;
   const int sub0 = ww.sub(MASS ? 0 : WW::PH - 1);
   wait_tiles<kPer>(min(kStages - 2, n_steps - 1));
-  lds_barrier();
+  tile_barrier();
   keys_op.load(sub_at(sub0));
   uint32_t tile = 0;
   int step = 0, batch0 = 0, batch0_slot = 0;    // first tile whose sums are not stored yet, and its slot
@@ -933,7 +923,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArg
     constexpr bool kFirst = decltype(first_tag)::value;
     if (__builtin_expect(n_steps - step > kStages - 2, 1)) wait_loads<(kStages - 3) * kPer>();
     else wait_loads<0>();
-    lds_barrier();                             // tile and successor are there for all, the stage before them is free
+    tile_barrier();                             // tile and successor are there for all, the stage before them is free
     if (to_fetch > 0) fetch();
     if (__builtin_expect(step == batch0 + L::kBatch + 1, 0)) {
       finish(batch0, batch0_slot, L::kBatch);
@@ -982,7 +972,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArg
       one(std::integral_constant<int, 2>{});
       one(std::integral_constant<int, 3>{});
       if constexpr (ROPE) {
-        lds_barrier();
+        tile_barrier();
         if (has_res) {
           const uint32_t hi_at = (uint32_t)L::kTurned + sub_at(ww.res_sub);
 #pragma unroll
@@ -1026,7 +1016,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArg
       leave_res(last_slot, err);
     }
   }
-  lds_barrier();
+  tile_barrier();
   while (batch0 < n_steps) {                    // at most two rounds
     finish(batch0, batch0_slot, min(L::kBatch, n_steps - batch0));
     batch0 += L::kBatch;
@@ -1038,9 +1028,9 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArg
     st_l = wave_sum_dpp(st_l);
     st_ll = wave_sum_dpp(st_ll);
     float* part = bias_lds;                    // every wave has read its biases for the last time
-    lds_barrier();
+    tile_barrier();
     if (lane == 0) { part[3 * wave] = st_n; part[3 * wave + 1] = st_l; part[3 * wave + 2] = st_ll; }
-    lds_barrier();
+    tile_barrier();
     if (threadIdx.x == 0) {
       float a = 0.f, b = 0.f, c = 0.f;
 #pragma unroll
