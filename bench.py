@@ -56,8 +56,8 @@ def compress_bytes_per_token_head(cfg) -> dict:
         "score_stats": row,                       # read K
         "mass_residual": row + 8,                 # read V, write mass and eps (K again: not algorithmic)
         "pool_scores": 8,                         # read mass, write score
-        "route": 8 + 1 + 8 * f_p,                 # read score, eps; write tier and index lists
-        "gather_rows": 2 * row * (f_p + f_r),     # read and write pool K rows and retained V rows
+        # read score, eps; write tier and index lists; read and write pool K rows and retained V rows
+        "route": 8 + 1 + 8 * f_p + 2 * row * (f_p + f_r),
     }
     alg["pass"] = sum(alg.values())
     alg["score_residual_pair"] = alg["score_stats"] + alg["mass_residual"]

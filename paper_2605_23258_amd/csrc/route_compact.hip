@@ -15,8 +15,8 @@
 //
 // A launch costs 4 us before it does anything and the first reads of a workgroup depend on each other, so
 // what the workgroups of a head repeat (the pool's residuals, a tenth of the tokens) is cheaper than another launch to
-// share it: with launches for the pool, for its split and for the rows, the routing of 32768 tokens x 8 heads took
-// 40 us (now 9 + 21), of 131072 tokens 65 us (17 + 41, rows 16 of them), of 49157 given scores 36 us (8 + 20).
+// share it.  32768 tokens x 8 heads take 9 + 21 us (with launches for the pool, for its split and for the rows 40),
+// 131072 tokens 17 + 43 (65; rows 16 of the 43), 49157 given scores 8 + 20 (36).
 // Bound: latency of dependent reads and barriers; the rows run at 5 TB/s.
 //
 // Every slot of an output comes from an ordered prefix sum (ties go to the lower token index);

@@ -1,20 +1,27 @@
 // Routing of a whole head in one launch (Section 3.2, Steps 1 and 3, and the packed cache), for heads of
-// up to kHeadTokens tokens: pooling of the attention mass, both selections, tiers, index lists and
+// up to 16384 tokens: pooling of the attention mass, both selections, tiers, index lists and
 // row copies.
 //
 // The chain of selections is latency: with the pieces of a head spread over workgroups, every exchange
-// between them is a kernel boundary, and the boundaries (bucket tables, pool list, split, gather: four
-// launches of 4-12 us whatever the size) cost more than the work.  So nothing is exchanged.  Every workgroup
-// of a head loads the head's scores and residuals whole into registers (16384 tokens: 32 + 32 per thread) and
-// finds both thresholds itself; then it emits and copies its own part of the tokens.  The redundant part
-// is about 50 vector instructions and two LDS atomics per token and workgroup: 16 us at 8192 tokens x 8 heads, 25
-// at 12289, 31 at 20011, against 29 and 28 us for the two launches of route_compact.hip at the last two.  There lies the line
-// between them.
+// between them is a kernel boundary, and a boundary costs 4 us or more whatever the size.  So nothing is exchanged.
+// Every workgroup of a head loads the head's scores and residuals whole into registers (16384 tokens: 32 + 32 per
+// thread) and finds both thresholds itself; then it emits and copies its own part of the tokens.  The redundant
+// part is about 50 vector instructions and two LDS atomics per token and workgroup: 15 us at 8192 tokens x 8 heads,
+// 25 us at 12289.
+//
+// The line to the two launches of route_compact.hip.  A whole compression pass in us, bf16, d = 128, 64 query rows,
+// this launch (with 24576 tokens in registers for the last two lengths) against the two:
+//     heads    2049        8192        14337       16384       20011       24576 tokens
+//       1   24 /  37    29 /  39    40 /  45    39 /  43    44 /  43    45 /  43
+//       8   24 /  37    32 /  43    46 /  51    47 /  51    59 /  57    62 /  61
+//      64   40 /  53   100 / 114   180 / 195   198 / 210   263 / 277   312 / 324
+// Up to 16384 tokens this launch is the faster one for any number of heads.  Beyond, for up to 16 heads, it is not; for many
+// more it still would be by 3 to 5 %, which is not used: registers for 24576 tokens would be one more set of kernels.
 //
 // A selection finds the k-th largest of the keys in registers: one LDS histogram over buckets laid
 // where a sample says that the keys lie (DigitMap), then the keys of the bucket that holds it are ranked
-// against each other by (key, lower token first); a bucket of more keys than kRankCap is cut further by
-// histograms over its own range, and equal keys by histograms over their tokens.
+// against each other by (key, lower token first); a bucket of more keys than kRankCap is cut further over the
+// range its keys really take (narrow()), and equal keys by histograms over their tokens.
 #include "common.hpp"
 #include "launch.hpp"
 #include "route_common.hpp"

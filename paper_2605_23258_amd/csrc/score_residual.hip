@@ -26,8 +26,17 @@ namespace {
 
 // How many tokens a workgroup takes (a multiple of `tile`), so that `count` sequences of n[b] tokens, each
 // with `heads` heads, make at most one workgroup per CU: their LDS lets one run on a CU at a time, and a
-// second, nearly empty round would cost as much as the first.  With too many heads for that to come out
-// even, workgroups are made small instead, four rounds or so.
+// second, nearly empty round would cost as much as the first.  With more than 128 heads, of which one round could
+// take one workgroup each and leave up to half the chip idle, about four rounds of smaller ones instead.
+// Stacked prompts of 8 heads, a compression pass in us, four rounds against one:
+//     heads     1024       2048       4100       8192      16000 tokens
+//      136    76 /  58   97 /  94  159 / 152  269 / 285  481 /  529
+//      192    72 /  60  118 /  97  203 / 175  347 / 330  638 /  636
+//      256    91 /  66  152 / 118  247 / 210  446 / 402  798 /  790
+//      384   107 / 110  205 / 214  349 / 363  630 / 692 1201 / 1322
+// The line holds where the heads do not fill whole rounds and the prompts are long; for short ones, and for a
+// multiple of 256 heads, one round would be better.  Up to 128 heads it is better throughout (64 heads, four rounds
+// against one: 56 / 30 at 1024 tokens, 236 / 210 at 16000).
 int tokens_per_workgroup(const int* n, int count, int64_t heads, int tile) {
   const int64_t target = heads * count > 128 ? 1024 : 256;
   auto workgroups = [&](int64_t tiles) {

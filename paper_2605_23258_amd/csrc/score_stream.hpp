@@ -10,9 +10,9 @@
 // With keys in registers and query rows in LDS instead, a wave's next keys can only be asked for after the last product
 // of the tile, and the staging (query rows, W^T two bytes at a time) takes 5 us per workgroup: the times in brackets
 // below.
-// Bounds: 32768 tokens x 8 heads, 256 query rows: 25 us (pass 1; 28 before) and 38 us (pass 2; 39), instruction
-// issue; 131072 tokens, 128 rows: 59 us (63) and 98 us (107), HBM at 4.6 and 5.5 TB/s; 8192 tokens: 9 us (9) and
-// 13 us (19), latency.
+// Bounds (averages of back-to-back passes): 32768 tokens x 8 heads, 256 query rows: 26 us (28) for pass 1 and 37 us (39)
+// for pass 2, instruction issue; 131072 tokens, 128 rows: 61 us (63) and 103 us (107), HBM at 4.4 and 5.3 TB/s;
+// 8192 tokens: 8.5 us (9) and 13 us (19), latency.
 // A lane's 16 bytes land at lane * 16, so rows cannot be padded: the 16-byte slots of a row are permuted by
 // the row instead (the lane fetches the piece that belongs in its slot), which keeps 16 rows read at one
 // piece in 16 different banks.
