@@ -27,6 +27,9 @@ KINDS = {
     "two_neighbours": lambda rng, sh: _ulps(rng, sh, 2),
     "64_ulps": lambda rng, sh: _ulps(rng, sh, 64),
     "700_ulps": lambda rng, sh: _ulps(rng, sh, 700),
+    # two candidates in the first chunk, at the very start of the head's lists
+    "late": lambda rng, sh: np.where(np.arange(sh[-1]) < 2046, np.float32(-1.0), np.full(sh, 0.25, np.float32)).astype(np.float32),
+    "late_neighbours": lambda rng, sh: np.where(np.arange(sh[-1]) < 2046, np.float32(-1.0), _ulps(rng, sh, 3)).astype(np.float32),
     "zeros": lambda rng, sh: _mostly(rng, sh, 0.95, 0.0, np.exp(4 * rng.standard_normal(sh))),
     "zeros_and_infinities": lambda rng, sh: _mostly(rng, sh, 0.7, 0.0, np.inf),
     "integers": lambda rng, sh: rng.integers(-3, 9, sh).astype(np.float32),
