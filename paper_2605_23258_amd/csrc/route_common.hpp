@@ -143,11 +143,10 @@ inline GatherParams gather_params(const vector_shape& s, const void* k, const vo
 }
 
 // ---------------------------------------------------------------------------
-// workgroups of 512 threads: scans, histogram picks, emission and row copies
+// workgroups of NT threads (512 or 1024): scans, histogram picks, emission and row copies
 // ---------------------------------------------------------------------------
-constexpr int HT = 512;                         // threads of a workgroup
-constexpr int HW = HT / kWave;
-constexpr int kHeadBlock = HT * 4;              // tokens per block: four consecutive ones per thread
+template <int NT> constexpr int kWaves = NT / kWave;
+template <int NT> constexpr int kBlock = NT * 4;        // tokens per block: four consecutive ones per thread
 constexpr int kHeadBins = 2048;
 constexpr int kRankCap = 256;                   // candidates ranked by comparison
 
@@ -168,46 +167,54 @@ __device__ __forceinline__ int low16(int x) { return x & 0xffff; }
 __device__ __forceinline__ int high16(int x) { return (int)((uint32_t)x >> 16); }
 
 // sum of a float over the waves' entries, the same bits in every lane
-__device__ __forceinline__ float sum_of_waves(const float* row, int lane) {
-  static_assert(HW == 8, "eight waves");
-  float x = row[lane & 7];
+template <int NT> __device__ __forceinline__ float sum_of_waves(const float* row, int lane) {
+  static_assert(kWaves<NT> == 8 || kWaves<NT> == 16, "a row of lanes");
+  float x = row[lane & (kWaves<NT> - 1)];
   x += dpp_take_f<0x111, 0xf>(0.f, x);
   x += dpp_take_f<0x112, 0xf>(0.f, x);
   x += dpp_take_f<0x114, 0xf>(0.f, x);
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 7));
+  if constexpr (kWaves<NT> == 16) x += dpp_take_f<0x118, 0xf>(0.f, x);
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), kWaves<NT> - 1));
 }
 
-// exclusive prefix over the workgroup's threads of a packed pair of counts, and the total; row: [HW]
-__device__ __forceinline__ void head_scan(int v, int* row, int& before, int& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// exclusive prefix over the workgroup's threads of a packed pair of counts, and the total; row: [waves]
+template <int NT> __device__ __forceinline__ void head_scan(int v, int* row, int& before, int& total) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int incl = wave_incl_scan_dpp(v);
   if (lane == 63) row[wave] = incl;
   lds_barrier();
-  int x = row[lane & 7];                         // every lane one wave's total
+  int x = row[lane & (kWaves<NT> - 1)];          // every lane one wave's total
   x += dpp_take<0x111, 0xf>(x);
   x += dpp_take<0x112, 0xf>(x);
   x += dpp_take<0x114, 0xf>(x);
+  if constexpr (kWaves<NT> == 16) x += dpp_take<0x118, 0xf>(x);
   const int upto = wave ? __builtin_amdgcn_readlane(x, wave - 1) : 0;
-  total = __builtin_amdgcn_readlane(x, 7);
+  total = __builtin_amdgcn_readlane(x, kWaves<NT> - 1);
   before = upto + incl - v;
 }
 
-__device__ __forceinline__ void clear_bins(int* hist) {
-  static_assert(kHeadBins == 4 * HT, "four buckets per thread");
-  *reinterpret_cast<int4*>(hist + 4 * threadIdx.x) = make_int4(0, 0, 0, 0);
+template <int NT> __device__ __forceinline__ void clear_bins(int* hist) {
+  if constexpr (kHeadBins == 4 * NT) *reinterpret_cast<int4*>(hist + 4 * threadIdx.x) = make_int4(0, 0, 0, 0);
+  else {
+    static_assert(kHeadBins == 2 * NT, "two or four buckets per thread");
+    *reinterpret_cast<int2*>(hist + 2 * threadIdx.x) = make_int2(0, 0);
+  }
 }
 
-// histogram counts -> the bucket with #(keys above it) < k <= #(keys in or above it); row: [HW], pick: [3]
-__device__ __forceinline__ void pick_bin(const int* hist, int* row, int* pick, int k, int& d, int& above, int& count) {
-  const int lo = kHeadBins - 4 - 4 * (int)threadIdx.x;
-  const int4 c = *reinterpret_cast<const int4*>(hist + lo);           // buckets lo .. lo + 3
+// histogram counts -> the bucket with #(keys above it) < k <= #(keys in or above it); row: [waves], pick: [3]
+template <int NT> __device__ __forceinline__ void pick_bin(const int* hist, int* row, int* pick, int k, int& d, int& above, int& count) {
+  constexpr int BPT = kHeadBins / NT;
+  const int lo = kHeadBins - BPT - BPT * (int)threadIdx.x;
+  int c[BPT], sum = 0;                           // buckets lo ..
+#pragma unroll
+  for (int q = 0; q < BPT; ++q) { c[q] = hist[lo + q]; sum += c[q]; }
   int before, total;
-  head_scan(c.x + c.y + c.z + c.w, row, before, total);
-  if (before < k && k <= before + c.x + c.y + c.z + c.w) {
-    int b = lo + 3, in = c.w;
-    if (k > before + in) { before += in; in = c.z; --b; }
-    if (b == lo + 2 && k > before + in) { before += in; in = c.y; --b; }
-    if (b == lo + 1 && k > before + in) { before += in; in = c.x; --b; }
+  head_scan<NT>(sum, row, before, total);
+  if (before < k && k <= before + sum) {
+    int b = lo + BPT - 1, in = c[BPT - 1];
+#pragma unroll
+    for (int q = BPT - 2; q >= 0; --q)
+      if (b == lo + q + 1 && k > before + in) { before += in; in = c[q]; --b; }
     pick[0] = b; pick[1] = before; pick[2] = in;
   }
   lds_barrier();
@@ -252,10 +259,10 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// smallest and largest of the workgroup's keys in [lo, lo + span]; each(f) hands every key to f; row: [2][HW], free
+// smallest and largest of the workgroup's keys in [lo, lo + span]; each(f) hands every key to f; row: [2][waves], free
 // until the barrier after this
-template <typename Each>
-__device__ __forceinline__ void key_range(Each each, uint32_t lo, uint32_t span, uint32_t (*row)[HW], uint32_t& least, uint32_t& most) {
+template <int NT, typename Each>
+__device__ __forceinline__ void key_range(Each each, uint32_t lo, uint32_t span, uint32_t (*row)[kWaves<NT>], uint32_t& least, uint32_t& most) {
   uint32_t a = 0xffffffffu, b = 0u;
   each([&](uint32_t x) {
     const bool in = x - lo <= span;
@@ -268,7 +275,7 @@ __device__ __forceinline__ void key_range(Each each, uint32_t lo, uint32_t span,
   if ((threadIdx.x & 63) == 0) { row[0][wave] = a; row[1][wave] = b; }
   lds_barrier();
 #pragma unroll
-  for (int w = 0; w < HW; ++w) { a = min(a, row[0][w]); b = max(b, row[1][w]); }
+  for (int w = 0; w < kWaves<NT>; ++w) { a = min(a, row[0][w]); b = max(b, row[1][w]); }
   least = (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
   most = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
 }
@@ -278,14 +285,14 @@ __device__ __forceinline__ void key_range(Each each, uint32_t lo, uint32_t span,
 // no count at all, and 64 lanes that add to the same word of a histogram take 64 turns (7 us for 16384 equal
 // keys, against 1 us for the look).  The buckets come in several copies, a lane's own by its number, for the same
 // reason.  tight: [lo, lo + span] starts and ends with a key already.
-template <typename Each>
+template <int NT, typename Each>
 __device__ __forceinline__ void narrow(Each each, bool tight, uint32_t& lo, uint32_t& span, int& k, int& count, int* hist, int* row, int* pick,
-                                       uint32_t (*range)[HW]) {
+                                       uint32_t (*range)[kWaves<NT>]) {
   const int lane = threadIdx.x & 63;
   while (__builtin_expect(count > kRankCap && span != 0u, 0)) {         // uniform
     if (!tight) {
       uint32_t most;
-      key_range(each, lo, span, range, lo, most);
+      key_range<NT>(each, lo, span, range, lo, most);
       span = most - lo;
       if (span == 0u) break;
     }
@@ -294,7 +301,7 @@ __device__ __forceinline__ void narrow(Each each, bool tight, uint32_t& lo, uint
     const uint32_t last = span >> s;
     const int copies_log = min(6, (int)__clz(last) - 21);               // 4 to 64 copies of each
     const int copy = lane & ((1 << copies_log) - 1);
-    clear_bins(hist);
+    clear_bins<NT>(hist);
     lds_barrier();
     each([&](uint32_t x) { if (x - lo <= span) atomicAdd(&hist[(int)(((x - lo) >> s) << copies_log) + copy], 1); });
     lds_barrier();
@@ -304,10 +311,10 @@ __device__ __forceinline__ void narrow(Each each, bool tight, uint32_t& lo, uint
     lds_barrier();
     hist[threadIdx.x] = sum;
 #pragma unroll
-    for (int q = 1; q < kHeadBins / HT; ++q) hist[q * HT + threadIdx.x] = 0;
+    for (int q = 1; q < kHeadBins / NT; ++q) hist[q * NT + threadIdx.x] = 0;
     lds_barrier();
     int d, above;
-    pick_bin(hist, row, pick, k, d, above, count);
+    pick_bin<NT>(hist, row, pick, k, d, above, count);
     k -= above;
     lo += (uint32_t)d << s;
     span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
@@ -316,8 +323,8 @@ __device__ __forceinline__ void narrow(Each each, bool tight, uint32_t& lo, uint
 
 // Whether the k-th largest key lies among those that agree with `center` but for their last 12 bits; then lo, span,
 // k and count describe these.  Worth a try where every key of a sample does (its sum of squares about the
-// center is 0): a histogram would put all of them into a few words.  row: [HW]
-template <typename Each>
+// center is 0): a histogram would put all of them into a few words.  row: [waves]
+template <int NT, typename Each>
 __device__ __forceinline__ bool around_center(Each each, uint32_t center, uint32_t& lo, uint32_t& span, int& k, int& count, int* row) {
   const uint32_t first = center & ~0xfffu;
   int in = 0, above = 0;
@@ -326,9 +333,9 @@ __device__ __forceinline__ bool around_center(Each each, uint32_t center, uint32
     above += x > first + 0xfffu;
   });
   int unused, total_in, total_above;
-  head_scan(in, row, unused, total_in);
+  head_scan<NT>(in, row, unused, total_in);
   lds_barrier();                                                        // the row is used again
-  head_scan(above, row, unused, total_above);
+  head_scan<NT>(above, row, unused, total_above);
   if (k <= total_above || k > total_above + total_in) return false;    // uniform
   lo = first;
   span = 0xfffu;
@@ -373,7 +380,7 @@ __device__ __forceinline__ void emit_tokens(const EmitTarget& o, int t0, uint32_
 }
 // Their rows into the packed cache: retained keys, retained values, approximated keys; each set goes to
 // consecutive rows.
-__device__ __forceinline__ void copy_rows(const GatherParams& g, int h, int n_approx, const int* list, int own_r, int own_a, int base_r, int base_a) {
+template <int NT> __device__ __forceinline__ void copy_rows(const GatherParams& g, int h, int n_approx, const int* list, int own_r, int own_a, int base_r, int base_a) {
   const int pieces = g.row_bytes / 16, log_pieces = 31 - __clz(pieces);
   const int64_t hs = g.hps ? h / g.hps : 0, hh = g.hps ? h % g.hps : h;
   const unsigned char* k_head = g.k + hs * g.k_sb + hh * g.k_sh;
@@ -383,12 +390,12 @@ __device__ __forceinline__ void copy_rows(const GatherParams& g, int h, int n_ap
   unsigned char* k_apx = g.k_apx + ((size_t)h * n_approx + base_a) * g.row_bytes;
   const int items = (2 * own_r + own_a) << log_pieces;
   constexpr int U = 4;
-  for (int i0 = threadIdx.x; i0 < items; i0 += HT * U) {
+  for (int i0 = threadIdx.x; i0 < items; i0 += NT * U) {
     u32x4 x[U];
     unsigned char* to[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = min(i0 + u * HT, items - 1);
+      const int i = min(i0 + u * NT, items - 1);
       const int row = i >> log_pieces, piece = i & (pieces - 1);
       const bool is_v = row >= own_r && row < 2 * own_r, is_a = row >= 2 * own_r;
       const int t = list[is_v || is_a ? row - own_r : row];
@@ -399,7 +406,7 @@ __device__ __forceinline__ void copy_rows(const GatherParams& g, int h, int n_ap
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (i0 + u * HT < items) *reinterpret_cast<u32x4*>(to[u]) = x[u];
+      if (i0 + u * NT < items) *reinterpret_cast<u32x4*>(to[u]) = x[u];
   }
 }
 

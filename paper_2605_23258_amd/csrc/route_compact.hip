@@ -407,6 +407,9 @@ struct RouteParams {
   int seq_hps;
 };
 
+constexpr int HT = 512;                  // threads of the list kernel
+constexpr int HW = kWaves<HT>;
+constexpr int kHeadBlock = kBlock<HT>;
 constexpr int kMaxGroups = 64 * HW;      // as many as the registers of a workgroup hold
 
 // Per chunk a run of the head's lists: its first entry, its length, and the groups of kRunGroup entries before it
@@ -612,22 +615,22 @@ __device__ __forceinline__ Cut list_select(const uint32_t (&key)[NS], More more,
   if (threadIdx.x == 0) sh.n_cand = 0;
   if ((int)threadIdx.x < kRankCap) sh.cand[threadIdx.x] = 0u;
   if (total > kRankCap && !tight) {                                     // uniform
-    clear_bins(sh.hist);
+    clear_bins<HT>(sh.hist);
     lds_barrier();
-    const float cnt = sum_of_waves(sh.stat[0], lane), s1 = sum_of_waves(sh.stat[1], lane), s2 = sum_of_waves(sh.stat[2], lane);
-    if (!(cnt >= 32.f && s2 == 0.f && around_center(each_first, center, lo, span, k, count, sh.wsum[0]))) {
+    const float cnt = sum_of_waves<HT>(sh.stat[0], lane), s1 = sum_of_waves<HT>(sh.stat[1], lane), s2 = sum_of_waves<HT>(sh.stat[2], lane);
+    if (!(cnt >= 32.f && s2 == 0.f && around_center<HT>(each_first, center, lo, span, k, count, sh.wsum[0]))) {
       const DigitMap map = digit_map_about(center, cnt, s1, s2);
       each_first([&](uint32_t x) { if (x != 0u) atomicAdd(&sh.hist[map.digit(x)], 1); });
       lds_barrier();
       int d, above;
-      pick_bin(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
+      pick_bin<HT>(sh.hist, sh.wsum[0], sh.pick, k, d, above, count);
       k -= above;
       bucket_range(map, d, lo, span);
     }
   } else {
     lds_barrier();
   }
-  narrow(each, tight, lo, span, k, count, sh.hist, sh.wsum[0], sh.pick, sh.range);
+  narrow<HT>(each, tight, lo, span, k, count, sh.hist, sh.wsum[0], sh.pick, sh.range);
   if (span == 0u) { lds_barrier(); return {lo, k, count == k}; }        // one key, however many tokens
   auto collect = [&](uint32_t x) {
     if (x - lo <= span) {
@@ -669,14 +672,14 @@ __device__ __forceinline__ int token_cut(Each each, uint32_t thr, int quota, int
   while (span != 0u) {
     const int s = max(0, 21 - (int)__clz(span));
     int d, above, count;
-    clear_bins(sh.hist);
+    clear_bins<HT>(sh.hist);
     lds_barrier();
     each(last - (int)(lo + span), last - (int)lo, [&](uint32_t key, int tok) {
       const uint32_t v = (uint32_t)(last - tok) - lo;
       if (key == thr && v <= span) atomicAdd(&sh.hist[v >> s], 1);
     });
     lds_barrier();
-    pick_bin(sh.hist, sh.wsum[0], sh.pick, quota, d, above, count);
+    pick_bin<HT>(sh.hist, sh.wsum[0], sh.pick, quota, d, above, count);
     quota -= above;
     lo += (uint32_t)d << s;
     span = min(span - ((uint32_t)d << s), (1u << s) - 1u);
@@ -727,7 +730,7 @@ __device__ __forceinline__ HeadCut cut_head(const RouteParams& p, int h, int own
     if (lane < p.n_chunks) { front = sh.front[lane]; cnt = sh.cand_count[lane]; }
     if (wave == 0) leave_runs(lane * p.chunk_tokens + front, cnt, p.n_chunks, sh.cand_runs);
     lds_barrier();
-    key_range([&](auto f) { walk_runs<4>(sh.cand_runs, sh.run_group, p.n_chunks, 0, p.n_chunks, keys_at, [&](u32x4 x, int e) { f(x[e]); }); }, least,
+    key_range<HT>([&](auto f) { walk_runs<4>(sh.cand_runs, sh.run_group, p.n_chunks, 0, p.n_chunks, keys_at, [&](u32x4 x, int e) { f(x[e]); }); }, least,
               most - least, sh.range, least, most);
     plateau = least == most;
     if (plateau) {
@@ -944,12 +947,12 @@ __global__ __launch_bounds__(HT) void route_list_kernel(KernelArgs<RouteParams, 
       apx4 |= (apx ? 1u : 0u) << e;
     }
     int at, own;
-    head_scan(__popc(ret4) + (__popc(apx4) << 16), sh.wsum[0], at, own);
+    head_scan<HT>(__popc(ret4) + (__popc(apx4) << 16), sh.wsum[0], at, own);
     const int own_r = low16(own), own_a = high16(own);
     if (t0 < end) emit_tokens(target, t0, ret4, apx4, low16(at), high16(at), own_r, base_r, base_a, sh.list);
     if (t + kHeadBlock < end) { sc = load4(score, t0 + kHeadBlock, end); ep = load4(eps, t0 + kHeadBlock, end); }
     lds_barrier();                                     // the list is whole
-    if (p.g.k) copy_rows(p.g, h, p.n_approx, sh.list, own_r, own_a, base_r, base_a);
+    if (p.g.k) copy_rows<HT>(p.g, h, p.n_approx, sh.list, own_r, own_a, base_r, base_a);
     base_r += own_r;
     base_a += own_a;
     lds_barrier();                                     // the list may be written again
