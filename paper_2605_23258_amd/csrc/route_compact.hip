@@ -26,6 +26,7 @@
 // gather_rows_kernel: row gather k_ret / v_ret / k_apx by the index lists.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "common.hpp"
 #include "launch.hpp"
@@ -38,8 +39,6 @@ namespace {
 constexpr int kBins = 2048;
 constexpr int kTableStride = kBins + 8;   // 16-bit entries of a D table: D[0 .. 2048] and padding to 16 bytes
 constexpr int EPT = 4;                    // consecutive elements per thread and tile (one 16-byte load)
-constexpr int BT = 512;                   // threads of the bucket kernel
-constexpr int kBucketTile = BT * EPT;
 constexpr int kStageTokens = 4096;        // a chunk's bucket list is put together in LDS up to this length
 constexpr int kMinChunk = 2048;           // tokens per chunk: doubled until a head has at most kMaxChunks
 constexpr int kMaxChunks = 32;
@@ -72,6 +71,13 @@ __device__ __forceinline__ void hist_add_thread_keys(int* hist, const uint32_t (
   uint32_t dg[EPT];
 #pragma unroll
   for (int j = 0; j < EPT; ++j) dg[j] = map.digit(key[j]);
+  // lanes that mostly go elsewhere than the first one: every key for itself
+  if (__popcll(__ballot(ok[0] && dg[0] == (uint32_t)__builtin_amdgcn_readfirstlane((int)dg[0]))) <= 8) {      // uniform
+#pragma unroll
+    for (int j = 0; j < EPT; ++j)
+      if (ok[j]) atomicAdd(&hist[dg[j]], 1);
+    return;
+  }
   int first = -1;
 #pragma unroll
   for (int j = EPT - 1; j >= 0; --j)
@@ -155,7 +161,11 @@ struct BucketParams {
   int seq_hps;
 };
 
-template <bool POOL, bool RAGGED = false>
+// Chunks of 2048 tokens: 512 threads; longer ones 1024, so that those of up to 4096 are one tile too.  What bounds it is
+// latency: statistics, inputs, a histogram, a scan, the scatter.  The inputs travel while the statistics are turned into the
+// map, by 16-byte loads at any element (a head whose length is no multiple of four took an element at a time: 20011
+// tokens x 8 heads 2 us more).
+template <int BT, bool POOL, bool RAGGED = false>
 __global__ __launch_bounds__(BT) void route_bucket_kernel(KernelArgs<BucketParams, RAGGED> args) {
   BucketParams p = args.p;
   int chunk, h;
@@ -184,13 +194,31 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(KernelArgs<BucketParam
     }
   }
   const float* src = p.src + (size_t)h * p.n;
-  const float* scores = POOL ? p.score + (size_t)h * p.n : src;
   const int begin = chunk * p.chunk_tokens, end = min(p.n, begin + p.chunk_tokens);
-  // the thread's first four inputs are requested now and only touched (not used) after the map is
-  // there: they travel while the statistics are turned into the map, and the first tile's loads
-  // below find them in the cache
-  float warm = 0.f;
-  if (do_buckets && p.n_range > 0) warm = src[min(begin + (int)threadIdx.x * EPT, p.n - 1)];
+  constexpr int kBucketTile = BT * EPT;
+  // tokens t .. t + 3 of a head's array; 0 outside [first, stop)
+  auto load4 = [&](const float* a, int t, int first, int stop) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (t >= first && t + 4 <= stop) {
+      x = *reinterpret_cast<const f32x4_u*>(a + t);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (t + e >= first && t + e < stop) x[e] = a[t + e];
+    }
+    return x;
+  };
+  const float* scores = POOL ? p.score + (size_t)h * p.n : src;
+  const float* eps = do_buckets ? p.eps + (size_t)h * p.n : nullptr;
+  // The first tile's inputs are requested before the statistics are turned into the map: the masses around the thread's
+  // four tokens (POOL: enough for kernels of up to 9, the usual ones), or the scores; and the residuals.
+  const int half = POOL ? p.kernel / 2 : 0;
+  constexpr int kNear = POOL ? 3 : 1;
+  const int first_t0 = begin + (int)threadIdx.x * EPT;
+  f32x4 near0[kNear], eps0 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q = 0; q < kNear; ++q) near0[q] = load4(src, first_t0 + (q - kNear / 2) * EPT, 0, POOL ? p.n : end);
+  if (do_buckets) eps0 = load4(eps, first_t0, 0, end);
   if (do_buckets) {
     for (int i = threadIdx.x; i < kBins; i += BT) hist[i] = 0;
     if (p.n_range > 0) {
@@ -203,7 +231,6 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(KernelArgs<BucketParam
         cnt += x.x; sl += x.y; sll += x.z;
       }
       map = digit_map_for_stats(wave_sum_dpp(cnt), wave_sum_dpp(sl), wave_sum_dpp(sll), p.log_ref);
-      asm volatile("" ::"v"(warm));
     }
     if (!POOL) {
       // no statistics came with the scores: four keys out of every 256, the same sample in every
@@ -246,30 +273,7 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(KernelArgs<BucketParam
     }
     __syncthreads();
   }
-  const bool vec4 = (p.n & 3) == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(scores)) & 15u) == 0;
-  auto load_scores = [&](int t0, float (&s)[EPT]) {
-    if (vec4 && t0 + EPT <= end) {
-      const float4 x = *reinterpret_cast<const float4*>(scores + t0);
-      s[0] = x.x; s[1] = x.y; s[2] = x.z; s[3] = x.w;
-    } else {
-#pragma unroll
-      for (int j = 0; j < EPT; ++j) s[j] = t0 + j < end ? scores[t0 + j] : 0.f;
-    }
-  };
-  const float* eps = do_buckets ? p.eps + (size_t)h * p.n : nullptr;
-  const bool eps4 = vec4 && (reinterpret_cast<uintptr_t>(eps) & 15u) == 0;
-  auto load_eps = [&](int t0, float (&e)[EPT]) {
-    if (eps4 && t0 + EPT <= end) {
-      const float4 x = *reinterpret_cast<const float4*>(eps + t0);
-      e[0] = x.x; e[1] = x.y; e[2] = x.z; e[3] = x.w;
-    } else {
-#pragma unroll
-      for (int j = 0; j < EPT; ++j) e[j] = t0 + j < end ? eps[t0 + j] : 0.f;
-    }
-  };
   uint32_t key0[EPT];                            // the keys of the first tile stay in registers for the scatter
-  float eps0[EPT];                               // and its residuals, requested with the scores
-  if (do_buckets) load_eps(begin + (int)threadIdx.x * EPT, eps0);
   for (int tile = begin; tile < end; tile += kBucketTile) {        // uniform trip count: whole waves take part
     const int t0 = tile + (int)threadIdx.x * EPT;
     float s[EPT];
@@ -277,50 +281,59 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(KernelArgs<BucketParam
 #pragma unroll
     for (int j = 0; j < EPT; ++j) ok[j] = t0 + j < end;
     if (POOL) {
-      const int half = p.kernel / 2;
-      if (vec4 && half <= EPT && t0 >= EPT && t0 + 2 * EPT <= p.n) {
-        // the 12 mass values around the thread's four tokens in three loads; each window is
-        // folded in ascending token order, like the general loop below (mass is never negative,
-        // so the maximum may start from zero)
-        float m[3 * EPT];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-          const float4 x = *reinterpret_cast<const float4*>(src + t0 - EPT + q * EPT);
-          m[q * EPT + 0] = x.x; m[q * EPT + 1] = x.y; m[q * EPT + 2] = x.z; m[q * EPT + 3] = x.w;
-        }
+      // windows of 2 half + 1 masses, folded in ascending token order over the prefix columns; mass is never
+      // negative, so the sums and maxima may start from zero
+      auto fold = [&](auto quads_tag, const f32x4* m) {
+        constexpr int Q = decltype(quads_tag)::value;        // quads on either side
 #pragma unroll
         for (int j = 0; j < EPT; ++j) {
-          const int t = t0 + j;
           float acc = 0.f;
 #pragma unroll
-          for (int d = -EPT; d <= EPT; ++d)
-            if (d >= -half && d <= half && t + d < p.n_prefix) acc = p.take_max ? fmaxf(acc, m[EPT + j + d]) : acc + m[EPT + j + d];
-          s[j] = (ok[j] && t < p.n_prefix) ? (p.take_max ? acc : pool_mean(acc, (float)p.kernel, p.inv_kernel)) : INFINITY;
+          for (int d = -Q * EPT; d <= Q * EPT; ++d) {
+            const int at = Q * EPT + j + d;
+            if (d >= -half && d <= half && t0 + j + d < p.n_prefix) acc = p.take_max ? fmaxf(acc, m[at >> 2][at & 3]) : acc + m[at >> 2][at & 3];
+          }
+          s[j] = acc;
         }
+      };
+      if (half <= EPT) {
+        f32x4 m[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) m[q] = tile == begin ? near0[q] : load4(src, t0 + (q - 1) * EPT, 0, p.n);
+        fold(std::integral_constant<int, 1>{}, m);
+      } else if (half <= 2 * EPT) {
+        f32x4 m[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) m[q] = load4(src, t0 + (q - 2) * EPT, 0, p.n);
+        fold(std::integral_constant<int, 2>{}, m);
       } else {
 #pragma unroll
         for (int j = 0; j < EPT; ++j) {
-          const int t = t0 + j;
-          float out = INFINITY;                                      // window columns
-          if (ok[j] && t < p.n_prefix) {
-            const int lo = max(0, t - half), hi = min(p.n_prefix - 1, t + half);
-            float acc = 0.f;
+          const int t = t0 + j, lo = max(0, t - half), hi = min(p.n_prefix - 1, t + half);
+          float acc = 0.f;
+          if (ok[j])
             for (int i = lo; i <= hi; ++i) acc = p.take_max ? fmaxf(acc, src[i]) : acc + src[i];
-            out = p.take_max ? acc : pool_mean(acc, (float)p.kernel, p.inv_kernel);
-          }
-          s[j] = out;
+          s[j] = acc;
         }
       }
       float* dst = p.score + (size_t)h * p.n;
-      if (vec4 && ok[EPT - 1]) {
-        *reinterpret_cast<float4*>(dst + t0) = make_float4(s[0], s[1], s[2], s[3]);
+#pragma unroll
+      for (int j = 0; j < EPT; ++j) {
+        if (!p.take_max) s[j] = pool_mean(s[j], (float)p.kernel, p.inv_kernel);
+        if (!ok[j] || t0 + j >= p.n_prefix) s[j] = INFINITY;         // window columns
+      }
+      if (ok[EPT - 1]) {
+        const f32x4 x = {s[0], s[1], s[2], s[3]};
+        *reinterpret_cast<f32x4_u*>(dst + t0) = x;
       } else {
 #pragma unroll
         for (int j = 0; j < EPT; ++j)
           if (ok[j]) dst[t0 + j] = s[j];
       }
     } else {
-      load_scores(t0, s);
+      const f32x4 x = tile == begin ? near0[0] : load4(scores, t0, 0, end);
+#pragma unroll
+      for (int j = 0; j < EPT; ++j) s[j] = x[j];
     }
     if (do_buckets) {
       uint32_t key[EPT];
@@ -347,16 +360,15 @@ __global__ __launch_bounds__(BT) void route_bucket_kernel(KernelArgs<BucketParam
   for (int tile = begin; tile < end; tile += kBucketTile) {
     const int t0 = tile + (int)threadIdx.x * EPT;
     uint32_t key[EPT];
-    float ev[EPT];
+    f32x4 ev = eps0;
     if (tile == begin) {
 #pragma unroll
-      for (int j = 0; j < EPT; ++j) { key[j] = key0[j]; ev[j] = eps0[j]; }
+      for (int j = 0; j < EPT; ++j) key[j] = key0[j];
     } else {                                     // later tiles: the scores this thread stored (or read) above
-      float s[EPT];
-      load_scores(t0, s);
-      load_eps(t0, ev);
+      const f32x4 x = load4(scores, t0, 0, end);
+      ev = load4(eps, t0, 0, end);
 #pragma unroll
-      for (int j = 0; j < EPT; ++j) key[j] = float_key(s[j]);
+      for (int j = 0; j < EPT; ++j) key[j] = float_key(x[j]);
     }
 #pragma unroll
     for (int j = 0; j < EPT; ++j) {
@@ -407,10 +419,13 @@ struct RouteParams {
   int seq_hps;
 };
 
-constexpr int HT = 512;                  // threads of the list kernel
+// Threads of the list kernel: every workgroup works through the head's pool, so sixteen waves share it (the routing of
+// 8 heads, sixteen waves against eight, in us: 20.0 / 20.4 at 32768 tokens, 24.5 / 25.9 at 65536, 34.5 / 38.3 at 131072).
+constexpr int HT = 1024;
 constexpr int HW = kWaves<HT>;
 constexpr int kHeadBlock = kBlock<HT>;
-constexpr int kMaxGroups = 64 * HW;      // as many as the registers of a workgroup hold
+constexpr int kTableGroups = kBins / 8;  // of eight bins
+constexpr int kMaxGroups = HT;           // as many as the registers of a workgroup hold, at most
 
 // Per chunk a run of the head's lists: its first entry, its length, and the groups of kRunGroup entries before it
 struct Runs {
@@ -421,7 +436,8 @@ constexpr int kRunGroup = 4 * kWave;     // entries that a wave takes at a time
 struct ListShared {
   __align__(16) int hist[kHeadBins];
   __align__(16) int list[kHeadBlock];    // tokens whose rows this workgroup copies: retained, then approximated
-  int coarse[HT + 1];                    // sums of the tables at every fourth bin
+  int coarse[HT / kTableGroups][kTableGroups + 2];      // sums of the tables at every eighth bin, the highest first, over every fourth chunk
+  __align__(16) uint16_t digit[kMaxChunks][16];         // the chosen eight bins' entries of every chunk's table, and the next bin's
   // per chunk: entries in front of the chosen bin, the groups of 64 of them before the chunk's, the entries
   // of the bin (candidates) before the chunk's, and the chunk's own
   int front[kMaxChunks], group_start[kMaxChunks], cand_start[kMaxChunks], cand_count[kMaxChunks];
@@ -463,59 +479,74 @@ __device__ __forceinline__ void leave_runs(int at, int count, int n_chunks, Runs
 
 // Leading digit of the k-th largest key of a head from the D tables of its chunks: summed over the
 // chunks, S[b] = #(digit >= b) falls from the key count at b = 0 to 0 at b = 2048, and the digit is
-// the one bin with S[b+1] < k <= S[b].  Two steps, because what this costs is load instructions: thread t
-// sums only the entry at the low end of its four bins (b = 2044 - 4t); the entry above its bins is
-// its neighbour's sum, and one thread finds k between the two.  Then lane c of wave 0 reads that thread's bins
-// of chunk c, and the sums over the lanes give the digit, and with it where every chunk keeps its entries.
-// prefetch() is called once the first loads are out.
+// the one bin with S[b+1] < k <= S[b].  What this costs is load instructions (16 cycles of a CU's address unit each,
+// however narrow) and trips to memory.  So a thread takes eight bins of every fourth chunk, 16 bytes a load and all in
+// one trip; the threads whose bins hold k, and those that hold the next bin up, leave their chunks' entries in LDS,
+// where lane c of wave 0 finds chunk c's: that gives the digit, and where every chunk keeps its entries.  (With two bytes
+// of every table per load and a second trip for the digit, routing and rows of 49157 given scores took 37.6 us, now 35.5.)
+// prefetch() is called once the loads are out.
 template <typename Prefetch>
 __device__ __forceinline__ void pick_from_tables(const uint16_t* tables, int n_chunks, int k, ListShared& sh, Prefetch prefetch) {
+  constexpr int kPer = HT / kTableGroups, kLoads = kMaxChunks / kPer;      // chunks taken side by side, one after the other
+  static_assert(HT % kTableGroups == 0 && kMaxChunks % kPer == 0 && kTableGroups % kWave == 0, "whole waves on a chunk");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lo = kBins - 4 - 4 * (int)threadIdx.x;
-  int s_lo = 0;
-  uint16_t e[2][kMaxChunks / 2];                // all chunks' entries requested together
+  const int t = (int)threadIdx.x % kTableGroups, first = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kTableGroups);
+  const int lo = kBins - 8 - 8 * t;             // the thread's bins: lo .. lo + 7
+  u32x4 e[2][kLoads / 2];
+  auto load_half = [&](int v) {
 #pragma unroll
-  for (int u = 0; u < kMaxChunks / 2; ++u) e[0][u] = tables[(size_t)min(u, n_chunks - 1) * kTableStride + lo];
-  if (n_chunks > kMaxChunks / 2) {              // uniform
+    for (int u = 0; u < kLoads / 2; ++u)
+      e[v][u] = *reinterpret_cast<const u32x4*>(tables + (size_t)min(first + (v * (kLoads / 2) + u) * kPer, n_chunks - 1) * kTableStride + lo);
+  };
+  load_half(0);
 #pragma unroll
-    for (int u = 0; u < kMaxChunks / 2; ++u) e[1][u] = tables[(size_t)min(kMaxChunks / 2 + u, n_chunks - 1) * kTableStride + lo];
-  }
+  for (int u = 0; u < kLoads / 2; ++u) e[1][u] = u32x4{0u, 0u, 0u, 0u};
+  if (n_chunks > kMaxChunks / 2) load_half(1);  // uniform
   prefetch();
+  int own = 0;                                  // S[lo] over the thread's chunks
 #pragma unroll
-  for (int u = 0; u < kMaxChunks / 2; ++u)
-    if (u < n_chunks) s_lo += (int)e[0][u];
-  if (n_chunks > kMaxChunks / 2) {
-#pragma unroll
-    for (int u = 0; u < kMaxChunks / 2; ++u)
-      if (kMaxChunks / 2 + u < n_chunks) s_lo += (int)e[1][u];
-  }
-  sh.coarse[threadIdx.x + 1] = s_lo;            // coarse[t + 1] = S[2044 - 4t]; coarse[0] = S[2048] = 0
-  if (threadIdx.x == 0) { sh.coarse[0] = 0; sh.pick[0] = 0; }       // no bracket (k outside the counts): the second step still reads inside the tables
+  for (int u = 0; u < kLoads; ++u)
+    if (first + u * kPer < n_chunks) own += (int)(e[u / (kLoads / 2)][u % (kLoads / 2)][0] & 0xffffu);
+  sh.coarse[first][t + 1] = own;
+  if ((int)threadIdx.x < kPer) { sh.coarse[threadIdx.x][0] = 0; sh.coarse[threadIdx.x][kTableGroups + 1] = 0; }
+  if (threadIdx.x == 0) sh.pick[0] = 0;
   lds_barrier();
-  const int s_hi = sh.coarse[threadIdx.x];      // S at the bin above this thread's four
-  if (s_hi < k && k <= s_lo) sh.pick[0] = lo;
+  int above = 0, here = 0, below = 0;           // S[lo + 8], S[lo], S[lo - 8]
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) { above += sh.coarse[q][t]; here += sh.coarse[q][t + 1]; below += sh.coarse[q][t + 2]; }
+  if (above < k && k <= here) {
+    sh.pick[0] = lo;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u)
+      *reinterpret_cast<u32x4*>(&sh.digit[first + u * kPer][0]) = e[u / (kLoads / 2)][u % (kLoads / 2)];
+  } else if (here < k && k <= below) {          // k is in the eight bins below: their upper end is this thread's
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) sh.digit[first + u * kPer][8] = (uint16_t)(e[u / (kLoads / 2)][u % (kLoads / 2)][0] & 0xffffu);
+  }
   lds_barrier();
   if (wave == 0) {
     const int at = sh.pick[0];
-    int d[5] = {0, 0, 0, 0, 0};
+    int d[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) d[q] = 0;
     if (lane < n_chunks) {
-      const uint16_t* t = tables + (size_t)lane * kTableStride + at;
-      const uint2 v = *reinterpret_cast<const uint2*>(t);
-      d[0] = (int)(v.x & 0xffffu); d[1] = (int)(v.x >> 16); d[2] = (int)(v.y & 0xffffu); d[3] = (int)(v.y >> 16);
-      d[4] = t[4];
+      const u32x4 x = *reinterpret_cast<const u32x4*>(&sh.digit[lane][0]);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) d[q] = (int)((x[q / 2] >> (16 * (q % 2))) & 0xffffu);
+      d[8] = at + 8 < kBins ? sh.digit[lane][8] : 0;
     }
-    int S[5], j = 0;
+    int S[9], j = 0;
 #pragma unroll
-    for (int q = 0; q < 5; ++q) S[q] = wave_total_of_scan(wave_incl_scan_dpp(d[q]));
+    for (int q = 0; q < 9; ++q) S[q] = wave_total_of_scan(wave_incl_scan_dpp(d[q]));
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < 8; ++q)
       if (S[q + 1] < k && k <= S[q]) j = q;
-    int front = d[1], cnt = d[0] - d[1], above = S[1], count = S[0] - S[1];
+    int front = d[1], cnt = d[0] - d[1], in_front = S[1], count = S[0] - S[1];
 #pragma unroll
-    for (int q = 1; q < 4; ++q)
-      if (j == q) { front = d[q + 1]; cnt = d[q] - d[q + 1]; above = S[q + 1]; count = S[q] - S[q + 1]; }
+    for (int q = 1; q < 8; ++q)
+      if (j == q) { front = d[q + 1]; cnt = d[q] - d[q + 1]; in_front = S[q + 1]; count = S[q] - S[q + 1]; }
     leave_chunk_counts(front, cnt, n_chunks, sh);
-    if (lane == 0) { sh.pick[0] = at + j; sh.pick[1] = above; sh.pick[2] = count; }
+    if (lane == 0) { sh.pick[0] = at + j; sh.pick[1] = in_front; sh.pick[2] = count; }
   }
   lds_barrier();
 }
@@ -688,7 +719,7 @@ __device__ __forceinline__ int token_cut(Each each, uint32_t thr, int quota, int
   return last - (int)lo;
 }
 
-constexpr int kCandSlots = 4;            // candidates per thread kept in registers
+constexpr int kCandSlots = 2;            // candidates per thread kept in registers
 
 // Where a head's tokens are cut: in_pool() and, inside the pool, is_approx(), of order-preserving keys and tokens; and how
 // many of the pool, and of its approximated tokens, this thread found in the chunks before the workgroup's own
@@ -763,7 +794,7 @@ __device__ __forceinline__ HeadCut cut_head(const RouteParams& p, int h, int own
     const int c = chunk_of(sh.cand_start, idx);
     return c * p.chunk_tokens + sh.front[c] + idx - sh.cand_start[c];
   };
-  static_assert(SLOTS * HW <= kMaxGroups && kMaxGroups == HT, "one group per thread");
+  static_assert(SLOTS * HW <= kMaxGroups && kMaxGroups == HT, "at most one group per thread");
   sh.group[tid] = tid < n_groups ? group_at(tid) : make_int2(0, 0);
   uint32_t ckey[kCandSlots], ceps[kCandSlots], key[SLOTS + kCandSlots];
   int cpos[kCandSlots];
@@ -993,6 +1024,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(GatherParams p) {
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
+static int bucket_threads(int chunk_tokens) { return chunk_tokens <= kMinChunk ? 512 : 1024; }
 static int route_chunk_tokens(int seq_len) {
   int ch = kMinChunk;
   while ((seq_len + ch - 1) / ch > kMaxChunks) ch *= 2;
@@ -1081,9 +1113,9 @@ RouteParams route_params(int n_kv_heads, int all_heads, int seq_len, const float
 // the fewest register slots that hold the pool: its groups of 64, a last one that is not full per chunk, over the waves
 template <bool RAGGED> void (*list_kernel(int n_pool, int n_chunks))(KernelArgs<RouteParams, RAGGED>) {
   const int groups = n_pool / kWave + n_chunks;
+  if (groups <= 8 * HW) return route_list_kernel<8, RAGGED>;
   if (groups <= 16 * HW) return route_list_kernel<16, RAGGED>;
-  if (groups <= 32 * HW) return route_list_kernel<32, RAGGED>;
-  return route_list_kernel<64, RAGGED>;
+  return route_list_kernel<32, RAGGED>;
 }
 unsigned route_parts(const RouteParams& p) { return (unsigned)((p.n + p.part_tokens - 1) / p.part_tokens); }
 
@@ -1099,8 +1131,8 @@ int launch_pool_scores(const float* mass, float* score, const float* eps, int n_
   if (n_range < 0 || n_range > route_mass_range_slots(n_kv_heads, seq_len) || (route_ws && !eps)) return VECTOR_ERR_ARG;
   RouteLayout L;
   const BucketParams bp = pool_bucket_params(mass, score, eps, n_kv_heads, seq_len, n_prefix, pool_kernel, pool_mode, route_ws, n_range, L);
-  auto kernel = route_bucket_kernel<true, false>;
-  VEC_LAUNCH(K_POOL, kernel, dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, KernelArgs<BucketParams, false>{bp});
+  const auto kernel = L.chunk_tokens <= kMinChunk ? route_bucket_kernel<512, true, false> : route_bucket_kernel<1024, true, false>;
+  VEC_LAUNCH(K_POOL, kernel, dim3(L.n_chunks, n_kv_heads), dim3(bucket_threads(L.chunk_tokens)), 0, stream, KernelArgs<BucketParams, false>{bp});
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
@@ -1126,7 +1158,8 @@ int launch_route(int n_kv_heads, int seq_len, const float* score, const float* e
     BucketParams bp;
     bp.src = score; bp.score = nullptr; bp.eps = eps; bp.n = seq_len; bp.n_prefix = seq_len; bp.kernel = 1; bp.inv_kernel = 1.f; bp.take_max = 0;
     fill_bucket_params(bp, L, ws);
-    hipLaunchKernelGGL((route_bucket_kernel<false, false>), dim3(L.n_chunks, n_kv_heads), dim3(BT), 0, stream, KernelArgs<BucketParams, false>{bp});
+    const auto kernel = L.chunk_tokens <= kMinChunk ? route_bucket_kernel<512, false, false> : route_bucket_kernel<1024, false, false>;
+    hipLaunchKernelGGL(kernel, dim3(L.n_chunks, n_kv_heads), dim3(bucket_threads(L.chunk_tokens)), 0, stream, KernelArgs<BucketParams, false>{bp});
   }
   hipLaunchKernelGGL(list_kernel<false>(n_pool, p.n_chunks), dim3(route_parts(p), n_kv_heads), dim3(HT), 0, stream, KernelArgs<RouteParams, false>{p});
   if (t_) timing_end(K_ROUTE, stream);
@@ -1157,18 +1190,20 @@ int launch_pool_scores_ragged(const PoolSeq* seqs, int count, int n_kv_heads, in
   if (count < 1 || count > kMaxRaggedSeqs) return VECTOR_ERR_ARG;
   BucketParams host[kMaxRaggedSeqs];
   unsigned gx = 0;
+  int longest_chunk = 0;
   for (int b = 0; b < count; ++b) {
     if (!seqs[b].route_ws || !seqs[b].eps || seqs[b].n_range < 0 || seqs[b].n_range > route_mass_range_slots(n_kv_heads, seqs[b].seq_len)) return VECTOR_ERR_ARG;
     RouteLayout L;
     host[b] = pool_bucket_params(seqs[b].mass, seqs[b].score, seqs[b].eps, n_kv_heads, seqs[b].seq_len, seqs[b].n_prefix, pool_kernel, pool_mode,
                                  seqs[b].route_ws, seqs[b].n_range, L);
     if ((unsigned)L.n_chunks > gx) gx = (unsigned)L.n_chunks;
+    longest_chunk = std::max(longest_chunk, L.chunk_tokens);
   }
   KernelArgs<BucketParams, true> args;
   const int rc = ragged_args(host, count, n_kv_heads, tables, stream, args);
   if (rc != VECTOR_OK) return rc;
-  auto kernel = route_bucket_kernel<true, true>;
-  VEC_LAUNCH(K_POOL, kernel, dim3(gx, (unsigned)count * n_kv_heads), dim3(BT), 0, stream, args);
+  const auto kernel = longest_chunk <= kMinChunk ? route_bucket_kernel<512, true, true> : route_bucket_kernel<1024, true, true>;
+  VEC_LAUNCH(K_POOL, kernel, dim3(gx, (unsigned)count * n_kv_heads), dim3(bucket_threads(longest_chunk)), 0, stream, args);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
