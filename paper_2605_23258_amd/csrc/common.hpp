@@ -11,6 +11,7 @@ namespace vec {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_u;   // 16-byte access at any element
 
 constexpr int kWave = 64;
 
@@ -121,6 +122,11 @@ __device__ __forceinline__ P params_again(int launch_head) {
     p = read_constant<P>((p.seq_table ? (uint64_t)p.seq_table : at + sizeof(P)) + (size_t)seq * sizeof(P));
   }
   return p;
+}
+
+// LDS address of a pointer into LDS
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p;
 }
 
 __device__ __forceinline__ chunk_t load_chunk(const void* p) { return *reinterpret_cast<const chunk_t*>(p); }

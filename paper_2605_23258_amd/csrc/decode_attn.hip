@@ -386,7 +386,8 @@ __global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeP
 // ---------------------------------------------------------------------------
 constexpr int kTileRows = 32;
 
-typedef __attribute__((ext_vector_type(8))) unsigned short u16x8;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(8))) short s16x8;
 
 template <int D> struct MfmaDecodeTile {
   static constexpr int kRowBytes = D * 2;
@@ -410,7 +411,9 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
   constexpr int JB = D / 32;               // 32-wide blocks of the output dimension
   constexpr int PSZ = 2 * G + G * D;
   constexpr float kNegBig = -1.0e30f;      // running maximum before any row: finite, so differences stay finite
-  static_assert(DW * (G * D + 2 * G) * 4 <= TL::kLdsBytes, "merge area must fit in the tile area");
+  constexpr int kRedStride = D + 4;        // floats per row of the merge area: 16-byte writes of 2 G rows hit distinct banks
+  static_assert(DW * (2 * G * kRedStride + 2 * G) * 4 <= TL::kLdsBytes, "merge area must fit in the tile area");
+  static_assert(2 * G <= 32, "weights and their remainders side by side");
 
   extern __shared__ __align__(16) unsigned char dec_lds[];
 
@@ -438,16 +441,20 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
 
   unsigned char* k_tile = dec_lds + wave * 2 * TL::kTileBytes;
   unsigned char* v_tile = k_tile + TL::kTileBytes;
-  const unsigned char* r_tile = (is_apx && !ROPE) ? k_tile : v_tile;
+  // Rows of the second product down their columns, by the transposing LDS read: of the 16 lanes of a group, lane i hands in
+  // the place of 4 consecutive columns of row i / 4 and gets the four rows of column i.
+  const uint32_t r_at = lds_address((is_apx && !ROPE) ? k_tile : v_tile) + (uint32_t)((4 * half + (lane & 15) / 4) * TL::kStride +
+                                                                                      (((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2);
   const bool literal = LITERAL && is_apx;                    // rebuild every approximated value row
 
-  // B operand of the score product: query row g on lane g, zero beyond G
+  // B operand of the score product: query row g on lanes g and G + g, zero beyond
+  const float remainder = l31 >= G ? 1.f : 0.f;
   chunk_t qf[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     qf[c] = make_uint4(0, 0, 0, 0);
-    if (l31 < G)
-      qf[c] = load_chunk(reinterpret_cast<const T*>(p.q) + ((size_t)b * p.Hq + (size_t)h * G + l31) * D + (2 * c + half) * 8);
+    if (l31 < 2 * G)
+      qf[c] = load_chunk(reinterpret_cast<const T*>(p.q) + ((size_t)b * p.Hq + (size_t)h * G + l31 % G) * D + (2 * c + half) * 8);
   }
 
   f32x16 o[JB];
@@ -610,15 +617,13 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
         for (int v = 0; v < 16; ++v) o[jb][v] *= alpha;
       m_run = m_new;
     }
-    // ---- weights, split into a bf16 value and the bf16 remainder ----
-    bf16x8 p_hi[2], p_lo[2];
+    // ---- weights: their bf16 values on lanes g, the bf16 remainders on lanes G + g ----
+    bf16x8 pw[2];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const float pv = fast_exp2(s[v] - m_run);
       l_run += pv;
-      const __bf16 hi = (__bf16)pv;
-      p_hi[v >> 3][v & 7] = hi;
-      p_lo[v >> 3][v & 7] = (__bf16)(pv - (float)hi);
+      pw[v >> 3][v & 7] = (__bf16)fmaf(-remainder, (float)(__bf16)pv, pv);
     }
     // ---- output: contraction index e of step ks on lane half `half` is tile row
     //      16 ks + 4 half + 8 (e / 4) + e % 4, the row accumulator register 8 ks + e holds ----
@@ -646,9 +651,8 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
             v_hi[e] = hi;
             v_lo[e] = (__bf16)(x - (float)hi);
           }
-          o[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_hi, p_hi[ks], o[jb], 0, 0, 0);
-          o[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_lo, p_hi[ks], o[jb], 0, 0, 0);
-          o[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_hi, p_lo[ks], o[jb], 0, 0, 0);
+          o[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_hi, pw[ks], o[jb], 0, 0, 0);
+          o[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_lo, pw[ks], o[jb], 0, 0, 0);
         }
       }
       return;
@@ -657,14 +661,12 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
     for (int jb = 0; jb < JB; ++jb) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        u16x8 a;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int row = 16 * ks + 4 * half + 8 * (e >> 2) + (e & 3);
-          a[e] = *reinterpret_cast<const unsigned short*>(r_tile + row * TL::kStride + (jb * 32 + l31) * 2);
-        }
-        o[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), p_hi[ks], o[jb], 0, 0, 0);
-        o[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), p_lo[ks], o[jb], 0, 0, 0);
+        typedef __attribute__((address_space(3))) s16x4 lds_quad;
+        const uint32_t at = r_at + (uint32_t)(16 * ks * TL::kStride + jb * 64);
+        const s16x4 a0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)at);
+        const s16x4 a1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)(at + 8 * TL::kStride));
+        const s16x8 a = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
+        o[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pw[ks], o[jb], 0, 0, 0);
       }
     }
   };
@@ -702,48 +704,209 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
   // ---- merge the waves ----
   const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
   __syncthreads();                                   // every wave is done with its tiles: reuse the area
-  float* red = reinterpret_cast<float*>(dec_lds);                    // [DW][G][D]
-  float* ml = red + DW * G * D;                                       // [DW][2][G]
-  if (l31 < G) {
+  float* red = reinterpret_cast<float*>(dec_lds);                    // [DW][2 G][kRedStride]: weights' part, remainders' part
+  float* ml = red + DW * 2 * G * kRedStride;                          // [DW][2][G]
+  if (l31 < 2 * G) {
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) red[(wave * G + l31) * D + jb * 32 + acc_row(v, half)] = o[jb][v];
-    if (half == 0) {
+      for (int v = 0; v < 16; v += 4) {
+        const f32x4 x = {o[jb][v], o[jb][v + 1], o[jb][v + 2], o[jb][v + 3]};
+        *reinterpret_cast<f32x4*>(red + (wave * 2 * G + l31) * kRedStride + jb * 32 + acc_row(v, half)) = x;
+      }
+    if (half == 0 && l31 < G) {
       ml[(wave * 2 + 0) * G + l31] = (l_tot > 0.f) ? m_run : -INFINITY;
       ml[(wave * 2 + 1) * G + l31] = l_tot;
     }
   }
   __syncthreads();
+  // a wave without rows has m = -inf and nothing but zeros: its share is 0 without a branch
   float* out = p.part + (bh * (p.splits_ret + p.splits_apx) + split) * PSZ;
-  for (int i = threadIdx.x; i < G * D; i += DT_) {
+  for (int i = threadIdx.x * 4; i < G * D; i += DT_ * 4) {
     const int g = i / D, j = i % D;
-    float m = -INFINITY;
+    float mw[DW], m = -INFINITY, l = 0.f;
 #pragma unroll
-    for (int wv = 0; wv < DW; ++wv) m = fmaxf(m, ml[(wv * 2) * G + g]);
-    float a = 0.f;
-#pragma unroll
-    for (int wv = 0; wv < DW; ++wv) {
-      const float mw = ml[(wv * 2) * G + g];
-      if (mw != -INFINITY) a += red[(wv * G + g) * D + j] * fast_exp2(mw - m);
-    }
-    out[2 * G + i] = a;
-  }
-  if (threadIdx.x < G) {
-    const int g = threadIdx.x;
-    float m = -INFINITY, l = 0.f;
-#pragma unroll
-    for (int wv = 0; wv < DW; ++wv) m = fmaxf(m, ml[(wv * 2) * G + g]);
+    for (int wv = 0; wv < DW; ++wv) { mw[wv] = ml[(wv * 2) * G + g]; m = fmaxf(m, mw[wv]); }
+    const float m_safe = m == -INFINITY ? 0.f : m;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int wv = 0; wv < DW; ++wv) {
-      const float mw = ml[(wv * 2) * G + g];
-      if (mw != -INFINITY) l += ml[(wv * 2 + 1) * G + g] * fast_exp2(mw - m);
+      const float sc = fast_exp2(mw[wv] - m_safe);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(red + (wv * 2 * G + g) * kRedStride + j);
+      const f32x4 y = *reinterpret_cast<const f32x4*>(red + (wv * 2 * G + G + g) * kRedStride + j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = fmaf(x[e] + y[e], sc, a[e]);
+      l = fmaf(ml[(wv * 2 + 1) * G + g], sc, l);
     }
-    out[g] = m;
-    out[G + g] = l;
+    *reinterpret_cast<f32x4_u*>(out + 2 * G + i) = a;
+    if (j == 0) {
+      out[g] = m;
+      out[G + g] = l;
+    }
   }
 }
 
+// Merge of the splits for bf16 caches, one workgroup per (sequence, KV head): reference and sum of every query row,
+// the weighted sums of the splits, z W, the division.  What bounds it is load instructions (16 cycles of the CU's
+// address unit each) and one trip to memory: a thread takes four neighbouring elements of every SG-th split with
+// 16-byte loads, the splits' references and sums go through LDS.  z W runs on the matrix cores: z in three bf16 parts
+// (all of its 24 bits), eight query rows by three parts on the M side, W's columns by the transposing LDS read.
+// Element by element, with z W on the vector unit, a step of one sequence (11 splits, four query heads) took 14.8 us, now
+// 11.9; with eight query heads per KV head (12 splits) 46.9 and 41.1.
+template <int D, int G> struct CombineLds {
+  static constexpr int kQuads = G * D / 4;
+  static constexpr int kSide = kQuads >= 256 ? 1 : 256 / kQuads;         // splits taken side by side
+  static constexpr int kRounds = (kQuads + 255) / 256;
+  static constexpr int kBlocks = (G + 7) / 8;                            // of eight query rows
+  static constexpr int kStride = D * 2 + 16;                             // bytes of a row of W, and of z's parts
+  static constexpr int kMl = 2 * kMaxSplits * 2 * G * 4, kParts = kBlocks * 32 * kStride;      // not at the same time
+  static constexpr int kSums = (kMl > kParts ? kMl : kParts);            // [2: retained, approximated][kSide][G * D]
+  static constexpr int kW = kSums + 2 * kSide * G * D * 4;
+  static constexpr int kInv = kW + D * kStride;
+  static constexpr int kTotal = kInv + G * 4;
+};
+template <int D, int G>
+__global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p) {
+  using T = bf16_t;
+  using L = CombineLds<D, G>;
+  constexpr int PSZ = 2 * G + G * D, WL = D * D / 8 / 256, kFlight = 8;
+  extern __shared__ __align__(16) unsigned char dec_lds[];
+  float* ml = reinterpret_cast<float*>(dec_lds);                         // [splits][2 G]
+  float* sums = reinterpret_cast<float*>(dec_lds + L::kSums);
+  float* inv = reinterpret_cast<float*>(dec_lds + L::kInv);
+  const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const size_t bh = (size_t)b * p.Hkv + h;
+  const int n_splits = p.splits_ret + p.splits_apx, n_ret = p.literal ? n_splits : p.splits_ret;      // literal partials are values already
+  const float* part = p.part + bh * n_splits * PSZ;
+  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l31 = lane & 31;
+  const bool use_w = p.n_approx > 0 && !p.literal;
+
+  // this thread's elements, and its first splits
+  const int quad = tid % L::kQuads, side = L::kSide > 1 ? tid / L::kQuads : 0;
+  const bool has_quad = side < L::kSide;
+  f32x4 x0[kFlight];
+  auto load_splits = [&](int round, int s0, f32x4* x) {
+    const int at = min(round * 256 + quad, L::kQuads - 1) * 4;
+#pragma unroll
+    for (int u = 0; u < kFlight; ++u) x[u] = *reinterpret_cast<const f32x4_u*>(part + (size_t)min(s0 + u * L::kSide, n_splits - 1) * PSZ + 2 * G + at);
+  };
+  for (int i = tid; i < n_splits * 2 * G; i += 256) ml[i] = part[(size_t)(i / (2 * G)) * PSZ + i % (2 * G)];
+  load_splits(0, min(side, n_splits - 1), x0);
+  uint4 wraw[WL];
+  const T* Wh = reinterpret_cast<const T*>(p.W) + (int64_t)h * p.w_sh;
+  if (use_w) {
+#pragma unroll
+    for (int i = 0; i < WL; ++i) wraw[i] = load_chunk(Wh + (size_t)(i * 256 + tid) * 8);
+  }
+  // the step's own token is now a row of the cache (the split launch has finished): one thread per
+  // sequence makes it live, unless the block was full
+  if (p.k_new && h == 0 && tid == 0) {
+    const int cap = p.cap_retain_seq ? max(p.cap_retain_seq[b], 0) : p.cap_retain;
+    int* len = const_cast<int*>(p.len_retain) + b;
+    *len = min(min(max(*len, 0), cap) + 1, cap);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int round = 0; round < L::kRounds; ++round) {
+    const int at = round * 256 + quad, g = min(at * 4, G * D - 1) / D;
+    float m = -INFINITY, l = 0.f;
+#pragma unroll 4
+    for (int s = 0; s < n_splits; ++s) m = fmaxf(m, ml[s * 2 * G + g]);
+    const float m_safe = m == -INFINITY ? 0.f : m;
+    f32x4 av = {0.f, 0.f, 0.f, 0.f}, az = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = side; s0 < n_splits; s0 += kFlight * L::kSide) {
+      f32x4 x[kFlight];
+      if (round == 0 && s0 == side) {
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) x[u] = x0[u];
+      } else {
+        load_splits(round, s0, x);
+      }
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        const int s = s0 + u * L::kSide;
+        if (s < n_splits) {
+          const float sc = fast_exp2(ml[s * 2 * G + g] - m_safe), cv = s < n_ret ? sc : 0.f, cz = sc - cv;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { av[e] = fmaf(x[u][e], cv, av[e]); az[e] = fmaf(x[u][e], cz, az[e]); }
+        }
+      }
+    }
+    if (has_quad && at < L::kQuads) {
+      *reinterpret_cast<f32x4*>(sums + side * G * D + at * 4) = av;
+      *reinterpret_cast<f32x4*>(sums + (L::kSide + side) * G * D + at * 4) = az;
+      if (side == 0 && at * 4 % D == 0) {
+#pragma unroll 4
+        for (int s = 0; s < n_splits; ++s) l = fmaf(ml[s * 2 * G + G + g], fast_exp2(ml[s * 2 * G + g] - m_safe), l);
+        inv[g] = l > 0.f ? 1.f / l : 0.f;
+      }
+    }
+  }
+  unsigned char* w_tile = dec_lds + L::kW;
+  if (use_w) {
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+      const int piece = i * 256 + tid;
+      *reinterpret_cast<uint4*>(w_tile + piece / (D / 8) * L::kStride + piece % (D / 8) * 16) = wraw[i];
+    }
+  }
+  __syncthreads();
+  // z, and its parts: part q of query row g in row (g / 8) * 32 + q * 8 + g % 8; inside 16 contraction indices 8 a + 4 h + c
+  // in the order 8 h + 4 a + c, which is how the transposing read hands out W's rows
+  for (int i = tid * 4; i < G * D; i += 1024) {
+    const int g = i / D, j = i % D;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f}, z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < L::kSide; ++q) {
+      v += *reinterpret_cast<const f32x4*>(sums + q * G * D + i);
+      z += *reinterpret_cast<const f32x4*>(sums + (L::kSide + q) * G * D + i);
+    }
+    if (L::kSide > 1) *reinterpret_cast<f32x4*>(sums + i) = v;
+    if (use_w) {
+      const int within = j & 15, pos = (j & ~15) + 8 * ((within >> 2) & 1) + 4 * (within >> 3);
+      unsigned char* row = dec_lds + ((g / 8) * 32 + g % 8) * L::kStride + pos * 2;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const uint2 w = make_uint2(pack_bf16(z[0], z[1]), pack_bf16(z[2], z[3]));
+        *reinterpret_cast<uint2*>(row + q * 8 * L::kStride) = w;
+        z[0] -= bf16_lo(w.x); z[1] -= bf16_hi(w.x); z[2] -= bf16_lo(w.y); z[3] -= bf16_hi(w.y);
+      }
+    }
+  }
+  __syncthreads();
+  if (wave * 32 >= D) return;
+  const int j = wave * 32 + l31;
+  const uint32_t w_at = lds_address(w_tile) + (uint32_t)((4 * half + (lane & 15) / 4) * L::kStride + (wave * 32 + ((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2);
+#pragma unroll
+  for (int blk = 0; blk < L::kBlocks; ++blk) {
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    if (use_w) {
+#pragma unroll
+      for (int c = 0; c < D / 16; ++c) {
+        typedef __attribute__((address_space(3))) s16x4 lds_quad;
+        const uint32_t at = w_at + (uint32_t)(16 * c * L::kStride);
+        const s16x4 b0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)at);
+        const s16x4 b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)(at + 8 * L::kStride));
+        const chunk_t a = *reinterpret_cast<const chunk_t*>(dec_lds + (blk * 32 + min(l31, 23)) * L::kStride + (16 * c + 8 * half) * 2);
+        mma_chunk<T>(acc, a, __builtin_bit_cast(chunk_t, __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7)));
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int g = blk * 8 + half * 4 + i;
+      if (g < G) {
+        const float r = (sums[g * D + j] + (acc[i] + (acc[4 + i] + acc[8 + i]))) * inv[g];
+        const size_t at = ((size_t)b * p.Hq + (size_t)h * G + g) * D + j;
+        if (p.out_f32) reinterpret_cast<float*>(p.out)[at] = r;
+        else store_elem(reinterpret_cast<T*>(p.out) + at, r);
+      }
+    }
+  }
+}
+
+// the same for fp32 caches, z W on the vector unit
 template <typename T, int D, int G>
 __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
   constexpr int PSZ = 2 * G + G * D;
@@ -928,7 +1091,13 @@ int run_decode_layout(const vector_cache& c, DecodeParams& p, hipStream_t stream
       VEC_LAUNCH(K_DECODE_SPLIT, (decode_split_kernel<T, D, G, PAGED, false>), grid, dim3(DT_), 0, stream, p, RopeParams{});
     }
   }
-  VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_kernel<T, D, G>), dim3(c.n_kv_heads, c.batch), dim3(256), 0, stream, p);
+  if constexpr (Elem<T>::kDtype == VECTOR_BF16) {
+    constexpr int lds = CombineLds<D, G>::kTotal;
+    VEC_HIP(set_max_lds(reinterpret_cast<const void*>(decode_combine_mfma_kernel<D, G>), lds));
+    VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_mfma_kernel<D, G>), dim3(c.n_kv_heads, c.batch), dim3(256), lds, stream, p);
+  } else {
+    VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_kernel<T, D, G>), dim3(c.n_kv_heads, c.batch), dim3(256), 0, stream, p);
+  }
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }

@@ -115,9 +115,6 @@ __device__ __forceinline__ void tile_barrier() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
-__device__ __forceinline__ uint32_t lds_address(const void* p) {
-  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p;
-}
 
 // the rows of a head (keys, or values) as a sequence of tiles, `dir` = 1 upwards or -1 downwards
 template <typename T, int D> struct TileSource {
