@@ -13,7 +13,13 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_u;   // 16-byte access at any element
 
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
 constexpr int kWave = 64;
+
+// every lambda of the larger kernels: one that stays a call (in a branch marked unlikely, say) would drag all it refers
+// to from registers into memory
+#define VEC_INLINE __attribute__((always_inline))
 
 struct bf16_t { uint16_t bits; };   // storage type of VECTOR_BF16 tensors
 

@@ -124,10 +124,7 @@ constexpr int kTargetWorkgroups = 768;
 #define VEC_DEC_TARGET 1024
 #endif
 constexpr int kTargetWorkgroupsMfma = VEC_DEC_TARGET;   // bf16 kernel: two workgroups fit a CU
-#ifndef VEC_ROPE_APX_COST
-#define VEC_ROPE_APX_COST 2.2
-#endif
-constexpr double kRopeApxCost = VEC_ROPE_APX_COST;
+constexpr double kRopeApxCost = 2.2;
 
 // sum over the LPR adjacent lanes that share a row; every lane of the group gets the total
 template <int LPR> __device__ __forceinline__ float group_sum(float x) {
@@ -374,15 +371,15 @@ __global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeP
 // wave-wide loads (16 bytes per lane, adjacent lanes on one row); a wave parks a tile of
 // 32 rows in its own slice of LDS and reads it back in operand order:
 //   scores   S[t][g] = sum_e K[t][e] q[g][e]     A = key tile (16-byte reads along a row),
-//                                                 B = the G query rows (columns >= G zero)
+//                                                 B = the G query rows, twice
 //   output   O[j][g] += sum_t R[t][j] P[t][g]    A = tile of R read down its columns
 //                                                 (R = values, or the keys themselves for
 //                                                 approximated rows), B = P
 // The accumulator layout of S (column g on lane g, sixteen tokens in the registers of a
 // lane) is already the B-operand layout of the second product once the contraction index
 // is numbered the way those registers number the tokens, so P never leaves its lane.  P is
-// fed to the matrix core as bf16 twice: its rounded value and the remainder of that
-// rounding, which keeps the weights to about 2^-16 relative.
+// fed to the matrix core as its bf16 value (columns g) and the remainder of that rounding
+// (columns G + g), which keeps the weights to about 2^-16 relative.
 // ---------------------------------------------------------------------------
 constexpr int kTileRows = 32;
 
@@ -416,9 +413,19 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
   static_assert(2 * G <= 32, "weights and their remainders side by side");
 
   extern __shared__ __align__(16) unsigned char dec_lds[];
+  // native vectors throughout: arrays of the uint4 class that are filled in one branch and used in another went to scratch
+  auto load16 = [](const T* at) VEC_INLINE { return *reinterpret_cast<const u32x4*>(at); };
+  auto unpack8 = [](u32x4 r, float* f) VEC_INLINE {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { f[2 * e] = bf16_lo(r[e]); f[2 * e + 1] = bf16_hi(r[e]); }
+  };
+  auto mfma = [](u32x4 a, u32x4 b, const f32x16& c) VEC_INLINE {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  };
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
   const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int l31 = lane & 31, half = lane >> 5;
   const SegmentRows seg = segment_rows(p, b, h);
   const bool is_apx = split >= p.splits_ret;
@@ -447,15 +454,12 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
                                                                                       (((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2);
   const bool literal = LITERAL && is_apx;                    // rebuild every approximated value row
 
-  // B operand of the score product: query row g on lanes g and G + g, zero beyond
+  // B operand of the score product: query row g on lanes g and G + g; what the columns beyond hold is never used
   const float remainder = l31 >= G ? 1.f : 0.f;
-  chunk_t qf[NC];
+  u32x4 qf[NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    qf[c] = make_uint4(0, 0, 0, 0);
-    if (l31 < 2 * G)
-      qf[c] = load_chunk(reinterpret_cast<const T*>(p.q) + ((size_t)b * p.Hq + (size_t)h * G + l31 % G) * D + (2 * c + half) * 8);
-  }
+  for (int c = 0; c < NC; ++c)
+    qf[c] = load16(reinterpret_cast<const T*>(p.q) + ((size_t)b * p.Hq + (size_t)h * G + l31 % G) * D + (2 * c + half) * 8);
 
   f32x16 o[JB];
 #pragma unroll
@@ -491,28 +495,49 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
     const int j = min((row_begin >> seg.block_shift) + lane, (row_end - 1) >> seg.block_shift);
     my_block = seg.blocks[j];
   }
-  auto fetch = [&](uint4* kraw, uint4* vraw, int base) {
-    if (!ROPE || !is_apx) {
-      size_t tile_shift = 0;                     // paged, one block per tile: array row = tile_shift + segment row
-      if (tile_in_block) {
-        const int blk = __builtin_amdgcn_readlane(my_block, (base >> seg.block_shift) - (row_begin >> seg.block_shift));
-        tile_shift = ((size_t)blk << seg.block_shift) - (size_t)((base >> seg.block_shift) << seg.block_shift);
-      }
+  // Rows of a tile in straight lines of loads, one line per case; the last tile of the live rows and the one with the step's
+  // own token look at every row.
+  const int plain_rows = is_apx || seg.new_row < 0 ? seg_len : seg.new_row;
+  u32x4 kraw[TL::kLoads], vraw[TL::kLoads];
+  auto fetch = [&](int base) VEC_INLINE {
+    if (ROPE && is_apx) {
 #pragma unroll
-      for (int i = 0; i < TL::kLoads; ++i) {
-        const int r = min(base + i * TL::kRowsPerLoad + ld_row, seg_len - 1);   // clamped: never past the live rows
-        const bool fresh = !is_apx && r == seg.new_row;      // the step's own token comes from the caller's buffers
-        const size_t at = (tile_in_block ? tile_shift + (size_t)r : seg_row(fresh ? 0 : r)) * D + ld_piece * 8;
-        kraw[i] = load_chunk(fresh ? k_new + ld_piece * 8 : kseg + at);
-        if (!is_apx) vraw[i] = load_chunk(fresh ? v_new + ld_piece * 8 : vseg + at);
-      }
-    } else {
+      for (int i = 0; i < TL::kLoads; ++i) kraw[i] = load16(kseg + (size_t)min(base + row_of(i), seg_len - 1) * D + piece_of(i) * 8);
 #pragma unroll
       for (int i = 0; i < TL::kLoads; ++i) {
         const int r = min(base + row_of(i), seg_len - 1);
-        kraw[i] = load_chunk(kseg + (size_t)r * D + piece_of(i) * 8);
-        vraw[i].x = (uint32_t)((pos_seg ? pos_seg[r] : r) + rp.pos_offset);
+        vraw[i][0] = (uint32_t)((pos_seg ? pos_seg[r] : r) + rp.pos_offset);
       }
+      return;
+    }
+    size_t tile_shift = is_apx ? 0 : seg.ret_row0;           // array row = tile_shift + segment row, where the tile is one run of rows
+    if (tile_in_block) {
+      const int blk = __builtin_amdgcn_readlane(my_block, (base >> seg.block_shift) - (row_begin >> seg.block_shift));
+      tile_shift = ((size_t)blk << seg.block_shift) - (size_t)((base >> seg.block_shift) << seg.block_shift);
+    }
+    if (base + kTileRows <= plain_rows && (!PAGED || is_apx || tile_in_block)) {       // uniform
+      const size_t at = (tile_shift + (size_t)base + ld_row) * D + ld_piece * 8;
+#pragma unroll
+      for (int i = 0; i < TL::kLoads; ++i) kraw[i] = load16(kseg + at + i * TL::kRowsPerLoad * D);
+      if (!is_apx) {
+#pragma unroll
+        for (int i = 0; i < TL::kLoads; ++i) vraw[i] = load16(vseg + at + i * TL::kRowsPerLoad * D);
+      }
+      asm volatile("; tile of live rows");       // keeps the lines apart: what they have in common at their ends would be joined, through scratch
+    } else if (is_apx) {
+#pragma unroll
+      for (int i = 0; i < TL::kLoads; ++i) kraw[i] = load16(kseg + (size_t)min(base + i * TL::kRowsPerLoad + ld_row, seg_len - 1) * D + ld_piece * 8);
+      asm volatile("; last approximated rows");
+    } else {
+#pragma unroll
+      for (int i = 0; i < TL::kLoads; ++i) {
+        const int r = min(base + i * TL::kRowsPerLoad + ld_row, seg_len - 1);   // clamped: never past the live rows
+        const bool fresh = r == seg.new_row;                 // the step's own token comes from the caller's buffers
+        const size_t at = (tile_in_block ? tile_shift + (size_t)r : seg_row(fresh ? 0 : r)) * D + ld_piece * 8;
+        kraw[i] = load16(fresh ? k_new + ld_piece * 8 : kseg + at);
+        vraw[i] = load16(fresh ? v_new + ld_piece * 8 : vseg + at);
+      }
+      asm volatile("; last retained rows");
     }
   };
   // the lane's pieces always cover the same rotary pairs: their frequencies stay in registers
@@ -526,14 +551,14 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
     }
   }
   auto pack8 = [](const float* f) {
-    return make_uint4(pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7]));
+    return u32x4{pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7])};
   };
   // both members of eight pairs (x[i], x[i + d/2]) of a cached key row, turned back by the row's position
-  auto unrotate_pair = [&](const uint4& ra, const uint4& rb, int pos, uint4& oa, uint4& ob) {
+  auto unrotate_pair = [&](u32x4 ra, u32x4 rb, int pos, u32x4& oa, u32x4& ob) VEC_INLINE {
     float a[8], b[8];
     const float pf = (float)pos;
-    Unpack16<T>::run(ra, a);
-    Unpack16<T>::run(rb, b);
+    unpack8(ra, a);
+    unpack8(rb, b);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       float cs, sn;
@@ -544,10 +569,10 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
     ob = pack8(b);
   };
   // pairs (x[2i], x[2i+1]): four of them inside one 16-byte piece
-  auto unrotate_piece = [&](const uint4& raw, int pos) {
+  auto unrotate_piece = [&](u32x4 raw, int pos) VEC_INLINE {
     float f[8];
     const float pf = (float)pos;
-    Unpack16<T>::run(raw, f);
+    unpack8(raw, f);
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
       float cs, sn;
@@ -556,26 +581,26 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
     }
     return pack8(f);
   };
-  auto stage = [&](const uint4* kraw, const uint4* vraw) {
+  auto stage = [&]() VEC_INLINE {
     if (!is_apx || !ROPE) {
 #pragma unroll
-      for (int i = 0; i < TL::kLoads; ++i) {
-        const int off = (i * TL::kRowsPerLoad + ld_row) * TL::kStride + ld_piece * 16;
-        *reinterpret_cast<uint4*>(k_tile + off) = kraw[i];
-        if (!is_apx) *reinterpret_cast<uint4*>(v_tile + off) = vraw[i];
+      for (int i = 0; i < TL::kLoads; ++i) *reinterpret_cast<u32x4*>(k_tile + (i * TL::kRowsPerLoad + ld_row) * TL::kStride + ld_piece * 16) = kraw[i];
+      if (!is_apx) {
+#pragma unroll
+        for (int i = 0; i < TL::kLoads; ++i) *reinterpret_cast<u32x4*>(v_tile + (i * TL::kRowsPerLoad + ld_row) * TL::kStride + ld_piece * 16) = vraw[i];
       }
     } else {
 #pragma unroll
       for (int i = 0; i < TL::kLoads; ++i) {
         const int off = row_of(i) * TL::kStride + piece_of(i) * 16;
-        *reinterpret_cast<uint4*>(k_tile + off) = kraw[i];
+        *reinterpret_cast<u32x4*>(k_tile + off) = kraw[i];
         if (!paired) {
-          *reinterpret_cast<uint4*>(v_tile + off) = unrotate_piece(kraw[i], (int)vraw[i].x);
+          *reinterpret_cast<u32x4*>(v_tile + off) = unrotate_piece(kraw[i], (int)vraw[i][0]);
         } else if (i & 1) {
-          uint4 oa, ob;
-          unrotate_pair(kraw[i - 1], kraw[i], (int)vraw[i].x, oa, ob);
-          *reinterpret_cast<uint4*>(v_tile + row_of(i - 1) * TL::kStride + piece_of(i - 1) * 16) = oa;
-          *reinterpret_cast<uint4*>(v_tile + off) = ob;
+          u32x4 oa, ob;
+          unrotate_pair(kraw[i - 1], kraw[i], (int)vraw[i][0], oa, ob);
+          *reinterpret_cast<u32x4*>(v_tile + row_of(i - 1) * TL::kStride + piece_of(i - 1) * 16) = oa;
+          *reinterpret_cast<u32x4*>(v_tile + off) = ob;
         }
       }
     }
@@ -588,13 +613,13 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
 
-  auto consume = [&](int base) {
+  auto consume = [&](int base) VEC_INLINE {
     // ---- scores ----
     f32x16 s;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const chunk_t a = *reinterpret_cast<const chunk_t*>(k_tile + l31 * TL::kStride + (2 * c + half) * 16);
-      if (c == 0) mma_chunk_first<T>(s, a, qf[c]); else mma_chunk<T>(s, a, qf[c]);
+      const u32x4 a = *reinterpret_cast<const u32x4*>(k_tile + l31 * TL::kStride + (2 * c + half) * 16);
+      s = mfma(a, qf[c], c == 0 ? zero : s);
     }
     float tmax = kNegBig;
     if (base + kTileRows > row_end) {               // ragged last tile: rows past the range score -inf
@@ -637,9 +662,9 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
         f32x16 vh;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          const chunk_t a = *reinterpret_cast<const chunk_t*>(k_tile + l31 * TL::kStride + (2 * c + half) * 16);
-          const chunk_t b = *reinterpret_cast<const chunk_t*>(wt + l31 * TL::kStride + (2 * c + half) * 16);
-          if (c == 0) mma_chunk_first<T>(vh, a, b); else mma_chunk<T>(vh, a, b);
+          const u32x4 a = *reinterpret_cast<const u32x4*>(k_tile + l31 * TL::kStride + (2 * c + half) * 16);
+          const u32x4 b = *reinterpret_cast<const u32x4*>(wt + l31 * TL::kStride + (2 * c + half) * 16);
+          vh = mfma(a, b, c == 0 ? zero : vh);
         }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
@@ -688,14 +713,17 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
     __syncthreads();
   }
 
-  uint4 kraw[TL::kLoads], vraw[TL::kLoads];
   int base = row_begin + wave * kTileRows;
-  if (base < row_end) fetch(kraw, vraw, base);
+  if (base < row_end) fetch(base);
+  // The query rows have arrived from here on.  Without this the wait for them sits in the loop, in front of the first
+  // product, and waits for the next tile's rows as well.
+#pragma unroll
+  for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(qf[c]));
   while (base < row_end) {
     wave_fence();                                    // last tile's reads are done before it is overwritten
-    stage(kraw, vraw);
+    stage();
     const int next = base + kStepRows;
-    if (next < row_end) fetch(kraw, vraw, next);     // in flight while this tile is consumed
+    if (next < row_end) fetch(next);     // in flight while this tile is consumed
     wave_fence();
     consume(base);
     base = next;

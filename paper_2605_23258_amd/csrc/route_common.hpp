@@ -150,7 +150,6 @@ template <int NT> constexpr int kBlock = NT * 4;        // tokens per block: fou
 constexpr int kHeadBins = 2048;
 constexpr int kRankCap = 256;                   // candidates ranked by comparison
 
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4), aligned(4))) uint32_t u32x4_u;
 
 // Workgroup barrier for data in LDS alone: global loads in flight (the residuals, while the scores are worked

@@ -72,10 +72,6 @@ __device__ __forceinline__ int64_t head_offset(const PassParams& p, int h, int64
 }
 __device__ __forceinline__ int w_head(const PassParams& p, int h) { return p.hps ? h % p.hps : h; }
 
-// every lambda of these kernels: one that stays a call (in a branch marked unlikely, say) would drag all it refers
-// to from registers into memory
-#define VEC_INLINE __attribute__((always_inline))
-
 template <typename T, int D> struct Stream {
   static constexpr int E = Elem<T>::kPerChunk;
   static constexpr int kRowBytes = D * (int)sizeof(T);
@@ -186,7 +182,6 @@ template <typename T, int D, int NRB> struct WaveWork {
 };
 
 // LDS by its 32-bit address (no trip through a flat pointer's arithmetic)
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 __device__ __forceinline__ chunk_t lds_read16(uint32_t at) {
   const u32x4 x = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(at);
   return make_uint4(x[0], x[1], x[2], x[3]);
