@@ -8,7 +8,7 @@
 //   solve_kernel : grid (d / 16 column blocks, heads).  Blocked fp64 Cholesky of K^T K with the column
 //                  block of K^T V riding along, then the backward substitution; all on fp64 matrix
 //                  instructions out of LDS.
-// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 64 + 12 + 51 us (products, sums, solve).
+// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 64 + 13 + 23 us (products, sums, solve).
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -244,10 +244,9 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(CalParams p) {
   p.sums[(size_t)h * (kTri + NB * NB) * 256 + to] = s;
 }
 
-// Cholesky of a 16 x 16 diagonal tile and the inverse of its factor, by one wave: every lane group of
-// 16 holds a row of the tile and a row of the inverse in the making per lane, and the pivot row's
-// elements are broadcast by readlane.  The tile is replaced by the inverse (zeros above its diagonal).
-// A pivot that is not positive marks the head.
+// fp64 on the matrix cores, C + A B.  16x16x4: lane (l15, l4) = (lane & 15, lane >> 4) holds A[l15][l4], B[l4][l15]
+// and C[4 v + l4][l15] in register v, so register v of a C is the B operand that four of its rows make, and the A operand of
+// the same rows of its transpose.  4x4x4, four blocks: as if A had 4 rows, which every group of four lanes holds; C is one register.
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 constexpr int kLdt = 18;                      // doubles between rows of a tile: operand reads of 16 rows hit distinct banks
 constexpr int kTileDoubles = 16 * kLdt;
@@ -258,36 +257,113 @@ __device__ __forceinline__ double readlane_f64(double x, int lane) {
   return __builtin_bit_cast(double, (unsigned long long)lo | ((unsigned long long)hi << 32));
 }
 
-__device__ __forceinline__ void factor_invert_tile(double* tile, int* bad) {
-  const int lane = threadIdx.x & 63, r = lane & 15;
-  double a[16], v[16];
+__device__ __forceinline__ f64x4 mfma_f64(double a, double b, const f64x4& c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ double mfma4_f64(double a, double b, double c) { return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0); }
+
+// of every 16 lanes, lanes 4 Q .. 4 Q + 3 in all four groups of four
+template <int Q> __device__ __forceinline__ double spread4(double x) {
+  const unsigned long long bits = __builtin_bit_cast(unsigned long long, x);
+  auto half = [](int w) VEC_INLINE {
+    int out = w;                                // row_ror:n takes from n lanes below; the last mask names the group written
+    if constexpr (Q != 0) out = __builtin_amdgcn_update_dpp(out, w, 0x120 + 4 * ((0 - Q) & 3), 0xf, 1, false);
+    if constexpr (Q != 1) out = __builtin_amdgcn_update_dpp(out, w, 0x120 + 4 * ((1 - Q) & 3), 0xf, 2, false);
+    if constexpr (Q != 2) out = __builtin_amdgcn_update_dpp(out, w, 0x120 + 4 * ((2 - Q) & 3), 0xf, 4, false);
+    if constexpr (Q != 3) out = __builtin_amdgcn_update_dpp(out, w, 0x120 + 4 * ((3 - Q) & 3), 0xf, 8, false);
+    return (uint32_t)out;
+  };
+  const uint32_t lo = half((int)(uint32_t)bits), hi = half((int)(uint32_t)(bits >> 32));
+  return __builtin_bit_cast(double, (unsigned long long)lo | ((unsigned long long)hi << 32));
+}
+
+// 1 / sqrt(x) and 1 / x: the hardware's estimate (good to about 2^-24) and one step of third order
+__device__ __forceinline__ double inverse_sqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+__device__ __forceinline__ double inverse(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
+// Cholesky of a 16 x 16 diagonal tile by one wave: the inverse of its factor (zeros above the diagonal) goes to `tile`.
+// The tile is A - X X^T, with A whole as an accumulator and X^T as one.  A pivot that is not positive marks the head.
+// Four columns at a time: every lane factors the 4 x 4 block on the diagonal and inverts the factor (T; the chain from pivot
+// to pivot is the square-root-free one), and the matrix cores do the rest: the four columns of the factor are
+// P = A_b T^t, formed as T A_b^t because that comes out as an operand again (A is symmetric: A_b^t is register b),
+// then the rows below lose P P^t; of the inverse, rows b become T times what stands there and the rows below lose
+// P times that.  All in 4x4x4 instructions, a quarter of a 16x16x4 each: what the next block waits for is two of them.
+// A wave alone issues an instruction about every six cycles, so their number counts as well as the chain: some 500 a tile,
+// 3200 cycles (28 % more with a square root per pivot and sixteen spreads for X X^T).  A column at a time, every
+// element of the pivot row broadcast by readlane to the tile and the inverse: 52 us for the solve, against 23.
+// Columns of `a` left of block b are never read again.
+__device__ __forceinline__ void factor_invert_tile(f64x4 a, const f64x4& xt, double* tile, int* bad) {
+  const int lane = threadIdx.x & 63, l15 = lane & 15, l4 = lane >> 4, l3 = lane & 3;
+  f64x4 inv;
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    a[j] = tile[r * kLdt + j];
-    v[j] = (j == r) ? 1.0 : 0.0;
-  }
+  for (int v = 0; v < 4; ++v) inv[v] = (4 * v + l4 == l15) ? 1.0 : 0.0;
+  auto each_row_block = [&](auto f) VEC_INLINE {
+    f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
+  };
+  // (as 4x4x4 instructions too this is more, not less: sixteen spreads)
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const double piv = readlane_f64(a[k], k);
-    if (!(piv > 0.0) && lane == 0) *bad = 1;
-    // 1 / sqrt(pivot): the hardware's estimate and two Newton steps
-    double y = __builtin_amdgcn_rsq(piv);
-    y = y * fma(-0.5 * piv * y, y, 1.5);
-    y = y * fma(-0.5 * piv * y, y, 1.5);
-    const double l = a[k] * y;                // column k of the factor; rows above k hold values nothing reads
-    const double f = r > k ? l : 0.0;
+  for (int kk = 0; kk < 4; ++kk) a = mfma_f64(-xt[kk], xt[kk], a);
+  // a choice by bits: of ?: the compiler makes branches, with the arithmetic moved into them
+  auto pick = [](uint32_t yes, double x, double y) VEC_INLINE {
+    const unsigned long long xb = __builtin_bit_cast(unsigned long long, x), yb = __builtin_bit_cast(unsigned long long, y);
+    const uint32_t lo = (yes & (uint32_t)xb) | (~yes & (uint32_t)yb), hi = (yes & (uint32_t)(xb >> 32)) | (~yes & (uint32_t)(yb >> 32));
+    return __builtin_bit_cast(double, (unsigned long long)lo | ((unsigned long long)hi << 32));
+  };
+  uint32_t is0 = l3 == 0 ? ~0u : 0u, is1 = l3 == 1 ? ~0u : 0u, is2 = l3 == 2 ? ~0u : 0u;
+  asm volatile("" : "+v"(is0), "+v"(is1), "+v"(is2));
+  bool ok = true;
+  each_row_block([&](auto bv) VEC_INLINE {
+    constexpr int b = decltype(bv)::value;
+    double u[4][4], m[4][4], t[4];
 #pragma unroll
-    for (int j = k + 1; j < 16; ++j) a[j] = fma(-f, readlane_f64(l, j), a[j]);
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j <= k; ++j) {
-      const double row = readlane_f64(v[j], k) * y;
-      v[j] = (r == k) ? row : fma(-f, row, v[j]);
+      for (int j = 0; j <= i; ++j) u[i][j] = readlane_f64(a[b], 16 * i + 4 * b + j);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k < 3) {
+        const double r = inverse(u[k][k]);
+#pragma unroll
+        for (int i = k + 1; i < 4; ++i) {
+          m[i][k] = u[i][k] * r;
+#pragma unroll
+          for (int j = k + 1; j <= i; ++j) u[i][j] = fma(-(u[i][k] * u[j][k]), r, u[i][j]);
+        }
+      }
+      // column l4 of the unit factor's inverse, a row at a time
+      t[k] = (l4 == k) ? 1.0 : 0.0;
+#pragma unroll
+      for (int j = 0; j < k; ++j) t[k] = fma(-m[k][j], t[j], t[k]);
     }
-  }
-  if (lane < 16) {
+    // this lane's row of T: one square root for all four
+    const double row = pick(is0, t[0], pick(is1, t[1], pick(is2, t[2], t[3])));
+    const double pivot = pick(is0, u[0][0], pick(is1, u[1][1], pick(is2, u[2][2], u[3][3])));
+    ok &= pivot > 0.0;
+    const double T = row * inverse_sqrt(pivot);
+    const double P = mfma4_f64(T, a[b], 0.0);                  // P[l15][l4]
+    const double minus_p = -P;
+    double below[4];
+    each_row_block([&](auto v) VEC_INLINE {
+      constexpr int V = decltype(v)::value;
+      if constexpr (V > b) {
+        below[V] = spread4<V>(minus_p);
+        a[V] = mfma4_f64(below[V], P, a[V]);
+      }
+    });
+    inv[b] = mfma4_f64(T, inv[b], 0.0);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) tile[r * kLdt + j] = (j <= r) ? v[j] : 0.0;
-  }
+    for (int v = b + 1; v < 4; ++v) inv[v] = mfma4_f64(below[v], inv[b], inv[v]);
+  });
+  if (!ok) *bad = 1;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) tile[(4 * v + l4) * kLdt + l15] = inv[v];
 }
 
 // (K^T K) W = K^T V for 16 columns of W.  Grid (d / 16, heads), eight waves; every workgroup factors
@@ -295,99 +371,127 @@ __device__ __forceinline__ void factor_invert_tile(double* tile, int* bad) {
 // shorten).  Everything lies in LDS as 16 x 16 fp64 tiles and every product is a v_mfma_f64_16x16x4:
 //   right-looking blocked Cholesky: the diagonal tile is factored and its factor inverted by one wave,
 //   the tiles below it are multiplied by that inverse, the tiles right of it lose their products.
-//   The wave that updates the next diagonal tile goes on to factor it while the others finish the step.
+//   The first wave keeps the chain in its registers: the tile below the diagonal comes out of its product as the
+//   operands that the next diagonal tile's update takes, and that tile is factored while the others update the rest.
 //   The right-hand sides ride along as one more block row, (K^T V)^T: after step s its tile s holds the
-//   forward solution, and the backward substitution runs over the same tiles.
-// Bound: the chain of pivots (16 reciprocal square roots and broadcasts per step).  51 us for d = 128, eight
-// heads; one workgroup per head with a thread per row and plain loops took 934 us (the sums included).
+//   forward solution.  For the backward substitution wave j takes rows 16 j .. of it into registers, and
+//   a solved block goes to the waves above through LDS.
+// Bound: the chain of 4 x 4 blocks.  23 us for d = 128, eight heads (cycles: 30000 in the diagonal tiles, 7000 in the tiles
+// below them, 7500 in the backward substitution; the other tiles' updates are waited for in the second step alone).
+// Reading the next tile's operands ahead of a tile's products made the updates slower (6500 cycles against 5200 in
+// that step).  One workgroup per head with a thread per row and plain loops took 934 us (the sums included).
 template <typename T, int D>
 __global__ __launch_bounds__(512) void solve_kernel(CalParams p) {
   constexpr int NB = D / 16, kTri = NB * (NB + 1) / 2, NW = 512 / kWave;
+  static_assert(NB <= NW, "a wave per tile of a block column");
   extern __shared__ __align__(16) double cal_tiles[];        // [kTri + NB][kTileDoubles]
   __shared__ int bad;
   const int h = blockIdx.y, cb = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, l4 = lane >> 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l15 = lane & 15, l4 = lane >> 4;
   auto tile = [&](int i, int j) { return cal_tiles + (i * (i + 1) / 2 + j) * kTileDoubles; };   // row NB: the right-hand sides
-  if (threadIdx.x == 0) bad = 0;
-  {
-    const double* src = p.sums + (size_t)h * (kTri + NB * NB) * 256;
-    constexpr int kPairs = (kTri + NB) * 128;                  // 16-byte pairs
-    for (int o = threadIdx.x; o < kPairs; o += 512) {
-      const int t = o >> 7, e = (o & 127) * 2;
-      const size_t from = (size_t)(t < kTri ? t : kTri + cb * NB + (t - kTri)) * 256 + e;
-      *reinterpret_cast<double2*>(cal_tiles + t * kTileDoubles + (e >> 4) * kLdt + (e & 15)) = *reinterpret_cast<const double2*>(src + from);
+  const double* src = p.sums + (size_t)h * (kTri + NB * NB) * 256;
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+  f64x4 diag = zero, xt = zero;                                // the next diagonal tile and what it loses, in the first wave
+  if (wave == 0) {
+    if (lane == 0) bad = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) diag[v] = src[(4 * v + l4) * 16 + l15];
+  } else {
+    // the other tiles, while the first wave factors: 16-byte pairs, all requested at once
+    constexpr int kThreads = 512 - kWave, kPairs = (kTri + NB - 1) * 128, kTrips = (kPairs + kThreads - 1) / kThreads;
+    double2 x[kTrips];
+#pragma unroll
+    for (int u = 0; u < kTrips; ++u) {
+      const int o = 128 + min((int)threadIdx.x - kWave + u * kThreads, kPairs - 1), t = o >> 7;
+      x[u] = *reinterpret_cast<const double2*>(src + (size_t)(t < kTri ? t : kTri + cb * NB + (t - kTri)) * 256 + (o & 127) * 2);
+    }
+#pragma unroll
+    for (int u = 0; u < kTrips; ++u) {
+      const int n = (int)threadIdx.x - kWave + u * kThreads, o = 128 + n, t = o >> 7, e = (o & 127) * 2;
+      if (n < kPairs) *reinterpret_cast<double2*>(cal_tiles + t * kTileDoubles + (e >> 4) * kLdt + (e & 15)) = x[u];
     }
   }
-  __syncthreads();
-  // C + sign * A B, or with kTransB A B^T: operand A row l15, element 4 kk + l4; operand B element 4 kk + l4, column l15;
-  // accumulator register v: row 4 v + l4, column l15
-  auto product = [&](const double* A, const double* B, bool trans_b, f64x4 acc, double sign) {
-    double av[4], bv[4];
+  // Operands of a tile by its rows: A operands of X, B operands of X^T.  Instruction kk takes elements 4 l4 + kk of the sum,
+  // whichever four they are, so that a lane reads 32 bytes in a row.
+  auto by_rows = [&](const double* X) VEC_INLINE {
+    const double2 x0 = *reinterpret_cast<const double2*>(X + l15 * kLdt + 4 * l4), x1 = *reinterpret_cast<const double2*>(X + l15 * kLdt + 4 * l4 + 2);
+    return f64x4{x0.x, x0.y, x1.x, x1.y};
+  };
+  // by its columns, X[4 kk + l4][l15]: as an accumulator, or A operands of X^T
+  auto by_columns = [&](const double* X) VEC_INLINE {
+    f64x4 x;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      av[kk] = sign * A[l15 * kLdt + 4 * kk + l4];
-      bv[kk] = trans_b ? B[l15 * kLdt + 4 * kk + l4] : B[(4 * kk + l4) * kLdt + l15];
-    }
+    for (int kk = 0; kk < 4; ++kk) x[kk] = X[(4 * kk + l4) * kLdt + l15];
+    return x;
+  };
+  auto products = [&](const f64x4& a, const f64x4& b, f64x4 acc) VEC_INLINE {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kk], bv[kk], acc, 0, 0, 0);
+    for (int kk = 0; kk < 4; ++kk) acc = mfma_f64(a[kk], b[kk], acc);
     return acc;
   };
-  auto load_acc = [&](const double* X) {
-    f64x4 acc;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = X[(4 * v + l4) * kLdt + l15];
-    return acc;
-  };
-  auto store_acc = [&](double* X, const f64x4& acc) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) X[(4 * v + l4) * kLdt + l15] = acc[v];
-  };
-  auto wave_fence = [&]() {                                    // a tile handed over inside one wave
+  auto wave_fence = [&]() VEC_INLINE {                         // a tile handed over inside one wave
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
-  if (wave == 0) factor_invert_tile(tile(0, 0), &bad);
-  __syncthreads();
-  for (int s = 0; s < NB; ++s) {
-    for (int i = s + 1 + wave; i <= NB; i += NW) {
-      const f64x4 x = product(tile(i, s), tile(s, s), true, zero, 1.0);
-      wave_fence();
-      store_acc(tile(i, s), x);
-    }
-    __syncthreads();
-    // tiles (i, j), s < j <= i: number 0 is the next diagonal tile
-    int t = 0;
-    for (int j = s + 1; j < NB; ++j)
-      for (int i = j; i <= NB; ++i, ++t) {
-        if ((t == 0 ? 0 : 1 + (t - 1) % (NW - 1)) != wave) continue;
-        store_acc(tile(i, j), product(tile(i, s), tile(j, s), true, load_acc(tile(i, j)), -1.0));
-      }
-    if (wave == 0 && s + 1 < NB) {
-      wave_fence();
-      factor_invert_tile(tile(s + 1, s + 1), &bad);
-    }
-    __syncthreads();
-  }
-  // L^T X = Y, on the transposed right-hand sides: X_s^T = Y_s^T L_ss^-1, then Y_j^T -= X_s^T L_sj for j < s
-  T* Wh = reinterpret_cast<T*>(p.W) + (size_t)h * D * D;
-  for (int s = NB - 1; s >= 0; --s) {
+  for (int s = 0;; ++s) {
     if (wave == 0) {
-      const f64x4 x = product(tile(NB, s), tile(s, s), false, zero, 1.0);
-      wave_fence();
-      store_acc(tile(NB, s), x);
+      factor_invert_tile(diag, xt, tile(s, s), &bad);
+    } else if (s > 0) {
+      // tiles (i, j), s <= j <= i, but for the next diagonal tile, lose the products of block column s - 1
+      int i = s + wave, j = s;
+      while (true) {
+        while (j < NB && i > NB) { ++j; i += j - (NB + 1); }
+        if (j >= NB) break;
+        const f64x4 c = products(-by_rows(tile(i, s - 1)), by_rows(tile(j, s - 1)), by_columns(tile(i, j)));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) tile(i, j)[(4 * v + l4) * kLdt + l15] = c[v];
+        i += NW - 1;
+      }
     }
     __syncthreads();
-    for (int j = wave; j < s; j += NW)
-      store_acc(tile(NB, j), product(tile(NB, s), tile(s, j), false, load_acc(tile(NB, j)), -1.0));
+    // below the diagonal: X = A L_ss^-T, a tile per wave, as X^T = L_ss^-1 A^T
+    const int i_own = s + 1 + wave;
+    if (i_own <= NB) {
+      xt = products(by_rows(tile(s, s)), by_rows(tile(i_own, s)), zero);
+      if (wave == 0 && s + 1 < NB) diag = by_columns(tile(s + 1, s + 1));
+      wave_fence();
+#pragma unroll
+      for (int v = 0; v < 4; ++v) tile(i_own, s)[l15 * kLdt + 4 * v + l4] = xt[v];
+    }
     __syncthreads();
+    if (s + 1 == NB) break;
   }
-  // row i of W, 16 columns side by side
-  for (int o = threadIdx.x; o < D * 16; o += 512) {
-    const int i = o >> 4, c = o & 15;
-    const double x = tile(NB, i >> 4)[c * kLdt + (i & 15)];
-    store_elem(Wh + (size_t)i * D + cb * 16 + c, bad ? __builtin_nanf("") : (float)x);       // not positive definite: say so
+  // L^T X = Y: X_s = L_ss^-T Y_s, then Y_j -= L_sj^T X_s for j < s.  X_s goes where Y_s^T was, register by register.
+  f64x4 x = zero, lt = zero;
+  if (wave < NB) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = tile(NB, wave)[l15 * kLdt + 4 * v + l4];
+    lt = by_columns(tile(NB - 1, wave));
+  }
+  for (int s = NB - 1; s >= 0; --s) {
+    if (wave == s) {
+      x = products(lt, x, zero);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) tile(NB, s)[v * 64 + lane] = x[v];
+    }
+    f64x4 lt_next = zero;
+    if (wave < s) lt_next = by_columns(tile(s - 1, wave));
+    __syncthreads();
+    if (wave < s) {
+      f64x4 solved;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) solved[kk] = tile(NB, s)[kk * 64 + lane];
+      x = products(-lt, solved, x);
+    }
+    lt = lt_next;
+  }
+  // x[v]: row 16 wave + 4 v + l4 of W, column 16 cb + l15
+  T* Wh = reinterpret_cast<T*>(p.W) + (size_t)h * D * D + cb * 16 + l15;
+  if (wave < NB) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      store_elem(Wh + (size_t)(16 * wave + 4 * v + l4) * D, bad ? __builtin_nanf("") : (float)x[v]);       // not positive definite: say so
   }
 }
 

@@ -129,3 +129,23 @@ def test_fit_at_the_edges_of_tiles_and_chunks(dtype, d, hkv, n):
     assert (np.abs(np.matmul(gram, got) - cross) <= slack).all()
     if n >= 2 * d:
         assert np.abs(got - ref).max() <= (2e-2 if dtype == "bf16" else 1e-3)
+
+
+@pytest.mark.parametrize("d,dim", [(64, 0), (64, 37), (64, 63), (128, 3), (128, 4), (128, 79), (128, 127)])
+def test_pivot_that_is_not_positive_marks_its_head_alone(d, dim):
+    """A key dimension that is zero throughout makes its pivot exactly zero, whichever block of the factorisation
+    holds it; the other head's keys are scaled per dimension over three decades, and its map is the oracle's."""
+    n = 4 * d
+    rng = np.random.default_rng(dim)
+    k = rng.standard_normal((2, n, d)).astype(np.float32)
+    scale = (10.0 ** rng.uniform(-1.5, 1.5, d)).astype(np.float32)
+    k[1] *= scale
+    k[0, :, dim] = 0.0
+    v = rng.standard_normal((2, n, d)).astype(np.float32)
+    cfg = dg.scaled(dg.CONFIGS["cfg1"], head_dim=d, n_kv_heads=2, n_q_heads=2, seq_len=n)
+    got = _fit_gpu(cfg, pl.to_device(k), pl.to_device(v))
+    assert np.isnan(got[0]).all()
+    ref = vo.ols_fit(k[1:].astype(np.float64), v[1:].astype(np.float64))[0]
+    # fp32 sums of n terms, times the condition number of the equilibrated matrix (n = 4 d Gaussian rows: (3/1)^2 = 9)
+    bound = 9 * n * 2.0 ** -24 * np.abs(ref * scale[:, None]).max()
+    assert (np.abs(got[1] - ref) * scale[:, None]).max() <= bound
