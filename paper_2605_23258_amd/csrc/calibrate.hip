@@ -8,7 +8,7 @@
 //   solve_kernel : grid (d / 16 column blocks, heads).  Blocked fp64 Cholesky of K^T K with the column
 //                  block of K^T V riding along, then the backward substitution; all on fp64 matrix
 //                  instructions out of LDS.
-// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 64 + 13 + 23 us (products, sums, solve).
+// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 64 + 12 + 23 us (products, sums, solve).
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -20,6 +20,8 @@ constexpr int kCalThreads = 256;
 constexpr int kCalTile = 128;                // chunks are multiples of the longest tile
 constexpr int kCalMaxChunks = 64;
 constexpr int kCalMinTokens = 256;
+
+typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 struct CalParams {
   const void* k; const void* v;
@@ -210,44 +212,52 @@ __global__ __launch_bounds__(kCalThreads) void gram_f32_kernel(CalParams p) {
 }
 
 // Chunk partials -> fp64 sums in 16 x 16 tiles, the order solve_kernel keeps them in LDS: tile (i, j),
-// j <= i, of K^T K, then tile (r, j) of (K^T V)^T.  Grid (tiles, heads), one element per thread; a wave
-// reads four 64-byte runs per partial.  (One workgroup per head summing all of it took most of the solve's
-// 0.9 ms at 65536 tokens.)
+// j <= i, of K^T K, then tile (r, j) of (K^T V)^T.  Grid (tiles, heads).  A wave takes a quarter of the chunks, a lane four
+// elements side by side in all of them, requested at once; the quarters meet in LDS, in order.  Bound: the partials, 54 MB
+// at 65536 tokens x 8 heads, in 11.9 us; one element per thread, its chunks in four trips: 12.6 us.  (One
+// workgroup per head summing all of it took most of the solve's 0.9 ms at 65536 tokens.)
 template <int D>
 __global__ __launch_bounds__(256) void gram_reduce_kernel(CalParams p) {
-  constexpr int NB = D / 16, kTri = NB * (NB + 1) / 2;
+  constexpr int NB = D / 16, kTri = NB * (NB + 1) / 2, U = (kCalMaxChunks + 3) / 4;
+  __shared__ __align__(16) f64x4 shares[3][kWave];
   const int h = blockIdx.y, tile = blockIdx.x;
-  const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
-  const float* part = p.part + (size_t)h * p.n_chunks * 2 * D * D;
-  size_t at, to;
-  if (tile < kTri) {
+  const int lane = threadIdx.x & 63, quarter = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), r = lane >> 2, c = (lane & 3) * 4;
+  const bool transposed = tile >= kTri;
+  size_t at;
+  if (!transposed) {
     int i = 0;
     while ((i + 1) * (i + 2) / 2 <= tile) ++i;
     const int j = tile - i * (i + 1) / 2;
     at = (size_t)(16 * i + r) * D + 16 * j + c;
-    to = (size_t)tile * 256 + r * 16 + c;
   } else {
-    const int t = tile - kTri, cb = t / NB, j = t % NB;           // rows 16 j .. of K^T V, columns 16 cb ..: stored transposed
+    const int t = tile - kTri, cb = t / NB, j = t % NB;           // rows 16 j .. of K^T V, columns 16 cb ..
     at = (size_t)D * D + (size_t)(16 * j + r) * D + 16 * cb + c;
-    to = (size_t)(kTri + cb * NB + j) * 256 + c * 16 + r;
   }
-  double s = 0.0;
-  constexpr int U = 16;
-  for (int c0 = 0; c0 < p.n_chunks; c0 += U) {
-    float x[U];
+  const float* part = p.part + (size_t)h * p.n_chunks * 2 * D * D + at;
+  const int per = (p.n_chunks + 3) / 4, c0 = quarter * per, c1 = min(p.n_chunks, c0 + per);      // per <= U
+  f32x4 x[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) x[u] = part[(size_t)min(c0 + u, p.n_chunks - 1) * 2 * D * D + at];
+  for (int u = 0; u < U; ++u) x[u] = *reinterpret_cast<const f32x4*>(part + (size_t)min(c0 + u, p.n_chunks - 1) * 2 * D * D);
+  f64x4 s = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (c0 + u < p.n_chunks) s += (double)x[u];
-  }
-  p.sums[(size_t)h * (kTri + NB * NB) * 256 + to] = s;
+  for (int u = 0; u < U; ++u)
+    if (c0 + u < c1) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] += (double)x[u][e];
+    }
+  if (quarter > 0) shares[quarter - 1][lane] = s;
+  __syncthreads();
+  if (quarter > 0) return;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) s += shares[q][lane];
+  double* out = p.sums + ((size_t)h * (kTri + NB * NB) + tile) * 256;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) out[transposed ? (c + e) * 16 + r : r * 16 + c + e] = s[e];
 }
 
 // fp64 on the matrix cores, C + A B.  16x16x4: lane (l15, l4) = (lane & 15, lane >> 4) holds A[l15][l4], B[l4][l15]
 // and C[4 v + l4][l15] in register v, so register v of a C is the B operand that four of its rows make, and the A operand of
 // the same rows of its transpose.  4x4x4, four blocks: as if A had 4 rows, which every group of four lanes holds; C is one register.
-typedef __attribute__((ext_vector_type(4))) double f64x4;
 constexpr int kLdt = 18;                      // doubles between rows of a tile: operand reads of 16 rows hit distinct banks
 constexpr int kTileDoubles = 16 * kLdt;
 
