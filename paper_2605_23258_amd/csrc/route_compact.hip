@@ -15,8 +15,8 @@
 //
 // A launch costs 4 us before it does anything and the first reads of a workgroup depend on each other, so
 // what the workgroups of a head repeat (the pool's residuals, a tenth of the tokens) is cheaper than another launch to
-// share it.  32768 tokens x 8 heads take 9 + 21 us (with launches for the pool, for its split and for the rows 40),
-// 131072 tokens 17 + 43 (65; rows 16 of the 43), 49157 given scores 8 + 20 (36).
+// share it.  32768 tokens x 8 heads take 8 + 21 us (with launches for the pool, for its split and for the rows 40),
+// 131072 tokens 13 + 40 (65; rows 16 of the 40), 49157 given scores 7 + 18 (36).
 // Bound: latency of dependent reads and barriers; the rows run at 5 TB/s.
 //
 // Every slot of an output comes from an ordered prefix sum (ties go to the lower token index);
