@@ -389,7 +389,9 @@ __device__ __forceinline__ void factor_invert_tile(f64x4 a, const f64x4& xt, dou
 // Bound: the chain of 4 x 4 blocks.  23 us for d = 128, eight heads (cycles: 30000 in the diagonal tiles, 7000 in the tiles
 // below them, 7500 in the backward substitution; the other tiles' updates are waited for in the second step alone).
 // Reading the next tile's operands ahead of a tile's products made the updates slower (6500 cycles against 5200 in
-// that step).  One workgroup per head with a thread per row and plain loops took 934 us (the sums included).
+// that step); L_ss^-1 L_sj formed by the idle waves while the tiles below the diagonal are multiplied, so that the backward
+// substitution waits for half as many products, lengthened those steps by more than it saved (the fit 97.0 -> 97.6 us).
+// One workgroup per head with a thread per row and plain loops took 934 us (the sums included).
 template <typename T, int D>
 __global__ __launch_bounds__(512) void solve_kernel(CalParams p) {
   constexpr int NB = D / 16, kTri = NB * (NB + 1) / 2, NW = 512 / kWave;
