@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "decode_rows.hpp"
 #include "launch.hpp"
 
 namespace vec {
@@ -487,10 +488,7 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
   const bool tile_in_block = PAGED && !is_apx && seg.block_shift >= 5 &&
                              ((row_end - 1) >> seg.block_shift) - (row_begin >> seg.block_shift) < kWave;
   int my_block = 0;
-  if (tile_in_block && row_begin < row_end) {
-    const int j = min((row_begin >> seg.block_shift) + lane, (row_end - 1) >> seg.block_shift);
-    my_block = seg.blocks[j];
-  }
+  if (tile_in_block && row_begin < row_end) my_block = seg.blocks[block_entry(row_begin, row_end, seg.cap, seg.block_shift, lane)];
   // Rows of a tile in straight lines of loads, one line per case; the last tile of the live rows and the one with the step's
   // own token look at every row.
   const int plain_rows = is_apx || seg.new_row < 0 ? seg_len : seg.new_row;
