@@ -772,7 +772,9 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
 // the weighted sums of the splits, z W, the division.  What bounds it is load instructions (16 cycles of the CU's
 // address unit each) and one trip to memory: a thread takes four neighbouring elements of every SG-th split with
 // 16-byte loads, the splits' references and sums go through LDS.  z W runs on the matrix cores: z in three bf16 parts
-// (all of its 24 bits), eight query rows by three parts on the M side, W's columns by the transposing LDS read.
+// (its 24 bits, eight at a time, cut and not rounded: above bf16's largest number a rounded first part would be infinite, and
+// the second minus infinity; of an infinite z the first part is all), eight query rows by three parts on the M side, W's
+// columns by the transposing LDS read.
 // Element by element, with z W on the vector unit, a step of one sequence (11 splits, four query heads) took 14.8 us, now
 // 11.9; with eight query heads per KV head (12 splits) 46.9 and 41.1.
 template <int D, int G> struct CombineLds {
@@ -889,9 +891,12 @@ __global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p
       unsigned char* row = dec_lds + ((g / 8) * 32 + g % 8) * L::kStride + pos * 2;
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
-        const uint2 w = make_uint2(pack_bf16(z[0], z[1]), pack_bf16(z[2], z[3]));
-        *reinterpret_cast<uint2*>(row + q * 8 * L::kStride) = w;
-        z[0] -= bf16_lo(w.x); z[1] -= bf16_hi(w.x); z[2] -= bf16_lo(w.y); z[3] -= bf16_hi(w.y);
+        uint32_t top[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) top[e] = __float_as_uint(z[e]) & 0xffff0000u;
+        *reinterpret_cast<uint2*>(row + q * 8 * L::kStride) = make_uint2(top[0] >> 16 | top[1], top[2] >> 16 | top[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = (top[e] & 0x7fffffffu) == 0x7f800000u ? 0.f : z[e] - __uint_as_float(top[e]);
       }
     }
   }

@@ -185,6 +185,41 @@ def test_step_over_per_sequence_blocks_and_bad_arguments():
     assert ei.value.code == vb.VECTOR_ERR_ARG
 
 
+@pytest.mark.parametrize("flags", [0, vb.VECTOR_DECODE_LITERAL])
+@pytest.mark.parametrize("d,G", [(64, 1), (128, 4), (128, 10)])
+def test_keys_as_large_as_the_type_allows(d, G, flags):
+    """Two approximated rows whose first element is bf16's largest number M, at weights 1 and 0.003: their weighted sum lies
+    between M's upper rounding bound (1.00196 M) and fp32's end (1.0039 M).  With equal weights it is infinite in fp32, and what
+    fp32 arithmetic makes of that is an infinite result, of W's sign."""
+    rng = np.random.default_rng(d + G)
+    store = _store("bf16")
+    M = dg.widen(np.array([0x7F7F], np.uint16))[0]
+    scale = 1.0 / np.sqrt(d)
+    k_apx, q = np.zeros((1, 1, 2, d)), rng.standard_normal((1, G, d))
+    k_apx[..., 0], k_apx[..., 2:] = M, 0.05 * rng.standard_normal((1, 1, 2, d - 2))
+    q[..., 0], q[..., 1], q[..., 2:] = 0.0, 8.0, 0.05 * q[..., 2:]
+    W = rng.standard_normal((1, d, d)) / np.sqrt(d)
+    W[:, 0] = rng.choice([-1.0, 1.0], (1, d)) * rng.uniform(2e-38, 1e-37, (1, d))
+    for second in (0.003, 1.0):
+        k_apx[0, 0, 1, 1] = np.log(second) / (8.0 * scale)
+        k, qs, Ws = store(k_apx), store(q), store(W)
+        t = dict(len=pl.to_device(np.zeros(1, np.int32)), k=pl.to_device(k), W=pl.to_device(Ws))
+        cache = vb.Cache(batch=1, n_q_heads=G, n_kv_heads=1, head_dim=d, dtype=vb.VECTOR_BF16, cap_retain=0, n_approx=2)
+        cache.len_retain, cache.k_apx, cache.W = t["len"].data_ptr(), t["k"].data_ptr(), t["W"].data_ptr()
+        shape = vb.Shape(n_q_heads=G, n_kv_heads=1, head_dim=d, seq_len=64, window=1, pool_kernel=1, dtype=cache.dtype)
+        ws = pl.alloc_workspace(vb.vector_workspace_bytes(shape, 2, 2, 1))
+        out = torch.full((1, G, d), 7.0, dtype=torch.float32, device="cuda:0")
+        vb.vector_decode_attn(cache, pl.to_device(qs), scale, out, ws, flags=flags | vb.VECTOR_DECODE_OUT_F32)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        none = np.zeros((1, 1, 0, d))
+        if second < 1.0 or flags:                # rebuilt row by row, nothing leaves the range
+            assert np.isfinite(got).all()
+            close(got, vo.decode_attn(dg.widen(qs), none, none, np.array([0]), dg.widen(k), dg.widen(Ws), scale), f"second weight {second}")
+        else:
+            assert np.array_equal(got[..., 1:], np.where(dg.widen(Ws)[:, :1, 1:] > 0, np.inf, -np.inf).repeat(G, axis=1))
+
+
 @pytest.mark.parametrize("dtype,d,block_rows", [("bf16", 128, 64), ("bf16", 64, 16), ("f32", 64, 32)])
 def test_paged_retained_segments(dtype, d, block_rows):
     """Retained segments scattered over a pool of blocks: attention and two steps with appends give
