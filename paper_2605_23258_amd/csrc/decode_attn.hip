@@ -806,7 +806,9 @@ __global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p
   const bool use_w = p.n_approx > 0 && !p.literal;
 
   // this thread's elements, and its first splits
-  const int quad = tid % L::kQuads, side = L::kSide > 1 ? tid / L::kQuads : 0;
+  const int quad = tid % L::kQuads;
+  int side = L::kSide > 1 ? tid / L::kQuads : 0;       // of a whole wave the same where it can be: then which split counts where is a scalar question
+  if constexpr (L::kQuads % kWave == 0) side = __builtin_amdgcn_readfirstlane(side);
   const bool has_quad = side < L::kSide;
   f32x4 x0[kFlight];
   auto load_splits = [&](int round, int s0, f32x4* x) {
@@ -850,9 +852,14 @@ __global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p
       for (int u = 0; u < kFlight; ++u) {
         const int s = s0 + u * L::kSide;
         if (s < n_splits) {
-          const float sc = fast_exp2(ml[s * 2 * G + g] - m_safe), cv = s < n_ret ? sc : 0.f, cz = sc - cv;
+          const float sc = fast_exp2(ml[s * 2 * G + g] - m_safe);
+          if (s < n_ret) {                       // not by weights of 0: a share may be infinite
 #pragma unroll
-          for (int e = 0; e < 4; ++e) { av[e] = fmaf(x[u][e], cv, av[e]); az[e] = fmaf(x[u][e], cz, az[e]); }
+            for (int e = 0; e < 4; ++e) av[e] = fmaf(x[u][e], sc, av[e]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) az[e] = fmaf(x[u][e], sc, az[e]);
+          }
         }
       }
     }
@@ -896,7 +903,7 @@ __global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p
         for (int e = 0; e < 4; ++e) top[e] = __float_as_uint(z[e]) & 0xffff0000u;
         *reinterpret_cast<uint2*>(row + q * 8 * L::kStride) = make_uint2(top[0] >> 16 | top[1], top[2] >> 16 | top[3]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) z[e] = (top[e] & 0x7fffffffu) == 0x7f800000u ? 0.f : z[e] - __uint_as_float(top[e]);
+        for (int e = 0; e < 4; ++e) z[e] = q == 0 && (top[e] & 0x7fffffffu) == 0x7f800000u ? 0.f : z[e] - __uint_as_float(top[e]);
       }
     }
   }

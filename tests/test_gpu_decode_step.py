@@ -217,7 +217,30 @@ def test_keys_as_large_as_the_type_allows(d, G, flags):
             assert np.isfinite(got).all()
             close(got, vo.decode_attn(dg.widen(qs), none, none, np.array([0]), dg.widen(k), dg.widen(Ws), scale), f"second weight {second}")
         else:
-            assert np.array_equal(got[..., 1:], np.where(dg.widen(Ws)[:, :1, 1:] > 0, np.inf, -np.inf).repeat(G, axis=1))
+            assert np.array_equal(got, np.where(dg.widen(Ws)[:, :1] > 0, np.inf, -np.inf).repeat(G, axis=1))
+
+
+@pytest.mark.parametrize("d,G,n", [(64, 1, 40), (128, 4, 40), (128, 4, 3000), (128, 10, 3000)])
+def test_infinite_values_stay_in_their_column(d, G, n):
+    """A retained value of infinity takes its own column out of the result, and no other one."""
+    rng = np.random.default_rng(n + G)
+    store = _store("bf16")
+    k_ret, v_ret, k_apx = (store(rng.standard_normal((1, 1, n, d))) for _ in range(3))
+    q, W = store(rng.standard_normal((1, G, d))), store(rng.standard_normal((1, d, d)) / np.sqrt(d))
+    scale, length = 1.0 / np.sqrt(d), np.array([n], np.int32)
+    ref = vo.decode_attn(dg.widen(q), dg.widen(k_ret), dg.widen(v_ret), length, dg.widen(k_apx), dg.widen(W), scale)
+    v_ret[0, 0, n // 2, 5] = 0x7F80
+    t = [pl.to_device(x) for x in (length, k_ret, v_ret, k_apx, W)]
+    cache = vb.Cache(batch=1, n_q_heads=G, n_kv_heads=1, head_dim=d, dtype=vb.VECTOR_BF16, cap_retain=n, n_approx=n)
+    cache.len_retain, cache.k_ret, cache.v_ret, cache.k_apx, cache.W = (x.data_ptr() for x in t)
+    shape = vb.Shape(n_q_heads=G, n_kv_heads=1, head_dim=d, seq_len=max(n, 64), window=1, pool_kernel=1, dtype=cache.dtype)
+    ws = pl.alloc_workspace(vb.vector_workspace_bytes(shape, n, n, 1))
+    out = torch.full((1, G, d), 7.0, dtype=torch.float32, device="cuda:0")
+    vb.vector_decode_attn(cache, pl.to_device(q), scale, out, ws, flags=vb.VECTOR_DECODE_OUT_F32)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert not np.isfinite(got[..., 5]).any() and np.isfinite(np.delete(got, 5, axis=-1)).all()
+    close(np.delete(got, 5, axis=-1), np.delete(ref, 5, axis=-1), "the other columns")
 
 
 @pytest.mark.parametrize("dtype,d,block_rows", [("bf16", 128, 64), ("bf16", 64, 16), ("f32", 64, 32)])
