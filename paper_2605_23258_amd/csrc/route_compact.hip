@@ -485,6 +485,8 @@ __device__ __forceinline__ void leave_runs(int at, int count, int n_chunks, Runs
 // where lane c of wave 0 finds chunk c's: that gives the digit, and where every chunk keeps its entries.  (With two bytes
 // of every table per load and a second trip for the digit, routing and rows of 49157 given scores took 37.6 us, now 35.5.)
 // prefetch() is called once the loads are out.
+// k lies between 1 and the number of keys (launch_route refuses any other n_pool, and every key is in one bin), so exactly one
+// bin holds it: sh.digit is read where it was written.
 template <typename Prefetch>
 __device__ __forceinline__ void pick_from_tables(const uint16_t* tables, int n_chunks, int k, ListShared& sh, Prefetch prefetch) {
   constexpr int kPer = HT / kTableGroups, kLoads = kMaxChunks / kPer;      // chunks taken side by side, one after the other
@@ -1139,6 +1141,7 @@ int launch_pool_scores(const float* mass, float* score, const float* eps, int n_
 
 int launch_route(int n_kv_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx, uint8_t* tier,
                  int32_t* idx_retain, int32_t* idx_approx, void* ws, bool have_buckets, const PackedRows* rows, hipStream_t stream) {
+  if (n_approx < 0 || n_pool < n_approx || n_pool > seq_len) return VECTOR_ERR_ARG;      // the selections rely on it
   if (n_pool == 0) {
     const size_t total = (size_t)n_kv_heads * seq_len;
     VEC_LAUNCH(K_ROUTE, route_evict_all_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, tier, total);
@@ -1215,7 +1218,8 @@ int launch_route_compact_ragged(const vector_shape& s, const RaggedSeq* seqs, in
   int most_pool = 0, most_chunks = 0;
   for (int b = 0; b < count; ++b) {
     const RaggedSeq& q = seqs[b];
-    if (q.n_pool < 1) return VECTOR_ERR_ARG;               // nothing kept: that sequence goes through launch_route on its own
+    // the selections rely on it; nothing kept: that sequence goes through launch_route on its own
+    if (q.n_pool < 1 || q.n_approx < 0 || q.n_pool < q.n_approx || q.n_pool > q.shape.seq_len) return VECTOR_ERR_ARG;
     host[b] = route_params(s.n_kv_heads, count * s.n_kv_heads, q.shape.seq_len, q.score, q.eps, q.n_pool, q.n_approx, q.tier, q.idx_retain,
                            q.idx_approx, q.route_ws);
     host[b].g = gather_params(q.shape, q.k, q.v, q.idx_retain, q.idx_approx, q.n_pool - q.n_approx, q.n_approx, q.k_ret, q.v_ret, q.k_apx,

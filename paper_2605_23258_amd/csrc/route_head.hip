@@ -411,7 +411,7 @@ bool route_head_pools(int pool_kernel) { return pool_kernel / 2 <= 4; }
 
 int launch_route_head(int n_kv_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx, uint8_t* tier,
                       int32_t* idx_retain, int32_t* idx_approx, const HeadPool* pool, const PackedRows* rows, hipStream_t stream) {
-  if (n_pool < 1 || !route_head_fits(seq_len) || (pool && !route_head_pools(pool->kernel))) return VECTOR_ERR_ARG;
+  if (n_pool < 1 || n_approx < 0 || n_pool < n_approx || n_pool > seq_len || !route_head_fits(seq_len) || (pool && !route_head_pools(pool->kernel))) return VECTOR_ERR_ARG;
   HeadParams p = head_params(pool ? pool->mass : nullptr, score, pool ? pool->score : nullptr, eps, seq_len, pool ? pool->n_prefix : seq_len,
                              pool ? pool->kernel : 1, pool ? pool->mode : VECTOR_POOL_AVG, n_pool, n_approx, tier, idx_retain, idx_approx);
   if (rows)
@@ -438,7 +438,7 @@ int launch_route_head_ragged(const vector_shape& s, const RaggedSeq* seqs, int c
   for (int b = 0; b < count; ++b) {
     const RaggedSeq& q = seqs[b];
     const int n = q.shape.seq_len;
-    if (q.n_pool < 1 || !route_head_fits(n)) return VECTOR_ERR_ARG;
+    if (q.n_pool < 1 || q.n_approx < 0 || q.n_pool < q.n_approx || q.n_pool > n || !route_head_fits(n)) return VECTOR_ERR_ARG;
     host[b] = head_params(score_mass(q.shape, q.score_ws), nullptr, q.score, q.eps, n, n - q.shape.window, s.pool_kernel, s.pool_mode, q.n_pool,
                           q.n_approx, q.tier, q.idx_retain, q.idx_approx);
     host[b].g = gather_params(q.shape, q.k, q.v, q.idx_retain, q.idx_approx, q.n_pool - q.n_approx, q.n_approx, q.k_ret, q.v_ret, q.k_apx,

@@ -97,6 +97,21 @@ def test_batch_workspace_follows_how_the_sequences_share_launches():
     assert batch_bytes([4096, 1000, 2500, 8192, 8192]) == max(ragged, one(8192, 2))
 
 
+@pytest.mark.parametrize("n", [64, 50000])           # routed in one launch and in two
+@pytest.mark.parametrize("over,apx", [(1, 0), (1, 5), (-20, -1), (-40, 30)])
+def test_counts_that_no_selection_can_meet_are_refused(n, over, apx):
+    """The routing kernels rely on 0 <= n_approx <= n_pool <= n: every way in refuses anything else before it launches."""
+    import ctypes as C
+    L = vb.lib()
+    n_pool = n + over if over != -40 else 20
+    some = C.c_void_p(4096)                           # an address that nothing may use
+    counts = (n_pool, apx)
+    assert L.vector_route(2, n, some, some, *counts, some, some, some, some, 1 << 40, None) == -1
+    assert L.vector_route_static(2, n, some, some, *counts, some, some, some, None) == -1
+    s = vb.Shape(n_q_heads=4, n_kv_heads=2, head_dim=64, seq_len=n, window=8, pool_kernel=7, dtype=vb.VECTOR_BF16)
+    assert L.vector_compress(C.byref(s), some, some, some, some, *counts, *([some] * 8), n, some, 1 << 40, None) == -1
+
+
 @pytest.mark.parametrize("dtype,esz", [("bf16", 2), ("f32", 4)])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("heads,n", [(8, 8192), (1, 600), (64, 4097), (8, 131072)])
