@@ -299,41 +299,41 @@ __global__ __launch_bounds__(NT) void route_head_kernel(KernelArgs<HeadParams, R
   // Step 1: the pool.  Then key[] turns into the residual keys of its members (smaller residual, larger
   // key), 0 elsewhere, and Step 3: the n_approx tokens of lowest residual in it lose their value.  One
   // copy of the selection's code for both: the instruction cache is filled once.
-  uint64_t in_pool = 0, in_apx = 0;                            // bit i: slot i
+  static_assert(4 * J <= 32, "a bit per slot");
+  uint32_t in_pool = 0, in_apx = 0;                            // bit i: slot i
 #pragma unroll 1
   for (int step = 0; step < 2; ++step) {
     const int k = step == 0 ? p.n_pool : p.n_approx;
     if (k == 0) break;
     const Threshold t = head_select(key, k, step == 0 ? center0 : center1, sh);
-    uint32_t bits[2] = {0u, 0u};
+    uint32_t bits = 0u;
     const int base = first_token();
 #pragma unroll
     for (int i = 4 * J - 1; i >= 0; --i) {                     // shifting in from the last slot: compare and add-with-carry
       const bool in = key[i] >= t.thr;
-      bits[i >> 5] = bits[i >> 5] + bits[i >> 5] + (in ? 1u : 0u);
+      bits = bits + bits + (in ? 1u : 0u);
       if ((i & 3) == 0) __builtin_amdgcn_sched_barrier(0);
     }
     if (!t.all_equal) {                                        // uniform: some keys equal to the threshold stay out
 #pragma unroll
       for (int i = 0; i < 4 * J; ++i)
-        if (key[i] == t.thr && (uint32_t)head_token<NT>(base, i) > t.tok) bits[i >> 5] &= ~(1u << (i & 31));
+        if (key[i] == t.thr && (uint32_t)head_token<NT>(base, i) > t.tok) bits &= ~(1u << i);
     }
-    const uint64_t set = ((uint64_t)bits[1] << 32) | bits[0];
-    if (step == 1) { in_apx = set; break; }
-    in_pool = set;
+    if (step == 1) { in_apx = bits; break; }
+    in_pool = bits;
 #pragma unroll
     for (int i = 0; i < 4 * J; ++i) {
-      key[i] = (bits[i >> 5] >> (i & 31)) & 1u ? ~float_key(ev[i >> 2][i & 3]) : 0u;
+      key[i] = (bits >> i) & 1u ? ~float_key(ev[i >> 2][i & 3]) : 0u;
       if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
     }
   }
-  const uint64_t in_ret = in_pool & ~in_apx;
+  const uint32_t in_ret = in_pool & ~in_apx;
   // fewer tokens leave the registers for them (1024 tokens: the second read costs 0.4 us; 8192 and 12289 gain 0.6 and 1.4)
   if constexpr (J * NT >= 2048) p = params_again<RAGGED, HeadParams>(launch_head);
   // ranks: members in earlier blocks, then the exclusive prefix inside the block
   const int block0 = unit0 / NW, block1 = (unit1 - 1) / NW + 1;
-  const uint64_t earlier_slots = ((uint64_t)1 << (4 * block0)) - 1u;
-  const int earlier = __popcll(in_ret & earlier_slots) + (__popcll(in_apx & earlier_slots) << 16);
+  const uint32_t earlier_slots = (1u << (4 * block0)) - 1u;          // block0 < J
+  const int earlier = __popc(in_ret & earlier_slots) + (__popc(in_apx & earlier_slots) << 16);
   int carry = 0;
   if (block0 > 0) {                                            // uniform
     int unused;
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(NT) void route_head_kernel(KernelArgs<HeadParams, R
   const EmitTarget target = {tier, ir, ia, n, n_retain, p.n_approx};
   for (int b = block0; b < block1; ++b) {
     const int wave0 = max(unit0 - b * NW, 0), wave1 = min(unit1 - b * NW, NW);
-    const uint32_t ret4 = (uint32_t)(in_ret >> (4 * b)) & 15u, apx4 = (uint32_t)(in_apx >> (4 * b)) & 15u;
+    const uint32_t ret4 = (in_ret >> (4 * b)) & 15u, apx4 = (in_apx >> (4 * b)) & 15u;
     int before, total;
     head_scan<NT>(__popc(ret4) + (__popc(apx4) << 16), sh.wsum[2], before, total);
     // the part's own range of ranks, from the waves' totals
