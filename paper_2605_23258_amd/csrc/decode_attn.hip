@@ -941,8 +941,9 @@ __global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p
 }
 
 // the same for fp32 caches, z W on the vector unit
-template <typename T, int D, int G>
+template <int D, int G>
 __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
+  using T = float;
   constexpr int PSZ = 2 * G + G * D;
   constexpr int E = Elem<T>::kPerChunk;    // elements of W per 16-byte load
   constexpr int CG = D / E;                // thread groups along a row of W
@@ -965,7 +966,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
   const int cg = threadIdx.x % CG, rg = threadIdx.x / CG;
   const T* Wh = reinterpret_cast<const T*>(p.W) + (int64_t)h * p.w_sh;
   uint4 wraw[RP];
-  const bool use_w = p.n_approx > 0 && !p.literal;      // literal partials are values already
+  const bool use_w = p.n_approx > 0;
   // the step's own token is now a row of the cache (the split launch has finished): one thread per
   // sequence makes it live, unless the block was full
   if (p.k_new && h == 0 && threadIdx.x == 0) {
@@ -1015,7 +1016,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
             if (s0 + u < n_splits && ms[e][u] != -INFINITY) {
               const float sc = fast_exp2(ms[e][u] - mx);
               L[e] = fmaf(ls[e][u], sc, L[e]);
-              if (s0 + u < p.splits_ret || p.literal) av[e] = fmaf(xs[e][u], sc, av[e]);
+              if (s0 + u < p.splits_ret) av[e] = fmaf(xs[e][u], sc, av[e]);
               else az[e] = fmaf(xs[e][u], sc, az[e]);
             }
           }
@@ -1077,9 +1078,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
     float zw = 0.f;
 #pragma unroll
     for (int q = 0; q < kWavesC; ++q) zw += zw_lds[q][g][j];
-    const float r = (v_lds[g][j] + zw) * linv_lds[g];
-    if (p.out_f32) reinterpret_cast<float*>(p.out)[((size_t)b * p.Hq + (size_t)h * G) * D + i] = r;
-    else store_elem(out + i, r);
+    out[i] = (v_lds[g][j] + zw) * linv_lds[g];
   }
 }
 
@@ -1142,7 +1141,7 @@ int run_decode_layout(const vector_cache& c, DecodeParams& p, hipStream_t stream
     VEC_HIP(set_max_lds(reinterpret_cast<const void*>(decode_combine_mfma_kernel<D, G>), lds));
     VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_mfma_kernel<D, G>), dim3(c.n_kv_heads, c.batch), dim3(256), lds, stream, p);
   } else {
-    VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_kernel<T, D, G>), dim3(c.n_kv_heads, c.batch), dim3(256), 0, stream, p);
+    VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_kernel<D, G>), dim3(c.n_kv_heads, c.batch), dim3(256), 0, stream, p);
   }
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
