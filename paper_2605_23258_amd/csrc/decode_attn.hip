@@ -22,7 +22,6 @@
 //                           dot product per lane, rotate-add across the lanes of a row,
 //                           online softmax per lane group).
 //   decode_combine_kernel : merges the splits, applies W to z, normalises, stores.
-#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -119,7 +118,6 @@ __device__ __forceinline__ void append_new_row(const DecodeParams& p, const Segm
 
 constexpr int DT_ = 256;          // threads per workgroup
 constexpr int DW = DT_ / kWave;   // waves
-constexpr int kMaxSplits = 64;
 constexpr int kUnroll = 4;        // rows per lane group in flight
 constexpr double kRopeApxCost = 2.2;
 
@@ -783,7 +781,7 @@ template <int D, int G> struct CombineLds {
   static constexpr int kRounds = (kQuads + 255) / 256;
   static constexpr int kBlocks = (G + 7) / 8;                            // of eight query rows
   static constexpr int kStride = D * 2 + 16;                             // bytes of a row of W, and of z's parts
-  static constexpr int kMl = 2 * kMaxSplits * 2 * G * 4, kParts = kBlocks * 32 * kStride;      // not at the same time
+  static constexpr int kMl = kMaxSplits * 2 * G * 4, kParts = kBlocks * 32 * kStride;      // not at the same time
   static constexpr int kSums = (kMl > kParts ? kMl : kParts);            // [2: retained, approximated][kSide][G * D]
   static constexpr int kW = kSums + 2 * kSide * G * D * 4;
   static constexpr int kInv = kW + D * kStride;
@@ -1082,38 +1080,6 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
   }
 }
 
-// Splits of either segment, by an estimate of the step in us.  A workgroup costs kStart, and a unit for every step_rows rows
-// it reads (a retained row counts twice, an approximated one apx_cost times): kAlone by itself, kUnit when kFull workgroups or
-// more share the memory.  kAtOnce run at the same time; with more, the last ones leave the chip idle for a quarter of the
-// longest one.  Every split costs the merge kMerge.  The splits are divided between the segments by their cost.  Against one
-// rule for all (1024 workgroups, 256 rows each at least), us: 16 sequences of 32768 tokens 70.9 -> 70.0 (768 workgroups),
-// 17 of 17000 31.3 -> 26.4 (510), 3 of 2000 with eight query heads 15.3 -> 13.5; fp32, 3 of 4000 36.5 -> 20.8.
-void pick_splits(int step_rows, int batch, int n_kv_heads, int cap_retain, int n_approx, double apx_cost, int& s_ret, int& s_apx) {
-  constexpr double kStart = 4.5, kUnit = 2.3, kAlone = 0.65, kMerge = 0.08;
-  constexpr int kAtOnce = 512, kFull = 300;
-  const double pairs = (double)batch * n_kv_heads;
-  const int steps_r = (int)(((int64_t)cap_retain + step_rows - 1) / step_rows), steps_a = (int)(((int64_t)n_approx + step_rows - 1) / step_rows);
-  const double cost_r = 2.0 * steps_r, cost_a = apx_cost * steps_a;
-  s_ret = steps_r > 0 || steps_a == 0 ? 1 : 0;   // nothing cached: one workgroup writes the empty partial
-  s_apx = steps_a > 0 ? 1 : 0;
-  if (cost_r + cost_a == 0.0) return;
-  double best = -1.0;
-  const int most = (int)std::min<int64_t>(kMaxSplits, (int64_t)steps_r + steps_a);
-  for (int total = s_ret + s_apx; total <= most; ++total) {
-    int r = (int)(total * cost_r / (cost_r + cost_a) + 0.5);
-    r = std::max(steps_r > 0 ? 1 : 0, std::min(r, steps_r));
-    const int a = std::max(steps_a > 0 ? 1 : 0, std::min(total - r, steps_a));
-    const double count = pairs * (r + a), full = std::min(1.0, count / kFull), unit = kAlone + (kUnit - kAlone) * full;
-    const double longest_r = r ? 2.0 * ((steps_r + r - 1) / r) : 0.0, longest_a = a ? apx_cost * ((steps_a + a - 1) / a) : 0.0;
-    const double longest = kStart + unit * std::max(longest_r, longest_a);
-    double t = longest;
-    if (count > kAtOnce) t = std::max(t, (kStart * count + unit * pairs * (cost_r + cost_a)) / kAtOnce + 0.25 * longest);
-    t += kMerge * (r + a);
-    if (best < 0.0 || t < best) { best = t; s_ret = r; s_apx = a; }
-    if (count > 4 * kAtOnce) break;              // more would only add starts
-  }
-}
-
 template <typename T, int D, int G, bool PAGED>
 int run_decode_layout(const vector_cache& c, DecodeParams& p, hipStream_t stream, const RopeParams* rope) {
   const dim3 grid(p.splits_ret + p.splits_apx, c.n_kv_heads, c.batch);
@@ -1173,7 +1139,7 @@ int run_decode_g(const vector_cache& c, DecodeParams& p, hipStream_t stream, con
 }  // namespace
 
 size_t decode_workspace_bytes(int batch, int n_q_heads, int n_kv_heads, int head_dim, int cap_retain, int n_approx) {
-  // sized for the largest split count so that the bound holds for any live length
+  // sized for the largest split count so that the bound holds for any live length (twice what a launch writes)
   (void)cap_retain; (void)n_approx;
   const int G = n_q_heads / n_kv_heads;
   return align_up((size_t)batch * n_kv_heads * 2 * kMaxSplits * (2 * G + G * head_dim) * sizeof(float), 256);

@@ -1,4 +1,4 @@
-"""Index arithmetic of the decode kernels, compiled for the host.  No GPU needed."""
+"""What the decode launches compute about rows, compiled for the host.  No GPU needed."""
 import os
 import subprocess
 
@@ -35,11 +35,45 @@ int main() {
 """
 
 
-@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
-def test_block_table_entries_stay_in_the_table(tmp_path):
-    (tmp_path / "rows.cpp").write_text(PROGRAM)
+def run(tmp_path, program):
+    (tmp_path / "rows.cpp").write_text(program)
     exe = str(tmp_path / "rows")
     subprocess.run([os.path.join(os.path.dirname(build.HIPCC), "amdclang++"), "-std=c++17", "-O2", "-w", "-I", build.CSRC,
                     str(tmp_path / "rows.cpp"), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
+def test_block_table_entries_stay_in_the_table(tmp_path):
+    run(tmp_path, PROGRAM)
+
+
+# segments of every kind of length, few and many (sequence, head) pairs, both kinds of steps
+SPLITS = r"""
+#include <cstdio>
+#include "decode_rows.hpp"
+int main() {
+  const int rows[] = {0, 1, 20, 100, 128, 129, 1000, 5000, 40000, 1000000, 2147483647};
+  for (int step : {32, 64, 128})
+    for (int pairs : {1, 2, 3, 8, 64, 300, 5000})
+      for (double apx : {1.0, 2.2})
+        for (int cap : rows)
+          for (int n : rows) {
+            int r = -1, a = -1;
+            vec::pick_splits(step, pairs, 1, cap, n, apx, r, a);
+            const bool none = cap == 0 && n == 0;
+            if (r + a > vec::kMaxSplits || r < (cap > 0 || none) || a < (n > 0) || (cap == 0 && !none && r) || (n == 0 && a)) {
+              printf("steps of %d, %d pairs, %d and %d rows: %d + %d\n", step, pairs, cap, n, r, a);
+              return 1;
+            }
+          }
+  return 0;
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
+def test_splits_stay_within_their_number(tmp_path):
+    """Every segment with rows gets a split, one without gets none, and both together get no more than a merge has room for."""
+    run(tmp_path, SPLITS)
