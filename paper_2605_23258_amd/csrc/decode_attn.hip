@@ -119,7 +119,6 @@ __device__ __forceinline__ void append_new_row(const DecodeParams& p, const Segm
 constexpr int DT_ = 256;          // threads per workgroup
 constexpr int DW = DT_ / kWave;   // waves
 constexpr int kUnroll = 4;        // rows per lane group in flight
-constexpr double kRopeApxCost = 2.2;
 
 // sum over the LPR adjacent lanes that share a row; every lane of the group gets the total
 template <int LPR> __device__ __forceinline__ float group_sum(float x) {
@@ -1080,28 +1079,40 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
   }
 }
 
+// Workgroups of a split kernel that fit a CU, asked for once per kernel.
+template <auto Kernel> int workgroups_per_cu(int lds) {
+  static const int n = [&] {
+    int fit = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, reinterpret_cast<const void*>(Kernel), DT_, lds) != hipSuccess) (void)hipGetLastError();
+    return fit > 0 ? fit : 1;
+  }();
+  return n;
+}
+
+template <auto Kernel, typename T, int D, int G>
+int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t stream, const RopeParams* rope) {
+  if (lds) VEC_HIP(set_max_lds(reinterpret_cast<const void*>(Kernel), lds));
+  const SplitCosts costs = split_costs(Elem<T>::kDtype == VECTOR_BF16, D, G, rope != nullptr, workgroups_per_cu<Kernel>(lds));
+  static_assert(Elem<T>::kDtype == VECTOR_BF16 ? DW * kTileRows == 128 : DW * kWave * 4 * kUnroll == 4096, "the rows of a step that split_costs states");
+  pick_splits(costs, c.batch, c.n_kv_heads, c.cap_retain, c.n_approx, p.splits_ret, p.splits_apx);
+  const dim3 grid(p.splits_ret + p.splits_apx, c.n_kv_heads, c.batch);
+  VEC_LAUNCH(K_DECODE_SPLIT, Kernel, grid, dim3(DT_), lds, stream, p, rope ? *rope : RopeParams{});
+  return VECTOR_OK;
+}
+
 template <typename T, int D, int G, bool PAGED>
 int run_decode_layout(const vector_cache& c, DecodeParams& p, hipStream_t stream, const RopeParams* rope) {
-  const dim3 grid(p.splits_ret + p.splits_apx, c.n_kv_heads, c.batch);
+  int rc;
   if constexpr (Elem<T>::kDtype == VECTOR_BF16) {
     constexpr int lds = MfmaDecodeTile<D>::kLdsBytes;
-    if (rope) {
-      VEC_HIP(set_max_lds(reinterpret_cast<const void*>(decode_split_mfma_kernel<D, G, true, false, PAGED>), lds));
-      VEC_LAUNCH(K_DECODE_SPLIT, (decode_split_mfma_kernel<D, G, true, false, PAGED>), grid, dim3(DT_), lds, stream, p, *rope);
-    } else if (p.literal) {
-      VEC_HIP(set_max_lds(reinterpret_cast<const void*>(decode_split_mfma_kernel<D, G, false, true, PAGED>), lds));
-      VEC_LAUNCH(K_DECODE_SPLIT, (decode_split_mfma_kernel<D, G, false, true, PAGED>), grid, dim3(DT_), lds, stream, p, RopeParams{});
-    } else {
-      VEC_HIP(set_max_lds(reinterpret_cast<const void*>(decode_split_mfma_kernel<D, G, false, false, PAGED>), lds));
-      VEC_LAUNCH(K_DECODE_SPLIT, (decode_split_mfma_kernel<D, G, false, false, PAGED>), grid, dim3(DT_), lds, stream, p, RopeParams{});
-    }
+    if (rope) rc = launch_split<decode_split_mfma_kernel<D, G, true, false, PAGED>, T, D, G>(c, p, lds, stream, rope);
+    else if (p.literal) rc = launch_split<decode_split_mfma_kernel<D, G, false, true, PAGED>, T, D, G>(c, p, lds, stream, rope);
+    else rc = launch_split<decode_split_mfma_kernel<D, G, false, false, PAGED>, T, D, G>(c, p, lds, stream, rope);
   } else {
-    if (rope) {
-      VEC_LAUNCH(K_DECODE_SPLIT, (decode_split_kernel<T, D, G, PAGED, true>), grid, dim3(DT_), 0, stream, p, *rope);
-    } else {
-      VEC_LAUNCH(K_DECODE_SPLIT, (decode_split_kernel<T, D, G, PAGED, false>), grid, dim3(DT_), 0, stream, p, RopeParams{});
-    }
+    if (rope) rc = launch_split<decode_split_kernel<T, D, G, PAGED, true>, T, D, G>(c, p, 0, stream, rope);
+    else rc = launch_split<decode_split_kernel<T, D, G, PAGED, false>, T, D, G>(c, p, 0, stream, rope);
   }
+  if (rc != VECTOR_OK) return rc;
   if constexpr (Elem<T>::kDtype == VECTOR_BF16) {
     constexpr int lds = CombineLds<D, G>::kTotal;
     VEC_HIP(set_max_lds(reinterpret_cast<const void*>(decode_combine_mfma_kernel<D, G>), lds));
@@ -1159,10 +1170,6 @@ int launch_decode_attn(const vector_cache& c, const void* q, float scale, void* 
   p.ret_row_start = c.ret_row_start; p.apx_row_start = c.apx_row_start;
   p.out = out; p.part = reinterpret_cast<float*>(ws);
   p.B = c.batch; p.Hq = c.n_q_heads; p.Hkv = c.n_kv_heads; p.cap_retain = c.cap_retain; p.n_approx = c.n_approx;
-  // an approximated row costs its bytes; with the rotary un-rotation its sines and cosines make
-  // it cost about as much as two rows' worth of streaming
-  const int step_rows = c.dtype == VECTOR_BF16 ? DW * kTileRows : DW * kWave * 4 / c.head_dim * kUnroll;
-  pick_splits(step_rows, c.batch, c.n_kv_heads, c.cap_retain, c.n_approx, rope ? kRopeApxCost : 1.0, p.splits_ret, p.splits_apx);
   p.w_sh = c.w_shared ? 0 : (int64_t)c.head_dim * c.head_dim;
   p.c2 = scale * kLog2e;
   if (c.dtype == VECTOR_BF16) {

@@ -16,35 +16,85 @@ constexpr int block_entry(int row_begin, int row_end, int cap, int block_shift, 
 
 constexpr int kMaxSplits = 64;    // of both segments together: what pick_splits keeps to, and the merge has room for
 
-// Splits of either segment, by an estimate of the step in us.  A workgroup costs kStart, and a unit for every step_rows rows
-// it reads (a retained row counts twice, an approximated one apx_cost times): kAlone by itself, kUnit when kFull workgroups or
-// more share the memory.  kAtOnce run at the same time; with more, the last ones leave the chip idle for a quarter of the
-// longest one.  Every split costs the merge kMerge.  The splits are divided between the segments by their cost.  Against one
-// rule for all (1024 workgroups, 256 rows each at least), us: 16 sequences of 32768 tokens 70.9 -> 70.0 (768 workgroups),
-// 17 of 17000 31.3 -> 26.4 (510), 3 of 2000 with eight query heads 15.3 -> 13.5; fp32, 3 of 4000 36.5 -> 20.8.
-inline void pick_splits(int step_rows, int batch, int n_kv_heads, int cap_retain, int n_approx, double apx_cost, int& s_ret, int& s_apx) {
-  constexpr double kStart = 4.5, kUnit = 2.3, kAlone = 0.65, kMerge = 0.08;
-  constexpr int kAtOnce = 512, kFull = 300;
+// What the estimate of a decode step is made of, in us.  A workgroup costs `start`, and for every step of its rows (step_rows of
+// them) between `alone`, when little else runs, and `full`, when full_at workgroups or more share the memory and the CUs.
+// at_once workgroups run at the same time; with more, the last ones leave the chip idle for `last` of the longest one.
+// The merge costs `slot` for every split that a trip of its loads has room for, and `trip` for every trip.
+struct SplitCosts {
+  int step_rows, at_once;
+  double start;
+  double alone_ret, full_ret, alone_apx, full_apx;      // a step of retained rows (keys and values), of approximated ones (keys)
+  double full_at, last, slot, trip;
+  int per_trip, per_long_trip;           // splits: up to per_trip of them, and more
+};
+
+// Measured on 437 shapes (1 to 32 sequences of 600 to 32768 tokens, 1 to 8 KV heads with 1 to 8 query heads each, plain and rotated
+// keys, contiguous and paged), each with its segments cut in all ways.  per_cu: workgroups that fit a CU, by the compiled
+// kernel's registers and LDS.
+//   bf16, d = 128: steps of 32 KB a tensor, two workgroups per CU; a retained step counts as two approximated ones.  Against one
+//     rule for all (1024 workgroups, 256 rows each at least), us: 16 sequences of 32768 tokens 70.9 -> 70.4 (768 workgroups),
+//     17 of 17000 31.3 -> 26.4 (510), 3 of 2000 with eight query heads 15.3 -> 13.5.
+//   bf16, d = 64: half the bytes, three per CU; alone, a step is latency, which both kinds of rows have alike.  With the constants
+//     of d = 128 in their place 16 sequences of 17000 tokens took 29.1 us, now 24.1; 24 unequal ones of up to 16000 28.0, now 25.8.
+//     In the mean the choice is 1.02 times the best cut (with those of d = 128: 1.06).
+//   fp32: half the bytes, and the vector unit's time, which grows with the query heads; one to five per CU.  The merge reads
+//     G d / 256 elements a thread, 8 or 16 splits in a trip.  With bf16's constants, d = 128: 32 sequences of 4096 tokens,
+//     four query heads, 76.6 us (four workgroups a CU where three fit), now 54; 10 of 1800, eight query heads, 51.6, now 28.3.
+//     In the mean 1.04 times the best cut (1.17).
+constexpr SplitCosts split_costs(bool bf16, int head_dim, int group, bool rope, int per_cu) {
+  SplitCosts c = {};
+  c.at_once = 256 * per_cu;
+  if (bf16) {
+    const bool wide = head_dim == 128;
+    c.step_rows = 128;
+    c.start = wide ? 4.5 : 5.2;
+    c.alone_ret = wide ? 1.3 : 1.2; c.full_ret = wide ? 4.6 : 2.2;
+    c.alone_apx = (wide ? 0.65 : 0.9) * (!rope ? 1.0 : wide ? 2.2 : 2.0);             // sines, cosines and the turn
+    c.full_apx = (wide ? 2.3 : 2.4) * (!rope ? 1.0 : wide ? 2.2 : 1.7);
+    c.full_at = wide ? 300.0 : 768.0;
+    c.last = 0.25;
+    c.slot = 0.08;
+    c.per_trip = c.per_long_trip = 1;
+    return c;
+  }
+  const int elements = (group * head_dim + 255) / 256;
+  c.step_rows = 4096 / head_dim;
+  c.start = 7.4;
+  c.alone_ret = 0.45 + 0.18 * group; c.full_ret = 3.45 + 0.35 * group;
+  c.alone_apx = (0.78 + 0.24 * group) * (rope ? 1.35 : 1.0);
+  c.full_apx = (4.5 + 0.9 * group) * (rope ? 1.25 : 1.0);
+  c.full_at = 0.65 * c.at_once;
+  c.last = 0.35;
+  c.slot = 0.044 * elements; c.trip = 0.36 * ((elements + 3) / 4);
+  c.per_trip = 8; c.per_long_trip = elements <= 2 ? 16 : 8;
+  return c;
+}
+
+// Splits of either segment: the least of the estimate.  The splits are divided between the segments by their cost.
+inline void pick_splits(const SplitCosts& c, int batch, int n_kv_heads, int cap_retain, int n_approx, int& s_ret, int& s_apx) {
   const double pairs = (double)batch * n_kv_heads;
-  const int steps_r = (int)(((int64_t)cap_retain + step_rows - 1) / step_rows), steps_a = (int)(((int64_t)n_approx + step_rows - 1) / step_rows);
-  const double cost_r = 2.0 * steps_r, cost_a = apx_cost * steps_a;
+  auto steps_of = [&](int rows) { return (int)(((int64_t)rows + c.step_rows - 1) / c.step_rows); };
+  const int steps_r = steps_of(cap_retain), steps_a = steps_of(n_approx);
   s_ret = steps_r > 0 || steps_a == 0 ? 1 : 0;   // nothing cached: one workgroup writes the empty partial
   s_apx = steps_a > 0 ? 1 : 0;
-  if (cost_r + cost_a == 0.0) return;
+  if (steps_r + (int64_t)steps_a == 0) return;
   double best = -1.0;
   const int most = (int)std::min<int64_t>(kMaxSplits, (int64_t)steps_r + steps_a);
   for (int total = s_ret + s_apx; total <= most; ++total) {
-    int r = (int)(total * cost_r / (cost_r + cost_a) + 0.5);
+    const double shared = std::min(1.0, pairs * total / c.full_at);
+    const double step_r = c.alone_ret + (c.full_ret - c.alone_ret) * shared, step_a = c.alone_apx + (c.full_apx - c.alone_apx) * shared;
+    const double work = step_r * steps_r + step_a * steps_a;
+    int r = (int)(total * step_r * steps_r / work + 0.5);
     r = std::max(steps_r > 0 ? 1 : 0, std::min({r, steps_r, total - (steps_a > 0 ? 1 : 0)}));      // r + a <= total
     const int a = std::max(steps_a > 0 ? 1 : 0, std::min(total - r, steps_a));
-    const double count = pairs * (r + a), full = std::min(1.0, count / kFull), unit = kAlone + (kUnit - kAlone) * full;
-    const double longest_r = r ? 2.0 * ((steps_r + r - 1) / r) : 0.0, longest_a = a ? apx_cost * ((steps_a + a - 1) / a) : 0.0;
-    const double longest = kStart + unit * std::max(longest_r, longest_a);
+    const double count = pairs * (r + a);
+    const double longest = c.start + std::max(r ? step_r * ((steps_r + r - 1) / r) : 0.0, a ? step_a * ((steps_a + a - 1) / a) : 0.0);
     double t = longest;
-    if (count > kAtOnce) t = std::max(t, (kStart * count + unit * pairs * (cost_r + cost_a)) / kAtOnce + 0.25 * longest);
-    t += kMerge * (r + a);
+    if (count > c.at_once) t = std::max(t, (c.start * count + pairs * work) / c.at_once + c.last * longest);
+    const int per_trip = r + a > c.per_trip ? c.per_long_trip : c.per_trip, trips = (r + a + per_trip - 1) / per_trip;
+    t += (c.slot * per_trip + c.trip) * trips;
     if (best < 0.0 || t < best) { best = t; s_ret = r; s_apx = a; }
-    if (count > 4 * kAtOnce) break;              // more would only add starts
+    if (count > 4.0 * c.at_once) break;          // more would only add starts
   }
 }
 
