@@ -1092,7 +1092,8 @@ template <auto Kernel> int workgroups_per_cu(int lds) {
 template <auto Kernel, typename T, int D, int G>
 int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t stream, const RopeParams* rope) {
   if (lds) VEC_HIP(set_max_lds(reinterpret_cast<const void*>(Kernel), lds));
-  const SplitCosts costs = split_costs(Elem<T>::kDtype == VECTOR_BF16, D, G, rope != nullptr, workgroups_per_cu<Kernel>(lds));
+  const ApproxRows kind = rope ? ApproxRows::kTurned : p.literal ? ApproxRows::kRebuilt : ApproxRows::kPlain;
+  const SplitCosts costs = split_costs(Elem<T>::kDtype == VECTOR_BF16, D, G, kind, workgroups_per_cu<Kernel>(lds));
   static_assert(Elem<T>::kDtype == VECTOR_BF16 ? DW * kTileRows == 128 : DW * kWave * 4 * kUnroll == 4096, "the rows of a step that split_costs states");
   pick_splits(costs, c.batch, c.n_kv_heads, c.cap_retain, c.n_approx, p.splits_ret, p.splits_apx);
   const dim3 grid(p.splits_ret + p.splits_apx, c.n_kv_heads, c.batch);

@@ -41,7 +41,11 @@ struct SplitCosts {
 //     G d / 256 elements a thread, 8 or 16 splits in a trip.  With bf16's constants, d = 128: 32 sequences of 4096 tokens,
 //     four query heads, 76.6 us (four workgroups a CU where three fit), now 54; 10 of 1800, eight query heads, 51.6, now 28.3.
 //     In the mean 1.04 times the best cut (1.17).
-constexpr SplitCosts split_costs(bool bf16, int head_dim, int group, bool rope, int per_cu) {
+//   Approximated rows that are turned back, or rebuilt one by one, cost more than their bytes.  Rebuilt, d = 128, with the costs
+//     of plain ones: 16 sequences of 32768 tokens 228 us (4 + 2 splits), now 170 (2 + 2; 206 under the one rule); one of 8192 24.6 and 19.9.
+enum class ApproxRows { kPlain, kTurned, kRebuilt };
+constexpr SplitCosts split_costs(bool bf16, int head_dim, int group, ApproxRows kind, int per_cu) {
+  const bool turned = kind == ApproxRows::kTurned, rebuilt = kind == ApproxRows::kRebuilt;
   SplitCosts c = {};
   c.at_once = 256 * per_cu;
   if (bf16) {
@@ -49,9 +53,15 @@ constexpr SplitCosts split_costs(bool bf16, int head_dim, int group, bool rope, 
     c.step_rows = 128;
     c.start = wide ? 4.5 : 5.2;
     c.alone_ret = wide ? 1.3 : 1.2; c.full_ret = wide ? 4.6 : 2.2;
-    c.alone_apx = (wide ? 0.65 : 0.9) * (!rope ? 1.0 : wide ? 2.2 : 2.0);             // sines, cosines and the turn
-    c.full_apx = (wide ? 2.3 : 2.4) * (!rope ? 1.0 : wide ? 2.2 : 1.7);
-    c.full_at = wide ? 300.0 : 768.0;
+    if (wide) {
+      c.alone_apx = turned ? 0.65 * 2.2 : rebuilt ? 3.0 : 0.65;
+      c.full_apx = turned ? 2.3 * 2.2 : rebuilt ? 6.0 : 2.3;
+      c.full_at = rebuilt ? 512.0 : 300.0;
+    } else {
+      c.alone_apx = turned ? 1.8 : rebuilt ? 1.2 : 0.9;
+      c.full_apx = turned ? 4.08 : rebuilt ? 3.2 : 2.4;
+      c.full_at = 768.0;
+    }
     c.last = 0.25;
     c.slot = 0.08;
     c.per_trip = c.per_long_trip = 1;
@@ -61,8 +71,8 @@ constexpr SplitCosts split_costs(bool bf16, int head_dim, int group, bool rope, 
   c.step_rows = 4096 / head_dim;
   c.start = 7.4;
   c.alone_ret = 0.45 + 0.18 * group; c.full_ret = 3.45 + 0.35 * group;
-  c.alone_apx = (0.78 + 0.24 * group) * (rope ? 1.35 : 1.0);
-  c.full_apx = (4.5 + 0.9 * group) * (rope ? 1.25 : 1.0);
+  c.alone_apx = (0.78 + 0.24 * group) * (turned ? 1.35 : 1.0);
+  c.full_apx = (4.5 + 0.9 * group) * (turned ? 1.25 : 1.0);
   c.full_at = 0.65 * c.at_once;
   c.last = 0.35;
   c.slot = 0.044 * elements; c.trip = 0.36 * ((elements + 3) / 4);
