@@ -4,7 +4,7 @@
 //
 //   gram_kernel / gram_f32_kernel : grid (token chunks, kv heads).  The two d x d products on the matrix
 //                  cores, fp32 accumulation inside a chunk; one fp32 partial pair per chunk.
-//   gram_reduce_kernel : the chunks' partials summed in fp64, in chunk order.
+//   gram_reduce_kernel : the chunks' partials summed in fp64: four quarters in chunk order, then their sum.
 //   solve_kernel : grid (d / 16 column blocks, heads).  Blocked fp64 Cholesky of K^T K with the column
 //                  block of K^T V riding along, then the backward substitution; all on fp64 matrix
 //                  instructions out of LDS.

@@ -21,7 +21,7 @@
 //   decode_split_kernel   : fp32 caches: the same split with vector-ALU dot products (partial
 //                           dot product per lane, rotate-add across the lanes of a row,
 //                           online softmax per lane group).
-//   decode_combine_kernel : merges the splits, applies W to z, normalises, stores.
+//   decode_combine_mfma_kernel (bf16), decode_combine_kernel (fp32): merge the splits, apply W to z, normalise, store.
 #include <type_traits>
 
 #include "common.hpp"
@@ -772,8 +772,8 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
 // (its 24 bits, eight at a time, cut and not rounded: above bf16's largest number a rounded first part would be infinite, and
 // the second minus infinity; of an infinite z the first part is all), eight query rows by three parts on the M side, W's
 // columns by the transposing LDS read.
-// Element by element, with z W on the vector unit, a step of one sequence (11 splits, four query heads) took 14.8 us, now
-// 11.9; with eight query heads per KV head (12 splits) 46.9 and 41.1.
+// Element by element, with z W on the vector unit, a step of one sequence (four query heads, 11 splits) took 14.8 us, with
+// this merge 11.9; with eight query heads per KV head (12 splits) 46.9 and 41.1.
 template <int D, int G> struct CombineLds {
   static constexpr int kQuads = G * D / 4;
   static constexpr int kSide = kQuads >= 256 ? 1 : 256 / kQuads;         // splits taken side by side
@@ -978,8 +978,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
 
   // A thread owns G*D/256 output elements and, for each, reads every split's (m, l, partial) itself (the (m, l)
   // reads of a query row are shared by the lanes that work on that row).  The reads of up to four elements and of 8 or
-  // 16 splits go out together and are folded into running maxima: one element and eight splits at a time, eleven
-  // splits of four query heads were four trips to memory one after the other (8k tokens, one sequence: 16.1 -> 14.8 us a step).
+  // 16 splits go out together and are folded into running maxima.  One element and eight splits at a time, a step of one sequence of
+  // 4096 tokens, d = 128, took 18.4 us against 16.8 with four query heads, 32.0 against 27.6 with eight.
   constexpr int NE = (G * D + 255) / 256, EB = NE < 4 ? NE : 4;
   auto fold_splits = [&](auto fold_tag) __attribute__((always_inline)) {
     constexpr int kFold = decltype(fold_tag)::value;

@@ -808,7 +808,7 @@ __device__ __forceinline__ HeadCut cut_head(const RouteParams& p, int h, int own
     for (int i = 0; i < kCandSlots; ++i) { ckey[i] = bkey[at[i]]; cpos[i] = bpos[at[i]]; ceps[i] = beps[at[i]]; }
   }
   lds_barrier();
-  // Slot i of wave w: group w + 8 i
+  // Slot i of wave w: group w + HW i
 #pragma unroll
   for (int i = 0; i < SLOTS; ++i) {
     const int2 g = sh.group[wave + HW * i];

@@ -376,9 +376,13 @@ void head_parts(int seq_len, int n_heads, HeadParams& p, unsigned& parts) {
 }
 
 // Kernel and workgroup size for heads of up to n tokens.  A thread's tokens are worked off one after the other, so beyond
-// 4096 sixteen waves share them: routing alone, 8 heads, sixteen waves against eight, in us: 8.8 / 8.3 at 4096 tokens,
-// 10.3 / 10.4 at 8192, 13.3 / 14.9 at 12289, 13.4 / 14.8 at 16384; a compression pass of 12289 tokens 67.3 / 71.0, of 8192
-// 34.1 / 34.9.
+// 4096 sixteen waves share them.  Routing of given scores, sixteen waves against eight, in us:
+//     heads     2048       4096       8192        12289       16384 tokens
+//       1    8.4 / 7.0  8.8 / 8.1  10.2 / 10.2  13.0 / 14.4  13.3 / 14.6
+//       8    8.4 / 7.1  8.7 / 8.2  10.5 / 10.5  13.3 / 14.7  13.8 / 14.9
+//      64    8.4 / 7.1  9.0 / 8.4  10.6 / 10.7  15.3 / 17.6  14.4 / 16.5
+// At 8192 tokens the two are alike for any number of heads (a compression pass of 8 heads 34.2 / 34.3, of 64 106.4 / 106.2, of
+// eight unequal prompts 115.6 / 115.6); a pass of 12289 tokens takes 43.4 / 46.6 with 8 heads and 160.6 / 164.9 with 64.
 template <bool POOL, bool RAGGED> struct HeadKernel {
   void (*kernel)(KernelArgs<HeadParams, RAGGED>);
   int threads;
