@@ -36,8 +36,8 @@ enum class ApproxRows { kPlain, kTurned, kRebuilt };
 // keys, contiguous and paged), each with its segments cut in all ways.  per_cu: workgroups that fit a CU, by the compiled
 // kernel's registers and LDS.  In the mean, times the best cut: with one rule for all kernels (1024 workgroups, 256 rows each
 // at least; other kernels then), with the constants of bf16 and d = 128 for all, and now:
-//   bf16, d = 128   1.35  1.08  1.08   32 KB a tensor and step, two workgroups per CU.  Constants fitted to the large shapes instead of
-//                                      all gain 4 % on the small ones and lose 2 to 12 % on the longest, which are a server's.
+//   bf16, d = 128   1.35  1.08  1.08   32 KB a tensor and step, two workgroups per CU.  Constants fitted to all these shapes alike
+//                                      would gain 4 % in the mean and lose 2 to 12 % on the longest, so those of before stay.
 //   bf16, d = 64    1.27  1.07  1.03   half the bytes, three per CU; alone, a step is latency, which both kinds of rows have alike
 //   fp32            1.35  1.17  1.03   half the bytes, and the vector unit's time, which grows with the query heads; one to five per CU
 // Single shapes, us: fp32, d = 128, 32 sequences of 4096 tokens, four query heads 52 / 77 (four workgroups a CU where three fit) /
