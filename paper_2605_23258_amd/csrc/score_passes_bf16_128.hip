@@ -4,8 +4,8 @@
 
 namespace vec {
 
-template int launch_passes<bf16_t, 128, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
-template int launch_passes<bf16_t, 128, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
+template int launch_passes<bf16_t, 128, false>(PassArgs<false>&, const PassLaunch&, hipStream_t);
+template int launch_passes<bf16_t, 128, true>(PassArgs<true>&, const PassLaunch&, hipStream_t);
 template int launch_probe<bf16_t, 128>(const PassLaunch&, hipStream_t);
 
 }  // namespace vec

@@ -4,7 +4,7 @@
 
 namespace vec {
 
-template int launch_passes<float, 128, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
-template int launch_passes<float, 128, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
+template int launch_passes<float, 128, false>(PassArgs<false>&, const PassLaunch&, hipStream_t);
+template int launch_passes<float, 128, true>(PassArgs<true>&, const PassLaunch&, hipStream_t);
 
 }  // namespace vec

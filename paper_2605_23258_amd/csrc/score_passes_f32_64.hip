@@ -4,7 +4,7 @@
 
 namespace vec {
 
-template int launch_passes<float, 64, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
-template int launch_passes<float, 64, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
+template int launch_passes<float, 64, false>(PassArgs<false>&, const PassLaunch&, hipStream_t);
+template int launch_passes<float, 64, true>(PassArgs<true>&, const PassLaunch&, hipStream_t);
 
 }  // namespace vec

@@ -129,6 +129,7 @@ static int prepare_passes(const SeqStack* stack, const vector_shape& s, const ve
   if (L.use_rope) L.rp = *rope;
   L.grid1 = dim3((p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg, s.n_kv_heads);
   L.grid2 = dim3((s.seq_len + p.tokens_per_wg - 1) / p.tokens_per_wg, s.n_kv_heads);
+  p.wgs1 = (int)L.grid1.x;
   p.range_stride = (int)L.grid2.x;
   return VECTOR_OK;
 }
@@ -143,7 +144,8 @@ static int run_passes(const SeqStack* stack, const vector_shape& s, const vector
   if (mass_out) *mass_out = L.pp.mass;
   if (n_prefix_out) *n_prefix_out = L.pp.n_prefix;
   if (n_range_out) *n_range_out = (int)L.grid2.x;
-  return launch_passes<T, D, false>(KernelArgs<PassParams, false>{L.pp}, L, L.grid1, L.grid2, stream);
+  PassArgs<false> args = {{L.pp}};
+  return launch_passes<T, D, false>(args, L, stream);
 }
 
 // Query heads per pair of passes: all G of a KV head when their G * w rows fit the kernels, else the largest
@@ -164,7 +166,10 @@ static int run_score_residual_ragged(const vector_shape& s, const RaggedSeq* seq
   if (count < 1 || count > kMaxRaggedSeqs) return VECTOR_ERR_ARG;
   PassParams host[kMaxRaggedSeqs];
   PassLaunch first;
-  unsigned g1 = 0, g2 = 0;
+  unsigned g1 = 0, g2 = 0;                      // workgroups of the launches
+  uint16_t first1[kMaxRaggedSeqs], first2[kMaxRaggedSeqs];
+  std::fill(first1, first1 + kMaxRaggedSeqs, 0xffff);
+  std::fill(first2, first2 + kMaxRaggedSeqs, 0xffff);
   int lens[kMaxRaggedSeqs];
   for (int b = 0; b < count; ++b) lens[b] = seqs[b].shape.seq_len;
   const int plan_wg = tokens_per_workgroup(lens, count, s.n_kv_heads, Stream<T, D>::kTokens);
@@ -180,15 +185,21 @@ static int run_score_residual_ragged(const vector_shape& s, const RaggedSeq* seq
     L.pp.pos_base = seqs[b].pos_base;
     host[b] = L.pp;
     if (b == 0) first = L;
-    if (L.grid1.x > g1) g1 = L.grid1.x;
-    if (L.grid2.x > g2) g2 = L.grid2.x;
+    first1[b] = (uint16_t)g1;
+    first2[b] = (uint16_t)g2;
+    g1 += L.grid1.x * s.n_kv_heads;
+    g2 += L.grid2.x * s.n_kv_heads;
+    if (std::max(g1, g2) > 0xffff) return VECTOR_ERR_SHAPE;      // cannot be: about 1024 are planned, or one per head, and a part has fewer heads
   }
   unsigned char* t8 = reinterpret_cast<unsigned char*>(tables);
-  KernelArgs<PassParams, true> args;
+  PassArgs<true> args;
   int rc = ragged_args(host, count, s.n_kv_heads, t8, stream, args);
   if (rc != VECTOR_OK) return rc;
-  const unsigned heads = (unsigned)count * s.n_kv_heads;
-  if ((rc = launch_passes<T, D, true>(args, first, dim3(g1, heads), dim3(g2, heads), stream)) != VECTOR_OK) return rc;
+  first.grid1 = dim3(g1);
+  first.grid2 = dim3(g2);
+  std::copy(first1, first1 + kMaxRaggedSeqs, first.first1);
+  std::copy(first2, first2 + kMaxRaggedSeqs, first.first2);
+  if ((rc = launch_passes<T, D, true>(args, first, stream)) != VECTOR_OK) return rc;
   if (leave_mass) return VECTOR_OK;
   // pooling + score-key buckets of every sequence
   PoolSeq pool[kMaxRaggedSeqs];

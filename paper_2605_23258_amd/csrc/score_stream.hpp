@@ -17,6 +17,7 @@
 // the row instead (the lane fetches the piece that belongs in its slot), which keeps 16 rows read at one
 // piece in 16 different banks.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -53,11 +54,11 @@ struct PassParams {
                         // l = log2(m) - log_ref; the routing's bucket launch turns them into the head's
                         // typical score range
   int range_stride;     // entries of `range` per head (the second pass's workgroups per head)
+  int wgs1;             // the first pass's workgroups per head
   int64_t pos_base;     // post-RoPE keys with a position array: token t of this head is at positions[pos_base + t]
                         // (+ the sequence's share when sequences are stacked)
-  // Several sequences of different lengths in one launch (template flag RAGGED, see KernelArgs): launch head hv
-  // belongs to sequence hv / seq_hps and is its head hv % seq_hps, and a workgroup whose chunk index lies beyond
-  // its sequence's chunks leaves at once.
+  // Several sequences of different lengths in one launch (template flag RAGGED, see PassArgs): a workgroup takes its
+  // sequence's block.
   const PassParams* seq_table;     // the sequences' parameter blocks, where they are too many for kernel arguments
   int seq_hps;
   const float* lse;     // null, or the log-sum-exp (natural log, logits scaled by 1/sqrt(d)) of every query row,
@@ -65,6 +66,38 @@ struct PassParams {
   float log_ref;        // log2 of the mean mass of a prefix column, -log2(n_prefix): keeps l small
   int repeat;           // probe kernels only: times each tile's arithmetic is run on the same operands
 };
+
+// The first argument of both passes.  RAGGED: the launch has just the workgroups that the sequences need, sequence after
+// sequence, head after head, chunk after chunk; first[b] is where sequence b's start (0xffff beyond the sequences).
+template <bool RAGGED> struct PassArgs : KernelArgs<PassParams, RAGGED> {};
+template <> struct PassArgs<true> : KernelArgs<PassParams, true> { uint16_t first[kMaxRaggedSeqs]; };
+static_assert(sizeof(PassArgs<true>) == sizeof(KernelArgs<PassParams, true>) + sizeof(uint16_t) * kMaxRaggedSeqs, "take_chunk reads first[] from there");
+
+// Which chunk of which head this workgroup takes.  RAGGED: every XCD takes a run of the launch's workgroups, so a head's
+// chunks share an L2, and each XCD and, inside it, each group of CUs (an XCD deals its workgroups out to its four in
+// turn) gets as many as the next.  A grid of the longest sequence's chunks for every head, whose surplus
+// workgroups left at once, was dealt out with that surplus: some groups of CUs had more than one workgroup per CU that
+// stayed, and started the second when the first had finished (eight prompts of 2048 to 8192 tokens, 8 heads: passes of 38 and 50 us, now 31 and 40).
+template <bool RAGGED>
+__device__ __forceinline__ void take_chunk(PassParams& p, int& wg, int& h, bool first_pass) {
+  if constexpr (RAGGED) {
+    const int total = gridDim.x, x = blockIdx.x % kXcds, share = total / kXcds;
+    const int at = x * share + min(x, total % kXcds) + (int)blockIdx.x / kXcds;
+    typedef const __attribute__((address_space(4))) unsigned char* bytes;
+    const bytes args = (bytes)__builtin_amdgcn_kernarg_segment_ptr();
+    const int first = *(const __attribute__((address_space(4))) uint16_t*)(args + sizeof(KernelArgs<PassParams, true>) + 2 * (threadIdx.x & 63));
+    static_assert(kMaxRaggedSeqs == kWave, "a lane per sequence");
+    const int seq = (int)__popcll(__ballot(first <= at)) - 1;
+    const int r = at - __builtin_amdgcn_readlane(first, seq);
+    const bytes table = p.seq_table ? (bytes)(const unsigned char*)p.seq_table : args + sizeof(PassParams);
+    __builtin_memcpy(&p, (const unsigned char*)(table + (size_t)seq * sizeof(PassParams)), sizeof(PassParams));
+    const int per_head = first_pass ? p.wgs1 : p.range_stride;
+    h = r / per_head;
+    wg = r - h * per_head;
+  } else {
+    xcd_chunk_head(wg, h);
+  }
+}
 
 // element offset of a launch head's keys (or values), and the KV head whose W it uses
 __device__ __forceinline__ int64_t head_offset(const PassParams& p, int h, int64_t seq_stride, int64_t head_stride) {
@@ -222,11 +255,10 @@ template <typename T, int D> struct KeyOperands {
 constexpr int kStages1 = 4;
 
 template <typename T, int D, int NRB, bool RAGGED>
-__global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(KernelArgs<PassParams, RAGGED> args) {
+__global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassArgs<RAGGED> args) {
   PassParams p = args.p;
   int wg, h;
-  xcd_chunk_head(wg, h);
-  take_sequence<RAGGED>(p, h);
+  take_chunk<RAGGED>(p, wg, h, true);
   using S = Stream<T, D>;
   using WW = WaveWork<T, D, NRB>;
   constexpr int NC = S::NC, U = WW::U, PH = WW::PH;
@@ -541,11 +573,10 @@ __device__ __forceinline__ float add_halves(float x) {
 // with memory out of the picture.  ROPE: the keys are cached after rotary position embedding; the
 // residual un-rotates them (the scores use them as cached).
 template <typename T, int D, int NRB, bool MASS, bool RES, bool ROPE, bool RAGGED, bool PROBE = false>
-__global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(KernelArgs<PassParams, RAGGED> args, RopeParams rp) {
+__global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<RAGGED> args, RopeParams rp) {
   PassParams p = args.p;
   int wg, h;
-  xcd_chunk_head(wg, h);
-  take_sequence<RAGGED>(p, h);
+  take_chunk<RAGGED>(p, wg, h, false);
   using S = Stream<T, D>;
   using WW = WaveWork<T, D, NRB>;
   using L = Pass2Lds<T, D, NRB, MASS, RES, ROPE>;
@@ -1040,17 +1071,20 @@ struct PassLaunch {
   PassParams pp;
   int units;                 // 32-row units of query rows the kernels are built for: 4, 8 or 16
   dim3 grid1, grid2;
+  uint16_t first1[kMaxRaggedSeqs], first2[kMaxRaggedSeqs];      // PassArgs::first of the two launches
   bool do_mass, do_res, use_rope;
   RopeParams rp;
 };
 
 template <typename T, int D, int NRB, bool RAGGED>
-int launch_passes_units(const KernelArgs<PassParams, RAGGED>& a, const PassLaunch& L, dim3 grid1, dim3 grid2, hipStream_t stream) {
-  using Args = KernelArgs<PassParams, RAGGED>;
+int launch_passes_units(PassArgs<RAGGED>& a, const PassLaunch& L, hipStream_t stream) {
+  using Args = PassArgs<RAGGED>;
+  const dim3 grid1 = L.grid1, grid2 = L.grid2;
   if (L.do_mass && !L.pp.lse) {               // pass 1; not needed when the caller brings the rows' log-sum-exp
     constexpr size_t lds = kStages1 * Stream<T, D>::kTileBytes + kStreamWaves * 32 * sizeof(float2);
     auto k1 = score_stats_kernel<T, D, NRB, RAGGED>;
     VEC_HIP(set_max_lds(reinterpret_cast<const void*>(k1), lds));
+    if constexpr (RAGGED) std::copy(L.first1, L.first1 + kMaxRaggedSeqs, a.first);
     VEC_LAUNCH(K_SCORE_STATS, k1, grid1, dim3(kStreamThreads), lds, stream, a);
   }
   void (*k2)(Args, RopeParams);
@@ -1068,6 +1102,7 @@ int launch_passes_units(const KernelArgs<PassParams, RAGGED>& a, const PassLaunc
     lds = L.use_rope ? Pass2Lds<T, D, 4, false, true, true>::kTotal : Pass2Lds<T, D, 4, false, true, false>::kTotal;
   }
   VEC_HIP(set_max_lds(reinterpret_cast<const void*>(k2), lds));
+  if constexpr (RAGGED) std::copy(L.first2, L.first2 + kMaxRaggedSeqs, a.first);
   VEC_LAUNCH(K_MASS_RESIDUAL, k2, grid2, dim3(kStreamThreads), lds, stream, a, L.rp);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
@@ -1077,11 +1112,11 @@ int launch_passes_units(const KernelArgs<PassParams, RAGGED>& a, const PassLaunc
 template <typename T, int D> constexpr int kMaxUnits = (sizeof(T) == 4 && D == 128) ? 8 : 16;
 
 template <typename T, int D, bool RAGGED>
-int launch_passes(const KernelArgs<PassParams, RAGGED>& a, const PassLaunch& L, dim3 grid1, dim3 grid2, hipStream_t stream) {
-  if (L.units == 4 || !L.do_mass) return launch_passes_units<T, D, 4, RAGGED>(a, L, grid1, grid2, stream);
-  if (L.units == 8) return launch_passes_units<T, D, 8, RAGGED>(a, L, grid1, grid2, stream);
+int launch_passes(PassArgs<RAGGED>& a, const PassLaunch& L, hipStream_t stream) {
+  if (L.units == 4 || !L.do_mass) return launch_passes_units<T, D, 4, RAGGED>(a, L, stream);
+  if (L.units == 8) return launch_passes_units<T, D, 8, RAGGED>(a, L, stream);
   if constexpr (kMaxUnits<T, D> == 16) {
-    if (L.units == 16) return launch_passes_units<T, D, 16, RAGGED>(a, L, grid1, grid2, stream);
+    if (L.units == 16) return launch_passes_units<T, D, 16, RAGGED>(a, L, stream);
   }
   return VECTOR_ERR_SHAPE;
 }
@@ -1091,20 +1126,20 @@ int launch_probe(const PassLaunch& L, hipStream_t stream) {
   auto k2 = mass_residual_kernel<T, D, 4, false, true, false, false, true>;
   constexpr size_t lds = Pass2Lds<T, D, 4, false, true, false>::kTotal;
   VEC_HIP(set_max_lds(reinterpret_cast<const void*>(k2), lds));
-  VEC_LAUNCH(K_MASS_RESIDUAL, k2, L.grid2, dim3(kStreamThreads), lds, stream, KernelArgs<PassParams, false>{L.pp}, L.rp);
+  VEC_LAUNCH(K_MASS_RESIDUAL, k2, L.grid2, dim3(kStreamThreads), lds, stream, (PassArgs<false>{{L.pp}}), L.rp);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
 
 #ifndef VEC_DEFINE_PASSES
-extern template int launch_passes<bf16_t, 128, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
-extern template int launch_passes<bf16_t, 128, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
-extern template int launch_passes<bf16_t, 64, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
-extern template int launch_passes<bf16_t, 64, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
-extern template int launch_passes<float, 128, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
-extern template int launch_passes<float, 128, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
-extern template int launch_passes<float, 64, false>(const KernelArgs<PassParams, false>&, const PassLaunch&, dim3, dim3, hipStream_t);
-extern template int launch_passes<float, 64, true>(const KernelArgs<PassParams, true>&, const PassLaunch&, dim3, dim3, hipStream_t);
+extern template int launch_passes<bf16_t, 128, false>(PassArgs<false>&, const PassLaunch&, hipStream_t);
+extern template int launch_passes<bf16_t, 128, true>(PassArgs<true>&, const PassLaunch&, hipStream_t);
+extern template int launch_passes<bf16_t, 64, false>(PassArgs<false>&, const PassLaunch&, hipStream_t);
+extern template int launch_passes<bf16_t, 64, true>(PassArgs<true>&, const PassLaunch&, hipStream_t);
+extern template int launch_passes<float, 128, false>(PassArgs<false>&, const PassLaunch&, hipStream_t);
+extern template int launch_passes<float, 128, true>(PassArgs<true>&, const PassLaunch&, hipStream_t);
+extern template int launch_passes<float, 64, false>(PassArgs<false>&, const PassLaunch&, hipStream_t);
+extern template int launch_passes<float, 64, true>(PassArgs<true>&, const PassLaunch&, hipStream_t);
 extern template int launch_probe<bf16_t, 128>(const PassLaunch&, hipStream_t);
 extern template int launch_probe<bf16_t, 64>(const PassLaunch&, hipStream_t);
 #endif
