@@ -21,7 +21,7 @@
 //   decode_split_kernel   : fp32 caches: the same split with vector-ALU dot products (partial
 //                           dot product per lane, rotate-add across the lanes of a row,
 //                           online softmax per lane group).
-//   decode_combine_mfma_kernel (bf16), decode_combine_kernel (fp32): merge the splits, apply W to z, normalise, store.
+//   decode_combine_kernel, decode_combine_few_kernel : merge the splits, apply W to z, normalise, store.
 #include <type_traits>
 
 #include "common.hpp"
@@ -46,7 +46,7 @@ struct DecodeParams {
   const int32_t* block_table;
   int block_shift, blocks_per_seq;
   void* out;
-  float* part;            // [B, Hkv, S, 2*G + G*D] floats: m[G], l[G], acc[G][D]
+  float* part;            // [B, Hkv, S, 2*G + G*D] floats: (m, l)[G], acc[G][D]
   int B, Hq, Hkv, cap_retain, n_approx;
   int splits_ret, splits_apx;   // workgroups per (sequence, head) on each segment
   int64_t w_sh;           // element stride between per-head W
@@ -355,8 +355,8 @@ __global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeP
       const float mw = ml_lds[wv][0][g];
       if (mw != -INFINITY) l += ml_lds[wv][1][g] * fast_exp2(mw - m);
     }
-    out[g] = m;
-    out[G + g] = l;
+    out[2 * g] = m;
+    out[2 * g + 1] = l;
   }
 }
 
@@ -759,83 +759,115 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
     }
     *reinterpret_cast<f32x4_u*>(out + 2 * G + i) = a;
     if (j == 0) {
-      out[g] = m;
-      out[G + g] = l;
+      out[2 * g] = m;
+      out[2 * g + 1] = l;
     }
   }
 }
 
-// Merge of the splits for bf16 caches, one workgroup per (sequence, KV head): reference and sum of every query row,
-// the weighted sums of the splits, z W, the division.  What bounds it is load instructions (16 cycles of the CU's
-// address unit each) and one trip to memory: a thread takes four neighbouring elements of every SG-th split with
-// 16-byte loads, the splits' references and sums go through LDS.  z W runs on the matrix cores: z in three bf16 parts
-// (its 24 bits, eight at a time, cut and not rounded: above bf16's largest number a rounded first part would be infinite, and
-// the second minus infinity; of an infinite z the first part is all), eight query rows by three parts on the M side, W's
-// columns by the transposing LDS read.
-// Element by element, with z W on the vector unit, a step of one sequence (four query heads, 11 splits) took 14.8 us, with
-// this merge 11.9; with eight query heads per KV head (12 splits) 46.9 and 41.1.
-template <int D, int G> struct CombineLds {
+// LDS of the merge, bytes
+template <typename T, int D, int G> struct CombineLds {
+  static constexpr bool kMfma = sizeof(T) == 2;
   static constexpr int kQuads = G * D / 4;
-  static constexpr int kSide = kQuads >= 256 ? 1 : 256 / kQuads;         // splits taken side by side
-  static constexpr int kRounds = (kQuads + 255) / 256;
+  static constexpr int kSide = kQuads >= DT_ ? 1 : DT_ / kQuads;         // splits taken side by side
+  static constexpr int kRounds = (kQuads + DT_ - 1) / DT_;
   static constexpr int kBlocks = (G + 7) / 8;                            // of eight query rows
   static constexpr int kStride = D * 2 + 16;                             // bytes of a row of W, and of z's parts
-  static constexpr int kMl = kMaxSplits * 2 * G * 4, kParts = kBlocks * 32 * kStride;      // not at the same time
-  static constexpr int kSums = (kMl > kParts ? kMl : kParts);            // [2: retained, approximated][kSide][G * D]
+  static constexpr int kWeights = kMaxSplits * G * 4, kParts = kMfma ? kBlocks * 32 * kStride : DW * G * D * 4;      // not at the same time
+  static constexpr int kSums = (kWeights > kParts ? kWeights : kParts);            // [2: retained, approximated][kSide][G * D]
   static constexpr int kW = kSums + 2 * kSide * G * D * 4;
-  static constexpr int kInv = kW + D * kStride;
+  static constexpr int kInv = kW + (kMfma ? D * kStride : 0);
   static constexpr int kTotal = kInv + G * 4;
 };
-template <int D, int G>
-__global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p) {
-  using T = bf16_t;
-  using L = CombineLds<D, G>;
-  constexpr int PSZ = 2 * G + G * D, WL = D * D / 8 / 256, kFlight = 8;
+
+// Merge of the splits, one workgroup per (sequence, KV head): reference and sum of every query row, the weighted sums of the
+// splits, z W, the division.  What bounds it is a chain: arguments, one trip to memory, weights, sums, z W.  Every load of the
+// first splits is out before the first is waited for.  The splits' weights: a wave takes a query row, lane s its split s, so that the
+// row's reference and sum are two reductions over the wave; a thread then takes four neighbouring elements of every kSide-th
+// split with 16-byte loads, and the weights from LDS.
+// bf16: z W runs on the matrix cores: z in three bf16 parts
+// (its 24 bits, eight at a time, cut and not rounded: above bf16's largest number a rounded first part would be infinite, and
+// the second minus infinity; of an infinite z the first part is all), eight query rows by three parts on the M side, W's
+// columns by the transposing LDS read.  fp32: on the vector unit, a thread with 16 bytes of some rows of W.
+// One sequence of 8192 tokens, 8 KV heads, 17 splits: from the launch's start 0.9 us to the loads, 0.5 to the weights, 1.0 to the
+// sums (W arrives), 0.3, and 0.8 for z W; with every thread looping over all splits' references the second and third took 2.2
+// (a step 11.7 us, now 11.2).  In the split launch's last workgroup of a (sequence, KV head) instead of a launch of its
+// own it is no faster: the acknowledgement of the written splits and the count of them take 1 us, as a launch does, and keep every
+// workgroup on its CU that much longer (11.6 / 12.1, and with 16 sequences of 32768 tokens 70.6 / 72.8).
+template <typename T, int D, int G>
+__global__ __launch_bounds__(DT_) void decode_combine_kernel(DecodeParams p) {
+  using L = CombineLds<T, D, G>;
+  constexpr int kFlight = 8, PSZ = 2 * G + G * D;
+  constexpr int E = Elem<T>::kPerChunk;    // elements of W per 16-byte load
+  constexpr int CG = D / E;                // fp32: thread groups along a row of W
+  constexpr int RG = DT_ / CG;             // thread groups along its rows (the contraction index)
+  constexpr int WL = D * D / E / DT_;      // pieces of W per thread
+  constexpr int RW = (G + DW - 1) / DW;    // query rows per wave
+  static_assert(kMaxSplits <= kWave, "a lane per split");
   extern __shared__ __align__(16) unsigned char dec_lds[];
-  float* ml = reinterpret_cast<float*>(dec_lds);                         // [splits][2 G]
-  float* sums = reinterpret_cast<float*>(dec_lds + L::kSums);
-  float* inv = reinterpret_cast<float*>(dec_lds + L::kInv);
+  unsigned char* lds = dec_lds;
+  float* weight = reinterpret_cast<float*>(lds);                         // [G][splits]
+  float* sums = reinterpret_cast<float*>(lds + L::kSums);
+  float* inv = reinterpret_cast<float*>(lds + L::kInv);
   const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const size_t bh = (size_t)b * p.Hkv + h;
   const int n_splits = p.splits_ret + p.splits_apx, n_ret = p.literal ? n_splits : p.splits_ret;      // literal partials are values already
   const float* part = p.part + bh * n_splits * PSZ;
-  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l31 = lane & 31;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5, l31 = lane & 31;
   const bool use_w = p.n_approx > 0 && !p.literal;
 
+  // the step's own token is now a row of the cache (the split launch has finished): one thread per
+  // sequence makes it live, unless the block was full
+  const bool advances = p.k_new && h == 0 && tid == 0;
+  int live = 0, cap = p.cap_retain;
+  if (advances) {
+    live = p.len_retain[b];
+    if (p.cap_retain_seq) cap = max(p.cap_retain_seq[b], 0);
+  }
   // this thread's elements, and its first splits
   const int quad = tid % L::kQuads;
   int side = L::kSide > 1 ? tid / L::kQuads : 0;       // of a whole wave the same where it can be: then which split counts where is a scalar question
   if constexpr (L::kQuads % kWave == 0) side = __builtin_amdgcn_readfirstlane(side);
-  const bool has_quad = side < L::kSide;
+  const int sides = min(L::kSide, n_splits);
+  const bool has_quad = side < sides;
   f32x4 x0[kFlight];
-  auto load_splits = [&](int round, int s0, f32x4* x) {
-    const int at = min(round * 256 + quad, L::kQuads - 1) * 4;
+  auto load_splits = [&](int round, int s0, f32x4* x) VEC_INLINE {
+    const int at = min(round * DT_ + quad, L::kQuads - 1) * 4;
 #pragma unroll
-    for (int u = 0; u < kFlight; ++u) x[u] = *reinterpret_cast<const f32x4_u*>(part + (size_t)min(s0 + u * L::kSide, n_splits - 1) * PSZ + 2 * G + at);
+    for (int u = 0; u < kFlight; ++u) {
+      x[u] = *reinterpret_cast<const f32x4_u*>(part + (size_t)min(s0 + u * L::kSide, n_splits - 1) * PSZ + 2 * G + at);
+    }
   };
-  for (int i = tid; i < n_splits * 2 * G; i += 256) ml[i] = part[(size_t)(i / (2 * G)) * PSZ + i % (2 * G)];
-  load_splits(0, min(side, n_splits - 1), x0);
   uint4 wraw[WL];
   const T* Wh = reinterpret_cast<const T*>(p.W) + (int64_t)h * p.w_sh;
-  if (use_w) {
+  const int cg = tid % CG, rg = tid / CG;
+  auto load_w = [&]() VEC_INLINE {
+    if (use_w) {
 #pragma unroll
-    for (int i = 0; i < WL; ++i) wraw[i] = load_chunk(Wh + (size_t)(i * 256 + tid) * 8);
+      for (int i = 0; i < WL; ++i) wraw[i] = load_chunk(L::kMfma ? Wh + (size_t)(i * DT_ + tid) * 8 : Wh + (size_t)(rg * WL + i) * D + cg * E);
+    }
+  };
+  if (!L::kMfma) load_w();                       // the larger part of what is read
+  float2 ml[RW];
+#pragma unroll
+  for (int i = 0; i < RW; ++i) ml[i] = *reinterpret_cast<const float2*>(part + (size_t)min(lane, n_splits - 1) * PSZ + 2 * min(wave + i * DW, G - 1));
+  load_splits(0, min(side, n_splits - 1), x0);
+  if (L::kMfma) load_w();
+#pragma unroll
+  for (int i = 0; i < RW; ++i) {
+    const int g = wave + i * DW;
+    if (G % DW == 0 || g < G) {                  // uniform
+      const float m = lane < n_splits ? ml[i].x : -INFINITY, top = wave_max_dpp(m);
+      const float w = fast_exp2(m - (top == -INFINITY ? 0.f : top)), l = wave_sum_dpp(lane < n_splits ? ml[i].y * w : 0.f);
+      if (lane < n_splits) weight[g * n_splits + lane] = w;
+      if (lane == 0) inv[g] = l > 0.f ? 1.f / l : 0.f;
+    }
   }
-  // the step's own token is now a row of the cache (the split launch has finished): one thread per
-  // sequence makes it live, unless the block was full
-  if (p.k_new && h == 0 && tid == 0) {
-    const int cap = p.cap_retain_seq ? max(p.cap_retain_seq[b], 0) : p.cap_retain;
-    int* len = const_cast<int*>(p.len_retain) + b;
-    *len = min(min(max(*len, 0), cap) + 1, cap);
-  }
+  if (advances) const_cast<int*>(p.len_retain)[b] = min(min(max(live, 0), cap) + 1, cap);
   __syncthreads();
 #pragma unroll
   for (int round = 0; round < L::kRounds; ++round) {
-    const int at = round * 256 + quad, g = min(at * 4, G * D - 1) / D;
-    float m = -INFINITY, l = 0.f;
-#pragma unroll 4
-    for (int s = 0; s < n_splits; ++s) m = fmaxf(m, ml[s * 2 * G + g]);
-    const float m_safe = m == -INFINITY ? 0.f : m;
+    const int at = round * DT_ + quad, g = min(at * 4, G * D - 1) / D;
     f32x4 av = {0.f, 0.f, 0.f, 0.f}, az = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = side; s0 < n_splits; s0 += kFlight * L::kSide) {
       f32x4 x[kFlight];
@@ -849,7 +881,7 @@ __global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p
       for (int u = 0; u < kFlight; ++u) {
         const int s = s0 + u * L::kSide;
         if (s < n_splits) {
-          const float sc = fast_exp2(ml[s * 2 * G + g] - m_safe);
+          const float sc = weight[g * n_splits + s];
           if (s < n_ret) {                       // not by weights of 0: a share may be infinite
 #pragma unroll
             for (int e = 0; e < 4; ++e) av[e] = fmaf(x[u][e], sc, av[e]);
@@ -863,36 +895,32 @@ __global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p
     if (has_quad && at < L::kQuads) {
       *reinterpret_cast<f32x4*>(sums + side * G * D + at * 4) = av;
       *reinterpret_cast<f32x4*>(sums + (L::kSide + side) * G * D + at * 4) = az;
-      if (side == 0 && at * 4 % D == 0) {
-#pragma unroll 4
-        for (int s = 0; s < n_splits; ++s) l = fmaf(ml[s * 2 * G + G + g], fast_exp2(ml[s * 2 * G + g] - m_safe), l);
-        inv[g] = l > 0.f ? 1.f / l : 0.f;
-      }
     }
   }
-  unsigned char* w_tile = dec_lds + L::kW;
-  if (use_w) {
+  unsigned char* w_tile = lds + L::kW;
+  if (L::kMfma && use_w) {
 #pragma unroll
     for (int i = 0; i < WL; ++i) {
-      const int piece = i * 256 + tid;
+      const int piece = i * DT_ + tid;
       *reinterpret_cast<uint4*>(w_tile + piece / (D / 8) * L::kStride + piece % (D / 8) * 16) = wraw[i];
     }
   }
   __syncthreads();
-  // z, and its parts: part q of query row g in row (g / 8) * 32 + q * 8 + g % 8; inside 16 contraction indices 8 a + 4 h + c
+  // z, and (bf16) its parts: part q of query row g in row (g / 8) * 32 + q * 8 + g % 8; inside 16 contraction indices 8 a + 4 h + c
   // in the order 8 h + 4 a + c, which is how the transposing read hands out W's rows
-  for (int i = tid * 4; i < G * D; i += 1024) {
+  for (int i = tid * 4; i < G * D; i += DT_ * 4) {
     const int g = i / D, j = i % D;
     f32x4 v = {0.f, 0.f, 0.f, 0.f}, z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < L::kSide; ++q) {
+    for (int q = 0; q < sides; ++q) {
       v += *reinterpret_cast<const f32x4*>(sums + q * G * D + i);
       z += *reinterpret_cast<const f32x4*>(sums + (L::kSide + q) * G * D + i);
     }
     if (L::kSide > 1) *reinterpret_cast<f32x4*>(sums + i) = v;
-    if (use_w) {
+    if (!L::kMfma) {
+      if (L::kSide > 1) *reinterpret_cast<f32x4*>(sums + L::kSide * G * D + i) = z;
+    } else if (use_w) {
       const int within = j & 15, pos = (j & ~15) + 8 * ((within >> 2) & 1) + 4 * (within >> 3);
-      unsigned char* row = dec_lds + ((g / 8) * 32 + g % 8) * L::kStride + pos * 2;
+      unsigned char* row = lds + ((g / 8) * 32 + g % 8) * L::kStride + pos * 2;
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
         uint32_t top[4];
@@ -905,41 +933,92 @@ __global__ __launch_bounds__(256) void decode_combine_mfma_kernel(DecodeParams p
     }
   }
   __syncthreads();
-  if (wave * 32 >= D) return;
-  const int j = wave * 32 + l31;
-  const uint32_t w_at = lds_address(w_tile) + (uint32_t)((4 * half + (lane & 15) / 4) * L::kStride + (wave * 32 + ((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2);
+  if constexpr (L::kMfma) {
+    if (wave * 32 >= D) return;
+    const int j = wave * 32 + l31;
+    const uint32_t w_at = lds_address(w_tile) + (uint32_t)((4 * half + (lane & 15) / 4) * L::kStride + (wave * 32 + ((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2);
 #pragma unroll
-  for (int blk = 0; blk < L::kBlocks; ++blk) {
-    f32x16 acc;
+    for (int blk = 0; blk < L::kBlocks; ++blk) {
+      f32x16 acc;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+      if (use_w) {
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) {
+          typedef __attribute__((address_space(3))) s16x4 lds_quad;
+          const uint32_t at = w_at + (uint32_t)(16 * c * L::kStride);
+          const s16x4 b0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)at);
+          const s16x4 b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)(at + 8 * L::kStride));
+          const chunk_t a = *reinterpret_cast<const chunk_t*>(lds + (blk * 32 + min(l31, 23)) * L::kStride + (16 * c + 8 * half) * 2);
+          mma_chunk<T>(acc, a, __builtin_bit_cast(chunk_t, __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7)));
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int g = blk * 8 + half * 4 + i;
+        if (g < G) {
+          const float r = (sums[g * D + j] + (acc[i] + (acc[4 + i] + acc[8 + i]))) * inv[g];
+          const size_t at = ((size_t)b * p.Hq + (size_t)h * G + g) * D + j;
+          if (p.out_f32) reinterpret_cast<float*>(p.out)[at] = r;
+          else store_elem(reinterpret_cast<T*>(p.out) + at, r);
+        }
+      }
+    }
+  } else {
+    // partial products over the thread's rows of W, summed over the row groups of a wave by lane exchange, over the waves
+    // through LDS
+    static_assert(CG <= kWave && D % RG == 0 && WL == D / RG, "a wave holds whole row groups");
+    const float* z = sums + L::kSide * G * D;
+    float (*zw)[G][D] = reinterpret_cast<float (*)[G][D]>(lds);
+    float a[G][E];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int e = 0; e < E; ++e) a[g][e] = 0.f;
     if (use_w) {
 #pragma unroll
-      for (int c = 0; c < D / 16; ++c) {
-        typedef __attribute__((address_space(3))) s16x4 lds_quad;
-        const uint32_t at = w_at + (uint32_t)(16 * c * L::kStride);
-        const s16x4 b0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)at);
-        const s16x4 b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)(at + 8 * L::kStride));
-        const chunk_t a = *reinterpret_cast<const chunk_t*>(dec_lds + (blk * 32 + min(l31, 23)) * L::kStride + (16 * c + 8 * half) * 2);
-        mma_chunk<T>(acc, a, __builtin_bit_cast(chunk_t, __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7)));
+      for (int r = 0; r < WL; ++r) {
+        float wf[E];
+        Unpack16<T>::run(wraw[r], wf);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const float zg = z[g * D + rg * WL + r];
+#pragma unroll
+          for (int e = 0; e < E; ++e) a[g][e] = fmaf(zg, wf[e], a[g][e]);
+        }
       }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int g = blk * 8 + half * 4 + i;
-      if (g < G) {
-        const float r = (sums[g * D + j] + (acc[i] + (acc[4 + i] + acc[8 + i]))) * inv[g];
-        const size_t at = ((size_t)b * p.Hq + (size_t)h * G + g) * D + j;
-        if (p.out_f32) reinterpret_cast<float*>(p.out)[at] = r;
-        else store_elem(reinterpret_cast<T*>(p.out) + at, r);
-      }
+    for (int o = CG; o < kWave; o <<= 1)
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < E; ++e) a[g][e] += __shfl_xor(a[g][e], o, kWave);
+    if (lane < CG) {
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < E; ++e) zw[wave][g][cg * E + e] = a[g][e];
+    }
+    __syncthreads();
+    T* out = reinterpret_cast<T*>(p.out) + ((size_t)b * p.Hq + (size_t)h * G) * D;
+    for (int i = tid; i < G * D; i += DT_) {
+      const int g = i / D, j = i % D;
+      float sum = 0.f;
+#pragma unroll
+      for (int q = 0; q < DW; ++q) sum += zw[q][g][j];
+      out[i] = (sums[i] + sum) * inv[g];
     }
   }
 }
 
-// the same for fp32 caches, z W on the vector unit
+// The same for fp32 caches with few elements: two barriers less, every thread with its own weights.  A step, us, captured,
+// this / decode_combine_kernel:
+//   d = 64:  5 sequences of 1040 tokens, two query heads 7.3 / 8.0; 27 of 2052, four 29.1 / 29.5; one of 747, eight 12.3 / 12.6
+//   d = 128: 23 of 1386, one 9.4 / 10.1; 3 of 673, two 10.6 / 10.5; one of 1153, four 14.3 / 12.9; 4 of 3461, four 19.9 / 16.4;
+//            one of 2440, eight 28.1 / 24.4
 template <int D, int G>
-__global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
+__global__ __launch_bounds__(256) void decode_combine_few_kernel(DecodeParams p) {
   using T = float;
   constexpr int PSZ = 2 * G + G * D;
   constexpr int E = Elem<T>::kPerChunk;    // elements of W per 16-byte load
@@ -995,8 +1074,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
 #pragma unroll
           for (int e = 0; e < EB; ++e) {
             const int i = min((int)threadIdx.x + (e0 + e) * 256, G * D - 1), g = i / D;
-            ms[e][u] = at[g];
-            ls[e][u] = at[G + g];
+            ms[e][u] = at[2 * g];
+            ls[e][u] = at[2 * g + 1];
             xs[e][u] = at[2 * G + i];
           }
         }
@@ -1079,6 +1158,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
   }
 }
 
+template <typename T, int D, int G> constexpr bool kFewElements = sizeof(T) == 4 && (D == 64 ? G <= 8 : G <= 2);
+
 // Workgroups of a split kernel that fit a CU, asked for once per kernel.
 template <auto Kernel> int workgroups_per_cu(int lds) {
   static const int n = [&] {
@@ -1114,12 +1195,13 @@ int run_decode_layout(const vector_cache& c, DecodeParams& p, hipStream_t stream
     else rc = launch_split<decode_split_kernel<T, D, G, PAGED, false>, T, D, G>(c, p, 0, stream, rope);
   }
   if (rc != VECTOR_OK) return rc;
-  if constexpr (Elem<T>::kDtype == VECTOR_BF16) {
-    constexpr int lds = CombineLds<D, G>::kTotal;
-    VEC_HIP(set_max_lds(reinterpret_cast<const void*>(decode_combine_mfma_kernel<D, G>), lds));
-    VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_mfma_kernel<D, G>), dim3(c.n_kv_heads, c.batch), dim3(256), lds, stream, p);
+  const dim3 merge_grid(c.n_kv_heads, c.batch);
+  if constexpr (kFewElements<T, D, G>) {
+    VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_few_kernel<D, G>), merge_grid, dim3(DT_), 0, stream, p);
   } else {
-    VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_kernel<D, G>), dim3(c.n_kv_heads, c.batch), dim3(256), 0, stream, p);
+    constexpr int lds = CombineLds<T, D, G>::kTotal;
+    VEC_HIP(set_max_lds(reinterpret_cast<const void*>(decode_combine_kernel<T, D, G>), lds));
+    VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_kernel<T, D, G>), merge_grid, dim3(DT_), lds, stream, p);
   }
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
