@@ -10,6 +10,12 @@
 // With keys in registers and query rows in LDS instead, a wave's next keys can only be asked for after the last product
 // of the tile, and the staging (query rows, W^T two bytes at a time) takes 5 us per workgroup: the times in brackets
 // below.
+// Rotated keys: a tile's keys are un-rotated into LDS by all waves, and the residual's products on them are issued between the
+// next tile's sines and cosines, so that a tile needs one barrier; what bounds a tile is issue (vector work 1.3 us, 48 MFMAs a
+// SIMD that keep it back for 16 cycles each) and LDS (320 KB of accesses).  With a second barrier before the products, and
+// the values staged with the keys, 20011 tokens x 8 heads took 2 us more, and fp32 at d = 128, which spilled 150 registers,
+// 1.5 to 1.9 times as long (a pass of 2546 tokens, 8 heads, 83 us, now 44).  Tiles of half the size (more of them on their way, a
+// barrier for every 32 tokens): 2.9 us per 64 tokens instead of 2.4.
 // Bounds (averages of back-to-back passes): 32768 tokens x 8 heads, 256 query rows: 26 us (28) for pass 1 and 37 us (39)
 // for pass 2, instruction issue; 131072 tokens, 128 rows: 61 us (63) and 103 us (107), HBM at 4.4 and 5.3 TB/s;
 // 8192 tokens: 8.5 us (9) and 13 us (19), latency.
@@ -536,30 +542,38 @@ template <> struct SplitPack<float> {
   }
 };
 
-// LDS of pass 2: a ring of stages (keys, values, positions), the un-rotated keys of the tile at hand, the
-// partial column sums of the last tiles, the row biases.  Sums are added up and stored kBatch tiles at a
+// LDS of pass 2: a ring of stages (keys, values), the partial column sums of the last tiles, the row biases.
+// Rotated keys: a ring of keys and positions; the values' blocks of the tile at hand and of the one before, each wave's own;
+// the un-rotated keys of these two tiles.  Sums are added up and stored kBatch tiles at a
 // time, by two waves per tile: done tile by tile, the other waves waited for that one wave's chain of LDS
 // reads at every barrier (a third of the kernel's time).
 template <typename T, int D, int NRB, bool MASS, bool RES, bool ROPE> struct Pass2Lds {
   using S = Stream<T, D>;
   using WW = WaveWork<T, D, NRB>;
-  static constexpr int kPosBytes = ROPE ? kStreamWaves * 256 : 0;
-  static constexpr int kStageBytes = S::kTileBytes * (RES ? 2 : 1) + kPosBytes;
+  // bf16 rows of 64 dims fill the LDS with rotated keys and leave registers: biases are kept there, and pass through the place of
+  // the second tile's un-rotated keys
+  static constexpr bool kBiasRegs = WW::U == 1 || (ROPE && sizeof(T) == 2 && D == 64), kBiasInTurned = ROPE && sizeof(T) == 2 && D == 64;
+  static constexpr int kPosBytes = ROPE ? S::kTokens <= 64 ? 256 : 512 : 0;
+  static constexpr int kStageBytes = S::kTileBytes * (RES && !ROPE ? 2 : 1) + kPosBytes;
   static constexpr int kStages = ROPE ? 3 : 4;
-  static constexpr int kTurned = kStages * kStageBytes;
+  static constexpr int kValues = kStages * kStageBytes;                                  // [2][kStreamWaves] blocks of 32 rows by 32 dims
+  static constexpr int kBlockBytes = 32 * 32 * (int)sizeof(T), kValuesBytes = ROPE ? kStreamWaves * kBlockBytes : 0;
+  static constexpr int kTurned = kValues + 2 * kValuesBytes;                             // [2]
   static constexpr int kTurnedBytes = ROPE ? S::kTileBytes * (SplitPack<T>::kTwoParts ? 2 : 1) : 0;
   static constexpr int kMassStep = MASS ? S::kSub * WW::kEntries * 32 * 4 : 0;
   static constexpr int kResStep = RES ? S::kSub * S::JB * 32 * 4 : 0;
   static constexpr int kBiasBytes = MASS ? NRB * 32 * 4 : 0;
-  static constexpr int kTurns = kTurned + kTurnedBytes;                                  // [D / 2] float2: rotary frequencies (hi, lo)
+  static constexpr int kTurns = kTurned + 2 * kTurnedBytes;                              // [D / 2] float2: rotary frequencies (hi, lo)
   static constexpr int kMassSums = kTurns + (ROPE ? D / 2 * 8 : 0);                      // [kSlots][kSub][kEntries][32]
   static constexpr int kFree = (int)kMaxLdsBytes - kMassSums - kBiasBytes;
   // a batch is stored while the two tiles after it leave their sums
   static constexpr int kBatch = kFree >= 6 * (kMassStep + kResStep) ? 4 : kFree >= 4 * (kMassStep + kResStep) ? 2 : 1;
   static constexpr int kSlots = kBatch + 2;
-  static constexpr int kResSums = kMassSums + kSlots * kMassStep;                        // [kSlots][kSub][JB][32]
-  static constexpr int kBias = kResSums + kSlots * kResStep;
-  static constexpr int kTotal = kBias + kBiasBytes;
+  static constexpr int kResSlots = ROPE ? kBatch + 1 : kSlots;      // rotated keys: a tile's residuals come a step later, all at once
+  static constexpr int kResSums = kMassSums + kSlots * kMassStep;                        // [kResSlots][kSub][JB][32]
+  static constexpr int kEnd = kResSums + kResSlots * kResStep;
+  static constexpr int kBias = kBiasInTurned ? kTurned + kTurnedBytes : kEnd;
+  static constexpr int kTotal = kBiasInTurned ? kEnd : kEnd + kBiasBytes;
   static_assert(kTotal <= (int)kMaxLdsBytes, "LDS");
 };
 
@@ -598,20 +612,20 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   TileSource<T, D> keys, values;
   const int t_top = t_begin + (n_steps - 1) * S::kTokens;
   keys.init(reinterpret_cast<const T*>(p.k) + head_offset(p, h, p.k_sb, p.k_sh), p.k_st, t_top, -1, wave, lane);
-  if (RES) values.init(reinterpret_cast<const T*>(p.v) + head_offset(p, h, p.v_sb, p.v_sh), p.v_st, t_top, -1, wave, lane);
+  if (RES && !ROPE) values.init(reinterpret_cast<const T*>(p.v) + head_offset(p, h, p.v_sb, p.v_sh), p.v_st, t_top, -1, wave, lane);
   const int32_t* positions = nullptr;
   if (ROPE && rp.positions) positions = rp.positions + p.pos_base + (p.hps ? (int64_t)(h / p.hps) * p.n : 0);
-  constexpr int kPer = S::kLoads * (RES ? 2 : 1) + (ROPE ? 1 : 0);
+  constexpr int kPer = S::kLoads * (RES && !ROPE ? 2 : 1) + (ROPE ? 1 : 0);
   constexpr uint32_t kRing = kStages * L::kStageBytes;
   auto token0 = [&](int step) VEC_INLINE { return t_top - step * S::kTokens; };
   uint32_t at_fetch = 0;                         // ring position of the tile to be fetched next
   int t_fetch = t_top, to_fetch = n_steps;       // its first token, and the tiles still to be fetched
   auto fetch = [&]() VEC_INLINE {
     keys.load(smem0 + at_fetch, t_fetch, t_end);
-    if (RES) values.load(smem0 + at_fetch + S::kTileBytes, t_fetch, t_end);
-    if (ROPE) {        // wave w: positions of tokens 64 (w % 2) ..; without an array any 4 bytes keep the count of loads the same
-      const int t = min(t_fetch + (wave & 1) * 64 + lane, t_end - 1);
-      load_to_lds4(smem0 + at_fetch + 2 * S::kTileBytes + wave * 256,
+    if (RES && !ROPE) values.load(smem0 + at_fetch + S::kTileBytes, t_fetch, t_end);
+    if (ROPE) {        // positions of tokens 64 (wave % 2) .., from every wave alike; without an array any 4 bytes keep the count of loads the same
+      const int half_tile = S::kTokens <= 64 ? 0 : wave & 1, t = min(t_fetch + half_tile * 64 + lane, t_end - 1);
+      load_to_lds4(smem0 + at_fetch + S::kTileBytes + half_tile * 256,
                    positions ? reinterpret_cast<const void*>(positions + t) : reinterpret_cast<const void*>(p.q ? p.q : p.W));
     }
     at_fetch = at_fetch + L::kStageBytes == kRing ? 0 : at_fetch + L::kStageBytes;
@@ -638,9 +652,15 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // value row in a run.  bf16: W goes through the last stage of the ring (free until the first tile's
   // barrier) in 8 x 8 blocks turned round with v_perm; fp32: four dims of one column, a word at a time.
   constexpr bool kTurnW = RES && sizeof(T) == 2;
-  unsigned char* w_lds = smem + (kStages - 1) * L::kStageBytes;
+  unsigned char* w_lds = smem + (ROPE ? L::kTurned : (kStages - 1) * L::kStageBytes);
+  static_assert(!(ROPE && kTurnW) || D * D * 2 <= 2 * L::kTurnedBytes, "W goes through the un-rotated keys' place");
   const T* Wh = RES ? reinterpret_cast<const T*>(p.W) + (int64_t)w_head(p, h) * p.w_sh : nullptr;
-  const int my_dim = (ww.has_res ? ww.res_block : 0) * 32 + ((l31 >> 2) & 1) * 16 + (l31 >> 3) * 4 + (l31 & 3);
+  // The residual's product of this wave.  Rotated keys share no operands with the scores: four products a tile go to the last
+  // four waves, one on each SIMD.
+  constexpr bool kLastFour = ROPE && S::kSub * JB == 4;
+  const int res_sub = kLastFour ? (wave & 3) / JB : ww.res_sub, res_block = kLastFour ? (wave & 3) % JB : ww.res_block;
+  const bool has_res = RES && (kLastFour ? wave >= 4 : ww.has_res);
+  const int my_dim = (has_res ? res_block : 0) * 32 + ((l31 >> 2) & 1) * 16 + (l31 >> 3) * 4 + (l31 & 3);
   auto w_slot = [&](int j, int piece) VEC_INLINE { return j * S::kRowBytes + ((piece ^ ((j ^ (j >> 3)) & (S::kPieces - 1))) * 16); };
   const int wb_j0 = ((int)threadIdx.x % (D / 8)) * 8, wb_d0 = ((int)threadIdx.x / (D / 8)) * 8;
   uint4 wraw[8];
@@ -698,8 +718,9 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // All of it has arrived from here on: what is waited for below are tiles.  The waits count the tiles' loads back from the
   // last one issued; the counter falls in order of issue, so whatever else lies between (the stores of finish(),
   // registers spilled to scratch and read back) can make a wait longer than need be, never shorter.  Spilled
-  // registers per lane: bf16 at d = 128 6 to 9 on rotated keys (51 with 16 units; unequal batches 46 to 81), 11 with 16
-  // units (40); fp32 at d = 128 99 to 191, at d = 64 up to 44 (91); elsewhere none.
+  // registers per lane (in unequal batches): bf16 at d = 128 11 (41) with 16 units, on rotated keys none (13), with 16 units 30 (49), at
+  // d = 64 (16 with 16 units on rotated keys); fp32 at d = 128 99 to 157 (176), on rotated keys up to 29 (86), at d = 64 up to 25 (67),
+  // on rotated keys none (26); elsewhere none.
   if (MASS) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -736,8 +757,9 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
 #pragma unroll
     for (int c = 0; c < NC; ++c) wf[c] = *reinterpret_cast<const chunk_t*>(w_lds + w_slot(my_dim, 2 * c + half));
   }
-  // a single unit's 16 biases (one per accumulator register) stay in registers; two units read them as they go
-  float bias_reg[16];
+  // a single unit's 16 biases (one per accumulator register) stay in registers; two units read them as they go (but see kBiasRegs)
+  constexpr bool kBiasRegs = L::kBiasRegs;
+  float bias_reg[kBiasRegs ? U : 1][16];
   auto read_bias = [&](int u, float* b) VEC_INLINE {
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4) {
@@ -746,9 +768,26 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       for (int i = 0; i < 4; ++i) b[g4 * 4 + i] = x[i];
     }
   };
-  if (MASS && U == 1) read_bias(0, bias_reg);
+  if (MASS && kBiasRegs) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) read_bias(u, bias_reg[kBiasRegs ? u : 0]);
+  }
+  // ROPE: the wave's block of the values of the tile at `t0`, rows res_sub * 32 .., dims res_block * 32 ..; four (fp32: eight)
+  // lanes on a row.  Nobody else reads it, so no barrier is needed between its arrival and its use.
+  constexpr int kVPieces = 32 * (int)sizeof(T) / 16, kVLoads = 32 * kVPieces / kWave;
+  auto values_at = [&](int step) VEC_INLINE { return (uint32_t)(L::kValues + (step & 1) * L::kValuesBytes + wave * L::kBlockBytes); };
+  auto fetch_values = [&](int step, int t0) VEC_INLINE {
+    const unsigned char* rows = reinterpret_cast<const unsigned char*>(reinterpret_cast<const T*>(p.v) + head_offset(p, h, p.v_sb, p.v_sh));
+#pragma unroll
+    for (int i = 0; i < kVLoads; ++i) {
+      const int row = i * (kWave / kVPieces) + lane / kVPieces, piece = (lane % kVPieces) ^ (row / 2 % kVPieces);
+      const int t = min(t0 + res_sub * 32 + row, t_end - 1);
+      load_to_lds16(smem0 + values_at(step) + i * 1024, rows + ((int64_t)t * p.v_st + res_block * 32) * (int64_t)sizeof(T) + piece * 16);
+    }
+  };
   // ROPE: this thread un-rotates pieces tp and tp + kPieces / 2 of one token per tile
   const int turn_tok = (int)threadIdx.x / (S::kPieces / 2), tp = (int)threadIdx.x % (S::kPieces / 2);
+  static_assert(S::kTokens * (S::kPieces / 2) == kStreamThreads, "a tile's pairs in one go");
   float2* turns = reinterpret_cast<float2*>(smem + L::kTurns);
   if (ROPE && (int)threadIdx.x < D / 2) turns[threadIdx.x] = make_float2(rp.turns_hi[threadIdx.x], rp.turns_lo[threadIdx.x]);
 
@@ -772,8 +811,10 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // One phase: the products of a subtile (query rows x tokens, dims x tokens), an operand
   // chunk at a time, each followed by its share of the finished products of the phase before: the
   // exponentials of mass_acc[1 - kCur] and the squared differences of the residual's against vf.
+  // kAhead: operand chunks give way to the next subtile's as they are used up.
   auto phase = [&](auto cur_tag, auto new_mass_tag, auto new_res_tag, auto fold_mass_tag, auto fold_res_tag,
-                   uint32_t this_at, uint32_t next_at, float& col, float& err) VEC_INLINE {
+                   uint32_t this_at, uint32_t next_at, float& col, float& err, auto ahead_tag) VEC_INLINE {
+    constexpr bool kAhead = decltype(ahead_tag)::value;
     constexpr int kCur = decltype(cur_tag)::value;
     constexpr bool kNewMass = decltype(new_mass_tag)::value, kNewRes = decltype(new_res_tag)::value;
     constexpr bool kFoldMass = decltype(fold_mass_tag)::value, kFoldRes = decltype(fold_res_tag)::value;
@@ -787,9 +828,9 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       for (int u = 0; u < U; ++u) {
         float b[16];
         if constexpr (kFoldMass) {
-          if constexpr (U == 1) {
+          if constexpr (kBiasRegs) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) b[v] = bias_reg[v];
+            for (int v = 0; v < 16; ++v) b[v] = bias_reg[u][v];
           } else {
             const int g4 = lo / 4;
             const f32x4 x = *reinterpret_cast<const f32x4*>(bias_lds + (ww.unit + 8 * u) * 32 + g4 * 8 + half * 4);
@@ -814,7 +855,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
         if (c == 0) mma_chunk_first<T>(res_acc[kNew], wf[c], keys_op.chunk(c));
         else mma_chunk<T>(res_acc[kNew], wf[c], keys_op.chunk(c));
       }
-      if constexpr (kNewMass || kNewRes) keys_op.used(c, this_at, next_at);
+      if constexpr ((kNewMass || kNewRes) && (kAhead || !decltype(keys_op)::kAll)) keys_op.used(c, this_at, next_at);
       if constexpr (kFoldRes) {
 #pragma unroll
         for (int v = lo; v < hi; ++v) {
@@ -839,8 +880,9 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   };
   auto leave_res = [&](int slot, float err) VEC_INLINE {
     err = add_halves(err);
-    if (half == 0) res_sums[((slot * S::kSub + ww.res_sub) * JB + ww.res_block) * 32 + l31] = err;
+    if (half == 0) res_sums[((slot * S::kSub + res_sub) * JB + res_block) * 32 + l31] = err;
   };
+  auto res_slot = [&](int step, int slot) VEC_INLINE { return ROPE ? (int)((uint32_t)step % (uint32_t)L::kResSlots) : slot; };
   // the finished sums of `count` tiles from tile `step` (slot `slot`) on, each added in one fixed order and stored
   auto finish = [&](int step, int slot, int count) VEC_INLINE {
     const int mine = wave % L::kBatch;
@@ -855,7 +897,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
     for (int i = 0; i < (S::kTokens + 63) / 64; ++i) {
       const int tok = i * 64 + lane, t = token0(step) + tok;
       if (S::kTokens < 64 && tok >= S::kTokens) return;
-      const int at = slot * S::kSub + (tok >> 5);
+      const int at = slot * S::kSub + (tok >> 5), res_at = res_slot(step, slot) * S::kSub + (tok >> 5);
       if (do_mass) {
         float m = 0.f;
 #pragma unroll
@@ -876,53 +918,107 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       if (do_res) {
         float e = 0.f;
 #pragma unroll
-        for (int x = 0; x < JB; ++x) e += res_sums[(at * JB + x) * 32 + (tok & 31)];
+        for (int x = 0; x < JB; ++x) e += res_sums[(res_at * JB + x) * 32 + (tok & 31)];
         if (t < t_end) p.eps[(size_t)h * p.n + t] = e;
       }
     }
   };
   auto read_values = [&](uint32_t tile) VEC_INLINE {
-    const int row = ww.res_sub * 32 + l31;
+    if constexpr (ROPE) {
+#pragma unroll
+      for (int i = 0; i < VP; ++i) vf[i] = lds_read16(smem0 + tile + (uint32_t)((l31 * kVPieces + ((half * VP + i) ^ (l31 / 2 % kVPieces))) * 16));
+      return;
+    }
+    const int row = res_sub * 32 + l31;
 #pragma unroll
     for (int i = 0; i < VP; ++i) {
-      const int piece = ww.res_block * (32 / E) + half * VP + i;
+      const int piece = res_block * (32 / E) + half * VP + i;
       vf[i] = lds_read16(smem0 + tile + (uint32_t)(row * S::kRowBytes + ((piece ^ S::twist(row)) * 16)));
     }
   };
-  // the un-rotated keys of the tile (rounded values, then the remainders), in the layout of a tile
-  auto unrotate = [&](int step, uint32_t tile) VEC_INLINE {
+  // ROPE: the residual's products of tile `step`, operand chunk by operand chunk, each read kOpsAhead chunks before its use (read
+  // when it is used, every product waited for its trip to LDS: 2.6 us a tile, now 2.4); and the finished ones against the
+  // tile's values
+  auto turned_at = [&](int step) VEC_INLINE { return (uint32_t)(L::kTurned + (step & 1) * L::kTurnedBytes); };
+  constexpr int kOpsAhead = 2;
+  struct Products { chunk_t hi[NC], lo[NC]; };
+  auto read_turned = [&](Products& o, int step, int c) VEC_INLINE {
+    const uint32_t at = turned_at(step) + sub_at(res_sub);
+    o.hi[c] = keys_op.read(at, c);
+    if (SplitPack<T>::kTwoParts) o.lo[c] = keys_op.read(at + (uint32_t)S::kTileBytes, c);
+  };
+  auto product = [&](Products& o, int step, int c) VEC_INLINE {
+    if (c + kOpsAhead < NC) read_turned(o, step, c + kOpsAhead);
+    if (c == 0) mma_chunk_first<T>(res_acc[0], wf[c], o.hi[c]);
+    else mma_chunk<T>(res_acc[0], wf[c], o.hi[c]);
+    if (SplitPack<T>::kTwoParts) mma_chunk<T>(res_acc[0], wf[c], o.lo[c]);
+  };
+  auto squares = [&]() VEC_INLINE {
+    float e0 = 0.f, e1 = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      float f[E];
+      Unpack16<T>::run(vf[v / E], f);
+      const float df = f[v % E] - res_acc[0][v];
+      if (v & 1) e1 = fmaf(df, df, e1); else e0 = fmaf(df, df, e0);
+    }
+    return e0 + e1;
+  };
+  // The un-rotated keys of the tile (rounded values, then the remainders), in the layout of a tile, into one of two places;
+  // with products: meanwhile the residual's of the tile before, out of the other.
+  auto unrotate = [&](int step, uint32_t tile, auto products_tag) VEC_INLINE {
+    constexpr bool kProducts = decltype(products_tag)::value;
     const int tok = turn_tok, x = S::twist(tok);
     const int at_a = tok * S::kRowBytes + ((tp ^ x) * 16), at_b = tok * S::kRowBytes + (((tp + S::kPieces / 2) ^ x) * 16);
-    const chunk_t ra = *reinterpret_cast<const chunk_t*>(smem + tile + at_a), rb = *reinterpret_cast<const chunk_t*>(smem + tile + at_b);
+    const chunk_t ra = lds_read16(smem0 + tile + at_a), rb = lds_read16(smem0 + tile + at_b);
+    Products ops;
+    if constexpr (kProducts) {
+#pragma unroll
+      for (int c = 0; c < kOpsAhead; ++c) read_turned(ops, step - 1, c);
+    }
     const int t = min(token0(step) + tok, t_end - 1);
-    const int at_pos = reinterpret_cast<const int*>(smem + tile + 2 * S::kTileBytes)[(tok >> 6) * 64 + (tok & 63)];
+    const int at_pos = reinterpret_cast<const int*>(smem + tile + S::kTileBytes)[tok];
+    // pairs (x[i], x[i + D/2]): E frequencies in a row; pairs (x[2i], x[2i+1]): half of them, and as many D / 4 further
+    f32x4 fr[E / 2];
+#pragma unroll
+    for (int i = 0; i < E / 2; ++i)
+      fr[i] = reinterpret_cast<const f32x4*>(turns)[rp.interleaved ? tp * (E / 4) + (i < E / 4 ? i : i - E / 4 + D / 8) : tp * (E / 2) + i];
     const float pos = (float)((positions ? at_pos : t) + rp.pos_offset);
     float a[E], b[E];
     Unpack16<T>::run(ra, a);
     Unpack16<T>::run(rb, b);
-    if (!rp.interleaved) {
+    // the pairs as (a[e], b[e]); moved about, and back, where they lie side by side
+    if (rp.interleaved) {                        // uniform
+      asm volatile("; pairs side by side");      // a branch: as selects the moves cost everyone
+      float c[2 * E];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        float cs, sn;
-        const float2 f = turns[tp * E + e];
-        rotary_cos_sin(pos, f.x, f.y, cs, sn);
-        rotary_back(a[e], b[e], cs, sn, a[e], b[e]);
-      }
-    } else {
+      for (int e = 0; e < E; ++e) { c[e] = a[e]; c[E + e] = b[e]; }
 #pragma unroll
-      for (int e = 0; e < E; e += 2) {
-        float cs, sn;
-        const float2 fa = turns[(tp * E + e) / 2], fb = turns[((tp + S::kPieces / 2) * E + e) / 2];
-        rotary_cos_sin(pos, fa.x, fa.y, cs, sn);
-        rotary_back(a[e], a[e + 1], cs, sn, a[e], a[e + 1]);
-        rotary_cos_sin(pos, fb.x, fb.y, cs, sn);
-        rotary_back(b[e], b[e + 1], cs, sn, b[e], b[e + 1]);
+      for (int e = 0; e < E; ++e) { a[e] = c[2 * e]; b[e] = c[2 * e + 1]; }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      if constexpr (kProducts) {
+#pragma unroll
+        for (int c = e * NC / E; c < (e + 1) * NC / E; ++c) product(ops, step - 1, c);
       }
+      float cs, sn;
+      rotary_cos_sin(pos, fr[e / 2][2 * (e % 2)], fr[e / 2][2 * (e % 2) + 1], cs, sn);
+      rotary_back(a[e], b[e], cs, sn, a[e], b[e]);
+      if constexpr (kProducts) VEC_PIN3(res_acc[0], a[e], b[e]);
+    }
+    if (rp.interleaved) {
+      asm volatile("; and back");
+      float c[2 * E];
+#pragma unroll
+      for (int e = 0; e < E; ++e) { c[2 * e] = a[e]; c[2 * e + 1] = b[e]; }
+#pragma unroll
+      for (int e = 0; e < E; ++e) { a[e] = c[e]; b[e] = c[E + e]; }
     }
     chunk_t ha, la, hb, lb;
     SplitPack<T>::run(a, ha, la);
     SplitPack<T>::run(b, hb, lb);
-    unsigned char* hi = smem + L::kTurned;
+    unsigned char* hi = smem + turned_at(step);
     *reinterpret_cast<chunk_t*>(hi + at_a) = ha;
     *reinterpret_cast<chunk_t*>(hi + at_b) = hb;
     if (SplitPack<T>::kTwoParts) {
@@ -932,11 +1028,13 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   };
   using No = std::false_type;
   using Yes = std::true_type;
-  const bool has_mass = MASS && ww.has_rows, has_res = RES && ww.has_res;
+  const bool has_mass = MASS && ww.has_rows;
   const int sub0 = ww.sub(MASS ? 0 : WW::PH - 1);
   wait_tiles<kPer>(min(kStages - 2, n_steps - 1));
-  tile_barrier();
-  keys_op.load(sub_at(sub0));
+  if constexpr (!ROPE) {
+    tile_barrier();
+    keys_op.load(sub_at(sub0));
+  }
   uint32_t tile = 0;
   int step = 0, batch0 = 0, batch0_slot = 0;    // first tile whose sums are not stored yet, and its slot
   // One tile.  Its successor is waited for here as well, so that the last phase can already read the next
@@ -944,10 +1042,19 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   auto run_step = [&](auto par_tag, auto first_tag) VEC_INLINE {
     constexpr int kPar = decltype(par_tag)::value;
     constexpr bool kFirst = decltype(first_tag)::value;
-    if (__builtin_expect(n_steps - step > kStages - 2, 1)) wait_loads<(kStages - 3) * kPer>();
-    else wait_loads<0>();
-    tile_barrier();                             // tile and successor are there for all, the stage before them is free
-    if (to_fetch > 0) fetch();
+    bool fetched = true;
+    if constexpr (ROPE) {
+      tile_barrier();                           // the tile is there for all, and the un-rotated one before it; the stage before it is free
+      if (has_mass) keys_op.load(tile + sub_at(sub0));
+      fetched = to_fetch > 0;
+      if (fetched) fetch();
+      if (has_res) fetch_values(step, token0(step));
+    } else {
+      if (__builtin_expect(n_steps - step > kStages - 2, 1)) wait_loads<(kStages - 3) * kPer>();
+      else wait_loads<0>();
+      tile_barrier();                           // tile and successor are there for all, the stage before them is free
+      if (to_fetch > 0) fetch();
+    }
     if (__builtin_expect(step == batch0 + L::kBatch + 1, 0)) {
       finish(batch0, batch0_slot, L::kBatch);
       batch0 += L::kBatch;
@@ -955,10 +1062,13 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       if (batch0_slot >= L::kSlots) batch0_slot -= L::kSlots;
     }
     const uint32_t next_tile = tile + L::kStageBytes == kRing ? 0 : tile + L::kStageBytes;
-    if constexpr (ROPE) unrotate(step, tile);
+    if constexpr (ROPE) {
+      if (!kFirst && has_res) unrotate(step, tile, std::integral_constant<bool, !kFirst>{});
+      else unrotate(step, tile, No{});
+    }
     for (int rep = 0; rep < (PROBE ? p.repeat : 1); ++rep) {
-      // the products of the residual start in the last phase, together with the last subtile's scores;
-      // post-RoPE keys have them in a phase of their own, when every thread has written its share
+      // the products of the residual start in the last phase, together with the last subtile's scores; those of rotated keys
+      // in the next tile's step, beside its un-rotation
       constexpr bool kResWithMass = RES && !ROPE;
       auto one = [&](auto ph_tag) VEC_INLINE {
         constexpr int ph = decltype(ph_tag)::value;
@@ -971,18 +1081,21 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
           float col, err;
           using Cur = std::integral_constant<int, cur>;
           using FoldM = std::integral_constant<bool, MASS && kFold>;
-          using FoldR = std::integral_constant<bool, RES && kFold && ph == 0>;
+          using FoldR = std::integral_constant<bool, RES && !ROPE && kFold && ph == 0>;
+          using Ahead = std::integral_constant<bool, !(ROPE && kLast)>;
           using NewR = std::integral_constant<bool, kResWithMass && kLast>;
           constexpr bool kAll = !(S::kSub * JB < kStreamWaves) && !(NRB == 4 && S::kSub == 1);
-          if constexpr (kAll) {
-            phase(Cur{}, std::integral_constant<bool, MASS>{}, NewR{}, FoldM{}, FoldR{}, here, next, col, err);
+          if constexpr (ROPE) {
+            if (has_mass) phase(Cur{}, std::integral_constant<bool, MASS>{}, No{}, FoldM{}, No{}, here, next, col, err, Ahead{});
+          } else if constexpr (kAll) {
+            phase(Cur{}, std::integral_constant<bool, MASS>{}, NewR{}, FoldM{}, FoldR{}, here, next, col, err, Yes{});
           } else {       // fp32: not every wave has products of both kinds
-            if (has_mass && has_res) phase(Cur{}, std::integral_constant<bool, MASS>{}, NewR{}, FoldM{}, FoldR{}, here, next, col, err);
-            else if (has_mass) phase(Cur{}, std::integral_constant<bool, MASS>{}, No{}, FoldM{}, No{}, here, next, col, err);
-            else if (has_res) phase(Cur{}, No{}, NewR{}, No{}, FoldR{}, here, next, col, err);
+            if (has_mass && has_res) phase(Cur{}, std::integral_constant<bool, MASS>{}, NewR{}, FoldM{}, FoldR{}, here, next, col, err, Yes{});
+            else if (has_mass) phase(Cur{}, std::integral_constant<bool, MASS>{}, No{}, FoldM{}, No{}, here, next, col, err, Yes{});
+            else if (has_res) phase(Cur{}, No{}, NewR{}, No{}, FoldR{}, here, next, col, err, Yes{});
           }
           if constexpr (FoldM::value) {
-            if (kAll || has_mass) leave_mass(ph == 0 ? last_slot : sums_slot, ww.sub(ph == 0 ? PH - 1 : ph - 1), col);
+            if ((kAll && !ROPE) || has_mass) leave_mass(ph == 0 ? last_slot : sums_slot, ww.sub(ph == 0 ? PH - 1 : ph - 1), col);
           }
           if constexpr (FoldR::value) {
             if constexpr (PROBE) asm volatile("" : "+v"(err));
@@ -995,20 +1108,18 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       one(std::integral_constant<int, 2>{});
       one(std::integral_constant<int, 3>{});
       if constexpr (ROPE) {
-        tile_barrier();
+        // the next tile, and the values of the one before, were asked for a step ago, before what this step asked for
         if (has_res) {
-          const uint32_t hi_at = (uint32_t)L::kTurned + sub_at(ww.res_sub);
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            const chunk_t kh = keys_op.read(hi_at, c);
-            f32x16& a = res_acc[PH == 1 ? kPar : 0];
-            if (c == 0) mma_chunk_first<T>(a, wf[c], kh);
-            else mma_chunk<T>(a, wf[c], kh);
-            if (SplitPack<T>::kTwoParts) mma_chunk<T>(a, wf[c], keys_op.read(hi_at + (uint32_t)S::kTileBytes, c));
-          }
+          if (fetched) wait_loads<kPer + kVLoads>(); else wait_loads<kVLoads>();
+        } else {
+          if (fetched) wait_loads<kPer>(); else wait_loads<0>();
+        }
+        if (!kFirst && has_res) {
+          read_values(values_at(step - 1));
+          leave_res(res_slot(step - 1, last_slot), squares());
         }
       }
-      if (has_res) read_values(tile + S::kTileBytes);
+      if (!ROPE && has_res) read_values(tile + S::kTileBytes);
     }
     tile = next_tile;
     last_slot = sums_slot;
@@ -1029,13 +1140,25 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
     float col = 0.f, err = 0.f;
     if (has_mass) {
       const bool odd = (PH * n_steps - 1) & 1;
-      if (odd) phase(std::integral_constant<int, 0>{}, No{}, No{}, Yes{}, No{}, 0u, 0u, col, err);
-      else phase(std::integral_constant<int, 1>{}, No{}, No{}, Yes{}, No{}, 0u, 0u, col, err);
+      if (odd) phase(std::integral_constant<int, 0>{}, No{}, No{}, Yes{}, No{}, 0u, 0u, col, err, Yes{});
+      else phase(std::integral_constant<int, 1>{}, No{}, No{}, Yes{}, No{}, 0u, 0u, col, err, Yes{});
       leave_mass(last_slot, ww.sub(PH - 1), col);
     }
-    if (has_res) {
-      if ((n_steps - 1) & 1) phase(std::integral_constant<int, 0>{}, No{}, No{}, No{}, Yes{}, 0u, 0u, col, err);
-      else phase(std::integral_constant<int, 1>{}, No{}, No{}, No{}, Yes{}, 0u, 0u, col, err);
+    if constexpr (ROPE) {
+      wait_loads<0>();
+      tile_barrier();                            // the last tile's un-rotated keys are there
+      if (has_res) {
+        Products ops;
+#pragma unroll
+        for (int c = 0; c < kOpsAhead; ++c) read_turned(ops, n_steps - 1, c);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) product(ops, n_steps - 1, c);
+        read_values(values_at(n_steps - 1));
+        leave_res(res_slot(n_steps - 1, last_slot), squares());
+      }
+    } else if (has_res) {
+      if ((n_steps - 1) & 1) phase(std::integral_constant<int, 0>{}, No{}, No{}, No{}, Yes{}, 0u, 0u, col, err, Yes{});
+      else phase(std::integral_constant<int, 1>{}, No{}, No{}, No{}, Yes{}, 0u, 0u, col, err, Yes{});
       leave_res(last_slot, err);
     }
   }
