@@ -196,7 +196,7 @@ __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(
 // Which subtiles of a tile a wave works on.  NRB (4, 8 or 16) units of 32 query rows, padded with zero
 // rows: with 4, waves w and w + 4 share unit w and split the subtiles; with 8, wave w takes unit w on every
 // subtile; with 16, units w and w + 8.  The residual has kSub * JB products of 32 tokens x 32 dims per
-// tile, one per wave (fp32: every other wave), on the subtile `res_sub` that the wave works on last.
+// tile, one per wave, on the subtile `res_sub` that the wave works on last (where there are four, see kLastFour).
 template <typename T, int D, int NRB> struct WaveWork {
   using S = Stream<T, D>;
   static constexpr int U = NRB == 16 ? 2 : 1;
@@ -554,10 +554,16 @@ template <typename T, int D, int NRB, bool MASS, bool RES, bool ROPE> struct Pas
   // the second tile's un-rotated keys
   static constexpr bool kBiasRegs = WW::U == 1 || (ROPE && sizeof(T) == 2 && D == 64), kBiasInTurned = ROPE && sizeof(T) == 2 && D == 64;
   static constexpr int kPosBytes = ROPE ? S::kTokens <= 64 ? 256 : 512 : 0;
-  static constexpr int kStageBytes = S::kTileBytes * (RES && !ROPE ? 2 : 1) + kPosBytes;
-  static constexpr int kStages = ROPE ? 3 : 4;
+  // The residual's products a tile late, on LDS operands of their own: rotated keys, and fp32 keys (with both kinds of products
+  // in one phase, on shared operands, the kernels at 128 dims spilled 99 to 176 registers: 3075 tokens x 8 heads, 64 query rows 83 us a
+  // pass, now 56; 1130 tokens, two prompts, 128 rows 68 and 49; at 64 dims 3 to 11 % less now).  bf16 keys share their operands: one
+  // read of LDS for both.
+  static constexpr bool kLate = RES && (ROPE || sizeof(T) == 4);
+  static constexpr int kStageBytes = S::kTileBytes * (RES && !kLate ? 2 : 1) + kPosBytes;
+  static constexpr int kStages = ROPE ? 3 : 4;                      // kLate: the tile before stays, un-rotated (rotated keys) or as it is
+  static constexpr int kFirstTiles = kLate ? 2 : kStages - 1;       // on their way before the first is worked on
   static constexpr int kValues = kStages * kStageBytes;                                  // [2][kStreamWaves] blocks of 32 rows by 32 dims
-  static constexpr int kBlockBytes = 32 * 32 * (int)sizeof(T), kValuesBytes = ROPE ? kStreamWaves * kBlockBytes : 0;
+  static constexpr int kBlockBytes = 32 * 32 * (int)sizeof(T), kValuesBytes = kLate ? kStreamWaves * kBlockBytes : 0;
   static constexpr int kTurned = kValues + 2 * kValuesBytes;                             // [2]
   static constexpr int kTurnedBytes = ROPE ? S::kTileBytes * (SplitPack<T>::kTwoParts ? 2 : 1) : 0;
   static constexpr int kMassStep = MASS ? S::kSub * WW::kEntries * 32 * 4 : 0;
@@ -569,7 +575,7 @@ template <typename T, int D, int NRB, bool MASS, bool RES, bool ROPE> struct Pas
   // a batch is stored while the two tiles after it leave their sums
   static constexpr int kBatch = kFree >= 6 * (kMassStep + kResStep) ? 4 : kFree >= 4 * (kMassStep + kResStep) ? 2 : 1;
   static constexpr int kSlots = kBatch + 2;
-  static constexpr int kResSlots = ROPE ? kBatch + 1 : kSlots;      // rotated keys: a tile's residuals come a step later, all at once
+  static constexpr int kResSlots = kLate ? kBatch + 1 : kSlots;      // kLate: a tile's residuals come a step later, all at once
   static constexpr int kResSums = kMassSums + kSlots * kMassStep;                        // [kResSlots][kSub][JB][32]
   static constexpr int kEnd = kResSums + kResSlots * kResStep;
   static constexpr int kBias = kBiasInTurned ? kTurned + kTurnedBytes : kEnd;
@@ -612,17 +618,17 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   TileSource<T, D> keys, values;
   const int t_top = t_begin + (n_steps - 1) * S::kTokens;
   keys.init(reinterpret_cast<const T*>(p.k) + head_offset(p, h, p.k_sb, p.k_sh), p.k_st, t_top, -1, wave, lane);
-  if (RES && !ROPE) values.init(reinterpret_cast<const T*>(p.v) + head_offset(p, h, p.v_sb, p.v_sh), p.v_st, t_top, -1, wave, lane);
+  if (RES && !L::kLate) values.init(reinterpret_cast<const T*>(p.v) + head_offset(p, h, p.v_sb, p.v_sh), p.v_st, t_top, -1, wave, lane);
   const int32_t* positions = nullptr;
   if (ROPE && rp.positions) positions = rp.positions + p.pos_base + (p.hps ? (int64_t)(h / p.hps) * p.n : 0);
-  constexpr int kPer = S::kLoads * (RES && !ROPE ? 2 : 1) + (ROPE ? 1 : 0);
+  constexpr int kPer = S::kLoads * (RES && !L::kLate ? 2 : 1) + (ROPE ? 1 : 0);
   constexpr uint32_t kRing = kStages * L::kStageBytes;
   auto token0 = [&](int step) VEC_INLINE { return t_top - step * S::kTokens; };
   uint32_t at_fetch = 0;                         // ring position of the tile to be fetched next
   int t_fetch = t_top, to_fetch = n_steps;       // its first token, and the tiles still to be fetched
   auto fetch = [&]() VEC_INLINE {
     keys.load(smem0 + at_fetch, t_fetch, t_end);
-    if (RES && !ROPE) values.load(smem0 + at_fetch + S::kTileBytes, t_fetch, t_end);
+    if (RES && !L::kLate) values.load(smem0 + at_fetch + S::kTileBytes, t_fetch, t_end);
     if (ROPE) {        // positions of tokens 64 (wave % 2) .., from every wave alike; without an array any 4 bytes keep the count of loads the same
       const int half_tile = S::kTokens <= 64 ? 0 : wave & 1, t = min(t_fetch + half_tile * 64 + lane, t_end - 1);
       load_to_lds4(smem0 + at_fetch + S::kTileBytes + half_tile * 256,
@@ -655,9 +661,9 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   unsigned char* w_lds = smem + (ROPE ? L::kTurned : (kStages - 1) * L::kStageBytes);
   static_assert(!(ROPE && kTurnW) || D * D * 2 <= 2 * L::kTurnedBytes, "W goes through the un-rotated keys' place");
   const T* Wh = RES ? reinterpret_cast<const T*>(p.W) + (int64_t)w_head(p, h) * p.w_sh : nullptr;
-  // The residual's product of this wave.  Rotated keys share no operands with the scores: four products a tile go to the last
+  // The residual's product of this wave.  Late ones share no operands with the scores: four products a tile go to the last
   // four waves, one on each SIMD.
-  constexpr bool kLastFour = ROPE && S::kSub * JB == 4;
+  constexpr bool kLate = L::kLate, kLastFour = kLate && S::kSub * JB == 4;
   const int res_sub = kLastFour ? (wave & 3) / JB : ww.res_sub, res_block = kLastFour ? (wave & 3) % JB : ww.res_block;
   const bool has_res = RES && (kLastFour ? wave >= 4 : ww.has_res);
   const int my_dim = (has_res ? res_block : 0) * 32 + ((l31 >> 2) & 1) * 16 + (l31 >> 3) * 4 + (l31 & 3);
@@ -718,9 +724,9 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // All of it has arrived from here on: what is waited for below are tiles.  The waits count the tiles' loads back from the
   // last one issued; the counter falls in order of issue, so whatever else lies between (the stores of finish(),
   // registers spilled to scratch and read back) can make a wait longer than need be, never shorter.  Spilled
-  // registers per lane (in unequal batches): bf16 at d = 128 11 (41) with 16 units, on rotated keys none (13), with 16 units 30 (49), at
-  // d = 64 (16 with 16 units on rotated keys); fp32 at d = 128 99 to 157 (176), on rotated keys up to 29 (86), at d = 64 up to 25 (67),
-  // on rotated keys none (26); elsewhere none.
+  // registers per lane (in unequal batches): bf16 at d = 128 11 (41) with 16 units, on rotated keys none (13), with 16 units 30 (48), at
+  // d = 64 (16 with 16 units on rotated keys); fp32 at d = 128 10 (36), on rotated keys 29 (86), at d = 64 (16, on rotated keys 26);
+  // elsewhere none.
   if (MASS) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -738,7 +744,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
     for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(wf[c].x), "+v"(wf[c].y), "+v"(wf[c].z), "+v"(wf[c].w));
   }
 #pragma unroll
-  for (int s = 1; s < kStages - 1; ++s)
+  for (int s = 1; s < L::kFirstTiles; ++s)
     if (to_fetch > 0) fetch();
   if constexpr (kTurnW) {
     if ((int)threadIdx.x < D * D / 64) {
@@ -772,7 +778,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
 #pragma unroll
     for (int u = 0; u < U; ++u) read_bias(u, bias_reg[kBiasRegs ? u : 0]);
   }
-  // ROPE: the wave's block of the values of the tile at `t0`, rows res_sub * 32 .., dims res_block * 32 ..; four (fp32: eight)
+  // kLate: the wave's block of the values of the tile at `t0`, rows res_sub * 32 .., dims res_block * 32 ..; four (fp32: eight)
   // lanes on a row.  Nobody else reads it, so no barrier is needed between its arrival and its use.
   constexpr int kVPieces = 32 * (int)sizeof(T) / 16, kVLoads = 32 * kVPieces / kWave;
   auto values_at = [&](int step) VEC_INLINE { return (uint32_t)(L::kValues + (step & 1) * L::kValuesBytes + wave * L::kBlockBytes); };
@@ -882,7 +888,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
     err = add_halves(err);
     if (half == 0) res_sums[((slot * S::kSub + res_sub) * JB + res_block) * 32 + l31] = err;
   };
-  auto res_slot = [&](int step, int slot) VEC_INLINE { return ROPE ? (int)((uint32_t)step % (uint32_t)L::kResSlots) : slot; };
+  auto res_slot = [&](int step, int slot) VEC_INLINE { return kLate ? (int)((uint32_t)step % (uint32_t)L::kResSlots) : slot; };
   // the finished sums of `count` tiles from tile `step` (slot `slot`) on, each added in one fixed order and stored
   auto finish = [&](int step, int slot, int count) VEC_INLINE {
     const int mine = wave % L::kBatch;
@@ -924,7 +930,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
     }
   };
   auto read_values = [&](uint32_t tile) VEC_INLINE {
-    if constexpr (ROPE) {
+    if constexpr (kLate) {
 #pragma unroll
       for (int i = 0; i < VP; ++i) vf[i] = lds_read16(smem0 + tile + (uint32_t)((l31 * kVPieces + ((half * VP + i) ^ (l31 / 2 % kVPieces))) * 16));
       return;
@@ -936,22 +942,30 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       vf[i] = lds_read16(smem0 + tile + (uint32_t)(row * S::kRowBytes + ((piece ^ S::twist(row)) * 16)));
     }
   };
-  // ROPE: the residual's products of tile `step`, operand chunk by operand chunk, each read kOpsAhead chunks before its use (read
+  // kLate: the residual's products of tile `step`, operand chunk by operand chunk, each read kOpsAhead chunks before its use (read
   // when it is used, every product waited for its trip to LDS: 2.6 us a tile, now 2.4); and the finished ones against the
   // tile's values
   auto turned_at = [&](int step) VEC_INLINE { return (uint32_t)(L::kTurned + (step & 1) * L::kTurnedBytes); };
   constexpr int kOpsAhead = 2;
   struct Products { chunk_t hi[NC], lo[NC]; };
+  uint32_t tile = 0, tile_before = 0;            // the tile at hand in the ring, and the one before it
   auto read_turned = [&](Products& o, int step, int c) VEC_INLINE {
-    const uint32_t at = turned_at(step) + sub_at(res_sub);
+    const uint32_t at = (ROPE ? turned_at(step) : tile_before) + sub_at(res_sub);
     o.hi[c] = keys_op.read(at, c);
-    if (SplitPack<T>::kTwoParts) o.lo[c] = keys_op.read(at + (uint32_t)S::kTileBytes, c);
+    if (ROPE && SplitPack<T>::kTwoParts) o.lo[c] = keys_op.read(at + (uint32_t)S::kTileBytes, c);
   };
   auto product = [&](Products& o, int step, int c) VEC_INLINE {
     if (c + kOpsAhead < NC) read_turned(o, step, c + kOpsAhead);
     if (c == 0) mma_chunk_first<T>(res_acc[0], wf[c], o.hi[c]);
     else mma_chunk<T>(res_acc[0], wf[c], o.hi[c]);
-    if (SplitPack<T>::kTwoParts) mma_chunk<T>(res_acc[0], wf[c], o.lo[c]);
+    if (ROPE && SplitPack<T>::kTwoParts) mma_chunk<T>(res_acc[0], wf[c], o.lo[c]);
+  };
+  auto products = [&](int step) VEC_INLINE {
+    Products ops;
+#pragma unroll
+    for (int c = 0; c < kOpsAhead; ++c) read_turned(ops, step, c);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) product(ops, step, c);
   };
   auto squares = [&]() VEC_INLINE {
     float e0 = 0.f, e1 = 0.f;
@@ -1030,12 +1044,11 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   using Yes = std::true_type;
   const bool has_mass = MASS && ww.has_rows;
   const int sub0 = ww.sub(MASS ? 0 : WW::PH - 1);
-  wait_tiles<kPer>(min(kStages - 2, n_steps - 1));
-  if constexpr (!ROPE) {
+  wait_tiles<kPer>(min(L::kFirstTiles - 1, n_steps - 1));
+  if constexpr (!kLate) {
     tile_barrier();
     keys_op.load(sub_at(sub0));
   }
-  uint32_t tile = 0;
   int step = 0, batch0 = 0, batch0_slot = 0;    // first tile whose sums are not stored yet, and its slot
   // One tile.  Its successor is waited for here as well, so that the last phase can already read the next
   // phase's operands; the products of the last phase of a tile are folded during the first of the next.
@@ -1043,9 +1056,9 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
     constexpr int kPar = decltype(par_tag)::value;
     constexpr bool kFirst = decltype(first_tag)::value;
     bool fetched = true;
-    if constexpr (ROPE) {
-      tile_barrier();                           // the tile is there for all, and the un-rotated one before it; the stage before it is free
-      if (has_mass) keys_op.load(tile + sub_at(sub0));
+    if constexpr (kLate) {
+      tile_barrier();                           // the tile is there for all, and the un-rotated one before it; a stage is free
+      if (decltype(keys_op)::kAll && has_mass) keys_op.load(tile + sub_at(sub0));
       fetched = to_fetch > 0;
       if (fetched) fetch();
       if (has_res) fetch_values(step, token0(step));
@@ -1065,11 +1078,13 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
     if constexpr (ROPE) {
       if (!kFirst && has_res) unrotate(step, tile, std::integral_constant<bool, !kFirst>{});
       else unrotate(step, tile, No{});
+    } else if constexpr (kLate && !kFirst) {
+      if (has_res) products(step - 1);
     }
     for (int rep = 0; rep < (PROBE ? p.repeat : 1); ++rep) {
       // the products of the residual start in the last phase, together with the last subtile's scores; those of rotated keys
       // in the next tile's step, beside its un-rotation
-      constexpr bool kResWithMass = RES && !ROPE;
+      constexpr bool kResWithMass = RES && !kLate;
       auto one = [&](auto ph_tag) VEC_INLINE {
         constexpr int ph = decltype(ph_tag)::value;
         if constexpr (ph < PH) {
@@ -1081,21 +1096,18 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
           float col, err;
           using Cur = std::integral_constant<int, cur>;
           using FoldM = std::integral_constant<bool, MASS && kFold>;
-          using FoldR = std::integral_constant<bool, RES && !ROPE && kFold && ph == 0>;
-          using Ahead = std::integral_constant<bool, !(ROPE && kLast)>;
+          using FoldR = std::integral_constant<bool, RES && !kLate && kFold && ph == 0>;
+          using Ahead = std::integral_constant<bool, !(kLate && kLast)>;
           using NewR = std::integral_constant<bool, kResWithMass && kLast>;
-          constexpr bool kAll = !(S::kSub * JB < kStreamWaves) && !(NRB == 4 && S::kSub == 1);
-          if constexpr (ROPE) {
+          constexpr bool kAll = !kLate && (!RES || S::kSub * JB >= kStreamWaves) && !(NRB == 4 && S::kSub == 1);      // every wave has products of both kinds
+          static_assert(kLate || kAll || !RES, "products of one kind alone are for late residuals");
+          if constexpr (kLate) {
             if (has_mass) phase(Cur{}, std::integral_constant<bool, MASS>{}, No{}, FoldM{}, No{}, here, next, col, err, Ahead{});
-          } else if constexpr (kAll) {
-            phase(Cur{}, std::integral_constant<bool, MASS>{}, NewR{}, FoldM{}, FoldR{}, here, next, col, err, Yes{});
-          } else {       // fp32: not every wave has products of both kinds
-            if (has_mass && has_res) phase(Cur{}, std::integral_constant<bool, MASS>{}, NewR{}, FoldM{}, FoldR{}, here, next, col, err, Yes{});
-            else if (has_mass) phase(Cur{}, std::integral_constant<bool, MASS>{}, No{}, FoldM{}, No{}, here, next, col, err, Yes{});
-            else if (has_res) phase(Cur{}, No{}, NewR{}, No{}, FoldR{}, here, next, col, err, Yes{});
+          } else {
+            if (kAll || has_mass) phase(Cur{}, std::integral_constant<bool, MASS>{}, NewR{}, FoldM{}, FoldR{}, here, next, col, err, Yes{});
           }
           if constexpr (FoldM::value) {
-            if ((kAll && !ROPE) || has_mass) leave_mass(ph == 0 ? last_slot : sums_slot, ww.sub(ph == 0 ? PH - 1 : ph - 1), col);
+            if (kAll || has_mass) leave_mass(ph == 0 ? last_slot : sums_slot, ww.sub(ph == 0 ? PH - 1 : ph - 1), col);
           }
           if constexpr (FoldR::value) {
             if constexpr (PROBE) asm volatile("" : "+v"(err));
@@ -1107,7 +1119,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       one(std::integral_constant<int, 1>{});
       one(std::integral_constant<int, 2>{});
       one(std::integral_constant<int, 3>{});
-      if constexpr (ROPE) {
+      if constexpr (kLate) {
         // the next tile, and the values of the one before, were asked for a step ago, before what this step asked for
         if (has_res) {
           if (fetched) wait_loads<kPer + kVLoads>(); else wait_loads<kVLoads>();
@@ -1119,8 +1131,9 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
           leave_res(res_slot(step - 1, last_slot), squares());
         }
       }
-      if (!ROPE && has_res) read_values(tile + S::kTileBytes);
+      if (!kLate && has_res) read_values(tile + S::kTileBytes);
     }
+    tile_before = tile;
     tile = next_tile;
     last_slot = sums_slot;
     if (++sums_slot == L::kSlots) sums_slot = 0;
@@ -1144,15 +1157,11 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       else phase(std::integral_constant<int, 1>{}, No{}, No{}, Yes{}, No{}, 0u, 0u, col, err, Yes{});
       leave_mass(last_slot, ww.sub(PH - 1), col);
     }
-    if constexpr (ROPE) {
+    if constexpr (kLate) {
       wait_loads<0>();
       tile_barrier();                            // the last tile's un-rotated keys are there
       if (has_res) {
-        Products ops;
-#pragma unroll
-        for (int c = 0; c < kOpsAhead; ++c) read_turned(ops, n_steps - 1, c);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) product(ops, n_steps - 1, c);
+        products(n_steps - 1);
         read_values(values_at(n_steps - 1));
         leave_res(res_slot(n_steps - 1, last_slot), squares());
       }

@@ -1,4 +1,4 @@
-"""Rotated keys: the residual's products come a tile after the un-rotation.  Every kernel for rotated keys, with one and with
+"""Rotated keys, and fp32 keys: the residual's products come a tile after the scores.  Each of these kernels, with one and with
 several tiles per workgroup, a partial last tile, row indices and position arrays, both pairings, against the oracle."""
 import numpy as np
 import pytest
@@ -20,9 +20,9 @@ KERNELS = [("bf16", 128, 1, 16), ("bf16", 128, 4, 64), ("bf16", 128, 8, 64), ("b
 SIZES = [(1, 70), (2, 128), (3, 333), (64, 650), (48, 1100)]
 
 
-@pytest.mark.parametrize("dtype,d,G,w", KERNELS)
+@pytest.mark.parametrize("dtype,d,G,w,rotated", [k + (True,) for k in KERNELS] + [k + (False,) for k in KERNELS if k[0] == "f32"])
 @pytest.mark.parametrize("H,n", SIZES)
-def test_residual_and_score(dtype, d, G, w, H, n):
+def test_residual_and_score(dtype, d, G, w, rotated, H, n):
     if H >= 48 and G * w > 256:
         H //= 4
     rng = np.random.default_rng(d + G + w + H + n)
@@ -39,12 +39,16 @@ def test_residual_and_score(dtype, d, G, w, H, n):
     ws.fill_(0xff)
     score, eps, alone = (torch.full((H, n), -1.0, device="cuda:0") for _ in range(3))
     dev = [pl.to_device(x) for x in (q, k, v, W)]
-    vb.vector_score_residual_rope(shape, *dev, rope, score, eps, ws)
-    vb.vector_residual_rope(shape, *dev[1:], rope, alone, ws)
+    if rotated:
+        vb.vector_score_residual_rope(shape, *dev, rope, score, eps, ws)
+        vb.vector_residual_rope(shape, *dev[1:], rope, alone, ws)
+    else:
+        vb.vector_score_residual(shape, *dev, score, eps, ws)
+        vb.vector_residual(shape, *dev[1:], alone, ws)
     torch.cuda.synchronize()
     del keep
     some = np.unique(np.linspace(0, H - 1, 6).astype(int))               # heads held against the oracle
-    ref = vo.residual(wide(k)[some], wide(v)[some], wide(W)[some], pos=pos, inv_freq=inv, interleaved=interleaved)
+    ref = vo.residual(wide(k)[some], wide(v)[some], wide(W)[some], **(dict(pos=pos, inv_freq=inv, interleaved=interleaved) if rotated else {}))
     close(eps.cpu().numpy()[some], ref, "residual beside the score")
     close(alone.cpu().numpy()[some], ref, "residual alone")
     rows = (some[:, None] * G + np.arange(G)).ravel()
