@@ -8,7 +8,7 @@
 //   solve_kernel : grid (d / 16 column blocks, heads).  Blocked fp64 Cholesky of K^T K with the column
 //                  block of K^T V riding along, then the backward substitution; all on fp64 matrix
 //                  instructions out of LDS.
-// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 64 + 12 + 23 us (products, sums, solve).
+// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 57 + 7 + 22 us (products, sums, solve).
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -17,9 +17,10 @@ namespace vec {
 namespace {
 
 constexpr int kCalThreads = 256;
-constexpr int kCalTile = 128;                // chunks are multiples of the longest tile
+constexpr int kCalTile = 128;                // chunks are multiples of the longest tile; 256 for bf16 keys of 64 dims
 constexpr int kCalMaxChunks = 64;
 constexpr int kCalMinTokens = 256;
+constexpr int kCalCus = 256;
 
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 
@@ -41,34 +42,43 @@ struct CalParams {
 // eight 2-byte reads per operand, and those reads bound the launch).  A row of LDS holds one dim's tokens
 // of the tile; the 16-byte slots of a row are permuted by the dim so that neither the stores (dims
 // eight apart) nor the operand reads (dims next to each other) meet in a bank.
-// Bound: HBM, every key and value once: 64 us (4.2 TB/s; 5.1 is a plain copy) at 65536 tokens x 8 heads, 74 us
-// with column reads of plain tiles.  Wave w owns the 32-row block w of both products
-// (d = 128; for d = 64 two waves take K^T K and two K^T V).
+// One workgroup of eight waves per CU: four take K^T K, four K^T V, a 32-row block each (d = 128; for d = 64 two and two,
+// and the other four the second half of the tile's tokens).  The tile after next is requested as soon as the next one's
+// registers are in LDS, so that the memory is never waited for by a whole CU.
+// An accumulator sums at most kRunTiles tiles and is then added to a total: chunks may be long (the partials,
+// 128 KB a workgroup, are traffic too) while the fp32 sums stay those of short ones.
+// Bound: HBM, every key and value once and 27 MB of partials: 57 us at 65536 tokens x 8 heads (5.2 TB/s; a plain copy moves
+// 5.1).  Two workgroups of four waves on a CU, each with both products and chunks of 1024 tokens: 64 us, and 12 in
+// place of 7 for the sums of twice the partials; 1474 tokens x 4 heads, d = 64: 21.8 -> 16.8 us for the fit.  Error of the
+// sums against 64-bit ones (root of the summed squares, 65536 tokens): 3.7e-8 there, 2.8e-8 here.
 // ---------------------------------------------------------------------------
+constexpr int kGramThreads = 512;
+constexpr int kRunTiles = 4;
 template <int D> struct GramTile {
-  static constexpr int kTokens = 64 * 128 / D;                    // one 8 x 8 block per thread and tile
+  static constexpr int kTokens = 128 * 128 / D;                   // one 8 x 8 block per thread and tile
   static constexpr int kOctets = kTokens / 8;
   static constexpr int kRowBytes = kTokens * 2;
-  static constexpr int kBytes = (D + (D == 128 ? 1 : 0)) * kRowBytes;
+  static constexpr int kBytes = D * kRowBytes;
   static __device__ __forceinline__ int at(int dim, int octet) {
-    return (dim + (D == 128 ? dim >> 6 : 0)) * kRowBytes + ((octet ^ (((dim >> 3) ^ dim) & 7)) * 16);
+    return dim * kRowBytes + ((octet ^ (((dim >> 3) * (128 / D) ^ dim) & 15)) * 16);
   }
 };
 
 template <int D>
-__global__ __launch_bounds__(kCalThreads, 2) void gram_kernel(CalParams p) {
+__global__ __launch_bounds__(kGramThreads) void gram_kernel(CalParams p) {
   using T = bf16_t;
   using TL = GramTile<D>;
   constexpr int JB = D / 32;
-  constexpr int kBlocks = kCalThreads / 2;                        // 8 x 8 blocks of K, and of V, per tile
+  constexpr int kBlocks = kGramThreads / 2;                       // 8 x 8 blocks of K, and of V, per tile
   static_assert((D / 8) * TL::kOctets == kBlocks, "one block per thread");
-  constexpr bool kBoth = (JB == 4);
+  constexpr int kShares = kGramThreads / kWave / (2 * JB);        // waves that share a block row of a product, by tokens
+  constexpr int kSteps = TL::kTokens / 16 / kShares;              // 16-token steps of a tile per wave
   extern __shared__ __align__(16) unsigned char gram_lds[];       // [buffer][K, V][kBytes]
 
   const int h = blockIdx.y, chunk = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, half = lane >> 5;
-  const int ib = kBoth ? wave : (wave % JB);
-  const bool do_g = kBoth || wave < JB, do_c = kBoth || wave >= JB;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l31 = lane & 31, half = lane >> 5;
+  const int ib = wave % JB, share = wave / (2 * JB);
+  const bool is_c = (wave / JB) & 1;
   // this thread's block of a tile: K or V, eight dims, eight tokens
   const bool is_v = (int)threadIdx.x >= kBlocks;
   const int bi = (int)threadIdx.x % kBlocks, dims0 = (bi % (D / 8)) * 8, octet = bi / (D / 8);
@@ -78,11 +88,11 @@ __global__ __launch_bounds__(kCalThreads, 2) void gram_kernel(CalParams p) {
   const int c_end = min(p.m, c_begin + p.tokens_per_chunk);
   const int n_tiles = (c_end - c_begin + TL::kTokens - 1) / TL::kTokens;
 
-  f32x16 accg[JB], accc[JB];
+  f32x16 acc[JB], total[JB];
 #pragma unroll
   for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-    for (int x = 0; x < 16; ++x) { accg[jb][x] = 0.f; accc[jb][x] = 0.f; }
+    for (int x = 0; x < 16; ++x) { acc[jb][x] = 0.f; total[jb][x] = 0.f; }
 
   uint4 raw[8];
   auto fetch = [&](int tile) {
@@ -116,31 +126,54 @@ __global__ __launch_bounds__(kCalThreads, 2) void gram_kernel(CalParams p) {
   };
 
   if (n_tiles > 0) { fetch(0); stash(0, 0); }
+  if (n_tiles > 1) fetch(1);
   for (int tile = 0; tile < n_tiles; ++tile) {
     __syncthreads();                         // tile is staged; the other buffer is free
-    if (tile + 1 < n_tiles) fetch(tile + 1);
     const unsigned char* kt = gram_lds + (tile & 1) * 2 * TL::kBytes;
-    const unsigned char* vt = kt + TL::kBytes;
-#pragma unroll (D == 128 ? 4 : 2)
-    for (int ks = 0; ks < TL::kTokens / 16; ++ks) {
+    const unsigned char* right = kt + (is_c ? TL::kBytes : 0);
+#pragma unroll 2
+    for (int i = 0; i < kSteps; ++i) {
+      const int ks = share * kSteps + i;
       const bf16x8 a = operand(kt, ib, ks);
 #pragma unroll
-      for (int jb = 0; jb < JB; ++jb) {
-        if (do_g) accg[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, operand(kt, jb, ks), accg[jb], 0, 0, 0);
-        if (do_c) accc[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, operand(vt, jb, ks), accc[jb], 0, 0, 0);
-      }
+      for (int jb = 0; jb < JB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, operand(right, jb, ks), acc[jb], 0, 0, 0);
+    }
+    if (tile % kRunTiles == kRunTiles - 1) {
+#pragma unroll
+      for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) { total[jb][x] += acc[jb][x]; acc[jb][x] = 0.f; }
     }
     if (tile + 1 < n_tiles) stash(tile + 1, (tile + 1) & 1);
+    if (tile + 2 < n_tiles) fetch(tile + 2);
   }
-  // accumulator register x of block jb: row 32*ib + acc_row(x, half), column 32*jb + l31
-  float* out = p.part + ((size_t)h * p.n_chunks + chunk) * 2 * D * D;
 #pragma unroll
   for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-    for (int x = 0; x < 16; ++x) {
-      const size_t at = (size_t)(32 * ib + acc_row(x, half)) * D + 32 * jb + l31;
-      if (do_g && jb <= ib) out[at] = accg[jb][x];                // K^T K is symmetric: the blocks up to the diagonal
-      if (do_c) out[(size_t)D * D + at] = accc[jb][x];
+    for (int x = 0; x < 16; ++x) total[jb][x] += acc[jb][x];
+  if constexpr (kShares == 2) {              // the second half's tokens, through LDS
+    __syncthreads();
+    float* mine = reinterpret_cast<float*>(gram_lds) + (wave % (2 * JB)) * (JB * 16 * kWave) + lane;
+    if (share == 1) {
+#pragma unroll
+      for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) mine[(jb * 16 + x) * kWave] = total[jb][x];
+    }
+    __syncthreads();
+    if (share == 1) return;
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+      for (int x = 0; x < 16; ++x) total[jb][x] += mine[(jb * 16 + x) * kWave];
+  }
+  // accumulator register x of block jb: row 32*ib + acc_row(x, half), column 32*jb + l31
+  float* out = p.part + (((size_t)h * p.n_chunks + chunk) * 2 + (is_c ? 1 : 0)) * D * D;
+#pragma unroll
+  for (int jb = 0; jb < JB; ++jb)
+    if (is_c || jb <= ib) {                  // K^T K is symmetric: the blocks up to the diagonal
+#pragma unroll
+      for (int x = 0; x < 16; ++x) out[(size_t)(32 * ib + acc_row(x, half)) * D + 32 * jb + l31] = total[jb][x];
     }
 }
 
@@ -213,8 +246,8 @@ __global__ __launch_bounds__(kCalThreads) void gram_f32_kernel(CalParams p) {
 
 // Chunk partials -> fp64 sums in 16 x 16 tiles, the order solve_kernel keeps them in LDS: tile (i, j),
 // j <= i, of K^T K, then tile (r, j) of (K^T V)^T.  Grid (tiles, heads).  A wave takes a quarter of the chunks, a lane four
-// elements side by side in all of them, requested at once; the quarters meet in LDS, in order.  Bound: the partials, 54 MB
-// at 65536 tokens x 8 heads, in 11.9 us; one element per thread, its chunks in four trips: 12.6 us.  (One
+// elements side by side in all of them, requested at once; the quarters meet in LDS, in order.  Bound: the partials, 27 MB
+// at 65536 tokens x 8 heads, in 7.1 us.  (One
 // workgroup per head summing all of it took most of the solve's 0.9 ms at 65536 tokens.)
 template <int D>
 __global__ __launch_bounds__(256) void gram_reduce_kernel(CalParams p) {
@@ -386,11 +419,11 @@ __device__ __forceinline__ void factor_invert_tile(f64x4 a, const f64x4& xt, dou
 //   The right-hand sides ride along as one more block row, (K^T V)^T: after step s its tile s holds the
 //   forward solution.  For the backward substitution wave j takes rows 16 j .. of it into registers, and
 //   a solved block goes to the waves above through LDS.
-// Bound: the chain of 4 x 4 blocks.  23 us for d = 128, eight heads (cycles: 30000 in the diagonal tiles, 7000 in the tiles
+// Bound: the chain of 4 x 4 blocks.  22 us for d = 128, eight heads (cycles: 30000 in the diagonal tiles, 7000 in the tiles
 // below them, 7500 in the backward substitution; the other tiles' updates are waited for in the second step alone).
 // Reading the next tile's operands ahead of a tile's products made the updates slower (6500 cycles against 5200 in
 // that step); L_ss^-1 L_sj formed by the idle waves while the tiles below the diagonal are multiplied, so that the backward
-// substitution waits for half as many products, lengthened those steps by more than it saved (the fit 97.0 -> 97.6 us).
+// substitution waits for half as many products, lengthened those steps by more than it saved (the fit 0.6 us longer).
 // One workgroup per head with a thread per row and plain loops took 934 us (the sums included).
 template <typename T, int D>
 __global__ __launch_bounds__(512) void solve_kernel(CalParams p) {
@@ -510,15 +543,31 @@ __global__ __launch_bounds__(512) void solve_kernel(CalParams p) {
 // fp64 tiles a head's sums take: K^T K up to its diagonal, and (K^T V)^T
 constexpr int cal_tiles_per_head(int d) { return (d / 16) * (d / 16 + 1) / 2 + (d / 16) * (d / 16); }
 
-// 1024 tokens per chunk, shorter ones while that leaves CUs without a workgroup (a chunk's tiles are a
-// chain, and shorter chunks only tighten the fp32 sums), longer ones past 64 chunks
-void calibrate_chunks(int m, int n_kv_heads, int& tokens_per_chunk, int& n_chunks) {
-  int want = 1024;
-  while (want > kCalMinTokens && (int64_t)((m + want - 1) / want) * n_kv_heads < 256) want >>= 1;
-  n_chunks = (m + want - 1) / want;
+// bf16: as many chunks as give each CU the one workgroup that its LDS holds, or, for heads that do not divide the CUs
+// well, each of them a few.  (Chunks of 1024 tokens and more than one workgroup for some CUs: 42443 tokens x 8 heads 82 us
+// for the fit, 75 with two workgroups of half the size on a CU.)
+// fp32: 1024 tokens per chunk, shorter ones while that leaves CUs without a workgroup (a chunk's tiles are a
+// chain, and shorter chunks only tighten the fp32 sums).  Both: longer ones past 64 chunks, none shorter than 256 tokens.
+void calibrate_chunks(const vector_shape& s, int& tokens_per_chunk, int& n_chunks) {
+  const int m = s.seq_len, heads = s.n_kv_heads;
+  int tile = kCalTile;
+  if (s.dtype == VECTOR_BF16) {
+    if (s.head_dim == 64) tile = 2 * kCalTile;
+    n_chunks = 1;
+    for (int per_cu = 1; per_cu <= 8; ++per_cu) {
+      n_chunks = kCalCus * per_cu / heads;
+      if (n_chunks * heads * 4 >= kCalCus * per_cu * 3) break;
+    }
+    const int most = (m + kCalMinTokens - 1) / kCalMinTokens;
+    if (n_chunks > most) n_chunks = most;
+  } else {
+    int want = 1024;
+    while (want > kCalMinTokens && (int64_t)((m + want - 1) / want) * heads < kCalCus) want >>= 1;
+    n_chunks = (m + want - 1) / want;
+  }
   if (n_chunks > kCalMaxChunks) n_chunks = kCalMaxChunks;
   if (n_chunks < 1) n_chunks = 1;
-  tokens_per_chunk = ((m + n_chunks - 1) / n_chunks + kCalTile - 1) / kCalTile * kCalTile;
+  tokens_per_chunk = ((m + n_chunks - 1) / n_chunks + tile - 1) / tile * tile;
   n_chunks = (m + tokens_per_chunk - 1) / tokens_per_chunk;
   if (n_chunks < 1) n_chunks = 1;
 }
@@ -529,7 +578,7 @@ int run_calibrate(const vector_shape& s, CalParams& p, hipStream_t stream) {
   if constexpr (Elem<T>::kDtype == VECTOR_BF16) {
     constexpr size_t lds = 4 * GramTile<D>::kBytes;
     VEC_HIP(set_max_lds(reinterpret_cast<const void*>(gram_kernel<D>), lds));
-    hipLaunchKernelGGL(gram_kernel<D>, grid, dim3(kCalThreads), lds, stream, p);
+    hipLaunchKernelGGL(gram_kernel<D>, grid, dim3(kGramThreads), lds, stream, p);
   } else {
     hipLaunchKernelGGL(gram_f32_kernel<D>, grid, dim3(kCalThreads), 0, stream, p);
   }
@@ -546,7 +595,7 @@ int run_calibrate(const vector_shape& s, CalParams& p, hipStream_t stream) {
 
 size_t calibrate_workspace_bytes(const vector_shape& s) {
   int tpc, nc;
-  calibrate_chunks(s.seq_len, s.n_kv_heads, tpc, nc);
+  calibrate_chunks(s, tpc, nc);
   const size_t dd = (size_t)s.head_dim * s.head_dim;
   return align_up((size_t)s.n_kv_heads * nc * 2 * dd * sizeof(float), 256) +
          align_up((size_t)s.n_kv_heads * cal_tiles_per_head(s.head_dim) * 256 * sizeof(double), 256);
@@ -560,7 +609,7 @@ int launch_calibrate(const vector_shape& s, const void* k, const void* v, void* 
   p.k_sh = s.k_stride_head ? s.k_stride_head : (int64_t)s.seq_len * p.k_st;
   p.v_st = s.v_stride_tok ? s.v_stride_tok : D;
   p.v_sh = s.v_stride_head ? s.v_stride_head : (int64_t)s.seq_len * p.v_st;
-  calibrate_chunks(s.seq_len, s.n_kv_heads, p.tokens_per_chunk, p.n_chunks);
+  calibrate_chunks(s, p.tokens_per_chunk, p.n_chunks);
   const size_t dd = (size_t)D * D;
   unsigned char* w8 = reinterpret_cast<unsigned char*>(ws);
   p.part = reinterpret_cast<float*>(w8);

@@ -1,0 +1,48 @@
+"""The value map's chunks of tokens: whole and cut tiles, runs of tiles before an accumulator is added to its total, one
+chunk per head and several, heads that do not divide the CUs."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import vector_oracle as vo
+from paper_2605_23258_amd import binding as vb
+from paper_2605_23258_amd import datagen as dg
+from paper_2605_23258_amd import pipeline as pl
+
+pytestmark = pytest.mark.gpu
+
+# (head dim, heads, tokens): tiles of 128 tokens for d = 128, 256 for d = 64; four tiles to a run
+SIZES = [
+    (128, 1, 128), (128, 1, 129), (128, 1, 257),        # chunks of 256 tokens, the last one with a single token
+    (128, 256, 511), (128, 256, 512), (128, 256, 513),  # one chunk per head: a run less a token, a run, a token more
+    (128, 300, 1290),                                   # two chunks per head on 300 heads, a run and a cut tile each
+    (128, 130, 2048 + 40),                              # four runs in a chunk and a cut tile
+    (64, 1, 64), (64, 1, 255), (64, 1, 257),            # the tile's second half empty, cut, and a second tile of one token
+    (64, 256, 1023), (64, 256, 1025),                   # one chunk per head around a run
+    (64, 33, 5000),                                     # seven chunks of three tiles
+]
+
+
+@pytest.mark.parametrize("d,heads,m", SIZES)
+def test_chunks_of_tokens(d, heads, m):
+    rng = np.random.default_rng(d + heads + m)
+    k = rng.standard_normal((heads, m, d), dtype=np.float32)
+    w = rng.standard_normal((heads, d, d), dtype=np.float32) / np.float32(np.sqrt(d))
+    v = np.matmul(k, w) + 0.1 * rng.standard_normal((heads, m, d), dtype=np.float32)
+    kb, vbf = torch.from_numpy(k).bfloat16(), torch.from_numpy(v).bfloat16()
+    shape = pl.shape_of(dg.scaled(dg.CONFIGS["cfg2"], seq_len=m, head_dim=d, n_kv_heads=heads, n_q_heads=heads))
+    W = torch.zeros((heads, d, d), dtype=torch.bfloat16, device="cuda:0")
+    ws = pl.alloc_workspace(vb.vector_calibrate_workspace_bytes(shape))
+    vb.vector_calibrate(shape, kb.cuda(), vbf.cuda(), W, ws)
+    torch.cuda.synchronize()
+    got = W.float().cpu().numpy()
+    for h in sorted({0, heads // 2, heads - 1}):
+        kd, vd = kb[h].double().numpy(), vbf[h].double().numpy()
+        ref = vo.ols_fit(kd[None], vd[None])[0]
+        # W is stored in bf16 (2^-9 relative).  The fp32 sums: runs of at most 512 tokens, 32 roundings each, then the runs': below
+        # 2^-24 * 40 of the norm of K^T K, and as much of K^T V, times the condition number and the norm of W (at most 3 here)
+        cond = np.linalg.cond(kd.T @ kd)
+        bound = 2.0 ** -8 * np.abs(ref) + 2.0 ** -24 * 40 * 2 * cond * 3 + 1e-6
+        err = np.abs(got[h] - ref)
+        assert (err <= bound).all(), f"head {h}: max err {err.max():.3e}, bound {bound.flat[err.argmax()]:.3e}, cond {cond:.1f}"
