@@ -105,6 +105,27 @@ __device__ __forceinline__ void take_sequence(P& p, int& h) {
   }
 }
 
+// RAGGED launches with just the workgroups that the sequences need (RunArgs): takes this workgroup's sequence's block and
+// returns the workgroup's number among the sequence's.  Every XCD takes a run of the launch's workgroups, so a head's
+// parts share an L2, and each XCD and, inside it, each group of CUs (an XCD deals its workgroups out to its four in
+// turn) gets as many as the next.  A grid of the longest sequence's parts for every head, whose surplus workgroups left at
+// once, was dealt out with that surplus: some groups of CUs had more than one workgroup per CU that stayed, and started the
+// second when the first had finished (eight prompts of 2048 to 8192 tokens, 8 heads: passes of 38 and 50 us, now 31 and 40).
+template <typename Args, typename P>
+__device__ __forceinline__ int take_workgroup(P& p, int& seq) {
+  const int total = gridDim.x, x = blockIdx.x % kXcds, share = total / kXcds;
+  const int at = x * share + min(x, total % kXcds) + (int)blockIdx.x / kXcds;
+  typedef const __attribute__((address_space(4))) unsigned char* bytes;
+  const bytes args = (bytes)__builtin_amdgcn_kernarg_segment_ptr();
+  static_assert(sizeof(Args::first) == sizeof(uint16_t) * kWave && sizeof(Args) == Args::kFirstAt + sizeof(Args::first), "a lane per sequence");
+  const int first = *(const __attribute__((address_space(4))) uint16_t*)(args + Args::kFirstAt + 2 * (threadIdx.x & 63));
+  seq = (int)__popcll(__ballot(first <= at)) - 1;
+  const int r = at - __builtin_amdgcn_readlane(first, seq);
+  const bytes table = p.seq_table ? (bytes)(const unsigned char*)p.seq_table : args + sizeof(P);
+  __builtin_memcpy(&p, (const unsigned char*)(table + (size_t)seq * sizeof(P)), sizeof(P));
+  return r;
+}
+
 // The parameters read anew, for what a kernel needs only at its end: held from the start they would fill the scalar
 // registers in between.  launch_head: the head as take_sequence was given it.  (Word by word through the constant
 // address space: that keeps the loads scalar behind the kernel's stores.)

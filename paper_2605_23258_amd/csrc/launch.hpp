@@ -100,6 +100,14 @@ template <typename P> constexpr int kInlineSeqs = (3400 - (int)sizeof(P)) / (int
 template <typename P, bool RAGGED> struct KernelArgs { P p; };
 template <typename P> struct KernelArgs<P, true> { P p; P seq[kInlineSeqs<P>]; };
 
+// The same for launches that have just the workgroups that the sequences need, sequence after sequence, head after head,
+// part after part (take_workgroup): first[b] is where sequence b's start (0xffff beyond the sequences).
+template <typename P, bool RAGGED> struct RunArgs : KernelArgs<P, RAGGED> {};
+template <typename P> struct RunArgs<P, true> : KernelArgs<P, true> {
+  uint16_t first[kMaxRaggedSeqs];
+  static constexpr size_t kFirstAt = sizeof(KernelArgs<P, true>);
+};
+
 // host bytes -> device memory in stream order, as kernel arguments of small copy launches (no
 // host buffer has to outlive the call, and the copies can be captured into a graph)
 int upload_table(const void* host, size_t bytes, void* dev, hipStream_t stream);

@@ -982,9 +982,11 @@ __global__ __launch_bounds__(HT) void route_list_kernel(KernelArgs<RouteParams, 
     int at, own;
     head_scan<HT>(__popc(ret4) + (__popc(apx4) << 16), sh.wsum[0], at, own);
     const int own_r = low16(own), own_a = high16(own);
-    if (t0 < end) emit_tokens(target, t0, ret4, apx4, low16(at), high16(at), own_r, base_r, base_a, sh.list);
+    if (t0 < end) list_tokens(t0, ret4, apx4, low16(at), high16(at), own_r, sh.list);
     if (t + kHeadBlock < end) { sc = load4(score, t0 + kHeadBlock, end); ep = load4(eps, t0 + kHeadBlock, end); }
     lds_barrier();                                     // the list is whole
+    if (t0 < end) store_tiers(target, t0, ret4, apx4);
+    store_indices<HT>(target, sh.list, own_r, own_a, base_r, base_a);
     if (p.g.k) copy_rows<HT>(p.g, h, p.n_approx, sh.list, own_r, own_a, base_r, base_a);
     base_r += own_r;
     base_a += own_a;

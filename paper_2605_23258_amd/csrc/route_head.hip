@@ -6,8 +6,8 @@
 // between them is a kernel boundary, and a boundary costs 4 us or more whatever the size.  So nothing is exchanged.
 // Every workgroup of a head loads the head's scores and residuals whole into registers (16384 tokens: 16 + 16 per
 // thread) and finds both thresholds itself; then it emits and copies its own part of the tokens.  The redundant
-// part is about 50 vector instructions and two LDS atomics per token and workgroup: 14 us at 8192 tokens x 8 heads,
-// 21 us at 12289.
+// part is about 50 vector instructions and two LDS atomics per token and workgroup: 13.1 us at 8192 tokens x 8 heads (loads 1.6,
+// pooling 1.2, selections 3.4 and 2.8, list 1.4, rows 2), 18.6 at 12289 with a maximum pooled.
 //
 // The line to the two launches of route_compact.hip.  A whole compression pass in us, bf16, d = 128, 64 query rows,
 // this launch (with 24576 tokens in registers for the last two lengths) against the two:
@@ -22,6 +22,9 @@
 // where a sample says that the keys lie (DigitMap), then the keys of the bucket that holds it are ranked
 // against each other by (key, lower token first); a bucket of more keys than kRankCap is cut further over the
 // range its keys really take (narrow()), and equal keys by histograms over their tokens.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 #include "route_common.hpp"
@@ -38,9 +41,10 @@ struct HeadParams {
   float* score;           // POOL: output [H, n]
   const float* eps;       // [H, n]
   int n, n_prefix, half, take_max;      // POOL: prefix columns, half the kernel (at most 4), maximum instead of mean
-  float kernel, inv_kernel;
+  float inv_kernel;       // of the kernel
   int n_pool, n_approx;
   int units_per_part;     // units of kUnit tokens that a workgroup emits
+  int parts;              // workgroups per head
   uint8_t* tier; int32_t* idx_retain; int32_t* idx_approx;
   GatherParams g;         // row copies (k null: none)
   const HeadParams* seq_table;          // RAGGED launches: the sequences' parameter blocks, seq_hps heads each
@@ -171,13 +175,19 @@ __device__ __forceinline__ Threshold head_select(const uint32_t (&key)[NS], int 
 
 // NT threads; J: blocks of 4 NT tokens a head may have
 template <int NT, int J, bool POOL, bool RAGGED>
-__global__ __launch_bounds__(NT) void route_head_kernel(KernelArgs<HeadParams, RAGGED> args) {
+__global__ __launch_bounds__(NT) void route_head_kernel(RunArgs<HeadParams, RAGGED> args) {
   HeadParams p = args.p;
-  int part, h;
-  if (RAGGED) { part = blockIdx.x; h = blockIdx.y; }
-  else xcd_chunk_head(part, h);
-  const int launch_head = h;
-  take_sequence<RAGGED>(p, h);
+  int part, h, launch_head = 0;
+  if constexpr (RAGGED) {
+    const int hps = p.seq_hps;
+    int seq;
+    const int r = take_workgroup<RunArgs<HeadParams, true>>(p, seq);
+    h = r / p.parts;
+    part = r - h * p.parts;
+    launch_head = seq * hps + h;
+  } else {
+    xcd_chunk_head(part, h);
+  }
   const int n = p.n;
   constexpr int NW = kWaves<NT>;
   const int n_units = (n + kUnit - 1) / kUnit;
@@ -223,7 +233,7 @@ __global__ __launch_bounds__(NT) void route_head_kernel(KernelArgs<HeadParams, R
     lds_barrier();
     float* dst = p.score + (size_t)h * n;
     // one block after the other through `fold`, which makes the pooled value of token e out of the 12 masses around the quad
-    auto pool_blocks = [&](auto fold) {
+    auto pool_blocks = [&](auto fold) __attribute__((always_inline)) {
 #pragma unroll
       for (int j = 0; j < J; ++j) {
         const int t0 = j * kBlock<NT> + (int)threadIdx.x * 4, slot = j * NW + wave;
@@ -258,25 +268,41 @@ __global__ __launch_bounds__(NT) void route_head_kernel(KernelArgs<HeadParams, R
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    // in ascending token order; mass is never negative, so the sums and maxima may start from zero
-    if (p.half == 3 && !p.take_max) {
-      pool_blocks([&](const float* m) {
-        float acc = m[-3];
+    // In ascending token order; mass is never negative.  Half the kernel is a constant of the code: as a number to compare with,
+    // the maximum over 7 took 0.9 us longer at 12289 tokens.  The mean over 7 comes first: code that is jumped to is code that
+    // has to be waited for (0.1 us).
+    auto mean_over = [&](auto half) __attribute__((always_inline)) {
+      constexpr int H = decltype(half)::value;
+      pool_blocks([&](const float* m) __attribute__((always_inline)) {
+        float acc = m[-H];
 #pragma unroll
-        for (int dlt = -2; dlt <= 3; ++dlt) acc += m[dlt];
-        return pool_mean(acc, 7.f, p.inv_kernel);
+        for (int dlt = 1 - H; dlt <= H; ++dlt) acc += m[dlt];
+        return pool_mean(acc, (float)(2 * H + 1), p.inv_kernel);
       });
+    };
+    auto pool_with = [&](auto half) __attribute__((always_inline)) {
+      constexpr int H = decltype(half)::value;
+      if (p.take_max) {
+        pool_blocks([&](const float* m) __attribute__((always_inline)) {
+          float most = 0.f;
+#pragma unroll
+          for (int dlt = -H; dlt <= H; ++dlt) most = fmaxf(most, m[dlt]);
+          return most;
+        });
+      } else {
+        mean_over(half);
+      }
+    };
+    if (__builtin_expect(p.half == 3 && !p.take_max, 1)) {       // uniform
+      mean_over(std::integral_constant<int, 3>{});
     } else {
-      pool_blocks([&](const float* m) {
-        float sum = 0.f, most = 0.f;
-#pragma unroll
-        for (int dlt = -4; dlt <= 4; ++dlt) {
-          const float x = (dlt >= -p.half && dlt <= p.half) ? m[dlt] : 0.f;
-          sum += x;
-          most = fmaxf(most, x);
-        }
-        return p.take_max ? most : pool_mean(sum, p.kernel, p.inv_kernel);
-      });
+      switch (p.half) {
+        case 0: pool_with(std::integral_constant<int, 0>{}); break;
+        case 1: pool_with(std::integral_constant<int, 1>{}); break;
+        case 2: pool_with(std::integral_constant<int, 2>{}); break;
+        case 3: pool_with(std::integral_constant<int, 3>{}); break;
+        default: pool_with(std::integral_constant<int, 4>{}); break;
+      }
     }
   }
 #pragma unroll
@@ -330,49 +356,64 @@ __global__ __launch_bounds__(NT) void route_head_kernel(KernelArgs<HeadParams, R
   const uint32_t in_ret = in_pool & ~in_apx;
   // fewer tokens leave the registers for them (1024 tokens: the second read costs 0.4 us; 8192 and 12289 gain 0.6 and 1.4)
   if constexpr (J * NT >= 2048) p = params_again<RAGGED, HeadParams>(launch_head);
-  // ranks: members in earlier blocks, then the exclusive prefix inside the block
+  // ranks: members in earlier blocks, then those of the waves before, then the exclusive prefix inside the wave
   const int block0 = unit0 / NW, block1 = (unit1 - 1) / NW + 1;
   const uint32_t earlier_slots = (1u << (4 * block0)) - 1u;          // block0 < J
-  const int earlier = __popc(in_ret & earlier_slots) + (__popc(in_apx & earlier_slots) << 16);
+  const int earlier = wave_incl_scan_dpp(__popc(in_ret & earlier_slots) + (__popc(in_apx & earlier_slots) << 16));
+  if (lane == 63) sh.wsum[1][wave] = earlier;
   int carry = 0;
-  if (block0 > 0) {                                            // uniform
-    int unused;
-    head_scan<NT>(earlier, sh.wsum[1], unused, carry);
-  }
   const int n_retain = p.n_pool - p.n_approx;
-  uint8_t* tier = p.tier + (size_t)h * n;
-  int32_t* ir = p.idx_retain + (size_t)h * n_retain;
-  int32_t* ia = p.idx_approx + (size_t)h * p.n_approx;
-  const EmitTarget target = {tier, ir, ia, n, n_retain, p.n_approx};
+  const EmitTarget target = {p.tier + (size_t)h * n, p.idx_retain + (size_t)h * n_retain, p.idx_approx + (size_t)h * p.n_approx, n, n_retain, p.n_approx};
   for (int b = block0; b < block1; ++b) {
     const int wave0 = max(unit0 - b * NW, 0), wave1 = min(unit1 - b * NW, NW);
     const uint32_t ret4 = (in_ret >> (4 * b)) & 15u, apx4 = (in_apx >> (4 * b)) & 15u;
-    int before, total;
-    head_scan<NT>(__popc(ret4) + (__popc(apx4) << 16), sh.wsum[2], before, total);
+    const int mine = __popc(ret4) + (__popc(apx4) << 16), incl = wave_incl_scan_dpp(mine);
+    if (lane == 63) sh.wsum[2][wave] = incl;
+    lds_barrier();
+    const int x = row_incl_scan<NT>(sh.wsum[2][lane & (NW - 1)]);
+    if (b == block0) carry = __builtin_amdgcn_readlane(row_incl_scan<NT>(sh.wsum[1][lane & (NW - 1)]), NW - 1);
     // the part's own range of ranks, from the waves' totals
-    int first = 0, own = 0;
-    {
-      const int x = wave_incl_scan_dpp(lane < NW ? sh.wsum[2][lane] : 0);
-      first = wave0 ? __builtin_amdgcn_readlane(x, wave0 - 1) : 0;
-      own = __builtin_amdgcn_readlane(x, wave1 - 1) - first;
-    }
+    const int first = wave0 ? __builtin_amdgcn_readlane(x, wave0 - 1) : 0;
+    const int own = __builtin_amdgcn_readlane(x, wave1 - 1) - first;
     const int own_r = low16(own), own_a = high16(own);
     const int base_r = low16(carry) + low16(first), base_a = high16(carry) + high16(first);
-    if (wave >= wave0 && wave < wave1)
-      emit_tokens(target, b * kBlock<NT> + (int)threadIdx.x * 4, ret4, apx4, low16(before) - low16(first), high16(before) - high16(first), own_r,
-                  base_r, base_a, sh.list);
-    carry += total;
+    const int t0 = b * kBlock<NT> + (int)threadIdx.x * 4;
+    const bool emits = wave >= wave0 && wave < wave1;
+    if (emits) {
+      const int before = (wave ? __builtin_amdgcn_readlane(x, wave - 1) : 0) + incl - mine;
+      list_tokens(t0, ret4, apx4, low16(before) - low16(first), high16(before) - high16(first), own_r, sh.list);
+    }
+    carry += __builtin_amdgcn_readlane(x, NW - 1);
     lds_barrier();                                           // the list is whole
+    if (emits) store_tiers(target, t0, ret4, apx4);
+    store_indices<NT>(target, sh.list, own_r, own_a, base_r, base_a);
     if (p.g.k) copy_rows<NT>(p.g, h, p.n_approx, sh.list, own_r, own_a, base_r, base_a);
     lds_barrier();                                           // the list may be written again
   }
 }
 
-// Workgroups per head: as many as fill the chip once
-void head_parts(int seq_len, int n_heads, HeadParams& p, unsigned& parts) {
-  const int units = (seq_len + kUnit - 1) / kUnit, want = n_heads >= 256 ? 1 : 256 / n_heads;
-  p.units_per_part = (units + want - 1) / want;
-  parts = (unsigned)((units + p.units_per_part - 1) / p.units_per_part);
+int units_of(int seq_len) { return (seq_len + kUnit - 1) / kUnit; }
+
+// Units per part: the fewest with which `count` sequences of n_heads heads each have no more workgroups than one per CU
+// (or one per head).  A part takes as long as its units (rows to copy above all), whoever's they are: with as many parts for
+// every head, the workgroups of eight prompts of 2048 to 8192 tokens, 8 heads, ended 14 to 26 us after the start, now 15 to 23.5 (their
+// rows, 50 MB in and out, take 8 of it).
+int part_units(const int* seq_len, int count, int n_heads) {
+  int units = 1;
+  for (;; ++units) {
+    int64_t parts = 0, longest = 1;
+    for (int b = 0; b < count; ++b) {
+      const int64_t of = (units_of(seq_len[b]) + units - 1) / units;
+      parts += of;
+      longest = std::max(longest, of);
+    }
+    if (parts * n_heads <= 256 || longest == 1) return units;
+  }
+}
+
+void head_parts(int seq_len, int units, HeadParams& p) {
+  p.units_per_part = units;
+  p.parts = (units_of(seq_len) + units - 1) / units;
 }
 
 // Kernel and workgroup size for heads of up to n tokens.  A thread's tokens are worked off one after the other, so beyond
@@ -384,7 +425,7 @@ void head_parts(int seq_len, int n_heads, HeadParams& p, unsigned& parts) {
 // At 8192 tokens the two are alike for any number of heads (a compression pass of 8 heads 34.2 / 34.3, of 64 106.4 / 106.2, of
 // eight unequal prompts 115.6 / 115.6); a pass of 12289 tokens takes 43.4 / 46.6 with 8 heads and 160.6 / 164.9 with 64.
 template <bool POOL, bool RAGGED> struct HeadKernel {
-  void (*kernel)(KernelArgs<HeadParams, RAGGED>);
+  void (*kernel)(RunArgs<HeadParams, RAGGED>);
   int threads;
   explicit HeadKernel(int n) {
     threads = n <= 4096 ? 512 : 1024;
@@ -400,7 +441,7 @@ HeadParams head_params(const float* mass, const float* score_in, float* score_ou
   HeadParams p;
   p.src = mass ? mass : score_in; p.score = score_out; p.eps = eps;
   p.n = n; p.n_prefix = n_prefix; p.half = pool_kernel / 2; p.take_max = pool_mode == VECTOR_POOL_MAX;
-  p.kernel = (float)pool_kernel; p.inv_kernel = 1.0f / (float)pool_kernel;
+  p.inv_kernel = 1.0f / (float)pool_kernel;
   p.n_pool = n_pool; p.n_approx = n_approx;
   p.tier = tier; p.idx_retain = idx_retain; p.idx_approx = idx_approx;
   p.g = GatherParams{};
@@ -421,13 +462,12 @@ int launch_route_head(int n_kv_heads, int seq_len, const float* score, const flo
   if (rows)
     p.g = gather_params(*rows->shape, rows->k, rows->v, idx_retain, idx_approx, n_pool - n_approx, n_approx, rows->k_ret, rows->v_ret,
                         rows->k_apx, rows->cap_retain, rows->stack);
-  unsigned parts;
-  head_parts(seq_len, n_kv_heads, p, parts);
+  head_parts(seq_len, part_units(&seq_len, 1, n_kv_heads), p);
   const HeadKernel<true, false> pooling(seq_len);
   const HeadKernel<false, false> given(seq_len);
   const auto k = pool ? pooling.kernel : given.kernel;
-  const KernelArgs<HeadParams, false> args = {p};
-  VEC_LAUNCH(K_ROUTE, k, dim3(parts, n_kv_heads), dim3(given.threads), 0, stream, args);
+  const RunArgs<HeadParams, false> args = {{p}};
+  VEC_LAUNCH(K_ROUTE, k, dim3(p.parts, n_kv_heads), dim3(given.threads), 0, stream, args);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
@@ -437,8 +477,12 @@ size_t route_head_table_bytes(int count) { return align_up(sizeof(HeadParams) * 
 int launch_route_head_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, void* tables, hipStream_t stream) {
   if (count < 1 || count > kMaxRaggedSeqs || !route_head_pools(s.pool_kernel)) return VECTOR_ERR_ARG;
   HeadParams host[kMaxRaggedSeqs];
-  unsigned most = 0;
-  int longest = 1;
+  int lens[kMaxRaggedSeqs];
+  for (int b = 0; b < count; ++b) lens[b] = seqs[b].shape.seq_len;
+  const int units = part_units(lens, count, s.n_kv_heads), longest = *std::max_element(lens, lens + count);
+  RunArgs<HeadParams, true> args;
+  std::fill(args.first, args.first + kMaxRaggedSeqs, 0xffff);
+  unsigned grid = 0;
   for (int b = 0; b < count; ++b) {
     const RaggedSeq& q = seqs[b];
     const int n = q.shape.seq_len;
@@ -447,16 +491,15 @@ int launch_route_head_ragged(const vector_shape& s, const RaggedSeq* seqs, int c
                           q.n_approx, q.tier, q.idx_retain, q.idx_approx);
     host[b].g = gather_params(q.shape, q.k, q.v, q.idx_retain, q.idx_approx, q.n_pool - q.n_approx, q.n_approx, q.k_ret, q.v_ret, q.k_apx,
                               q.cap_retain, nullptr);
-    unsigned parts;
-    head_parts(n, count * s.n_kv_heads, host[b], parts);
-    if (parts > most) most = parts;
-    if (n > longest) longest = n;
+    head_parts(n, units, host[b]);
+    args.first[b] = (uint16_t)grid;
+    grid += (unsigned)(host[b].parts * s.n_kv_heads);
+    if (grid > 0xffff) return VECTOR_ERR_SHAPE;      // cannot be: 256 workgroups at most, or one per head, and a batch's part has fewer heads
   }
-  KernelArgs<HeadParams, true> args;
   const int rc = ragged_args(host, count, s.n_kv_heads, tables, stream, args);
   if (rc != VECTOR_OK) return rc;
   const HeadKernel<true, true> k(longest);
-  VEC_LAUNCH(K_ROUTE, k.kernel, dim3(most, (unsigned)count * s.n_kv_heads), dim3(k.threads), 0, stream, args);
+  VEC_LAUNCH(K_ROUTE, k.kernel, dim3(grid), dim3(k.threads), 0, stream, args);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }

@@ -73,30 +73,15 @@ struct PassParams {
   int repeat;           // probe kernels only: times each tile's arithmetic is run on the same operands
 };
 
-// The first argument of both passes.  RAGGED: the launch has just the workgroups that the sequences need, sequence after
-// sequence, head after head, chunk after chunk; first[b] is where sequence b's start (0xffff beyond the sequences).
-template <bool RAGGED> struct PassArgs : KernelArgs<PassParams, RAGGED> {};
-template <> struct PassArgs<true> : KernelArgs<PassParams, true> { uint16_t first[kMaxRaggedSeqs]; };
-static_assert(sizeof(PassArgs<true>) == sizeof(KernelArgs<PassParams, true>) + sizeof(uint16_t) * kMaxRaggedSeqs, "take_chunk reads first[] from there");
+// The first argument of both passes
+template <bool RAGGED> using PassArgs = RunArgs<PassParams, RAGGED>;
 
-// Which chunk of which head this workgroup takes.  RAGGED: every XCD takes a run of the launch's workgroups, so a head's
-// chunks share an L2, and each XCD and, inside it, each group of CUs (an XCD deals its workgroups out to its four in
-// turn) gets as many as the next.  A grid of the longest sequence's chunks for every head, whose surplus
-// workgroups left at once, was dealt out with that surplus: some groups of CUs had more than one workgroup per CU that
-// stayed, and started the second when the first had finished (eight prompts of 2048 to 8192 tokens, 8 heads: passes of 38 and 50 us, now 31 and 40).
+// Which chunk of which head this workgroup takes
 template <bool RAGGED>
 __device__ __forceinline__ void take_chunk(PassParams& p, int& wg, int& h, bool first_pass) {
   if constexpr (RAGGED) {
-    const int total = gridDim.x, x = blockIdx.x % kXcds, share = total / kXcds;
-    const int at = x * share + min(x, total % kXcds) + (int)blockIdx.x / kXcds;
-    typedef const __attribute__((address_space(4))) unsigned char* bytes;
-    const bytes args = (bytes)__builtin_amdgcn_kernarg_segment_ptr();
-    const int first = *(const __attribute__((address_space(4))) uint16_t*)(args + sizeof(KernelArgs<PassParams, true>) + 2 * (threadIdx.x & 63));
-    static_assert(kMaxRaggedSeqs == kWave, "a lane per sequence");
-    const int seq = (int)__popcll(__ballot(first <= at)) - 1;
-    const int r = at - __builtin_amdgcn_readlane(first, seq);
-    const bytes table = p.seq_table ? (bytes)(const unsigned char*)p.seq_table : args + sizeof(PassParams);
-    __builtin_memcpy(&p, (const unsigned char*)(table + (size_t)seq * sizeof(PassParams)), sizeof(PassParams));
+    int seq;
+    const int r = take_workgroup<PassArgs<true>>(p, seq);
     const int per_head = first_pass ? p.wgs1 : p.range_stride;
     h = r / per_head;
     wg = r - h * per_head;
