@@ -34,13 +34,17 @@ namespace vec {
 namespace {
 
 constexpr int kMaxHead = 16384;                 // tokens
+// Half of the widest pooling kernel: two quads on either side of a token's own.  Wider ones are pooled by a launch of their own,
+// and unequal prompts routed by two more.  Kernel 13 with that limit at nine, and now, us a compression pass: 8192 tokens, 8 heads
+// 38.6 / 34.1, 2049 30.5 / 25.8, five prompts of 1500 to 6000 tokens 80.8 / 56.1, two of 750 and 1500, two heads 42 / 25.
+constexpr int kMaxHalf = 8;
 constexpr int kUnit = 4 * kWave;                // tokens of a wave in a block: what the head is shared out in
 
 struct HeadParams {
   const float* src;       // POOL: attention mass [H, n]; otherwise the scores [H, n]
   float* score;           // POOL: output [H, n]
   const float* eps;       // [H, n]
-  int n, n_prefix, half, take_max;      // POOL: prefix columns, half the kernel (at most 4), maximum instead of mean
+  int n, n_prefix, half, take_max;      // POOL: prefix columns, half the kernel (at most kMaxHalf), maximum instead of mean
   float inv_kernel;       // of the kernel
   int n_pool, n_approx;
   int units_per_part;     // units of kUnit tokens that a workgroup emits
@@ -53,7 +57,7 @@ struct HeadParams {
 
 template <int NT> struct HeadShared {
   __align__(16) int hist[kHeadBins];
-  __align__(16) f32x4 first[kMaxHead / kUnit], last[kMaxHead / kUnit];     // POOL: the quads at the edges of every wave's run of a block
+  __align__(16) f32x4 first[2][kMaxHead / kUnit], last[2][kMaxHead / kUnit];     // POOL: the quads at the edges of every wave's run of a block, and the next ones
   __align__(16) unsigned long long cand[kRankCap];     // (key, ~token)
   __align__(16) int list[kBlock<NT>];                  // tokens whose rows this workgroup copies: retained, then approximated
   int wsum[3][kWaves<NT>];
@@ -227,29 +231,35 @@ __global__ __launch_bounds__(NT) void route_head_kernel(RunArgs<HeadParams, RAGG
         for (int e = 0; e < 4; ++e)
           if (t0 + e >= p.n_prefix) q[j][e] = 0.f;
       }
-      if (lane == 0) sh.first[j * NW + wave] = q[j];
-      if (lane == 63) sh.last[j * NW + wave] = q[j];
+      if (lane < 2) sh.first[lane][j * NW + wave] = q[j];
+      if (lane > 61) sh.last[63 - lane][j * NW + wave] = q[j];
     }
     lds_barrier();
     float* dst = p.score + (size_t)h * n;
-    // one block after the other through `fold`, which makes the pooled value of token e out of the 12 masses around the quad
-    auto pool_blocks = [&](auto fold) __attribute__((always_inline)) {
+    // One block after the other through `fold`, which makes the pooled value of token e out of the masses around its quad: those of
+    // one or two quads on either side.
+    auto pool_blocks = [&](auto quads, auto fold) __attribute__((always_inline)) {
+      constexpr int Q = decltype(quads)::value;
 #pragma unroll
       for (int j = 0; j < J; ++j) {
         const int t0 = j * kBlock<NT> + (int)threadIdx.x * 4, slot = j * NW + wave;
-        f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-        if (slot > 0) lo = sh.last[slot - 1];
-        if (slot + 1 < J * NW) hi = sh.first[slot + 1];
-        float m[12];
+        float m[4 * (2 * Q + 1)];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          m[e] = dpp_take_f<0x138, 0xf>(lo[e], q[j][e]);         // wave_shr:1, the quad before
-          m[4 + e] = q[j][e];
-          m[8 + e] = dpp_take_f<0x130, 0xf>(hi[e], q[j][e]);     // wave_shl:1, the quad after
+        for (int e = 0; e < 4; ++e) m[4 * Q + e] = q[j][e];
+#pragma unroll
+        for (int d = 1; d <= Q; ++d) {
+          f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
+          if (slot > 0) lo = sh.last[d - 1][slot - 1];
+          if (slot + 1 < J * NW) hi = sh.first[d - 1][slot + 1];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            m[4 * (Q - d) + e] = dpp_take_f<0x138, 0xf>(lo[e], m[4 * (Q - d + 1) + e]);         // wave_shr:1, the quad before
+            m[4 * (Q + d) + e] = dpp_take_f<0x130, 0xf>(hi[e], m[4 * (Q + d - 1) + e]);         // wave_shl:1, the quad after
+          }
         }
         f32x4 s;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s[e] = fold(m + 4 + e);
+        for (int e = 0; e < 4; ++e) s[e] = fold(m + 4 * Q + e);
         if (t0 - lane * 4 + 4 * kWave > p.n_prefix) {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -273,7 +283,7 @@ __global__ __launch_bounds__(NT) void route_head_kernel(RunArgs<HeadParams, RAGG
     // has to be waited for (0.1 us).
     auto mean_over = [&](auto half) __attribute__((always_inline)) {
       constexpr int H = decltype(half)::value;
-      pool_blocks([&](const float* m) __attribute__((always_inline)) {
+      pool_blocks(std::integral_constant<int, (H > 4 ? 2 : 1)>{}, [&](const float* m) __attribute__((always_inline)) {
         float acc = m[-H];
 #pragma unroll
         for (int dlt = 1 - H; dlt <= H; ++dlt) acc += m[dlt];
@@ -283,7 +293,7 @@ __global__ __launch_bounds__(NT) void route_head_kernel(RunArgs<HeadParams, RAGG
     auto pool_with = [&](auto half) __attribute__((always_inline)) {
       constexpr int H = decltype(half)::value;
       if (p.take_max) {
-        pool_blocks([&](const float* m) __attribute__((always_inline)) {
+        pool_blocks(std::integral_constant<int, (H > 4 ? 2 : 1)>{}, [&](const float* m) __attribute__((always_inline)) {
           float most = 0.f;
 #pragma unroll
           for (int dlt = -H; dlt <= H; ++dlt) most = fmaxf(most, m[dlt]);
@@ -301,7 +311,11 @@ __global__ __launch_bounds__(NT) void route_head_kernel(RunArgs<HeadParams, RAGG
         case 1: pool_with(std::integral_constant<int, 1>{}); break;
         case 2: pool_with(std::integral_constant<int, 2>{}); break;
         case 3: pool_with(std::integral_constant<int, 3>{}); break;
-        default: pool_with(std::integral_constant<int, 4>{}); break;
+        case 4: pool_with(std::integral_constant<int, 4>{}); break;
+        case 5: pool_with(std::integral_constant<int, 5>{}); break;
+        case 6: pool_with(std::integral_constant<int, 6>{}); break;
+        case 7: pool_with(std::integral_constant<int, 7>{}); break;
+        default: pool_with(std::integral_constant<int, kMaxHalf>{}); break;
       }
     }
   }
@@ -452,7 +466,7 @@ HeadParams head_params(const float* mass, const float* score_in, float* score_ou
 }  // namespace
 
 bool route_head_fits(int seq_len) { return seq_len <= kMaxHead; }
-bool route_head_pools(int pool_kernel) { return pool_kernel / 2 <= 4; }
+bool route_head_pools(int pool_kernel) { return pool_kernel / 2 <= kMaxHalf; }
 
 int launch_route_head(int n_kv_heads, int seq_len, const float* score, const float* eps, int n_pool, int n_approx, uint8_t* tier,
                       int32_t* idx_retain, int32_t* idx_approx, const HeadPool* pool, const PackedRows* rows, hipStream_t stream) {

@@ -1,5 +1,4 @@
-"""Batches of unequal prompts whose routing takes two launches: prompts beyond the length of one, and pooling kernels wider
-than nine.  Their parameter blocks are kernel arguments, or a table when there are many."""
+"""Batches of unequal prompts whose routing takes two launches, prompts beyond the length of one, and wide pooling kernels.  Their parameter blocks are kernel arguments, or a table when there are many."""
 import numpy as np
 import pytest
 
