@@ -8,7 +8,7 @@
 //   solve_kernel : grid (d / 16 column blocks, heads).  Blocked fp64 Cholesky of K^T K with the column
 //                  block of K^T V riding along, then the backward substitution; all on fp64 matrix
 //                  instructions out of LDS.
-// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 57 + 7 + 22 us (products, sums, solve).
+// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 62 + 7 + 23 us (products, sums, solve; averages over inputs in turn).
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -47,8 +47,8 @@ struct CalParams {
 // registers are in LDS, so that the memory is never waited for by a whole CU.
 // An accumulator sums at most kRunTiles tiles and is then added to a total: chunks may be long (the partials,
 // 128 KB a workgroup, are traffic too) while the fp32 sums stay those of short ones.
-// Bound: HBM, every key and value once and 27 MB of partials: 57 us at 65536 tokens x 8 heads (5.2 TB/s; a plain copy moves
-// 5.1).  Two workgroups of four waves on a CU, each with both products and chunks of 1024 tokens: 64 us, and 12 in
+// Bound: HBM, every key and value once and 27 MB of partials: 62 us at 65536 tokens x 8 heads, inputs in turn (4.8 TB/s; 56.5 at
+// best, 5.2; a plain copy moves 5.3).  Two workgroups of four waves on a CU, each with both products and chunks of 1024 tokens: 64 us (58 at best), and 12 in
 // place of 7 for the sums of twice the partials; 1474 tokens x 4 heads, d = 64: 21.8 -> 16.8 us for the fit.  Error of the
 // sums against 64-bit ones (root of the summed squares, 65536 tokens): 3.7e-8 there, 2.8e-8 here.
 // ---------------------------------------------------------------------------
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kCalThreads) void gram_f32_kernel(CalParams p) {
 // Chunk partials -> fp64 sums in 16 x 16 tiles, the order solve_kernel keeps them in LDS: tile (i, j),
 // j <= i, of K^T K, then tile (r, j) of (K^T V)^T.  Grid (tiles, heads).  A wave takes a quarter of the chunks, a lane four
 // elements side by side in all of them, requested at once; the quarters meet in LDS, in order.  Bound: the partials, 27 MB
-// at 65536 tokens x 8 heads, in 7.1 us.  (One
+// at 65536 tokens x 8 heads, in 7.4 us.  (One
 // workgroup per head summing all of it took most of the solve's 0.9 ms at 65536 tokens.)
 template <int D>
 __global__ __launch_bounds__(256) void gram_reduce_kernel(CalParams p) {
@@ -419,7 +419,7 @@ __device__ __forceinline__ void factor_invert_tile(f64x4 a, const f64x4& xt, dou
 //   The right-hand sides ride along as one more block row, (K^T V)^T: after step s its tile s holds the
 //   forward solution.  For the backward substitution wave j takes rows 16 j .. of it into registers, and
 //   a solved block goes to the waves above through LDS.
-// Bound: the chain of 4 x 4 blocks.  22 us for d = 128, eight heads (cycles: 30000 in the diagonal tiles, 7000 in the tiles
+// Bound: the chain of 4 x 4 blocks.  23 us for d = 128, eight heads (cycles: 30000 in the diagonal tiles, 7000 in the tiles
 // below them, 7500 in the backward substitution; the other tiles' updates are waited for in the second step alone).
 // Reading the next tile's operands ahead of a tile's products made the updates slower (6500 cycles against 5200 in
 // that step); L_ss^-1 L_sj formed by the idle waves while the tiles below the diagonal are multiplied, so that the backward
