@@ -9,6 +9,8 @@
 //                  block of K^T V riding along, then the backward substitution; all on fp64 matrix
 //                  instructions out of LDS.
 // At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 62 + 7 + 23 us (products, sums, solve; averages over inputs in turn).
+#include <algorithm>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -20,6 +22,7 @@ constexpr int kCalThreads = 256;
 constexpr int kCalTile = 128;                // chunks are multiples of the longest tile; 256 for bf16 keys of 64 dims
 constexpr int kCalMaxChunks = 64;
 constexpr int kCalMinTokens = 256;
+constexpr int kCalMaxTokens = 2048;           // bf16
 constexpr int kCalCus = 256;
 
 typedef __attribute__((ext_vector_type(4))) double f64x4;
@@ -45,15 +48,19 @@ struct CalParams {
 // One workgroup of eight waves per CU: four take K^T K, four K^T V, a 32-row block each (d = 128; for d = 64 two and two,
 // and the other four the second half of the tile's tokens).  The tile after next is requested as soon as the next one's
 // registers are in LDS, so that the memory is never waited for by a whole CU.
-// An accumulator sums at most kRunTiles tiles and is then added to a total: chunks may be long (the partials,
-// 128 KB a workgroup, are traffic too) while the fp32 sums stay those of short ones.
+// An accumulator sums 128 tokens and is then added to a total: the errors of longer runs on the matrix cores need not average
+// out over chunks (the diagonal of K^T K of normal keys comes out 6e-8 too large in every chunk of 1024 tokens, 6e-9 in runs of
+// 128), those of the additions to the total do.  A total takes at most 16 of them (kCalMaxTokens; beyond 64 chunks a head m / 8192).
+// Relative error of that diagonal against 64 bits (root mean square): one run over 1024 tokens (256 for few heads and tokens) / runs
+// of 512 in chunks as long as one workgroup per CU makes them / this:
+//   8 heads x 12000 tokens 1.2e-8 / 3.4e-8 / 1.0e-8, x 65536 6.4e-8 / 4.3e-8 / 1.2e-8; 32 x 65536 6.4e-8 / 4.7e-8 / 1.2e-8;
+//   96 x 65536 6.6e-8 / 8.3e-8 / 1.2e-8; 256 x 4096 9.9e-8 / 7.5e-8 / 4.5e-8, x 32768 7.0e-8 / 11.4e-8 / 1.6e-8.
+// All elements, keys and values of one sign, in units of the factors' norms: 8 x 12000 8e-9 / 11e-9 / 6e-9, x 65536 23e-9 / 12e-9 / 11e-9.
 // Bound: HBM, every key and value once and 27 MB of partials: 62 us at 65536 tokens x 8 heads, inputs in turn (4.8 TB/s; 56.5 at
 // best, 5.2; a plain copy moves 5.3).  Two workgroups of four waves on a CU, each with both products and chunks of 1024 tokens: 64 us (58 at best), and 12 in
-// place of 7 for the sums of twice the partials; 1474 tokens x 4 heads, d = 64: 21.8 -> 16.8 us for the fit.  Error of the
-// sums against 64-bit ones (root of the summed squares, 65536 tokens): 3.7e-8 there, 2.8e-8 here.
+// place of 7 for the sums of twice the partials; 1474 tokens x 4 heads, d = 64: 21.8 -> 16.8 us for the fit.
 // ---------------------------------------------------------------------------
 constexpr int kGramThreads = 512;
-constexpr int kRunTiles = 4;
 template <int D> struct GramTile {
   static constexpr int kTokens = 128 * 128 / D;                   // one 8 x 8 block per thread and tile
   static constexpr int kOctets = kTokens / 8;
@@ -92,7 +99,7 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(CalParams p) {
 #pragma unroll
   for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-    for (int x = 0; x < 16; ++x) { acc[jb][x] = 0.f; total[jb][x] = 0.f; }
+    for (int x = 0; x < 16; ++x) total[jb][x] = 0.f;
 
   uint4 raw[8];
   auto fetch = [&](int tile) {
@@ -131,26 +138,22 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(CalParams p) {
     __syncthreads();                         // tile is staged; the other buffer is free
     const unsigned char* kt = gram_lds + (tile & 1) * 2 * TL::kBytes;
     const unsigned char* right = kt + (is_c ? TL::kBytes : 0);
-#pragma unroll 2
-    for (int i = 0; i < kSteps; ++i) {
+    auto step = [&](int i) {
       const int ks = share * kSteps + i;
       const bf16x8 a = operand(kt, ib, ks);
 #pragma unroll
-      for (int jb = 0; jb < JB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, operand(right, jb, ks), acc[jb], 0, 0, 0);
-    }
-    if (tile % kRunTiles == kRunTiles - 1) {
+      for (int jb = 0; jb < JB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, operand(right, jb, ks), i == 0 ? f32x16{} : acc[jb], 0, 0, 0);
+    };
+    step(0);
+#pragma unroll 2
+    for (int i = 1; i < kSteps; ++i) step(i);
 #pragma unroll
-      for (int jb = 0; jb < JB; ++jb)
+    for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-        for (int x = 0; x < 16; ++x) { total[jb][x] += acc[jb][x]; acc[jb][x] = 0.f; }
-    }
+      for (int x = 0; x < 16; ++x) total[jb][x] += acc[jb][x];
     if (tile + 1 < n_tiles) stash(tile + 1, (tile + 1) & 1);
     if (tile + 2 < n_tiles) fetch(tile + 2);
   }
-#pragma unroll
-  for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-    for (int x = 0; x < 16; ++x) total[jb][x] += acc[jb][x];
   if constexpr (kShares == 2) {              // the second half's tokens, through LDS
     __syncthreads();
     float* mine = reinterpret_cast<float*>(gram_lds) + (wave % (2 * JB)) * (JB * 16 * kWave) + lane;
@@ -543,9 +546,16 @@ __global__ __launch_bounds__(512) void solve_kernel(CalParams p) {
 // fp64 tiles a head's sums take: K^T K up to its diagonal, and (K^T V)^T
 constexpr int cal_tiles_per_head(int d) { return (d / 16) * (d / 16 + 1) / 2 + (d / 16) * (d / 16); }
 
-// bf16: as many chunks as give each CU the one workgroup that its LDS holds, or, for heads that do not divide the CUs
-// well, each of them a few.  (Chunks of 1024 tokens and more than one workgroup for some CUs: 42443 tokens x 8 heads 82 us
-// for the fit, 75 with two workgroups of half the size on a CU.)
+// bf16: as many chunks as give each CU the one workgroup that its LDS holds, in as many rounds as it takes for no chunk to be
+// longer than kCalMaxTokens (its partial sums are added in fp32, see gram_kernel) and for at least three quarters of the rounds' CUs
+// to have one.  The fit, us, with chunks per head x their tokens:
+//   8 heads x 42443: 31 x 1408 (0.97 rounds) 60, 34 x 1280 (1.06) 78, 56 x 768 (1.75) 72; 8 x 12000: 32 x 384 (1.00) 43, 47 x 256 50
+//   48 x 8192: 5 x 1664 (0.94) 87, 6 x 1408 (1.12) 104; 96 x 4096: 2 x 2048 (0.75) 114, 3 x 1408 (1.12) 128, 8 x 512 (3.00) 145
+//   65 x 2100: 3 x 768 (0.76) 90, 4 x 640 (1.02) 102, 5 x 512 (1.27) 98; 65 x 16384: 8 x 2048 (2.03) 230, 11 x 1536 (2.79) 214, 16 x 1024 247
+//   130 x 8192: 4 x 2048 (2.03) 276, 5 x 1664 (2.54) 259, 8 x 1024 (4.06) 287; 300 x 2048: 1 x 2048 (1.17) 336, 2 x 1024 (2.34) 332
+//   d = 64: 65 x 8192: 4 x 2048 (1.02) 52, 7 x 1280 (1.78) 45, 8 x 1024 (2.03) 51; 130 x 2088: 2 x 1280 (1.02) 49, 3 x 768 (1.52) 44
+// With two workgroups of half the size on a CU and chunks of 1024 tokens: 8 x 42443 75, 32 x 16384 100 (now 92), 65 x 16384 236 (214),
+// 96 x 16384 297 (271), 130 x 32768 722 (639).
 // fp32: 1024 tokens per chunk, shorter ones while that leaves CUs without a workgroup (a chunk's tiles are a
 // chain, and shorter chunks only tighten the fp32 sums).  Both: longer ones past 64 chunks, none shorter than 256 tokens.
 void calibrate_chunks(const vector_shape& s, int& tokens_per_chunk, int& n_chunks) {
@@ -553,12 +563,10 @@ void calibrate_chunks(const vector_shape& s, int& tokens_per_chunk, int& n_chunk
   int tile = kCalTile;
   if (s.dtype == VECTOR_BF16) {
     if (s.head_dim == 64) tile = 2 * kCalTile;
-    n_chunks = 1;
-    for (int per_cu = 1; per_cu <= 8; ++per_cu) {
-      n_chunks = kCalCus * per_cu / heads;
-      if (n_chunks * heads * 4 >= kCalCus * per_cu * 3) break;
-    }
-    const int most = (m + kCalMinTokens - 1) / kCalMinTokens;
+    const int most = (m + kCalMinTokens - 1) / kCalMinTokens, least = std::min(kCalMaxChunks, (m + kCalMaxTokens - 1) / kCalMaxTokens);
+    int64_t rounds = ((int64_t)least * heads + kCalCus - 1) / kCalCus;
+    do n_chunks = (int)(kCalCus * rounds / heads);
+    while (4 * (int64_t)n_chunks * heads < 3 * kCalCus * rounds++);
     if (n_chunks > most) n_chunks = most;
   } else {
     int want = 1024;

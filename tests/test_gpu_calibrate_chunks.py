@@ -46,3 +46,45 @@ def test_chunks_of_tokens(d, heads, m):
         bound = 2.0 ** -8 * np.abs(ref) + 2.0 ** -24 * 40 * 2 * cond * 3 + 1e-6
         err = np.abs(got[h] - ref)
         assert (err <= bound).all(), f"head {h}: max err {err.max():.3e}, bound {bound.flat[err.argmax()]:.3e}, cond {cond:.1f}"
+
+
+# (head dim, heads, tokens, chunk): fp32 sums of many tokens.  With 256 heads a chunk is as long as one may be, with 8 heads of
+# 12000 tokens as short as a workgroup per CU makes it.
+LONG_SUMS = [(128, 256, 32768, 1024), (64, 256, 32768, 1024), (128, 8, 12000, 256), (64, 96, 32768, 1024)]
+
+
+@pytest.mark.parametrize("d,heads,m,chunk", LONG_SUMS)
+def test_sums_are_as_good_as_those_of_short_chunks(d, heads, m, chunk):
+    """Keys that are nearly one direction: the map magnifies what the fp32 sums lose (by 1 / spread^2, 6e4), far beyond its own
+    rounding to bf16.  It may be off by as much as sums over chunks of `chunk` tokens would make it, 16 tokens at a time
+    into one accumulator that rounds to nearest, the chunks added in 64 bits."""
+    g = torch.Generator(device="cuda").manual_seed(d + heads)
+    spread = 2.0 ** -8
+    k, v = (torch.empty((heads, m, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    for h in range(heads):
+        size = 0.5 + 0.5 * torch.rand(m, 1, generator=g, device="cuda")
+        k[h] = (size * (1 + spread * torch.randn(m, d, generator=g, device="cuda"))).bfloat16()
+        v[h] = (k[h].float() @ (torch.randn(d, d, generator=g, device="cuda") / d ** 0.5)).bfloat16()
+    shape = pl.shape_of(dg.scaled(dg.CONFIGS["cfg2"], seq_len=m, head_dim=d, n_kv_heads=heads, n_q_heads=heads))
+    W = torch.full((heads, d, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    vb.vector_calibrate(shape, k, v, W, pl.alloc_workspace(vb.vector_calibrate_workspace_bytes(shape)))
+    torch.cuda.synchronize()
+    # root mean square of the relative error of a sum of equal terms: the k-th of a chunk's K additions rounds at k / K of the chunk,
+    # by 2^-24 / sqrt(3); the chunks' errors are independent
+    K, M = chunk / 16, m / 16
+    rel = 2.0 ** -24 / 3 ** 0.5 * K / (3 * M) ** 0.5
+    rng = np.random.default_rng(m)
+    got, off, magnified = W.double().cpu().numpy(), 0.0, 0.0
+    some = sorted({0, heads // 2, heads - 1})
+    for h in some:
+        kd, vd = k[h].double().cpu().numpy(), v[h].double().cpu().numpy()
+        gram, cross = kd.T @ kd, kd.T @ vd
+        ref = np.linalg.solve(gram, cross)
+        off += ((got[h] - ref) ** 2).mean() / len(some)
+        # what errors of that size do to the map
+        e = np.tril(rng.standard_normal((d, d)))
+        e = (e + np.tril(e, -1).T) * rel * gram
+        c = rng.standard_normal((d, d)) * rel * np.abs(cross)
+        magnified += (np.linalg.solve(gram, c - e @ ref) ** 2).mean() / len(some)
+    stored = (2.0 ** -9) ** 2 * (got[some] ** 2).mean()          # at most half a unit of bf16 per element
+    assert off <= magnified + stored, f"rms {off ** 0.5:.2e}, of the sums {magnified ** 0.5:.2e}, of bf16 {stored ** 0.5:.2e}"
