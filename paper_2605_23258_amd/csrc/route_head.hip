@@ -27,6 +27,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "plan.hpp"
 #include "route_common.hpp"
 
 namespace vec {
@@ -408,23 +409,6 @@ __global__ __launch_bounds__(NT) void route_head_kernel(RunArgs<HeadParams, RAGG
 
 int units_of(int seq_len) { return (seq_len + kUnit - 1) / kUnit; }
 
-// Units per part: the fewest with which `count` sequences of n_heads heads each have no more workgroups than one per CU
-// (or one per head).  A part takes as long as its units (rows to copy above all), whoever's they are: with as many parts for
-// every head, the workgroups of eight prompts of 2048 to 8192 tokens, 8 heads, ended 14 to 26 us after the start, now 15 to 23.5 (their
-// rows, 50 MB in and out, take 8 of it).
-int part_units(const int* seq_len, int count, int n_heads) {
-  int units = 1;
-  for (;; ++units) {
-    int64_t parts = 0, longest = 1;
-    for (int b = 0; b < count; ++b) {
-      const int64_t of = (units_of(seq_len[b]) + units - 1) / units;
-      parts += of;
-      longest = std::max(longest, of);
-    }
-    if (parts * n_heads <= 256 || longest == 1) return units;
-  }
-}
-
 void head_parts(int seq_len, int units, HeadParams& p) {
   p.units_per_part = units;
   p.parts = (units_of(seq_len) + units - 1) / units;
@@ -476,7 +460,8 @@ int launch_route_head(int n_kv_heads, int seq_len, const float* score, const flo
   if (rows)
     p.g = gather_params(*rows->shape, rows->k, rows->v, idx_retain, idx_approx, n_pool - n_approx, n_approx, rows->k_ret, rows->v_ret,
                         rows->k_apx, rows->cap_retain, rows->stack);
-  head_parts(seq_len, part_units(&seq_len, 1, n_kv_heads), p);
+  const int n_units = units_of(seq_len);
+  head_parts(seq_len, part_units(&n_units, 1, n_kv_heads), p);
   const HeadKernel<true, false> pooling(seq_len);
   const HeadKernel<false, false> given(seq_len);
   const auto k = pool ? pooling.kernel : given.kernel;
@@ -491,9 +476,12 @@ size_t route_head_table_bytes(int count) { return align_up(sizeof(HeadParams) * 
 int launch_route_head_ragged(const vector_shape& s, const RaggedSeq* seqs, int count, void* tables, hipStream_t stream) {
   if (count < 1 || count > kMaxRaggedSeqs || !route_head_pools(s.pool_kernel)) return VECTOR_ERR_ARG;
   HeadParams host[kMaxRaggedSeqs];
-  int lens[kMaxRaggedSeqs];
-  for (int b = 0; b < count; ++b) lens[b] = seqs[b].shape.seq_len;
-  const int units = part_units(lens, count, s.n_kv_heads), longest = *std::max_element(lens, lens + count);
+  int n_units[kMaxRaggedSeqs], longest = 0;
+  for (int b = 0; b < count; ++b) {
+    n_units[b] = units_of(seqs[b].shape.seq_len);
+    longest = std::max(longest, seqs[b].shape.seq_len);
+  }
+  const int units = part_units(n_units, count, s.n_kv_heads);
   RunArgs<HeadParams, true> args;
   std::fill(args.first, args.first + kMaxRaggedSeqs, 0xffff);
   unsigned grid = 0;

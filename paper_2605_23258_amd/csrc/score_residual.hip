@@ -18,6 +18,7 @@
 // chunks, and which kernel runs.  Both passes put all chunks of a KV head on one XCD.
 #include <algorithm>
 
+#include "plan.hpp"
 #include "score_stream.hpp"
 
 namespace vec {
@@ -44,14 +45,9 @@ int tokens_per_workgroup(const int* n, int count, int64_t heads, int tile) {
     for (int b = 0; b < count; ++b) total += heads * ((n[b] + tiles * tile - 1) / (tiles * tile));
     return total;
   };
-  int64_t lo = 1, hi = 1;                       // tiles per workgroup: the fewest that meet the target
-  for (int b = 0; b < count; ++b) hi = std::max<int64_t>(hi, (n[b] + tile - 1) / tile);
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) / 2;
-    if (workgroups(mid) <= target) hi = mid;
-    else lo = mid + 1;
-  }
-  return (int)(lo * tile);
+  int64_t most = 1;
+  for (int b = 0; b < count; ++b) most = std::max<int64_t>(most, (n[b] + tile - 1) / tile);
+  return (int)(smallest_step(most, target, workgroups) * tile);
 }
 constexpr int kMaxChunks = 256;                 // per head; reached by a single head
 
