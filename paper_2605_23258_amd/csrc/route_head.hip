@@ -197,7 +197,6 @@ __global__ __launch_bounds__(NT) void route_head_kernel(RunArgs<HeadParams, RAGG
   constexpr int NW = kWaves<NT>;
   const int n_units = (n + kUnit - 1) / kUnit;
   const int unit0 = part * p.units_per_part, unit1 = min(n_units, unit0 + p.units_per_part);      // what this workgroup emits
-  if (unit0 >= n_units) return;
   __shared__ HeadShared<NT> sh;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 

@@ -5,7 +5,8 @@
 // needs it, in operand order: a 32-row block of the query rows (a "unit"; two for more than 256 rows) and
 // one 32-dim block of W^T.  What streams is the token axis: tiles of 16 KB of keys (and as much of values) go
 // from memory straight into a ring of LDS stages (global_load_lds, 16 bytes a lane), three tiles ahead of
-// their use, with one barrier per tile.  The loads need no registers and no wave waits on its own trip to
+// their use, with one barrier per tile.  (Where the residual's products come a tile late, rotated keys and fp32, two tiles ahead, and the
+// values' blocks, outside the ring, while the tile itself is worked on: see Pass2Lds.)  The loads need no registers and no wave waits on its own trip to
 // memory, so the copies run on while the matrix cores and the exponentials work.
 // With keys in registers and query rows in LDS instead, a wave's next keys can only be asked for after the last product
 // of the tile, and the staging (query rows, W^T two bytes at a time) takes 5 us per workgroup: the times in brackets
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassArgs<RA
 
   int chunk = wg * p.chunks_per_wg;
   const int chunk_end = min(p.n_chunks, chunk + p.chunks_per_wg);
-  if (chunk >= chunk_end) return;
+  if (chunk >= chunk_end) return;                // as in pass 2
   const int t_begin = chunk * p.tpc1, t_end = min(p.n, chunk_end * p.tpc1);
   const int n_steps = (t_end - t_begin + S::kTokens - 1) / S::kTokens;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), half = lane >> 5, l31 = lane & 31;
@@ -591,6 +592,8 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   extern __shared__ __align__(16) unsigned char smem[];
 
   const int t_begin = wg * p.tokens_per_wg, t_end = min(p.n, t_begin + p.tokens_per_wg);
+  // Never taken: the grid has just the workgroups that have tokens.  But without it the kernels on rotated keys in unequal batches
+  // spill 8 to 19 registers more.
   if (t_begin >= t_end) return;
   const int n_steps = (t_end - t_begin + S::kTokens - 1) / S::kTokens;
   const int mass_end = min(t_end, p.n_prefix);          // the mass of window columns is never used
