@@ -51,9 +51,9 @@ BATCHES = {
 class RaggedBatch:
     """Seeded sequences of one layer, concatenated along the token axis, and their per-sequence sizes."""
 
-    def __init__(self, name):
-        base, over, lens, spare = BATCHES[name][:4]
-        given = BATCHES[name][4] if len(BATCHES[name]) > 4 else None
+    def __init__(self, case):
+        base, over, lens, spare = case[:4]
+        given = case[4] if len(case) > 4 else None
         self.cfg = dg.scaled(dg.CONFIGS[base], **over)
         self.lens = list(lens)
         self.layers = [wl.make_layer(dg.scaled(self.cfg, seq_len=n), layer=b) for b, n in enumerate(lens)]
@@ -115,7 +115,10 @@ def _blocks(rb, out, b):
 
 @pytest.mark.parametrize("name", list(BATCHES))
 def test_compress_batch_against_the_oracle_sequence_by_sequence(name):
-    rb = RaggedBatch(name)
+    against_the_oracle(RaggedBatch(BATCHES[name]), name)
+
+
+def against_the_oracle(rb, name):
     cfg = rb.cfg
     shape, dev, out = _run_batch(rb)
     w_wide = dg.widen(rb.W)
@@ -147,14 +150,18 @@ def test_compress_batch_against_the_oracle_sequence_by_sequence(name):
 def test_compress_batch_equals_one_call_per_sequence(name):
     """Bit for bit what vector_compress gives for each sequence alone, also where sequences share
     their launches (equal ones with their heads stacked, unequal ones over parameter tables)."""
-    rb = RaggedBatch(name)
+    equals_one_call_per_sequence(RaggedBatch(BATCHES[name]))
+
+
+def equals_one_call_per_sequence(rb):
     cfg = rb.cfg
     H, d = cfg.n_kv_heads, cfg.head_dim
+    tdt = torch.bfloat16 if cfg.dtype == "bf16" else torch.float32
     shape, dev, out = _run_batch(rb)
     for b, li in enumerate(rb.layers):
         n, n_p, n_a, n_r, cap = rb.lens[b], rb.n_pool[b], rb.n_approx[b], rb.n_retain[b], rb.cap[b]
         s1 = pl.shape_of(cfg, seq_len=n)
-        one = pl.alloc_outputs(s1, n_p, n_a, cap, torch.bfloat16)
+        one = pl.alloc_outputs(s1, n_p, n_a, cap, tdt)
         ws = pl.alloc_workspace(vb.vector_compress_workspace_bytes(s1, n_p, n_a))
         pl.compress_layer(s1, pl.to_device(li.q_win), pl.to_device(li.k), pl.to_device(li.v), dev["W"], n_p, n_a, one, ws,
                           cap_retain=cap, one_call=True)
@@ -171,7 +178,7 @@ def test_compress_batch_equals_one_call_per_sequence(name):
 
 
 def test_compress_batch_rejects_bad_sizes_before_any_launch():
-    rb = RaggedBatch("bf16_max_pool")
+    rb = RaggedBatch(BATCHES["bf16_max_pool"])
     cfg = rb.cfg
     shape = pl.shape_of(cfg, seq_len=1)
     H, d = cfg.n_kv_heads, cfg.head_dim
@@ -207,7 +214,7 @@ def test_compress_batch_rejects_bad_sizes_before_any_launch():
 def test_decode_over_per_sequence_blocks(name, flags):
     """Decode attention straight over the blocks vector_compress_batch wrote (each sequence with its
     own capacities), a few appended rows included, against the oracle sequence by sequence."""
-    rb = RaggedBatch(name)
+    rb = RaggedBatch(BATCHES[name])
     cfg = rb.cfg
     H, Hq, d, B = cfg.n_kv_heads, cfg.n_q_heads, cfg.head_dim, len(rb.lens)
     is_bf = cfg.dtype == "bf16"

@@ -14,13 +14,12 @@ CASES = {
     "wgs_five_heads_512_rows": ("cfg2", dict(n_kv_heads=5, n_q_heads=40, window=64), (700, 3333, 90), (1, 0, 0)),
     "wgs_sixty_four_prompts": ("cfg2", dict(n_kv_heads=2, n_q_heads=4, window=16, head_dim=64), tuple(100 + 37 * ((11 * i) % 64) for i in range(64)), (0,) * 64),
 }
-tb.BATCHES.update(CASES)
 
 
 @pytest.mark.parametrize("name", list(CASES))
 def test_equals_one_call_per_prompt(name):
-    tb.test_compress_batch_equals_one_call_per_sequence(name)
+    tb.equals_one_call_per_sequence(tb.RaggedBatch(CASES[name]))
 
 
 def test_against_the_oracle():
-    tb.test_compress_batch_against_the_oracle_sequence_by_sequence("wgs_three_heads")
+    tb.against_the_oracle(tb.RaggedBatch(CASES["wgs_three_heads"]), "wgs_three_heads")
