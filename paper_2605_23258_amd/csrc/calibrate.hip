@@ -8,7 +8,7 @@
 //   solve_kernel : grid (d / 16 column blocks, heads).  Blocked fp64 Cholesky of K^T K with the column
 //                  block of K^T V riding along, then the backward substitution; all on fp64 matrix
 //                  instructions out of LDS.
-// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 62 + 7 + 23 us (products, sums, solve; averages over inputs in turn).
+// At 65536 tokens x 8 heads, d = 128 (268 MB of keys and values): 58 + 7 + 23 us (products, sums, solve; averages over inputs in turn).
 #include <algorithm>
 
 #include "common.hpp"
@@ -56,9 +56,9 @@ struct CalParams {
 //   8 heads x 12000 tokens 1.2e-8 / 3.4e-8 / 1.0e-8, x 65536 6.4e-8 / 4.3e-8 / 1.2e-8; 32 x 65536 6.4e-8 / 4.7e-8 / 1.2e-8;
 //   96 x 65536 6.6e-8 / 8.3e-8 / 1.2e-8; 256 x 4096 9.9e-8 / 7.5e-8 / 4.5e-8, x 32768 7.0e-8 / 11.4e-8 / 1.6e-8.
 // All elements, keys and values of one sign, in units of the factors' norms: 8 x 12000 8e-9 / 11e-9 / 6e-9, x 65536 23e-9 / 12e-9 / 11e-9.
-// Bound: HBM, every key and value once and 27 MB of partials: 62 us at 65536 tokens x 8 heads, inputs in turn (4.8 TB/s; 56.5 at
-// best, 5.2; a plain copy moves 5.3).  Two workgroups of four waves on a CU, each with both products and chunks of 1024 tokens: 64 us (58 at best), and 12 in
-// place of 7 for the sums of twice the partials; 1474 tokens x 4 heads, d = 64: 21.8 -> 16.8 us for the fit.
+// Bound: HBM, every key and value once and 27 MB of partials: 58 us at 65536 tokens x 8 heads, inputs in turn (5.1 TB/s; 53.4 at
+// best, 5.5; a plain copy moves 5.3).  Two workgroups of four waves on a CU, each with both products and chunks of 1024 tokens: 64 us (58 at best), and 12 in
+// place of 7 for the sums of twice the partials; 1474 tokens x 4 heads, d = 64: 21.8 us for the fit, 17 with these.
 // ---------------------------------------------------------------------------
 constexpr int kGramThreads = 512;
 template <int D> struct GramTile {

@@ -90,9 +90,10 @@ __device__ __forceinline__ void xcd_chunk_head(int& chunk, int& h) {
   }
 }
 
-// RAGGED launches (several sequences of different lengths at once): launch head hv is head hv % seq_hps of sequence
-// hv / seq_hps, whose parameter block replaces the launch's own.  It is read with scalar loads, from behind
-// the launch's own parameters (the first kernel argument) or from a table that an earlier launch wrote.
+// RAGGED launches (several sequences of different lengths at once) over a grid of (the longest sequence's parts, heads of all):
+// launch head hv is head hv % seq_hps of sequence hv / seq_hps, whose parameter block replaces the launch's own.  It is
+// read with scalar loads, from behind the launch's own parameters (the first kernel argument) or from a table that an earlier
+// launch wrote.
 template <bool RAGGED, typename P>
 __device__ __forceinline__ void take_sequence(P& p, int& h) {
   if constexpr (RAGGED) {
@@ -127,7 +128,7 @@ __device__ __forceinline__ int take_workgroup(P& p, int& seq) {
 }
 
 // The parameters read anew, for what a kernel needs only at its end: held from the start they would fill the scalar
-// registers in between.  launch_head: the head as take_sequence was given it.  (Word by word through the constant
+// registers in between.  launch_head: the head among those of all sequences.  (Word by word through the constant
 // address space: that keeps the loads scalar behind the kernel's stores.)
 template <typename P> __device__ __forceinline__ P read_constant(uint64_t at) {
   typedef const __attribute__((address_space(4))) uint32_t* words;

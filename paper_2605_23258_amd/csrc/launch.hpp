@@ -66,7 +66,8 @@ float* score_mass(const vector_shape& s, void* ws);
 // its own blocks, its own workspace), and gets exactly the parameters that call would compute.
 // The parameter blocks are kernel arguments (KernelArgs), or go to `tables` (device,
 // ragged_table_bytes(count) bytes) where they are too many, and every workgroup picks its
-// sequence's block (launch head hv: sequence hv / Hkv, head hv % Hkv).
+// sequence's block: by its launch head hv (sequence hv / Hkv, head hv % Hkv; take_sequence), or, in launches of just
+// the workgroups that the sequences need (the two passes, the single-launch routing), by its number (RunArgs, take_workgroup).
 constexpr int kMaxRaggedSeqs = 64;
 struct RaggedSeq {
   vector_shape shape;

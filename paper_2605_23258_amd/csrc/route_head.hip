@@ -6,8 +6,9 @@
 // between them is a kernel boundary, and a boundary costs 4 us or more whatever the size.  So nothing is exchanged.
 // Every workgroup of a head loads the head's scores and residuals whole into registers (16384 tokens: 16 + 16 per
 // thread) and finds both thresholds itself; then it emits and copies its own part of the tokens.  The redundant
-// part is about 50 vector instructions and two LDS atomics per token and workgroup: 13.1 us at 8192 tokens x 8 heads (loads 1.6,
-// pooling 1.2, selections 3.4 and 2.8, list 1.4, rows 2), 18.6 at 12289 with a maximum pooled.
+// part is about 50 vector instructions and two LDS atomics per token and workgroup.  At 8192 tokens x 8 heads 13.1 us from the first
+// workgroup's start to the last one's end (a kernel trace has 15), 12 in the mean workgroup (loads 1.6, pooling 1.2, selections
+// 3.4 and 2.8, list 1.4, rows 2); at 12289 tokens with a maximum pooled 18.6 (19.4).
 //
 // The line to the two launches of route_compact.hip.  A whole compression pass in us, bf16, d = 128, 64 query rows,
 // this launch (with 24576 tokens in registers for the last two lengths) against the two:

@@ -17,9 +17,9 @@
 // the values staged with the keys, 20011 tokens x 8 heads took 2 us more, and fp32 at d = 128, which spilled 150 registers,
 // 1.5 to 1.9 times as long (a pass of 2546 tokens, 8 heads, 83 us, now 44).  Tiles of half the size (more of them on their way, a
 // barrier for every 32 tokens): 2.9 us per 64 tokens instead of 2.4.
-// Bounds (averages of back-to-back passes): 32768 tokens x 8 heads, 256 query rows: 26 us (28) for pass 1 and 37 us (39)
-// for pass 2, instruction issue; 131072 tokens, 128 rows: 61 us (63) and 103 us (107), HBM at 4.4 and 5.3 TB/s;
-// 8192 tokens: 8.5 us (9) and 13 us (19), latency.
+// Bounds (averages of a kernel trace of back-to-back passes): 32768 tokens x 8 heads, 256 query rows: 27 us (28) for pass 1 and 38 us (39)
+// for pass 2, instruction issue, at a clock of 2.0 GHz; 131072 tokens, 128 rows: 61 us (63) and 100 us (107), HBM at 4.4 and 5.4 TB/s;
+// 8192 tokens: 8.4 us (9) and 12 us (19), latency.
 // A lane's 16 bytes land at lane * 16, so rows cannot be padded: the 16-byte slots of a row are permuted by
 // the row instead (the lane fetches the piece that belongs in its slot), which keeps 16 rows read at one
 // piece in 16 different banks.
