@@ -56,9 +56,11 @@ struct CalParams {
 //   8 heads x 12000 tokens 1.2e-8 / 3.4e-8 / 1.0e-8, x 65536 6.4e-8 / 4.3e-8 / 1.2e-8; 32 x 65536 6.4e-8 / 4.7e-8 / 1.2e-8;
 //   96 x 65536 6.6e-8 / 8.3e-8 / 1.2e-8; 256 x 4096 9.9e-8 / 7.5e-8 / 4.5e-8, x 32768 7.0e-8 / 11.4e-8 / 1.6e-8.
 // All elements, keys and values of one sign, in units of the factors' norms: 8 x 12000 8e-9 / 11e-9 / 6e-9, x 65536 23e-9 / 12e-9 / 11e-9.
+// d = 64: the two halves' totals and last accumulators are added in 64 bits and rounded once: 8 x 12000 (K^T K, K^T V) 6.6e-9 and 6.9e-9;
+// rounded three times 8.1e-9 and 8.6e-9, chunks of 256 tokens in one run 8.9e-9 and 7.0e-9.
 // Bound: HBM, every key and value once and 27 MB of partials: 58 us at 65536 tokens x 8 heads, inputs in turn (5.1 TB/s; 53.4 at
 // best, 5.5; a plain copy moves 5.3).  Two workgroups of four waves on a CU, each with both products and chunks of 1024 tokens: 64 us (58 at best), and 12 in
-// place of 7 for the sums of twice the partials; 1474 tokens x 4 heads, d = 64: 21.8 us for the fit, 17 with these.
+// place of 7 for the sums of twice the partials; 1474 tokens x 4 heads, d = 64: 22.4 us for the fit, 17.9 with these.
 // ---------------------------------------------------------------------------
 constexpr int kGramThreads = 512;
 template <int D> struct GramTile {
@@ -147,28 +149,30 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(CalParams p) {
     step(0);
 #pragma unroll 2
     for (int i = 1; i < kSteps; ++i) step(i);
+    if (kShares == 1 || tile + 1 < n_tiles) {      // d = 64: the last tile's sums stay in acc
 #pragma unroll
-    for (int jb = 0; jb < JB; ++jb)
+      for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-      for (int x = 0; x < 16; ++x) total[jb][x] += acc[jb][x];
+        for (int x = 0; x < 16; ++x) total[jb][x] += acc[jb][x];
+    }
     if (tile + 1 < n_tiles) stash(tile + 1, (tile + 1) & 1);
     if (tile + 2 < n_tiles) fetch(tile + 2);
   }
-  if constexpr (kShares == 2) {              // the second half's tokens, through LDS
+  if constexpr (kShares == 2) {              // the second half's tokens, through LDS; the four sums are rounded once
     __syncthreads();
-    float* mine = reinterpret_cast<float*>(gram_lds) + (wave % (2 * JB)) * (JB * 16 * kWave) + lane;
+    double* mine = reinterpret_cast<double*>(gram_lds) + (wave % (2 * JB)) * (JB * 16 * kWave) + lane;
     if (share == 1) {
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-        for (int x = 0; x < 16; ++x) mine[(jb * 16 + x) * kWave] = total[jb][x];
+        for (int x = 0; x < 16; ++x) mine[(jb * 16 + x) * kWave] = (double)total[jb][x] + (double)acc[jb][x];
     }
     __syncthreads();
     if (share == 1) return;
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-      for (int x = 0; x < 16; ++x) total[jb][x] += mine[(jb * 16 + x) * kWave];
+      for (int x = 0; x < 16; ++x) total[jb][x] = (float)((double)total[jb][x] + (double)acc[jb][x] + mine[(jb * 16 + x) * kWave]);
   }
   // accumulator register x of block jb: row 32*ib + acc_row(x, half), column 32*jb + l31
   float* out = p.part + (((size_t)h * p.n_chunks + chunk) * 2 + (is_c ? 1 : 0)) * D * D;

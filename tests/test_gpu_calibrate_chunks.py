@@ -62,7 +62,7 @@ def test_chunks_of_tokens(d, heads, m, chunks):
 
 # (head dim, heads, tokens, chunk): fp32 sums of many tokens.  With 256 heads a chunk is as long as one may be, with 8 heads of
 # 12000 tokens as short as a workgroup per CU makes it.
-LONG_SUMS = [(128, 256, 32768, 1024), (64, 256, 32768, 1024), (128, 8, 12000, 256), (64, 96, 32768, 1024)]
+LONG_SUMS = [(128, 256, 32768, 1024), (64, 256, 32768, 1024), (128, 8, 12000, 256), (64, 8, 12000, 256), (64, 96, 32768, 1024)]
 
 
 @pytest.mark.parametrize("d,heads,m,chunk", LONG_SUMS)
