@@ -11,8 +11,8 @@
 // row_bytes/16 adjacent lanes, 16 bytes each, so every load instruction of a wave covers
 // 1 KiB of consecutive memory, and every cache row is read exactly once per step.
 //
-//   decode_split_mfma_kernel : bf16 caches.  grid (split, kv head, sequence); a workgroup owns
-//                           a range of rows of one segment (retained or approximated).  Waves
+//   decode_split_mfma_kernel : bf16 caches.  A workgroup owns a range of rows of one segment (retained or
+//                           approximated; see grid_split), or several ranges (see PlannedSplits).  Waves
 //                           park 32-row tiles in LDS and run both products (scores, then
 //                           weights times rows) on the matrix cores; see the comment above
 //                           the kernel.  Variants: ROPE (approximated rows are un-rotated
@@ -49,6 +49,11 @@ struct DecodeParams {
   float* part;            // [B, Hkv, S, 2*G + G*D] floats: (m, l)[G], acc[G][D]
   int B, Hq, Hkv, cap_retain, n_approx;
   int splits_ret, splits_apx;   // workgroups per (sequence, head) on each segment
+  int by_kind;                  // the grid is (KV head, sequence, split) and not (split, KV head, sequence)
+  // Sequences of different lengths (see PlannedSplits): [B, Hkv, 2] (first partial, number of partials) of either segment; and what
+  // a step of approximated rows counts in steps of retained ones
+  int2* plan;
+  float plan_apx;
   int64_t w_sh;           // element stride between per-head W
   float c2;               // scale * log2(e)
   int literal;            // approximated rows: rebuild v_hat = k W per row instead of (sum p k) W
@@ -70,20 +75,12 @@ __device__ __forceinline__ size_t retained_row(const SegmentRows& s, int r) {
   if (PAGED) return ((size_t)s.blocks[r >> s.block_shift] << s.block_shift) + (size_t)(r & ((1 << s.block_shift) - 1));
   return s.ret_row0 + (size_t)r;
 }
-__device__ __forceinline__ SegmentRows segment_rows(const DecodeParams& p, int b, int h) {
+// of a sequence with the capacity, approximated rows, live retained rows and first rows given
+__device__ __forceinline__ SegmentRows sequence_rows(const DecodeParams& p, int b, int h, int cap, int n_approx, int live, int64_t ret0, int64_t apx0) {
   SegmentRows s;
-  int cap = p.cap_retain;
-  s.n_approx = p.n_approx;
-  if (p.cap_retain_seq) {
-    cap = max(p.cap_retain_seq[b], 0);
-    s.n_approx = max(p.n_approx_seq[b], 0);
-    s.ret_row0 = (size_t)p.ret_row_start[b] + (size_t)h * cap;
-    s.apx_row0 = (size_t)p.apx_row_start[b] + (size_t)h * s.n_approx;
-  } else {
-    const size_t bh = (size_t)b * p.Hkv + h;
-    s.ret_row0 = bh * cap;
-    s.apx_row0 = bh * s.n_approx;
-  }
+  s.n_approx = n_approx;
+  s.ret_row0 = (size_t)ret0 + (size_t)h * cap;
+  s.apx_row0 = (size_t)apx0 + (size_t)h * n_approx;
   s.blocks = nullptr;
   s.block_shift = 0;
   if (p.block_table) {
@@ -91,11 +88,182 @@ __device__ __forceinline__ SegmentRows segment_rows(const DecodeParams& p, int b
     s.block_shift = p.block_shift;
     s.ret_row0 = 0;
   }
-  s.len_retain = min(max(p.len_retain[b], 0), cap);
+  s.len_retain = live;
   s.cap = cap;
   s.new_row = -1;
   if (p.k_new) { s.new_row = s.len_retain; s.len_retain += 1; }      // the new token is the last live row
   return s;
+}
+__device__ __forceinline__ SegmentRows segment_rows(const DecodeParams& p, int b, int h) {
+  int cap = p.cap_retain, n_approx = p.n_approx;
+  int64_t ret0 = (int64_t)b * p.Hkv * cap, apx0 = (int64_t)b * p.Hkv * n_approx;
+  if (p.cap_retain_seq) {
+    cap = max(p.cap_retain_seq[b], 0);
+    n_approx = max(p.n_approx_seq[b], 0);
+    ret0 = p.ret_row_start[b];
+    apx0 = p.apx_row_start[b];
+  }
+  return sequence_rows(p, b, h, cap, n_approx, min(max(p.len_retain[b], 0), cap), ret0, apx0);
+}
+
+constexpr int DT_ = 256;          // threads per workgroup
+constexpr int DW = DT_ / kWave;   // waves
+constexpr int kUnroll = 4;        // rows per lane group in flight
+
+// Rows of one segment of one (sequence, KV head) that a workgroup takes
+struct SplitRows {
+  int b, h;
+  bool is_apx;
+  int begin, end;
+  size_t slot;                    // of the partial
+  SegmentRows seg;
+};
+// One range per workgroup, the grid says which: as many splits for every sequence.  Ranges are multiples of STEP rows, so
+// that loads stay aligned to it.
+template <int STEP> __device__ __forceinline__ SplitRows grid_split(const DecodeParams& p) {
+  SplitRows r;
+  const int split = p.by_kind ? blockIdx.z : blockIdx.x;
+  r.h = p.by_kind ? blockIdx.x : blockIdx.y;
+  r.b = p.by_kind ? blockIdx.y : blockIdx.z;
+  r.seg = segment_rows(p, r.b, r.h);
+  r.is_apx = split >= p.splits_ret;
+  const int len = r.is_apx ? r.seg.n_approx : r.seg.len_retain;
+  const int n_sp = r.is_apx ? p.splits_apx : p.splits_ret, sp = r.is_apx ? split - p.splits_ret : split;
+  const int steps = (len + STEP - 1) / STEP;
+  r.begin = (int)((int64_t)steps * sp / n_sp) * STEP;
+  r.end = min(len, (int)((int64_t)steps * (sp + 1) / n_sp) * STEP);
+  r.slot = ((size_t)r.b * p.Hkv + r.h) * (p.splits_ret + p.splits_apx) + split;
+  return r;
+}
+
+// Sequences of different lengths: the same share of the work for every workgroup, wherever one sequence's rows end and
+// the next one's begin.  With as many splits for every sequence the longest are waited for.  The host does not know the live lengths;
+// every workgroup adds the work up itself, lane b that of sequence b.  The retained rows are one line, sequence after
+// sequence, head after head, and the approximated rows another; the first workgroups share the first, the others the second, so
+// that a CU, which gets two workgroups half a grid apart, has one of each (all of both lines in one, 32 sequences of up to
+// 32768 tokens 89 us, now 86; 16 of them 52.5, 48.6).  A segment is kPieceGranules for the change to it and one unit per granule
+// of 32 rows; a workgroup takes the granules that begin in its share.  A share has room for a step of granules, so a
+// segment's partials are those of workgroups next to each other, and (sequence, head), counted, keeps segments apart: place
+// workgroup + that number.  The workgroup with a segment's first granule says in `plan` where they begin and how many there are.
+//   A step, us, as many splits for every sequence / this: 24 sequences of 4000 to 16000 tokens on rotated keys 51.5 / 44.6, plain 43.1 /
+//   40.4; 16 of 8192 to 32768 62.2 / 52.2, plain 55.2 / 48.6.
+struct PlannedSequence { int cap, n_approx, live; long long ret0, apx0; };
+struct PlannedSplits {
+  const DecodeParams& p;
+  int id, share, lo, hi, log_rows;           // a granule is 1 << log_rows rows
+  int b, h, at;                              // the segment at hand begins at `at`
+  bool is_apx, done;
+  PlannedSequence s;                         // sequence b
+  // Scalars are kept scalar: the compiler would keep in vector registers what follows from a float or from memory.
+  static __device__ __forceinline__ int same(int x) { return __builtin_amdgcn_readfirstlane(x); }
+  static __device__ __forceinline__ long long same(long long x) { return ((long long)same((int)(x >> 32)) << 32) | (uint32_t)same((int)x); }
+  __device__ __forceinline__ int granules(int len) const { return (int)(((unsigned)len + (1u << log_rows) - 1u) >> log_rows); }
+  // of a sequence with nothing cached an empty granule, whose workgroup writes the empty partial
+  __device__ __forceinline__ int granules_ret(const PlannedSequence& x) const {
+    const int n = granules(x.live + (p.k_new ? 1 : 0));
+    return x.n_approx == 0 ? max(n, 1) : n;
+  }
+  static __device__ __forceinline__ int length(int n) { return n > 0 ? kPieceGranules + n : 0; }
+  static __device__ __forceinline__ PlannedSequence sequence(const DecodeParams& p, int i) {
+    const int cap = max(p.cap_retain_seq[i], 0);
+    return {cap, max(p.n_approx_seq[i], 0), min(max(p.len_retain[i], 0), cap), p.ret_row_start[i], p.apx_row_start[i]};
+  }
+  __device__ __forceinline__ explicit PlannedSplits(const DecodeParams& p_) : p(p_) {
+    const int lane = threadIdx.x & 63;
+    const PlannedSequence x = sequence(p, min(lane, p.B - 1));
+    // granules so long that a line stays shorter than kMaxPlanUnits: 32 rows unless the cache were larger than the memory
+    log_rows = kLogGranule;
+    int len_r = length(granules_ret(x)), len_a = length(granules(x.n_approx));
+    float top_r = wave_max_dpp((float)len_r), top_a = wave_max_dpp((float)len_a);
+    while (__builtin_expect(fmaxf(top_r, top_a) * (float)p.B * (float)p.Hkv >= (float)kMaxPlanUnits && log_rows < 30, 0)) {
+      log_rows = same(log_rows + 1);
+      len_r = length(granules_ret(x));
+      len_a = length(granules(x.n_approx));
+      top_r = wave_max_dpp((float)len_r);
+      top_a = wave_max_dpp((float)len_a);
+    }
+    const int seq_r = lane < p.B ? len_r * p.Hkv : 0, seq_a = lane < p.B ? len_a * p.Hkv : 0;
+    const int upto_r = wave_incl_scan_dpp(seq_r), upto_a = wave_incl_scan_dpp(seq_a);
+    const int total_r = __builtin_amdgcn_readlane(upto_r, 63), total_a = __builtin_amdgcn_readlane(upto_a, 63), wgs = gridDim.x;
+    const float work_r = (float)total_r, work_a = (float)total_a * p.plan_apx;
+    int wgs_r = same((int)((float)wgs * work_r * __builtin_amdgcn_rcpf(work_r + work_a) + 0.5f));
+    // by their work, but half of them where there are approximated rows to go with retained ones
+    wgs_r = max(total_a > 0 ? min(wgs_r, wgs / 2) : wgs, total_r > 0 ? 1 : 0);
+    id = blockIdx.x;
+    is_apx = id >= wgs_r;
+    const int mine = is_apx ? id - wgs_r : id, total = is_apx ? total_a : total_r;
+    // an even share, rounded up, and by as much as its float may be below it; no more than half of kMaxSplits for a segment
+    const float even = fmaxf((float)total * 1.000001f * __builtin_amdgcn_rcpf((float)(is_apx ? wgs - wgs_r : wgs_r)),
+                             (is_apx ? top_a : top_r) * (1.f / (float)(kMaxSplits / 2 - 2)));
+    share = max(same((int)even) + 1, kStepGranules);
+    lo = mine * share;
+    hi = lo + share;
+    done = lo >= total;                      // of small caches fewer workgroups than the grid has
+    b = h = at = 0;
+    s = PlannedSequence{};
+    if (done) return;
+    const int upto = is_apx ? upto_a : upto_r, of_sequence = is_apx ? seq_a : seq_r;
+    b = __popcll(__ballot(upto <= lo));
+    at = __builtin_amdgcn_readlane(upto - of_sequence, b);
+    const int head = __builtin_amdgcn_readlane(is_apx ? len_a : len_r, b);
+    h = same((int)((float)(lo - at) * __builtin_amdgcn_rcpf((float)head)));       // at most one off
+    if (h * head > lo - at) --h;
+    if ((h + 1) * head <= lo - at) ++h;
+    at += h * head;
+    auto of_b = [&](int v) VEC_INLINE { return __builtin_amdgcn_readlane(v, b); };
+    auto of_b64 = [&](long long v) VEC_INLINE { return ((long long)of_b((int)(v >> 32)) << 32) | (uint32_t)of_b((int)v); };
+    s = {of_b(x.cap), of_b(x.n_approx), of_b(x.live), of_b64(x.ret0), of_b64(x.apx0)};
+  }
+  // the next rows of this workgroup; false: there are none
+  __device__ __forceinline__ bool next(SplitRows& r) {
+    while (!done) {
+      const int n_r = granules_ret(s), n_a = granules(s.n_approx), n = is_apx ? n_a : n_r;
+      const int first = at + kPieceGranules;         // where granule 0 begins
+      const int g0 = max(lo - first, 0), g1 = min(hi - first, n);
+      const int pair = b * p.Hkv + h, place = id + pair + (is_apx ? p.B * p.Hkv : 0);
+      const bool any = g0 < g1;
+      if (any) {
+        r.b = b; r.h = h; r.is_apx = is_apx;
+        r.seg = sequence_rows(p, b, h, s.cap, s.n_approx, s.live, s.ret0, s.apx0);
+        r.begin = g0 << log_rows;
+        r.end = (int)min((int64_t)(is_apx ? r.seg.n_approx : r.seg.len_retain), (int64_t)g1 << log_rows);
+        r.slot = (size_t)place;
+        if (g0 == 0 && threadIdx.x == 0) {
+          p.plan[2 * pair + (is_apx ? 1 : 0)] = make_int2(place, (first + n - 1) / share - lo / share + 1);
+          if ((is_apx ? n_r : n_a) == 0) p.plan[2 * pair + (is_apx ? 0 : 1)] = make_int2(0, 0);
+        }
+      }
+      at += length(n);
+      done = at >= hi;
+      if (++h == p.Hkv) {
+        h = 0;
+        if (++b == p.B) done = true;
+        if (!done) {
+          const PlannedSequence x = sequence(p, b);
+          s = {same(x.cap), same(x.n_approx), same(x.live), same(x.ret0), same(x.apx0)};
+        }
+      }
+      if (any) return true;
+    }
+    return false;
+  }
+};
+
+// what a workgroup of a split launch does
+template <int STEP, bool PLANNED, typename F> __device__ __forceinline__ void for_split_rows(const DecodeParams& p, F attend) {
+  if constexpr (PLANNED) {
+    static_assert(STEP == kStepGranules << kLogGranule, "a step of the bf16 kernel");
+    PlannedSplits splits(p);
+    SplitRows r;
+    while (splits.next(r)) {
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));                  // what is made of it would be kept in registers from range to range
+      attend(r, tid);
+      __syncthreads();                               // LDS may be written again
+    }
+  } else {
+    attend(grid_split<STEP>(p), (int)threadIdx.x);
+  }
 }
 
 // The workgroup whose rows include the step's own token stores it in the cache (when the block has
@@ -103,22 +271,18 @@ __device__ __forceinline__ SegmentRows segment_rows(const DecodeParams& p, int b
 // the store.
 template <typename T, int D, bool PAGED>
 __device__ __forceinline__ void append_new_row(const DecodeParams& p, const SegmentRows& seg, bool is_apx, int row_begin, int row_end,
-                                               const T* k_new, const T* v_new) {
+                                               const T* k_new, const T* v_new, int tid) {
   constexpr int kPieces = D * (int)sizeof(T) / 16;
   if (is_apx || seg.new_row < row_begin || seg.new_row >= row_end || seg.new_row >= seg.cap) return;
-  if ((int)threadIdx.x < 2 * kPieces) {
-    const int piece = (int)threadIdx.x % kPieces;
-    const bool is_v = (int)threadIdx.x >= kPieces;
+  if (tid < 2 * kPieces) {
+    const int piece = tid % kPieces;
+    const bool is_v = tid >= kPieces;
     unsigned char* dst = reinterpret_cast<unsigned char*>(const_cast<void*>(is_v ? p.v_ret : p.k_ret)) +
                          retained_row<PAGED>(seg, seg.new_row) * D * sizeof(T) + piece * 16;
     const unsigned char* src = reinterpret_cast<const unsigned char*>(is_v ? v_new : k_new) + piece * 16;
     *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
   }
 }
-
-constexpr int DT_ = 256;          // threads per workgroup
-constexpr int DW = DT_ / kWave;   // waves
-constexpr int kUnroll = 4;        // rows per lane group in flight
 
 // sum over the LPR adjacent lanes that share a row; every lane of the group gets the total
 template <int LPR> __device__ __forceinline__ float group_sum(float x) {
@@ -138,8 +302,8 @@ template <int LPR> __device__ __forceinline__ float group_sum(float x) {
 // ROPE: the cache holds keys after their rotary embedding; logits use them as cached, and the rows
 // that stand in for values of approximated tokens are the keys turned back by their original
 // positions (rp.positions, one per row of k_apx).
-template <typename T, int D, int G, bool PAGED = false, bool ROPE = false>
-__global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeParams rp) {
+template <typename T, int D, int G, bool PAGED, bool ROPE>
+__device__ __forceinline__ void attend_rows(const DecodeParams& p, const RopeParams& rp, const SplitRows& range, int tid) {
   constexpr int E = Elem<T>::kPerChunk;          // elements per 16-byte piece
   constexpr int LPR = D / E;                     // lanes per row
   constexpr int RPI = kWave / LPR;               // rows per wave-wide load instruction
@@ -148,19 +312,14 @@ __global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeP
   __shared__ float ml_lds[DW][2][G];
   __shared__ float red_lds[DW][G][D];
 
-  const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int grp = lane / LPR, piece = lane % LPR;
-  const SegmentRows seg = segment_rows(p, b, h);
-  const bool is_apx = split >= p.splits_ret;
-  const int seg_len = is_apx ? seg.n_approx : seg.len_retain;
-  const int n_sp = is_apx ? p.splits_apx : p.splits_ret;
-  const int sp = is_apx ? split - p.splits_ret : split;
-  // ranges are multiples of the workgroup's row step so that loads stay aligned to it
   constexpr int kStepRows = DW * RPI * kUnroll;
-  const int steps = (seg_len + kStepRows - 1) / kStepRows;
-  const int row_begin = (int)((int64_t)steps * sp / n_sp) * kStepRows;
-  const int row_end = min(seg_len, (int)((int64_t)steps * (sp + 1) / n_sp) * kStepRows);
+  const int h = range.h, b = range.b;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int grp = lane / LPR, piece = lane % LPR;
+  const SegmentRows seg = range.seg;
+  const bool is_apx = range.is_apx;
+  const int seg_len = is_apx ? seg.n_approx : seg.len_retain;
+  const int row_begin = range.begin, row_end = range.end;
 
   const size_t bh = (size_t)b * p.Hkv + h;
   // a segment's rows: the approximated block, the retained block, or (paged) the retained pool
@@ -169,7 +328,7 @@ __global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeP
   auto seg_row = [&](int r) { return is_apx ? (size_t)r : retained_row<PAGED>(seg, r); };
   const T* k_new = p.k_new ? reinterpret_cast<const T*>(p.k_new) + bh * D : kseg;
   const T* v_new = p.k_new ? reinterpret_cast<const T*>(p.v_new) + bh * D : vseg;
-  append_new_row<T, D, PAGED>(p, seg, is_apx, row_begin, row_end, k_new, v_new);
+  append_new_row<T, D, PAGED>(p, seg, is_apx, row_begin, row_end, k_new, v_new, tid);
 
   // this lane's slice of the G query rows, pre-scaled into the log2 domain
   float qf[G][E];
@@ -331,8 +490,8 @@ __global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeP
   }
   __syncthreads();
 
-  float* out = p.part + (bh * (p.splits_ret + p.splits_apx) + split) * PSZ;
-  for (int i = threadIdx.x; i < G * D; i += DT_) {
+  float* out = p.part + range.slot * PSZ;
+  for (int i = tid; i < G * D; i += DT_) {
     const int g = i / D, j = i % D;
     float m = -INFINITY;
 #pragma unroll
@@ -345,8 +504,8 @@ __global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeP
     }
     out[2 * G + i] = a;
   }
-  if (threadIdx.x < G) {
-    const int g = threadIdx.x;
+  if (tid < G) {
+    const int g = tid;
     float m = -INFINITY, l = 0.f;
 #pragma unroll
     for (int wv = 0; wv < DW; ++wv) m = fmaxf(m, ml_lds[wv][0][g]);
@@ -358,6 +517,11 @@ __global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeP
     out[2 * g] = m;
     out[2 * g + 1] = l;
   }
+}
+template <typename T, int D, int G, bool PAGED = false, bool ROPE = false>
+__global__ __launch_bounds__(DT_) void decode_split_kernel(DecodeParams p, RopeParams rp) {
+  constexpr int kStepRows = DW * (kWave / (D / Elem<T>::kPerChunk)) * kUnroll;
+  for_split_rows<kStepRows, false>(p, [&](const SplitRows& r, int tid) VEC_INLINE { attend_rows<T, D, G, PAGED, ROPE>(p, rp, r, tid); });
 }
 
 // ---------------------------------------------------------------------------
@@ -394,8 +558,8 @@ template <int D> struct MfmaDecodeTile {
 // rows that stand in for values of approximated tokens are the keys turned back by their
 // original positions (rp.positions, one per row of k_apx), written to the second tile as bf16.
 // LITERAL: approximated rows are rebuilt one by one, v_hat = k W, before they are weighted.
-template <int D, int G, bool ROPE, bool LITERAL = false, bool PAGED = false>
-__global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams p, RopeParams rp) {
+template <int D, int G, bool ROPE, bool LITERAL, bool PAGED>
+__device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const RopeParams& rp, const SplitRows& range, int tid) {
   using T = bf16_t;
   using TL = MfmaDecodeTile<D>;
   constexpr int NC = D / 16;               // 16-element steps of the score contraction
@@ -418,18 +582,14 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
   };
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int l31 = lane & 31, half = lane >> 5;
-  const SegmentRows seg = segment_rows(p, b, h);
-  const bool is_apx = split >= p.splits_ret;
-  const int seg_len = is_apx ? seg.n_approx : seg.len_retain;
-  const int n_sp = is_apx ? p.splits_apx : p.splits_ret;
-  const int sp = is_apx ? split - p.splits_ret : split;
   constexpr int kStepRows = DW * kTileRows;
-  const int steps = (seg_len + kStepRows - 1) / kStepRows;
-  const int row_begin = (int)((int64_t)steps * sp / n_sp) * kStepRows;
-  const int row_end = min(seg_len, (int)((int64_t)steps * (sp + 1) / n_sp) * kStepRows);
+  const int h = range.h, b = range.b;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l31 = lane & 31, half = lane >> 5;
+  const SegmentRows seg = range.seg;
+  const bool is_apx = range.is_apx;
+  const int seg_len = is_apx ? seg.n_approx : seg.len_retain;
+  const int row_begin = range.begin, row_end = range.end;
 
   const size_t bh = (size_t)b * p.Hkv + h;
   // a segment's rows: the approximated block, the retained block, or (paged) the retained pool
@@ -438,7 +598,7 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
   auto seg_row = [&](int r) { return is_apx ? (size_t)r : retained_row<PAGED>(seg, r); };
   const T* k_new = p.k_new ? reinterpret_cast<const T*>(p.k_new) + bh * D : kseg;
   const T* v_new = p.k_new ? reinterpret_cast<const T*>(p.v_new) + bh * D : vseg;
-  append_new_row<T, D, PAGED>(p, seg, is_apx, row_begin, row_end, k_new, v_new);
+  append_new_row<T, D, PAGED>(p, seg, is_apx, row_begin, row_end, k_new, v_new, tid);
 
   unsigned char* k_tile = dec_lds + wave * 2 * TL::kTileBytes;
   unsigned char* v_tile = k_tile + TL::kTileBytes;
@@ -691,7 +851,7 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
   // do not use (32 rows of W^T per slot, same row stride as a tile).
   if (LITERAL && literal) {
     const T* Wh = reinterpret_cast<const T*>(p.W) + (int64_t)h * p.w_sh;
-    for (int idx = threadIdx.x; idx < D * D / 8; idx += DT_) {
+    for (int idx = tid; idx < D * D / 8; idx += DT_) {
       const int i = idx / (D / 8), j0 = (idx % (D / 8)) * 8;
       union { uint4 raw; unsigned short el[8]; } w;
       w.raw = load_chunk(Wh + (size_t)i * D + j0);
@@ -740,8 +900,8 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
   }
   __syncthreads();
   // a wave without rows has m = -inf and nothing but zeros: its share is 0 without a branch
-  float* out = p.part + (bh * (p.splits_ret + p.splits_apx) + split) * PSZ;
-  for (int i = threadIdx.x * 4; i < G * D; i += DT_ * 4) {
+  float* out = p.part + range.slot * PSZ;
+  for (int i = tid * 4; i < G * D; i += DT_ * 4) {
     const int g = i / D, j = i % D;
     float mw[DW], m = -INFINITY, l = 0.f;
 #pragma unroll
@@ -762,6 +922,26 @@ __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams 
       out[2 * g] = m;
       out[2 * g + 1] = l;
     }
+  }
+}
+template <int D, int G, bool ROPE, bool LITERAL = false, bool PAGED = false, bool PLANNED = false>
+__global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams p, RopeParams rp) {
+  for_split_rows<DW * kTileRows, PLANNED>(p, [&](const SplitRows& r, int tid) VEC_INLINE { attend_rows_mfma<D, G, ROPE, LITERAL, PAGED>(p, rp, r, tid); });
+}
+
+// The partials of a (sequence, KV head): those of the retained segment from `first` on, then those of the approximated one, `gap`
+// further on than the end of these
+struct MergeSplits {
+  int ret, apx, gap;
+  size_t first;
+  __device__ __forceinline__ size_t place(int split) const { return (size_t)(split + (split >= ret ? gap : 0)); }
+};
+template <bool PLANNED> __device__ __forceinline__ MergeSplits merge_splits(const DecodeParams& p, size_t bh) {
+  if constexpr (PLANNED) {
+    const int2 r = p.plan[2 * bh], a = p.plan[2 * bh + 1];
+    return {r.y, a.y, r.y > 0 && a.y > 0 ? a.x - r.x - r.y : 0, (size_t)(r.y > 0 ? r.x : a.x)};
+  } else {
+    return {p.splits_ret, p.splits_apx, 0, bh * (p.splits_ret + p.splits_apx)};
   }
 }
 
@@ -794,7 +974,7 @@ template <typename T, int D, int G> struct CombineLds {
 // (a step 11.7 us, now 11.2).  In the split launch's last workgroup of a (sequence, KV head) instead of a launch of its
 // own it is no faster: the acknowledgement of the written splits and the count of them take 1 us, as a launch does, and keep every
 // workgroup on its CU that much longer (11.6 / 12.1, and with 16 sequences of 32768 tokens 70.6 / 72.8).
-template <typename T, int D, int G>
+template <typename T, int D, int G, bool PLANNED = false>
 __global__ __launch_bounds__(DT_) void decode_combine_kernel(DecodeParams p) {
   using L = CombineLds<T, D, G>;
   constexpr int kFlight = 8, PSZ = 2 * G + G * D;
@@ -811,8 +991,9 @@ __global__ __launch_bounds__(DT_) void decode_combine_kernel(DecodeParams p) {
   float* inv = reinterpret_cast<float*>(lds + L::kInv);
   const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const size_t bh = (size_t)b * p.Hkv + h;
-  const int n_splits = p.splits_ret + p.splits_apx, n_ret = p.literal ? n_splits : p.splits_ret;      // literal partials are values already
-  const float* part = p.part + bh * n_splits * PSZ;
+  const MergeSplits cut = merge_splits<PLANNED>(p, bh);
+  const int n_splits = cut.ret + cut.apx, n_ret = p.literal ? n_splits : cut.ret;      // literal partials are values already
+  const float* part = p.part + cut.first * PSZ;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5, l31 = lane & 31;
   const bool use_w = p.n_approx > 0 && !p.literal;
 
@@ -835,7 +1016,7 @@ __global__ __launch_bounds__(DT_) void decode_combine_kernel(DecodeParams p) {
     const int at = min(round * DT_ + quad, L::kQuads - 1) * 4;
 #pragma unroll
     for (int u = 0; u < kFlight; ++u) {
-      x[u] = *reinterpret_cast<const f32x4_u*>(part + (size_t)min(s0 + u * L::kSide, n_splits - 1) * PSZ + 2 * G + at);
+      x[u] = *reinterpret_cast<const f32x4_u*>(part + cut.place(min(s0 + u * L::kSide, n_splits - 1)) * PSZ + 2 * G + at);
     }
   };
   uint4 wraw[WL];
@@ -850,7 +1031,7 @@ __global__ __launch_bounds__(DT_) void decode_combine_kernel(DecodeParams p) {
   if (!L::kMfma) load_w();                       // the larger part of what is read
   float2 ml[RW];
 #pragma unroll
-  for (int i = 0; i < RW; ++i) ml[i] = *reinterpret_cast<const float2*>(part + (size_t)min(lane, n_splits - 1) * PSZ + 2 * min(wave + i * DW, G - 1));
+  for (int i = 0; i < RW; ++i) ml[i] = *reinterpret_cast<const float2*>(part + cut.place(min(lane, n_splits - 1)) * PSZ + 2 * min(wave + i * DW, G - 1));
   load_splits(0, min(side, n_splits - 1), x0);
   if (L::kMfma) load_w();
 #pragma unroll
@@ -1176,15 +1357,42 @@ int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t st
   const ApproxRows kind = rope ? ApproxRows::kTurned : p.literal ? ApproxRows::kRebuilt : ApproxRows::kPlain;
   const SplitCosts costs = split_costs(Elem<T>::kDtype == VECTOR_BF16, D, G, kind, workgroups_per_cu<Kernel>(lds));
   static_assert(Elem<T>::kDtype == VECTOR_BF16 ? DW * kTileRows == 128 : DW * kWave * 4 * kUnroll == 4096, "the rows of a step that split_costs states");
-  pick_splits(costs, c.batch, c.n_kv_heads, c.cap_retain, c.n_approx, p.splits_ret, p.splits_apx);
-  const dim3 grid(p.splits_ret + p.splits_apx, c.n_kv_heads, c.batch);
+  // paged: a range's block ids fit a register across the wave, see tile_in_block
+  const int least_ret = c.ret_block_table ? (int)(((int64_t)c.cap_retain + (int64_t)(kWave - 1) * c.ret_block_rows - 1) / ((int64_t)(kWave - 1) * c.ret_block_rows)) : 1;
+  p.by_kind = kind == ApproxRows::kPlain && costs.one_round &&
+              pick_one_round(costs, c.batch, c.n_kv_heads, c.cap_retain, c.n_approx, least_ret, p.splits_ret, p.splits_apx);
+  if (!p.by_kind) pick_splits(costs, c.batch, c.n_kv_heads, c.cap_retain, c.n_approx, p.splits_ret, p.splits_apx);
+  const unsigned splits = p.splits_ret + p.splits_apx, heads = c.n_kv_heads, batch = c.batch;
+  const dim3 grid = p.by_kind ? dim3(heads, batch, splits) : dim3(splits, heads, batch);
   VEC_LAUNCH(K_DECODE_SPLIT, Kernel, grid, dim3(DT_), lds, stream, p, rope ? *rope : RopeParams{});
+  return VECTOR_OK;
+}
+
+// Sequences of different lengths, and their merge
+template <auto Kernel, typename T, int D, int G>
+int launch_planned(const vector_cache& c, DecodeParams& p, hipStream_t stream, const RopeParams* rope) {
+  constexpr int lds = MfmaDecodeTile<D>::kLdsBytes, merge_lds = CombineLds<T, D, G>::kTotal;
+  constexpr auto merge = decode_combine_kernel<T, D, G, true>;
+  VEC_HIP(set_max_lds(reinterpret_cast<const void*>(Kernel), lds));
+  VEC_HIP(set_max_lds(reinterpret_cast<const void*>(merge), merge_lds));
+  const int pairs = c.batch * c.n_kv_heads;
+  p.plan_apx = rope ? kPlanTurned : 1.f;
+  p.plan = reinterpret_cast<int2*>(p.part + (size_t)pairs * kMaxSplits * (2 * G + G * D));      // behind the partials, half of the workspace
+  VEC_LAUNCH(K_DECODE_SPLIT, Kernel, dim3(plan_workgroups(workgroups_per_cu<Kernel>(lds), pairs)), dim3(DT_), lds, stream, p, rope ? *rope : RopeParams{});
+  VEC_LAUNCH(K_DECODE_COMBINE, merge, dim3(c.n_kv_heads, c.batch), dim3(DT_), merge_lds, stream, p);
+  VEC_HIP(hipGetLastError());
   return VECTOR_OK;
 }
 
 template <typename T, int D, int G, bool PAGED>
 int run_decode_layout(const vector_cache& c, DecodeParams& p, hipStream_t stream, const RopeParams* rope) {
   int rc;
+  if constexpr (!PAGED && Elem<T>::kDtype == VECTOR_BF16) {
+    if (c.cap_retain_seq && !p.literal && worth_a_plan(c.batch, c.cap_retain, c.n_approx)) {
+      if (rope) return launch_planned<decode_split_mfma_kernel<D, G, true, false, false, true>, T, D, G>(c, p, stream, rope);
+      return launch_planned<decode_split_mfma_kernel<D, G, false, false, false, true>, T, D, G>(c, p, stream, rope);
+    }
+  }
   if constexpr (Elem<T>::kDtype == VECTOR_BF16) {
     constexpr int lds = MfmaDecodeTile<D>::kLdsBytes;
     if (rope) rc = launch_split<decode_split_mfma_kernel<D, G, true, false, PAGED>, T, D, G>(c, p, lds, stream, rope);
@@ -1233,7 +1441,8 @@ int run_decode_g(const vector_cache& c, DecodeParams& p, hipStream_t stream, con
 }  // namespace
 
 size_t decode_workspace_bytes(int batch, int n_q_heads, int n_kv_heads, int head_dim, int cap_retain, int n_approx) {
-  // sized for the largest split count so that the bound holds for any live length (twice what a launch writes)
+  // sized for the largest split count so that the bound holds for any live length (twice what a launch writes; a planned
+  // one keeps its plan in the other half)
   (void)cap_retain; (void)n_approx;
   const int G = n_q_heads / n_kv_heads;
   return align_up((size_t)batch * n_kv_heads * 2 * kMaxSplits * (2 * G + G * head_dim) * sizeof(float), 256);
@@ -1255,6 +1464,9 @@ int launch_decode_attn(const vector_cache& c, const void* q, float scale, void* 
   p.B = c.batch; p.Hq = c.n_q_heads; p.Hkv = c.n_kv_heads; p.cap_retain = c.cap_retain; p.n_approx = c.n_approx;
   p.w_sh = c.w_shared ? 0 : (int64_t)c.head_dim * c.head_dim;
   p.c2 = scale * kLog2e;
+  p.plan = nullptr;
+  p.plan_apx = 0.f;
+  p.by_kind = 0;
   if (c.dtype == VECTOR_BF16) {
     if (c.head_dim == 128) return run_decode_g<bf16_t, 128>(c, p, stream, rope);
     if (c.head_dim == 64) return run_decode_g<bf16_t, 64>(c, p, stream, rope);

@@ -28,6 +28,7 @@ struct SplitCosts {
   double alone_ret, full_ret, alone_apx, full_apx;      // a step of retained rows (keys and values), of approximated ones (keys)
   double full_at, by_cu, last, idle, slot, trip;
   int per_trip, per_long_trip;           // splits: up to per_trip of them, and more
+  bool one_round;                        // pick_one_round first
 };
 
 enum class ApproxRows { kPlain, kTurned, kRebuilt };
@@ -57,6 +58,7 @@ constexpr SplitCosts split_costs(bool bf16, int head_dim, int group, ApproxRows 
     c.full_at = rebuilt ? 512.0 : 300.0;
     c.last = 0.25;
     c.slot = 0.08;
+    c.one_round = true;
   } else if (bf16) {
     c.step_rows = 128;
     c.start = 5.0;
@@ -107,6 +109,48 @@ inline void pick_splits(const SplitCosts& c, int batch, int n_kv_heads, int cap_
     if (best < 0.0 || t < best) { best = t; s_ret = r; s_apx = a; }
     if (rounds > 4.0) break;                     // more would only add starts
   }
+}
+
+// Splits that make one round of workgroups, with as few steps as can be in the longest piece of either segment (and no more splits
+// than that takes); at least least_ret of them for the retained one.  For plain rows of 128 dims in bf16, whose launch puts the
+// retained pieces of all sequences first, the approximated ones behind them: the workgroups of a CU, half a grid apart, are then one
+// of each where there are as many of both, and every XCD has both kinds.  (In the order (split, head, sequence) an XCD has one
+// split of eight, often all retained or all approximated.)  A step, us, the estimate of before in its order / these / these in that order:
+//   16 sequences of 32768 tokens 70.6 (4 + 2) / 64.4 (2 + 2) / 71.4; 13 66.7 (2 + 1) / 56.6; 10 48.9 / 45.7 / 50.3; 4 23.0 / 22.3; 1 15.4 (28 + 13) /
+//   15.1; 24 of 16000 64.4 / 55.1 / 62.8; 32 of 8000 44.7 / 39.8 / 42.8; 64 of 8000 73.8 / 73.9; 1 of 8192 11.5 / 10.7.
+//   Four times as many approximated rows as retained ones 75.2 / 70.9; four times as many retained ones 93.3 / 97.7 (26.7 / 27.1 for nine
+//   sequences of 12000): more than three times as many are left to the estimate.  Rotated keys (approximated rows are vector
+//   work) 69.2 / 82, and rows of 64 dims 37.1 / 37.5, 30.8 / 32.9, 14.7 / 14.7: the estimate.
+inline bool pick_one_round(const SplitCosts& c, int batch, int n_kv_heads, int cap_retain, int n_approx, int least_ret, int& s_ret, int& s_apx) {
+  const int64_t steps_r = ((int64_t)cap_retain + c.step_rows - 1) / c.step_rows, steps_a = ((int64_t)n_approx + c.step_rows - 1) / c.step_rows;
+  if (steps_r == 0 || steps_a == 0 || steps_r > 3 * steps_a) return false;
+  const int64_t pairs = (int64_t)batch * n_kv_heads;
+  const int most = (int)std::max<int64_t>(2, std::min<int64_t>(kMaxSplits, 256 * c.per_cu / pairs));
+  double best = -1.0;
+  for (int r = std::max(1, least_ret); r < most && r <= steps_r; ++r) {
+    const int64_t long_r = (steps_r + r - 1) / r;
+    // as many as bring the approximated segment's pieces down to the retained one's, if there are that many
+    int64_t a = std::min<int64_t>(std::min<int64_t>(most - r, steps_a), (steps_a + long_r - 1) / long_r);
+    const int64_t long_a = (steps_a + a - 1) / a;
+    a = (steps_a + long_a - 1) / long_a;
+    const double t = (double)std::max(long_r, long_a) + 0.02 * (double)(r + a);
+    if (best < 0.0 || t < best) { best = t; s_ret = r; s_apx = (int)a; }
+  }
+  return best >= 0.0;
+}
+
+// Sequences of different lengths, whose live rows only the device knows, cut by a plan that the split launch makes (PlannedSplits in
+// decode_attn.hip): granules of 32 rows, four to a step; what the change to another segment costs, in granules (fitted to the workgroups'
+// ends: 0.5 us a granule with the chip full, 5 a change; 4, 6 and 9 measured); and how long a line of granules may be.
+constexpr int kLogGranule = 5, kStepGranules = 4, kPieceGranules = 6, kMaxPlanned = 64, kMaxPlanUnits = 1 << 28;
+constexpr float kPlanTurned = 1.86f;   // a granule of approximated rows that are turned back, in plain ones
+// As many workgroups as run at the same time.  Their partials, and one more for every segment, of which there are two per (sequence,
+// head), are to fit kMaxSplits per pair.
+constexpr int plan_workgroups(int per_cu, int pairs) { return 256 * per_cu < (kMaxSplits - 2) * pairs ? 256 * per_cu : (kMaxSplits - 2) * pairs; }
+// A lane per sequence; and segments long enough for the plan to pay (a step of 24 sequences on rotated keys, as many splits for every
+// one / a plan: 5500 tokens 26.9 / 24.3 us at 18 steps; 32 of 4000, 11 steps, 24.8 / 26.7; two of 12000, 22 steps, 15.2 / 15.6).
+constexpr bool worth_a_plan(int batch, int cap_retain, int n_approx) {
+  return batch > 1 && batch <= kMaxPlanned && ((int64_t)cap_retain + 127) / 128 + ((int64_t)n_approx + 127) / 128 >= 16;
 }
 
 }  // namespace vec

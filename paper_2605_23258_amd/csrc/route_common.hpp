@@ -82,18 +82,6 @@ __device__ __forceinline__ DigitMap digit_map_for_sample(unsigned long long cnt,
 // ---------------------------------------------------------------------------
 // prefix sums inside a wave on the DPP network
 // ---------------------------------------------------------------------------
-template <int CTRL, int ROW_MASK> __device__ __forceinline__ int dpp_take(int v) {   // 0 where no lane feeds this one
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, false);
-}
-__device__ __forceinline__ int wave_incl_scan_dpp(int v) {
-  v += dpp_take<0x111, 0xf>(v);      // row_shr:1 .. 8: inclusive scan inside each row of 16 lanes
-  v += dpp_take<0x112, 0xf>(v);
-  v += dpp_take<0x114, 0xf>(v);
-  v += dpp_take<0x118, 0xf>(v);
-  v += dpp_take<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
-  v += dpp_take<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
-  return v;
-}
 __device__ __forceinline__ int wave_total_of_scan(int incl) { return __builtin_amdgcn_readlane(incl, 63); }
 
 

@@ -105,3 +105,34 @@ def test_splits_are_among_the_fastest_measured(tmp_path):
     lines = "".join("  { int r, a; vec::pick_splits(vec::split_costs(%d, %d, %d, (vec::ApproxRows)%d, %d), %d, %d, %d, %d, r, a); char s[32]; sprintf(s, \" %%d+%%d \", r, a);"
                     " if (!strstr(\" %s \", s)) { printf(\"%s:%%s\\n\", s); bad = 1; } }\n" % (shape + (fast, shape)) for shape, fast in MEASURED)
     run(tmp_path, '#include <cstdio>\n#include <cstring>\n#include "decode_rows.hpp"\nint main() {\n  int bad = 0;\n' + lines + "  return bad;\n}\n")
+
+
+# the same for the splits of one round
+ONE_ROUND = r"""
+#include <cstdio>
+#include "decode_rows.hpp"
+int main() {
+  const int rows[] = {0, 1, 20, 128, 129, 1000, 5000, 40000, 1000000, 2147483647};
+  for (int per_cu = 1; per_cu <= 4; ++per_cu)
+    for (int pairs : {1, 2, 3, 8, 64, 100, 300, 5000})
+      for (int least : {1, 2, 70})
+        for (int cap : rows)
+          for (int n : rows) {
+            int r = -1, a = -1;
+            const vec::SplitCosts costs = vec::split_costs(true, 128, 4, vec::ApproxRows::kPlain, per_cu);
+            if (!vec::pick_one_round(costs, pairs, 1, cap, n, least, r, a)) continue;
+            const long long round = 256 * per_cu > 2 * pairs ? 256 * per_cu : 2 * pairs;
+            if (cap == 0 || n == 0 || r < least || r < 1 || a < 1 || r + a > vec::kMaxSplits || (long long)pairs * (r + a) > round ||
+                r > (cap + 127ll) / 128 || a > (n + 127ll) / 128) {
+              printf("%d per CU, %d pairs, %d and %d rows: %d + %d\n", per_cu, pairs, cap, n, r, a);
+              return 1;
+            }
+          }
+  return 0;
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
+def test_splits_of_one_round_make_one(tmp_path):
+    run(tmp_path, ONE_ROUND)
