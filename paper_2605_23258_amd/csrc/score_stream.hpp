@@ -241,10 +241,39 @@ template <typename T, int D> struct KeyOperands {
   }
 };
 
+// A wave's units of query rows, through LDS of its own: whole rows with one load, laid out as a subtile of keys is.  (Asked for in
+// operand order, 16 bytes of 64 different rows with one load, they kept a CU's address unit busy for 1.1 us per eight units.)
+template <typename T, int D> struct QueryUnit {
+  using S = Stream<T, D>;
+  static constexpr int kBytes = 32 * S::kRowBytes, kLoads = kBytes / (kWave * 16);
+  // rows unit * 32 .. of the `R` at `rows`; those beyond are copies of the last
+  static __device__ __forceinline__ void load(uint32_t lds, const T* rows, int unit, int R, int lane) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int row = i * S::kRowsPerLoad + lane / S::kPieces, piece = (lane % S::kPieces) ^ S::twist(row);
+      load_to_lds16(lds + i * 1024, reinterpret_cast<const unsigned char*>(rows) + (size_t)min(unit * 32 + row, R - 1) * S::kRowBytes + piece * 16);
+    }
+  }
+  // operand chunk c of the lane's row
+  static __device__ __forceinline__ chunk_t read(uint32_t lds, int row, int half, int c) { return lds_read16(lds + operand_at<T, D>(row, half, c)); }
+};
+
 // ---------------------------------------------------------------------------
 // pass 1: per-row softmax statistics over a chunk of tokens
 // ---------------------------------------------------------------------------
 constexpr int kStages1 = 4;
+// LDS of pass 1: the ring, [2][4][32] float2 for the waves that share a unit, and the query rows on their way into the registers, where
+// there is room for them; else in the place of the tiles after the first.  bf16 rows of 64 dims and one unit a wave: two workgroups
+// fit a CU as long as they have no more than the ring; their query rows go straight into the registers.
+template <typename T, int D, int NRB> struct Pass1Lds {
+  static constexpr int kQueryBytes = kStreamWaves * WaveWork<T, D, NRB>::U * QueryUnit<T, D>::kBytes;
+  static constexpr bool kThrough = !(sizeof(T) == 2 && D == 64 && NRB < 16);
+  static constexpr int kRing = kStages1 * kStreamTileBytes, kShares = kRing, kSharesEnd = kRing + kStreamWaves * 32 * (int)sizeof(float2);
+  static constexpr bool kApart = kSharesEnd + kQueryBytes <= (int)kMaxLdsBytes;
+  static constexpr int kQuery = kApart ? kSharesEnd : kStreamTileBytes;
+  static constexpr int kTotal = !kThrough ? kSharesEnd : kQuery + kQueryBytes > kSharesEnd ? kQuery + kQueryBytes : kSharesEnd;
+  static_assert(kTotal <= (int)kMaxLdsBytes, "LDS");
+};
 
 template <typename T, int D, int NRB, bool RAGGED>
 __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassArgs<RAGGED> args) {
@@ -254,7 +283,8 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassArgs<RA
   using S = Stream<T, D>;
   using WW = WaveWork<T, D, NRB>;
   constexpr int NC = S::NC, U = WW::U, PH = WW::PH;
-  extern __shared__ __align__(16) unsigned char smem[];        // [kStages1][tile], then [2][4][32] float2
+  using L = Pass1Lds<T, D, NRB>;
+  extern __shared__ __align__(16) unsigned char smem[];
 
   int chunk = wg * p.chunks_per_wg;
   const int chunk_end = min(p.n_chunks, chunk + p.chunks_per_wg);
@@ -263,7 +293,7 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassArgs<RA
   const int n_steps = (t_end - t_begin + S::kTokens - 1) / S::kTokens;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), half = lane >> 5, l31 = lane & 31;
   const WW ww(wave);
-  float2* grp = reinterpret_cast<float2*>(smem + kStages1 * S::kTileBytes);
+  float2* grp = reinterpret_cast<float2*>(smem + L::kShares);
   const uint32_t smem0 = lds_address(smem);
 
   TileSource<T, D> keys;
@@ -281,12 +311,25 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassArgs<RA
   // this wave's query rows: zero beyond R
   chunk_t qf[U][NC];
   int qrow[U];
+  const T* q_rows = reinterpret_cast<const T*>(p.q) + ((size_t)h * p.q_head_rows + p.q_row0) * D;
+  using Q = QueryUnit<T, D>;
+  const uint32_t q_lds = smem0 + L::kQuery + wave * U * Q::kBytes;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     qrow[u] = (ww.unit + 8 * u) * 32 + l31;
-    const T* row = reinterpret_cast<const T*>(p.q) + ((size_t)h * p.q_head_rows + p.q_row0 + min(qrow[u], p.R - 1)) * D;
+    if constexpr (L::kThrough) {
+      Q::load(q_lds + u * Q::kBytes, q_rows, ww.unit + 8 * u, p.R, lane);
+    } else {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) qf[u][c] = load_chunk(row + chunk_elem_offset<T>(c, half));
+      for (int c = 0; c < NC; ++c) qf[u][c] = load_chunk(q_rows + (size_t)min(qrow[u], p.R - 1) * D + chunk_elem_offset<T>(c, half));
+    }
+  }
+  if constexpr (L::kThrough) {
+    wait_loads<0>();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) qf[u][c] = Q::read(q_lds + u * Q::kBytes, l31, half, c);
   }
 #pragma unroll
   for (int u = 0; u < U; ++u)
@@ -295,6 +338,7 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassArgs<RA
       if (qrow[u] >= p.R) qf[u][c] = make_uint4(0, 0, 0, 0);
       asm volatile("" : "+v"(qf[u][c].x), "+v"(qf[u][c].y), "+v"(qf[u][c].z), "+v"(qf[u][c].w));     // arrived: no wait on them below
     }
+  if constexpr (L::kThrough && !L::kApart) tile_barrier();      // everyone's rows are out of the tiles' places
 #pragma unroll
   for (int s = 1; s < kStages1 - 1; ++s)
     if (to_fetch > 0) fetch();
@@ -1201,7 +1245,7 @@ int launch_passes_units(PassArgs<RAGGED>& a, const PassLaunch& L, hipStream_t st
   using Args = PassArgs<RAGGED>;
   const dim3 grid1 = L.grid1, grid2 = L.grid2;
   if (L.do_mass && !L.pp.lse) {               // pass 1; not needed when the caller brings the rows' log-sum-exp
-    constexpr size_t lds = kStages1 * Stream<T, D>::kTileBytes + kStreamWaves * 32 * sizeof(float2);
+    constexpr size_t lds = Pass1Lds<T, D, NRB>::kTotal;
     auto k1 = score_stats_kernel<T, D, NRB, RAGGED>;
     VEC_HIP(set_max_lds(reinterpret_cast<const void*>(k1), lds));
     if constexpr (RAGGED) std::copy(L.first1, L.first1 + kMaxRaggedSeqs, a.first);
