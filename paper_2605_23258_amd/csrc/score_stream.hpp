@@ -609,7 +609,14 @@ template <typename T, int D, int NRB, bool MASS, bool RES, bool ROPE> struct Pas
   static constexpr int kResSums = kMassSums + kSlots * kMassStep;                        // [kResSlots][kSub][JB][32]
   static constexpr int kEnd = kResSums + kResSlots * kResStep;
   static constexpr int kBias = kBiasInTurned ? kTurned + kTurnedBytes : kEnd;
-  static constexpr int kTotal = kBiasInTurned ? kEnd : kEnd + kBiasBytes;
+  // The query rows pass through the places of the tiles after the first and of what lies behind these, until a barrier after which the
+  // tiles are asked for and W and the biases are put down.  Not those of rotated fp32 keys of 128 dims: the kernels would spill
+  // up to six registers more (2546 to 8192 tokens, 8 heads, 1.4 % longer).
+  static constexpr bool kThrough = MASS && !(ROPE && sizeof(T) == 4 && D == 128);
+  static constexpr int kQuery = kStageBytes, kQueryBytes = kThrough ? kStreamWaves * WW::U * QueryUnit<T, D>::kBytes : 0;
+  static constexpr int kW = ROPE ? kTurned : (kStages - 1) * kStageBytes;      // W on its way into the registers
+  static constexpr int kUsed = kBiasInTurned ? kEnd : kEnd + kBiasBytes;
+  static constexpr int kTotal = kQuery + kQueryBytes > kUsed ? kQuery + kQueryBytes : kUsed;
   static_assert(kTotal <= (int)kMaxLdsBytes, "LDS");
 };
 
@@ -675,13 +682,19 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // ---- what stays in registers ----
   chunk_t qf[U][NC], wf[NC];
   int qrow[U];
+  using Q = QueryUnit<T, D>;
+  const uint32_t q_lds = smem0 + L::kQuery + wave * U * Q::kBytes;
   if (MASS) {
+    const T* q_rows = reinterpret_cast<const T*>(p.q) + ((size_t)h * p.q_head_rows + p.q_row0) * D;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       qrow[u] = (ww.unit + 8 * u) * 32 + l31;
-      const T* row = reinterpret_cast<const T*>(p.q) + ((size_t)h * p.q_head_rows + p.q_row0 + min(qrow[u], p.R - 1)) * D;
+      if constexpr (L::kThrough) {
+        Q::load(q_lds + u * Q::kBytes, q_rows, ww.unit + 8 * u, p.R, lane);
+      } else {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) qf[u][c] = load_chunk(row + chunk_elem_offset<T>(c, half));
+        for (int c = 0; c < NC; ++c) qf[u][c] = load_chunk(q_rows + (size_t)min(qrow[u], p.R - 1) * D + chunk_elem_offset<T>(c, half));
+      }
     }
   }
   // W^T as the M-side operand.  MFMA row m of block jb stands for value dim
@@ -690,7 +703,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // value row in a run.  bf16: W goes through the last stage of the ring (free until the first tile's
   // barrier) in 8 x 8 blocks turned round with v_perm; fp32: four dims of one column, a word at a time.
   constexpr bool kTurnW = RES && sizeof(T) == 2;
-  unsigned char* w_lds = smem + (ROPE ? L::kTurned : (kStages - 1) * L::kStageBytes);
+  unsigned char* w_lds = smem + L::kW;
   static_assert(!(ROPE && kTurnW) || D * D * 2 <= 2 * L::kTurnedBytes, "W goes through the un-rotated keys' place");
   const T* Wh = RES ? reinterpret_cast<const T*>(p.W) + (int64_t)w_head(p, h) * p.w_sh : nullptr;
   // The residual's product of this wave.  Late ones share no operands with the scores: four products a tile go to the last
@@ -720,10 +733,12 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // row), or the caller's log-sum-exp in the log2 domain of the logits; padded rows get +inf, which adds
   // exp2(-inf) = 0 to every column
   float* bias_lds = reinterpret_cast<float*>(smem + L::kBias);
+  float bias_u[U];
   if (MASS) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      float bias = INFINITY;
+      float& bias = bias_u[u];
+      bias = INFINITY;
       if (p.lse) {
         const int qr = p.q_row0 + min(qrow[u], p.R - 1), g = qr / p.w;
         bias = p.lse[((int64_t)h * (p.q_head_rows / p.w) + g) * p.lse_sh + (qr - g * p.w)] * kLog2e;
@@ -750,16 +765,22 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
         const float mn = fmaxf(m, m2), ms = (mn == -INFINITY) ? 0.f : mn;
         bias = mn + __builtin_amdgcn_logf(l * fast_exp2(m - ms) + l2 * fast_exp2(m2 - ms));
       }
-      if (half == 0 && ww.has_rows) bias_lds[(ww.unit + 8 * u) * 32 + l31] = qrow[u] < p.R ? bias : INFINITY;
     }
   }
   // All of it has arrived from here on: what is waited for below are tiles.  The waits count the tiles' loads back from the
   // last one issued; the counter falls in order of issue, so whatever else lies between (the stores of finish(),
   // registers spilled to scratch and read back) can make a wait longer than need be, never shorter.  Spilled
-  // registers per lane (in unequal batches): bf16 at d = 128 11 (41) with 16 units, on rotated keys none (13), with 16 units 30 (48), at
-  // d = 64 (16 with 16 units on rotated keys); fp32 at d = 128 10 (36), on rotated keys 29 (86), at d = 64 (16, on rotated keys 26);
+  // registers per lane (in unequal batches): bf16 at d = 128 13 (42) with 16 units, on rotated keys none (17), with 16 units 29 (48), at
+  // d = 64 (16 with 16 units on rotated keys); fp32 at d = 128 10 (39), on rotated keys 29 (90), at d = 64 (6, on rotated keys 13);
   // elsewhere none.
   if (MASS) {
+    if constexpr (L::kThrough) {
+      wait_loads<0>();
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) qf[u][c] = Q::read(q_lds + u * Q::kBytes, l31, half, c);
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -767,6 +788,10 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
         if (qrow[u] >= p.R) qf[u][c] = make_uint4(0, 0, 0, 0);
         asm volatile("" : "+v"(qf[u][c].x), "+v"(qf[u][c].y), "+v"(qf[u][c].z), "+v"(qf[u][c].w));
       }
+    if constexpr (L::kThrough) tile_barrier();   // everyone's query rows have left LDS
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (half == 0 && ww.has_rows) bias_lds[(ww.unit + 8 * u) * 32 + l31] = qrow[u] < p.R ? bias_u[u] : INFINITY;
   }
   if constexpr (kTurnW) {
 #pragma unroll
@@ -791,6 +816,8 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
         *reinterpret_cast<uint4*>(w_lds + w_slot(wb_j0 + j, wb_d0 / 8)) = make_uint4(word(0), word(1), word(2), word(3));
       }
     }
+  }
+  if constexpr (kTurnW) {
     tile_barrier();
 #pragma unroll
     for (int c = 0; c < NC; ++c) wf[c] = *reinterpret_cast<const chunk_t*>(w_lds + w_slot(my_dim, 2 * c + half));
