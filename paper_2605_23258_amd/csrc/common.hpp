@@ -316,4 +316,13 @@ __device__ __forceinline__ void rotary_back(float a, float b, float c, float s, 
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// 64 lanes x 16 (or 4) bytes from memory into LDS at lds + lane * 16 (or 4); tracked by vmcnt alone
+__device__ __forceinline__ void load_to_lds16(uint32_t lds, const void* g) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(g) : "m0", "memory");
+}
+__device__ __forceinline__ void load_to_lds4(uint32_t lds, const void* g) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(g) : "m0", "memory");
+}
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
 }  // namespace vec

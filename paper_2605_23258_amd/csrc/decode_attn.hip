@@ -49,6 +49,7 @@ struct DecodeParams {
   float* part;            // [B, Hkv, S, 2*G + G*D] floats: (m, l)[G], acc[G][D]
   int B, Hq, Hkv, cap_retain, n_approx;
   int splits_ret, splits_apx;   // workgroups per (sequence, head) on each segment
+  int apply_w;                  // pieces of approximated rows leave values (see kAppliesW)
   int by_kind;                  // the grid is (KV head, sequence, split) and not (split, KV head, sequence)
   // Sequences of different lengths (see PlannedSplits): [B, Hkv, 2] (first partial, number of partials) of either segment; and what
   // a step of approximated rows counts in steps of retained ones
@@ -551,8 +552,36 @@ template <int D> struct MfmaDecodeTile {
   static constexpr int kRowsPerLoad = kWave / kPieces;
   static constexpr int kLoads = kTileRows / kRowsPerLoad;   // wave-wide loads per tile and tensor
   static constexpr int kTileBytes = kTileRows * kStride;
-  static constexpr int kLdsBytes = DW * 2 * kTileBytes;
+  static constexpr int kTiles = DW * 2 * kTileBytes;
+  static constexpr int kParts = kTiles;                     // z's three parts, where the launch applies W (kAppliesW)
+  static constexpr int kLdsBytes = kTiles + 24 * kStride;
+  // W^T's place while approximated rows stream: the value tiles, 32 rows each; the 16-byte slots of a row are permuted by the row
+  static __device__ __forceinline__ uint32_t w_row(int row) { return (uint32_t)((row / kTileRows * 2 + 1) * kTileBytes + row % kTileRows * kRowBytes); }
+  static __device__ __forceinline__ int w_twist(int row) { return kPieces >= 16 ? (row & 15) : ((row >> 1) & 7); }
 };
+// Plain rows, where the launch is small (see apply_w): a piece of approximated rows leaves values, its weighted key sum times W, and the
+// merge has no W to wait for.  W comes into the value tiles, which plain keys do not use, while the rows stream, and these pieces
+// have half the bytes of the others.  Not with more than eight query heads, whose sums take the tiles' place; nor for rotated
+// keys, where these pieces are the longer ones.
+constexpr int kMostApplying = 8;
+template <int G, bool ROPE, bool LITERAL> constexpr bool kAppliesW = !ROPE && !LITERAL && G <= kMostApplying;
+
+// Elements j .. j + 3 (j a multiple of 4) of a row of z, in three bf16 parts eight rows of `STRIDE` bytes apart: its 24 bits, eight at a
+// time, cut and not rounded (above bf16's largest number a rounded first part would be infinite, and the second minus infinity; of an
+// infinite z the first part is all).  Inside 16 contraction indices 8 a + 4 h + c in the order 8 h + 4 a + c, which is how the
+// transposing read hands out W's rows.
+template <int STRIDE> __device__ __forceinline__ void store_parts(unsigned char* row, int j, f32x4 z) {
+  const int within = j & 15, pos = (j & ~15) + 8 * ((within >> 2) & 1) + 4 * (within >> 3);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    uint32_t top[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) top[e] = __float_as_uint(z[e]) & 0xffff0000u;
+    *reinterpret_cast<uint2*>(row + q * 8 * STRIDE + pos * 2) = make_uint2(top[0] >> 16 | top[1], top[2] >> 16 | top[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z[e] = q == 0 && (top[e] & 0x7fffffffu) == 0x7f800000u ? 0.f : z[e] - __uint_as_float(top[e]);
+  }
+}
 
 // ROPE: the cached keys carry rotary position embedding.  Logits use them as cached; the
 // rows that stand in for values of approximated tokens are the keys turned back by their
@@ -567,7 +596,9 @@ __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const Ro
   constexpr int PSZ = 2 * G + G * D;
   constexpr float kNegBig = -1.0e30f;      // running maximum before any row: finite, so differences stay finite
   constexpr int kRedStride = D + 4;        // floats per row of the merge area: 16-byte writes of 2 G rows hit distinct banks
-  static_assert(DW * (2 * G * kRedStride + 2 * G) * 4 <= TL::kLdsBytes, "merge area must fit in the tile area");
+  constexpr bool kOwnRed = kAppliesW<G, ROPE, LITERAL>;              // a wave's sums in the place of its key tile
+  static_assert(DW * (2 * G * kRedStride + 2 * G) * 4 <= TL::kTiles && (!kOwnRed || (2 * G * kRedStride + 2 * G) * 4 <= TL::kTileBytes),
+                "merge area must fit in the tile area");
   static_assert(2 * G <= 32, "weights and their remainders side by side");
 
   extern __shared__ __align__(16) unsigned char dec_lds[];
@@ -864,6 +895,17 @@ __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const Ro
     __syncthreads();
   }
 
+  // W for the weighted key sum: asked for before the rows, so that what waits for these has it
+  const bool applies_w = kOwnRed && is_apx && p.apply_w;
+  if (applies_w) {
+    const unsigned char* Wh = reinterpret_cast<const unsigned char*>(reinterpret_cast<const T*>(p.W) + (int64_t)h * p.w_sh);
+    constexpr int kLoads = D * TL::kRowBytes / (kWave * 16) / DW;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int first = (wave * kLoads + i) * TL::kRowsPerLoad, row = first + ld_row, piece = ld_piece ^ TL::w_twist(row);
+      load_to_lds16(lds_address(dec_lds) + TL::w_row(first), Wh + (size_t)row * TL::kRowBytes + piece * 16);
+    }
+  }
   int base = row_begin + wave * kTileRows;
   if (base < row_end) fetch(base);
   // The query rows have arrived from here on.  Without this the wait for them sits in the loop, in front of the first
@@ -882,22 +924,26 @@ __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const Ro
 
   // ---- merge the waves ----
   const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
-  __syncthreads();                                   // every wave is done with its tiles: reuse the area
-  float* red = reinterpret_cast<float*>(dec_lds);                    // [DW][2 G][kRedStride]: weights' part, remainders' part
-  float* ml = red + DW * 2 * G * kRedStride;                          // [DW][2][G]
+  if (kOwnRed) wave_fence();
+  else __syncthreads();                              // every wave is done with its tiles: reuse the area
+  // [DW][2 G][kRedStride]: weights' part, remainders' part; and [DW][2][G]
+  constexpr int kRedWave = kOwnRed ? 2 * TL::kTileBytes / 4 : 2 * G * kRedStride, kMlWave = kOwnRed ? kRedWave : 2 * G;
+  float* red = reinterpret_cast<float*>(dec_lds);
+  float* ml = red + (kOwnRed ? 1 : DW) * 2 * G * kRedStride;
   if (l31 < 2 * G) {
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
       for (int v = 0; v < 16; v += 4) {
         const f32x4 x = {o[jb][v], o[jb][v + 1], o[jb][v + 2], o[jb][v + 3]};
-        *reinterpret_cast<f32x4*>(red + (wave * 2 * G + l31) * kRedStride + jb * 32 + acc_row(v, half)) = x;
+        *reinterpret_cast<f32x4*>(red + wave * kRedWave + l31 * kRedStride + jb * 32 + acc_row(v, half)) = x;
       }
     if (half == 0 && l31 < G) {
-      ml[(wave * 2 + 0) * G + l31] = (l_tot > 0.f) ? m_run : -INFINITY;
-      ml[(wave * 2 + 1) * G + l31] = l_tot;
+      ml[wave * kMlWave + l31] = (l_tot > 0.f) ? m_run : -INFINITY;
+      ml[wave * kMlWave + G + l31] = l_tot;
     }
   }
+  if (applies_w) wait_loads<0>();
   __syncthreads();
   // a wave without rows has m = -inf and nothing but zeros: its share is 0 without a branch
   float* out = p.part + range.slot * PSZ;
@@ -905,22 +951,50 @@ __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const Ro
     const int g = i / D, j = i % D;
     float mw[DW], m = -INFINITY, l = 0.f;
 #pragma unroll
-    for (int wv = 0; wv < DW; ++wv) { mw[wv] = ml[(wv * 2) * G + g]; m = fmaxf(m, mw[wv]); }
+    for (int wv = 0; wv < DW; ++wv) { mw[wv] = ml[wv * kMlWave + g]; m = fmaxf(m, mw[wv]); }
     const float m_safe = m == -INFINITY ? 0.f : m;
     f32x4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int wv = 0; wv < DW; ++wv) {
       const float sc = fast_exp2(mw[wv] - m_safe);
-      const f32x4 x = *reinterpret_cast<const f32x4*>(red + (wv * 2 * G + g) * kRedStride + j);
-      const f32x4 y = *reinterpret_cast<const f32x4*>(red + (wv * 2 * G + G + g) * kRedStride + j);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(red + wv * kRedWave + g * kRedStride + j);
+      const f32x4 y = *reinterpret_cast<const f32x4*>(red + wv * kRedWave + (G + g) * kRedStride + j);
 #pragma unroll
       for (int e = 0; e < 4; ++e) a[e] = fmaf(x[e] + y[e], sc, a[e]);
-      l = fmaf(ml[(wv * 2 + 1) * G + g], sc, l);
+      l = fmaf(ml[wv * kMlWave + G + g], sc, l);
     }
-    *reinterpret_cast<f32x4_u*>(out + 2 * G + i) = a;
+    if (applies_w) store_parts<TL::kStride>(dec_lds + TL::kParts + g * TL::kStride, j, a);
+    else *reinterpret_cast<f32x4_u*>(out + 2 * G + i) = a;
     if (j == 0) {
       out[2 * g] = m;
       out[2 * g + 1] = l;
+    }
+  }
+  if constexpr (kOwnRed) {
+    if (!applies_w) return;
+    __syncthreads();
+    if (wave * 32 >= D) return;
+    // W's columns by the transposing read, as in the merge
+    typedef __attribute__((address_space(3))) s16x4 lds_quad;
+    const int col = wave * 32 + ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
+    uint32_t w_at[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int row = 8 * k + 4 * half + (lane & 15) / 4;
+      w_at[k] = lds_address(dec_lds) + TL::w_row(row) + (uint32_t)(((col / 8) ^ TL::w_twist(row)) * 16 + col % 8 * 2);
+    }
+    f32x16 acc;
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c) {
+      const s16x4 b0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)(w_at[0] + TL::w_row(16 * c) - TL::w_row(0)));
+      const s16x4 b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad*)(uintptr_t)(w_at[1] + TL::w_row(16 * c) - TL::w_row(0)));
+      const u32x4 a = *reinterpret_cast<const u32x4*>(dec_lds + TL::kParts + min(l31, 23) * TL::kStride + (16 * c + 8 * half) * 2);
+      acc = mfma(a, __builtin_bit_cast(u32x4, __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7)), c == 0 ? zero : acc);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int g = half * 4 + i;
+      if (g < G) out[2 * G + g * D + wave * 32 + l31] = acc[i] + (acc[4 + i] + acc[8 + i]);
     }
   }
 }
@@ -1087,8 +1161,7 @@ __global__ __launch_bounds__(DT_) void decode_combine_kernel(DecodeParams p) {
     }
   }
   __syncthreads();
-  // z, and (bf16) its parts: part q of query row g in row (g / 8) * 32 + q * 8 + g % 8; inside 16 contraction indices 8 a + 4 h + c
-  // in the order 8 h + 4 a + c, which is how the transposing read hands out W's rows
+  // z, and (bf16) its parts: part q of query row g in row (g / 8) * 32 + q * 8 + g % 8
   for (int i = tid * 4; i < G * D; i += DT_ * 4) {
     const int g = i / D, j = i % D;
     f32x4 v = {0.f, 0.f, 0.f, 0.f}, z = {0.f, 0.f, 0.f, 0.f};
@@ -1100,17 +1173,7 @@ __global__ __launch_bounds__(DT_) void decode_combine_kernel(DecodeParams p) {
     if (!L::kMfma) {
       if (L::kSide > 1) *reinterpret_cast<f32x4*>(sums + L::kSide * G * D + i) = z;
     } else if (use_w) {
-      const int within = j & 15, pos = (j & ~15) + 8 * ((within >> 2) & 1) + 4 * (within >> 3);
-      unsigned char* row = lds + ((g / 8) * 32 + g % 8) * L::kStride + pos * 2;
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        uint32_t top[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) top[e] = __float_as_uint(z[e]) & 0xffff0000u;
-        *reinterpret_cast<uint2*>(row + q * 8 * L::kStride) = make_uint2(top[0] >> 16 | top[1], top[2] >> 16 | top[3]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) z[e] = q == 0 && (top[e] & 0x7fffffffu) == 0x7f800000u ? 0.f : z[e] - __uint_as_float(top[e]);
-      }
+      store_parts<L::kStride>(lds + ((g / 8) * 32 + g % 8) * L::kStride, j, z);
     }
   }
   __syncthreads();
@@ -1362,6 +1425,12 @@ int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t st
   p.by_kind = kind == ApproxRows::kPlain && costs.one_round &&
               pick_one_round(costs, c.batch, c.n_kv_heads, c.cap_retain, c.n_approx, least_ret, p.splits_ret, p.splits_apx);
   if (!p.by_kind) pick_splits(costs, c.batch, c.n_kv_heads, c.cap_retain, c.n_approx, p.splits_ret, p.splits_apx);
+  // As long as a CU has one workgroup: the pieces of approximated rows wait for W beside their rows, and the merge has less to wait
+  // for.  With two, W's share of what they wait for is longer than what the merge loses.  A step without / with, us: one sequence of
+  // 8192 tokens 10.3 / 9.8, of 30000 14.7 / 14.1, two of 32768 16.0 / 15.1, three of 8192 13.6 / 13.1 (192 workgroups);
+  // four 14.6 / 15.2 (352), 16 30.9 / 31.7, ten of 32768 45.2 / 46.2.
+  p.apply_w = Elem<T>::kDtype == VECTOR_BF16 && G <= kMostApplying && kind == ApproxRows::kPlain && c.n_approx > 0 &&
+              (int64_t)c.batch * c.n_kv_heads * (p.splits_ret + p.splits_apx) <= 256;
   const unsigned splits = p.splits_ret + p.splits_apx, heads = c.n_kv_heads, batch = c.batch;
   const dim3 grid = p.by_kind ? dim3(heads, batch, splits) : dim3(splits, heads, batch);
   VEC_LAUNCH(K_DECODE_SPLIT, Kernel, grid, dim3(DT_), lds, stream, p, rope ? *rope : RopeParams{});
@@ -1403,6 +1472,7 @@ int run_decode_layout(const vector_cache& c, DecodeParams& p, hipStream_t stream
     else rc = launch_split<decode_split_kernel<T, D, G, PAGED, false>, T, D, G>(c, p, 0, stream, rope);
   }
   if (rc != VECTOR_OK) return rc;
+  if (p.apply_w) p.literal = 1;      // the partials are values
   const dim3 merge_grid(c.n_kv_heads, c.batch);
   if constexpr (kFewElements<T, D, G>) {
     VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_few_kernel<D, G>), merge_grid, dim3(DT_), 0, stream, p);
@@ -1467,6 +1537,7 @@ int launch_decode_attn(const vector_cache& c, const void* q, float scale, void* 
   p.plan = nullptr;
   p.plan_apx = 0.f;
   p.by_kind = 0;
+  p.apply_w = 0;
   if (c.dtype == VECTOR_BF16) {
     if (c.head_dim == 128) return run_decode_g<bf16_t, 128>(c, p, stream, rope);
     if (c.head_dim == 64) return run_decode_g<bf16_t, 64>(c, p, stream, rope);

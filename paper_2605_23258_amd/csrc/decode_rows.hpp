@@ -111,13 +111,15 @@ inline void pick_splits(const SplitCosts& c, int batch, int n_kv_heads, int cap_
   }
 }
 
-// Splits that make one round of workgroups, with as few steps as can be in the longest piece of either segment (and no more splits
-// than that takes); at least least_ret of them for the retained one.  For plain rows of 128 dims in bf16, whose launch puts the
-// retained pieces of all sequences first, the approximated ones behind them: the workgroups of a CU, half a grid apart, are then one
-// of each where there are as many of both, and every XCD has both kinds.  (In the order (split, head, sequence) an XCD has one
-// split of eight, often all retained or all approximated.)  A step, us, the estimate of before in its order / these / these in that order:
-//   16 sequences of 32768 tokens 70.6 (4 + 2) / 64.4 (2 + 2) / 71.4; 13 66.7 (2 + 1) / 56.6; 10 48.9 / 45.7 / 50.3; 4 23.0 / 22.3; 1 15.4 (28 + 13) /
-//   15.1; 24 of 16000 64.4 / 55.1 / 62.8; 32 of 8000 44.7 / 39.8 / 42.8; 64 of 8000 73.8 / 73.9; 1 of 8192 11.5 / 10.7.
+// Splits that make one round of workgroups; at least least_ret of them for the retained segment.  For plain rows of 128 dims in bf16,
+// whose launch puts the retained pieces of all sequences first, the approximated ones behind them: the workgroups of a CU,
+// half a grid apart, are then one of each where there are as many of both, and every XCD has both kinds.  (In the order (split,
+// head, sequence) an XCD has one split of eight, often all retained or all approximated.)  What a round takes: its bytes, or the steps
+// of its longest piece, twice as long each where CUs have two; the merge; and something for the last pieces to end.
+// A step, us, the estimate of before in its order / these / these in that order:
+//   16 sequences of 32768 tokens 70.6 (4 + 2) / 64.4 (2 + 2) / 71.4; 13 66.7 (2 + 1) / 56.6; 10 48.9 / 45.7 / 50.3; 4 23.0 / 22.3;
+//   24 of 16000 64.4 / 55.1 / 62.8; 32 of 8000 44.7 / 39.8 / 42.8; 64 of 8000 73.8 / 73.9; 1 of 8192 11.4 / 10.3.
+//   One of 16000, eight heads, cut into 6 / 11 / 21 and about as many: 14.6 / 12.6 / 13.5; two of 8192, 4 / 6 / 12: 13.2 / 11.9 / 12.7.
 //   Four times as many approximated rows as retained ones 75.2 / 70.9; four times as many retained ones 93.3 / 97.7 (26.7 / 27.1 for nine
 //   sequences of 12000): more than three times as many are left to the estimate.  Rotated keys (approximated rows are vector
 //   work) 69.2 / 82, and rows of 64 dims 37.1 / 37.5, 30.8 / 32.9, 14.7 / 14.7: the estimate.
@@ -126,6 +128,7 @@ inline bool pick_one_round(const SplitCosts& c, int batch, int n_kv_heads, int c
   if (steps_r == 0 || steps_a == 0 || steps_r > 3 * steps_a) return false;
   const int64_t pairs = (int64_t)batch * n_kv_heads;
   const int most = (int)std::max<int64_t>(2, std::min<int64_t>(kMaxSplits, 256 * c.per_cu / pairs));
+  const double bytes = (double)pairs * (0.0121 * (double)steps_r + 0.0061 * (double)steps_a);      // us at 5.4 TB/s
   double best = -1.0;
   for (int r = std::max(1, least_ret); r < most && r <= steps_r; ++r) {
     const int64_t long_r = (steps_r + r - 1) / r;
@@ -133,7 +136,8 @@ inline bool pick_one_round(const SplitCosts& c, int batch, int n_kv_heads, int c
     int64_t a = std::min<int64_t>(std::min<int64_t>(most - r, steps_a), (steps_a + long_r - 1) / long_r);
     const int64_t long_a = (steps_a + a - 1) / a;
     a = (steps_a + long_a - 1) / long_a;
-    const double t = (double)std::max(long_r, long_a) + 0.02 * (double)(r + a);
+    const double longest = (double)std::max(long_r, long_a);
+    const double t = std::max(bytes, (pairs * (r + a) > 256 ? 2.8 : 1.4) * longest) + 0.15 * longest + 0.05 * (double)(r + a);
     if (best < 0.0 || t < best) { best = t; s_ret = r; s_apx = (int)a; }
   }
   return best >= 0.0;

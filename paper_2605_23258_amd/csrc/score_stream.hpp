@@ -116,14 +116,6 @@ template <typename T, int D> struct Stream {
   static __device__ __forceinline__ int twist(int row) { return kPieces >= 16 ? (row & 15) : ((row >> 1) & 7); }
 };
 
-// 64 lanes x 16 (or 4) bytes from memory into LDS at lds + lane * 16 (or 4); tracked by vmcnt alone
-__device__ __forceinline__ void load_to_lds16(uint32_t lds, const void* g) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(g) : "m0", "memory");
-}
-__device__ __forceinline__ void load_to_lds4(uint32_t lds, const void* g) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(g) : "m0", "memory");
-}
-template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 // at most `tiles` tiles of PER loads each may still be on their way
 template <int PER> __device__ __forceinline__ void wait_tiles(int tiles) {
   if (tiles >= 2) wait_loads<2 * PER>();
