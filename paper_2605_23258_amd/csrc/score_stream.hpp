@@ -181,11 +181,13 @@ template <typename T, int D, int NRB> struct WaveWork {
   static constexpr int PH = NRB == 4 ? (S::kSub == 4 ? 2 : 1) : S::kSub;          // subtiles per wave and tile
   static constexpr int kPerSub = kStreamWaves / S::kSub;                           // waves that end on one subtile
   static constexpr int kEntries = NRB == 4 ? 4 : 8;                                // partial column sums per token
-  int unit, first, res_sub, res_block;
+  static constexpr bool kPairs = NRB == 4;                                         // two waves share a unit
+  static constexpr int kUnitSlots = kPairs ? 4 : kStreamWaves * U;                 // units that the waves hold, with those beyond the rows
+  int unit, grp, first, res_sub, res_block;
   bool has_rows, has_res;
   __device__ __forceinline__ WaveWork(int wave) {
     unit = NRB == 4 ? (wave & 3) : wave;
-    const int grp = wave >> 2;
+    grp = wave >> 2;
     has_rows = !(NRB == 4 && S::kSub == 1 && grp == 1);
     first = (NRB == 4 && S::kSub > 1) ? grp * (S::kSub / 2) : 0;
     res_sub = wave / kPerSub;
@@ -233,16 +235,20 @@ template <typename T, int D> struct KeyOperands {
   }
 };
 
-// A wave's units of query rows, through LDS of its own: whole rows with one load, laid out as a subtile of keys is.  (Asked for in
+// A wave's units of query rows, through LDS: whole rows with one load, laid out as a subtile of keys is.  (Asked for in
 // operand order, 16 bytes of 64 different rows with one load, they kept a CU's address unit busy for 1.1 us per eight units.)
+// Waves that share a unit (up to 128 rows) fetch half of it each, and add up half of its chunks' sums in pass 2; both are there a barrier
+// later.  Both waves doing all of it kept the address unit busy for twice as long (64 of 256 loads of pass 2's first 3.4 us at 8192 tokens; a
+// compression pass, us, both doing all / half each: 1024 tokens fp32 24.7 / 24.2, 8192 tokens 32.9 / 32.6, 20011 with log-sum-exp 54.3 / 53.8,
+// two heads of 11469 tokens, 128 chunks each, 37.5 / 36.0).
 template <typename T, int D> struct QueryUnit {
   using S = Stream<T, D>;
   static constexpr int kBytes = 32 * S::kRowBytes, kLoads = kBytes / (kWave * 16);
-  // rows unit * 32 .. of the `R` at `rows`; those beyond are copies of the last
-  static __device__ __forceinline__ void load(uint32_t lds, const T* rows, int unit, int R, int lane) {
+  // rows unit * 32 .. of the `R` at `rows`, or (PARTS 2) half of them; those beyond are copies of the last
+  template <int PARTS> static __device__ __forceinline__ void load(uint32_t lds, const T* rows, int unit, int part, int R, int lane) {
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const int row = i * S::kRowsPerLoad + lane / S::kPieces, piece = (lane % S::kPieces) ^ S::twist(row);
+    for (int j = 0; j < kLoads / PARTS; ++j) {
+      const int i = PARTS == 1 ? j : part * (kLoads / PARTS) + j, row = i * S::kRowsPerLoad + lane / S::kPieces, piece = (lane % S::kPieces) ^ S::twist(row);
       load_to_lds16(lds + i * 1024, reinterpret_cast<const unsigned char*>(rows) + (size_t)min(unit * 32 + row, R - 1) * S::kRowBytes + piece * 16);
     }
   }
@@ -258,7 +264,7 @@ constexpr int kStages1 = 4;
 // there is room for them; else in the place of the tiles after the first.  bf16 rows of 64 dims and one unit a wave: two workgroups
 // fit a CU as long as they have no more than the ring; their query rows go straight into the registers.
 template <typename T, int D, int NRB> struct Pass1Lds {
-  static constexpr int kQueryBytes = kStreamWaves * WaveWork<T, D, NRB>::U * QueryUnit<T, D>::kBytes;
+  static constexpr int kQueryBytes = WaveWork<T, D, NRB>::kUnitSlots * QueryUnit<T, D>::kBytes;
   static constexpr bool kThrough = !(sizeof(T) == 2 && D == 64 && NRB < 16);
   static constexpr int kRing = kStages1 * kStreamTileBytes, kShares = kRing, kSharesEnd = kRing + kStreamWaves * 32 * (int)sizeof(float2);
   static constexpr bool kApart = kSharesEnd + kQueryBytes <= (int)kMaxLdsBytes;
@@ -305,12 +311,12 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassArgs<RA
   int qrow[U];
   const T* q_rows = reinterpret_cast<const T*>(p.q) + ((size_t)h * p.q_head_rows + p.q_row0) * D;
   using Q = QueryUnit<T, D>;
-  const uint32_t q_lds = smem0 + L::kQuery + wave * U * Q::kBytes;
+  const uint32_t q_lds = smem0 + L::kQuery + (WW::kPairs ? ww.unit : wave * U) * Q::kBytes;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     qrow[u] = (ww.unit + 8 * u) * 32 + l31;
     if constexpr (L::kThrough) {
-      Q::load(q_lds + u * Q::kBytes, q_rows, ww.unit + 8 * u, p.R, lane);
+      Q::template load<WW::kPairs ? 2 : 1>(q_lds + u * Q::kBytes, q_rows, ww.unit + 8 * u, ww.grp, p.R, lane);
     } else {
 #pragma unroll
       for (int c = 0; c < NC; ++c) qf[u][c] = load_chunk(q_rows + (size_t)min(qrow[u], p.R - 1) * D + chunk_elem_offset<T>(c, half));
@@ -318,6 +324,7 @@ __global__ __launch_bounds__(kStreamThreads) void score_stats_kernel(PassArgs<RA
   }
   if constexpr (L::kThrough) {
     wait_loads<0>();
+    if constexpr (WW::kPairs) tile_barrier();
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -605,11 +612,15 @@ template <typename T, int D, int NRB, bool MASS, bool RES, bool ROPE> struct Pas
   // tiles are asked for and W and the biases are put down.  Not those of rotated fp32 keys of 128 dims: the kernels would spill
   // up to six registers more (2546 to 8192 tokens, 8 heads, 1.4 % longer).
   static constexpr bool kThrough = MASS && !(ROPE && sizeof(T) == 4 && D == 128);
-  static constexpr int kQuery = kStageBytes, kQueryBytes = kThrough ? kStreamWaves * WW::U * QueryUnit<T, D>::kBytes : 0;
+  static constexpr int kQuery = kStageBytes, kQueryBytes = kThrough ? WW::kUnitSlots * QueryUnit<T, D>::kBytes : 0;
   static constexpr int kW = ROPE ? kTurned : (kStages - 1) * kStageBytes;      // W on its way into the registers
   static constexpr int kUsed = kBiasInTurned ? kEnd : kEnd + kBiasBytes;
-  static constexpr int kTotal = kQuery + kQueryBytes > kUsed ? kQuery + kQueryBytes : kUsed;
+  // waves that share a unit: their shares of its rows' sums, [2][4][32] float2, between two barriers or (not kThrough) a while before the
+  // column sums come there
+  static constexpr int kShares = kMassSums > kQuery + kQueryBytes ? kMassSums : kQuery + kQueryBytes, kSharesEnd = kShares + (MASS && WW::kPairs ? 2048 : 0);
+  static constexpr int kTotal = kSharesEnd > kUsed ? kSharesEnd : kUsed;
   static_assert(kTotal <= (int)kMaxLdsBytes, "LDS");
+  static_assert(kThrough || !WW::kPairs || !MASS || kSharesEnd <= kEnd, "the shares end before the biases");
 };
 
 // x of this lane + x of the lane 32 further
@@ -675,14 +686,14 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   chunk_t qf[U][NC], wf[NC];
   int qrow[U];
   using Q = QueryUnit<T, D>;
-  const uint32_t q_lds = smem0 + L::kQuery + wave * U * Q::kBytes;
+  const uint32_t q_lds = smem0 + L::kQuery + (WW::kPairs ? ww.unit : wave * U) * Q::kBytes;
   if (MASS) {
     const T* q_rows = reinterpret_cast<const T*>(p.q) + ((size_t)h * p.q_head_rows + p.q_row0) * D;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       qrow[u] = (ww.unit + 8 * u) * 32 + l31;
       if constexpr (L::kThrough) {
-        Q::load(q_lds + u * Q::kBytes, q_rows, ww.unit + 8 * u, p.R, lane);
+        Q::template load<WW::kPairs ? 2 : 1>(q_lds + u * Q::kBytes, q_rows, ww.unit + 8 * u, ww.grp, p.R, lane);
       } else {
 #pragma unroll
         for (int c = 0; c < NC; ++c) qf[u][c] = load_chunk(q_rows + (size_t)min(qrow[u], p.R - 1) * D + chunk_elem_offset<T>(c, half));
@@ -722,10 +733,12 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
     }
   }
   // one bias per row: reference + log2(sum) over pass 1's chunks (a lane takes every second chunk of its
-  // row), or the caller's log-sum-exp in the log2 domain of the logits; padded rows get +inf, which adds
+  // row; where two waves share a unit, every fourth, and a barrier later each adds the other's share), or the caller's log-sum-exp in the log2 domain of the logits; padded rows get +inf, which adds
   // exp2(-inf) = 0 to every column
   float* bias_lds = reinterpret_cast<float*>(smem + L::kBias);
   float bias_u[U];
+  float2* shares = reinterpret_cast<float2*>(smem + L::kShares) + ww.unit * 32 + l31;      // [2][4][32]
+  const bool shared_bias = MASS && WW::kPairs && !p.lse;
   if (MASS) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -734,28 +747,33 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       if (p.lse) {
         const int qr = p.q_row0 + min(qrow[u], p.R - 1), g = qr / p.w;
         bias = p.lse[((int64_t)h * (p.q_head_rows / p.w) + g) * p.lse_sh + (qr - g * p.w)] * kLog2e;
-      } else if (ww.has_rows) {
-        constexpr int kBatch = 16;
+      } else if (WW::kPairs || ww.has_rows) {
+        constexpr int kBatch = WW::kPairs ? 8 : 16, kApart = WW::kPairs ? 4 : 2;      // 32 chunks at once
         const float2* part = p.part + (size_t)h * p.n_chunks * p.R_pad + qrow[u];
         float m = -INFINITY, l = 0.f;
-        for (int c0 = half; c0 < p.n_chunks; c0 += 2 * kBatch) {
+        for (int c0 = WW::kPairs ? half + 2 * ww.grp : half; c0 < p.n_chunks; c0 += kApart * kBatch) {
           float2 sv[kBatch];
 #pragma unroll
-          for (int i = 0; i < kBatch; ++i) sv[i] = part[(size_t)min(c0 + 2 * i, p.n_chunks - 1) * p.R_pad];
+          for (int i = 0; i < kBatch; ++i) sv[i] = part[(size_t)min(c0 + kApart * i, p.n_chunks - 1) * p.R_pad];
           float bm = m;
 #pragma unroll
           for (int i = 0; i < kBatch; ++i)
-            if (c0 + 2 * i < p.n_chunks) bm = fmaxf(bm, sv[i].x);
+            if (c0 + kApart * i < p.n_chunks) bm = fmaxf(bm, sv[i].x);
           const float bs = (bm == -INFINITY) ? 0.f : bm;
           l *= fast_exp2(m - bs);
 #pragma unroll
           for (int i = 0; i < kBatch; ++i)
-            if (c0 + 2 * i < p.n_chunks) l += sv[i].y * fast_exp2(sv[i].x - bs);
+            if (c0 + kApart * i < p.n_chunks) l += sv[i].y * fast_exp2(sv[i].x - bs);
           m = bm;
         }
         const float m2 = __shfl_xor(m, 32, kWave), l2 = __shfl_xor(l, 32, kWave);
         const float mn = fmaxf(m, m2), ms = (mn == -INFINITY) ? 0.f : mn;
-        bias = mn + __builtin_amdgcn_logf(l * fast_exp2(m - ms) + l2 * fast_exp2(m2 - ms));
+        const float sum = l * fast_exp2(m - ms) + l2 * fast_exp2(m2 - ms);
+        if (WW::kPairs) {
+          if (half == 0) shares[ww.grp * 4 * 32] = make_float2(mn, sum);
+        } else {
+          bias = mn + __builtin_amdgcn_logf(sum);
+        }
       }
     }
   }
@@ -766,12 +784,18 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // d = 64 (16 with 16 units on rotated keys); fp32 at d = 128 10 (39), on rotated keys 29 (90), at d = 64 (6, on rotated keys 13);
   // elsewhere none.
   if (MASS) {
+    if constexpr (L::kThrough) wait_loads<0>();
+    if constexpr (WW::kPairs) tile_barrier();    // everyone's shares and query rows are there
     if constexpr (L::kThrough) {
-      wait_loads<0>();
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int c = 0; c < NC; ++c) qf[u][c] = Q::read(q_lds + u * Q::kBytes, l31, half, c);
+    }
+    if (shared_bias) {
+      const float2 a = shares[0], b = shares[4 * 32];
+      const float mn = fmaxf(a.x, b.x), ms = (mn == -INFINITY) ? 0.f : mn;
+      bias_u[0] = mn + __builtin_amdgcn_logf(a.y * fast_exp2(a.x - ms) + b.y * fast_exp2(b.x - ms));
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
