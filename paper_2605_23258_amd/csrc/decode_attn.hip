@@ -49,7 +49,6 @@ struct DecodeParams {
   float* part;            // [B, Hkv, S, 2*G + G*D] floats: (m, l)[G], acc[G][D]
   int B, Hq, Hkv, cap_retain, n_approx;
   int splits_ret, splits_apx;   // workgroups per (sequence, head) on each segment
-  int apply_w;                  // pieces of approximated rows leave values (see kAppliesW)
   int by_kind;                  // the grid is (KV head, sequence, split) and not (split, KV head, sequence)
   // Sequences of different lengths (see PlannedSplits): [B, Hkv, 2] (first partial, number of partials) of either segment; and what
   // a step of approximated rows counts in steps of retained ones
@@ -553,18 +552,17 @@ template <int D> struct MfmaDecodeTile {
   static constexpr int kLoads = kTileRows / kRowsPerLoad;   // wave-wide loads per tile and tensor
   static constexpr int kTileBytes = kTileRows * kStride;
   static constexpr int kTiles = DW * 2 * kTileBytes;
-  static constexpr int kParts = kTiles;                     // z's three parts, where the launch applies W (kAppliesW)
+  static constexpr int kParts = kTiles;                     // z's three parts, where the launch applies W (APPLY)
   static constexpr int kLdsBytes = kTiles + 24 * kStride;
   // W^T's place while approximated rows stream: the value tiles, 32 rows each; the 16-byte slots of a row are permuted by the row
   static __device__ __forceinline__ uint32_t w_row(int row) { return (uint32_t)((row / kTileRows * 2 + 1) * kTileBytes + row % kTileRows * kRowBytes); }
   static __device__ __forceinline__ int w_twist(int row) { return kPieces >= 16 ? (row & 15) : ((row >> 1) & 7); }
 };
-// Plain rows, where the launch is small (see apply_w): a piece of approximated rows leaves values, its weighted key sum times W, and the
+// APPLY, plain rows where the launch is small (see launch_split): a piece of approximated rows leaves values, its weighted key sum times W, and the
 // merge has no W to wait for.  W comes into the value tiles, which plain keys do not use, while the rows stream, and these pieces
 // have half the bytes of the others.  Not with more than eight query heads, whose sums take the tiles' place; nor for rotated
 // keys, where these pieces are the longer ones.
 constexpr int kMostApplying = 8;
-template <int G, bool ROPE, bool LITERAL> constexpr bool kAppliesW = !ROPE && !LITERAL && G <= kMostApplying;
 
 // Elements j .. j + 3 (j a multiple of 4) of a row of z, in three bf16 parts eight rows of `STRIDE` bytes apart: its 24 bits, eight at a
 // time, cut and not rounded (above bf16's largest number a rounded first part would be infinite, and the second minus infinity; of an
@@ -587,7 +585,7 @@ template <int STRIDE> __device__ __forceinline__ void store_parts(unsigned char*
 // rows that stand in for values of approximated tokens are the keys turned back by their
 // original positions (rp.positions, one per row of k_apx), written to the second tile as bf16.
 // LITERAL: approximated rows are rebuilt one by one, v_hat = k W, before they are weighted.
-template <int D, int G, bool ROPE, bool LITERAL, bool PAGED>
+template <int D, int G, bool ROPE, bool LITERAL, bool PAGED, bool APPLY>
 __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const RopeParams& rp, const SplitRows& range, int tid) {
   using T = bf16_t;
   using TL = MfmaDecodeTile<D>;
@@ -596,8 +594,9 @@ __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const Ro
   constexpr int PSZ = 2 * G + G * D;
   constexpr float kNegBig = -1.0e30f;      // running maximum before any row: finite, so differences stay finite
   constexpr int kRedStride = D + 4;        // floats per row of the merge area: 16-byte writes of 2 G rows hit distinct banks
-  constexpr bool kOwnRed = kAppliesW<G, ROPE, LITERAL>;              // a wave's sums in the place of its key tile
-  static_assert(DW * (2 * G * kRedStride + 2 * G) * 4 <= TL::kTiles && (!kOwnRed || (2 * G * kRedStride + 2 * G) * 4 <= TL::kTileBytes),
+  static_assert(!APPLY || (!ROPE && !LITERAL && G <= kMostApplying), "plain rows");
+  // APPLY: a wave's sums in the place of its key tile
+  static_assert(DW * (2 * G * kRedStride + 2 * G) * 4 <= TL::kTiles && (!APPLY || (2 * G * kRedStride + 2 * G) * 4 <= TL::kTileBytes),
                 "merge area must fit in the tile area");
   static_assert(2 * G <= 32, "weights and their remainders side by side");
 
@@ -896,7 +895,7 @@ __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const Ro
   }
 
   // W for the weighted key sum: asked for before the rows, so that what waits for these has it
-  const bool applies_w = kOwnRed && is_apx && p.apply_w;
+  const bool applies_w = APPLY && is_apx;
   if (applies_w) {
     const unsigned char* Wh = reinterpret_cast<const unsigned char*>(reinterpret_cast<const T*>(p.W) + (int64_t)h * p.w_sh);
     constexpr int kLoads = D * TL::kRowBytes / (kWave * 16) / DW;
@@ -924,12 +923,12 @@ __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const Ro
 
   // ---- merge the waves ----
   const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
-  if (kOwnRed) wave_fence();
+  if (APPLY) wave_fence();
   else __syncthreads();                              // every wave is done with its tiles: reuse the area
   // [DW][2 G][kRedStride]: weights' part, remainders' part; and [DW][2][G]
-  constexpr int kRedWave = kOwnRed ? 2 * TL::kTileBytes / 4 : 2 * G * kRedStride, kMlWave = kOwnRed ? kRedWave : 2 * G;
+  constexpr int kRedWave = APPLY ? 2 * TL::kTileBytes / 4 : 2 * G * kRedStride, kMlWave = APPLY ? kRedWave : 2 * G;
   float* red = reinterpret_cast<float*>(dec_lds);
-  float* ml = red + (kOwnRed ? 1 : DW) * 2 * G * kRedStride;
+  float* ml = red + (APPLY ? 1 : DW) * 2 * G * kRedStride;
   if (l31 < 2 * G) {
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb)
@@ -970,7 +969,7 @@ __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const Ro
       out[2 * g + 1] = l;
     }
   }
-  if constexpr (kOwnRed) {
+  if constexpr (APPLY) {
     if (!applies_w) return;
     __syncthreads();
     if (wave * 32 >= D) return;
@@ -998,9 +997,9 @@ __device__ __forceinline__ void attend_rows_mfma(const DecodeParams& p, const Ro
     }
   }
 }
-template <int D, int G, bool ROPE, bool LITERAL = false, bool PAGED = false, bool PLANNED = false>
+template <int D, int G, bool ROPE, bool LITERAL = false, bool PAGED = false, bool PLANNED = false, bool APPLY = false>
 __global__ __launch_bounds__(DT_, 2) void decode_split_mfma_kernel(DecodeParams p, RopeParams rp) {
-  for_split_rows<DW * kTileRows, PLANNED>(p, [&](const SplitRows& r, int tid) VEC_INLINE { attend_rows_mfma<D, G, ROPE, LITERAL, PAGED>(p, rp, r, tid); });
+  for_split_rows<DW * kTileRows, PLANNED>(p, [&](const SplitRows& r, int tid) VEC_INLINE { attend_rows_mfma<D, G, ROPE, LITERAL, PAGED, APPLY>(p, rp, r, tid); });
 }
 
 // The partials of a (sequence, KV head): those of the retained segment from `first` on, then those of the approximated one, `gap`
@@ -1414,7 +1413,8 @@ template <auto Kernel> int workgroups_per_cu(int lds) {
   return n;
 }
 
-template <auto Kernel, typename T, int D, int G>
+// Applying: the kernel for plain rows where a small launch applies W (APPLY), or Kernel
+template <auto Kernel, typename T, int D, int G, auto Applying = Kernel>
 int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t stream, const RopeParams* rope) {
   if (lds) VEC_HIP(set_max_lds(reinterpret_cast<const void*>(Kernel), lds));
   const ApproxRows kind = rope ? ApproxRows::kTurned : p.literal ? ApproxRows::kRebuilt : ApproxRows::kPlain;
@@ -1428,11 +1428,20 @@ int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t st
   // As long as a CU has one workgroup: the pieces of approximated rows wait for W beside their rows, and the merge has less to wait
   // for.  With two, W's share of what they wait for is longer than what the merge loses.  A step without / with, us: one sequence of
   // 8192 tokens 10.3 / 9.8, of 30000 14.7 / 14.1, two of 32768 16.0 / 15.1, three of 8192 13.6 / 13.1 (192 workgroups);
-  // four 14.6 / 15.2 (352), 16 30.9 / 31.7, ten of 32768 45.2 / 46.2.
-  p.apply_w = Elem<T>::kDtype == VECTOR_BF16 && G <= kMostApplying && kind == ApproxRows::kPlain && c.n_approx > 0 &&
-              (int64_t)c.batch * c.n_kv_heads * (p.splits_ret + p.splits_apx) <= 256;
+  // four 14.6 / 15.2 (352), 16 30.9 / 31.7, ten of 32768 45.2 / 46.2.  A kernel of its own: as a branch of the other one its 1.5 KB of
+  // code had to come into the instruction cache of every launch (one sequence of 8192 tokens 9.8 / 9.7).
+  const bool apply_w = Applying != Kernel && c.n_approx > 0 && (int64_t)c.batch * c.n_kv_heads * (p.splits_ret + p.splits_apx) <= 256;
   const unsigned splits = p.splits_ret + p.splits_apx, heads = c.n_kv_heads, batch = c.batch;
   const dim3 grid = p.by_kind ? dim3(heads, batch, splits) : dim3(splits, heads, batch);
+  if constexpr (Applying != Kernel) {
+    if (apply_w) {
+      constexpr int more_lds = MfmaDecodeTile<D>::kLdsBytes;
+      VEC_HIP(set_max_lds(reinterpret_cast<const void*>(Applying), more_lds));
+      VEC_LAUNCH(K_DECODE_SPLIT, Applying, grid, dim3(DT_), more_lds, stream, p, RopeParams{});
+      p.literal = 1;      // the partials are values
+      return VECTOR_OK;
+    }
+  }
   VEC_LAUNCH(K_DECODE_SPLIT, Kernel, grid, dim3(DT_), lds, stream, p, rope ? *rope : RopeParams{});
   return VECTOR_OK;
 }
@@ -1440,7 +1449,7 @@ int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t st
 // Sequences of different lengths, and their merge
 template <auto Kernel, typename T, int D, int G>
 int launch_planned(const vector_cache& c, DecodeParams& p, hipStream_t stream, const RopeParams* rope) {
-  constexpr int lds = MfmaDecodeTile<D>::kLdsBytes, merge_lds = CombineLds<T, D, G>::kTotal;
+  constexpr int lds = MfmaDecodeTile<D>::kTiles, merge_lds = CombineLds<T, D, G>::kTotal;
   constexpr auto merge = decode_combine_kernel<T, D, G, true>;
   VEC_HIP(set_max_lds(reinterpret_cast<const void*>(Kernel), lds));
   VEC_HIP(set_max_lds(reinterpret_cast<const void*>(merge), merge_lds));
@@ -1463,16 +1472,16 @@ int run_decode_layout(const vector_cache& c, DecodeParams& p, hipStream_t stream
     }
   }
   if constexpr (Elem<T>::kDtype == VECTOR_BF16) {
-    constexpr int lds = MfmaDecodeTile<D>::kLdsBytes;
+    constexpr int lds = MfmaDecodeTile<D>::kTiles;
     if (rope) rc = launch_split<decode_split_mfma_kernel<D, G, true, false, PAGED>, T, D, G>(c, p, lds, stream, rope);
     else if (p.literal) rc = launch_split<decode_split_mfma_kernel<D, G, false, true, PAGED>, T, D, G>(c, p, lds, stream, rope);
-    else rc = launch_split<decode_split_mfma_kernel<D, G, false, false, PAGED>, T, D, G>(c, p, lds, stream, rope);
+    else rc = launch_split<decode_split_mfma_kernel<D, G, false, false, PAGED>, T, D, G, decode_split_mfma_kernel<D, G, false, false, PAGED, false, (G <= kMostApplying)>>(
+        c, p, lds, stream, rope);
   } else {
     if (rope) rc = launch_split<decode_split_kernel<T, D, G, PAGED, true>, T, D, G>(c, p, 0, stream, rope);
     else rc = launch_split<decode_split_kernel<T, D, G, PAGED, false>, T, D, G>(c, p, 0, stream, rope);
   }
   if (rc != VECTOR_OK) return rc;
-  if (p.apply_w) p.literal = 1;      // the partials are values
   const dim3 merge_grid(c.n_kv_heads, c.batch);
   if constexpr (kFewElements<T, D, G>) {
     VEC_LAUNCH(K_DECODE_COMBINE, (decode_combine_few_kernel<D, G>), merge_grid, dim3(DT_), 0, stream, p);
@@ -1537,7 +1546,6 @@ int launch_decode_attn(const vector_cache& c, const void* q, float scale, void* 
   p.plan = nullptr;
   p.plan_apx = 0.f;
   p.by_kind = 0;
-  p.apply_w = 0;
   if (c.dtype == VECTOR_BF16) {
     if (c.head_dim == 128) return run_decode_g<bf16_t, 128>(c, p, stream, rope);
     if (c.head_dim == 64) return run_decode_g<bf16_t, 64>(c, p, stream, rope);
