@@ -610,17 +610,18 @@ template <typename T, int D, int NRB, bool MASS, bool RES, bool ROPE> struct Pas
   static constexpr int kBias = kBiasInTurned ? kTurned + kTurnedBytes : kEnd;
   // The query rows pass through the places of the tiles after the first and of what lies behind these, until a barrier after which the
   // tiles are asked for and W and the biases are put down.  Not those of rotated fp32 keys of 128 dims: the kernels would spill
-  // up to six registers more (2546 to 8192 tokens, 8 heads, 1.4 % longer).
+  // up to six registers more (2546 to 8192 tokens, 8 heads, 1.4 % longer).  Nor do two waves that share a unit of those rows each take
+  // half of its chunks' sums: the six registers again, 35 spilled in place of 29 (8192 tokens, 8 heads, 93.7 us a compression pass
+  // with halves, 88.2 without; with log-sum-exp, which has no sums to take, 71.2 and 67.1; 2546 tokens 48.9 and 47.0).
   static constexpr bool kThrough = MASS && !(ROPE && sizeof(T) == 4 && D == 128);
+  static constexpr bool kHalves = kThrough && WW::kPairs;
   static constexpr int kQuery = kStageBytes, kQueryBytes = kThrough ? WW::kUnitSlots * QueryUnit<T, D>::kBytes : 0;
   static constexpr int kW = ROPE ? kTurned : (kStages - 1) * kStageBytes;      // W on its way into the registers
   static constexpr int kUsed = kBiasInTurned ? kEnd : kEnd + kBiasBytes;
-  // waves that share a unit: their shares of its rows' sums, [2][4][32] float2, between two barriers or (not kThrough) a while before the
-  // column sums come there
-  static constexpr int kShares = kMassSums > kQuery + kQueryBytes ? kMassSums : kQuery + kQueryBytes, kSharesEnd = kShares + (MASS && WW::kPairs ? 2048 : 0);
+  // waves that share a unit: their shares of its rows' sums, [2][4][32] float2, between two barriers
+  static constexpr int kShares = kMassSums > kQuery + kQueryBytes ? kMassSums : kQuery + kQueryBytes, kSharesEnd = kShares + (kHalves ? 2048 : 0);
   static constexpr int kTotal = kSharesEnd > kUsed ? kSharesEnd : kUsed;
   static_assert(kTotal <= (int)kMaxLdsBytes, "LDS");
-  static_assert(kThrough || !WW::kPairs || !MASS || kSharesEnd <= kEnd, "the shares end before the biases");
 };
 
 // x of this lane + x of the lane 32 further
@@ -738,7 +739,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   float* bias_lds = reinterpret_cast<float*>(smem + L::kBias);
   float bias_u[U];
   float2* shares = reinterpret_cast<float2*>(smem + L::kShares) + ww.unit * 32 + l31;      // [2][4][32]
-  const bool shared_bias = MASS && WW::kPairs && !p.lse;
+  const bool shared_bias = L::kHalves && !p.lse;
   if (MASS) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -747,11 +748,11 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
       if (p.lse) {
         const int qr = p.q_row0 + min(qrow[u], p.R - 1), g = qr / p.w;
         bias = p.lse[((int64_t)h * (p.q_head_rows / p.w) + g) * p.lse_sh + (qr - g * p.w)] * kLog2e;
-      } else if (WW::kPairs || ww.has_rows) {
-        constexpr int kBatch = WW::kPairs ? 8 : 16, kApart = WW::kPairs ? 4 : 2;      // 32 chunks at once
+      } else if (L::kHalves || ww.has_rows) {
+        constexpr int kBatch = L::kHalves ? 8 : 16, kApart = L::kHalves ? 4 : 2;      // 32 chunks at once
         const float2* part = p.part + (size_t)h * p.n_chunks * p.R_pad + qrow[u];
         float m = -INFINITY, l = 0.f;
-        for (int c0 = WW::kPairs ? half + 2 * ww.grp : half; c0 < p.n_chunks; c0 += kApart * kBatch) {
+        for (int c0 = L::kHalves ? half + 2 * ww.grp : half; c0 < p.n_chunks; c0 += kApart * kBatch) {
           float2 sv[kBatch];
 #pragma unroll
           for (int i = 0; i < kBatch; ++i) sv[i] = part[(size_t)min(c0 + kApart * i, p.n_chunks - 1) * p.R_pad];
@@ -769,7 +770,7 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
         const float m2 = __shfl_xor(m, 32, kWave), l2 = __shfl_xor(l, 32, kWave);
         const float mn = fmaxf(m, m2), ms = (mn == -INFINITY) ? 0.f : mn;
         const float sum = l * fast_exp2(m - ms) + l2 * fast_exp2(m2 - ms);
-        if (WW::kPairs) {
+        if (L::kHalves) {
           if (half == 0) shares[ww.grp * 4 * 32] = make_float2(mn, sum);
         } else {
           bias = mn + __builtin_amdgcn_logf(sum);
@@ -780,12 +781,12 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // All of it has arrived from here on: what is waited for below are tiles.  The waits count the tiles' loads back from the
   // last one issued; the counter falls in order of issue, so whatever else lies between (the stores of finish(),
   // registers spilled to scratch and read back) can make a wait longer than need be, never shorter.  Spilled
-  // registers per lane (in unequal batches): bf16 at d = 128 13 (42) with 16 units, on rotated keys none (17), with 16 units 29 (48), at
-  // d = 64 (16 with 16 units on rotated keys); fp32 at d = 128 10 (39), on rotated keys 29 (90), at d = 64 (6, on rotated keys 13);
-  // elsewhere none.
+  // registers per lane (in unequal batches), with 4, 8 and 16 units: bf16 at d = 128 - - 13 (- - 42), on rotated keys - - 29 (15 8 48), at
+  // d = 64 on rotated keys (- - 16); fp32 at d = 128, of 4 and 8 units, 7 10 (38 39), on rotated keys 29 22 (90 73), at d = 64 (- - 6), on
+  // rotated keys (- - 13); elsewhere none.
   if (MASS) {
     if constexpr (L::kThrough) wait_loads<0>();
-    if constexpr (WW::kPairs) tile_barrier();    // everyone's shares and query rows are there
+    if constexpr (L::kHalves) tile_barrier();    // everyone's shares and query rows are there
     if constexpr (L::kThrough) {
 #pragma unroll
       for (int u = 0; u < U; ++u)
