@@ -165,8 +165,8 @@ struct PlannedSplits {
   }
   static __device__ __forceinline__ int length(int n) { return n > 0 ? kPieceGranules + n : 0; }
   static __device__ __forceinline__ PlannedSequence sequence(const DecodeParams& p, int i) {
-    const int cap = max(p.cap_retain_seq[i], 0);
-    return {cap, max(p.n_approx_seq[i], 0), min(max(p.len_retain[i], 0), cap), p.ret_row_start[i], p.apx_row_start[i]};
+    const int cap = planned_rows(p.cap_retain, p.cap_retain_seq[i]);
+    return {cap, planned_rows(p.n_approx, p.n_approx_seq[i]), min(max(p.len_retain[i], 0), cap), p.ret_row_start[i], p.apx_row_start[i]};
   }
   __device__ __forceinline__ explicit PlannedSplits(const DecodeParams& p_) : p(p_) {
     const int lane = threadIdx.x & 63;

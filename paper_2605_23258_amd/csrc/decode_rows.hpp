@@ -151,6 +151,9 @@ constexpr float kPlanTurned = 1.86f;   // a granule of approximated rows that ar
 // As many workgroups as run at the same time.  Their partials, and one more for every segment, of which there are two per (sequence,
 // head), are to fit kMaxSplits per pair.
 constexpr int plan_workgroups(int per_cu, int pairs) { return 256 * per_cu < (kMaxSplits - 2) * pairs ? 256 * per_cu : (kMaxSplits - 2) * pairs; }
+// Rows of a sequence's segment.  Where the call itself says that it has none, the segment may have no memory (nor W, with no
+// approximated rows), and is left out whatever the sequence's own count says, as where every sequence gets as many splits.
+constexpr int planned_rows(int of_call, int of_sequence) { return of_call > 0 && of_sequence > 0 ? of_sequence : 0; }
 // A lane per sequence; and segments long enough for the plan to pay (a step of 24 sequences on rotated keys, as many splits for every
 // one / a plan: 5500 tokens 26.9 / 24.3 us at 18 steps; 32 of 4000, 11 steps, 24.8 / 26.7; two of 12000, 22 steps, 15.2 / 15.6).
 constexpr bool worth_a_plan(int batch, int cap_retain, int n_approx) {

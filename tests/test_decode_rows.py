@@ -136,3 +136,8 @@ int main() {
 @pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
 def test_splits_of_one_round_make_one(tmp_path):
     run(tmp_path, ONE_ROUND)
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
+def test_a_plan_leaves_out_what_the_call_leaves_out(tmp_path):
+    run(tmp_path, '#include "decode_rows.hpp"\nusing vec::planned_rows;\nint main() { return planned_rows(0, 500) || planned_rows(7, 500) != 500 || planned_rows(500, 0) || planned_rows(500, -3); }\n')

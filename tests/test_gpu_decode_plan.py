@@ -67,3 +67,37 @@ def test_step(d):
     assert np.array_equal(pl.to_host(keep[0]), np.concatenate([r.reshape(-1, d) for r in k]))
     assert np.array_equal(pl.to_host(keep[1]), np.concatenate([r.reshape(-1, d) for r in v]))
     assert np.array_equal(keep[4].cpu().numpy(), np.minimum(np.array(lens) + 1, caps))
+
+
+@pytest.mark.parametrize("retained", [True, False])
+def test_segment_that_the_call_leaves_out(retained):
+    """A capacity of 0 for the batch leaves the segment out whatever the sequences' own counts say, and its rows need no memory."""
+    rng = np.random.default_rng(retained)
+    store = lambda a: dg.f32_to_bf16_bits(np.asarray(a, np.float32))
+    d, H, G, rows, other = 128, 2, 4, [2300, 700, 1], [40, 300, 90]
+    B, Hq, scale = len(rows), H * G, 1.0 / np.sqrt(d)
+    q, W = store(rng.standard_normal((B, Hq, d))), store(rng.standard_normal((H, d, d)) / np.sqrt(d))
+    k, v = ([store(rng.standard_normal((H, n, d))) for n in rows] for _ in range(2))
+    flat = lambda x: pl.to_device(np.concatenate([r.reshape(-1, d) for r in x]))
+    starts = lambda n: pl.to_device(np.concatenate([[0], np.cumsum([H * x for x in n])[:-1]]).astype(np.int64))
+    i32 = lambda x: pl.to_device(np.array(x, np.int32))
+    ret, apx = (rows, other) if retained else (other, rows)
+    keep = [flat(k), flat(v), pl.to_device(W), i32(ret), i32(ret), i32(apx), starts(ret), starts(apx)]
+    cache = vb.Cache(batch=B, n_q_heads=Hq, n_kv_heads=H, head_dim=d, dtype=vb.VECTOR_BF16, cap_retain=max(ret) if retained else 0, n_approx=0 if retained else max(apx))
+    cache.len_retain, cache.cap_retain_seq, cache.n_approx_seq, cache.ret_row_start, cache.apx_row_start = (t.data_ptr() for t in keep[3:])
+    if retained:
+        cache.k_ret, cache.v_ret = keep[0].data_ptr(), keep[1].data_ptr()
+    else:
+        cache.k_apx, cache.W = keep[0].data_ptr(), keep[2].data_ptr()
+    shape = vb.Shape(n_q_heads=Hq, n_kv_heads=H, head_dim=d, seq_len=max(rows), window=1, pool_kernel=1, dtype=vb.VECTOR_BF16)
+    ws = pl.alloc_workspace(vb.vector_workspace_bytes(shape, max(rows), max(rows), B))
+    ws.fill_(0xff)
+    out = torch.full((B, Hq, d), 7.0, dtype=torch.float32, device="cuda:0")
+    vb.vector_decode_attn(cache, pl.to_device(q), scale, out, ws, flags=vb.VECTOR_DECODE_OUT_F32)
+    torch.cuda.synchronize()
+    none = np.zeros((1, H, 0, d))
+    for b, n in enumerate(rows):
+        kb, vbt = dg.widen(k[b])[None], dg.widen(v[b])[None]
+        ref = vo.decode_attn(dg.widen(q[b:b + 1]), kb if retained else none, vbt if retained else none, np.array([n if retained else 0]),
+                             none if retained else kb, dg.widen(W), scale)[0]
+        close(out[b].cpu().numpy(), ref, f"sequence {b}")
