@@ -1407,7 +1407,8 @@ template <typename T, int D, int G> constexpr bool kFewElements = sizeof(T) == 4
 template <auto Kernel> int workgroups_per_cu(int lds) {
   static const int n = [&] {
     int fit = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, reinterpret_cast<const void*>(Kernel), DT_, lds) != hipSuccess) (void)hipGetLastError();
+    if (set_max_lds(reinterpret_cast<const void*>(Kernel), lds) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, reinterpret_cast<const void*>(Kernel), DT_, lds) != hipSuccess) (void)hipGetLastError();
     return fit > 0 ? fit : 1;
   }();
   return n;
@@ -1466,9 +1467,16 @@ template <typename T, int D, int G, bool PAGED>
 int run_decode_layout(const vector_cache& c, DecodeParams& p, hipStream_t stream, const RopeParams* rope) {
   int rc;
   if constexpr (!PAGED && Elem<T>::kDtype == VECTOR_BF16) {
-    if (c.cap_retain_seq && !p.literal && worth_a_plan(c.batch, c.cap_retain, c.n_approx)) {
-      if (rope) return launch_planned<decode_split_mfma_kernel<D, G, true, false, false, true>, T, D, G>(c, p, stream, rope);
-      return launch_planned<decode_split_mfma_kernel<D, G, false, false, false, true>, T, D, G>(c, p, stream, rope);
+    if (c.cap_retain_seq && !p.literal) {
+      constexpr int lds = MfmaDecodeTile<D>::kTiles;
+      if constexpr (D == 128) {
+        constexpr auto turned = decode_split_mfma_kernel<D, G, true, false, false, true>;
+        if (rope && worth_a_plan(D, true, workgroups_per_cu<turned>(lds), c.batch, c.n_kv_heads, c.cap_retain, c.n_approx))
+          return launch_planned<turned, T, D, G>(c, p, stream, rope);
+      }
+      constexpr auto plain = decode_split_mfma_kernel<D, G, false, false, false, true>;
+      if (!rope && worth_a_plan(D, false, workgroups_per_cu<plain>(lds), c.batch, c.n_kv_heads, c.cap_retain, c.n_approx))
+        return launch_planned<plain, T, D, G>(c, p, stream, rope);
     }
   }
   if constexpr (Elem<T>::kDtype == VECTOR_BF16) {

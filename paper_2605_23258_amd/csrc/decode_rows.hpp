@@ -154,10 +154,19 @@ constexpr int plan_workgroups(int per_cu, int pairs) { return 256 * per_cu < (kM
 // Rows of a sequence's segment.  Where the call itself says that it has none, the segment may have no memory (nor W, with no
 // approximated rows), and is left out whatever the sequence's own count says, as where every sequence gets as many splits.
 constexpr int planned_rows(int of_call, int of_sequence) { return of_call > 0 && of_sequence > 0 ? of_sequence : 0; }
-// A lane per sequence; and segments long enough for the plan to pay (a step of 24 sequences on rotated keys, as many splits for every
-// one / a plan: 5500 tokens 26.9 / 24.3 us at 18 steps; 32 of 4000, 11 steps, 24.8 / 26.7; two of 12000, 22 steps, 15.2 / 15.6).
-constexpr bool worth_a_plan(int batch, int cap_retain, int n_approx) {
-  return batch > 1 && batch <= kMaxPlanned && ((int64_t)cap_retain + 127) / 128 + ((int64_t)n_approx + 127) / 128 >= 16;
+// A lane per sequence; and enough steps of rows for the launch's workgroups (every sequence counted as the longest), since a plan costs
+// a workgroup about a step, and small launches end when their one or two steps do, however they are cut.  Measured on one in which the longest
+// sequence has four times the shortest one's rows, retained : approximated rows 1/6 to 6, as many splits for every sequence / a plan, us:
+//   128 dims, from three steps per workgroup: 6 sequences of 4000 rows 20.5 / 19.9 (rotated 26.1 / 23.5), 16 of 3200 28.1 / 26.9 (36.6 / 32.3), 12 of 8000 48.0 / 45.0
+//     (59.2 / 49.9); in the mean of 60 shapes of three to four steps 4 % less, at worst 5 % more (16 query heads: 9 %).  Below: 2 of 1700 11.1 / 13.1 (13.1 / 14.9), two heads,
+//     4 of 8000 13.9 / 16.5 (18.1 / 20.5), 6 of 1700 9.9 / 12.5; 3 of 3200 13.8 / 15.3 (but rotated 19.0 / 17.2).
+//   64 dims, plain, from eight: 12 of 8000 30.1 / 27.7, 32 of 4000 35.6 / 33.0, 64 of 3200 51.5 / 48.4; below, 16 of 1700 13.9 / 15.5, 16 of 3200 18.1 / 19.3, two heads,
+//     64 of 1700 14.1 / 15.1.  Rotated, whose pieces of approximated rows are cut well by the estimate, never: 64 of 3200 49.5 / 57.4, 24 of 3200 26.9 / 28.4, 16 of 8000
+//     35.5 / 36.1, and at best (12 of 8000) 31.7 / 30.5.
+constexpr bool worth_a_plan(int head_dim, bool turned, int per_cu, int batch, int n_kv_heads, int cap_retain, int n_approx) {
+  if (batch < 2 || batch > kMaxPlanned || (head_dim == 64 && turned)) return false;
+  const int64_t steps = ((int64_t)cap_retain + 127) / 128 + ((int64_t)n_approx + 127) / 128;
+  return steps * batch * n_kv_heads >= (head_dim == 64 ? 8 : 3) * 256 * (int64_t)per_cu;
 }
 
 }  // namespace vec

@@ -141,3 +141,24 @@ def test_splits_of_one_round_make_one(tmp_path):
 @pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
 def test_a_plan_leaves_out_what_the_call_leaves_out(tmp_path):
     run(tmp_path, '#include "decode_rows.hpp"\nusing vec::planned_rows;\nint main() { return planned_rows(0, 500) || planned_rows(7, 500) != 500 || planned_rows(500, 0) || planned_rows(500, -3); }\n')
+
+
+# Unequal sequences for which a plan and as many splits for every one were measured more than 3 % apart
+PLANNED = [
+    # head_dim, rotated keys, workgroups per CU, sequences, KV heads, largest capacity, most approximated rows, whether the plan is the faster
+    (128, 0, 2, 2, 8, 1106, 850, 0), (128, 1, 2, 2, 8, 1106, 850, 0), (128, 0, 2, 3, 8, 1856, 1600, 0), (128, 1, 2, 4, 8, 1106, 850, 0),
+    (128, 0, 2, 4, 2, 4256, 4000, 0), (128, 1, 2, 4, 2, 4256, 4000, 0), (128, 0, 2, 6, 2, 1106, 850, 0), (128, 1, 2, 8, 2, 4256, 4000, 0),
+    (128, 0, 2, 8, 8, 1856, 1600, 1), (128, 1, 2, 6, 8, 4256, 4000, 1), (128, 0, 2, 16, 8, 1106, 850, 1), (128, 0, 2, 64, 2, 4256, 4000, 1),
+    (128, 0, 2, 24, 8, 2999, 457, 1), (128, 1, 2, 24, 8, 2999, 457, 1), (128, 0, 2, 24, 8, 3456, 0, 1),
+    (64, 0, 3, 3, 8, 4256, 4000, 0), (64, 0, 3, 16, 8, 1106, 850, 0), (64, 0, 3, 16, 8, 1856, 1600, 0), (64, 0, 3, 64, 2, 1106, 850, 0),
+    (64, 1, 3, 64, 8, 1856, 1600, 0), (64, 1, 3, 24, 8, 1856, 1600, 0), (64, 1, 3, 6, 2, 4256, 4000, 0),
+    (64, 0, 3, 12, 8, 4256, 4000, 1), (64, 0, 3, 32, 8, 2256, 2000, 1), (64, 0, 3, 64, 8, 1856, 1600, 1),
+    # one sequence, and more than a wave has lanes
+    (128, 0, 2, 1, 8, 100000, 100000, 0), (128, 0, 2, 65, 8, 4000, 4000, 0),
+]
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
+def test_plans_where_they_were_measured_faster(tmp_path):
+    lines = "".join("  if (vec::worth_a_plan(%d, %d, %d, %d, %d, %d, %d) != %d) { printf(\"%s\\n\"); bad = 1; }\n" % (shape + (shape,)) for shape in PLANNED)
+    run(tmp_path, '#include <cstdio>\n#include "decode_rows.hpp"\nint main() {\n  int bad = 0;\n' + lines + "  return bad;\n}\n")

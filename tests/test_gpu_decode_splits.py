@@ -44,8 +44,9 @@ def check(got, q, k_ret, v_ret, k_apx, W, scale, what, pos=None, inv=None):
         assert told_apart(ref, reference(q, k_ret, v_ret, k_apx, W, scale, pos + 1, inv)), f"{what}: blind to the positions"
 
 
-def run(d, G, H, lens, apxs, ragged, rope=False, literal=False, seed=0):
-    """One attention over sequences of lens[b] retained and apxs[b] approximated rows; `ragged`: blocks of their own."""
+def run(d, G, H, lens, apxs, ragged, rope=False, literal=False, seed=0, steer=0):
+    """One attention over sequences of lens[b] retained and apxs[b] approximated rows; `ragged`: blocks of their own, with at least
+    `steer` as the largest capacity, which there only steers how the work is split."""
     rng = np.random.default_rng(seed)
     store = lambda a: dg.f32_to_bf16_bits(a.astype(np.float32))
     B, Hq = len(lens), H * G
@@ -62,7 +63,7 @@ def run(d, G, H, lens, apxs, ragged, rope=False, literal=False, seed=0):
     scale, inv = 1.0 / np.sqrt(d), dg.rotary_inv_freq(d, THETA)
     flat = lambda rows: pl.to_device(np.concatenate([r.reshape(-1, d) for r in rows] + [np.zeros((1, d), np.uint16)]))
     keep = [flat(k_ret), flat(v_ret), flat(k_apx), pl.to_device(W), pl.to_device(np.array(lens, dtype=np.int32))]
-    cache = vb.Cache(batch=B, n_q_heads=Hq, n_kv_heads=H, head_dim=d, dtype=vb.VECTOR_BF16, cap_retain=max(caps), n_approx=max(apxs))
+    cache = vb.Cache(batch=B, n_q_heads=Hq, n_kv_heads=H, head_dim=d, dtype=vb.VECTOR_BF16, cap_retain=max(max(caps), steer), n_approx=max(apxs))
     cache.k_ret, cache.v_ret, cache.k_apx, cache.W, cache.len_retain = (t.data_ptr() for t in keep)
     if ragged:
         starts = lambda n: np.concatenate([[0], np.cumsum([H * x for x in n])[:-1]]).astype(np.int64)
