@@ -54,6 +54,7 @@ struct DecodeParams {
   // a step of approximated rows counts in steps of retained ones
   int2* plan;
   float plan_apx;
+  int plan_most_retained;       // workgroups
   int64_t w_sh;           // element stride between per-head W
   float c2;               // scale * log2(e)
   int literal;            // approximated rows: rebuild v_hat = k W per row instead of (sum p k) W
@@ -141,10 +142,8 @@ template <int STEP> __device__ __forceinline__ SplitRows grid_split(const Decode
 // every workgroup adds the work up itself, lane b that of sequence b.  The retained rows are one line, sequence after
 // sequence, head after head, and the approximated rows another; the first workgroups share the first, the others the second, so
 // that a CU, which gets two workgroups half a grid apart, has one of each (all of both lines in one, 32 sequences of up to
-// 32768 tokens 89 us, now 86; 16 of them 52.5, 48.6).  A segment is kPieceGranules for the change to it and one unit per granule
-// of 32 rows; a workgroup takes the granules that begin in its share.  A share has room for a step of granules, so a
-// segment's partials are those of workgroups next to each other, and (sequence, head), counted, keeps segments apart: place
-// workgroup + that number.  The workgroup with a segment's first granule says in `plan` where they begin and how many there are.
+// 32768 tokens 89 us, now 86; 16 of them 52.5, 48.6).  A workgroup takes the granules that begin in its share; the arithmetic is in
+// decode_rows.hpp.  The workgroup with a segment's first granule says in `plan` where its partials begin and how many there are.
 //   A step, us, as many splits for every sequence / this: 24 sequences of 4000 to 16000 tokens on rotated keys 51.5 / 44.6, plain 43.1 /
 //   40.4; 16 of 8192 to 32768 62.2 / 52.2, plain 55.2 / 48.6.
 struct PlannedSequence { int cap, n_approx, live; long long ret0, apx0; };
@@ -157,13 +156,12 @@ struct PlannedSplits {
   // Scalars are kept scalar: the compiler would keep in vector registers what follows from a float or from memory.
   static __device__ __forceinline__ int same(int x) { return __builtin_amdgcn_readfirstlane(x); }
   static __device__ __forceinline__ long long same(long long x) { return ((long long)same((int)(x >> 32)) << 32) | (uint32_t)same((int)x); }
-  __device__ __forceinline__ int granules(int len) const { return (int)(((unsigned)len + (1u << log_rows) - 1u) >> log_rows); }
+  __device__ __forceinline__ int granules(int len) const { return plan_granules(len, log_rows); }
   // of a sequence with nothing cached an empty granule, whose workgroup writes the empty partial
   __device__ __forceinline__ int granules_ret(const PlannedSequence& x) const {
     const int n = granules(x.live + (p.k_new ? 1 : 0));
     return x.n_approx == 0 ? max(n, 1) : n;
   }
-  static __device__ __forceinline__ int length(int n) { return n > 0 ? kPieceGranules + n : 0; }
   static __device__ __forceinline__ PlannedSequence sequence(const DecodeParams& p, int i) {
     const int cap = planned_rows(p.cap_retain, p.cap_retain_seq[i]);
     return {cap, planned_rows(p.n_approx, p.n_approx_seq[i]), min(max(p.len_retain[i], 0), cap), p.ret_row_start[i], p.apx_row_start[i]};
@@ -173,29 +171,23 @@ struct PlannedSplits {
     const PlannedSequence x = sequence(p, min(lane, p.B - 1));
     // granules so long that a line stays shorter than kMaxPlanUnits: 32 rows unless the cache were larger than the memory
     log_rows = kLogGranule;
-    int len_r = length(granules_ret(x)), len_a = length(granules(x.n_approx));
+    int len_r = plan_length(granules_ret(x)), len_a = plan_length(granules(x.n_approx));
     float top_r = wave_max_dpp((float)len_r), top_a = wave_max_dpp((float)len_a);
-    while (__builtin_expect(fmaxf(top_r, top_a) * (float)p.B * (float)p.Hkv >= (float)kMaxPlanUnits && log_rows < 30, 0)) {
+    while (__builtin_expect(plan_too_long(fmaxf(top_r, top_a), p.B, p.Hkv, log_rows), 0)) {
       log_rows = same(log_rows + 1);
-      len_r = length(granules_ret(x));
-      len_a = length(granules(x.n_approx));
+      len_r = plan_length(granules_ret(x));
+      len_a = plan_length(granules(x.n_approx));
       top_r = wave_max_dpp((float)len_r);
       top_a = wave_max_dpp((float)len_a);
     }
     const int seq_r = lane < p.B ? len_r * p.Hkv : 0, seq_a = lane < p.B ? len_a * p.Hkv : 0;
     const int upto_r = wave_incl_scan_dpp(seq_r), upto_a = wave_incl_scan_dpp(seq_a);
     const int total_r = __builtin_amdgcn_readlane(upto_r, 63), total_a = __builtin_amdgcn_readlane(upto_a, 63), wgs = gridDim.x;
-    const float work_r = (float)total_r, work_a = (float)total_a * p.plan_apx;
-    int wgs_r = same((int)((float)wgs * work_r * __builtin_amdgcn_rcpf(work_r + work_a) + 0.5f));
-    // by their work, but half of them where there are approximated rows to go with retained ones
-    wgs_r = max(total_a > 0 ? min(wgs_r, wgs / 2) : wgs, total_r > 0 ? 1 : 0);
+    const int wgs_r = same(plan_retained(wgs, p.plan_most_retained, total_r, total_a, __builtin_amdgcn_rcpf((float)total_r + (float)total_a * p.plan_apx)));
     id = blockIdx.x;
     is_apx = id >= wgs_r;
     const int mine = is_apx ? id - wgs_r : id, total = is_apx ? total_a : total_r;
-    // an even share, rounded up, and by as much as its float may be below it; no more than half of kMaxSplits for a segment
-    const float even = fmaxf((float)total * 1.000001f * __builtin_amdgcn_rcpf((float)(is_apx ? wgs - wgs_r : wgs_r)),
-                             (is_apx ? top_a : top_r) * (1.f / (float)(kMaxSplits / 2 - 2)));
-    share = max(same((int)even) + 1, kStepGranules);
+    share = same(plan_share(total, is_apx ? top_a : top_r, __builtin_amdgcn_rcpf((float)(is_apx ? wgs - wgs_r : wgs_r))));
     lo = mine * share;
     hi = lo + share;
     done = lo >= total;                      // of small caches fewer workgroups than the grid has
@@ -206,9 +198,7 @@ struct PlannedSplits {
     b = __popcll(__ballot(upto <= lo));
     at = __builtin_amdgcn_readlane(upto - of_sequence, b);
     const int head = __builtin_amdgcn_readlane(is_apx ? len_a : len_r, b);
-    h = same((int)((float)(lo - at) * __builtin_amdgcn_rcpf((float)head)));       // at most one off
-    if (h * head > lo - at) --h;
-    if ((h + 1) * head <= lo - at) ++h;
+    h = same(plan_head(lo - at, head, __builtin_amdgcn_rcpf((float)head)));
     at += h * head;
     auto of_b = [&](int v) VEC_INLINE { return __builtin_amdgcn_readlane(v, b); };
     auto of_b64 = [&](long long v) VEC_INLINE { return ((long long)of_b((int)(v >> 32)) << 32) | (uint32_t)of_b((int)v); };
@@ -218,22 +208,21 @@ struct PlannedSplits {
   __device__ __forceinline__ bool next(SplitRows& r) {
     while (!done) {
       const int n_r = granules_ret(s), n_a = granules(s.n_approx), n = is_apx ? n_a : n_r;
-      const int first = at + kPieceGranules;         // where granule 0 begins
-      const int g0 = max(lo - first, 0), g1 = min(hi - first, n);
-      const int pair = b * p.Hkv + h, place = id + pair + (is_apx ? p.B * p.Hkv : 0);
-      const bool any = g0 < g1;
+      const PlanPiece piece = plan_piece(at, n, lo, share);
+      const int pair = b * p.Hkv + h, place = plan_place(id, pair, is_apx, p.B * p.Hkv);
+      const bool any = piece.first < piece.last;
       if (any) {
         r.b = b; r.h = h; r.is_apx = is_apx;
         r.seg = sequence_rows(p, b, h, s.cap, s.n_approx, s.live, s.ret0, s.apx0);
-        r.begin = g0 << log_rows;
-        r.end = (int)min((int64_t)(is_apx ? r.seg.n_approx : r.seg.len_retain), (int64_t)g1 << log_rows);
+        r.begin = piece.first << log_rows;
+        r.end = (int)min((int64_t)(is_apx ? r.seg.n_approx : r.seg.len_retain), (int64_t)piece.last << log_rows);
         r.slot = (size_t)place;
-        if (g0 == 0 && threadIdx.x == 0) {
-          p.plan[2 * pair + (is_apx ? 1 : 0)] = make_int2(place, (first + n - 1) / share - lo / share + 1);
+        if (piece.first == 0 && threadIdx.x == 0) {
+          p.plan[2 * pair + (is_apx ? 1 : 0)] = make_int2(place, plan_partials(at, n, lo, share));
           if ((is_apx ? n_r : n_a) == 0) p.plan[2 * pair + (is_apx ? 0 : 1)] = make_int2(0, 0);
         }
       }
-      at += length(n);
+      at += plan_length(n);
       done = at >= hi;
       if (++h == p.Hkv) {
         h = 0;
@@ -1457,7 +1446,9 @@ int launch_planned(const vector_cache& c, DecodeParams& p, hipStream_t stream, c
   const int pairs = c.batch * c.n_kv_heads;
   p.plan_apx = rope ? kPlanTurned : 1.f;
   p.plan = reinterpret_cast<int2*>(p.part + (size_t)pairs * kMaxSplits * (2 * G + G * D));      // behind the partials, half of the workspace
-  VEC_LAUNCH(K_DECODE_SPLIT, Kernel, dim3(plan_workgroups(workgroups_per_cu<Kernel>(lds), pairs)), dim3(DT_), lds, stream, p, rope ? *rope : RopeParams{});
+  const int per_cu = workgroups_per_cu<Kernel>(lds), wgs = plan_workgroups(per_cu, pairs);
+  p.plan_most_retained = plan_most_retained(per_cu, wgs);
+  VEC_LAUNCH(K_DECODE_SPLIT, Kernel, dim3(wgs), dim3(DT_), lds, stream, p, rope ? *rope : RopeParams{});
   VEC_LAUNCH(K_DECODE_COMBINE, merge, dim3(c.n_kv_heads, c.batch), dim3(DT_), merge_lds, stream, p);
   VEC_HIP(hipGetLastError());
   return VECTOR_OK;
@@ -1553,6 +1544,7 @@ int launch_decode_attn(const vector_cache& c, const void* q, float scale, void* 
   p.c2 = scale * kLog2e;
   p.plan = nullptr;
   p.plan_apx = 0.f;
+  p.plan_most_retained = 0;
   p.by_kind = 0;
   if (c.dtype == VECTOR_BF16) {
     if (c.head_dim == 128) return run_decode_g<bf16_t, 128>(c, p, stream, rope);

@@ -151,6 +151,43 @@ constexpr float kPlanTurned = 1.86f;   // a granule of approximated rows that ar
 // As many workgroups as run at the same time.  Their partials, and one more for every segment, of which there are two per (sequence,
 // head), are to fit kMaxSplits per pair.
 constexpr int plan_workgroups(int per_cu, int pairs) { return 256 * per_cu < (kMaxSplits - 2) * pairs ? 256 * per_cu : (kMaxSplits - 2) * pairs; }
+// What the workgroups of a plan compute; `inverse` is that of the float named, one step off at most.
+// A line of rows is a sequence of segments, each as long as its granules and kPieceGranules for the change to it.
+constexpr int plan_granules(int rows, int log_rows) { return (int)(((unsigned)rows + (1u << log_rows) - 1u) >> log_rows); }
+constexpr int plan_length(int granules) { return granules > 0 ? kPieceGranules + granules : 0; }
+// whether a line could be too long, `longest` the length of its longest segment: then granules are twice as long
+constexpr bool plan_too_long(float longest, int batch, int n_kv_heads, int log_rows) {
+  return longest * (float)batch * (float)n_kv_heads >= (float)kMaxPlanUnits && log_rows < 30;
+}
+// The most workgroups for the retained line where there are approximated rows to go with it: half of them
+constexpr int plan_most_retained(int per_cu, int wgs) { (void)per_cu; return wgs / 2; }
+// Workgroups of the retained line: by the lines' work.  inverse: of total_r + total_a * apx
+constexpr int plan_retained(int wgs, int most, int total_r, int total_a, float inverse) {
+  const int by_work = (int)((float)wgs * (float)total_r * inverse + 0.5f), wgs_r = total_a > 0 ? (by_work < most ? by_work : most) : wgs;
+  return total_r > 0 && wgs_r < 1 ? 1 : wgs_r;
+}
+// A workgroup's share of its line: an even one, rounded up, and by as much as its float may be below it; no more than half of kMaxSplits for
+// a segment.  inverse: of the line's workgroups
+constexpr int plan_share(int total, float longest, float inverse) {
+  const float even = (float)total * 1.000001f * inverse, least = longest * (1.f / (float)(kMaxSplits / 2 - 2));
+  const int share = (int)(even > least ? even : least) + 1;
+  return share > kStepGranules ? share : kStepGranules;
+}
+// The head whose segment a place lies in, `offset` from where its sequence begins.  inverse: of the segment's length
+constexpr int plan_head(int offset, int length, float inverse) {
+  const int h = (int)((float)offset * inverse), not_after = h * length > offset ? h - 1 : h;           // at most one off
+  return (not_after + 1) * length <= offset ? not_after + 1 : not_after;
+}
+// Granules first .. last - 1 of a segment of n that begins at `at` fall to the workgroup whose share begins at lo
+struct PlanPiece { int first, last; };
+constexpr PlanPiece plan_piece(int at, int n, int lo, int share) {
+  const int zero = at + kPieceGranules;         // where granule 0 begins
+  return {lo > zero ? lo - zero : 0, lo + share - zero < n ? lo + share - zero : n};
+}
+// Where the partial of workgroup `id` goes, `pair` the (sequence, head): a share has room for a step of granules, so a segment's
+// workgroups are next to each other; of how many partials a segment has the workgroup with granule 0 knows
+constexpr int plan_place(int id, int pair, bool is_apx, int pairs) { return id + pair + (is_apx ? pairs : 0); }
+constexpr int plan_partials(int at, int n, int lo, int share) { return (at + kPieceGranules + n - 1) / share - lo / share + 1; }
 // Rows of a sequence's segment.  Where the call itself says that it has none, the segment may have no memory (nor W, with no
 // approximated rows), and is left out whatever the sequence's own count says, as where every sequence gets as many splits.
 constexpr int planned_rows(int of_call, int of_sequence) { return of_call > 0 && of_sequence > 0 ? of_sequence : 0; }

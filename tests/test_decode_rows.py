@@ -162,3 +162,107 @@ PLANNED = [
 def test_plans_where_they_were_measured_faster(tmp_path):
     lines = "".join("  if (vec::worth_a_plan(%d, %d, %d, %d, %d, %d, %d) != %d) { printf(\"%s\\n\"); bad = 1; }\n" % (shape + (shape,)) for shape in PLANNED)
     run(tmp_path, '#include <cstdio>\n#include "decode_rows.hpp"\nint main() {\n  int bad = 0;\n' + lines + "  return bad;\n}\n")
+
+
+# A plan's workgroups, one after another, over sequences of random and of extreme lengths: every granule belongs to one of them, no two
+# partials share a place, a segment's lie next to each other from the one with granule 0 on, and there are no more than the merge has room for.
+# The inverses a bit too small, exact and a bit too large.
+PLAN = r"""
+#include <cstdio>
+#include <map>
+#include <random>
+#include <vector>
+#include "decode_rows.hpp"
+using namespace vec;
+struct Segment { int n, next = 0, place = -1, count = 0, said_place = -1, said_count = 0; };
+int check(const std::vector<int>& ret, const std::vector<int>& apx, int H, int per_cu, float plan_apx, float off) {
+  const int B = (int)ret.size(), pairs = B * H, wgs = plan_workgroups(per_cu, pairs), most = plan_most_retained(per_cu, wgs);
+  int log_rows = kLogGranule;
+  std::vector<int> len[2];
+  std::vector<Segment> segments[2];
+  float top[2];
+  for (;; ++log_rows) {
+    for (int s = 0; s < 2; ++s) {
+      len[s].clear(); segments[s].clear(); top[s] = 0.f;
+      for (int b = 0; b < B; ++b) {
+        int n = plan_granules(s ? apx[b] : ret[b], log_rows);
+        if (s == 0 && apx[b] == 0 && n < 1) n = 1;
+        len[s].push_back(plan_length(n));
+        top[s] = std::max(top[s], (float)plan_length(n));
+        for (int h = 0; h < H; ++h) { segments[s].push_back({}); segments[s].back().n = n; }
+      }
+    }
+    if (!plan_too_long(std::max(top[0], top[1]), B, H, log_rows)) break;
+  }
+  long long total[2] = {0, 0};
+  for (int s = 0; s < 2; ++s) for (int x : len[s]) total[s] += (long long)x * H;
+  if (total[0] > kMaxPlanUnits * 1.0001 || total[1] > kMaxPlanUnits * 1.0001) { printf("line of %lld + %lld\n", total[0], total[1]); return 1; }
+  auto inverse = [&](float x) { return 1.0f / x * off; };
+  const int wgs_r = plan_retained(wgs, most, (int)total[0], (int)total[1], inverse((float)total[0] + (float)total[1] * plan_apx));
+  if (wgs_r > wgs || (total[0] && wgs_r < 1) || (total[1] && wgs_r >= wgs)) { printf("%d of %d workgroups\n", wgs_r, wgs); return 1; }
+  std::map<long long, int> places;
+  for (int id = 0; id < wgs; ++id) {
+    const int s = id >= wgs_r, mine = s ? id - wgs_r : id, share = plan_share((int)total[s], top[s], inverse((float)(s ? wgs - wgs_r : wgs_r)));
+    const long long lo64 = (long long)mine * share;
+    if (lo64 + share > 2147483647ll) { printf("share %d of workgroup %d\n", share, mine); return 1; }
+    const int lo = (int)lo64;
+    if (lo >= total[s]) continue;
+    long long at = 0;
+    int b = 0;
+    while (at + (long long)len[s][b] * H <= lo) at += (long long)len[s][b++] * H;
+    int h = plan_head(lo - (int)at, len[s][b], inverse((float)len[s][b]));
+    at += (long long)h * len[s][b];
+    if (h < 0 || h >= H || at > lo || at + len[s][b] <= lo) { printf("head %d\n", h); return 1; }
+    while (b < B && at < lo64 + share) {
+      Segment& g = segments[s][b * H + h];
+      const PlanPiece piece = plan_piece((int)at, g.n, lo, share);
+      if (piece.first < piece.last) {
+        const int place = plan_place(id, b * H + h, s, pairs);
+        if (piece.first != g.next || piece.last > g.n || place < 0 || place >= kMaxSplits * pairs || places.count(place)) {
+          printf("segment %d of %d granules: %d..%d after %d, place %d\n", b * H + h, g.n, piece.first, piece.last, g.next, place);
+          return 1;
+        }
+        places[place] = 1;
+        if (g.count == 0) g.place = place;
+        if (place != g.place + g.count) { printf("places %d and %d\n", g.place, place); return 1; }
+        ++g.count;
+        g.next = piece.last;
+        if (piece.first == 0) { g.said_place = place; g.said_count = plan_partials((int)at, g.n, lo, share); }
+      }
+      at += plan_length(g.n);
+      if (++h == H) { h = 0; ++b; }
+    }
+  }
+  for (int s = 0; s < 2; ++s)
+    for (const Segment& g : segments[s])
+      if (g.next != g.n || g.count > kMaxSplits / 2 || g.count != g.said_count || (g.n && g.place != g.said_place)) {
+        printf("segment of %d granules: %d, %d partials at %d, said %d at %d\n", g.n, g.next, g.count, g.place, g.said_count, g.said_place);
+        return 1;
+      }
+  return 0;
+}
+int main() {
+  std::mt19937 rng(1);
+  const float offs[] = {1.f - 1.2e-7f, 1.f, 1.f + 1.2e-7f};
+  for (int i = 0; i < 30000; ++i) {
+    const int B = 2 + rng() % (i % 5 ? 20 : 63), H = i % 7 ? 1 + rng() % 8 : 1 + rng() % 40, per_cu = 1 + rng() % 4;
+    // of one case the lengths reach from up to a few granules to up to all that 32 bits hold
+    auto length = [&](int bits) { return rng() % 4 == 0 ? 0 : (int)(rng() >> (31 - (bits ? rng() % bits : 0)) & 0x7fffffff) + (int)(rng() % 2); };
+    const int bits_r = 1 + rng() % (i % 10 ? 17 : 30), bits_a = 1 + rng() % (i % 10 ? 17 : 30);
+    std::vector<int> ret, apx;
+    for (int b = 0; b < B; ++b) { ret.push_back(length(bits_r)); apx.push_back(i % 11 ? length(bits_a) : 0); }
+    if (i % 13 == 0) ret.assign(B, ret[0]), apx.assign(B, apx[0]);
+    if (i % 17 == 0) ret.assign(B, 0);
+    if (check(ret, apx, H, per_cu, i % 2 ? 1.f : kPlanTurned, offs[i % 3])) { printf("case %d: %d sequences, %d heads\n", i, B, H); return 1; }
+  }
+  // the longest lines
+  for (int B : {2, 64}) for (int H : {1, 8, 1000}) for (int n : {2147483646, 1 << 30, 1 << 20})
+    if (check(std::vector<int>(B, n), std::vector<int>(B, n / 3), H, 2, 1.f, 1.f)) { printf("%d sequences of %d, %d heads\n", B, n, H); return 1; }
+  return 0;
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
+def test_plans_share_every_row_out_once(tmp_path):
+    run(tmp_path, PLAN)
