@@ -159,8 +159,15 @@ constexpr int plan_length(int granules) { return granules > 0 ? kPieceGranules +
 constexpr bool plan_too_long(float longest, int batch, int n_kv_heads, int log_rows) {
   return longest * (float)batch * (float)n_kv_heads >= (float)kMaxPlanUnits && log_rows < 30;
 }
-// The most workgroups for the retained line where there are approximated rows to go with it: half of them
-constexpr int plan_most_retained(int per_cu, int wgs) { (void)per_cu; return wgs / 2; }
+// The most workgroups for the retained line where there are approximated rows: all but one of every CU's, so that each CU has at most
+// so many pieces of two tensors (workgroups that are a CU's lie 256 apart).  Shares by work alone are slower however uneven the lines, also with one
+// piece of approximated rows in all, and so for them the retained line's are the longest.  A step of unequal sequences, us:
+//   128 dims, two per CU, 24 of 3200 rows, retained : approximated 1.3, 2, 3.5, 6 and 32 approximated rows in all: at most half 39.4, 41.9, 43.6, 44.6, 46.1; at most three
+//     quarters 43.9, 45.0, 46.2, 48.2, 50.0; by work alone 43.9, 45.0, 46.2, 47.2, 52.7; as many splits for every sequence 44.3, 47.8, 45.6, 46.9, 49.9.  (At 1 and below
+//     the work gives less than half.)  Rotated 44.4, 45.7, 44.5, 46.3, 46.5; 44.3, 45.7, 48.9, 49.5, 50.4; 44.4, 45.7, 49.0, 49.4, 50.6; 50.2, 49.5, 49.7, 47.7, 49.1.
+//   64 dims, three per CU, 40 of 3200 rows at 2, 3.5, 6, 30: half 37.3, 37.8, 39.5, 41.4; two thirds 35.9, 36.3, 38.2, 39.7; three quarters 35.9, 38.8, 41.2, 44.2; as many splits
+//     34.1, 36.8, 38.7, 40.2.  64 of 1700: 31.7, 34.8, 35.6, 37.9; 31.1, 32.3, 33.2, 35.2; 31.1, 34.4, 35.5, 38.5; 29.7, 31.9, 33.1, 35.8.
+constexpr int plan_most_retained(int per_cu, int wgs) { return per_cu > 2 ? wgs / per_cu * (per_cu - 1) : wgs / 2; }
 // Workgroups of the retained line: by the lines' work.  inverse: of total_r + total_a * apx
 constexpr int plan_retained(int wgs, int most, int total_r, int total_a, float inverse) {
   const int by_work = (int)((float)wgs * (float)total_r * inverse + 0.5f), wgs_r = total_a > 0 ? (by_work < most ? by_work : most) : wgs;

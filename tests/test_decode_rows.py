@@ -266,3 +266,13 @@ int main() {
 @pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
 def test_plans_share_every_row_out_once(tmp_path):
     run(tmp_path, PLAN)
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
+def test_every_cu_of_a_plan_keeps_a_workgroup_for_approximated_rows(tmp_path):
+    """Of the workgroups of a CU, 256 apart, all but the last are for retained rows where these are nearly all of the work (64 dims, three per
+    CU: half of all, as with two, took up to 8 % longer); with less of them the work says how many."""
+    run(tmp_path, '#include "decode_rows.hpp"\nint main() {\n  for (int per_cu = 2; per_cu <= 4; ++per_cu) {\n    const int wgs = vec::plan_workgroups(per_cu, 200);\n'
+        '    const int most = vec::plan_most_retained(per_cu, wgs);\n'
+        '    if (wgs != 256 * per_cu || most != 256 * (per_cu - 1) || vec::plan_retained(wgs, most, 100000, 100, 1.f / 100100.f) != most) return 1;\n'
+        '    if (vec::plan_retained(wgs, most, 1000, 3000, 1.f / 4000.f) != wgs / 4 || vec::plan_retained(wgs, most, 1000, 0, 1.f / 1000.f) != wgs) return 1;\n  }\n  return 0;\n}\n')
