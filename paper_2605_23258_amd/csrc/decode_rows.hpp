@@ -111,7 +111,7 @@ inline void pick_splits(const SplitCosts& c, int batch, int n_kv_heads, int cap_
   }
 }
 
-// Splits that make one round of workgroups; at least least_ret of them for the retained segment.  For plain rows of 128 dims in bf16,
+// Splits that make one round of workgroups, or one piece of either segment for many sequences; at least least_ret of them for the retained segment.  For plain rows of 128 dims in bf16,
 // whose launch puts the retained pieces of all sequences first, the approximated ones behind them: the workgroups of a CU,
 // half a grid apart, are then one of each where there are as many of both, and every XCD has both kinds.  (In the order (split,
 // head, sequence) an XCD has one split of eight, often all retained or all approximated.)  What a round takes: its bytes, or the steps
@@ -123,11 +123,21 @@ inline void pick_splits(const SplitCosts& c, int batch, int n_kv_heads, int cap_
 //   Four times as many approximated rows as retained ones 75.2 / 70.9; four times as many retained ones 93.3 / 97.7 (26.7 / 27.1 for nine
 //   sequences of 12000): more than three times as many are left to the estimate.  Rotated keys (approximated rows are vector
 //   work) 69.2 / 82, and rows of 64 dims 37.1 / 37.5, 30.8 / 32.9, 14.7 / 14.7: the estimate.
+// With more (sequence, head) pairs than half a round it is one piece of either segment each, and the order is all there is to choose.  A few
+// workgroups beyond a round end alone: up to half a round more is left to the estimate, and all where the retained segment is the longer by
+// half.  The estimate / these in that order, eight heads, retained + approximated rows, 256 more of capacity:
+//   2000 + 2000: 33 sequences 89.3 / 99.0, 40 96.2 / 104.3 (with 344 to 383 pairs, 43 110.1 / 107.5 is given up); 48 117.0 / 113.2, 64 146.6 / 143.2, 65 152.8 / 160.1, 96 216.2 / 209.9;
+//   700 + 700: 33 41.2 / 43.4, 43 47.0 / 47.8; 52 54.3 / 50.8, 64 61.7 / 59.2, 128 112.0 / 109.0; 1200 + 2400: 36 79.8 / 84.5; 48 99.4 / 94.6, 64 115.8 / 116.5, 80 157.5 / 151.6;
+//   2400 + 1200: 36 88.7 / 94.1, 48 111.0 / 113.5, 64 142.3 / 146.8, 96 211.4 / 212.7.
+// Inside a round, one piece each with the approximated one longer by half: left to the estimate where that comes to one piece each as well
+// (1600 + 3500: 28 75.7 / 80.3, 32 85.1 / 87.2; 1000 + 3000: 28 63.2 / 65.3, 32 67.4 / 67.7; but 24, which it cuts finer, 63.2 / 61.0), and where
+// less than three quarters of a round would run (1600 + 3500: 22 67.9 / 71.4, one query head 65.2 / 70.5, 23 71.0 / 72.1; 1000 + 3000: 22 58.2 / 57.9).
 inline bool pick_one_round(const SplitCosts& c, int batch, int n_kv_heads, int cap_retain, int n_approx, int least_ret, int& s_ret, int& s_apx) {
   const int64_t steps_r = ((int64_t)cap_retain + c.step_rows - 1) / c.step_rows, steps_a = ((int64_t)n_approx + c.step_rows - 1) / c.step_rows;
   if (steps_r == 0 || steps_a == 0 || steps_r > 3 * steps_a) return false;
-  const int64_t pairs = (int64_t)batch * n_kv_heads;
-  const int most = (int)std::max<int64_t>(2, std::min<int64_t>(kMaxSplits, 256 * c.per_cu / pairs));
+  const int64_t pairs = (int64_t)batch * n_kv_heads, at_once = 256 * c.per_cu;
+  if (2 * pairs > at_once && (4 * pairs < 3 * at_once || 2 * steps_r > 3 * steps_a)) return false;
+  const int most = (int)std::max<int64_t>(2, std::min<int64_t>(kMaxSplits, at_once / pairs));
   const double bytes = (double)pairs * (0.0121 * (double)steps_r + 0.0061 * (double)steps_a);      // us at 5.4 TB/s
   double best = -1.0;
   for (int r = std::max(1, least_ret); r < most && r <= steps_r; ++r) {
@@ -139,6 +149,11 @@ inline bool pick_one_round(const SplitCosts& c, int batch, int n_kv_heads, int c
     const double longest = (double)std::max(long_r, long_a);
     const double t = std::max(bytes, (pairs * (r + a) > 256 ? 2.8 : 1.4) * longest) + 0.15 * longest + 0.05 * (double)(r + a);
     if (best < 0.0 || t < best) { best = t; s_ret = r; s_apx = (int)a; }
+  }
+  if (best >= 0.0 && 2 * pairs <= at_once && s_ret + s_apx == 2 && 2 * steps_a > 3 * steps_r) {
+    int r = 1, a = 1;
+    if (8 * pairs >= 3 * at_once) pick_splits(c, batch, n_kv_heads, cap_retain, n_approx, r, a);
+    if (r + a == 2) return false;
   }
   return best >= 0.0;
 }

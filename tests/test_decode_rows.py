@@ -114,14 +114,15 @@ ONE_ROUND = r"""
 int main() {
   const int rows[] = {0, 1, 20, 128, 129, 1000, 5000, 40000, 1000000, 2147483647};
   for (int per_cu = 1; per_cu <= 4; ++per_cu)
-    for (int pairs : {1, 2, 3, 8, 64, 100, 300, 5000})
+    for (int pairs : {1, 2, 3, 8, 64, 100, 129, 257, 300, 383, 384, 5000})
       for (int least : {1, 2, 70})
         for (int cap : rows)
           for (int n : rows) {
             int r = -1, a = -1;
             const vec::SplitCosts costs = vec::split_costs(true, 128, 4, vec::ApproxRows::kPlain, per_cu);
             if (!vec::pick_one_round(costs, pairs, 1, cap, n, least, r, a)) continue;
-            const long long round = 256 * per_cu > 2 * pairs ? 256 * per_cu : 2 * pairs;
+            // one round, or one piece each and at least half a round more
+            const long long at_once = 256 * per_cu, round = 4 * pairs >= 3 * at_once && r + a == 2 ? 2 * pairs : at_once;
             if (cap == 0 || n == 0 || r < least || r < 1 || a < 1 || r + a > vec::kMaxSplits || (long long)pairs * (r + a) > round ||
                 r > (cap + 127ll) / 128 || a > (n + 127ll) / 128) {
               printf("%d per CU, %d pairs, %d and %d rows: %d + %d\n", per_cu, pairs, cap, n, r, a);
@@ -276,3 +277,21 @@ def test_every_cu_of_a_plan_keeps_a_workgroup_for_approximated_rows(tmp_path):
         '    const int most = vec::plan_most_retained(per_cu, wgs);\n'
         '    if (wgs != 256 * per_cu || most != 256 * (per_cu - 1) || vec::plan_retained(wgs, most, 100000, 100, 1.f / 100100.f) != most) return 1;\n'
         '    if (vec::plan_retained(wgs, most, 1000, 3000, 1.f / 4000.f) != wgs / 4 || vec::plan_retained(wgs, most, 1000, 0, 1.f / 1000.f) != wgs) return 1;\n  }\n  return 0;\n}\n')
+
+
+# Plain rows of 128 dims whose cuts were measured both ways, more than 2 % apart: sequences (eight heads, two workgroups per CU), capacity,
+# approximated rows; the cut in one round's order, or nothing where the estimate's was the faster
+ONE_ROUND_MEASURED = [
+    ((33, 2256, 2000), ""), ((40, 2256, 2000), ""), ((36, 956, 700), ""), ((36, 1456, 2400), ""), ((36, 2656, 1200), ""), ((48, 2656, 1200), ""), ((64, 2656, 1200), ""),
+    ((48, 2256, 2000), "1+1"), ((96, 2256, 2000), "1+1"), ((52, 956, 700), "1+1"), ((128, 956, 700), "1+1"), ((48, 1456, 2400), "1+1"), ((80, 1456, 2400), "1+1"),
+    ((22, 1856, 3500), ""), ((28, 1856, 3500), ""), ((31, 1856, 3500), ""), ((28, 1256, 3000), ""), ((24, 1256, 3000), "1+1"), ((21, 1856, 3500), "1+2"), ((17, 1256, 3000), "1+2"),
+    ((24, 2256, 2000), "1+1"), ((32, 2256, 2000), "1+1"), ((17, 956, 700), "2+1"), ((32, 956, 700), "1+1"), ((26, 2656, 1200), "1+1"), ((17, 2656, 1200), "2+1"),
+    ((16, 3532, 3276), "2+2"), ((30, 3256, 1000), ""),
+]
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
+def test_one_round_where_it_was_measured_faster(tmp_path):
+    lines = "".join("  { int r = 0, a = 0; char s[32] = \"\"; if (vec::pick_one_round(vec::split_costs(true, 128, 4, vec::ApproxRows::kPlain, 2), %d, 8, %d, %d, 1, r, a)) sprintf(s, \"%%d+%%d\", r, a);"
+                    " if (strcmp(s, \"%s\")) { printf(\"%s: %%s\\n\", s); bad = 1; } }\n" % (shape + (cut, shape)) for shape, cut in ONE_ROUND_MEASURED)
+    run(tmp_path, '#include <cstdio>\n#include <cstring>\n#include "decode_rows.hpp"\nint main() {\n  int bad = 0;\n' + lines + "  return bad;\n}\n")
