@@ -1406,7 +1406,6 @@ template <auto Kernel> int workgroups_per_cu(int lds) {
 // Applying: the kernel for plain rows where a small launch applies W (APPLY), or Kernel
 template <auto Kernel, typename T, int D, int G, auto Applying = Kernel>
 int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t stream, const RopeParams* rope) {
-  if (lds) VEC_HIP(set_max_lds(reinterpret_cast<const void*>(Kernel), lds));
   const ApproxRows kind = rope ? ApproxRows::kTurned : p.literal ? ApproxRows::kRebuilt : ApproxRows::kPlain;
   const SplitCosts costs = split_costs(Elem<T>::kDtype == VECTOR_BF16, D, G, kind, workgroups_per_cu<Kernel>(lds));
   static_assert(Elem<T>::kDtype == VECTOR_BF16 ? DW * kTileRows == 128 : DW * kWave * 4 * kUnroll == 4096, "the rows of a step that split_costs states");
@@ -1432,6 +1431,7 @@ int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t st
       return VECTOR_OK;
     }
   }
+  VEC_HIP(set_max_lds(reinterpret_cast<const void*>(Kernel), lds));
   VEC_LAUNCH(K_DECODE_SPLIT, Kernel, grid, dim3(DT_), lds, stream, p, rope ? *rope : RopeParams{});
   return VECTOR_OK;
 }
