@@ -69,6 +69,11 @@ constexpr SplitCosts split_costs(bool bf16, int head_dim, int group, ApproxRows 
     c.slot = 0.12;
   } else {
     const int elements = (group * head_dim + 255) / 256;         // of a thread of the merge, four at a time
+    // Three query heads at 128 dims: four fit by their registers (121), but what four of them take is no less than what three do.  Cut for three /
+    // four, eight heads: 16 sequences of 1000 + 1000 rows 46.6 / 52.5 us a step, 24 65.2 / 70.6, 8 of 800 + 200 21.9 / 27.6, 24 of 200 + 800 33.5 / 38.9;
+    // 43 shapes in the mean 4 % less, at worst (14 of 200 + 800) 30.0 / 27.1.  With more heads the cuts for as many as fit are the better ones:
+    // five, 24 of 400 + 400 52.6 (two) / 43.1 (three), ten, 16 of 1000 + 1000 288 (one) / 164 (two).
+    if (head_dim == 128 && group == 3) c.per_cu = per_cu = std::min(per_cu, 3);
     c.step_rows = 4096 / head_dim;
     c.start = 7.5;
     c.alone_ret = 0.9 + 0.13 * group; c.full_ret = (2.75 + 0.11 * group) * per_cu;

@@ -97,6 +97,11 @@ MEASURED = [
     ((1, 128, 8, 2, 2, 4, 8, 1894, 1638), "5+7 5+8 6+7 6+8 4+4"),
     ((1, 128, 4, 2, 2, 8, 8, 665, 409), "2+2 2+4 3+4 1+2"),
     ((1, 64, 4, 2, 2, 8, 8, 665, 409), "2+2 4+4 3+4 2+4 3+3"),
+    # four workgroups fit a CU here, and the cuts for four were measured 8 to 25 % slower than these
+    ((0, 128, 3, 0, 4, 16, 8, 1256, 1000), "3+3"), ((0, 128, 3, 0, 4, 24, 8, 1256, 1000), "2+2"), ((0, 128, 3, 0, 4, 8, 8, 1056, 200), "9+3"),
+    ((0, 128, 3, 0, 4, 16, 8, 656, 400), "3+3"), ((0, 128, 3, 0, 4, 24, 8, 456, 800), "1+3"),
+    # two, three and two, with registers that once let one, two and one fit
+    ((0, 128, 10, 0, 2, 16, 8, 1256, 1000), "2+2"), ((0, 128, 5, 0, 3, 24, 8, 656, 400), "2+2"), ((0, 128, 10, 0, 2, 6, 8, 656, 400), "5+5"),
 ]
 
 
