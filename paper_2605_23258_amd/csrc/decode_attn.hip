@@ -3,9 +3,9 @@
 //
 // One softmax runs over the live retained rows and the approximated rows together.
 // Because the rebuilt value is linear in the key, sum_t p_t (k_t W) = (sum_t p_t k_t) W:
-// the kernel accumulates z = sum p_t k_t over the approximated rows and applies W once
-// per (sequence, KV head) in the combine step, so every cache row is read exactly once
-// and no value row is ever materialised.
+// the kernels accumulate z = sum p_t k_t over the approximated rows and apply W to that, once
+// per (sequence, KV head) in the combine step or, in small launches, once per piece of approximated
+// rows (APPLY), so every cache row is read exactly once and no value row is ever materialised.
 //
 // The path is bound by HBM (about 5 flop per byte): a row of the cache is read by
 // row_bytes/16 adjacent lanes, 16 bytes each, so every load instruction of a wave covers
@@ -17,7 +17,8 @@
 //                           weights times rows) on the matrix cores; see the comment above
 //                           the kernel.  Variants: ROPE (approximated rows are un-rotated
 //                           before they stand in for values), LITERAL (v_hat = k W rebuilt per
-//                           row instead of the reassociated sum).
+//                           row instead of the reassociated sum), PAGED, PLANNED (sequences of different
+//                           lengths cut on the device), APPLY (pieces of approximated rows apply W).
 //   decode_split_kernel   : fp32 caches: the same split with vector-ALU dot products (partial
 //                           dot product per lane, rotate-add across the lanes of a row,
 //                           online softmax per lane group).
@@ -58,6 +59,7 @@ struct DecodeParams {
   int64_t w_sh;           // element stride between per-head W
   float c2;               // scale * log2(e)
   int literal;            // approximated rows: rebuild v_hat = k W per row instead of (sum p k) W
+  int only_values;        // the partials of approximated rows are values already: W is not the merge's
   int out_f32;            // store the result as fp32 whatever the cache dtype
 };
 
@@ -1031,9 +1033,10 @@ template <typename T, int D, int G> struct CombineLds {
 // (its 24 bits, eight at a time, cut and not rounded: above bf16's largest number a rounded first part would be infinite, and
 // the second minus infinity; of an infinite z the first part is all), eight query rows by three parts on the M side, W's
 // columns by the transposing LDS read.  fp32: on the vector unit, a thread with 16 bytes of some rows of W.
-// One sequence of 8192 tokens, 8 KV heads, 17 splits: from the launch's start 0.9 us to the loads, 0.5 to the weights, 1.0 to the
+// One sequence of 8192 tokens, 8 KV heads, 17 splits, W applied here (that launch's pieces apply it themselves now, which ends the chain
+// at the sums): from the launch's start 0.9 us to the loads, 0.5 to the weights, 1.0 to the
 // sums (W arrives), 0.3, and 0.8 for z W; with every thread looping over all splits' references the second and third took 2.2
-// (a step 11.7 us, now 11.2).  In the split launch's last workgroup of a (sequence, KV head) instead of a launch of its
+// (a step 11.7 us, then 11.2).  In the split launch's last workgroup of a (sequence, KV head) instead of a launch of its
 // own it is no faster: the acknowledgement of the written splits and the count of them take 1 us, as a launch does, and keep every
 // workgroup on its CU that much longer (11.6 / 12.1, and with 16 sequences of 32768 tokens 70.6 / 72.8).
 template <typename T, int D, int G, bool PLANNED = false>
@@ -1054,10 +1057,10 @@ __global__ __launch_bounds__(DT_) void decode_combine_kernel(DecodeParams p) {
   const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const size_t bh = (size_t)b * p.Hkv + h;
   const MergeSplits cut = merge_splits<PLANNED>(p, bh);
-  const int n_splits = cut.ret + cut.apx, n_ret = p.literal ? n_splits : cut.ret;      // literal partials are values already
+  const int n_splits = cut.ret + cut.apx, n_ret = p.only_values ? n_splits : cut.ret;
   const float* part = p.part + cut.first * PSZ;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5, l31 = lane & 31;
-  const bool use_w = p.n_approx > 0 && !p.literal;
+  const bool use_w = p.n_approx > 0 && !p.only_values;
 
   // the step's own token is now a row of the cache (the split launch has finished): one thread per
   // sequence makes it live, unless the block was full
@@ -1427,7 +1430,7 @@ int launch_split(const vector_cache& c, DecodeParams& p, int lds, hipStream_t st
       constexpr int more_lds = MfmaDecodeTile<D>::kLdsBytes;
       VEC_HIP(set_max_lds(reinterpret_cast<const void*>(Applying), more_lds));
       VEC_LAUNCH(K_DECODE_SPLIT, Applying, grid, dim3(DT_), more_lds, stream, p, RopeParams{});
-      p.literal = 1;      // the partials are values
+      p.only_values = 1;
       return VECTOR_OK;
     }
   }
@@ -1530,6 +1533,7 @@ int launch_decode_attn(const vector_cache& c, const void* q, float scale, void* 
                        hipStream_t stream, const RopeParams* rope, const void* k_new, const void* v_new) {
   DecodeParams p;
   p.literal = (flags & VECTOR_DECODE_LITERAL) ? 1 : 0;
+  p.only_values = p.literal;
   p.out_f32 = (flags & VECTOR_DECODE_OUT_F32) ? 1 : 0;
   if (p.literal && (rope || c.dtype != VECTOR_BF16)) return VECTOR_ERR_DTYPE;
   p.q = q; p.k_ret = c.k_ret; p.v_ret = c.v_ret; p.k_apx = c.k_apx; p.W = c.W; p.len_retain = c.len_retain;

@@ -42,7 +42,8 @@ enum class ApproxRows { kPlain, kTurned, kRebuilt };
 //   bf16, d = 64    1.27  1.07  1.03   half the bytes, three per CU; alone, a step is latency, which both kinds of rows have alike
 //   fp32            1.35  1.17  1.03   half the bytes, and the vector unit's time, which grows with the query heads; one to five per CU
 // Single shapes, us: fp32, d = 128, 32 sequences of 4096 tokens, four query heads 52 / 77 (four workgroups a CU where three fit) /
-// 54; 10 of 1798, eight query heads 42 / 52 / 28; bf16, d = 64, 16 of 17000 32 / 29 / 24; bf16, d = 128, 16 of 32768 70.9 / 70.4 / 70.4.
+// 54; 10 of 1798, eight query heads 42 / 52 / 28; bf16, d = 64, 16 of 17000 32 / 29 / 24; bf16, d = 128, 16 of 32768 70.9 / 70.4 / 70.4
+// (64.4 in one round, see pick_one_round).  The fp32 kernels of 128 dims have fewer registers since, and one more of them fits a CU.
 // Approximated rows that are turned back, or rebuilt one by one, cost more than their bytes.  Rebuilt, d = 128, with the costs of
 // plain ones: 16 sequences of 32768 tokens 228 us (4 + 2 splits), now 169 (2 + 2; 205 under the one rule); one of 8192 24.6 and 19.2.
 constexpr SplitCosts split_costs(bool bf16, int head_dim, int group, ApproxRows kind, int per_cu) {

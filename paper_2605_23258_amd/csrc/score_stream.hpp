@@ -833,8 +833,6 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
         *reinterpret_cast<uint4*>(w_lds + w_slot(wb_j0 + j, wb_d0 / 8)) = make_uint4(word(0), word(1), word(2), word(3));
       }
     }
-  }
-  if constexpr (kTurnW) {
     tile_barrier();
 #pragma unroll
     for (int c = 0; c < NC; ++c) wf[c] = *reinterpret_cast<const chunk_t*>(w_lds + w_slot(my_dim, 2 * c + half));
