@@ -187,11 +187,13 @@ constexpr bool plan_too_long(float longest, int batch, int n_kv_heads, int log_r
 //     quarters 43.9, 45.0, 46.2, 48.2, 50.0; by work alone 43.9, 45.0, 46.2, 47.2, 52.7; as many splits for every sequence 44.3, 47.8, 45.6, 46.9, 49.9.  (At 1 and below
 //     the work gives less than half.)  Rotated 44.4, 45.7, 44.5, 46.3, 46.5; 44.3, 45.7, 48.9, 49.5, 50.4; 44.4, 45.7, 49.0, 49.4, 50.6; 50.2, 49.5, 49.7, 47.7, 49.1.
 //   64 dims, three per CU, 40 of 3200 rows at 2, 3.5, 6, 30: half 37.3, 37.8, 39.5, 41.4; two thirds 35.9, 36.3, 38.2, 39.7; three quarters 35.9, 38.8, 41.2, 44.2; as many splits
-//     34.1, 36.8, 38.7, 40.2.  64 of 1700: 31.7, 34.8, 35.6, 37.9; 31.1, 32.3, 33.2, 35.2; 31.1, 34.4, 35.5, 38.5; 29.7, 31.9, 33.1, 35.8.
+//     34.1, 36.8, 38.7, 40.2.  64 of 1700: 31.7, 34.8, 35.6, 37.9; 31.1, 32.3, 33.2, 35.2; 31.1, 34.4, 35.5, 38.5; 29.7, 31.9, 33.1, 35.8.  A few more than half are no
+//     gain (24 of 1600 at 1 and the step's token 23.5 / 23.9; at 1.3 25.2 / 25.5, at 1.5 35.1 / 35.2): from three fifths of the work on.
 constexpr int plan_most_retained(int per_cu, int wgs) { return per_cu > 2 ? wgs / per_cu * (per_cu - 1) : wgs / 2; }
 // Workgroups of the retained line: by the lines' work.  inverse: of total_r + total_a * apx
 constexpr int plan_retained(int wgs, int most, int total_r, int total_a, float inverse) {
-  const int by_work = (int)((float)wgs * (float)total_r * inverse + 0.5f), wgs_r = total_a > 0 ? (by_work < most ? by_work : most) : wgs;
+  const int by_work = (int)((float)wgs * (float)total_r * inverse + 0.5f), limit = 5 * by_work > 3 * wgs ? most : wgs / 2;
+  const int wgs_r = total_a > 0 ? (by_work < limit ? by_work : limit) : wgs;
   return total_r > 0 && wgs_r < 1 ? 1 : wgs_r;
 }
 // A workgroup's share of its line: an even one, rounded up, and by as much as its float may be below it; no more than half of kMaxSplits for
@@ -225,13 +227,13 @@ constexpr int planned_rows(int of_call, int of_sequence) { return of_call > 0 &&
 //   128 dims, from three steps per workgroup: 6 sequences of 4000 rows 20.5 / 19.9 (rotated 26.1 / 23.5), 16 of 3200 28.1 / 26.9 (36.6 / 32.3), 12 of 8000 48.0 / 45.0
 //     (59.2 / 49.9); in the mean of 60 shapes of three to four steps 4 % less, at worst 5 % more (16 query heads: 9 %).  Below: 2 of 1700 11.1 / 13.1 (13.1 / 14.9), two heads,
 //     4 of 8000 13.9 / 16.5 (18.1 / 20.5), 6 of 1700 9.9 / 12.5; 3 of 3200 13.8 / 15.3 (but rotated 19.0 / 17.2).
-//   64 dims, plain, from eight: 12 of 8000 30.1 / 27.7, 32 of 4000 35.6 / 33.0, 64 of 3200 51.5 / 48.4; below, 16 of 1700 13.9 / 15.5, 16 of 3200 18.1 / 19.3, two heads,
-//     64 of 1700 14.1 / 15.1.  Rotated, whose pieces of approximated rows are cut well by the estimate, never: 64 of 3200 49.5 / 57.4, 24 of 3200 26.9 / 28.4, 16 of 8000
+//   64 dims, plain, from six: 10 of 8000 26.5 / 25.5, 12 30.1 / 27.7, 28 of 3200 29.6 / 27.6, 64 51.5 / 48.4, but 24 24.3 / 25.0; below, 8 of 8000 22.9 / 23.1, 32 of 1700
+//     20.9 / 21.4, 16 13.9 / 15.5, 16 of 3200 18.1 / 19.3, two heads, 64 of 1700 14.1 / 15.1.  Rotated, whose pieces of approximated rows are cut well by the estimate, never: 64 of 3200 49.5 / 57.4, 24 of 3200 26.9 / 28.4, 16 of 8000
 //     35.5 / 36.1, and at best (12 of 8000) 31.7 / 30.5.
 constexpr bool worth_a_plan(int head_dim, bool turned, int per_cu, int batch, int n_kv_heads, int cap_retain, int n_approx) {
   if (batch < 2 || batch > kMaxPlanned || (head_dim == 64 && turned)) return false;
   const int64_t steps = ((int64_t)cap_retain + 127) / 128 + ((int64_t)n_approx + 127) / 128;
-  return steps * batch * n_kv_heads >= (head_dim == 64 ? 8 : 3) * 256 * (int64_t)per_cu;
+  return steps * batch * n_kv_heads >= (head_dim == 64 ? 6 : 3) * 256 * (int64_t)per_cu;
 }
 
 }  // namespace vec

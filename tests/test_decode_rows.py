@@ -158,7 +158,7 @@ PLANNED = [
     (128, 0, 2, 24, 8, 2999, 457, 1), (128, 1, 2, 24, 8, 2999, 457, 1), (128, 0, 2, 24, 8, 3456, 0, 1),
     (64, 0, 3, 3, 8, 4256, 4000, 0), (64, 0, 3, 16, 8, 1106, 850, 0), (64, 0, 3, 16, 8, 1856, 1600, 0), (64, 0, 3, 64, 2, 1106, 850, 0),
     (64, 1, 3, 64, 8, 1856, 1600, 0), (64, 1, 3, 24, 8, 1856, 1600, 0), (64, 1, 3, 6, 2, 4256, 4000, 0),
-    (64, 0, 3, 12, 8, 4256, 4000, 1), (64, 0, 3, 32, 8, 2256, 2000, 1), (64, 0, 3, 64, 8, 1856, 1600, 1),
+    (64, 0, 3, 10, 8, 4256, 4000, 1), (64, 0, 3, 12, 8, 4256, 4000, 1), (64, 0, 3, 28, 8, 1856, 1600, 1), (64, 0, 3, 32, 8, 1106, 850, 0), (64, 0, 3, 32, 8, 2256, 2000, 1), (64, 0, 3, 64, 8, 1856, 1600, 1),
     # one sequence, and more than a wave has lanes
     (128, 0, 2, 1, 8, 100000, 100000, 0), (128, 0, 2, 65, 8, 4000, 4000, 0),
 ]
@@ -277,10 +277,12 @@ def test_plans_share_every_row_out_once(tmp_path):
 @pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the ROCm toolchain")
 def test_every_cu_of_a_plan_keeps_a_workgroup_for_approximated_rows(tmp_path):
     """Of the workgroups of a CU, 256 apart, all but the last are for retained rows where these are nearly all of the work (64 dims, three per
-    CU: half of all, as with two, took up to 8 % longer); with less of them the work says how many."""
+    CU: half of all, as with two, took up to 8 % longer); with less of them the work says how many, but no
+    more than half up to three fifths of the work."""
     run(tmp_path, '#include "decode_rows.hpp"\nint main() {\n  for (int per_cu = 2; per_cu <= 4; ++per_cu) {\n    const int wgs = vec::plan_workgroups(per_cu, 200);\n'
         '    const int most = vec::plan_most_retained(per_cu, wgs);\n'
         '    if (wgs != 256 * per_cu || most != 256 * (per_cu - 1) || vec::plan_retained(wgs, most, 100000, 100, 1.f / 100100.f) != most) return 1;\n'
+        '    if (vec::plan_retained(wgs, most, 1010, 1000, 1.f / 2010.f) != wgs / 2) return 1;\n'
         '    if (vec::plan_retained(wgs, most, 1000, 3000, 1.f / 4000.f) != wgs / 4 || vec::plan_retained(wgs, most, 1000, 0, 1.f / 1000.f) != wgs) return 1;\n  }\n  return 0;\n}\n')
 
 
