@@ -615,13 +615,20 @@ template <typename T, int D, int NRB, bool MASS, bool RES, bool ROPE> struct Pas
   // with halves, 88.2 without; with log-sum-exp, which has no sums to take, 71.2 and 67.1; 2546 tokens 48.9 and 47.0).
   static constexpr bool kThrough = MASS && !(ROPE && sizeof(T) == 4 && D == 128);
   static constexpr bool kHalves = kThrough && WW::kPairs;
-  static constexpr int kQuery = kStageBytes, kQueryBytes = kThrough ? WW::kUnitSlots * QueryUnit<T, D>::kBytes : 0;
+  static constexpr int kQueryBytes = kThrough ? WW::kUnitSlots * QueryUnit<T, D>::kBytes : 0, kSharesBytes = kHalves ? 2048 : 0;
+  // Where they fit the place of the column sums, which are not written before a tile's barrier, the rows go there: no barrier of
+  // their own behind them, and a wave asks for its tiles as soon as its own loads are there, not when the slowest wave's are (bf16 rows of 64 dims, 8 heads,
+  // a compression pass, us, in the place of tiles / here: 32768 tokens 56.4 / 55.6, five unequal prompts of up to 8000 45.4 / 44.9, 700 20.0 / 19.9; with log-sum-exp, two
+  // unequal prompts of up to 7484, two query heads, 25.8 / 25.4 - and 25.4 with every wave's rows straight into its registers).
+  static constexpr bool kRowsApart = kThrough && kEnd - kMassSums >= kQueryBytes + kSharesBytes;
+  static constexpr int kQuery = kRowsApart ? kMassSums : kStageBytes;
   static constexpr int kW = ROPE ? kTurned : (kStages - 1) * kStageBytes;      // W on its way into the registers
   static constexpr int kUsed = kBiasInTurned ? kEnd : kEnd + kBiasBytes;
-  // waves that share a unit: their shares of its rows' sums, [2][4][32] float2, between two barriers
-  static constexpr int kShares = kMassSums > kQuery + kQueryBytes ? kMassSums : kQuery + kQueryBytes, kSharesEnd = kShares + (kHalves ? 2048 : 0);
+  // waves that share a unit: their shares of its rows' sums, [2][4][32] float2, behind the query rows, for as long as these
+  static constexpr int kShares = kMassSums > kQuery + kQueryBytes ? kMassSums : kQuery + kQueryBytes, kSharesEnd = kShares + kSharesBytes;
   static constexpr int kTotal = kSharesEnd > kUsed ? kSharesEnd : kUsed;
   static_assert(kTotal <= (int)kMaxLdsBytes, "LDS");
+  static_assert(!kRowsApart || (kQuery >= kTurns && kSharesEnd <= kEnd && (kBias >= kEnd || kBias + kBiasBytes <= kMassSums)), "of the sums' place only");
 };
 
 // x of this lane + x of the lane 32 further
@@ -786,6 +793,16 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
   // rotated keys (- - 13); elsewhere none.
   if (MASS) {
     if constexpr (L::kThrough) wait_loads<0>();
+    if constexpr (L::kRowsApart) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) asm volatile("" : "+v"(bias_u[u]));
+      static_assert(!L::kRowsApart || kTurnW, "W's loads are waited for here as well");
+#pragma unroll
+      for (int u = 0; u < 8; ++u) asm volatile("" : "+v"(wraw[u].x), "+v"(wraw[u].y), "+v"(wraw[u].z), "+v"(wraw[u].w));
+#pragma unroll
+      for (int s = 1; s < L::kFirstTiles; ++s)
+        if (to_fetch > 0) fetch();
+    }
     if constexpr (L::kHalves) tile_barrier();    // everyone's shares and query rows are there
     if constexpr (L::kThrough) {
 #pragma unroll
@@ -805,21 +822,24 @@ __global__ __launch_bounds__(kStreamThreads) void mass_residual_kernel(PassArgs<
         if (qrow[u] >= p.R) qf[u][c] = make_uint4(0, 0, 0, 0);
         asm volatile("" : "+v"(qf[u][c].x), "+v"(qf[u][c].y), "+v"(qf[u][c].z), "+v"(qf[u][c].w));
       }
-    if constexpr (L::kThrough) tile_barrier();   // everyone's query rows have left LDS
+    if constexpr (L::kThrough && !L::kRowsApart) tile_barrier();      // everyone's query rows have left LDS
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (half == 0 && ww.has_rows) bias_lds[(ww.unit + 8 * u) * 32 + l31] = qrow[u] < p.R ? bias_u[u] : INFINITY;
   }
-  if constexpr (kTurnW) {
+  if constexpr (L::kRowsApart) {
+  } else if constexpr (kTurnW) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) asm volatile("" : "+v"(wraw[u].x), "+v"(wraw[u].y), "+v"(wraw[u].z), "+v"(wraw[u].w));
   } else if constexpr (RES) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(wf[c].x), "+v"(wf[c].y), "+v"(wf[c].z), "+v"(wf[c].w));
   }
+  if constexpr (!L::kRowsApart) {
 #pragma unroll
-  for (int s = 1; s < L::kFirstTiles; ++s)
-    if (to_fetch > 0) fetch();
+    for (int s = 1; s < L::kFirstTiles; ++s)
+      if (to_fetch > 0) fetch();
+  }
   if constexpr (kTurnW) {
     if ((int)threadIdx.x < D * D / 64) {
 #pragma unroll
